@@ -2,6 +2,7 @@
 // matrix cores, deterministic per-cluster means, and the node -> page layout (Sec. 4.1-4.2,
 // Alg. 2 of the paper restricted to two levels and iterated as Lloyd rounds).
 #include <algorithm>
+#include <type_traits>
 
 #include "ice_internal.h"
 
@@ -268,7 +269,7 @@ __host__ __device__ constexpr int assign_lds_bytes(bool aug) {
     return 2 * 256 * 256 + (aug ? 2 * 256 * 32 : 0) + 2 * 256 * 8;
 }
 
-template <int CT, int CW, bool AUG>
+template <int CT, int CW, bool AUG, bool FULL>
 __global__ __launch_bounds__(512) void assign_kernel(const bf16_t *__restrict__ K, const bf16_t *__restrict__ cent,
                                                       const float *__restrict__ cnorm, int n, int keys_per_wg, int zsplit,
                                                       int Cpad, int cur, Dev d) {  // (scalars first: preloaded at wave start)
@@ -283,8 +284,15 @@ __global__ __launch_bounds__(512) void assign_kernel(const bf16_t *__restrict__ 
 
     const int u = blockIdx.z, tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63, col = lane & 31, half = lane >> 5;
-    const int cw = wave % CW, kw = wave / CW;
-    const int cbase = (blockIdx.y * CW + cw) * CT * 32;
+    // Wave (cw, kw) holds CT centroid tiles of the slice: neighbours when every slice is full (FULL), else cw
+    // and cw + CW.  Waves w and w + 4 share a SIMD: tiles missing at the slice's end are spread over the
+    // SIMDs that way (with all eight waves on the centroids tile t belongs to SIMD t mod 4; with fewer
+    // the upper four waves take the columns in a shifted order), and a wave skips what it does not have
+    // (ctv), so a slice costs what its fullest SIMD holds: 12 tiles run in 3/4 of the time of 16.
+    constexpr int CS = FULL ? 1 : CW;  // distance between a wave's tiles
+    const int kw = wave / CW, cw = FULL || CW == 8 ? wave % CW : (wave + (wave >> 2) * (CW / 2)) % CW;
+    const int wt0 = FULL ? cw * CT : cw, tile0 = blockIdx.y * CW * CT + wt0;
+    const int ctv = __builtin_amdgcn_readfirstlane(tile0 * 32 >= Cpad ? 0 : CT == 2 && (tile0 + CS) * 32 < Cpad ? 2 : 1);
     const int k0 = blockIdx.x * keys_per_wg;
     const int kend = min(n, k0 + keys_per_wg);
     const int ntiles = (kend - k0 + kAssignTile - 1) / kAssignTile;
@@ -311,7 +319,7 @@ __global__ __launch_bounds__(512) void assign_kernel(const bf16_t *__restrict__ 
     f32x16 seed[CT];
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {
-        const int row0 = cbase + ct * 32;
+        const int row0 = (tile0 + ct * CS) * 32;
         if (row0 < Cpad) {
             const float *wn = cnorm + (size_t)u * Cpad + row0;
 #pragma unroll
@@ -378,7 +386,7 @@ __global__ __launch_bounds__(512) void assign_kernel(const bf16_t *__restrict__ 
     bf16x8 A[CT][KS];
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {
-        const int r = (cw * CT + ct) * 32 + col;
+        const int r = (wt0 + ct * CS) * 32 + col;
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) A[ct][ks] = __builtin_bit_cast(bf16x8, *(const uint4 *)(keys + slot(r, 2 * ks + half)));
         if constexpr (AUG) A[ct][8] = __builtin_bit_cast(bf16x8, kext[r * 2 + half]);
@@ -399,7 +407,7 @@ __global__ __launch_bounds__(512) void assign_kernel(const bf16_t *__restrict__ 
     ICE_BSTAMP(1);
 
     constexpr int NSUB = 8 / KW;  // 32-key sub-tiles of this wave per tile
-    const uint32_t inv_cid0 = 0xFFFFFFFFu - (uint32_t)(cbase + 4 * half);  // low word for local centroid id 0
+    const uint32_t inv_cid0 = 0xFFFFFFFFu - (uint32_t)(tile0 * 32 + 4 * half);  // low word for local centroid id 0
     for (int t = 0; t < ntiles; ++t) {
         const int buf = t & 1;
         u64 *bestt = best + buf * kAssignTile;
@@ -412,7 +420,6 @@ __global__ __launch_bounds__(512) void assign_kernel(const bf16_t *__restrict__ 
         // run the 8-MFMA chain of slot j+1 into one accumulator set, the vector unit
         // reduces slot j's 16 scores per lane from the other set (argmax16).  The key operand of a
         // sub-tile is read from LDS one sub-tile ahead.
-        constexpr int NSLOT = NSUB * CT;
         bf16x8 B[2][KS];
         auto load_b = [&](int i, bf16x8 (&dst)[KS]) {
             const char *sub = keys + buf * (kAssignTile * 256) + (kw + i * KW) * 32 * 256;  // (32 rows: r & 15 is col & 15)
@@ -420,43 +427,48 @@ __global__ __launch_bounds__(512) void assign_kernel(const bf16_t *__restrict__ 
             for (int ks = 0; ks < 8; ++ks) dst[ks] = __builtin_bit_cast(bf16x8, *(const uint4 *)(sub + frag[ks]));
             if constexpr (AUG) dst[8] = __builtin_bit_cast(bf16x8, kext[(buf * kAssignTile + (kw + i * KW) * 32 + col) * 2 + half]);
         };
-        f32x16 acc[2];
-        auto chain = [&](int j, f32x16 &dst) {
-            const int i = j / CT, ct = j % CT;
-            dst = seed[ct];
+        auto compute = [&](auto tiles_held) {
+            constexpr int CTV = decltype(tiles_held)::value, NSLOT = NSUB * CTV;
+            f32x16 acc[2];
+            auto chain = [&](int j, f32x16 &dst) {
+                const int i = j / CTV, ct = j % CTV;
+                dst = seed[ct];
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-                dst = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[ct][ks], B[i & 1][ks], dst, 0, 0, 0);
+                for (int ks = 0; ks < KS; ++ks)
+                    dst = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[ct][ks], B[i & 1][ks], dst, 0, 0, 0);
+            };
+            load_b(0, B[0]);
+            if (CTV == 1 && NSUB > 1) load_b(1, B[1]);
+            chain(0, acc[0]);
+            float sv = 0.f;
+            uint32_t sidx = 0;
+#pragma unroll
+            for (int j = 0; j < NSLOT; ++j) {
+                const int i = j / CTV, ct = j % CTV;
+                // LDS reads for the sub-tile whose first chain is issued in the NEXT iteration
+                if ((j + 2) % CTV == 0 && (j + 2) / CTV < NSUB && (j + 2) / CTV >= 1 && !(CTV == 1 && j + 2 == 1))
+                    load_b((j + 2) / CTV, B[((j + 2) / CTV) & 1]);
+                if (j + 1 < NSLOT) chain(j + 1, acc[(j + 1) & 1]);
+                // element v of this lane has local centroid id ct*32*CS + 8*(v/4) + v%4 (+ 4*half), ascending in v
+                float m;
+                uint32_t li;
+                argmax16(acc[j & 1], m, li);
+                if (ct == 0) {
+                    sv = m;
+                    sidx = li;
+                } else {
+                    const bool gt = m > sv;
+                    sv = gt ? m : sv;
+                    sidx = gt ? li + 32u * CS * ct : sidx;
+                }
+                if (ct == CTV - 1) {
+                    const u64 pk = ((u64)f32_ordered(sv + 0.0f) << 32) | (u64)(inv_cid0 - sidx);
+                    atomicMax(&bestt[(kw + i * KW) * 32 + col], pk);
+                }
+            }
         };
-        load_b(0, B[0]);
-        if (CT == 1 && NSUB > 1) load_b(1, B[1]);
-        chain(0, acc[0]);
-        float sv = 0.f;
-        uint32_t sidx = 0;
-#pragma unroll
-        for (int j = 0; j < NSLOT; ++j) {
-            const int i = j / CT, ct = j % CT;
-            // LDS reads for the sub-tile whose first chain is issued in the NEXT iteration
-            if ((j + 2) % CT == 0 && (j + 2) / CT < NSUB && (j + 2) / CT >= 1 && !(CT == 1 && j + 2 == 1))
-                load_b((j + 2) / CT, B[((j + 2) / CT) & 1]);
-            if (j + 1 < NSLOT) chain(j + 1, acc[(j + 1) & 1]);
-            // element v of this lane has local centroid id ct*32 + 8*(v/4) + v%4 (+ 4*half), ascending in v
-            float m;
-            uint32_t li;
-            argmax16(acc[j & 1], m, li);
-            if (ct == 0) {
-                sv = m;
-                sidx = li;
-            } else {
-                const bool gt = m > sv;
-                sv = gt ? m : sv;
-                sidx = gt ? li + 32u * ct : sidx;
-            }
-            if (ct == CT - 1) {
-                const u64 pk = ((u64)f32_ordered(sv + 0.0f) << 32) | (u64)(inv_cid0 - sidx);
-                atomicMax(&bestt[(kw + i * KW) * 32 + col], pk);
-            }
-        }
+        if (FULL || ctv == CT) compute(std::integral_constant<int, CT>{});  // (wave-uniform)
+        else if (CT == 2 && ctv == 1) compute(std::integral_constant<int, 1>{});
         ICE_BSTAMP(2 + 2 * (t & 3));
         ICE_WSTAMP(t, 1);
         if (t + 1 < ntiles) {
@@ -488,22 +500,40 @@ void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, hipStream_t st
     while (CW < 8 && CW * CT < tiles) CW *= 2;
     const int cblock = CT * CW * 32;
     const int zsplit = (d.Cpad + cblock - 1) / cblock;
-    // One workgroup per CU when the work allows it (a workgroup fills a CU: 132-148 KB of LDS, 8 waves
-    // of 226-256 registers), each amortising its prologue over as many key tiles as possible.
-    int keys_per_wg = kAssignTile;
-    const int wg_target = 256;
-    while ((long long)((n + keys_per_wg - 1) / keys_per_wg) * zsplit * d.U > wg_target && keys_per_wg < n) keys_per_wg *= 2;
+    // A workgroup fills a CU (132-148 KB of LDS, 8 waves of 226-256 registers) and takes a run of key tiles
+    // of one unit, any number of them: the run for which the chip's rounds of 256 workgroups, each its
+    // tiles plus a prologue worth about one tile, come out shortest.  (Runs of a power of two tiles only:
+    // 16 units x 92 tiles, 12 of 16 centroid tiles, transformed, are 192 workgroups of 8 tiles and took
+    // 56 us, 256 of 6 with the tiles dealt over the SIMDs 43; a ten-round build of 8 units x 40001 keys
+    // with 625 clusters, 160 workgroups of 8 tiles against 256 of 10, 1314 us against 1031.)
+    const int ktiles = (n + kAssignTile - 1) / kAssignTile;
+    int run = 1;
+    long long best_cost = -1;
+    for (int g = 1; g <= ktiles && g <= 4096; ++g) {  // g workgroups per unit and slice
+        const int r = (ktiles + g - 1) / g;
+        const long long wgs = (long long)((ktiles + r - 1) / r) * zsplit * d.U;
+        const long long cost = (wgs + 255) / 256 * (r + 1);
+        if (best_cost < 0 || cost < best_cost) { best_cost = cost; run = r; }
+        if (wgs > 256 * 64) break;  // (more, shorter runs only repeat the prologue)
+    }
+    const int keys_per_wg = run * kAssignTile;
     dim3 grid((n + keys_per_wg - 1) / keys_per_wg, zsplit, d.U);
     const size_t lds = assign_lds_bytes(d.tk != 0);
     if (zsplit > 1) {
         const size_t tot = (size_t)d.U * d.max_tokens;
         hipLaunchKernelGGL(fill_u64_kernel, dim3(1024), dim3(256), 0, st, d.packed, tot, 0ull);
     }
+    const bool full = tiles % (CT * CW) == 0;
+#define ICE_ASSIGN_F(ct, cw, aug, full)                                                             \
+    do {                                                                                            \
+        allow_dynamic_lds((const void *)assign_kernel<ct, cw, aug, full>, lds);                     \
+        hipLaunchKernelGGL((assign_kernel<ct, cw, aug, full>), grid, dim3(512), lds, st, K, d.cent_bf16[cur], d.cnorm[cur], n, \
+                           keys_per_wg, zsplit, d.Cpad, cur, d);                                    \
+    } while (0)
 #define ICE_ASSIGN_A(ct, cw, aug)                                                                   \
     do {                                                                                            \
-        allow_dynamic_lds((const void *)assign_kernel<ct, cw, aug>, lds);                           \
-        hipLaunchKernelGGL((assign_kernel<ct, cw, aug>), grid, dim3(512), lds, st, K, d.cent_bf16[cur], d.cnorm[cur], n, keys_per_wg, \
-                           zsplit, d.Cpad, cur, d);                                                 \
+        if (full || ct * cw <= 2) ICE_ASSIGN_F(ct, cw, aug, true);  /* (one or two tiles are always full) */ \
+        else ICE_ASSIGN_F(ct, cw, aug, false);                                                      \
     } while (0)
 #define ICE_ASSIGN(ct, cw)                                                                          \
     do {                                                                                            \
@@ -517,6 +547,7 @@ void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, hipStream_t st
     else ICE_ASSIGN(2, 8);
 #undef ICE_ASSIGN
 #undef ICE_ASSIGN_A
+#undef ICE_ASSIGN_F
 }
 
 // ------------------------------------------------------------------------------------------------
