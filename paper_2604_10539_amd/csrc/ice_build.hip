@@ -494,12 +494,15 @@ __global__ __launch_bounds__(512) void assign_kernel(const bf16_t *__restrict__ 
     }
 }
 
-void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, hipStream_t st) {
+// Slices of at most 512 centroids (blockIdx.y) that meet through an atomic maximum in `packed`.
+int assign_slices(const Dev &d) { return (d.Cpad + 511) / 512; }
+
+// clear: with several slices the winners start from zero, here or (between Lloyd rounds) by the sort that read them
+void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, bool clear, hipStream_t st) {
     const int tiles = d.Cpad / 32;
     int CT = tiles == 1 ? 1 : 2, CW = 1;
     while (CW < 8 && CW * CT < tiles) CW *= 2;
-    const int cblock = CT * CW * 32;
-    const int zsplit = (d.Cpad + cblock - 1) / cblock;
+    const int zsplit = assign_slices(d);
     // A workgroup fills a CU (132-148 KB of LDS, 8 waves of 226-256 registers) and takes a run of key tiles
     // of one unit, any number of them: the run for which the chip's rounds of 256 workgroups, each its
     // tiles plus a prologue worth about one tile, come out shortest.  (Runs of a power of two tiles only:
@@ -519,7 +522,7 @@ void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, hipStream_t st
     const int keys_per_wg = run * kAssignTile;
     dim3 grid((n + keys_per_wg - 1) / keys_per_wg, zsplit, d.U);
     const size_t lds = assign_lds_bytes(d.tk != 0);
-    if (zsplit > 1) {
+    if (zsplit > 1 && clear) {
         const size_t tot = (size_t)d.U * d.max_tokens;
         hipLaunchKernelGGL(fill_u64_kernel, dim3(1024), dim3(256), 0, st, d.packed, tot, 0ull);
     }
@@ -551,237 +554,197 @@ void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, hipStream_t st
 }
 
 // ------------------------------------------------------------------------------------------------
-// Stable counting sort of the tokens by cluster (ascending position inside a cluster): the order
-// both the deterministic means and the page layout need.  A unit's tokens are cut into R ranges,
-// one workgroup of 16 waves each (R = 1 once there are 256 units; with fewer units more workgroups
-// per unit keep the chip busy), all counters in LDS.  With R > 1 a first kernel leaves every
-// range's member count per cluster in global memory (sort_totals_kernel).  The sorting kernel
-// cuts its range into W segments of `seg` tokens (a multiple of 64), wave w owns segment w:
-//   count  the wave unpacks its tokens' winners (and writes the assignment) and bumps
-//          cnt[w][cluster]; with REG (a segment has at most 32 groups of 64 tokens) the cluster
-//          ids stay in registers for the last phase;
-//   scan   per cluster an exclusive scan over the earlier ranges (their totals) and over the
-//          segments, then over the clusters (member counts and page counts of the whole unit),
-//          which turns cnt[w][c] into the first output slot of segment w's members of cluster c
-//          and yields the cluster and page offsets (written by the workgroup of range 0);
-//   rank   the wave walks its segment in token order, 64 tokens at a time: lanes with the same
-//          cluster find each other through a lane mask per cluster, the first of them moves the
-//          cluster's cursor past all of them.
-// A segment and cluster take 12 bytes of LDS (counter + lane mask): W = min(16, 12288 / Cpad)
-// segments fit in 144 KB.
-__global__ __launch_bounds__(1024) void sort_totals_kernel(Dev d, int n, int range_len) {
-    extern __shared__ int tot[];  // [Cpad]
-    const int r = blockIdx.x, u = blockIdx.y, tid = threadIdx.x;
-    const int Cpad = d.Cpad;
-    const uint32_t *pk = (const uint32_t *)(d.packed + (size_t)u * d.max_tokens);
-    const int rb = r * range_len, re = min(n, rb + range_len);
-    uint32_t v[4];  // (the first 4096 tokens are in flight while the counters are cleared)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = rb + j * 1024 + tid < re ? pk[2 * (rb + j * 1024 + tid)] : 0u;
-    for (int c = tid; c < Cpad; c += 1024) tot[c] = 0;
-    __syncthreads();
-    for (int i0 = rb; i0 < re; i0 += 4096) {
-        if (i0 > rb) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v[j] = i0 + j * 1024 + tid < re ? pk[2 * (i0 + j * 1024 + tid)] : 0u;
-        }
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (i0 + j * 1024 + tid < re) atomicAdd(&tot[(int)min(0xFFFFFFFFu - v[j], (uint32_t)Cpad - 1u)], 1);
-    }
-    __syncthreads();
-    int *out = d.range_tot + ((size_t)u * gridDim.x + r) * Cpad;
-    for (int c = tid; c < Cpad; c += 1024) out[c] = tot[c];
+// Sorting the tokens by cluster (ascending position inside a cluster), range by range: a unit's tokens
+// are cut into R ranges of L, one workgroup each, and every range is sorted by itself (`order`, stable
+// counting sort) with every cluster's piece (first slot, members) beside it (`range_off`).  The members of
+// a cluster in ascending position are its pieces of range 0, 1, ...: what reads members (the means, the
+// page layout) finds member j through the pieces' lengths (MemberList), so no pass over the
+// whole unit ties the ranges together: one launch per round, bound by its latencies.  (With a second
+// launch that turned the ranges' totals into unit-wide positions the two took 17.2 us per round at
+// 8 units x 32768 tokens x 512 clusters and 32 us at 131072 x 2048, most of it reading R totals per
+// cluster in every workgroup; this one takes 6.1 and 16 us, and the means and the page layout
+// read their lists at 3 to 8 us more.  A fifth wave in the means that prepared the next cluster's list while
+// four summed was slower, 24 against 17.3 us: its chain of list reads is the longer one.)
+// A range is cut into W segments, one per wave.  A wave walks its segment 64 tokens at a time: lanes
+// with the same cluster find each other bit by bit of the id (ballots), the first of them moves the
+// segment's counter of that cluster past all of them, and a token's rank among its cluster's
+// members of the segment stays in its register.  The counters are then scanned over segments and
+// clusters and every token's slot is counter + rank.  W x Cpad counters of 4 bytes fit 144 KB.
+constexpr int kSortMaxLen = 4096;  // tokens per range at most
+constexpr int kSortCounters = 36864;
+
+int sort_range_len(int U, int n) {
+    // short ranges keep the chip busy, few ranges keep the reading of their pieces short: at most 64 per
+    // unit and one workgroup per CU unless even the longest ranges are more
+    int L = 1024;
+    while (L < kSortMaxLen && ((n + L - 1) / L > 64 || (long long)U * ((n + L - 1) / L) > 256)) L *= 2;
+    return L;
+}
+size_t sort_ranges_max(int U, int max_tokens) {
+    return std::max<size_t>(256, (size_t)U * ((max_tokens + kSortMaxLen - 1) / kSortMaxLen));
 }
 
-constexpr int kSortRegGroups = 32;
-
-template <bool REG>
-__global__ __launch_bounds__(1024) void sort_unit_kernel(Dev d, int n, int range_len, int W, int seg, float *best_out,
-                                                         int *assign_out) {
-    extern __shared__ __align__(8) int cnt[];  // [W][Cpad] counters, then [W][Cpad] 64-bit lane masks
-    __shared__ int wsum[2][16];
-    __shared__ int carry[2];
+template <int NG>  // groups of 64 tokens per wave at most
+__global__ __launch_bounds__(1024) void range_sort_kernel(Dev d, int n, int L, int W, int nbits, int clear, float *best_out,
+                                                          int *assign_out) {
+    extern __shared__ __align__(16) int pos_all[];  // [W][Cpad]
+    __shared__ int wsum[16];
+    __shared__ int carry;
     const int r = blockIdx.x, R = gridDim.x, u = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int Cpad = d.Cpad;
-    const int rb = r * range_len, re = min(n, rb + range_len);  // this workgroup's tokens
+    const int rb = r * L, re = min(n, rb + L), seg = L / W;
     // low word of a packed winner = ~cluster id (the high word, the score, is read only for best_out)
-    const uint32_t *pk = (const uint32_t *)(d.packed + (size_t)u * d.max_tokens);
+    u64 *packed = d.packed + (size_t)u * d.max_tokens;
+    const uint32_t *pk = (const uint32_t *)packed;
     const int beg = min(re, rb + wave * seg), end = wave < W ? min(re, beg + seg) : beg;  // this wave's tokens
-    // the winners of the first groups are in flight while the counters are cleared
-    constexpr int NB = REG ? kSortRegGroups : 16;  // groups per batch of loads
-    uint32_t v[NB];
+    uint32_t v[NG];
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
+    for (int j = 0; j < NG; ++j) {
         const int i = beg + j * 64 + lane;
         v[j] = i < end ? pk[2 * i] : 0u;
     }
-    u64 *mask_all = (u64 *)(cnt + W * Cpad);  // [W][Cpad] lane masks of the rank phase
-    for (int x = tid; x < W * Cpad; x += 1024) { cnt[x] = 0; mask_all[x] = 0ull; }
-    if (tid < 2) carry[tid] = 0;
+    for (int x = tid; x < W * Cpad / 4; x += 1024) ((int4 *)pos_all)[x] = make_int4(0, 0, 0, 0);  // (Cpad is a multiple of 32)
+    if (tid == 0) carry = 0;
     __syncthreads();
-    int *pos = cnt + (wave < W ? wave : 0) * Cpad;
-    u64 *mask = mask_all + (size_t)(wave < W ? wave : 0) * Cpad;
-    // cluster id of a packed winner (always < Cpad for finite keys; clamped so that no input can
-    // send a counter update or an output slot out of range)
-    auto cluster_of = [&](uint32_t w) { return (int)min(0xFFFFFFFFu - w, (uint32_t)Cpad - 1u); };
-    auto count_one = [&](int i, uint32_t w) {
-        const int a = cluster_of(w);
-        d.assign[(size_t)u * d.max_tokens + i] = a;
-        if (assign_out) assign_out[(size_t)u * n + i] = a;
-        if (best_out) best_out[(size_t)u * n + i] = -2.0f * ordered_f32(pk[2 * i + 1]);
-        atomicAdd(&pos[a], 1);
-        return a;
-    };
-    int areg[REG ? kSortRegGroups : 1];
-    // ---- count
-    if constexpr (REG) {
+    // ---- rank inside the segment (row `wave` of the counters is this wave's alone)
+    int *pos = pos_all + (wave < W ? wave : 0) * Cpad;
+    const u64 lt = (1ull << lane) - 1ull;
+    int cl[NG], rank[NG];
 #pragma unroll
-        for (int j = 0; j < NB; ++j) {
-            const int i = beg + j * 64 + lane;
-            areg[j] = i < end ? count_one(i, v[j]) : 0;
+    for (int j = 0; j < NG; ++j) {
+        const int i = beg + j * 64 + lane;
+        const bool valid = i < end;
+        // (always < Cpad for finite keys; clamped so that no input can send a counter out of range)
+        const int a = (int)min(0xFFFFFFFFu - v[j], (uint32_t)Cpad - 1u);
+        cl[j] = a;
+        rank[j] = 0;
+        if (beg + j * 64 >= end) continue;  // (wave-uniform)
+        u64 peers = __ballot(valid);
+        for (int b = 0; b < nbits; ++b) {
+            const bool bit = (a >> b) & 1;
+            const u64 m = __ballot(bit);
+            peers &= bit ? m : ~m;
         }
-    } else {
-        for (int g0 = beg; g0 < end; g0 += NB * 64) {
-            if (g0 > beg) {
-#pragma unroll
-                for (int j = 0; j < NB; ++j) {
-                    const int i = g0 + j * 64 + lane;
-                    v[j] = i < end ? pk[2 * i] : 0u;
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                const int i = g0 + j * 64 + lane;
-                if (i < end) count_one(i, v[j]);
-            }
+        if (valid) {
+            const int base = pos[a];
+            rank[j] = base + (int)__popcll(peers & lt);
+            if ((peers & lt) == 0ull) pos[a] = base + (int)__popcll(peers);
+            d.assign[(size_t)u * d.max_tokens + i] = a;
+            if (assign_out) assign_out[(size_t)u * n + i] = a;
+            if (best_out) best_out[(size_t)u * n + i] = -2.0f * ordered_f32(pk[2 * i + 1]);
+            if (clear) packed[i] = 0ull;
         }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // (the LDS unit executes a wave's accesses in order)
     }
     __syncthreads();
-    // ---- scan
-    const int *rtot = d.range_tot + (size_t)u * R * Cpad;
+    // ---- scan over segments and clusters
+    uint32_t *off = d.range_off + ((size_t)u * R + r) * Cpad;
     for (int c0 = 0; c0 < Cpad; c0 += 1024) {
         const int c = c0 + tid;
-        int own = 0, before = 0, tot = 0;
-        if (c < Cpad) {
-            for (int w = 0; w < W; ++w) {
-                const int t = cnt[w * Cpad + c];
-                cnt[w * Cpad + c] = own;
-                own += t;
-            }
-            tot = own;
-            if (R > 1) {
-                tot = 0;
-                for (int q0 = 0; q0 < R; q0 += 32) {  // 32 counts in flight per round trip
-                    int t[32];
+        int t[16], tot = 0;
 #pragma unroll
-                    for (int j = 0; j < 32; ++j) t[j] = q0 + j < R ? rtot[(size_t)(q0 + j) * Cpad + c] : 0;
-#pragma unroll
-                    for (int j = 0; j < 32; ++j) {
-                        if (q0 + j < r) before += t[j];
-                        tot += t[j];
-                    }
-                }
-            }
+        for (int w = 0; w < 16; ++w) {
+            t[w] = c < Cpad && w < W ? pos_all[w * Cpad + c] : 0;
+            tot += t[w];
         }
-        const int pages = (tot + d.s - 1) / d.s;
-        int a = tot, b = pages;  // inclusive wave scans of (tot, pages)
-        for (int off = 1; off < 64; off <<= 1) {
-            const int ta = __shfl_up(a, off), tb = __shfl_up(b, off);
-            if (lane >= off) { a += ta; b += tb; }
+        int incl = tot;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int x = __shfl_up(incl, o);
+            if (lane >= o) incl += x;
         }
-        if (lane == 63) { wsum[0][wave] = a; wsum[1][wave] = b; }
+        if (lane == 63) wsum[wave] = incl;
         __syncthreads();
-        int pa = carry[0], pb = carry[1];
-        for (int w = 0; w < wave; ++w) { pa += wsum[0][w]; pb += wsum[1][w]; }
-        const int ex_a = pa + a - tot, ex_b = pb + b - pages;
+        int ex = carry + incl - tot;
+        for (int w = 0; w < wave; ++w) ex += wsum[w];
         if (c < Cpad) {
-            for (int w = 0; w < W; ++w) cnt[w * Cpad + c] += ex_a + before;
-            if (r == 0) {
-                d.cluster_start[(size_t)u * (Cpad + 1) + c] = ex_a;
-                d.page_base[(size_t)u * (Cpad + 1) + c] = ex_b;
-                if (c < d.C) {
-                    d.cluster_cnt[(size_t)u * d.C + c] = tot;
-                    d.cluster_tail[(size_t)u * d.C + c] = tot > 0 ? ex_b + pages - 1 : -1;
-                }
+            off[c] = (uint32_t)ex << 16 | (uint32_t)tot;  // (both at most kSortMaxLen)
+            int run = ex;
+#pragma unroll
+            for (int w = 0; w < 16; ++w) {
+                if (w < W) pos_all[w * Cpad + c] = run;
+                run += t[w];
             }
         }
         __syncthreads();
-        if (tid == 1023) { carry[0] = pa + a; carry[1] = pb + b; }
+        if (tid == 1023) carry = ex + tot;  // (threads past Cpad add nothing)
         __syncthreads();
     }
-    if (tid == 0 && r == 0) {
-        d.cluster_start[(size_t)u * (Cpad + 1) + Cpad] = carry[0];
-        d.page_base[(size_t)u * (Cpad + 1) + Cpad] = carry[1];
-        d.n_pages[u] = carry[1];
-    }
-    // ---- rank (row `wave` of the counters is touched by this wave only from here on)
-    int *order = d.order + (size_t)u * d.max_tokens;
-    const u64 lt = (1ull << lane) - 1ull;
-    // Lanes of one group with the same cluster find each other through a 64-bit lane mask per
-    // cluster in LDS (a table of this wave's own): every lane ORs its bit into its cluster's entry,
-    // reads the entry back and clears it.  The LDS unit executes one wave's instructions in order,
-    // so the three steps need no wait between them, only their program order.
-    auto rank_group = [&](int i, int a) {
-        const bool valid = i < end;
-        u64 peers = 0ull;
-        int base = 0;
-        if (valid) atomicOr(&mask[a], 1ull << lane);
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        if (valid) { peers = mask[a]; base = pos[a]; }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        if (valid) {
-            mask[a] = 0ull;
-            if ((peers & lt) == 0ull) pos[a] = base + (int)__popcll(peers);  // the first of them moves the cursor
-            order[base + (int)__popcll(peers & lt)] = i;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    };
-    if constexpr (REG) {
+    // ---- place
+    int *order = d.order + (size_t)u * d.max_tokens + rb;
 #pragma unroll
-        for (int j = 0; j < NB; ++j) {
-            if (beg + j * 64 >= end) break;  // (wave-uniform)
-            rank_group(beg + j * 64 + lane, areg[j]);
-        }
-    } else {
-        for (int g0 = beg; g0 < end; g0 += NB * 64) {
-#pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                const int i = g0 + j * 64 + lane;
-                v[j] = i < end ? pk[2 * i] : 0u;  // (read again; nothing written above is read back)
-            }
-#pragma unroll
-            for (int j = 0; j < NB; ++j) {
-                if (g0 + j * 64 >= end) break;  // (wave-uniform)
-                rank_group(g0 + j * 64 + lane, cluster_of(v[j]));
-            }
-        }
+    for (int j = 0; j < NG; ++j) {
+        const int i = beg + j * 64 + lane;
+        if (i < end) order[pos[cl[j]] + rank[j]] = i;
     }
 }
 
-// ranges per unit of the sort: enough workgroups for the chip, at least 1024 tokens each
-int sort_ranges(int U, int n, int *range_len) {
-    int R = std::max(1, std::min(256 / std::max(U, 1), (n + 1023) / 1024));
-    *range_len = round_up((n + R - 1) / R, 64);
-    return (n + *range_len - 1) / *range_len;
+void launch_sort(const Dev &d, int n, bool clear, float *best_out, int *assign_out, hipStream_t st) {
+    const int L = sort_range_len(d.U, n), R = (n + L - 1) / L;
+    int W = 16, nbits = 0;
+    while (W * d.Cpad > kSortCounters) W /= 2;  // (Cpad <= 8192: W >= 4)
+    while ((1 << nbits) < d.Cpad) ++nbits;
+    const size_t lds = (size_t)W * d.Cpad * 4;
+    clear = clear && assign_slices(d) > 1;
+#define ICE_SORT(ng)                                                                                                       \
+    do {                                                                                                                   \
+        allow_dynamic_lds((const void *)range_sort_kernel<ng>, lds);                                                       \
+        hipLaunchKernelGGL(range_sort_kernel<ng>, dim3(R, d.U), dim3(1024), lds, st, d, n, L, W, nbits, clear ? 1 : 0, best_out, assign_out); \
+    } while (0)
+    if (L / W <= 4 * 64) ICE_SORT(4);
+    else ICE_SORT(16);
+#undef ICE_SORT
 }
 
-void launch_sort(const Dev &d, int n, float *best_out, int *assign_out, hipStream_t st) {
-    int range_len;
-    const int R = sort_ranges(d.U, n, &range_len);
-    const int W = d.Cpad <= 768 ? 16 : 12288 / d.Cpad;  // (12 bytes per segment and cluster in 144 KB; Cpad <= 8192: W >= 1)
-    const int seg = round_up((range_len + W - 1) / W, 64);
-    const size_t lds = (size_t)W * d.Cpad * 12;
-    if (R > 1)
-        hipLaunchKernelGGL(sort_totals_kernel, dim3(R, d.U), dim3(1024), (size_t)d.Cpad * sizeof(int), st, d, n, range_len);
-    if (seg <= kSortRegGroups * 64) {
-        allow_dynamic_lds((const void *)sort_unit_kernel<true>, lds);
-        hipLaunchKernelGGL(sort_unit_kernel<true>, dim3(R, d.U), dim3(1024), lds, st, d, n, range_len, W, seg, best_out, assign_out);
-    } else {
-        allow_dynamic_lds((const void *)sort_unit_kernel<false>, lds);
-        hipLaunchKernelGGL(sort_unit_kernel<false>, dim3(R, d.U), dim3(1024), lds, st, d, n, range_len, W, seg, best_out, assign_out);
+// The members of one cluster in ascending position, out of the ranges' sorted pieces.  pre[r] = members
+// in the ranges before r, at[r] = index into the unit's `order` of range r's first one, both in LDS; member
+// j sits in the last range with pre[r] <= j.
+struct MemberList {
+    const int *order, *pre, *at;
+    int R;
+    __device__ int operator()(int j) const {
+        int lo = 0, hi = R;
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (pre[mid] <= j) lo = mid; else hi = mid;
+        }
+        return order[at[lo] + j - pre[lo]];
     }
+};
+// inclusive sum over the wave on the vector unit (no trip through LDS)
+__device__ inline int wave_scan_add(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);  // row_shr 1, 2, 4, 8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);  // row_bcast 15 into rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // row_bcast 31 into rows 2 and 3
+    return x;
 }
+// One wave fills pre[0..R) and at[0..R) of cluster c and returns the number of members (to every lane).  With
+// `slots` the members' indexes into `order` go to slots[0..kMemberSlots) as well, piece by piece, as long as
+// no piece has more than kMemberPiece of them (*listed): one read per member instead of a search.
+constexpr int kMemberSlots = 512, kMemberPiece = 32;
+__device__ inline int member_ranges(const uint32_t *off, int Cpad, int R, int L, int c, int lane, int *pre, int *at, int *slots, bool *listed) {
+    int total = 0;
+    bool ok = slots != nullptr;
+    for (int r0 = 0; r0 < R; r0 += 64) {
+        const int r = r0 + lane;
+        const uint32_t o = r < R ? off[(size_t)r * Cpad + c] : 0u;
+        const int cnt = (int)(o & 0xFFFFu), from = r * L + (int)(o >> 16);
+        const int incl = wave_scan_add(cnt), first = total + incl - cnt;
+        if (r < R) {
+            pre[r] = first;
+            at[r] = from;
+        }
+        total += __builtin_amdgcn_readlane(incl, 63);
+        ok = ok && total <= kMemberSlots && __ballot(cnt > kMemberPiece) == 0ull;
+        for (int e = 0; ok && __ballot(e < cnt) != 0ull; ++e)
+            if (e < cnt) slots[first + e] = from + e;
+    }
+    if (listed) *listed = ok;
+    return total;
+}
+
 // The key rows of one clustering pass are read by assign, then by means (and once more by paginate).
 // While they fit the chip's last-level cache (256 MB) the second reader finds them there; beyond
 // that every pass streams from HBM, and the non-temporal hint is what gets the most out of it.
@@ -796,13 +759,25 @@ static bool keys_exceed_cache(const Dev &d, int n) { return (size_t)d.U * (size_
 // bf16 rounding + squared norm of the mean into the OTHER centroid buffer; an empty cluster keeps
 // its centroid.
 template <bool STREAM>
-__global__ __launch_bounds__(256) void means_kernel(Dev d, const bf16_t *__restrict__ K, int n, int cur) {
+__global__ __launch_bounds__(256) void means_kernel(Dev d, const bf16_t *__restrict__ K, int n, int cur, int R, int L) {
+    extern __shared__ int lists[];  // pre [R], at [R]
     __shared__ float4 part_sum[3][16][2];
+    __shared__ int slots[kMemberSlots], sh_cnt, sh_listed;
     const int u = blockIdx.y, c = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int g = lane >> 4, ch = lane & 15;
-    const int start = d.cluster_start[(size_t)u * (d.Cpad + 1) + c];
-    const int cnt = d.cluster_start[(size_t)u * (d.Cpad + 1) + c + 1] - start;
-    const int *ord = d.order + (size_t)u * d.max_tokens + start;
+    const MemberList search = {d.order + (size_t)u * d.max_tokens, lists, lists + R, R};
+    if (wave == 0) {
+        bool listed;
+        const int m = member_ranges(d.range_off + (size_t)u * R * d.Cpad, d.Cpad, R, L, c, lane, lists, lists + R, slots, &listed);
+        if (lane == 0) {
+            sh_cnt = m;
+            sh_listed = listed;
+            d.cluster_cnt[(size_t)u * d.C + c] = m;
+        }
+    }
+    lds_barrier();
+    const int cnt = sh_cnt;
+    const bool listed = sh_listed != 0;
     const bf16_t *Ku = K + (size_t)u * n * kD;
     const int quarter = (cnt + 3) / 4;
     const int lo = min(cnt, wave * quarter), hi = min(cnt, lo + quarter);
@@ -813,7 +788,8 @@ __global__ __launch_bounds__(256) void means_kernel(Dev d, const bf16_t *__restr
     // list is read 64 entries at a time (one per lane) and the rows are fetched eight per group at
     // once, so a wave keeps 8 KB of key rows in flight instead of one dependent load pair per step.
     for (int base = lo; base < hi; base += 64) {
-        const int mine = base + lane < hi ? ord[base + lane] : -1;
+        int mine = -1;
+        if (base + lane < hi) mine = listed ? search.order[slots[base + lane]] : search(base + lane);
         const int rows = min(64, hi - base);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -842,7 +818,7 @@ __global__ __launch_bounds__(256) void means_kernel(Dev d, const bf16_t *__restr
     // order by the first wave, requested before the waves meet
     float aug_part = 0.f;
     if (d.tk && wave == 0)
-        for (int r = lane; r < cnt; r += 64) aug_part += bf16_to_f32(d.kaug[(size_t)u * d.max_tokens + ord[r]]);
+        for (int r = lane; r < cnt; r += 64) aug_part += bf16_to_f32(d.kaug[(size_t)u * d.max_tokens + (listed ? search.order[slots[r]] : search(r))]);
     if (wave > 0 && g == 0) {
         part_sum[wave - 1][ch][0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
         part_sum[wave - 1][ch][1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
@@ -900,8 +876,10 @@ __global__ __launch_bounds__(256) void means_kernel(Dev d, const bf16_t *__restr
 }
 
 void launch_means(const Dev &d, const bf16_t *K, int n, int cur, hipStream_t st) {
-    if (keys_exceed_cache(d, n)) hipLaunchKernelGGL(means_kernel<true>, dim3(d.C, d.U), dim3(256), 0, st, d, K, n, cur);
-    else hipLaunchKernelGGL(means_kernel<false>, dim3(d.C, d.U), dim3(256), 0, st, d, K, n, cur);
+    const int L = sort_range_len(d.U, n), R = (n + L - 1) / L;
+    const size_t lds = (size_t)R * 8;
+    if (keys_exceed_cache(d, n)) hipLaunchKernelGGL(means_kernel<true>, dim3(d.C, d.U), dim3(256), lds, st, d, K, n, cur, R, L);
+    else hipLaunchKernelGGL(means_kernel<false>, dim3(d.C, d.U), dim3(256), lds, st, d, K, n, cur, R, L);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -909,39 +887,91 @@ void launch_means(const Dev &d, const bf16_t *K, int n, int cur, hipStream_t st)
 // tokens; consecutive page ids.  One wave per page copies the s key rows and s value rows into
 // the page's contiguous tiles, records their positions, and forms the representative: the fp32
 // sum of the page's keys in slot order (one add per slot), divided by the fill, rounded to bf16.
+//
+// layout_kernel, one workgroup per unit, goes first: the exclusive scan of the clusters' page counts
+// (`page_base`, n_pages, tails) and every page's cluster, found by a search over the scan in LDS.  With
+// `arm` it also sets the unit's counters for the decode calls (a build; not a re-run of the stage).
+__global__ __launch_bounds__(1024) void layout_kernel(Dev d, int n, int arm) {
+    extern __shared__ int pb[];  // [C + 1]
+    __shared__ int wsum[16];
+    __shared__ int carry;
+    const int u = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, C = d.C;
+    if (tid == 0) carry = 0;
+    __syncthreads();
+    for (int c0 = 0; c0 < C; c0 += 1024) {
+        const int c = c0 + tid;
+        const size_t cl = (size_t)u * C + c;
+        const int cnt = c < C ? d.cluster_cnt[cl] : 0, pages = (cnt + d.s - 1) / d.s;
+        int incl = pages;
+        for (int o = 1; o < 64; o <<= 1) {
+            const int x = __shfl_up(incl, o);
+            if (lane >= o) incl += x;
+        }
+        if (lane == 63) wsum[wave] = incl;
+        __syncthreads();
+        int ex = carry + incl - pages;
+        for (int w = 0; w < wave; ++w) ex += wsum[w];
+        if (c < C) {
+            pb[c] = ex;
+            d.page_base[cl] = ex;
+            d.cluster_tail[cl] = cnt > 0 ? ex + pages - 1 : -1;
+            if (cnt == 0) {  // (the state of the other clusters' tail pages follows with those pages)
+                d.tail_fill[cl] = d.s;
+                for (int x = 0; x < kD / 4; ++x) ((float4 *)(d.tail_sum + cl * kD))[x] = make_float4(0.f, 0.f, 0.f, 0.f);
+            }
+        }
+        __syncthreads();
+        if (tid == 1023) carry = ex + pages;
+        __syncthreads();
+    }
+    const int np = carry;
+    if (tid == 0) {
+        d.n_pages[u] = np;
+        if (arm) { d.n_tokens[u] = n; d.counter[u] = 0; d.attn_arrive[u] = 0; }
+    }
+    for (int p = tid; p < d.max_pages; p += 1024) {
+        int c = -1;
+        if (p < np) {  // largest c with pb[c] <= p (clusters without pages are skipped)
+            int lo = 0, hi = C;
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if (pb[mid] <= p) lo = mid; else hi = mid;
+            }
+            c = lo;
+        }
+        d.page_cluster[(size_t)u * d.max_pages + p] = c;
+    }
+}
+
 template <bool STREAM>
 __global__ __launch_bounds__(256) void paginate_kernel(Dev d, const bf16_t *__restrict__ K,
-                                                        const bf16_t *__restrict__ V, int n) {
-    extern __shared__ __align__(16) char smem[];  // [4][s][128] bf16
+                                                        const bf16_t *__restrict__ V, int n, int R, int L, int arm) {
+    extern __shared__ __align__(16) char smem[];  // [4][s][128] bf16, then [4] (pre [R], at [R])
     const int u = blockIdx.y, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int p = blockIdx.x * 4 + wave;
     if (p >= d.max_pages) return;
     const int s = d.s;
     const size_t pg = (size_t)u * d.max_pages + p;
-    const int np = d.n_pages[u];
-    if (p >= np) {  // unused page: clear its table entries
-        if (lane == 0) { d.page_cluster[pg] = -1; d.page_fill[pg] = 0; }
+    const int c = d.page_cluster[pg];
+    if (arm && lane == 0) d.scores[pg] = 0xFFFFFFFFu;  // (empty)
+    if (c < 0) {  // unused page: clear its table entries
+        if (lane == 0) d.page_fill[pg] = 0;
         for (int t = lane; t < s; t += 64) d.page_pos[pg * s + t] = -1;
         return;
     }
-    const int *pb = d.page_base + (size_t)u * (d.Cpad + 1);
-    int lo = 0, hi = d.Cpad;  // largest c with pb[c] <= p (clusters without pages are skipped)
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (pb[mid] <= p) lo = mid; else hi = mid;
-    }
-    const int c = lo;
-    const int start = d.cluster_start[(size_t)u * (d.Cpad + 1) + c];
-    const int cnt = d.cluster_start[(size_t)u * (d.Cpad + 1) + c + 1] - start;
-    const int r0 = (p - pb[c]) * s;
+    int *pre = (int *)(smem + (size_t)4 * s * kD * 2) + wave * 2 * R, *at = pre + R;
+    const int r0 = (p - d.page_base[(size_t)u * d.C + c]) * s;
+    const int cnt = member_ranges(d.range_off + (size_t)u * R * d.Cpad, d.Cpad, R, L, c, lane, pre, at, nullptr, nullptr);
+    const MemberList member = {d.order + (size_t)u * d.max_tokens, pre, at, R};
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     const int fill = min(s, cnt - r0);
-    const int *ord = d.order + (size_t)u * d.max_tokens + start + r0;
+    const int mine = lane < fill ? member(r0 + lane) : -1;  // slot `lane`'s token (s <= 64)
     const int g = lane >> 4, ch = lane & 15;
     bf16_t *tile = (bf16_t *)smem + (size_t)wave * s * kD;
     for (int t4 = 0; t4 < s; t4 += 4) {
         const int slot = t4 + g;
         const bool valid = slot < fill;
-        const int tok = valid ? ord[slot] : -1;
+        const int tok = __shfl(mine, slot);
         uint4 kw = make_uint4(0, 0, 0, 0), vw = kw;
         if (valid) {
             kw = load16<STREAM>((const uint4 *)(K + ((size_t)u * n + tok) * kD) + ch);
@@ -950,9 +980,9 @@ __global__ __launch_bounds__(256) void paginate_kernel(Dev d, const bf16_t *__re
         store16<STREAM>((uint4 *)(d.Kp + (pg * s + slot) * kD) + ch, kw);
         store16<STREAM>((uint4 *)(d.Vp + (pg * s + slot) * kD) + ch, vw);
         ((uint4 *)(tile + (size_t)slot * kD))[ch] = kw;
-        if (ch == 0) d.page_pos[pg * s + slot] = tok;
     }
-    if (lane == 0) { d.page_cluster[pg] = c; d.page_fill[pg] = fill; }
+    if (lane < s) d.page_pos[pg * s + lane] = mine;
+    if (lane == 0) d.page_fill[pg] = fill;
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the tile writes above are visible to the wave
     float a0 = 0.f, a1 = 0.f;
@@ -964,13 +994,25 @@ __global__ __launch_bounds__(256) void paginate_kernel(Dev d, const bf16_t *__re
     ((float2 *)(d.page_sum + pg * kD))[lane] = make_float2(a0, a1);
     const float f = (float)fill;
     ((uint32_t *)(d.rep + pg * kD))[lane] = (uint32_t)f32_to_bf16(a0 / f) | ((uint32_t)f32_to_bf16(a1 / f) << 16);
+    if (r0 + fill == cnt) {  // the cluster's last page: what an insertion needs of it, beside the cluster
+        const size_t cl = (size_t)u * d.C + c;
+        ((float2 *)(d.tail_sum + cl * kD))[lane] = make_float2(a0, a1);
+        if (lane == 0) d.tail_fill[cl] = fill;
+    }
 }
 
-void launch_paginate(const Dev &d, const bf16_t *K, const bf16_t *V, int n, hipStream_t st) {
-    const size_t lds = (size_t)4 * d.s * kD * 2;
-    if (keys_exceed_cache(d, n)) hipLaunchKernelGGL(paginate_kernel<true>, dim3((d.max_pages + 3) / 4, d.U), dim3(256), lds, st, d, K, V, n);
-    else hipLaunchKernelGGL(paginate_kernel<false>, dim3((d.max_pages + 3) / 4, d.U), dim3(256), lds, st, d, K, V, n);
-    launch_refresh_tails(d, st);
+void launch_paginate(const Dev &d, const bf16_t *K, const bf16_t *V, int n, bool arm, hipStream_t st) {
+    const int L = sort_range_len(d.U, n), R = (n + L - 1) / L;
+    const size_t lds = (size_t)4 * d.s * kD * 2 + (size_t)4 * R * 8;
+    hipLaunchKernelGGL(layout_kernel, dim3(d.U), dim3(1024), (size_t)(d.C + 1) * 4, st, d, n, arm ? 1 : 0);
+#define ICE_PAGINATE(stream)                                                                                               \
+    do {                                                                                                                   \
+        allow_dynamic_lds((const void *)paginate_kernel<stream>, lds);                                                     \
+        hipLaunchKernelGGL(paginate_kernel<stream>, dim3((d.max_pages + 3) / 4, d.U), dim3(256), lds, st, d, K, V, n, R, L, arm ? 1 : 0); \
+    } while (0)
+    if (keys_exceed_cache(d, n)) ICE_PAGINATE(true);
+    else ICE_PAGINATE(false);
+#undef ICE_PAGINATE
 }
 
 // ------------------------------------------------------------------------------------------------

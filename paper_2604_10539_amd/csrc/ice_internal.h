@@ -62,12 +62,11 @@ struct Dev {
     int *init_idx;              // [U][C]
     int *assign;                // [U][max_tokens]
     unsigned long long *packed; // [U][max_tokens] (ordered score << 32) | ~cluster
-    int *order;                 // [U][max_tokens] tokens sorted by (cluster, position)
-    int *cluster_start;         // [U][Cpad+1] exclusive scan of counts
-    int *page_base;             // [U][Cpad+1] exclusive scan of pages per cluster
+    int *order;                 // [U][max_tokens] tokens sorted by (cluster, position) inside every range of the sort
+    int *page_base;             // [U][C] exclusive scan of pages per cluster
     float *attn_part;           // [256][G][130] partial results of the split attention (shares x units <= 256)
     int *attn_arrive;           // [U] arrival counters of its shares (zero between launches)
-    int *range_tot;             // [U][R][Cpad] members per cluster in each of the sort's R token ranges (R = max(1, 256 / U) at most)
+    uint32_t *range_off;        // [U][R][Cpad] a cluster's piece of each of the sort's R token ranges: first slot << 16 | members
     // decode scratch
     uint32_t *scores;           // [U][max_pages] fp32 bits of the page scores; 0xFFFFFFFF = empty slot
     int *counter;               // [U] arrival counters of the decode-step kernel (zero between launches)
@@ -99,12 +98,14 @@ void launch_init_centroids(const Dev &d, const bf16_t *K, int n, const int *init
                            uint64_t seed, int cur, hipStream_t st);
 void launch_load_centroids(const Dev &d, const bf16_t *cent, int cur, hipStream_t st);
 void launch_key_aug(const Dev &d, const bf16_t *K, int n, hipStream_t st);
-void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, hipStream_t st);
-void launch_sort(const Dev &d, int n, float *best_out_or_null, int *assign_out_or_null, hipStream_t st);
+void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, bool clear, hipStream_t st);
+void launch_sort(const Dev &d, int n, bool clear, float *best_out_or_null, int *assign_out_or_null, hipStream_t st);
+size_t sort_ranges_max(int U, int max_tokens);  // (unit, range) pairs of any sort of at most max_tokens tokens
 void launch_means(const Dev &d, const bf16_t *K, int n, int cur, hipStream_t st);
-void launch_paginate(const Dev &d, const bf16_t *K, const bf16_t *V, int n, hipStream_t st);
+// arm: also the decode state of a fresh index (token counters, arrival counters, empty score slots)
+void launch_paginate(const Dev &d, const bf16_t *K, const bf16_t *V, int n, bool arm, hipStream_t st);
 void launch_refresh_centroids(const Dev &d, int cur, hipStream_t st);
-void launch_refresh_tails(const Dev &d, hipStream_t st);  // tail_fill / tail_sum from the page tables (after a build or an import)
+void launch_refresh_tails(const Dev &d, hipStream_t st);  // tail_fill / tail_sum from the page tables (after an import)
 void launch_insert(const Dev &d, const bf16_t *k, const bf16_t *v, int m, int cur, hipStream_t st);
 // scores + top-P selection (+ attention when out != nullptr) in one launch
 // np_hint: host-side upper bound of the live pages per unit (tokens / page_size + clusters)

@@ -61,3 +61,62 @@ def test_assignment_at_every_share_of_a_centroid_slice(tiles, n):
             # both candidates' fp32 chains (129 or 128 products and the seed), halved objective doubled again
             mag = 0.5 * (cen ** 2).sum(1).max() + np.linalg.norm(keys, axis=1) * np.linalg.norm(cen, axis=1).max()
             assert np.all(obj[np.arange(n), a] - best <= 4.0 * (D + 3) * 2.0 ** -24 * mag)
+
+
+@pytest.mark.parametrize("U,n,C,s,lump", [
+    (1, 1, 1, 16, 0),            # one token
+    (2, 1023, 7, 16, 0), (2, 1024, 7, 16, 0), (2, 1025, 7, 64, 0),    # around one range; clusters longer than the member table
+    (3, 2500, 300, 16, 600),     # 600 tokens in a row of one cluster: a piece longer than the table takes
+    (40, 3000, 40, 32, 0),       # many units: longer ranges
+    (1, 66000, 900, 16, 0),      # two centroid slices; ranges of 2048
+    (1, 270000, 64, 64, 5000),   # more than 64 ranges
+    (1, 9000, 8192, 16, 0),      # four segments per range
+])
+def test_pages_hold_the_members_in_ascending_position(U, n, C, s, lump):
+    """The page layout is the stable sort of the assignment, whatever the sort's ranges and segments are, and the
+    means are the members' means."""
+    from paper_2604_10539_amd import IceIndex
+    w = datagen.small(n_tokens=n, n_clusters=C, n_kv_heads=U, n_components=max(2, C // 3))
+    K, V = datagen.keys_values(w)
+    if lump:
+        K[0, 0, n // 3:n // 3 + lump] = K[0, 0, n // 3]
+    ix = IceIndex(1, U, 4, n, s, C, kmeans_iters=2, init_idx=up(datagen.init_indices(w)))
+    ix.build_index(up(K), up(V))
+    ex = {k: down(v) for k, v in ix.export().items() if k != "view"}
+    for u in range(U):
+        a = ex["assign"][u, :n]
+        order = np.argsort(a, kind="stable")
+        cnt = np.bincount(a, minlength=C)
+        pages = (cnt + s - 1) // s
+        base, start = np.cumsum(pages) - pages, np.cumsum(cnt) - cnt
+        npg = int(pages.sum())
+        assert ex["n_pages"][u] == npg and np.array_equal(ex["cluster_cnt"][u], cnt)
+        assert np.array_equal(ex["cluster_tail"][u], np.where(cnt > 0, base + pages - 1, -1))
+        want = np.full((ex["page_pos"].shape[1], s), -1)
+        r = np.arange(n) - start[a[order]]
+        want[base[a[order]] + r // s, r % s] = order
+        assert np.array_equal(ex["page_pos"][u], want)
+        assert np.array_equal(ex["page_fill"][u], (want >= 0).sum(1))
+        assert np.array_equal(ex["page_cluster"][u], np.concatenate([np.repeat(np.arange(C), pages), np.full(len(want) - npg, -1)]))
+        live = want[:npg] >= 0
+        assert np.array_equal(ex["Kp"][u, :npg][live], K[0, u][want[:npg][live]])
+        assert np.array_equal(ex["Vp"][u, :npg][live], V[0, u][want[:npg][live]])
+        sums = np.zeros((C, D))
+        np.add.at(sums, a, widen(K[0, u]).astype(np.float64))
+        mags = np.zeros((C, D))
+        np.add.at(mags, a, np.abs(widen(K[0, u])).astype(np.float64))
+        # at most cnt + 8 roundings of partial sums bounded by the sum of magnitudes
+        assert np.all(np.abs(ex["cluster_sum"][u] - sums) <= (cnt[:, None] + 8) * 2.0 ** -24 * mags)
+    # an insertion finds the tail pages' state beside the clusters
+    k1 = narrow(np.random.default_rng(5).standard_normal((1, U, D)).astype(np.float32))
+    ix2 = IceIndex(1, U, 4, n + 1, s, C, kmeans_iters=2, init_idx=up(datagen.init_indices(w)))
+    ix2.build_index(up(K), up(V))
+    ix2.insert(up(k1), up(k1))
+    e2 = {k: down(v) for k, v in ix2.export().items() if k != "view"}
+    for u in range(U):
+        p, t = np.argwhere(e2["page_pos"][u] == n)[0]
+        c = e2["page_cluster"][u, p]
+        cnt0 = int(ex["cluster_cnt"][u, c])
+        assert t == cnt0 % s and e2["page_fill"][u, p] == t + 1 and e2["cluster_cnt"][u, c] == cnt0 + 1
+        old = ex["page_sum"][u, p] if t else np.zeros(D, np.float32)
+        assert np.array_equal(e2["page_sum"][u, p], old + widen(k1[0, u]))
