@@ -743,8 +743,8 @@ void launch_insert(const Dev &d, const bf16_t *k, const bf16_t *v, int m, int cu
 }
 
 // ------------------------------------------------------------------------------------------------
-template <int G, int NW, bool RES>
-__global__ __launch_bounds__(NW * 64) void attend_kernel(const bf16_t *__restrict__ q, const int *__restrict__ ids,
+template <int G, int NW, int RES, bool FILLS>
+__global__ __launch_bounds__(NW * 64, 4) void attend_kernel(const bf16_t *__restrict__ q, const int *__restrict__ ids,
                                                           const int *__restrict__ n_sel, int P, Dev d, Resident res,
                                                           float *__restrict__ out) {  // (scalars first: preloaded)
     extern __shared__ __align__(16) char smem[];
@@ -753,7 +753,7 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const bf16_t *__restric
     load_query_operand<G>(q, u, threadIdx.x & 63, qa, nullptr);
     const int *list = ids + (size_t)u * P;
     const int ns = ids ? max(0, min(n_sel[u], P)) : 0;  // (no page list: resident tokens only; negative count: none)
-    attend_pages<G, NW, RES>(d, u, qa, [=](int x) { return list[x]; }, ns, res, out, (float *)smem, [] {});
+    attend_pages<G, NW, RES, false, FILLS>(d, u, qa, [=](int x) { return list[x]; }, ns, res, out, (float *)smem, [] {});
 }
 
 // Few units and many pages per unit: one workgroup per unit would pull every tile through a single
@@ -761,11 +761,12 @@ __global__ __launch_bounds__(NW * 64) void attend_kernel(const bf16_t *__restric
 // workgroup leaves its partial result (attend_pages, PARTIAL) as device-scope words and bumps the
 // unit's arrival counter once those stores have completed; the last one to arrive merges the shares:
 // out = sum_s O_s e^(M_s - M) / sum_s L_s e^(M_s - M).  `arrive` is zero between launches (the last
-// workgroup puts it back).
-template <int G, int NW>
-__global__ __launch_bounds__(NW * 64) void attend_split_kernel(const bf16_t *__restrict__ q, const int *__restrict__ ids,
-                                                                const int *__restrict__ n_sel, int P, Dev d,
-                                                                float *__restrict__ part, int *__restrict__ arrive,
+// workgroup puts it back).  RES: the first SP shares are the pages', the others take `rper` 16-token blocks
+// each of the dense run or of the list of positions (SP = 0: no pages at all).
+template <int G, int NW, int RES>
+__global__ __launch_bounds__(NW * 64, 4) void attend_split_kernel(const bf16_t *__restrict__ q, const int *__restrict__ ids,
+                                                                const int *__restrict__ n_sel, int P, int SP, int rper, int after_select, Dev d,
+                                                                Resident res, float *__restrict__ part, int *__restrict__ arrive,
                                                                 float *__restrict__ out) {
     extern __shared__ __align__(16) char smem[];
     __shared__ int sh_last;
@@ -776,14 +777,23 @@ __global__ __launch_bounds__(NW * 64) void attend_split_kernel(const bf16_t *__r
     // shares are cut from the list's capacity P, not from the unit's count, so that every wave can ask
     // for its first page id together with the count (one round trip less); entries past the count
     // are dropped below
-    const int per = (P + S - 1) / S, lo = min(P, s * per), wave = tid >> 6;
-    const int *list = ids + (size_t)u * P + lo;
-    const int first = lo + wave < P ? list[wave] : -1;
-    const int ns = max(0, min(n_sel[u], P));
-    const int cnt = max(0, min(ns - lo, per));
-    attend_pages<G, NW, false, true>(d, u, qa, [=](int x) { return x == wave ? first : list[x]; }, cnt,
-                                     Resident{nullptr, nullptr, 0, nullptr, nullptr, 0}, part + ((size_t)u * S + s) * G * (kD + 2),
-                                     (float *)smem, [] {});
+    const int wave = tid >> 6;
+    float *mine = part + ((size_t)u * S + s) * G * (kD + 2);
+    if (RES == kNoRows || s < SP) {
+        const int per = (P + SP - 1) / SP, lo = min(P, s * per);
+        const int *list = ids + (size_t)u * P + lo;
+        const int first = lo + wave < P ? list[wave] : -1;
+        const int ns = max(0, min(n_sel[u], P));
+        const int cnt = max(0, min(ns - lo, per));
+        attend_pages<G, NW, kNoRows, true, false>(d, u, qa, [=](int x) { return x == wave ? first : list[x]; }, cnt,
+                                                  Resident{nullptr, nullptr, 0, nullptr, nullptr, 0}, mine, (float *)smem, [] {});
+    } else if constexpr (RES != kNoRows) {
+        Resident r = res;
+        r.b0 = (s - SP) * rper;
+        r.b1 = r.b0 + rper;
+        if (after_select && n_sel[u] < 0) r.b1 = r.b0;  // (a unit whose selection failed: zero output)
+        attend_pages<G, NW, RES, true, true>(d, u, qa, [](int) { return -1; }, 0, r, mine, (float *)smem, [] {});
+    }
     if (s == 0) ICE_STAMP(17);
     __syncthreads();  // every wave's partial stores have completed
     if (s == 0) ICE_STAMP(18);
@@ -837,17 +847,51 @@ static size_t attend_split_lds(int G, int NW, int S) {
 constexpr int kSplitMaxLdsBytes = 128 * 1024;
 // shares per unit of the split attention: as many workgroups as the chip has CUs, at least one page
 // per wave; below `min_shares` the exchange of the partial results costs more than the shares save
-constexpr int kPagesPerShare = 4;
+constexpr int kPagesPerShare = 8;
 constexpr int kFusedSplitMinShares = 4;  // when the attention follows the selection of the same call (it then takes a launch of its own)
-int attend_shares(const Dev &d, int P, int min_shares) {
+constexpr int kRowsSplitMinBlocks = 48, kRowsSplitMaxUnits = 32;  // pages and a dense run, in blocks of 16 tokens
+constexpr int kTokensSplitMinBlocks = 17;                         // gathered rows alone
+struct SplitPlan {
+    int S = 1, SP = 1;  // shares per unit; of them the pages'
+    int rper = 0;       // 16-token blocks per share of the dense run or list of positions
+};
+// P pages (0: none) and n_rows rows beside them
+SplitPlan attend_shares(const Dev &d, int P, int n_rows, int min_shares) {
     const int NW = d.G == 8 ? 8 : 16;
-    // (a CU draws ~30 GB/s from cold HBM however many waves ask: what shortens the attention is the
-    // number of CUs, so a share is kPagesPerShare pages even though a workgroup has a wave per page;
-    // fewer than min_shares workgroups' worth of pages, counted NW to a workgroup, are not split)
-    if ((P + NW - 1) / NW < min_shares) return 1;
+    SplitPlan p;
+    // A CU draws ~30 GB/s from cold HBM however many waves ask, so what shortens the attention is the number of
+    // CUs: a share is kPagesPerShare pages, or as many 16-row blocks, even though a workgroup of 16 waves
+    // could take 16 at once.  (Eight beat four, whose shares are twice as many to merge: fused step of 8 units
+    // x (64 pages + 512 rows) 30.5 us against 31.5, x (16 pages + 1024 rows) 18.2 against 19.5.)  Pages alone: less than
+    // min_shares workgroups' worth, counted NW to a workgroup, is not split.  With a dense run beside them
+    // the work splits from 48 blocks on while there are at most 32 units: 8 units x (16 + 32) blocks 19.6 us
+    // in one workgroup per unit and 17.8 split, 8 x (64 + 32) 36.9 and 30.5, 32 x (32 + 32) 28.5 and 26.3;
+    // eight heads a group 4 x (16 + 32) 17.4 and 17.3, 8 x (92 + 19) 24.6 and 19.6; but 8 x (16 + 13) 14.8 and
+    // 15.9, 64 x (16 + 32) 25.1 and 26.1, 128 x (16 + 64) 31.9 and 36.1.  Gathered rows split from 17 blocks on
+    // (32 units x 512 positions, two such layers behind a step: 46.6 and 44.5 us).
+    const int blocks = (n_rows + 15) / 16, items = P + blocks;
+    if (blocks > 0 && (P > 0 ? d.U > kRowsSplitMaxUnits || (long long)P * (d.s / 16) + blocks < kRowsSplitMinBlocks
+                             : blocks < kTokensSplitMinBlocks))
+        return p;
+    if (blocks == 0 && (items + NW - 1) / NW < min_shares) return p;
     const int fit = kSplitMaxLdsBytes / (int)(sizeof(float) * d.G * (kD + 2));  // shares whose results fit the merging workgroup's LDS
-    return std::max(1, std::min({256 / std::max(d.U, 1), (P + kPagesPerShare - 1) / kPagesPerShare, fit}));
+    const int S = std::min({256 / std::max(d.U, 1), (items + kPagesPerShare - 1) / kPagesPerShare, fit});
+    if (S < (P > 0) + (blocks > 0) || S < 2) return p;
+    int SR = blocks == 0 ? 0 : P == 0 ? S : std::max(1, std::min(S - 1, (int)(((long long)S * blocks + items / 2) / items)));
+    p.SP = S - SR;
+    if (blocks) {
+        p.rper = (blocks + SR - 1) / SR;
+        SR = (blocks + p.rper - 1) / p.rper;
+    }
+    p.S = p.SP + SR;
+    return p;
 }
+
+// Whether the attention over P pages fetches the pages' fills first (FILLS of attend_pages): with at least half
+// the chip's CUs busy and several pages per wave it is bound by its bytes (256 units x 64 pages of 16 slots,
+// fused step: 49.4 us without, 47.3 with); with few units by its round trips (8 units x 32 pages: 20.1
+// without, 20.6 with).
+static bool attend_by_fills(const Dev &d, int P) { return d.U >= 128 && P > 2 * (d.G == 8 ? 8 : 16); }
 
 // the token positions of the listed pages, in list and slot order, padded with -1
 __global__ void selected_tokens_kernel(Dev d, const int *__restrict__ ids, const int *__restrict__ n_sel, int P,
@@ -884,16 +928,22 @@ void launch_selected_tokens(const Dev &d, const int *ids, const int *n_sel, int 
 }
 
 void launch_attend(const Dev &d, const bf16_t *q, const int *ids, const int *n_sel, int P, const Resident &res_in,
-                   float *out, hipStream_t st, int min_shares) {
+                   float *out, hipStream_t st, int min_shares, int after_select, bool may_split) {
     const Resident res = res_in;
     const int n_res = res.n;
-    const int S = ids && n_res == 0 && !res.pos ? attend_shares(d, P, min_shares) : 1;
-    if (S > 1) {
+    const SplitPlan sp = may_split ? attend_shares(d, ids ? P : 0, n_res, min_shares) : SplitPlan{};
+    if (sp.S > 1) {
+#define ICE_ATTEND_SPLIT_K(g, nw, rows)                                                                                    \
+    do {                                                                                                                   \
+        allow_dynamic_lds((const void *)attend_split_kernel<g, nw, rows>, attend_split_lds(g, nw, sp.S));                  \
+        hipLaunchKernelGGL((attend_split_kernel<g, nw, rows>), dim3(sp.S, d.U), dim3(nw * 64), attend_split_lds(g, nw, sp.S), st, q, \
+                           ids, n_sel, P, sp.SP, sp.rper, after_select, d, res, d.attn_part, d.attn_arrive, out);                        \
+    } while (0)
 #define ICE_ATTEND_SPLIT(g, nw)                                                                                            \
     do {                                                                                                                   \
-        allow_dynamic_lds((const void *)attend_split_kernel<g, nw>, attend_split_lds(g, nw, S));                           \
-        hipLaunchKernelGGL((attend_split_kernel<g, nw>), dim3(S, d.U), dim3(nw * 64), attend_split_lds(g, nw, S), st, q, ids, \
-                           n_sel, P, d, d.attn_part, d.attn_arrive, out);                                                  \
+        if (res.pos) ICE_ATTEND_SPLIT_K(g, nw, kGatheredRows);                                                             \
+        else if (n_res > 0) ICE_ATTEND_SPLIT_K(g, nw, kDenseRows);                                                         \
+        else ICE_ATTEND_SPLIT_K(g, nw, kNoRows);                                                                           \
     } while (0)
         switch (d.G) {
             case 1: ICE_ATTEND_SPLIT(1, 16); break;
@@ -902,16 +952,18 @@ void launch_attend(const Dev &d, const bf16_t *q, const int *ids, const int *n_s
             default: ICE_ATTEND_SPLIT(8, 8); break;
         }
 #undef ICE_ATTEND_SPLIT
+#undef ICE_ATTEND_SPLIT_K
         return;
     }
+#define ICE_ATTEND_K(g, nw, rows, fills)                                                                                  \
+    hipLaunchKernelGGL((attend_kernel<g, nw, rows, fills>), dim3(d.U), dim3(nw * 64), sizeof(float) * attend_scratch_floats(g, nw), st, q, \
+                       ids, n_sel, P, d, res, out)
 #define ICE_ATTEND(g, nw)                                                                                                  \
     do {                                                                                                                   \
-        if (n_res > 0)                                                                                                     \
-            hipLaunchKernelGGL((attend_kernel<g, nw, true>), dim3(d.U), dim3(nw * 64),                                     \
-                               sizeof(float) * attend_scratch_floats(g, nw), st, q, ids, n_sel, P, d, res, out);           \
-        else                                                                                                               \
-            hipLaunchKernelGGL((attend_kernel<g, nw, false>), dim3(d.U), dim3(nw * 64),                                    \
-                               sizeof(float) * attend_scratch_floats(g, nw), st, q, ids, n_sel, P, d, res, out);           \
+        if (res.pos) ICE_ATTEND_K(g, nw, kGatheredRows, true);                                                             \
+        else if (n_res > 0) ICE_ATTEND_K(g, nw, kDenseRows, true);                                                         \
+        else if (attend_by_fills(d, P)) ICE_ATTEND_K(g, nw, kNoRows, true);                                                \
+        else ICE_ATTEND_K(g, nw, kNoRows, false);                                                                          \
     } while (0)
     switch (d.G) {
         case 1: ICE_ATTEND(1, 16); break;
@@ -920,6 +972,7 @@ void launch_attend(const Dev &d, const bf16_t *q, const int *ids, const int *n_s
         default: ICE_ATTEND(8, 8); break;
     }
 #undef ICE_ATTEND
+#undef ICE_ATTEND_K
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -972,9 +1025,9 @@ hipError_t launch_attend_static(const Dev &d, const bf16_t *q, const int *ids, c
     const int S = std::max(1, std::min({kStaticPairs / d.U, (P + kPagesPerShare - 1) / kPagesPerShare, fit}));
 #define ICE_ATTEND_SPLIT(g, nw)                                                                                            \
     do {                                                                                                                   \
-        allow_dynamic_lds((const void *)attend_split_kernel<g, nw>, attend_split_lds(g, nw, S));                           \
-        hipLaunchKernelGGL((attend_split_kernel<g, nw>), dim3(S, d.U), dim3(nw * 64), attend_split_lds(g, nw, S), st, q, ids, \
-                           n_sel, P, d, part, (int *)(part + kStaticPartFloats), out);                                     \
+        allow_dynamic_lds((const void *)attend_split_kernel<g, nw, kNoRows>, attend_split_lds(g, nw, S));                  \
+        hipLaunchKernelGGL((attend_split_kernel<g, nw, kNoRows>), dim3(S, d.U), dim3(nw * 64), attend_split_lds(g, nw, S), st, q, ids, \
+                           n_sel, P, S, 0, 0, d, Resident{nullptr, nullptr, 0, nullptr, nullptr, 0}, part, (int *)(part + kStaticPartFloats), out); \
     } while (0)
     switch (d.G) {
         case 1: ICE_ATTEND_SPLIT(1, 16); break;
@@ -1013,8 +1066,9 @@ hipError_t launch_attend_static(const Dev &d, const bf16_t *q, const int *ids, c
 // first 16 dwords of the kernel arguments are in scalar registers when a wave starts
 // (kernel-argument preload; structures passed by value are not eligible), the rest arrives by
 // scalar loads while the first loads are in flight.
-template <int G, int NW, int EMAX, bool RES>
-__global__ __launch_bounds__(NW * 64) void decode_step_kernel(int U, int max_pages, int P, int chunks, int np_hint, int lds_scores_off,
+// (Four waves per SIMD, i.e. two workgroups of eight waves per CU, also for G = 8 where the keys leave room for it.)
+template <int G, int NW, int EMAX, bool RES, bool FILLS>
+__global__ __launch_bounds__(NW * 64, EMAX * NW <= 64 ? 4 : 1) void decode_step_kernel(int U, int max_pages, int P, int chunks, int np_hint, int lds_scores_off,
                                                                int wait_cfg, int cand_cap, const bf16_t *__restrict__ rep_all,
                                                                const bf16_t *__restrict__ q,
                                                                const int *__restrict__ n_pages, Dev d, int *__restrict__ ids_out,
@@ -1604,7 +1658,7 @@ __global__ __launch_bounds__(NW * 64) void decode_step_kernel(int U, int max_pag
         ICE_STAMP(6);
         bf16x8 qa[4];
         SR::to_plain(qs, lane, qa);
-        attend_pages<G, NW, RES>(d, u, qa, [=](int x) { return all_pages ? x : (int)(0xFFFFFFFFu - (uint32_t)sel_comp[x]); }, k,
+        attend_pages<G, NW, RES ? kDenseRows : kNoRows, false, FILLS>(d, u, qa, [=](int x) { return all_pages ? x : (int)(0xFFFFFFFFu - (uint32_t)sel_comp[x]); }, k,
                                  res, out, (float *)region, order_ids);
         ICE_STAMP(7);
     } else {
@@ -1626,9 +1680,10 @@ int decode_step_chunks(const Dev &d, int np_hint) {
 }
 
 // the attention of a selection call as a launch of its own (few units, many pages per unit)
-bool launch_attend_would_split(const Dev &d, int P) { return attend_shares(d, P, kFusedSplitMinShares) > 1; }
-void launch_attend_split_after_select(const Dev &d, const bf16_t *q, const int *ids, const int *n_sel, int P, float *out, hipStream_t st) {
-    launch_attend(d, q, ids, n_sel, P, Resident{nullptr, nullptr, 0, nullptr, nullptr, 0}, out, st, kFusedSplitMinShares);
+bool launch_attend_would_split(const Dev &d, int P, int n_rows) { return attend_shares(d, P, n_rows, kFusedSplitMinShares).S > 1; }
+void launch_attend_split_after_select(const Dev &d, const bf16_t *q, const int *ids, const int *n_sel, int P, const Resident &res, float *out,
+                                      hipStream_t st) {
+    launch_attend(d, q, ids, n_sel, P, res, out, st, kFusedSplitMinShares, 1);
 }
 
 // Launch shape and LDS of a decode step.  LDS: the winner lists ([Pk] ids, [Pk] composites), then
@@ -1669,22 +1724,23 @@ void launch_decode_step(const Dev &d, const bf16_t *q, int P, int np_hint, int *
     const int chunks = plan.chunks;
     // few units and a large budget: select in this launch, attend with the unit's pages spread over
     // several workgroups (one more launch, see attend_split_kernel)
-    const bool split_attend = out && chunks > 1 && n_res == 0 && launch_attend_would_split(d, P);
+    const bool split_attend = out && chunks > 1 && launch_attend_would_split(d, P, n_res);
     float *out_fused = split_attend ? nullptr : out;
     const size_t lds = plan.lds;
     const int grid = round_up(d.U, 8) * chunks;
     const int E = (d.max_pages + NW * 64 - 1) / (NW * 64);
     const Resident res = {res_k, res_v, out_fused ? n_res : 0, nullptr, nullptr, 0};
-#define ICE_STEP_R(g, nw, e, r)                                                                                     \
+#define ICE_STEP_R(g, nw, e, r, f)                                                                                  \
     do {                                                                                                            \
-        allow_dynamic_lds((const void *)decode_step_kernel<g, nw, e, r>, lds);                                      \
-        hipLaunchKernelGGL((decode_step_kernel<g, nw, e, r>), dim3(grid), dim3(nw * 64), lds, st, d.U, d.max_pages, P, chunks, np_hint, \
+        allow_dynamic_lds((const void *)decode_step_kernel<g, nw, e, r, f>, lds);                                   \
+        hipLaunchKernelGGL((decode_step_kernel<g, nw, e, r, f>), dim3(grid), dim3(nw * 64), lds, st, d.U, d.max_pages, P, chunks, np_hint, \
                            plan.scores_off, wait_cfg, plan.cand_cap, d.rep, q, d.n_pages, d, ids, n_sel, scores_out, res, out_fused); \
     } while (0)
 #define ICE_STEP(g, nw, e)                                                                                          \
     do {                                                                                                            \
-        if (res.n > 0) ICE_STEP_R(g, nw, e, true);                                                                  \
-        else ICE_STEP_R(g, nw, e, false);                                                                           \
+        if (res.n > 0) ICE_STEP_R(g, nw, e, true, true);                                                            \
+        else if (e <= 16 && out_fused && attend_by_fills(d, P)) ICE_STEP_R(g, nw, e, false, (e <= 16));             \
+        else ICE_STEP_R(g, nw, e, false, false);                                                                    \
     } while (0)
     if (d.G == 8) { if (E <= 8) ICE_STEP(8, 8, 8); else if (E <= 32) ICE_STEP(8, 8, 32); else ICE_STEP(8, 8, 64); }
     else if (d.G == 4) { if (E <= 4) ICE_STEP(4, 16, 4); else if (E <= 16) ICE_STEP(4, 16, 16); else ICE_STEP(4, 16, 32); }
@@ -1692,7 +1748,7 @@ void launch_decode_step(const Dev &d, const bf16_t *q, int P, int np_hint, int *
     else { if (E <= 4) ICE_STEP(1, 16, 4); else if (E <= 16) ICE_STEP(1, 16, 16); else ICE_STEP(1, 16, 32); }
 #undef ICE_STEP
 #undef ICE_STEP_R
-    if (split_attend) launch_attend_split_after_select(d, q, ids, n_sel, P, out, st);
+    if (split_attend) launch_attend_split_after_select(d, q, ids, n_sel, P, Resident{res_k, res_v, n_res, nullptr, nullptr, 0}, out, st);
 }
 
 // largest page count launch_decode_step can serve (a unit's scores are ranked from one workgroup's registers)

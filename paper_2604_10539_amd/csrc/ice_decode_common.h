@@ -36,9 +36,9 @@ __device__ inline float dot8(const uint4 &a, const uint4 &b) {
 //            tokens {g, 4+g, 8+g, 12+g} x dims 8c..8c+7, which is exactly the B operand of eight
 //            column tiles if tile j is made of dims {8c + j} and contraction slot 4g+i stands for
 //            token 4i+g (a permutation of the sum); two byte-permutes per tile pack it.
-// The NW waves are merged by the (max, sum, output) rule.  page_of(x) names the x-th listed page;
-// `red` is LDS scratch of attend_scratch_floats() floats; aside() is work of the caller that needs
-// no barrier and runs where a wave would otherwise wait for the slowest wave's pages.
+// The NW waves are merged by the (max, sum, output) rule.  page_of(x) names the x-th listed page
+// (x differs by lane); `red` is LDS scratch of attend_scratch_floats() floats; aside() is work of the
+// caller that needs no barrier and runs where a wave would otherwise wait for the slowest wave's pages.
 __host__ __device__ constexpr int attend_scratch_floats(int G, int NW) { return NW * (G * (kD + 2) + 16 * 8); }
 
 template <int G>
@@ -139,14 +139,18 @@ struct SplitRow {
 // what a later merge needs: per head h the unnormalised sum at out[h * (kD + 2) + j], the running
 // maximum at [.. + kD] and the denominator at [.. + kD + 1] (`out` then points at the workgroup's own
 // block and `u` only addresses the pages).
-template <int G, int NW, bool RES, bool PARTIAL = false, typename PageOf, typename Aside>
+// RES: what is attended besides the pages (kNoRows, kDenseRows, kGatheredRows: see Resident).
+// FILLS: the pages' fills are fetched ahead of all but the wave's first page (one lane per page), so that rows past
+// a page's fill are not read: worth it where the bytes count (many units with several pages per wave, a window
+// beside the pages), not where a few units wait for one or two round trips (attend_by_fills).
+template <int G, int NW, int RES, bool PARTIAL, bool FILLS, typename PageOf, typename Aside>
 __device__ inline void attend_pages(const Dev &d, int u, const bf16x8 (&qa)[4], PageOf page_of, int ns, Resident res,
                                     float *__restrict__ out, float *red, Aside aside) {
     constexpr int GR = (G + 3) / 4;  // row groups that hold logits and outputs
     float(*wacc)[G][kD] = (float(*)[G][kD])red;                   // [NW][G][128]
     float(*wm)[G] = (float(*)[G])(red + NW * G * kD);             // [NW][G]
     float(*wl)[G] = (float(*)[G])(red + NW * G * (kD + 1));       // [NW][G]
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int g = lane >> 4, ch = lane & 15;
     float *px = red + NW * G * (kD + 2) + wave * (16 * 8);        // [16 tokens][8 heads] weights of this wave
     const float scale = 0.08838834764831845f;  // 1/sqrt(128)
@@ -160,17 +164,16 @@ __device__ inline void attend_pages(const Dev &d, int u, const bf16x8 (&qa)[4], 
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
     bool first = true;
-    // one 16-token block whose key pieces (kb) and value rows (vt) are in registers; tokens from
-    // nvalid on are masked
-    auto block = [&](int b0, int fill, uint4 (&kb)[4], uint4 (&vt)[4]) {
+    // one 16-token block whose key pieces (kb) and value rows (vt) are in registers, its first nv tokens
+    // (nv >= 1) taking part; next_keys() / next_values() request the next block into kb / vt
+    uint4 kb[4], vt[4];
+    auto block = [&](int nv, auto next_keys, auto next_values) __attribute__((always_inline)) {
         f32x4 z = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks)
             z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[ks], __builtin_bit_cast(bf16x8, kb[ks]), z, 0, 0, 0);
-#ifdef ICE_PROF_ATTEND
-        if (threadIdx.x == 0 && u == 0 && z[0] != 12345.f) ice::prof::stamps[9] = wall_clock64();
-#endif
-        const bool tok_ok = b0 + ch < fill;  // this lane's logits belong to token b0 + ch
+        next_keys();
+        const bool tok_ok = ch < nv;  // this lane's logits belong to token ch of the block
         float pw[4], alpha[4];
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
@@ -180,7 +183,7 @@ __device__ inline void attend_pages(const Dev &d, int u, const bf16x8 (&qa)[4], 
             mx = fmaxf(mx, dpp_f32<0x4E>(mx));
             mx = fmaxf(mx, dpp_f32<0x141>(mx));
             mx = fmaxf(mx, dpp_f32<0x140>(mx));   // block maximum of head 4g+v on all 16 lanes of the row
-            const float mn = fmaxf(m[v], mx);     // finite: every live page has at least one token
+            const float mn = fmaxf(m[v], mx);     // finite: every block has at least one token
             alpha[v] = __expf(m[v] - mn);
             pw[v] = __expf(zz - mn);
             l[v] = l[v] * alpha[v] + pw[v];
@@ -210,10 +213,10 @@ __device__ inline void attend_pages(const Dev &d, int u, const bf16x8 (&qa)[4], 
                 for (int v = 0; v < 4; ++v) acc[j][v] *= alpha[v];
         }
         first = false;
-        if (fill - b0 < 16) {  // a partly filled block: rows past the end must not reach the matrix core
+        if (nv < 16) {  // a partly filled block: rows past the end must not reach the matrix core
 #pragma unroll
             for (int t = 0; t < 4; ++t)
-                if (b0 + 4 * t + g >= fill) vt[t] = make_uint4(0, 0, 0, 0);
+                if (4 * t + g >= nv) vt[t] = make_uint4(0, 0, 0, 0);
         }
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
@@ -227,63 +230,169 @@ __device__ inline void attend_pages(const Dev &d, int u, const bf16x8 (&qa)[4], 
             acc[j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(bf16x4s, ahi), __builtin_bit_cast(bf16x4s, bv), acc[j], 0, 0, 0);
             acc[j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(bf16x4s, alo), __builtin_bit_cast(bf16x4s, bv), acc[j], 0, 0, 0);
         }
+        next_values();
         __builtin_amdgcn_wave_barrier();  // the next block overwrites px
     };
-    // the first 16-token block of a page is fetched before its fill count is known (one fewer
-    // dependent round trip); slots >= fill may hold stale bytes and are masked after the load
-    for (int x = wave; x < ns; x += NW) {
-        const int p = page_of(x);
-        if ((unsigned)p >= (unsigned)d.max_pages) continue;  // not a page id: ignored
-        const size_t pg = (size_t)u * d.max_pages + p;
-        uint4 kb[4], vt[4];
+    // a block of contiguous rows: rows from nv on are not read (row nv - 1 stands in for them)
+    auto load_keys = [&](const uint4 *rows, int nv) {
+        const uint4 *src = rows + min(ch, nv - 1) * 16 + g;
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            kb[t] = ((const uint4 *)(d.Kp + (pg * s + ch) * kD))[t * 4 + g];
-            vt[t] = ((const uint4 *)(d.Vp + (pg * s + 4 * t + g) * kD))[ch];
+        for (int t = 0; t < 4; ++t) kb[t] = src[4 * t];
+    };
+    auto load_values = [&](const uint4 *rows, int nv) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) vt[t] = (rows + min(4 * t + g, nv - 1) * 16)[ch];
+    };
+    // this wave's resident blocks: rj, rj + NW, ... below rend, dealt where the pages leave off
+    int rj = 0, rend = 0, nres = 0;
+    if constexpr (RES != kNoRows) {
+        nres = RES == kGatheredRows ? max(0, min(res.cnt[u], res.n)) : res.n;
+        rj = res.b0 + ((wave - ns) % NW + NW) % NW;
+        rend = min(res.b1, (nres + 15) >> 4);
+    }
+    if constexpr (RES == kNoRows && !FILLS) {
+        // the first 16-token block of a page is fetched before its fill count is known (one fewer
+        // dependent round trip); slots >= fill may hold stale bytes and are masked after the load
+        for (int x = tid >> 6; x < ns; x += NW) {
+            const int p = page_of(x);
+            if ((unsigned)p >= (unsigned)d.max_pages) continue;  // not a page id: ignored
+            const size_t pg = (size_t)u * d.max_pages + p;
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                kb[t] = ((const uint4 *)(d.Kp + (pg * s + ch) * kD))[t * 4 + g];
+                vt[t] = ((const uint4 *)(d.Vp + (pg * s + 4 * t + g) * kD))[ch];
+            }
+            const int fill = d.page_fill[pg];
+            ICE_STAMP(8);
+            for (int b0 = 0; b0 < fill; b0 += 16) {
+                if (b0 > 0) {
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        kb[t] = ((const uint4 *)(d.Kp + (pg * s + b0 + ch) * kD))[t * 4 + g];
+                        vt[t] = ((const uint4 *)(d.Vp + (pg * s + b0 + 4 * t + g) * kD))[ch];
+                    }
+                }
+                block(fill - b0, [] {}, [] {});
+            }
         }
-        const int fill = d.page_fill[pg];
-        ICE_STAMP(8);
-        for (int b0 = 0; b0 < fill; b0 += 16) {
-            if (b0 > 0) {
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    kb[t] = ((const uint4 *)(d.Kp + (pg * s + b0 + ch) * kD))[t * 4 + g];
-                    vt[t] = ((const uint4 *)(d.Vp + (pg * s + b0 + 4 * t + g) * kD))[ch];
+    } else if constexpr (RES != kGatheredRows) {
+        // Contiguous blocks: the pages' (16 tokens at a time), then the dense run's.  Everything that says
+        // which block comes next is the same for the whole wave.  The wave's pages are taken 64 at a time,
+        // one per lane (id, fill); `live` = those still to come that hold tokens.
+        int x0 = wave, id = -1, fl = 0, i = 0, b0 = 0, fill = 0;
+        u64 live = 0ull;
+        const uint4 *nk = nullptr, *nval = nullptr;  // the block requested next: key rows, value rows, tokens from there on
+        int nnv = 0;
+        auto tile = [&](int page, int from, int nv) {
+            const size_t row = ((size_t)u * d.max_pages + page) * s + from;
+            nk = (const uint4 *)(d.Kp + row * kD);
+            nval = (const uint4 *)(d.Vp + row * kD);
+            nnv = nv;
+        };
+        auto refill = [&] {
+            const int xl = x0 + lane * NW;
+            id = -1;
+            fl = 0;
+            if (xl < ns) id = page_of(xl);
+            if ((unsigned)id < (unsigned)d.max_pages) fl = d.page_fill[(size_t)u * d.max_pages + id];  // (not a page id: ignored)
+            live = __ballot(fl > 0);
+        };
+        auto next = [&]() -> bool {
+            if (b0 + 16 < fill) {  // this page goes on
+                b0 += 16;
+                tile(__builtin_amdgcn_readlane(id, i), b0, fill - b0);
+                return true;
+            }
+            b0 = fill = 0;
+            while (live == 0ull && x0 + 64 * NW < ns) {
+                x0 += 64 * NW;
+                refill();
+            }
+            if (live != 0ull) {
+                i = (int)__builtin_ctzll(live);
+                live &= live - 1ull;
+                fill = __builtin_amdgcn_readlane(fl, i);
+                tile(__builtin_amdgcn_readlane(id, i), 0, fill);
+                return true;
+            }
+            if constexpr (RES == kDenseRows) {
+                if (rj < rend) {
+                    const size_t row = (size_t)u * res.n + 16 * rj;
+                    nk = (const uint4 *)(res.k + row * kD);
+                    nval = (const uint4 *)(res.v + row * kD);
+                    nnv = nres - 16 * rj;
+                    rj += NW;
+                    return true;
                 }
             }
-            block(b0, fill, kb, vt);
+            return false;
+        };
+        // The first page's first block is requested before anything else, its fill included (all 16 slots are
+        // there to be read, slots past the fill are masked); the ids and fills of the others follow.
+        if (x0 < ns) {
+            id = __builtin_amdgcn_readfirstlane(page_of(x0));
+            if ((unsigned)id < (unsigned)d.max_pages) {
+                tile(id, 0, 16);
+                load_keys(nk, 16);
+                load_values(nval, 16);
+                fl = d.page_fill[(size_t)u * d.max_pages + id];
+            }
+            ICE_STAMP(8);
+            if (x0 + NW < ns) refill();
+            fill = __builtin_amdgcn_readfirstlane(fl);
+            live &= ~1ull;
+        }
+        int nv = fill;
+        bool have = fill > 0;
+        if (!have && next()) {  // (no page, or an empty one, at the head of the list)
+            have = true;
+            nv = nnv;
+            load_keys(nk, nv);
+            load_values(nval, nv);
+        }
+        while (have) {
+            if constexpr (RES == kDenseRows) {
+                // the next block's keys are requested as soon as the logits have consumed this one's, its values behind
+                // this block's value contraction
+                have = next();
+                block(nv, [&] { if (have) load_keys(nk, nnv); }, [&] { if (have) load_values(nval, nnv); });
+            } else {
+                block(nv, [] {}, [] {});
+                have = next();
+                if (have) {
+                    load_keys(nk, nnv);
+                    load_values(nval, nnv);
+                }
+            }
+            nv = nnv;
         }
     }
-    if constexpr (RES) {
-        // resident tokens, 16 per block, dealt to the waves where the pages left off; rows past the
-        // end of the run are not there to be read
-        const int nres = res.pos ? min(res.cnt[u], res.n) : res.n;
-        const int nrb = (nres + 15) >> 4;
-        for (int j = ((wave - ns) % NW + NW) % NW; j < nrb; j += NW) {
-            const int r0 = 16 * j, fill = min(16, nres - r0);
-            uint4 kb[4], vt[4];
-            if (!res.pos) {
-                const bf16_t *ktile = res.k + ((size_t)u * res.n + r0) * kD;
-                const bf16_t *vtile = res.v + ((size_t)u * res.n + r0) * kD;
+    if constexpr (RES == kGatheredRows) {
+        // Gathered rows: a block's 16 positions sit on lanes ch, the next block's are fetched while this one is
+        // worked on.  List entries past the unit's count are read (the list has res.n of them) and not used.
+        const int *pl = res.pos + (size_t)u * res.n;
+        const uint4 *kbase = (const uint4 *)(res.k + (size_t)u * res.rows * kD), *vbase = (const uint4 *)(res.v + (size_t)u * res.rows * kD);
+        auto position = [&](int j) { return min(max(pl[min(16 * j + ch, res.n - 1)], 0), res.rows - 1); };
+        auto gather_keys = [&](int row) {
+            const uint4 *src = kbase + (size_t)row * 16 + g;
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    kb[t] = ch < fill ? ((const uint4 *)(ktile + (size_t)ch * kD))[t * 4 + g] : make_uint4(0, 0, 0, 0);
-                    vt[t] = 4 * t + g < fill ? ((const uint4 *)(vtile + (size_t)(4 * t + g) * kD))[ch] : make_uint4(0, 0, 0, 0);
-                }
-            } else {
-                const int *pl = res.pos + (size_t)u * res.n + r0;
-                const int krow = ch < fill ? min(max(pl[ch], 0), res.rows - 1) : 0;
-                int vrow[4];
+            for (int t = 0; t < 4; ++t) kb[t] = src[4 * t];
+        };
+        auto gather_values = [&](int row) {
 #pragma unroll
-                for (int t = 0; t < 4; ++t) vrow[t] = 4 * t + g < fill ? min(max(pl[4 * t + g], 0), res.rows - 1) : 0;
-                const bf16_t *kbase = res.k + (size_t)u * res.rows * kD, *vbase = res.v + (size_t)u * res.rows * kD;
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    kb[t] = ch < fill ? ((const uint4 *)(kbase + (size_t)krow * kD))[t * 4 + g] : make_uint4(0, 0, 0, 0);
-                    vt[t] = 4 * t + g < fill ? ((const uint4 *)(vbase + (size_t)vrow[t] * kD))[ch] : make_uint4(0, 0, 0, 0);
-                }
+            for (int t = 0; t < 4; ++t) vt[t] = (vbase + (size_t)__shfl(row, 4 * t + g) * 16)[ch];
+        };
+        if (rj < rend) {
+            int row = position(rj);
+            gather_keys(row);
+            gather_values(row);
+            int row1 = position(rj + NW);
+            for (; rj + NW < rend; rj += NW) {
+                row = row1;
+                row1 = position(rj + 2 * NW);
+                block(nres - 16 * rj, [&] { gather_keys(row); }, [&] { gather_values(row); });
             }
-            block(0, fill, kb, vt);
+            block(nres - 16 * rj, [] {}, [] {});
         }
     }
     ICE_STAMP(10);

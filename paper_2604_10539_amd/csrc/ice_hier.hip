@@ -237,7 +237,8 @@ __host__ __device__ inline HierLds hier_lds(int Cpad, int max_pages, int n_probe
 // scalar registers at wave start; cent_all = the centroid rows in use.)
 // TOP: three levels (a stage in front that ranks the top nodes; compiled apart so that the two-level
 // instantiations keep their register budget).
-template <int G, int NW, int EMAX, bool TOP>
+// FILLS: see attend_pages.
+template <int G, int NW, int EMAX, bool TOP, bool FILLS>
 __global__ __launch_bounds__(NW * 64) void decode_hier_kernel(int Cpad, int max_pages, int np_hint, int P, int n_probe, int n_refine,
                                                                const bf16_t *__restrict__ cent_all, const bf16_t *__restrict__ q,
                                                                const int *__restrict__ page_cluster, const int *__restrict__ n_pages, Dev d,
@@ -581,7 +582,7 @@ __global__ __launch_bounds__(NW * 64) void decode_hier_kernel(int Cpad, int max_
     };
     bf16x8 qa[4];
     if (out) SR::to_plain(qs, lane, qa);
-    if (out) attend_pages<G, NW, false>(d, u, qa, [=](int x) { return (int)(0xFFFFFFFFu - (uint32_t)win[x]); }, k, Resident{nullptr, nullptr, 0, nullptr, nullptr, 0}, out, red, order_ids);
+    if (out) attend_pages<G, NW, kNoRows, false, FILLS>(d, u, qa, [=](int x) { return (int)(0xFFFFFFFFu - (uint32_t)win[x]); }, k, Resident{nullptr, nullptr, 0, nullptr, nullptr, 0}, out, red, order_ids);
     else order_ids();
     ICE_HSTAMP(7);
 }
@@ -599,23 +600,26 @@ void launch_decode_hier(const Dev &d, const bf16_t *q, int cur, int P, int n_top
     // few units and many pages: the attention moves to a launch of its own that spreads a unit's pages
     // over several workgroups (see attend_split_kernel)
     float *out_split = nullptr;
-    if (out && launch_attend_would_split(d, P)) {
+    if (out && launch_attend_would_split(d, P, 0)) {
         out_split = out;
         out = nullptr;
     }
     if (np_hint > d.max_pages) np_hint = d.max_pages;
     const int E = (d.max_pages + NW * 64 - 1) / (NW * 64);
-#define ICE_HIER_T(g, nw, e, top)                                                                                    \
+    // half the chip's CUs busy: the attention is bound by its bytes, and rows past a page's fill are not read (128
+    // units x 16 pages: 25.0 us per call without, 24.3 with); few units wait for the fills
+    const bool fills = d.U >= 128;
+#define ICE_HIER_T(g, nw, e, top, fills)                                                                             \
     do {                                                                                                             \
-        allow_dynamic_lds((const void *)decode_hier_kernel<g, nw, e, top>, lds);                                     \
-        hipLaunchKernelGGL((decode_hier_kernel<g, nw, e, top>), dim3(d.U), dim3(nw * 64), lds, st, d.Cpad, d.max_pages, np_hint, P, \
+        allow_dynamic_lds((const void *)decode_hier_kernel<g, nw, e, top, fills>, lds);                              \
+        hipLaunchKernelGGL((decode_hier_kernel<g, nw, e, top, fills>), dim3(d.U), dim3(nw * 64), lds, st, d.Cpad, d.max_pages, np_hint, P, \
                            n_probe, n_refine, d.cent_bf16[cur], q, d.page_cluster, d.n_pages, d, ids, n_sel, scores_out,   \
                            clusters_out, out, n_top, n_probe_top, tops_out);                                         \
     } while (0)
 #define ICE_HIER(g, nw, e)                                                                                           \
     do {                                                                                                             \
-        if (n_top > 0) ICE_HIER_T(g, nw, e, true);                                                                   \
-        else ICE_HIER_T(g, nw, e, false);                                                                            \
+        if (n_top > 0) { if (fills) ICE_HIER_T(g, nw, e, true, true); else ICE_HIER_T(g, nw, e, true, false); }      \
+        else { if (fills) ICE_HIER_T(g, nw, e, false, true); else ICE_HIER_T(g, nw, e, false, false); }              \
     } while (0)
     if (d.G == 8) { if (E <= 8) ICE_HIER(8, 8, 8); else ICE_HIER(8, 8, 32); }
     else if (d.G == 4) { if (E <= 4) ICE_HIER(4, 16, 4); else ICE_HIER(4, 16, 16); }
@@ -623,7 +627,7 @@ void launch_decode_hier(const Dev &d, const bf16_t *q, int cur, int P, int n_top
     else { if (E <= 4) ICE_HIER(1, 16, 4); else ICE_HIER(1, 16, 16); }
 #undef ICE_HIER
 #undef ICE_HIER_T
-    if (out_split) launch_attend_split_after_select(d, q, ids, n_sel, P, out_split, st);
+    if (out_split) launch_attend_split_after_select(d, q, ids, n_sel, P, Resident{nullptr, nullptr, 0, nullptr, nullptr, 0}, out_split, st);
 }
 
 // largest page count per unit the kernel serves (page -> cluster entries held in registers)

@@ -79,6 +79,7 @@ struct Host {
     Dev dev;
     bool laid_out;   // dev pointers valid for (s, C)
     bool built;
+    bool armed;      // the arrival counters of the split attention have been zeroed under this layout
     int n_tokens;    // per unit
     int build_n;     // tokens per unit of the last ice_build_index (0: none, or the index was imported)
     int n_top;       // nodes of the level above the clusters (0: not built)
@@ -142,24 +143,29 @@ DecodePlan decode_step_plan(const Dev &d, int P, int np_hint);
 //   gathered  rows pos[u][0 .. cnt[u]) of a whole cache k, v bf16 [U][rows][d] (token positions
 //             chosen elsewhere, e.g. by another layer's selection, App. B); n is then the length of
 //             a unit's position list.  Positions outside [0, rows) are clamped into the cache.
+enum { kNoRows = 0, kDenseRows = 1, kGatheredRows = 2 };  // which of the two forms a kernel is compiled for
 struct Resident {
     const bf16_t *k, *v;
     int n;
     const int *pos;
     const int *cnt;
     int rows;
+    int b0 = 0, b1 = 1 << 30;  // the 16-token blocks of the run or list that the workgroup takes
 };
 
+// min_shares: workgroups' worth of pages per unit from which they are split; may_split false: never; after_select: it follows the selection of the
+// same call, a unit that could not be selected (negative n_sel) gets zeros
 void launch_attend(const Dev &d, const bf16_t *q, const int *ids_or_null, const int *n_sel, int P, const Resident &res,
-                   float *out, hipStream_t st, int min_shares = 4);
+                   float *out, hipStream_t st, int min_shares = 4, int after_select = 0,
+                   bool may_split = true);
 // the same attention with the shares' partial results in the library's own static device array
 // (no workspace region involved); at most attend_static_max_units() units
 hipError_t launch_attend_static(const Dev &d, const bf16_t *q, const int *ids, const int *n_sel, int P, float *out,
                                 hipStream_t st);
 int attend_static_max_units();
-bool launch_attend_would_split(const Dev &d, int P);  // few units, many pages: a selection call attends in a launch of its own
-void launch_attend_split_after_select(const Dev &d, const bf16_t *q, const int *ids, const int *n_sel, int P, float *out,
-                                      hipStream_t st);
+bool launch_attend_would_split(const Dev &d, int P, int n_rows);  // few units, many pages: a selection call attends in a launch of its own
+void launch_attend_split_after_select(const Dev &d, const bf16_t *q, const int *ids, const int *n_sel, int P, const Resident &res,
+                                      float *out, hipStream_t st);
 void launch_selected_tokens(const Dev &d, const int *ids, const int *n_sel, int P, int *pos_out, int *n_tok_out,
                             hipStream_t st);
 

@@ -120,3 +120,117 @@ def test_pages_hold_the_members_in_ascending_position(U, n, C, s, lump):
         assert t == cnt0 % s and e2["page_fill"][u, p] == t + 1 and e2["cluster_cnt"][u, c] == cnt0 + 1
         old = ex["page_sum"][u, p] if t else np.zeros(D, np.float32)
         assert np.array_equal(e2["page_sum"][u, p], old + widen(k1[0, u]))
+
+
+def _attention_rows(q, k, v):
+    """softmax(q k^T / sqrt(d)) v in 64 bits: q [G, D], k, v [m, D]."""
+    z = q @ k.T / np.sqrt(D)
+    p = np.exp(z - z.max(1, keepdims=True))
+    return (p / p.sum(1, keepdims=True)) @ v
+
+
+def _listed_rows(ex, u, ids, n):
+    """Keys and values of the tokens of a unit's first n listed pages."""
+    ks, vs = [np.empty((0, D))], [np.empty((0, D))]
+    for p in ids[:max(n, 0)]:
+        f = ex["page_fill"][u, p]
+        ks.append(widen(ex["Kp"][u, p, :f]).astype(np.float64))
+        vs.append(widen(ex["Vp"][u, p, :f]).astype(np.float64))
+    return np.concatenate(ks), np.concatenate(vs)
+
+
+# The output is a mean of N(0, 1) values: weights in two bf16 terms (2^-16 relative each, at most a few hundred tokens of
+# weight below one) and fp32 sums stay below 2e-4 of a value of magnitude about 4.
+ATTEND_TOL = 2e-4
+
+
+@pytest.mark.parametrize("U,G,s,budget,n_res", [
+    (2, 4, 16, 512, 512),     # split: pages' and rows' shares, none of them ragged
+    (2, 4, 16, 560, 497),     # ragged shares of both
+    (1, 8, 64, 64, 400),      # one page, many row shares
+    (3, 2, 32, 1600, 16),     # many pages, one row share
+    (33, 1, 16, 512, 700),    # too many units to split
+    (4, 4, 16, 256, 1),       # too little to split
+    (130, 4, 16, 640, 0),     # fills fetched ahead, no rows
+])
+def test_attention_split_over_workgroups_with_rows_beside_the_pages(U, G, s, budget, n_res):
+    """select_attend_resident and attend_resident on both sides of the rules that split the attention, whole lists
+    and lists cut short."""
+    from paper_2604_10539_amd import IceIndex
+    w = datagen.small(n_tokens=2600, n_clusters=40, n_kv_heads=U, group_size=G, page_size=s, n_components=16)
+    K, V = datagen.keys_values(w)
+    ix = IceIndex(1, U, G, 2600, s, 40, kmeans_iters=1, init_idx=up(datagen.init_indices(w)))
+    ix.build_index(up(K), up(V))
+    rng = np.random.default_rng(U + n_res)
+    rk = narrow(rng.standard_normal((1, U, max(n_res, 1), D)).astype(np.float32))[:, :, :n_res].copy()
+    rv = narrow(rng.standard_normal((1, U, max(n_res, 1), D)).astype(np.float32))[:, :, :n_res].copy()
+    q = datagen.queries(w)
+    if n_res:
+        ids, n_sel, out = ix.select_attend_resident(up(q), budget, up(rk), up(rv))
+    else:
+        ids, n_sel, out = ix.select_attend(up(q), budget)
+    ex = {k: down(v) for k, v in ix.export().items() if k != "view"}
+    n_cut = n_sel.clone()
+    n_cut[0, ::2] = 3
+    n_cut[0, U // 2] = 0 if n_res else 1
+    cut = ix.attend_resident(up(q), ids, n_cut, up(rk), up(rv)) if n_res else ix.attend(up(q), ids, n_cut)
+    qf = widen(q).astype(np.float64).reshape(U, G, D)
+    for u in range(U):
+        for got, n in ((out, n_sel), (cut, n_cut)):
+            k, v = _listed_rows(ex, u, down(ids)[0, u], int(n[0, u]))
+            k = np.concatenate([k, widen(rk[0, u]).astype(np.float64)])
+            v = np.concatenate([v, widen(rv[0, u]).astype(np.float64)])
+            assert np.abs(down(got).reshape(U, G, D)[u] - _attention_rows(qf[u], k, v)).max() <= ATTEND_TOL
+
+
+@pytest.mark.parametrize("U,G,max_tok,built", [(1, 4, 1, True), (2, 8, 512, True), (8, 4, 513, True), (5, 1, 250, True), (40, 2, 300, True),
+                                                (2, 4, 600, False)])
+def test_attention_by_position_split_over_workgroups(U, G, max_tok, built):
+    """Gathered rows on both sides of the split, lists that end anywhere (also at once), and on an index that was laid
+    out but never built (whose workspace holds anything)."""
+    from paper_2604_10539_amd import IceIndex
+    n = 1500
+    w = datagen.small(n_tokens=n, n_clusters=24, n_kv_heads=U, group_size=G)
+    K, V = datagen.keys_values(w)
+    ix = IceIndex(1, U, G, n, 16, 24, kmeans_iters=1, init_idx=up(datagen.init_indices(w)))
+    ix.workspace.fill_(0x5A)
+    if built:
+        ix.build_index(up(K), up(V))
+    else:
+        ix.debug_assign(up(K), up(K[0, :, :24]))
+    rng = np.random.default_rng(max_tok)
+    pos = np.stack([rng.permutation(n)[:max_tok] for _ in range(U)])[None].astype(np.int32)
+    n_tok = rng.integers(0, max_tok + 1, (1, U)).astype(np.int32)
+    n_tok[0, 0] = max_tok
+    if U > 1:
+        n_tok[0, 1] = 0
+    for u in range(U):
+        pos[0, u, n_tok[0, u]:] = -1
+    q = datagen.queries(w)
+    qf = widen(q).astype(np.float64).reshape(U, G, D)
+    for _ in range(2):  # (the second call finds what the first left behind)
+        out = down(ix.attend_tokens(up(q), up(K), up(V), up(pos), up(n_tok))).reshape(U, G, D)
+        for u in range(U):
+            p = pos[0, u, :n_tok[0, u]]
+            ref = _attention_rows(qf[u], widen(K[0, u, p]).astype(np.float64), widen(V[0, u, p]).astype(np.float64)) if len(p) else np.zeros((G, D))
+            assert np.abs(out[u] - ref).max() <= ATTEND_TOL
+
+
+def test_unit_whose_selection_failed_gets_zeros_with_a_window_too():
+    """The attention of a selection call that moved to a launch of its own leaves the failed unit's output zero, as the
+    fused one does, although there are rows to attend to."""
+    from paper_2604_10539_amd import IceIndex
+    from paper_2604_10539_amd.binding import ice_debug_select_fault
+    w = datagen.small(n_tokens=8000, n_clusters=100, n_kv_heads=2)
+    K, V = datagen.keys_values(w)
+    ix = IceIndex(1, 2, 4, 8000, 16, 100, kmeans_iters=1, init_idx=up(datagen.init_indices(w)))
+    ix.build_index(up(K), up(V))
+    q, rows = up(datagen.queries(w)), up(K[:, :, :600])
+    for budget, n_res in ((256, 16), (512, 600)):  # fused, split
+        ids, n_sel, good = ix.select_attend_resident(q, budget, rows[:, :, :n_res].contiguous(), rows[:, :, :n_res].contiguous())
+        assert int(n_sel.min()) == budget // 16 and float(good.abs().max()) > 0
+    ids, n_sel = ix._sel_buffers(256)
+    ice_debug_select_fault(ix.handle, q, 256, ids, n_sel, None, 0, 2)
+    for budget, n_res in ((256, 16), (512, 600)):
+        ids, n_sel, out = ix.select_attend_resident(q, budget, rows[:, :, :n_res].contiguous(), rows[:, :, :n_res].contiguous())
+        assert int(n_sel.max()) == -1 and int(ids.max()) == -1 and float(out.abs().max()) == 0.0
