@@ -129,8 +129,15 @@ def _ptr(t) -> int | None:
     return t.data_ptr()
 
 
+# address of a device's current stream without building a Stream object around it (0.3 us against 3.8 per call,
+# a third of what a one-layer step costs the host); None where this torch has no such getter
+_raw_current_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> int | None:
     if stream is None:
+        if _raw_current_stream is not None and torch.cuda.is_initialized():
+            return _raw_current_stream(torch.cuda.current_device())
         return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else None
     return stream if isinstance(stream, int) else stream.cuda_stream
 
