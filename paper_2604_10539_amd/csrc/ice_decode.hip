@@ -23,7 +23,7 @@ constexpr int kUnitFailed = -(1 << 30);        // arrival counter of a unit whos
 // launches leaves the same bits.  The cluster then moves (ordered fp32: sum -> centroid -> bf16 row
 // and squared norm) and the row is appended to the cluster's tail page (page sum -> representative).
 constexpr int kInsertWaves = 16;
-constexpr int kInsertTokens = 16;  // tokens per launch of the batched kernel at most (one per wave)
+constexpr int kInsertTokens = 16;  // tokens per round of the batched kernel at most (one per wave)
 
 __device__ inline float insert_objective(float w, float dot, float kaf, float ce) {
     return __builtin_fmaf(-2.0f, __builtin_fmaf(kaf, ce, dot), w);
@@ -172,7 +172,7 @@ __device__ inline void insert_read_tile(const char *stg, int lane, uint4 (&b)[4]
 // (cent, cnorm: the live centroid buffer d.cent_bf16[cur] / d.cnorm[cur], which this kernel also
 // writes, hence neither const nor restrict)
 __global__ __launch_bounds__(kInsertWaves * 64) void insert_one_kernel(const bf16_t *__restrict__ k, const bf16_t *__restrict__ v,
-                                                                        bf16_t *cent, float *cnorm, int m_total, int t0, int cur,
+                                                                        bf16_t *cent, float *cnorm, int cur,
                                                                         int C, int Cpad, int tk_arg, Dev d_arg) {  // (scalars first: preloaded)
     extern __shared__ __align__(16) char insert_stage[];  // [16 waves][2 tiles]
     __shared__ u64 s_best;
@@ -181,7 +181,7 @@ __global__ __launch_bounds__(kInsertWaves * 64) void insert_one_kernel(const bf1
     char *stg = insert_stage + wave * 2 * kInsertTileBytes;
     const bf16_t *cb = cent + (size_t)u * Cpad * kD;
     const float *wn = cnorm + (size_t)u * Cpad;
-    const bf16_t *ku = k + ((size_t)u * m_total + t0) * kD, *vu = v + ((size_t)u * m_total + t0) * kD;
+    const bf16_t *ku = k + (size_t)u * kD, *vu = v + (size_t)u * kD;
     ICE_STAMP(40);
     if (tid == 0) s_best = ~0ull;
     const int tiles = (C + 15) / 16;
@@ -311,7 +311,10 @@ __global__ __launch_bounds__(kInsertWaves * 64) void insert_one_kernel(const bf1
 //            order and writes the representative; the tables follow.
 // Worst case: all tokens of a launch crowd into a few clusters, and the settle step handles them one
 // after the other (about 3 us each on one wave).
-// k, v: bf16 [U, m_total, d], tokens t0 .. t0 + mt of them in this launch.
+// More tokens than the tables hold (`per`: 16, fewer when the clusters are many) are taken in rounds by the same
+// workgroup: bound by the steps' latencies, a round saves the launch, the start of 16 waves and the argument loads of
+// a launch per 16 tokens (32 units, 128 clusters, 200 tokens: 163 us in 13 launches, 127 in one).
+// k, v: bf16 [U, m_total, d].
 __host__ __device__ inline int insert_row_stride(int C) { return round_up(C, 16) + 4; }  // (+4: the four token groups of a store hit different banks)
 // dynamic LDS: D [mt][stride], norms [Cr] (+ extras [Cr]), the tokens' keys and moved rows [16][64] words each,
 // per slot the cluster sum before and after the guessed move and the tail page's sum [16][64] float2 each
@@ -320,7 +323,7 @@ __host__ __device__ inline size_t insert_fixed_lds(int C, bool tk) {
 }
 
 __global__ __launch_bounds__(kInsertWaves * 64) void insert_batch_kernel(const bf16_t *__restrict__ k, const bf16_t *__restrict__ v,
-                                                                          bf16_t *cent, float *cnorm, int m_total, int t0, int mt,
+                                                                          bf16_t *cent, float *cnorm, int m_total, int per,
                                                                           int cur, int C, int Cpad, int stage_tiles, int tk_arg,
                                                                           Dev d_arg) {  // (scalars first: preloaded)
     extern __shared__ __align__(16) char insert_lds[];
@@ -335,41 +338,51 @@ __global__ __launch_bounds__(kInsertWaves * 64) void insert_batch_kernel(const b
     __shared__ int s_fail[kInsertTokens];                       // bit t': token t's guess fails if token t' < t moves as it guessed
     __shared__ int s_stood;                                     // bit t: token t's guessed move stands (wave t stores it); bit 16: every token went where it guessed
     __shared__ int t_cluster[2][kInsertTokens], t_page[2][kInsertTokens], t_slot[2][kInsertTokens], t_src[2][kInsertTokens], t_pages[2];  // page_table
-    const int u = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int g = lane >> 4, i = lane & 15;
+    const int u = blockIdx.x;
+    int tid = threadIdx.x;
     const int Cr = round_up(C, 16), Cs = insert_row_stride(C);
-    char *stg = insert_lds + wave * stage_tiles * kInsertTileBytes;  // this wave's staging area (first in LDS: placed by preloaded arguments alone)
+    char *stg = insert_lds + (tid >> 6) * stage_tiles * kInsertTileBytes;  // this wave's staging area (first in LDS: placed by preloaded arguments alone)
     const bf16_t *cb = cent + (size_t)u * Cpad * kD;
     const float *wn = cnorm + (size_t)u * Cpad;
-    const bf16_t *ku = k + ((size_t)u * m_total + t0) * kD, *vu = v + ((size_t)u * m_total + t0) * kD;
+    const bf16_t *ku = k + (size_t)u * m_total * kD, *vu = v + (size_t)u * m_total * kD;  // the tokens at hand
+    int mt = min(per, m_total);
 
     // ---- scan (the tile loads go out first; the small tables are staged while they are in flight)
     ICE_STAMP(32);
     const int tiles = Cr / 16;
-    if (wave < tiles) {
-        insert_stage_tile(cb, wave, stg, lane);
-        if (stage_tiles == 2 && wave + kInsertWaves < tiles) insert_stage_tile(cb, wave + kInsertWaves, stg + kInsertTileBytes, lane);
-    }
     bf16x8 ka[4];  // A operand: row i = token i, lane (g, i) holds its dims [32 ks + 8 g, +8)
+    auto request = [&] {
+        const int wave = tid >> 6, lane = tid & 63, g = lane >> 4, i = lane & 15;
+        if (wave < tiles) {
+            insert_stage_tile(cb, wave, stg, lane);
+            if (stage_tiles == 2 && wave + kInsertWaves < tiles) insert_stage_tile(cb, wave + kInsertWaves, stg + kInsertTileBytes, lane);
+        }
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {  // (a load under a condition, not a choice between two addresses: no zero constant in memory)
-        uint4 w = make_uint4(0, 0, 0, 0);
-        if (i < mt) w = ((const uint4 *)(ku + (size_t)i * kD))[ks * 4 + g];
-        ka[ks] = __builtin_bit_cast(bf16x8, w);
-    }
+        for (int ks = 0; ks < 4; ++ks) {  // (a load under a condition, not a choice between two addresses: no zero constant in memory)
+            uint4 w = make_uint4(0, 0, 0, 0);
+            if (i < mt) w = ((const uint4 *)(ku + (size_t)i * kD))[ks * 4 + g];
+            ka[ks] = __builtin_bit_cast(bf16x8, w);
+        }
+    };
+    request();
     // The other arguments are fetched here, once, while tiles and keys are on their way.
     const bool tk = tk_arg != 0;
     Dev d;
     bf16_t *caug_cur;
     pin_insert_fields(d, d_arg, cur, caug_cur);
     float *Dl = (float *)(insert_lds + kInsertWaves * stage_tiles * kInsertTileBytes);
-    float *lw = Dl + (size_t)mt * Cs;
+    float *lw = Dl + (size_t)mt * Cs;  // (the first round is the longest)
     float *lce = lw + Cr;
     uint32_t *lkey = (uint32_t *)(lce + (tk ? Cr : 0));
     uint32_t *lrow = lkey + kInsertTokens * 64;  // [t][64]: the bf16 row token t's move forms (a B operand is read back from it)
     float2 *s_cs = (float2 *)(lrow + kInsertTokens * 64);  // slot t: the guessed cluster's sum as it stands
     float2 *s_cs1 = s_cs + kInsertTokens * 64;             // ... and after token t's guessed move
     float2 *s_ps = s_cs1 + kInsertTokens * 64;             // ... and its tail page's sum before this launch
+    for (int t0 = 0;;) {
+    // (opaque to the compiler in every round: hoisted out of the loop, the lanes' addresses would not fit the registers)
+    asm volatile("" : "+v"(tid));
+    const int wave = tid >> 6, lane = tid & 63;
+    const int g = lane >> 4, i = lane & 15;
     uint32_t vw = 0;
     if (wave < mt) {
         lkey[wave * 64 + lane] = ((const uint32_t *)(ku + (size_t)wave * kD))[lane];
@@ -718,6 +731,18 @@ __global__ __launch_bounds__(kInsertWaves * 64) void insert_batch_kernel(const b
         }
     }
     ICE_STAMP(55);
+    // ---- the next tokens: what this round stored is read back by this workgroup, whose waves share a vector
+    // cache, once every wave's stores are done
+    t0 += mt;
+    if (t0 >= m_total) break;
+    ku += (size_t)mt * kD;
+    vu += (size_t)mt * kD;
+    mt = min(mt, m_total - t0);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __threadfence_block();
+    __syncthreads();
+    request();
+    }
 }
 
 void launch_insert(const Dev &d, const bf16_t *k, const bf16_t *v, int m, int cur, hipStream_t st) {
@@ -725,21 +750,19 @@ void launch_insert(const Dev &d, const bf16_t *k, const bf16_t *v, int m, int cu
     const size_t budget = 156u * 1024u, stage1 = (size_t)kInsertWaves * kInsertTileBytes;
     const size_t fixed = insert_fixed_lds(d.C, d.tk != 0), row = (size_t)insert_row_stride(d.C) * 4;
     const int cap = (int)std::min<size_t>(kInsertTokens, (budget - fixed - stage1) / row);  // >= 1 up to 8192 clusters
-    const size_t one_lds = 2 * stage1;
-    for (int t0 = 0; t0 < m; t0 += std::max(cap, 1)) {
-        const int mt = std::min(std::max(cap, 1), m - t0);
-        if (mt == 1) {
-            allow_dynamic_lds((const void *)insert_one_kernel, one_lds);
-            hipLaunchKernelGGL(insert_one_kernel, dim3(d.U), dim3(kInsertWaves * 64), one_lds, st, k, v, d.cent_bf16[cur], d.cnorm[cur], m,
-                               t0, cur, d.C, d.Cpad, d.tk, d);
-            continue;
-        }
-        const int stage_tiles = fixed + mt * row + 2 * stage1 <= budget ? 2 : 1;
-        const size_t lds = fixed + mt * row + stage_tiles * stage1;
-        allow_dynamic_lds((const void *)insert_batch_kernel, lds);
-        hipLaunchKernelGGL(insert_batch_kernel, dim3(d.U), dim3(kInsertWaves * 64), lds, st, k, v, d.cent_bf16[cur], d.cnorm[cur], m, t0,
-                           mt, cur, d.C, d.Cpad, stage_tiles, d.tk, d);
+    if (m == 1) {
+        const size_t one_lds = 2 * stage1;
+        allow_dynamic_lds((const void *)insert_one_kernel, one_lds);
+        hipLaunchKernelGGL(insert_one_kernel, dim3(d.U), dim3(kInsertWaves * 64), one_lds, st, k, v, d.cent_bf16[cur], d.cnorm[cur], cur, d.C,
+                           d.Cpad, d.tk, d);
+        return;
     }
+    const int per = std::max(1, std::min(cap, m));
+    const int stage_tiles = fixed + per * row + 2 * stage1 <= budget ? 2 : 1;
+    const size_t lds = fixed + per * row + stage_tiles * stage1;
+    allow_dynamic_lds((const void *)insert_batch_kernel, lds);
+    hipLaunchKernelGGL(insert_batch_kernel, dim3(d.U), dim3(kInsertWaves * 64), lds, st, k, v, d.cent_bf16[cur], d.cnorm[cur], m, per, cur, d.C,
+                       d.Cpad, stage_tiles, d.tk, d);
 }
 
 // ------------------------------------------------------------------------------------------------

@@ -234,3 +234,32 @@ def test_unit_whose_selection_failed_gets_zeros_with_a_window_too():
     for budget, n_res in ((256, 16), (512, 600)):
         ids, n_sel, out = ix.select_attend_resident(q, budget, rows[:, :, :n_res].contiguous(), rows[:, :, :n_res].contiguous())
         assert int(n_sel.max()) == -1 and int(ids.max()) == -1 and float(out.abs().max()) == 0.0
+
+
+@pytest.mark.parametrize("m,C,s,tk", [(2, 20, 16, 0), (16, 20, 16, 0), (17, 20, 16, 1), (33, 300, 64, 0), (100, 20, 16, 1), (21, 5000, 16, 0)])
+def test_insertions_in_rounds_equal_single_ones(m, C, s, tk):
+    """A call takes as many tokens at a time as its tables hold (16, fewer with many clusters) and reads back what it
+    stored: remainders of one token, rows moved and pages opened in one round and used in the next."""
+    from paper_2604_10539_amd import IceIndex
+    n, U = max(700, C), 3
+    w = datagen.small(n_tokens=n, n_clusters=C, n_kv_heads=U, n_components=6, page_size=s)
+    K, V = datagen.keys_values(w)
+    new = narrow((widen(K[:, :, :1]) + 0.4 * np.random.default_rng(m).standard_normal((1, U, m, D))).astype(np.float32))  # they crowd
+    new[:, :, 1::3] = K[:, :, 5:5 + len(range(1, m, 3))]
+    state = []
+    for batch in (True, False):
+        ix = IceIndex(1, U, 4, n + m, s, C, kmeans_iters=1, init_idx=up(datagen.init_indices(w)), geometry=tk)
+        ix.workspace.zero_()
+        ix.build_index(up(K), up(V))
+        if batch:
+            ix.insert_batch(up(new), up(new[:, :, ::-1]))
+        else:
+            for t in range(m):
+                ix.insert(up(new[:, :, t]), up(new[:, :, ::-1][:, :, t]))
+        ex = {k: down(v).copy() for k, v in ix.export().items() if k not in ("view", "assign")}
+        if tk:
+            ex.update({k: down(v).copy() for k, v in ix.export_geometry().items()})
+        state.append(ex)
+    for name in state[0]:
+        if name not in ("assign_centroid_bf16", "assign_centroid_extra_bf16"):
+            assert np.array_equal(state[0][name], state[1][name]), name
