@@ -263,3 +263,60 @@ def test_insertions_in_rounds_equal_single_ones(m, C, s, tk):
     for name in state[0]:
         if name not in ("assign_centroid_bf16", "assign_centroid_extra_bf16"):
             assert np.array_equal(state[0][name], state[1][name]), name
+
+
+@pytest.mark.parametrize("P,s", [(1, 16), (2, 64), (63, 16), (128, 16), (129, 32), (1024, 64)])
+def test_positions_of_listed_pages(P, s):
+    """The positions in list and slot order, padded with -1: lists up to the longest, cut short, empty, with entries that
+    are not page ids."""
+    from paper_2604_10539_amd import IceIndex
+    w = datagen.small(n_tokens=5000, n_clusters=60, n_kv_heads=3, page_size=s)
+    K, V = datagen.keys_values(w)
+    ix = IceIndex(1, 3, 4, 5000, s, 60, kmeans_iters=1, init_idx=up(datagen.init_indices(w)))
+    ix.build_index(up(K), up(V))
+    ex = {k: down(v) for k, v in ix.export().items() if k != "view"}
+    rng = np.random.default_rng(P)
+    ids = np.stack([rng.integers(0, ex["n_pages"][u], P) for u in range(3)])[None].astype(np.int32)
+    ids[0, 0, P // 2] = ex["page_fill"].shape[1] + 5
+    n_sel = np.array([[P, max(P - 1, 0), 0]], np.int32)
+    pos, n_tok = ix.selected_tokens(up(ids), up(n_sel))
+    pos, n_tok = down(pos), down(n_tok)
+    for u in range(3):
+        want = [t for p in ids[0, u, :n_sel[0, u]] if 0 <= p < ex["page_fill"].shape[1] for t in ex["page_pos"][u, p, :ex["page_fill"][u, p]]]
+        assert n_tok[0, u] == len(want)
+        assert np.array_equal(pos[0, u], np.array(want + [-1] * (P * s - len(want))))
+
+
+@pytest.mark.parametrize("kw,odd", [(dict(n_tokens=1000, n_clusters=33), False), (dict(n_tokens=1000, n_clusters=33), True),
+                                    (dict(n_tokens=70, n_clusters=3, n_kv_heads=1, page_size=64), False)])
+def test_imports_in_one_launch_and_through_copies(kw, odd):
+    """Both forms of an import (odd: one array at an address the single launch does not take) leave the caller's arrays,
+    and insertion and selection work on what they derived."""
+    from paper_2604_10539_amd import IceIndex
+    from paper_2604_10539_amd.binding import IMPORT_FIELDS
+    import torch
+    w = datagen.small(**kw)
+    U, s, C, n = w.n_kv_heads, w.page_size, w.n_clusters, w.n_tokens
+    K, V = datagen.keys_values(w)
+    make = lambda: IceIndex(1, U, 4, n + 40, s, C, kmeans_iters=2, init_idx=up(datagen.init_indices(w)))
+    a = make()
+    a.build_index(up(K), up(V))
+    arrays = {f: a.export()[f].clone() for f in IMPORT_FIELDS}
+    if odd:
+        t = arrays["n_pages"]
+        buf = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)
+        buf[1:] = t
+        arrays["n_pages"] = buf[1:]
+    b = make()
+    b.workspace.fill_(0x33)
+    b.import_arrays(arrays, n)
+    for f in IMPORT_FIELDS:
+        assert torch.equal(b.export()[f], arrays[f]), f
+    k1, q = up(K[:, :, :20].copy()), up(datagen.queries(w))
+    for ix in (a, b):
+        ix.insert_batch(k1, k1)
+    (ia, na, oa), (ib, nb, ob) = (ix.select_attend(q, 4 * s) for ix in (a, b))
+    assert torch.equal(ia, ib) and torch.equal(na, nb) and torch.equal(oa, ob)
+    ea, eb = a.export(), b.export()
+    for f in ("page_fill", "page_pos", "cluster_cnt", "cluster_sum", "centroid", "cluster_tail", "n_pages"):
+        assert torch.equal(ea[f], eb[f]), f
