@@ -127,6 +127,34 @@ ice_status_t device_status(const char *what) {
     return ICE_OK;
 }
 
+// whether every array is 16-byte aligned device memory of the GPU that holds `ws`, which is the current one, and lies
+// inside its allocation
+bool all_on_device(const void *const *p, const size_t *bytes, int n, const void *ws) {
+    int dev = -1;
+    hipPointerAttribute_t at;
+    if (hipGetDevice(&dev) != hipSuccess || hipPointerGetAttributes(&at, ws) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (at.type != hipMemoryTypeDevice || at.device != dev) return false;
+    for (int i = 0; i < n; ++i) {
+        if (!aligned16(p[i])) return false;
+        if (hipPointerGetAttributes(&at, p[i]) != hipSuccess) {
+            (void)hipGetLastError();  // (not an error of the call: the copy calls decide)
+            return false;
+        }
+        if (at.type != hipMemoryTypeDevice || at.device != dev) return false;
+        hipDeviceptr_t base = nullptr;
+        size_t size = 0;
+        if (hipMemGetAddressRange(&base, &size, const_cast<void *>(p[i])) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        if ((size_t)(static_cast<const char *>(p[i]) - static_cast<const char *>(base)) + bytes[i] > size) return false;
+    }
+    return true;
+}
+
 __global__ void fill_i32_kernel(int *p, int n, int v) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v;
@@ -499,30 +527,30 @@ ice_status_t ice_import_index(ice_index_t *ix, const ice_index_view_t *v, void *
     hipStream_t s = static_cast<hipStream_t>(stream);
     const Dev &d = ix->dev;
     const size_t U = d.U, MP = d.max_pages, C = d.C, ps = d.s;
-    hipError_t e = hipSuccess;
-    auto copy = [&](void *dst, const void *src, size_t bytes) {
-        if (e == hipSuccess) e = hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, s);
-    };
-    copy(d.Kp, v->Kp, U * MP * ps * kD * 2);
-    copy(d.Vp, v->Vp, U * MP * ps * kD * 2);
-    copy(d.page_cluster, v->page_cluster, U * MP * 4);
-    copy(d.page_fill, v->page_fill, U * MP * 4);
-    copy(d.page_pos, v->page_pos, U * MP * ps * 4);
-    copy(d.cluster_tail, v->cluster_tail, U * C * 4);
-    copy(d.cluster_cnt, v->cluster_cnt, U * C * 4);
-    copy(d.cluster_sum, v->cluster_sum, U * C * kD * 4);
-    copy(d.centroid, v->centroid, U * C * kD * 4);
-    copy(d.page_sum, v->page_sum, U * MP * kD * 4);
-    copy(d.rep, v->rep, U * MP * kD * 2);
-    copy(d.n_pages, v->n_pages, U * 4);
-    if (e != hipSuccess) return fail(ICE_ERR_DEVICE, "ice_import_index: %s", hipGetErrorString(e));
-    reset_decode_state(d, v->n_tokens, s);
+    const void *src[12] = {v->Kp, v->Vp, v->page_sum, v->rep, v->page_pos, v->cluster_sum, v->centroid, v->page_cluster, v->page_fill,
+                           v->cluster_tail, v->cluster_cnt, v->n_pages};
+    void *dst[12] = {d.Kp, d.Vp, d.page_sum, d.rep, d.page_pos, d.cluster_sum, d.centroid, d.page_cluster, d.page_fill,
+                     d.cluster_tail, d.cluster_cnt, d.n_pages};
+    const size_t bytes[12] = {U * MP * ps * kD * 2, U * MP * ps * kD * 2, U * MP * kD * 4, U * MP * kD * 2, U * MP * ps * 4, U * C * kD * 4,
+                              U * C * kD * 4, U * MP * 4, U * MP * 4, U * C * 4, U * C * 4, U * 4};
+    // One launch when all arrays are aligned memory of the workspace's own GPU; anything else a copy call
+    // takes (another GPU's memory, pinned or managed memory, an odd address) or refuses (an array that ends
+    // before its size) goes through copy calls.
+    if (all_on_device(src, bytes, 12, ix->ws)) {
+        launch_import(d, src, dst, bytes, *v, s);
+    } else {
+        for (int i = 0; i < 12; ++i) {
+            const hipError_t e = hipMemcpyAsync(dst[i], src[i], bytes[i], hipMemcpyDeviceToDevice, s);
+            if (e != hipSuccess) return fail(ICE_ERR_DEVICE, "ice_import_index: %s", hipGetErrorString(e));
+        }
+        reset_decode_state(d, v->n_tokens, s);
+        launch_refresh_centroids(d, 0, s);
+        launch_refresh_centroids(d, 1, s);
+        launch_refresh_tails(d, s);
+    }
     ix->cur = 0;
     ix->geometry = 0;  // (an imported index carries no extra coordinate)
     ix->dev.tk = 0;
-    launch_refresh_centroids(d, 0, s);
-    launch_refresh_centroids(d, 1, s);
-    launch_refresh_tails(d, s);
     if (ice_status_t st = device_status("ice_import_index")) return st;
     ix->n_tokens = v->n_tokens;
     ix->build_n = 0;  // (not the product of a build here: no stage to re-run)

@@ -196,6 +196,110 @@ void launch_refresh_tails(const Dev &d, hipStream_t st) {
     hipLaunchKernelGGL(refresh_tails_kernel, dim3((d.C + 3) / 4, d.U), dim3(256), 0, st, d);
 }
 
+// An import in one launch: the caller's arrays are copied, what is derived from them is formed from the
+// caller's copies beside that (the centroids' bf16 rounding and squared norms for both buffers, the tail
+// pages' state), and the decode state is set.  Bound by the copy; apart, twelve copies and seven small
+// launches cost their start-up and drain each (32 units x 8392 tokens, 400 MB read and written: 81 us in one launch
+// where a turn of 200 tokens took 252 us with them apart and 221 with this).
+// Blocks [0, copy_blocks) copy 32 KB each, the next cluster_blocks take four clusters each (one wave per
+// cluster), the rest the score slots and the units' counters.
+constexpr int kImportArrays = 12, kImportChunk = 32768;
+struct ImportArgs {
+    const char *src[kImportArrays];
+    char *dst[kImportArrays];
+    size_t bytes[kImportArrays];
+    unsigned first[kImportArrays];  // first copy block of the array
+    const float *centroid, *page_sum;
+    const int *cluster_tail, *page_fill;
+    unsigned copy_blocks, cluster_blocks;
+    int n_tokens;
+};
+__global__ __launch_bounds__(256) void import_kernel(Dev d, ImportArgs a) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    unsigned blk = blockIdx.x;
+    if (blk < a.copy_blocks) {
+        int x = 0;
+#pragma unroll
+        for (int i = 1; i < kImportArrays; ++i) x = blk >= a.first[i] ? i : x;
+        const size_t at = (size_t)(blk - a.first[x]) * kImportChunk, left = a.bytes[x] - at;
+        const uint4 *src = (const uint4 *)(a.src[x] + at);
+        uint4 *dst = (uint4 *)(a.dst[x] + at);
+        if (left >= (size_t)kImportChunk) {
+            uint4 w[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) w[i] = src[i * 256 + tid];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) dst[i * 256 + tid] = w[i];
+        } else {
+            const int n16 = (int)(left / 16), n4 = (int)(left / 4);
+            for (int i = tid; i < n16; i += 256) dst[i] = src[i];
+            for (int i = n16 * 4 + tid; i < n4; i += 256) ((uint32_t *)dst)[i] = ((const uint32_t *)src)[i];
+        }
+        return;
+    }
+    blk -= a.copy_blocks;
+    if (blk < a.cluster_blocks) {
+        const unsigned row = blk * 4 + (tid >> 6);
+        if (row >= (unsigned)d.U * d.Cpad) return;
+        const int u = (int)(row / d.Cpad), c = (int)(row % d.Cpad);
+        if (c >= d.C) {
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                ((uint32_t *)(d.cent_bf16[b] + (size_t)row * kD))[lane] = 0u;
+                if (lane == 0) d.cnorm[b][row] = INFINITY;
+            }
+            return;
+        }
+        const size_t cl = (size_t)u * d.C + c;
+        const float2 m = ((const float2 *)(a.centroid + cl * kD))[lane];
+        const int tail = a.cluster_tail[cl];
+        const bf16_t b0 = f32_to_bf16(m.x), b1 = f32_to_bf16(m.y);
+        const float lo = bf16_to_f32(b0), hi = bf16_to_f32(b1);
+        const float nn = wave_sum(lo * lo + hi * hi);
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            ((uint32_t *)(d.cent_bf16[b] + (size_t)row * kD))[lane] = (uint32_t)b0 | ((uint32_t)b1 << 16);
+            if (lane == 0) d.cnorm[b][row] = nn;
+        }
+        float2 ps = make_float2(0.f, 0.f);
+        int fill = d.s;
+        if (tail >= 0 && tail < d.max_pages) {
+            const size_t pg = (size_t)u * d.max_pages + tail;
+            fill = a.page_fill[pg];
+            ps = ((const float2 *)(a.page_sum + pg * kD))[lane];
+        }
+        ((float2 *)(d.tail_sum + cl * kD))[lane] = ps;
+        if (lane == 0) d.tail_fill[cl] = fill;
+        return;
+    }
+    const size_t i = ((size_t)(blk - a.cluster_blocks) * 256 + tid) * 4, ns = (size_t)d.U * d.max_pages;
+    if (i + 4 <= ns) {
+        ((uint4 *)d.scores)[i / 4] = make_uint4(~0u, ~0u, ~0u, ~0u);
+    } else {
+        for (size_t x = i; x < ns; ++x) d.scores[x] = ~0u;
+    }
+    const size_t u = i / 4;
+    if (u < (size_t)d.U) { d.n_tokens[u] = a.n_tokens; d.counter[u] = 0; d.attn_arrive[u] = 0; }
+}
+
+void launch_import(const Dev &d, const void *const *src, void *const *dst, const size_t *bytes, const ice_index_view_t &v, hipStream_t st) {
+    ImportArgs a;
+    unsigned blocks = 0;
+    for (int i = 0; i < kImportArrays; ++i) {
+        a.src[i] = (const char *)src[i];
+        a.dst[i] = (char *)dst[i];
+        a.bytes[i] = bytes[i];
+        a.first[i] = blocks;
+        blocks += (unsigned)((bytes[i] + kImportChunk - 1) / kImportChunk);
+    }
+    a.centroid = v.centroid; a.page_sum = v.page_sum; a.cluster_tail = v.cluster_tail; a.page_fill = v.page_fill;
+    a.copy_blocks = blocks;
+    a.cluster_blocks = (unsigned)(((size_t)d.U * d.Cpad + 3) / 4);
+    a.n_tokens = v.n_tokens;
+    const size_t state = std::max<size_t>(((size_t)d.U * d.max_pages + 3) / 4, (size_t)d.U);  // one thread per four score slots and per unit
+    hipLaunchKernelGGL(import_kernel, dim3(a.copy_blocks + a.cluster_blocks + (unsigned)((state + 255) / 256)), dim3(256), 0, st, d, a);
+}
+
 __global__ void fill_u64_kernel(u64 *p, size_t n, u64 v) {
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = v;
 }

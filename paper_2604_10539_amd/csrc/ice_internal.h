@@ -107,6 +107,8 @@ void launch_means(const Dev &d, const bf16_t *K, int n, int cur, hipStream_t st)
 void launch_paginate(const Dev &d, const bf16_t *K, const bf16_t *V, int n, bool arm, hipStream_t st);
 void launch_refresh_centroids(const Dev &d, int cur, hipStream_t st);
 void launch_refresh_tails(const Dev &d, hipStream_t st);  // tail_fill / tail_sum from the page tables (after an import)
+// copies the arrays of an import (12 of them, 16-byte aligned device memory of this GPU) and sets everything derived, in one launch
+void launch_import(const Dev &d, const void *const *src, void *const *dst, const size_t *bytes, const ice_index_view_t &v, hipStream_t st);
 void launch_insert(const Dev &d, const bf16_t *k, const bf16_t *v, int m, int cur, hipStream_t st);
 // scores + top-P selection (+ attention when out != nullptr) in one launch
 // np_hint: host-side upper bound of the live pages per unit (tokens / page_size + clusters)
