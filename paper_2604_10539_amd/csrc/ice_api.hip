@@ -98,7 +98,7 @@ size_t lay_out(const ice_config_t &cfg, int s, int C, char *base, Dev *out) {
     d.packed = (unsigned long long *)take(U * MT * 8);
     d.order = (int *)take(U * MT * 4);
     d.page_base = (int *)take(U * C * 4);
-    d.range_off = (uint32_t *)take(sort_ranges_max(d.U, d.max_tokens) * CP * 4);
+    d.range_off = (uint32_t *)take(sort_ranges_max(d.U, d.max_tokens, d.Cpad) * CP * 4);
     d.attn_part = (float *)take((size_t)256 * d.G * (kD + 2) * 4);
     d.attn_arrive = (int *)take(U * 4);
     d.scores = (uint32_t *)take(U * MP * 4);

@@ -674,21 +674,31 @@ void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, bool clear, hi
 // segment's counter of that cluster past all of them, and a token's rank among its cluster's
 // members of the segment stays in its register.  The counters are then scanned over segments and
 // clusters and every token's slot is counter + rank.  W x Cpad counters of 4 bytes fit 144 KB.
-constexpr int kSortMaxLen = 4096;  // tokens per range at most
-constexpr int kSortCounters = 36864;
+constexpr int kSortCounters = 36864, kSortMaxSeg = 2048;  // LDS counters; tokens per segment at most
 
-int sort_range_len(int U, int n) {
+static int sort_segments(int Cpad) {
+    int W = 16;
+    while (W * Cpad > kSortCounters) W /= 2;  // (Cpad <= 8192: W >= 4)
+    return W;
+}
+static int sort_max_len(int Cpad) { return sort_segments(Cpad) * kSortMaxSeg; }
+int sort_range_len(int U, int n, int Cpad) {
     // short ranges keep the chip busy, few ranges keep the reading of their pieces short: at most 64 per
-    // unit and one workgroup per CU unless even the longest ranges are more
+    // unit and one workgroup per CU unless even the longest ranges are more (256 units x 32768 tokens: ranges
+    // of 4096 85 us and the means 449, one range 69 and 427; a sort over the whole unit with the same cost took 64 and 407)
     int L = 1024;
-    while (L < kSortMaxLen && ((n + L - 1) / L > 64 || (long long)U * ((n + L - 1) / L) > 256)) L *= 2;
+    while (L < sort_max_len(Cpad) && L < n && ((n + L - 1) / L > 64 || (long long)U * ((n + L - 1) / L) > 256)) L *= 2;
     return L;
 }
-size_t sort_ranges_max(int U, int max_tokens) {
-    return std::max<size_t>(256, (size_t)U * ((max_tokens + kSortMaxLen - 1) / kSortMaxLen));
+size_t sort_ranges_max(int U, int max_tokens, int Cpad) {
+    const int L = sort_max_len(Cpad);
+    return std::max<size_t>(std::max(256, U), (size_t)U * (((size_t)max_tokens + L - 1) / L));
 }
 
-template <int NG>  // groups of 64 tokens per wave at most
+// NG: groups of 64 tokens per wave at most.  MASK: the lanes of a group with the same cluster meet in a 64-bit lane mask per
+// cluster in LDS (OR, read back, clear) instead of by ballots: cheaper per group, but the masks have to be cleared and
+// take 8 more bytes per counter, so it is for long ranges (256 units x 32768 tokens: 78 us with ballots, 69 so).
+template <int NG, bool MASK>
 __global__ __launch_bounds__(1024) void range_sort_kernel(Dev d, int n, int L, int W, int nbits, int clear, float *best_out,
                                                           int *assign_out) {
     extern __shared__ __align__(16) int pos_all[];  // [W][Cpad]
@@ -707,31 +717,39 @@ __global__ __launch_bounds__(1024) void range_sort_kernel(Dev d, int n, int L, i
         const int i = beg + j * 64 + lane;
         v[j] = i < end ? pk[2 * i] : 0u;
     }
-    for (int x = tid; x < W * Cpad / 4; x += 1024) ((int4 *)pos_all)[x] = make_int4(0, 0, 0, 0);  // (Cpad is a multiple of 32)
+    for (int x = tid; x < W * Cpad / 4 * (MASK ? 3 : 1); x += 1024) ((int4 *)pos_all)[x] = make_int4(0, 0, 0, 0);  // (Cpad is a multiple of 32)
     if (tid == 0) carry = 0;
     __syncthreads();
     // ---- rank inside the segment (row `wave` of the counters is this wave's alone)
     int *pos = pos_all + (wave < W ? wave : 0) * Cpad;
+    u64 *mask = (u64 *)(pos_all + W * Cpad) + (size_t)(wave < W ? wave : 0) * Cpad;  // (MASK)
     const u64 lt = (1ull << lane) - 1ull;
-    int cl[NG], rank[NG];
 #pragma unroll
-    for (int j = 0; j < NG; ++j) {
+    for (int j = 0; j < NG; ++j) {  // v[j]: from here on cluster << 16 | rank
         const int i = beg + j * 64 + lane;
         const bool valid = i < end;
         // (always < Cpad for finite keys; clamped so that no input can send a counter out of range)
         const int a = (int)min(0xFFFFFFFFu - v[j], (uint32_t)Cpad - 1u);
-        cl[j] = a;
-        rank[j] = 0;
+        v[j] = (uint32_t)a << 16;
         if (beg + j * 64 >= end) continue;  // (wave-uniform)
-        u64 peers = __ballot(valid);
-        for (int b = 0; b < nbits; ++b) {
-            const bool bit = (a >> b) & 1;
-            const u64 m = __ballot(bit);
-            peers &= bit ? m : ~m;
+        u64 peers;
+        if constexpr (MASK) {
+            if (valid) atomicOr(&mask[a], 1ull << lane);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            peers = valid ? mask[a] : 0ull;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (valid) mask[a] = 0ull;
+        } else {
+            peers = __ballot(valid);
+            for (int b = 0; b < nbits; ++b) {
+                const bool bit = (a >> b) & 1;
+                const u64 m = __ballot(bit);
+                peers &= bit ? m : ~m;
+            }
         }
         if (valid) {
             const int base = pos[a];
-            rank[j] = base + (int)__popcll(peers & lt);
+            v[j] |= (uint32_t)(base + (int)__popcll(peers & lt));
             if ((peers & lt) == 0ull) pos[a] = base + (int)__popcll(peers);
             d.assign[(size_t)u * d.max_tokens + i] = a;
             if (assign_out) assign_out[(size_t)u * n + i] = a;
@@ -761,7 +779,7 @@ __global__ __launch_bounds__(1024) void range_sort_kernel(Dev d, int n, int L, i
         int ex = carry + incl - tot;
         for (int w = 0; w < wave; ++w) ex += wsum[w];
         if (c < Cpad) {
-            off[c] = (uint32_t)ex << 16 | (uint32_t)tot;  // (both at most kSortMaxLen)
+            off[c] = (uint32_t)ex << 16 | (uint32_t)tot;  // (both at most 32768)
             int run = ex;
 #pragma unroll
             for (int w = 0; w < 16; ++w) {
@@ -778,24 +796,25 @@ __global__ __launch_bounds__(1024) void range_sort_kernel(Dev d, int n, int L, i
 #pragma unroll
     for (int j = 0; j < NG; ++j) {
         const int i = beg + j * 64 + lane;
-        if (i < end) order[pos[cl[j]] + rank[j]] = i;
+        if (i < end) order[pos[v[j] >> 16] + (int)(v[j] & 0xFFFFu)] = i;
     }
 }
 
 void launch_sort(const Dev &d, int n, bool clear, float *best_out, int *assign_out, hipStream_t st) {
-    const int L = sort_range_len(d.U, n), R = (n + L - 1) / L;
-    int W = 16, nbits = 0;
-    while (W * d.Cpad > kSortCounters) W /= 2;  // (Cpad <= 8192: W >= 4)
+    const int L = sort_range_len(d.U, n, d.Cpad), R = (n + L - 1) / L, W = sort_segments(d.Cpad);
+    int nbits = 0;
     while ((1 << nbits) < d.Cpad) ++nbits;
-    const size_t lds = (size_t)W * d.Cpad * 4;
+    const bool masks = L / W > 4 * 64 && W * d.Cpad * 3 <= kSortCounters;
+    const size_t lds = (size_t)W * d.Cpad * (masks ? 12 : 4);
     clear = clear && assign_slices(d) > 1;
-#define ICE_SORT(ng)                                                                                                       \
+#define ICE_SORT(ng, mk)                                                                                                   \
     do {                                                                                                                   \
-        allow_dynamic_lds((const void *)range_sort_kernel<ng>, lds);                                                       \
-        hipLaunchKernelGGL(range_sort_kernel<ng>, dim3(R, d.U), dim3(1024), lds, st, d, n, L, W, nbits, clear ? 1 : 0, best_out, assign_out); \
+        allow_dynamic_lds((const void *)range_sort_kernel<ng, mk>, lds);                                                   \
+        hipLaunchKernelGGL((range_sort_kernel<ng, mk>), dim3(R, d.U), dim3(1024), lds, st, d, n, L, W, nbits, clear ? 1 : 0, best_out, assign_out); \
     } while (0)
-    if (L / W <= 4 * 64) ICE_SORT(4);
-    else ICE_SORT(16);
+    if (L / W <= 4 * 64) ICE_SORT(4, false);
+    else if (L / W <= 16 * 64) { if (masks) ICE_SORT(16, true); else ICE_SORT(16, false); }
+    else { if (masks) ICE_SORT(32, true); else ICE_SORT(32, false); }
 #undef ICE_SORT
 }
 
@@ -827,7 +846,7 @@ __device__ inline int wave_scan_add(int x) {
 // One wave fills pre[0..R) and at[0..R) of cluster c and returns the number of members (to every lane).  With
 // `slots` the members' indexes into `order` go to slots[0..kMemberSlots) as well, piece by piece, as long as
 // no piece has more than kMemberPiece of them (*listed): one read per member instead of a search.
-constexpr int kMemberSlots = 512, kMemberPiece = 32;
+constexpr int kMemberSlots = 512, kMemberPiece = 32, kFewPieces = 4;
 __device__ inline int member_ranges(const uint32_t *off, int Cpad, int R, int L, int c, int lane, int *pre, int *at, int *slots, bool *listed) {
     int total = 0;
     bool ok = slots != nullptr;
@@ -870,18 +889,45 @@ __global__ __launch_bounds__(256) void means_kernel(Dev d, const bf16_t *__restr
     const int u = blockIdx.y, c = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int g = lane >> 4, ch = lane & 15;
     const MemberList search = {d.order + (size_t)u * d.max_tokens, lists, lists + R, R};
-    if (wave == 0) {
-        bool listed;
-        const int m = member_ranges(d.range_off + (size_t)u * R * d.Cpad, d.Cpad, R, L, c, lane, lists, lists + R, slots, &listed);
-        if (lane == 0) {
-            sh_cnt = m;
-            sh_listed = listed;
-            d.cluster_cnt[(size_t)u * d.C + c] = m;
+    // Up to four pieces (many units) every wave reads by itself, a choice per member; more of them the first wave
+    // lays out in LDS for all.  (256 units x 32768 tokens, one piece: means 449 us through LDS, 427 without.)
+    const uint32_t *off = d.range_off + (size_t)u * R * d.Cpad;
+    const bool few = R <= kFewPieces;
+    int before[kFewPieces], from[kFewPieces], cnt = 0;
+    bool listed = false;
+    if (few) {
+#pragma unroll
+        for (int r = 0; r < kFewPieces; ++r) {
+            const uint32_t o = r < R ? off[(size_t)r * d.Cpad + c] : 0u;
+            before[r] = cnt;
+            from[r] = r * L + (int)(o >> 16);
+            cnt += (int)(o & 0xFFFFu);
         }
+        if (threadIdx.x == 0) d.cluster_cnt[(size_t)u * d.C + c] = cnt;
+    } else {
+        if (wave == 0) {
+            bool ok;
+            const int m = member_ranges(off, d.Cpad, R, L, c, lane, lists, lists + R, slots, &ok);
+            if (lane == 0) {
+                sh_cnt = m;
+                sh_listed = ok;
+                d.cluster_cnt[(size_t)u * d.C + c] = m;
+            }
+        }
+        lds_barrier();
+        cnt = sh_cnt;
+        listed = sh_listed != 0;
     }
-    lds_barrier();
-    const int cnt = sh_cnt;
-    const bool listed = sh_listed != 0;
+    auto member = [&](int j) -> int {
+        if (few) {
+            int at = from[0] + j;
+#pragma unroll
+            for (int r = 1; r < kFewPieces; ++r)
+                if (r < R && j >= before[r]) at = from[r] + j - before[r];
+            return search.order[at];
+        }
+        return listed ? search.order[slots[j]] : search(j);
+    };
     const bf16_t *Ku = K + (size_t)u * n * kD;
     const int quarter = (cnt + 3) / 4;
     const int lo = min(cnt, wave * quarter), hi = min(cnt, lo + quarter);
@@ -893,7 +939,7 @@ __global__ __launch_bounds__(256) void means_kernel(Dev d, const bf16_t *__restr
     // once, so a wave keeps 8 KB of key rows in flight instead of one dependent load pair per step.
     for (int base = lo; base < hi; base += 64) {
         int mine = -1;
-        if (base + lane < hi) mine = listed ? search.order[slots[base + lane]] : search(base + lane);
+        if (base + lane < hi) mine = member(base + lane);
         const int rows = min(64, hi - base);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -922,7 +968,7 @@ __global__ __launch_bounds__(256) void means_kernel(Dev d, const bf16_t *__restr
     // order by the first wave, requested before the waves meet
     float aug_part = 0.f;
     if (d.tk && wave == 0)
-        for (int r = lane; r < cnt; r += 64) aug_part += bf16_to_f32(d.kaug[(size_t)u * d.max_tokens + (listed ? search.order[slots[r]] : search(r))]);
+        for (int r = lane; r < cnt; r += 64) aug_part += bf16_to_f32(d.kaug[(size_t)u * d.max_tokens + member(r)]);
     if (wave > 0 && g == 0) {
         part_sum[wave - 1][ch][0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
         part_sum[wave - 1][ch][1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
@@ -980,7 +1026,7 @@ __global__ __launch_bounds__(256) void means_kernel(Dev d, const bf16_t *__restr
 }
 
 void launch_means(const Dev &d, const bf16_t *K, int n, int cur, hipStream_t st) {
-    const int L = sort_range_len(d.U, n), R = (n + L - 1) / L;
+    const int L = sort_range_len(d.U, n, d.Cpad), R = (n + L - 1) / L;
     const size_t lds = (size_t)R * 8;
     if (keys_exceed_cache(d, n)) hipLaunchKernelGGL(means_kernel<true>, dim3(d.C, d.U), dim3(256), lds, st, d, K, n, cur, R, L);
     else hipLaunchKernelGGL(means_kernel<false>, dim3(d.C, d.U), dim3(256), lds, st, d, K, n, cur, R, L);
@@ -1106,7 +1152,7 @@ __global__ __launch_bounds__(256) void paginate_kernel(Dev d, const bf16_t *__re
 }
 
 void launch_paginate(const Dev &d, const bf16_t *K, const bf16_t *V, int n, bool arm, hipStream_t st) {
-    const int L = sort_range_len(d.U, n), R = (n + L - 1) / L;
+    const int L = sort_range_len(d.U, n, d.Cpad), R = (n + L - 1) / L;
     const size_t lds = (size_t)4 * d.s * kD * 2 + (size_t)4 * R * 8;
     hipLaunchKernelGGL(layout_kernel, dim3(d.U), dim3(1024), (size_t)(d.C + 1) * 4, st, d, n, arm ? 1 : 0);
 #define ICE_PAGINATE(stream)                                                                                               \

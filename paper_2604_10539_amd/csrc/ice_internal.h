@@ -101,7 +101,7 @@ void launch_load_centroids(const Dev &d, const bf16_t *cent, int cur, hipStream_
 void launch_key_aug(const Dev &d, const bf16_t *K, int n, hipStream_t st);
 void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, bool clear, hipStream_t st);
 void launch_sort(const Dev &d, int n, bool clear, float *best_out_or_null, int *assign_out_or_null, hipStream_t st);
-size_t sort_ranges_max(int U, int max_tokens);  // (unit, range) pairs of any sort of at most max_tokens tokens
+size_t sort_ranges_max(int U, int max_tokens, int Cpad);  // (unit, range) pairs of any sort of at most max_tokens tokens
 void launch_means(const Dev &d, const bf16_t *K, int n, int cur, hipStream_t st);
 // arm: also the decode state of a fresh index (token counters, arrival counters, empty score slots)
 void launch_paginate(const Dev &d, const bf16_t *K, const bf16_t *V, int n, bool arm, hipStream_t st);
