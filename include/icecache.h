@@ -193,8 +193,8 @@ ice_status_t ice_select_attend_resident(ice_index_t *idx, const void *q, int32_t
  *       n_tok int32 [B, H_kv].  n_ids_per_unit in [1, 1024].
  *   ice_attend_tokens    attention (Eq. 1) of q over rows token_pos[b, h, 0 .. n_tok[b, h]) of a
  *       dense cache K, V bf16 [B, H_kv, n_rows, d] (any layer's; caller-owned device memory);
- *       max_tok = length of a unit's position list.  The index only supplies B, H_kv and the group
- *       size (STATE before a build or import).  Positions must lie in [0, n_rows) (others are
+ *       max_tok = length of a unit's position list.  The index supplies B, H_kv, the group size and
+ *       scratch in its workspace, not its tables (STATE before a build or import).  Positions must lie in [0, n_rows) (others are
  *       clamped into the cache, not skipped).
  * With the cache the index was built from, ice_attend_tokens over ice_selected_tokens' positions
  * gives ice_attend's result over those pages. */

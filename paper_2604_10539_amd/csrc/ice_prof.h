@@ -18,7 +18,6 @@ static __device__ long long unit_stamps[4 * 1024];
 // decode kernels: thread 0 of unit 0 (`u` in scope); per unit: start, end of scoring, of selection, end
 #define ICE_STAMP(i) do { if (threadIdx.x == 0 && u == 0) ice::prof::stamps[i] = wall_clock64(); } while (0)
 #define ICE_USTAMP(i) do { if (threadIdx.x == 0 && u < 1024) ice::prof::unit_stamps[4 * u + (i)] = wall_clock64(); } while (0)
-#define ICE_PROF_ATTEND 1
 // build kernels: thread 0 of workgroup (0, *, 0); per wave of that workgroup for tile 1
 #define ICE_BSTAMP(i) do { if (threadIdx.x == 0 && blockIdx.x == 0 && blockIdx.z == 0) ice::prof::stamps[i] = wall_clock64(); } while (0)
 #define ICE_WSTAMP(t, i) do { if ((t) == 1 && (threadIdx.x & 63) == 0 && blockIdx.x == 0 && blockIdx.z == 0) { ice::prof::wave_stamps[(threadIdx.x >> 6) * 8 + (i)] = wall_clock64(); ice::prof::wave_stamps[64 + (threadIdx.x >> 6) * 8 + (i)] = clock64(); } } while (0)
