@@ -172,7 +172,7 @@ __device__ inline void insert_read_tile(const char *stg, int lane, uint4 (&b)[4]
 // (cent, cnorm: the live centroid buffer d.cent_bf16[cur] / d.cnorm[cur], which this kernel also
 // writes, hence neither const nor restrict)
 __global__ __launch_bounds__(kInsertWaves * 64) void insert_one_kernel(const bf16_t *__restrict__ k, const bf16_t *__restrict__ v,
-                                                                        bf16_t *cent, float *cnorm, int cur,
+                                                                        bf16_t *cent, float *cnorm, int m_total, int t0, int cur,
                                                                         int C, int Cpad, int tk_arg, Dev d_arg) {  // (scalars first: preloaded)
     extern __shared__ __align__(16) char insert_stage[];  // [16 waves][2 tiles]
     __shared__ u64 s_best;
@@ -181,7 +181,7 @@ __global__ __launch_bounds__(kInsertWaves * 64) void insert_one_kernel(const bf1
     char *stg = insert_stage + wave * 2 * kInsertTileBytes;
     const bf16_t *cb = cent + (size_t)u * Cpad * kD;
     const float *wn = cnorm + (size_t)u * Cpad;
-    const bf16_t *ku = k + (size_t)u * kD, *vu = v + (size_t)u * kD;
+    const bf16_t *ku = k + ((size_t)u * m_total + t0) * kD, *vu = v + ((size_t)u * m_total + t0) * kD;
     ICE_STAMP(40);
     if (tid == 0) s_best = ~0ull;
     const int tiles = (C + 15) / 16;
@@ -379,369 +379,369 @@ __global__ __launch_bounds__(kInsertWaves * 64) void insert_batch_kernel(const b
     float2 *s_cs1 = s_cs + kInsertTokens * 64;             // ... and after token t's guessed move
     float2 *s_ps = s_cs1 + kInsertTokens * 64;             // ... and its tail page's sum before this launch
     for (int t0 = 0;;) {
-    // (opaque to the compiler in every round: hoisted out of the loop, the lanes' addresses would not fit the registers)
-    asm volatile("" : "+v"(tid));
-    const int wave = tid >> 6, lane = tid & 63;
-    const int g = lane >> 4, i = lane & 15;
-    uint32_t vw = 0;
-    if (wave < mt) {
-        lkey[wave * 64 + lane] = ((const uint32_t *)(ku + (size_t)wave * kD))[lane];
-        vw = ((const uint32_t *)(vu + (size_t)wave * kD))[lane];
-    }
-    for (int r = tid; r < Cr; r += kInsertWaves * 64) {
-        lw[r] = r < C ? wn[r] : INFINITY;
-        if (tk) lce[r] = r < C ? bf16_to_f32(caug_cur[(size_t)u * Cpad + r]) : 0.f;
-    }
-    auto store_dots = [&](const f32x4 &acc, int tile) {
+        // (opaque to the compiler in every round: hoisted out of the loop, the lanes' addresses would not fit the registers)
+        asm volatile("" : "+v"(tid));
+        const int wave = tid >> 6, lane = tid & 63;
+        const int g = lane >> 4, i = lane & 15;
+        uint32_t vw = 0;
+        if (wave < mt) {
+            lkey[wave * 64 + lane] = ((const uint32_t *)(ku + (size_t)wave * kD))[lane];
+            vw = ((const uint32_t *)(vu + (size_t)wave * kD))[lane];
+        }
+        for (int r = tid; r < Cr; r += kInsertWaves * 64) {
+            lw[r] = r < C ? wn[r] : INFINITY;
+            if (tk) lce[r] = r < C ? bf16_to_f32(caug_cur[(size_t)u * Cpad + r]) : 0.f;
+        }
+        auto store_dots = [&](const f32x4 &acc, int tile) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            if (4 * g + j < mt) Dl[(size_t)(4 * g + j) * Cs + tile * 16 + i] = acc[j];
-    };
-    for (int tile = wave; tile < tiles; tile += stage_tiles * kInsertWaves) {
-        const int tb = tile + kInsertWaves;
-        const bool two = stage_tiles == 2 && tb < tiles;
-        if (tile != wave) {
-            insert_stage_tile(cb, tile, stg, lane);
-            if (two) insert_stage_tile(cb, tb, stg + kInsertTileBytes, lane);
-        }
-        wait_lds_dma();
-        uint4 b0[4];
-        insert_read_tile(stg, lane, b0);
-        store_dots(insert_dots(ka, b0), tile);
-        if (two) {
-            uint4 b1[4];
-            insert_read_tile(stg + kInsertTileBytes, lane, b1);
-            store_dots(insert_dots(ka, b1), tb);
-        }
-    }
-    const int np0 = d.n_pages[u], tok0 = d.n_tokens[u];
-    ICE_STAMP(33);
-    __syncthreads();
-    ICE_STAMP(34);
-
-    // nearest row for token t over all rows, from LDS
-    auto nearest = [&](int t, float kaf) {
-        u64 b = ~0ull;
-        for (int c = lane; c < C; c += 64) {
-            const float val = insert_objective(lw[c], Dl[(size_t)t * Cs + c], kaf, tk ? lce[c] : 0.f);
-            if (!(val != val)) {
-                const u64 key = insert_pack(val, c);
-                b = key < b ? key : b;
+            for (int j = 0; j < 4; ++j)
+                if (4 * g + j < mt) Dl[(size_t)(4 * g + j) * Cs + tile * 16 + i] = acc[j];
+        };
+        for (int tile = wave; tile < tiles; tile += stage_tiles * kInsertWaves) {
+            const int tb = tile + kInsertWaves;
+            const bool two = stage_tiles == 2 && tb < tiles;
+            if (tile != wave) {
+                insert_stage_tile(cb, tile, stg, lane);
+                if (two) insert_stage_tile(cb, tb, stg + kInsertTileBytes, lane);
+            }
+            wait_lds_dma();
+            uint4 b0[4];
+            insert_read_tile(stg, lane, b0);
+            store_dots(insert_dots(ka, b0), tile);
+            if (two) {
+                uint4 b1[4];
+                insert_read_tile(stg + kInsertTileBytes, lane, b1);
+                store_dots(insert_dots(ka, b1), tb);
             }
         }
-        return wave_min_u64(b);
-    };
-    // the row a move forms against every token: lanes (g, 0) end with tokens 4g .. 4g+3
-    auto row_dots = [&](const uint32_t *row) {
-        uint4 bm[4];
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            bm[ks] = make_uint4(0, 0, 0, 0);
-            if (i == 0) bm[ks] = ((const uint4 *)row)[ks * 4 + g];
-        }
-        return insert_dots(ka, bm);
-    };
+        const int np0 = d.n_pages[u], tok0 = d.n_tokens[u];
+        ICE_STAMP(33);
+        __syncthreads();
+        ICE_STAMP(34);
 
-    // ---- guess
-    ClusterMove mine = {};
-    if (wave < mt) {
-        const int t = wave;
-        bf16_t kab = 0;
-        if (tk) kab = key_extra_coordinate(d.c2[u], key_sqnorm16(((const uint4 *)(ku + (size_t)t * kD))[i]));
-        const float kaf = bf16_to_f32(kab);
-        u64 b = ~0ull, b2 = ~0ull;  // the nearest row and the runner-up
-        for (int c = lane; c < C; c += 64) {
-            const float val = insert_objective(lw[c], Dl[(size_t)t * Cs + c], kaf, tk ? lce[c] : 0.f);
-            if (!(val != val)) merge_min2(b, b2, insert_pack(val, c), ~0ull);
-        }
-        wave_min2_u64(b, b2);
-        const int p = insert_winner(b);
-        const size_t cl = (size_t)u * d.C + p;
-        const int cnt = d.cluster_cnt[cl];
-        const float2 cs = ((const float2 *)(d.cluster_sum + cl * kD))[lane];
-        const float es = tk ? d.csum_aug[cl] : 0.f;
-        const int tail = d.cluster_tail[cl];
-        const int fill = d.tail_fill[cl];
-        const float2 ps = ((const float2 *)(d.tail_sum + cl * kD))[lane];
-        mine = insert_move(cnt, cs, es, lkey[t * 64 + lane], kaf, tk);
-        lrow[t * 64 + lane] = mine.packed;
-        if (lane == 0) {
-            s_best[t] = b;
-            s_best2[t] = b2;
-            s_cluster[t] = p;
-            s_cnt[t] = cnt;
-            s_es[t] = es;
-            s_es1[t] = mine.es;
-            s_tail[t] = tail;
-            s_fill[t] = fill;
-            s_kaf[t] = kaf;
-            s_ka[t] = kab;
-            s_nn[t] = mine.nn;
-            s_ef[t] = mine.ef;
-        }
-        s_cs[t * 64 + lane] = cs;
-        s_cs1[t * 64 + lane] = mine.cs;
-        s_ps[t * 64 + lane] = ps;
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        const f32x4 acc = row_dots(lrow + t * 64);
-        if (i == 0) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) s_dm[t][4 * g + j] = acc[j];
-        }
-    }
-    ICE_STAMP(35);
-    __syncthreads();
-    ICE_STAMP(36);
-
-    // ---- check, all pairs at once (wave t, the earlier tokens on its lanes): token t's guess fails against an
-    // earlier token t' that moves as IT guessed if both guessed the same cluster or the row t' moves comes
-    // out nearer to t than t's guess.  A token whose guess fails against no earlier move goes where it
-    // guessed, with the move its wave worked out.
-    if (wave < mt) {
-        const int t = wave, lt = lane < mt ? lane : 0;
-        const int p_l = s_cluster[lt];
-        const float val = insert_objective(s_nn[lt], s_dm[lt][t], s_kaf[t], s_ef[lt]);
-        const bool bad = lane < t && (p_l == s_cluster[t] || (!(val != val) && insert_pack(val, p_l) < s_best[t]));
-        const u64 bads = __ballot(bad);
-        if (lane == 0) s_fail[t] = (int)bads;
-    }
-    lds_barrier();
-
-    // Where every token goes, token j on lane j: cj = its cluster, gj / tail_s / fill_s = what slot j
-    // caches (the guessed cluster, its tail page and that page's fill before this launch).  Written to
-    // table `buf` in LDS; one wave works it out.
-    auto page_table = [&](int buf, int cj, int gj, int tail_s, int fill_s) {
-        const int s = d.s;
-        int src = -1;  // lowest slot that caches this token's cluster (-1: nobody guessed it)
-        u64 equal = 0; // tokens of the same cluster
-        for (int jj = 0; jj < mt; ++jj) {
-            const int gjj = __builtin_amdgcn_readlane(gj, jj), cjj = __builtin_amdgcn_readlane(cj, jj);
-            if (src < 0 && gjj == cj) src = jj;
-            const u64 eq = __ballot(cjj == cj);
-            if (lane == jj) equal = eq;
-        }
-        int tail0 = __shfl(tail_s, max(src, 0)), fill0 = __shfl(fill_s, max(src, 0));
-        if (lane < mt && src < 0) {
-            tail0 = d.cluster_tail[(size_t)u * d.C + cj];
-            fill0 = d.tail_fill[(size_t)u * d.C + cj];
-        }
-        const int r = __popcll(equal & ((1ull << lane) - 1ull));  // tokens of the same cluster before this one
-        const int q = fill0 + r;
-        const bool onold = q < s;
-        const int slot = onold ? q : (q - s) % s;
-        const u64 openers = __ballot(lane < mt && !onold && slot == 0);
-        u64 mm = equal;  // the token that opened this token's page: the (r - slot)-th of its cluster
-        for (int x = 0; x < r - slot; ++x) mm &= mm - 1;
-        const int opener = mm ? __ffsll((long long)mm) - 1 : lane;
-        const int page = onold ? tail0 : np0 + __popcll(openers & ((1ull << opener) - 1ull));
-        if (lane < mt) {
-            t_cluster[buf][lane] = cj;
-            t_page[buf][lane] = page;
-            t_slot[buf][lane] = slot | (onold ? 1 << 30 : 0);
-            t_src[buf][lane] = src;
-        }
-        if (lane == 0) t_pages[buf] = __popcll(openers);
-    };
-
-    if (wave == 1) {
-        // while wave 0 settles: the table as it is if every token goes where it guessed
-        const int lt = lane < mt ? lane : 0;
-        const int gj = lane < mt ? s_cluster[lt] : -1 - lane;
-        page_table(0, gj, gj, s_tail[lt], s_fill[lt]);
-    }
-    // ---- settle (wave 0; token j's entry lives on lane j)
-    if (wave == 0) {
-        const int lt = lane < mt ? lane : 0;
-        const int r_guess = lane < mt ? s_cluster[lt] : -1 - lane;  // the cluster slot `lane` caches
-        const int r_tail = s_tail[lt], r_fill = s_fill[lt];
-        const u64 r_best = s_best[lt];
-        const float r_kaf = s_kaf[lt];
-        float r_nn = s_nn[lt], r_ef = s_ef[lt];  // of the row token `lane` moves (the guessed move until settled otherwise)
-        int r_row = -1 - lane;                   // cluster token `lane` went to (set when it is settled)
-        u64 live = 0;     // the latest move of its row
-        u64 stood = 0;    // the guessed move stands (and no later token moved the cluster again): wave t stores it
-        u64 post = 0;     // slot t's cluster is in the state AFTER token t's guessed move (s_cnt + 1, s_cs1, s_es1)
-        u64 patched = 0;  // D and the norms hold this move
-        bool all_guessed = true;
-        const u64 r_best2 = s_best2[lt];
-        const int r_fail = lane < mt ? s_fail[lt] : 0;  // against the guessed moves of earlier tokens
-        u64 dfail = 0;                                  // tokens whose guess fails against a move settled here
-        const u64 all = mt >= 64 ? ~0ull : (1ull << mt) - 1ull;
-        int t = -1;
-        for (;;) {
-            // the next token whose guess does not stand, taking every token up to it as standing
-            const u64 done = t < 0 ? 0ull : (2ull << t) - 1ull;  // tokens 0 .. t
-            const u64 assumed = stood | (all & ~done);
-            const bool bad = lane > t && lane < mt &&
-                             ((((u64)(uint32_t)r_fail & assumed & ((1ull << lane) - 1ull)) != 0ull) || ((dfail >> lane) & 1ull));
-            const u64 bads = __ballot(bad);
-            const int next = bads ? __ffsll((long long)bads) - 1 : mt;
-            const u64 run = ((1ull << next) - 1ull) & ~done;  // tokens t+1 .. next-1: settled as guessed
-            stood |= run;
-            post |= run;
-            live |= run;
-            if ((run >> lane) & 1ull) r_row = r_guess;
-            if (next >= mt) break;
-            t = next;
-            const float kaf = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r_kaf), t));
-            const u64 b1 = readlane_u64(r_best, t), b2 = readlane_u64(r_best2, t);
-            const int p = insert_winner(b1);
-            const bool is_live = (live >> lane) & 1ull;
-            // fresh objectives of the rows moved so far
-            u64 cand = ~0ull;
-            if (is_live) {
-                const float val = insert_objective(r_nn, s_dm[lt][t], kaf, r_ef);
-                if (!(val != val)) cand = insert_pack(val, r_row);
-            }
-            cand = readlane_u64(row16_min_u64(cand), 0);
-            const bool p_moved = __ballot(is_live && r_row == p) != 0ull;
-            const bool p2_moved = b2 != ~0ull && __ballot(is_live && r_row == insert_winner(b2)) != 0ull;
-            u64 b;
-            if (!p_moved) {
-                b = cand < b1 ? cand : b1;  // the guess still stands among the rows that have not moved
-            } else if (!p2_moved) {
-                b = cand < b2 ? cand : b2;  // ... or the runner-up does
-            } else {
-                // a full pass: D and the norms first catch up with the moves that are live
-                for (u64 need = live & ~patched; need; need &= need - 1) {
-                    const int j = __ffsll((long long)need) - 1;
-                    const int row = __builtin_amdgcn_readlane(r_row, j);
-                    if (lane >= t && lane < mt) Dl[(size_t)lane * Cs + row] = s_dm[j][lane];
-                    if (lane == 0) {
-                        lw[row] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r_nn), j));
-                        if (tk) lce[row] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r_ef), j));
-                    }
-                }
-                patched |= live;
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                b = nearest(t, kaf);
-            }
-            const int c = insert_winner(b);
-            all_guessed = all_guessed && c == p;
-            const u64 same_slot = __ballot(r_guess == c);  // slots that cache this cluster
-            if (c == p && !p_moved) {
-                // the guessed move stands after all: wave t stores it; slot t now stands for the state after it
-                stood |= 1ull << t;
-                post |= 1ull << t;
-            } else {
-                // (a move of this cluster that stood is superseded: everything it would store is stored here)
-                stood &= ~__ballot(lane < t && r_row == c);
-                const size_t cl = (size_t)u * d.C + c;
-                int cnt;
-                float2 cs;
-                float es_old;
-                if (same_slot & post) {
-                    const int j = __ffsll((long long)(same_slot & post)) - 1;
-                    cnt = s_cnt[j] + 1;
-                    cs = s_cs1[j * 64 + lane];
-                    es_old = s_es1[j];
-                } else if (same_slot) {
-                    const int j = __ffsll((long long)same_slot) - 1;
-                    cnt = s_cnt[j];
-                    cs = s_cs[j * 64 + lane];
-                    es_old = s_es[j];
-                } else {
-                    cnt = d.cluster_cnt[cl];
-                    cs = ((const float2 *)(d.cluster_sum + cl * kD))[lane];
-                    es_old = tk ? d.csum_aug[cl] : 0.f;
-                }
-                const ClusterMove mv = insert_move(cnt, cs, es_old, lkey[t * 64 + lane], kaf, tk);
-                insert_store_move(d, cent, cnorm, caug_cur, u, c, Cpad, lane, mv, tk);
-                if (same_slot) {  // the lowest slot that caches this cluster holds its state from now on
-                    const int j = __ffsll((long long)same_slot) - 1;
-                    s_cs[j * 64 + lane] = mv.cs;
-                    if (lane == 0) { s_cnt[j] = mv.cnt; s_es[j] = mv.es; }
-                }
-                post &= ~same_slot;
-                if (lane == t) { r_nn = mv.nn; r_ef = mv.ef; }
-                if (t + 1 < mt) {
-                    lrow[t * 64 + lane] = mv.packed;
-                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                    const f32x4 acc = row_dots(lrow + t * 64);
-                    if (i == 0) {
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) s_dm[t][4 * g + j] = acc[j];
-                    }
-                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                    // the later tokens against this move: same cluster guessed, or the moved row nearer than their guess
-                    const float val = insert_objective(mv.nn, s_dm[t][lt], r_kaf, mv.ef);
-                    dfail |= __ballot(lane > t && lane < mt && (r_guess == c || (!(val != val) && insert_pack(val, c) < r_best)));
+        // nearest row for token t over all rows, from LDS
+        auto nearest = [&](int t, float kaf) {
+            u64 b = ~0ull;
+            for (int c = lane; c < C; c += 64) {
+                const float val = insert_objective(lw[c], Dl[(size_t)t * Cs + c], kaf, tk ? lce[c] : 0.f);
+                if (!(val != val)) {
+                    const u64 key = insert_pack(val, c);
+                    b = key < b ? key : b;
                 }
             }
-            live &= ~__ballot(is_live && r_row == c);
-            live |= 1ull << t;
-            if (lane == t) r_row = c;
-        }
-        if (lane == 0) s_stood = (int)stood | (all_guessed ? 1 << 16 : 0);
-        if (!all_guessed) page_table(1, r_row, r_guess, r_tail, r_fill);
-    }
-    ICE_STAMP(37);
-    __syncthreads();
-    ICE_STAMP(38);
-
-    // ---- commit
-    const int stood_all = s_stood;
-    if (wave < mt && ((stood_all >> wave) & 1)) insert_store_move(d, cent, cnorm, caug_cur, u, s_cluster[wave], Cpad, lane, mine, tk);
-
-    // ---- append
-    ICE_STAMP(53);
-    if (wave < mt) {
-        const int s = d.s, t = wave, buf = (stood_all >> 16) & 1 ? 0 : 1;
-        const int lt = lane < mt ? lane : 0;
-        const int cj = lane < mt ? t_cluster[buf][lt] : -1 - lane, page = lane < mt ? t_page[buf][lt] : -1 - lane;
-        const int c = t_cluster[buf][t], pg_t = t_page[buf][t], slot_t = t_slot[buf][t] & ~(1 << 30), src_t = t_src[buf][t];
-        const bool onold_t = (t_slot[buf][t] >> 30) & 1;
-        const size_t cl = (size_t)u * d.C + c;
-        const size_t pg = (size_t)u * d.max_pages + pg_t;
-        ((uint32_t *)(d.Kp + (pg * s + slot_t) * kD))[lane] = lkey[t * 64 + lane];
-        ((uint32_t *)(d.Vp + (pg * s + slot_t) * kD))[lane] = vw;
-        if (lane == 0) {
-            d.page_pos[pg * s + slot_t] = tok0 + t;
-            if (tk) d.kaug[(size_t)u * d.max_tokens + tok0 + t] = s_ka[t];
-        }
-        const u64 members = __ballot(page == pg_t);
-        if ((members >> t) == 1ull) {  // the page's last token of this launch: its sum and representative
-            float2 ps = make_float2(0.f, 0.f);
-            // (the page's own sum when nobody cached it: the cluster's copy may already belong to a later page)
-            if (onold_t) ps = src_t >= 0 ? s_ps[src_t * 64 + lane] : ((const float2 *)(d.page_sum + pg * kD))[lane];
-            for (u64 hm = members; hm; hm &= hm - 1) {  // ascending token order, one add per key
-                const uint32_t kwj = lkey[(__ffsll((long long)hm) - 1) * 64 + lane];
-                ps.x = ps.x + bf16_lo(kwj);
-                ps.y = ps.y + bf16_hi(kwj);
+            return wave_min_u64(b);
+        };
+        // the row a move forms against every token: lanes (g, 0) end with tokens 4g .. 4g+3
+        auto row_dots = [&](const uint32_t *row) {
+            uint4 bm[4];
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                bm[ks] = make_uint4(0, 0, 0, 0);
+                if (i == 0) bm[ks] = ((const uint4 *)row)[ks * 4 + g];
             }
-            ((float2 *)(d.page_sum + pg * kD))[lane] = ps;
-            const float ff = (float)(slot_t + 1);
-            ((uint32_t *)(d.rep + pg * kD))[lane] = (uint32_t)f32_to_bf16(ps.x / ff) | ((uint32_t)f32_to_bf16(ps.y / ff) << 16);
+            return insert_dots(ka, bm);
+        };
+
+        // ---- guess
+        ClusterMove mine = {};
+        if (wave < mt) {
+            const int t = wave;
+            bf16_t kab = 0;
+            if (tk) kab = key_extra_coordinate(d.c2[u], key_sqnorm16(((const uint4 *)(ku + (size_t)t * kD))[i]));
+            const float kaf = bf16_to_f32(kab);
+            u64 b = ~0ull, b2 = ~0ull;  // the nearest row and the runner-up
+            for (int c = lane; c < C; c += 64) {
+                const float val = insert_objective(lw[c], Dl[(size_t)t * Cs + c], kaf, tk ? lce[c] : 0.f);
+                if (!(val != val)) merge_min2(b, b2, insert_pack(val, c), ~0ull);
+            }
+            wave_min2_u64(b, b2);
+            const int p = insert_winner(b);
+            const size_t cl = (size_t)u * d.C + p;
+            const int cnt = d.cluster_cnt[cl];
+            const float2 cs = ((const float2 *)(d.cluster_sum + cl * kD))[lane];
+            const float es = tk ? d.csum_aug[cl] : 0.f;
+            const int tail = d.cluster_tail[cl];
+            const int fill = d.tail_fill[cl];
+            const float2 ps = ((const float2 *)(d.tail_sum + cl * kD))[lane];
+            mine = insert_move(cnt, cs, es, lkey[t * 64 + lane], kaf, tk);
+            lrow[t * 64 + lane] = mine.packed;
             if (lane == 0) {
-                d.page_fill[pg] = slot_t + 1;
-                if (!onold_t) d.page_cluster[pg] = c;
+                s_best[t] = b;
+                s_best2[t] = b2;
+                s_cluster[t] = p;
+                s_cnt[t] = cnt;
+                s_es[t] = es;
+                s_es1[t] = mine.es;
+                s_tail[t] = tail;
+                s_fill[t] = fill;
+                s_kaf[t] = kaf;
+                s_ka[t] = kab;
+                s_nn[t] = mine.nn;
+                s_ef[t] = mine.ef;
             }
-            const u64 same_cluster = __ballot(cj == c);
-            if ((same_cluster >> t) == 1ull) {  // ... and the cluster's last: this page is its tail from now on
-                ((float2 *)(d.tail_sum + cl * kD))[lane] = ps;
+            s_cs[t * 64 + lane] = cs;
+            s_cs1[t * 64 + lane] = mine.cs;
+            s_ps[t * 64 + lane] = ps;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            const f32x4 acc = row_dots(lrow + t * 64);
+            if (i == 0) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) s_dm[t][4 * g + j] = acc[j];
+            }
+        }
+        ICE_STAMP(35);
+        __syncthreads();
+        ICE_STAMP(36);
+
+        // ---- check, all pairs at once (wave t, the earlier tokens on its lanes): token t's guess fails against an
+        // earlier token t' that moves as IT guessed if both guessed the same cluster or the row t' moves comes
+        // out nearer to t than t's guess.  A token whose guess fails against no earlier move goes where it
+        // guessed, with the move its wave worked out.
+        if (wave < mt) {
+            const int t = wave, lt = lane < mt ? lane : 0;
+            const int p_l = s_cluster[lt];
+            const float val = insert_objective(s_nn[lt], s_dm[lt][t], s_kaf[t], s_ef[lt]);
+            const bool bad = lane < t && (p_l == s_cluster[t] || (!(val != val) && insert_pack(val, p_l) < s_best[t]));
+            const u64 bads = __ballot(bad);
+            if (lane == 0) s_fail[t] = (int)bads;
+        }
+        lds_barrier();
+
+        // Where every token goes, token j on lane j: cj = its cluster, gj / tail_s / fill_s = what slot j
+        // caches (the guessed cluster, its tail page and that page's fill before this launch).  Written to
+        // table `buf` in LDS; one wave works it out.
+        auto page_table = [&](int buf, int cj, int gj, int tail_s, int fill_s) {
+            const int s = d.s;
+            int src = -1;  // lowest slot that caches this token's cluster (-1: nobody guessed it)
+            u64 equal = 0; // tokens of the same cluster
+            for (int jj = 0; jj < mt; ++jj) {
+                const int gjj = __builtin_amdgcn_readlane(gj, jj), cjj = __builtin_amdgcn_readlane(cj, jj);
+                if (src < 0 && gjj == cj) src = jj;
+                const u64 eq = __ballot(cjj == cj);
+                if (lane == jj) equal = eq;
+            }
+            int tail0 = __shfl(tail_s, max(src, 0)), fill0 = __shfl(fill_s, max(src, 0));
+            if (lane < mt && src < 0) {
+                tail0 = d.cluster_tail[(size_t)u * d.C + cj];
+                fill0 = d.tail_fill[(size_t)u * d.C + cj];
+            }
+            const int r = __popcll(equal & ((1ull << lane) - 1ull));  // tokens of the same cluster before this one
+            const int q = fill0 + r;
+            const bool onold = q < s;
+            const int slot = onold ? q : (q - s) % s;
+            const u64 openers = __ballot(lane < mt && !onold && slot == 0);
+            u64 mm = equal;  // the token that opened this token's page: the (r - slot)-th of its cluster
+            for (int x = 0; x < r - slot; ++x) mm &= mm - 1;
+            const int opener = mm ? __ffsll((long long)mm) - 1 : lane;
+            const int page = onold ? tail0 : np0 + __popcll(openers & ((1ull << opener) - 1ull));
+            if (lane < mt) {
+                t_cluster[buf][lane] = cj;
+                t_page[buf][lane] = page;
+                t_slot[buf][lane] = slot | (onold ? 1 << 30 : 0);
+                t_src[buf][lane] = src;
+            }
+            if (lane == 0) t_pages[buf] = __popcll(openers);
+        };
+
+        if (wave == 1) {
+            // while wave 0 settles: the table as it is if every token goes where it guessed
+            const int lt = lane < mt ? lane : 0;
+            const int gj = lane < mt ? s_cluster[lt] : -1 - lane;
+            page_table(0, gj, gj, s_tail[lt], s_fill[lt]);
+        }
+        // ---- settle (wave 0; token j's entry lives on lane j)
+        if (wave == 0) {
+            const int lt = lane < mt ? lane : 0;
+            const int r_guess = lane < mt ? s_cluster[lt] : -1 - lane;  // the cluster slot `lane` caches
+            const int r_tail = s_tail[lt], r_fill = s_fill[lt];
+            const u64 r_best = s_best[lt];
+            const float r_kaf = s_kaf[lt];
+            float r_nn = s_nn[lt], r_ef = s_ef[lt];  // of the row token `lane` moves (the guessed move until settled otherwise)
+            int r_row = -1 - lane;                   // cluster token `lane` went to (set when it is settled)
+            u64 live = 0;     // the latest move of its row
+            u64 stood = 0;    // the guessed move stands (and no later token moved the cluster again): wave t stores it
+            u64 post = 0;     // slot t's cluster is in the state AFTER token t's guessed move (s_cnt + 1, s_cs1, s_es1)
+            u64 patched = 0;  // D and the norms hold this move
+            bool all_guessed = true;
+            const u64 r_best2 = s_best2[lt];
+            const int r_fail = lane < mt ? s_fail[lt] : 0;  // against the guessed moves of earlier tokens
+            u64 dfail = 0;                                  // tokens whose guess fails against a move settled here
+            const u64 all = mt >= 64 ? ~0ull : (1ull << mt) - 1ull;
+            int t = -1;
+            for (;;) {
+                // the next token whose guess does not stand, taking every token up to it as standing
+                const u64 done = t < 0 ? 0ull : (2ull << t) - 1ull;  // tokens 0 .. t
+                const u64 assumed = stood | (all & ~done);
+                const bool bad = lane > t && lane < mt &&
+                                 ((((u64)(uint32_t)r_fail & assumed & ((1ull << lane) - 1ull)) != 0ull) || ((dfail >> lane) & 1ull));
+                const u64 bads = __ballot(bad);
+                const int next = bads ? __ffsll((long long)bads) - 1 : mt;
+                const u64 run = ((1ull << next) - 1ull) & ~done;  // tokens t+1 .. next-1: settled as guessed
+                stood |= run;
+                post |= run;
+                live |= run;
+                if ((run >> lane) & 1ull) r_row = r_guess;
+                if (next >= mt) break;
+                t = next;
+                const float kaf = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r_kaf), t));
+                const u64 b1 = readlane_u64(r_best, t), b2 = readlane_u64(r_best2, t);
+                const int p = insert_winner(b1);
+                const bool is_live = (live >> lane) & 1ull;
+                // fresh objectives of the rows moved so far
+                u64 cand = ~0ull;
+                if (is_live) {
+                    const float val = insert_objective(r_nn, s_dm[lt][t], kaf, r_ef);
+                    if (!(val != val)) cand = insert_pack(val, r_row);
+                }
+                cand = readlane_u64(row16_min_u64(cand), 0);
+                const bool p_moved = __ballot(is_live && r_row == p) != 0ull;
+                const bool p2_moved = b2 != ~0ull && __ballot(is_live && r_row == insert_winner(b2)) != 0ull;
+                u64 b;
+                if (!p_moved) {
+                    b = cand < b1 ? cand : b1;  // the guess still stands among the rows that have not moved
+                } else if (!p2_moved) {
+                    b = cand < b2 ? cand : b2;  // ... or the runner-up does
+                } else {
+                    // a full pass: D and the norms first catch up with the moves that are live
+                    for (u64 need = live & ~patched; need; need &= need - 1) {
+                        const int j = __ffsll((long long)need) - 1;
+                        const int row = __builtin_amdgcn_readlane(r_row, j);
+                        if (lane >= t && lane < mt) Dl[(size_t)lane * Cs + row] = s_dm[j][lane];
+                        if (lane == 0) {
+                            lw[row] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r_nn), j));
+                            if (tk) lce[row] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r_ef), j));
+                        }
+                    }
+                    patched |= live;
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                    b = nearest(t, kaf);
+                }
+                const int c = insert_winner(b);
+                all_guessed = all_guessed && c == p;
+                const u64 same_slot = __ballot(r_guess == c);  // slots that cache this cluster
+                if (c == p && !p_moved) {
+                    // the guessed move stands after all: wave t stores it; slot t now stands for the state after it
+                    stood |= 1ull << t;
+                    post |= 1ull << t;
+                } else {
+                    // (a move of this cluster that stood is superseded: everything it would store is stored here)
+                    stood &= ~__ballot(lane < t && r_row == c);
+                    const size_t cl = (size_t)u * d.C + c;
+                    int cnt;
+                    float2 cs;
+                    float es_old;
+                    if (same_slot & post) {
+                        const int j = __ffsll((long long)(same_slot & post)) - 1;
+                        cnt = s_cnt[j] + 1;
+                        cs = s_cs1[j * 64 + lane];
+                        es_old = s_es1[j];
+                    } else if (same_slot) {
+                        const int j = __ffsll((long long)same_slot) - 1;
+                        cnt = s_cnt[j];
+                        cs = s_cs[j * 64 + lane];
+                        es_old = s_es[j];
+                    } else {
+                        cnt = d.cluster_cnt[cl];
+                        cs = ((const float2 *)(d.cluster_sum + cl * kD))[lane];
+                        es_old = tk ? d.csum_aug[cl] : 0.f;
+                    }
+                    const ClusterMove mv = insert_move(cnt, cs, es_old, lkey[t * 64 + lane], kaf, tk);
+                    insert_store_move(d, cent, cnorm, caug_cur, u, c, Cpad, lane, mv, tk);
+                    if (same_slot) {  // the lowest slot that caches this cluster holds its state from now on
+                        const int j = __ffsll((long long)same_slot) - 1;
+                        s_cs[j * 64 + lane] = mv.cs;
+                        if (lane == 0) { s_cnt[j] = mv.cnt; s_es[j] = mv.es; }
+                    }
+                    post &= ~same_slot;
+                    if (lane == t) { r_nn = mv.nn; r_ef = mv.ef; }
+                    if (t + 1 < mt) {
+                        lrow[t * 64 + lane] = mv.packed;
+                        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                        const f32x4 acc = row_dots(lrow + t * 64);
+                        if (i == 0) {
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) s_dm[t][4 * g + j] = acc[j];
+                        }
+                        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                        // the later tokens against this move: same cluster guessed, or the moved row nearer than their guess
+                        const float val = insert_objective(mv.nn, s_dm[t][lt], r_kaf, mv.ef);
+                        dfail |= __ballot(lane > t && lane < mt && (r_guess == c || (!(val != val) && insert_pack(val, c) < r_best)));
+                    }
+                }
+                live &= ~__ballot(is_live && r_row == c);
+                live |= 1ull << t;
+                if (lane == t) r_row = c;
+            }
+            if (lane == 0) s_stood = (int)stood | (all_guessed ? 1 << 16 : 0);
+            if (!all_guessed) page_table(1, r_row, r_guess, r_tail, r_fill);
+        }
+        ICE_STAMP(37);
+        __syncthreads();
+        ICE_STAMP(38);
+
+        // ---- commit
+        const int stood_all = s_stood;
+        if (wave < mt && ((stood_all >> wave) & 1)) insert_store_move(d, cent, cnorm, caug_cur, u, s_cluster[wave], Cpad, lane, mine, tk);
+
+        // ---- append
+        ICE_STAMP(53);
+        if (wave < mt) {
+            const int s = d.s, t = wave, buf = (stood_all >> 16) & 1 ? 0 : 1;
+            const int lt = lane < mt ? lane : 0;
+            const int cj = lane < mt ? t_cluster[buf][lt] : -1 - lane, page = lane < mt ? t_page[buf][lt] : -1 - lane;
+            const int c = t_cluster[buf][t], pg_t = t_page[buf][t], slot_t = t_slot[buf][t] & ~(1 << 30), src_t = t_src[buf][t];
+            const bool onold_t = (t_slot[buf][t] >> 30) & 1;
+            const size_t cl = (size_t)u * d.C + c;
+            const size_t pg = (size_t)u * d.max_pages + pg_t;
+            ((uint32_t *)(d.Kp + (pg * s + slot_t) * kD))[lane] = lkey[t * 64 + lane];
+            ((uint32_t *)(d.Vp + (pg * s + slot_t) * kD))[lane] = vw;
+            if (lane == 0) {
+                d.page_pos[pg * s + slot_t] = tok0 + t;
+                if (tk) d.kaug[(size_t)u * d.max_tokens + tok0 + t] = s_ka[t];
+            }
+            const u64 members = __ballot(page == pg_t);
+            if ((members >> t) == 1ull) {  // the page's last token of this launch: its sum and representative
+                float2 ps = make_float2(0.f, 0.f);
+                // (the page's own sum when nobody cached it: the cluster's copy may already belong to a later page)
+                if (onold_t) ps = src_t >= 0 ? s_ps[src_t * 64 + lane] : ((const float2 *)(d.page_sum + pg * kD))[lane];
+                for (u64 hm = members; hm; hm &= hm - 1) {  // ascending token order, one add per key
+                    const uint32_t kwj = lkey[(__ffsll((long long)hm) - 1) * 64 + lane];
+                    ps.x = ps.x + bf16_lo(kwj);
+                    ps.y = ps.y + bf16_hi(kwj);
+                }
+                ((float2 *)(d.page_sum + pg * kD))[lane] = ps;
+                const float ff = (float)(slot_t + 1);
+                ((uint32_t *)(d.rep + pg * kD))[lane] = (uint32_t)f32_to_bf16(ps.x / ff) | ((uint32_t)f32_to_bf16(ps.y / ff) << 16);
                 if (lane == 0) {
-                    d.cluster_tail[cl] = pg_t;
-                    d.tail_fill[cl] = slot_t + 1;
+                    d.page_fill[pg] = slot_t + 1;
+                    if (!onold_t) d.page_cluster[pg] = c;
+                }
+                const u64 same_cluster = __ballot(cj == c);
+                if ((same_cluster >> t) == 1ull) {  // ... and the cluster's last: this page is its tail from now on
+                    ((float2 *)(d.tail_sum + cl * kD))[lane] = ps;
+                    if (lane == 0) {
+                        d.cluster_tail[cl] = pg_t;
+                        d.tail_fill[cl] = slot_t + 1;
+                    }
                 }
             }
+            if (t == 0 && lane == 0) {
+                d.n_pages[u] = np0 + t_pages[buf];
+                d.n_tokens[u] = tok0 + mt;
+            }
         }
-        if (t == 0 && lane == 0) {
-            d.n_pages[u] = np0 + t_pages[buf];
-            d.n_tokens[u] = tok0 + mt;
-        }
-    }
-    ICE_STAMP(55);
-    // ---- the next tokens: what this round stored is read back by this workgroup, whose waves share a vector
-    // cache, once every wave's stores are done
-    t0 += mt;
-    if (t0 >= m_total) break;
-    ku += (size_t)mt * kD;
-    vu += (size_t)mt * kD;
-    mt = min(mt, m_total - t0);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __threadfence_block();
-    __syncthreads();
-    request();
+        ICE_STAMP(55);
+        // ---- the next tokens: what this round stored is read back by this workgroup, whose waves share a vector
+        // cache, once every wave's stores are done
+        t0 += mt;
+        if (t0 >= m_total) break;
+        ku += (size_t)mt * kD;
+        vu += (size_t)mt * kD;
+        mt = min(mt, m_total - t0);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __threadfence_block();
+        __syncthreads();
+        request();
     }
 }
 
@@ -749,15 +749,16 @@ void launch_insert(const Dev &d, const bf16_t *k, const bf16_t *v, int m, int cu
     // LDS of the batched kernel: the fixed tables, one staging tile per wave at least, a row of D per token
     const size_t budget = 156u * 1024u, stage1 = (size_t)kInsertWaves * kInsertTileBytes;
     const size_t fixed = insert_fixed_lds(d.C, d.tk != 0), row = (size_t)insert_row_stride(d.C) * 4;
-    const int cap = (int)std::min<size_t>(kInsertTokens, (budget - fixed - stage1) / row);  // >= 1 up to 8192 clusters
-    if (m == 1) {
+    const int cap = fixed + stage1 < budget ? (int)std::min<size_t>(kInsertTokens, (budget - fixed - stage1) / row) : 0;
+    if (m == 1 || cap < 2) {  // (the tables of two tokens do not fit beside very many clusters: one at a time)
         const size_t one_lds = 2 * stage1;
         allow_dynamic_lds((const void *)insert_one_kernel, one_lds);
-        hipLaunchKernelGGL(insert_one_kernel, dim3(d.U), dim3(kInsertWaves * 64), one_lds, st, k, v, d.cent_bf16[cur], d.cnorm[cur], cur, d.C,
-                           d.Cpad, d.tk, d);
+        for (int t0 = 0; t0 < m; ++t0)
+            hipLaunchKernelGGL(insert_one_kernel, dim3(d.U), dim3(kInsertWaves * 64), one_lds, st, k, v, d.cent_bf16[cur], d.cnorm[cur], m, t0,
+                               cur, d.C, d.Cpad, d.tk, d);
         return;
     }
-    const int per = std::max(1, std::min(cap, m));
+    const int per = std::min(cap, m);
     const int stage_tiles = fixed + per * row + 2 * stage1 <= budget ? 2 : 1;
     const size_t lds = fixed + per * row + stage_tiles * stage1;
     allow_dynamic_lds((const void *)insert_batch_kernel, lds);

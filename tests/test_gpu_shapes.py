@@ -243,7 +243,8 @@ def test_unit_whose_selection_failed_gets_zeros_with_a_window_too():
         assert int(n_sel.max()) == -1 and int(ids.max()) == -1 and float(out.abs().max()) == 0.0
 
 
-@pytest.mark.parametrize("m,C,s,tk", [(2, 20, 16, 0), (16, 20, 16, 0), (17, 20, 16, 1), (33, 300, 64, 0), (100, 20, 16, 1), (21, 5000, 16, 0)])
+@pytest.mark.parametrize("m,C,s,tk", [(2, 20, 16, 0), (16, 20, 16, 0), (17, 20, 16, 1), (33, 300, 64, 0), (100, 20, 16, 1), (21, 5000, 16, 0),
+                                       (3, 8192, 16, 0), (3, 8192, 16, 1), (5, 6000, 16, 1)])
 def test_insertions_in_rounds_equal_single_ones(m, C, s, tk):
     """A call takes as many tokens at a time as its tables hold (16, fewer with many clusters) and reads back what it
     stored: remainders of one token, rows moved and pages opened in one round and used in the next."""
