@@ -738,7 +738,7 @@ __global__ __launch_bounds__(kInsertWaves * 64) void insert_batch_kernel(const b
         ku += (size_t)mt * kD;
         vu += (size_t)mt * kD;
         mt = min(mt, m_total - t0);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        wait_vmem();
         __threadfence_block();
         __syncthreads();
         request();
@@ -819,7 +819,8 @@ __global__ __launch_bounds__(NW * 64, 4) void attend_split_kernel(const bf16_t *
         attend_pages<G, NW, RES, true, true>(d, u, qa, [](int) { return -1; }, 0, r, mine, (float *)smem, [] {});
     }
     if (s == 0) ICE_STAMP(17);
-    __syncthreads();  // every wave's partial stores have completed
+    wait_vmem();      // this wave's partial stores have completed (the barrier alone does not wait for them)
+    __syncthreads();  // ... and every wave's
     if (s == 0) ICE_STAMP(18);
     if (tid == 0) {
         const int old = __hip_atomic_fetch_add(arrive + u, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1257,7 +1258,8 @@ __global__ __launch_bounds__(NW * 64, EMAX * NW <= 64 ? 4 : 1) void decode_step_
     // used (on this chip it writes back / invalidates a whole L2, per workgroup): scores travel as
     // device-scope atomic words, each slot doubles as its own ready flag (kScoreEmpty until written),
     // and the reader re-reads a slot until it is filled.  Writers never wait, so the reader only ever
-    // waits for stores that were issued and completed (barrier below) before the counter moved.
+    // waits for stores that were issued (barrier below) before the counter moved; whether they have
+    // landed is what the slots themselves say.
     // (With one workgroup per unit only LDS is exchanged.)
     if (chunk == 0) ICE_STAMP(14);
     if (single) lds_barrier();

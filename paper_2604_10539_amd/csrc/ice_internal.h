@@ -231,10 +231,14 @@ __device__ inline float wave_sum(float x) {
 
 // squared norm of a key held 8 dims per lane by a 16-lane row (fixed summation order), and the extra
 // coordinate sqrt(c^2 - ||k||^2) of the transformed keys (Eq. 2), rounded to bf16
-// Workgroup barrier that orders LDS traffic only: global loads that are still outstanding stay in
-// flight across it (__syncthreads() waits for them as well).  For steps that exchange data through
-// LDS alone.
+// Workgroup barrier that orders LDS traffic only: global loads and stores that are still outstanding stay in
+// flight across it.  For steps that exchange data through LDS alone.
+// __syncthreads() does not wait for them either on this chip: the waves of a workgroup share a vector cache, so what
+// one of them stored is seen by the others behind the barrier, but nothing says that it has reached memory.  Where
+// another workgroup is told that stores are done, every wave that stored waits for them first (wait_vmem).
 __device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+// this wave's outstanding vector memory operations have completed (device-scope stores: at device scope)
+__device__ inline void wait_vmem() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // 16-byte load / store with the non-temporal hint, for data that a launch touches exactly once (the
 // representative rows, key rows of a clustering pass, the page tiles being written)
