@@ -662,7 +662,7 @@ void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, bool clear, hi
 // are cut into R ranges of L, one workgroup each, and every range is sorted by itself (`order`, stable
 // counting sort) with every cluster's piece (first slot, members) beside it (`range_off`).  The members of
 // a cluster in ascending position are its pieces of range 0, 1, ...: what reads members (the means, the
-// page layout) finds member j through the pieces' lengths (MemberList), so no pass over the
+// page layout) finds member j through the pieces' lengths (Pieces), so no pass over the
 // whole unit ties the ranges together: one launch per round, bound by its latencies.  (With a second
 // launch that turned the ranges' totals into unit-wide positions the two took 17.2 us per round at
 // 8 units x 32768 tokens x 512 clusters and 32 us at 131072 x 2048, most of it reading R totals per
@@ -818,21 +818,6 @@ void launch_sort(const Dev &d, int n, bool clear, float *best_out, int *assign_o
 #undef ICE_SORT
 }
 
-// The members of one cluster in ascending position, out of the ranges' sorted pieces.  pre[r] = members
-// in the ranges before r, at[r] = index into the unit's `order` of range r's first one, both in LDS; member
-// j sits in the last range with pre[r] <= j.
-struct MemberList {
-    const int *order, *pre, *at;
-    int R;
-    __device__ int operator()(int j) const {
-        int lo = 0, hi = R;
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (pre[mid] <= j) lo = mid; else hi = mid;
-        }
-        return order[at[lo] + j - pre[lo]];
-    }
-};
 // inclusive sum over the wave on the vector unit (no trip through LDS)
 __device__ inline int wave_scan_add(int x) {
     x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);  // row_shr 1, 2, 4, 8
@@ -843,28 +828,59 @@ __device__ inline int wave_scan_add(int x) {
     x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // row_bcast 31 into rows 2 and 3
     return x;
 }
-// One wave fills pre[0..R) and at[0..R) of cluster c and returns the number of members (to every lane).  With
-// `slots` the members' indexes into `order` go to slots[0..kMemberSlots) as well, piece by piece, as long as
-// no piece has more than kMemberPiece of them (*listed): one read per member instead of a search.
-constexpr int kMemberSlots = 512, kMemberPiece = 32, kFewPieces = 4;
-__device__ inline int member_ranges(const uint32_t *off, int Cpad, int R, int L, int c, int lane, int *pre, int *at, int *slots, bool *listed) {
-    int total = 0;
-    bool ok = slots != nullptr;
-    for (int r0 = 0; r0 < R; r0 += 64) {
+// The members of cluster c in ascending position, out of the ranges' sorted pieces: member j sits in the last piece that
+// starts at or before it.  A wave holds 64 pieces at a time, one per lane: `first` = members in the pieces before the lane's
+// own, `from` = index into the unit's `order` of its first one.  Nothing is kept per range, so any number of ranges will do.
+struct Pieces {
+    const uint32_t *off;  // the unit's range_off, at cluster c
+    int Cpad, R, L;
+    __device__ uint32_t word(int r) const { return r < R ? off[(size_t)r * Cpad] : 0u; }
+    // pieces r0 .. r0 + 63, `before` members in front of them; returns the members up to their end (the same on every lane)
+    __device__ int load(int r0, int lane, int before, int &first, int &from, int &cnt) const {
         const int r = r0 + lane;
-        const uint32_t o = r < R ? off[(size_t)r * Cpad + c] : 0u;
-        const int cnt = (int)(o & 0xFFFFu), from = r * L + (int)(o >> 16);
-        const int incl = wave_scan_add(cnt), first = total + incl - cnt;
-        if (r < R) {
-            pre[r] = first;
-            at[r] = from;
+        const uint32_t o = word(r);
+        cnt = (int)(o & 0xFFFFu);
+        const int incl = wave_scan_add(cnt);
+        first = before + incl - cnt;
+        from = r * L + (int)(o >> 16);
+        return before + __builtin_amdgcn_readlane(incl, 63);
+    }
+    // index into `order` of member j, which is in the 64 pieces at hand (all lanes take part, j differs by lane)
+    __device__ static int find(int first, int from, int j) {
+        int x = 0;
+#pragma unroll
+        for (int step = 32; step > 0; step >>= 1) x += __shfl(first, x + step) <= j ? step : 0;
+        return __shfl(from, x) + j - __shfl(first, x);
+    }
+    // the same over all pieces, 64 at a time, for lanes' j in [j0, j0 + 64) (all lanes take part; -1 past the last member)
+    __device__ int search(int j0, int j, int lane) const {
+        int index = -1;
+        for (int r0 = 0, before = 0; r0 < R && before < j0 + 64; r0 += 64) {
+            int first, from, cnt;
+            const int end = load(r0, lane, before, first, from, cnt);
+            if (end > j0) {  // (wave-uniform)
+                const int at = find(first, from, j);
+                index = j >= before && j < end ? at : index;
+            }
+            before = end;
         }
-        total += __builtin_amdgcn_readlane(incl, 63);
+        return index;
+    }
+};
+// One wave counts the members of a cluster and lists their indexes into `order` in slots[0..kMemberSlots), piece by piece,
+// as long as they fit and no piece has more than kMemberPiece of them (*listed): one read per member instead of a search.
+constexpr int kMemberSlots = 512, kMemberPiece = 32, kFewPieces = 4;
+__device__ inline int list_members(const Pieces &pieces, int lane, int *slots, bool *listed) {
+    int total = 0;
+    bool ok = true;
+    for (int r0 = 0; r0 < pieces.R; r0 += 64) {
+        int first, from, cnt;
+        total = pieces.load(r0, lane, total, first, from, cnt);
         ok = ok && total <= kMemberSlots && __ballot(cnt > kMemberPiece) == 0ull;
         for (int e = 0; ok && __ballot(e < cnt) != 0ull; ++e)
             if (e < cnt) slots[first + e] = from + e;
     }
-    if (listed) *listed = ok;
+    *listed = ok;
     return total;
 }
 
@@ -883,22 +899,21 @@ static bool keys_exceed_cache(const Dev &d, int n) { return (size_t)d.U * (size_
 // its centroid.
 template <bool STREAM>
 __global__ __launch_bounds__(256) void means_kernel(Dev d, const bf16_t *__restrict__ K, int n, int cur, int R, int L) {
-    extern __shared__ int lists[];  // pre [R], at [R]
     __shared__ float4 part_sum[3][16][2];
     __shared__ int slots[kMemberSlots], sh_cnt, sh_listed;
     const int u = blockIdx.y, c = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int g = lane >> 4, ch = lane & 15;
-    const MemberList search = {d.order + (size_t)u * d.max_tokens, lists, lists + R, R};
+    const int *order = d.order + (size_t)u * d.max_tokens;
     // Up to four pieces (many units) every wave reads by itself, a choice per member; more of them the first wave
     // lays out in LDS for all.  (256 units x 32768 tokens, one piece: means 449 us through LDS, 427 without.)
-    const uint32_t *off = d.range_off + (size_t)u * R * d.Cpad;
+    const Pieces pieces = {d.range_off + (size_t)u * R * d.Cpad + c, d.Cpad, R, L};
     const bool few = R <= kFewPieces;
     int before[kFewPieces], from[kFewPieces], cnt = 0;
     bool listed = false;
     if (few) {
 #pragma unroll
         for (int r = 0; r < kFewPieces; ++r) {
-            const uint32_t o = r < R ? off[(size_t)r * d.Cpad + c] : 0u;
+            const uint32_t o = pieces.word(r);
             before[r] = cnt;
             from[r] = r * L + (int)(o >> 16);
             cnt += (int)(o & 0xFFFFu);
@@ -907,7 +922,7 @@ __global__ __launch_bounds__(256) void means_kernel(Dev d, const bf16_t *__restr
     } else {
         if (wave == 0) {
             bool ok;
-            const int m = member_ranges(off, d.Cpad, R, L, c, lane, lists, lists + R, slots, &ok);
+            const int m = list_members(pieces, lane, slots, &ok);
             if (lane == 0) {
                 sh_cnt = m;
                 sh_listed = ok;
@@ -918,15 +933,23 @@ __global__ __launch_bounds__(256) void means_kernel(Dev d, const bf16_t *__restr
         cnt = sh_cnt;
         listed = sh_listed != 0;
     }
-    auto member = [&](int j) -> int {
+    // lane l: the token of member j0 + l, -1 from `end` on (all lanes take part)
+    auto member = [&](int j0, int end) -> int {
+        const int j = j0 + lane;
+        int at;
         if (few) {
-            int at = from[0] + j;
+            at = from[0] + j;
 #pragma unroll
             for (int r = 1; r < kFewPieces; ++r)
                 if (r < R && j >= before[r]) at = from[r] + j - before[r];
-            return search.order[at];
+        } else if (listed) {
+            at = slots[min(j, kMemberSlots - 1)];
+        } else {
+            at = pieces.search(j0, j, lane);
         }
-        return listed ? search.order[slots[j]] : search(j);
+        int tok = -1;
+        if (j < end) tok = order[at];
+        return tok;
     };
     const bf16_t *Ku = K + (size_t)u * n * kD;
     const int quarter = (cnt + 3) / 4;
@@ -938,8 +961,7 @@ __global__ __launch_bounds__(256) void means_kernel(Dev d, const bf16_t *__restr
     // list is read 64 entries at a time (one per lane) and the rows are fetched eight per group at
     // once, so a wave keeps 8 KB of key rows in flight instead of one dependent load pair per step.
     for (int base = lo; base < hi; base += 64) {
-        int mine = -1;
-        if (base + lane < hi) mine = member(base + lane);
+        const int mine = member(base, hi);
         const int rows = min(64, hi - base);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -968,7 +990,10 @@ __global__ __launch_bounds__(256) void means_kernel(Dev d, const bf16_t *__restr
     // order by the first wave, requested before the waves meet
     float aug_part = 0.f;
     if (d.tk && wave == 0)
-        for (int r = lane; r < cnt; r += 64) aug_part += bf16_to_f32(d.kaug[(size_t)u * d.max_tokens + member(r)]);
+        for (int r0 = 0; r0 < cnt; r0 += 64) {
+            const int tok = member(r0, cnt);
+            if (tok >= 0) aug_part += bf16_to_f32(d.kaug[(size_t)u * d.max_tokens + tok]);
+        }
     if (wave > 0 && g == 0) {
         part_sum[wave - 1][ch][0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
         part_sum[wave - 1][ch][1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
@@ -1027,9 +1052,8 @@ __global__ __launch_bounds__(256) void means_kernel(Dev d, const bf16_t *__restr
 
 void launch_means(const Dev &d, const bf16_t *K, int n, int cur, hipStream_t st) {
     const int L = sort_range_len(d.U, n, d.Cpad), R = (n + L - 1) / L;
-    const size_t lds = (size_t)R * 8;
-    if (keys_exceed_cache(d, n)) hipLaunchKernelGGL(means_kernel<true>, dim3(d.C, d.U), dim3(256), lds, st, d, K, n, cur, R, L);
-    else hipLaunchKernelGGL(means_kernel<false>, dim3(d.C, d.U), dim3(256), lds, st, d, K, n, cur, R, L);
+    if (keys_exceed_cache(d, n)) hipLaunchKernelGGL(means_kernel<true>, dim3(d.C, d.U), dim3(256), 0, st, d, K, n, cur, R, L);
+    else hipLaunchKernelGGL(means_kernel<false>, dim3(d.C, d.U), dim3(256), 0, st, d, K, n, cur, R, L);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1096,7 +1120,7 @@ __global__ __launch_bounds__(1024) void layout_kernel(Dev d, int n, int arm) {
 template <bool STREAM>
 __global__ __launch_bounds__(256) void paginate_kernel(Dev d, const bf16_t *__restrict__ K,
                                                         const bf16_t *__restrict__ V, int n, int R, int L, int arm) {
-    extern __shared__ __align__(16) char smem[];  // [4][s][128] bf16, then [4] (pre [R], at [R])
+    extern __shared__ __align__(16) char smem[];  // [4][s][128] bf16
     const int u = blockIdx.y, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int p = blockIdx.x * 4 + wave;
     if (p >= d.max_pages) return;
@@ -1109,13 +1133,12 @@ __global__ __launch_bounds__(256) void paginate_kernel(Dev d, const bf16_t *__re
         for (int t = lane; t < s; t += 64) d.page_pos[pg * s + t] = -1;
         return;
     }
-    int *pre = (int *)(smem + (size_t)4 * s * kD * 2) + wave * 2 * R, *at = pre + R;
-    const int r0 = (p - d.page_base[(size_t)u * d.C + c]) * s;
-    const int cnt = member_ranges(d.range_off + (size_t)u * R * d.Cpad, d.Cpad, R, L, c, lane, pre, at, nullptr, nullptr);
-    const MemberList member = {d.order + (size_t)u * d.max_tokens, pre, at, R};
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    const int fill = min(s, cnt - r0);
-    const int mine = lane < fill ? member(r0 + lane) : -1;  // slot `lane`'s token (s <= 64)
+    const size_t cl = (size_t)u * d.C + c;
+    const int r0 = (p - d.page_base[cl]) * s, cnt = d.cluster_cnt[cl], fill = min(s, cnt - r0);
+    const Pieces pieces = {d.range_off + (size_t)u * R * d.Cpad + c, d.Cpad, R, L};
+    const int at = pieces.search(r0, r0 + lane, lane);
+    int mine = -1;  // slot `lane`'s token (s <= 64)
+    if (lane < fill) mine = d.order[(size_t)u * d.max_tokens + at];
     const int g = lane >> 4, ch = lane & 15;
     bf16_t *tile = (bf16_t *)smem + (size_t)wave * s * kD;
     for (int t4 = 0; t4 < s; t4 += 4) {
@@ -1145,7 +1168,6 @@ __global__ __launch_bounds__(256) void paginate_kernel(Dev d, const bf16_t *__re
     const float f = (float)fill;
     ((uint32_t *)(d.rep + pg * kD))[lane] = (uint32_t)f32_to_bf16(a0 / f) | ((uint32_t)f32_to_bf16(a1 / f) << 16);
     if (r0 + fill == cnt) {  // the cluster's last page: what an insertion needs of it, beside the cluster
-        const size_t cl = (size_t)u * d.C + c;
         ((float2 *)(d.tail_sum + cl * kD))[lane] = make_float2(a0, a1);
         if (lane == 0) d.tail_fill[cl] = fill;
     }
@@ -1153,11 +1175,10 @@ __global__ __launch_bounds__(256) void paginate_kernel(Dev d, const bf16_t *__re
 
 void launch_paginate(const Dev &d, const bf16_t *K, const bf16_t *V, int n, bool arm, hipStream_t st) {
     const int L = sort_range_len(d.U, n, d.Cpad), R = (n + L - 1) / L;
-    const size_t lds = (size_t)4 * d.s * kD * 2 + (size_t)4 * R * 8;
+    const size_t lds = (size_t)4 * d.s * kD * 2;
     hipLaunchKernelGGL(layout_kernel, dim3(d.U), dim3(1024), (size_t)(d.C + 1) * 4, st, d, n, arm ? 1 : 0);
 #define ICE_PAGINATE(stream)                                                                                               \
     do {                                                                                                                   \
-        allow_dynamic_lds((const void *)paginate_kernel<stream>, lds);                                                     \
         hipLaunchKernelGGL(paginate_kernel<stream>, dim3((d.max_pages + 3) / 4, d.U), dim3(256), lds, st, d, K, V, n, R, L, arm ? 1 : 0); \
     } while (0)
     if (keys_exceed_cache(d, n)) ICE_PAGINATE(true);

@@ -129,6 +129,40 @@ def test_pages_hold_the_members_in_ascending_position(U, n, C, s, lump):
         assert np.array_equal(e2["page_sum"][u, p], old + widen(k1[0, u]))
 
 
+def test_a_prefill_of_thousands_of_ranges():
+    """Nothing in the build is sized by the number of ranges the sort cuts a unit into: 25.3 million tokens in ranges of
+    8192 (the longest beside 4640 clusters) are 3089 of them, and the pages still hold the clusters' members in order."""
+    import torch
+    from paper_2604_10539_amd import IceIndex
+    n, C, s = 25_300_000, 4640, 64
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    K = torch.empty(1, 1, n, D, dtype=torch.int16, device="cuda")
+    for i in range(0, n, 1 << 20):
+        part = K[0, 0, i:i + (1 << 20)]
+        part.copy_(torch.randn(part.shape, generator=gen, device="cuda").to(torch.bfloat16).view(torch.int16))
+    ix = IceIndex(1, 1, 4, n, s, C, kmeans_iters=1)
+    ix.build_index(K, K)
+    ex = ix.export()
+    assign = ex["assign"][0, :n].long()
+    a, order = torch.sort(assign, stable=True)
+    cnt = torch.bincount(assign, minlength=C)
+    pages = (cnt + s - 1) // s
+    base, start = torch.cumsum(pages, 0) - pages, torch.cumsum(cnt, 0) - cnt
+    assert int(ex["n_pages"][0]) == int(pages.sum()) and torch.equal(ex["cluster_cnt"][0].long(), cnt)
+    want = torch.full_like(ex["page_pos"][0], -1)
+    r = torch.arange(n, device="cuda") - start[a]
+    want[base[a] + r // s, r % s] = order.int()
+    assert torch.equal(ex["page_pos"][0], want)
+    assert torch.equal(ex["page_fill"][0], (want >= 0).sum(1).int())
+    tail = ex["page_pos"][0, int(ex["cluster_tail"][0, 17])]
+    live = tail[tail >= 0].long()
+    assert torch.equal(ex["Kp"][0, int(ex["cluster_tail"][0, 17]), :len(live)], K[0, 0, live])
+    # a mean of thousands of rows, from pieces in every range: at most cnt + 8 roundings of partial sums
+    rows = K[0, 0, torch.nonzero(assign == 17)[:, 0]].view(torch.bfloat16).double()
+    bound = (len(rows) + 8) * 2.0 ** -24 * rows.abs().sum(0)
+    assert bool(((ex["cluster_sum"][0, 17].double() - rows.sum(0)).abs() <= bound).all())
+
+
 def _attention_rows(q, k, v):
     """softmax(q k^T / sqrt(d)) v in 64 bits: q [G, D], k, v [m, D]."""
     z = q @ k.T / np.sqrt(D)
