@@ -666,8 +666,8 @@ void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, bool clear, hi
 // whole unit ties the ranges together: one launch per round, bound by its latencies.  (With a second
 // launch that turned the ranges' totals into unit-wide positions the two took 17.2 us per round at
 // 8 units x 32768 tokens x 512 clusters and 32 us at 131072 x 2048, most of it reading R totals per
-// cluster in every workgroup; this one takes 6.1 and 16 us, and the means and the page layout
-// read their lists at 3 to 8 us more.  A fifth wave in the means that prepared the next cluster's list while
+// cluster in every workgroup; this one takes 6.1 and 16 us, and the means
+// read their lists at 3 to 6 us more.  A fifth wave in the means that prepared the next cluster's list while
 // four summed was slower, 24 against 17.3 us: its chain of list reads is the longer one.)
 // A range is cut into W segments, one per wave.  A wave walks its segment 64 tokens at a time: lanes
 // with the same cluster find each other bit by bit of the id (ballots), the first of them moves the
@@ -684,8 +684,8 @@ static int sort_segments(int Cpad) {
 static int sort_max_len(int Cpad) { return sort_segments(Cpad) * kSortMaxSeg; }
 int sort_range_len(int U, int n, int Cpad) {
     // short ranges keep the chip busy, few ranges keep the reading of their pieces short: at most 64 per
-    // unit and one workgroup per CU unless even the longest ranges are more (256 units x 32768 tokens: ranges
-    // of 4096 85 us and the means 449, one range 69 and 427; a sort over the whole unit with the same cost took 64 and 407)
+    // unit and one workgroup per CU unless even the longest ranges are more (256 units x 32768 tokens: two
+    // ranges 80 us and the means 426, one range 94 and 411; 64 units: eight ranges 24 and 115, four 20 and 109)
     int L = 1024;
     while (L < sort_max_len(Cpad) && L < n && ((n + L - 1) / L > 64 || (long long)U * ((n + L - 1) / L) > 256)) L *= 2;
     return L;
@@ -869,7 +869,7 @@ struct Pieces {
 };
 // One wave counts the members of a cluster and lists their indexes into `order` in slots[0..kMemberSlots), piece by piece,
 // as long as they fit and no piece has more than kMemberPiece of them (*listed): one read per member instead of a search.
-constexpr int kMemberSlots = 512, kMemberPiece = 32, kFewPieces = 4;
+constexpr int kMemberSlots = 512, kMemberPiece = 32, kFewPieces = 8;
 __device__ inline int list_members(const Pieces &pieces, int lane, int *slots, bool *listed) {
     int total = 0;
     bool ok = true;
@@ -897,28 +897,36 @@ static bool keys_exceed_cache(const Dev &d, int n) { return (size_t)d.U * (size_
 // large cluster costs a quarter of the dependent round trips.  Writes sum, count, mean, and the
 // bf16 rounding + squared norm of the mean into the OTHER centroid buffer; an empty cluster keeps
 // its centroid.
-template <bool STREAM>
-__global__ __launch_bounds__(256) void means_kernel(Dev d, const bf16_t *__restrict__ K, int n, int cur, int R, int L) {
+// NP: 1, a cluster is one piece; kFewPieces, at most that many, which every wave fetches with one load and picks from per
+// member; 0, more, which the first wave lists in LDS for all (or every wave searches, see list_members).  Bound by the key
+// rows where units are many and by the chain piece -> entry -> row where they are few.  Measured (us; pieces looked up one
+// after the other and no entry ahead, as it is, and over one contiguous list per cluster, which takes a unit-wide sort):
+// 256 units x 32768 tokens x 512 clusters, one piece, 429, 411, 410; 40 units, four pieces, 77.5, 68.5, 66; 32 units, eight,
+// 59 through LDS, 56.4, 53.5; 8 units x 131072 x 2048, 32 pieces, 61.7, 60.7, 55; 2 x 131072 x 64, clusters of thousands, 131, 108, 103.
+// (Eight waves per SIMD: 256 units 418 us with seven; the last form keeps two registers in scratch for it, 62 -> 60.6 at 8 units.)
+template <bool STREAM, int NP>
+__global__ __launch_bounds__(256, 8) void means_kernel(Dev d, const bf16_t *__restrict__ K, int n, int cur, int R, int L) {
     __shared__ float4 part_sum[3][16][2];
     __shared__ int slots[kMemberSlots], sh_cnt, sh_listed;
     const int u = blockIdx.y, c = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int g = lane >> 4, ch = lane & 15;
     const int *order = d.order + (size_t)u * d.max_tokens;
-    // Up to four pieces (many units) every wave reads by itself, a choice per member; more of them the first wave
-    // lays out in LDS for all.  (256 units x 32768 tokens, one piece: means 449 us through LDS, 427 without.)
     const Pieces pieces = {d.range_off + (size_t)u * R * d.Cpad + c, d.Cpad, R, L};
-    const bool few = R <= kFewPieces;
-    int before[kFewPieces], from[kFewPieces], cnt = 0;
+    int before[kFewPieces], from[kFewPieces], cnt = 0, first = 0, first_at = 0;
     bool listed = false;
-    if (few) {
+    if constexpr (NP == 1) {
+        const uint32_t o = pieces.word(0);
+        from[0] = (int)(o >> 16);
+        cnt = (int)(o & 0xFFFFu);
+    } else if constexpr (NP == kFewPieces) {
+        const uint32_t o = pieces.word(lane);
 #pragma unroll
         for (int r = 0; r < kFewPieces; ++r) {
-            const uint32_t o = pieces.word(r);
+            const uint32_t x = __builtin_amdgcn_readlane(o, r);  // (no members past the last piece)
             before[r] = cnt;
-            from[r] = r * L + (int)(o >> 16);
-            cnt += (int)(o & 0xFFFFu);
+            from[r] = r * L + (int)(x >> 16);
+            cnt += (int)(x & 0xFFFFu);
         }
-        if (threadIdx.x == 0) d.cluster_cnt[(size_t)u * d.C + c] = cnt;
     } else {
         if (wave == 0) {
             bool ok;
@@ -926,26 +934,29 @@ __global__ __launch_bounds__(256) void means_kernel(Dev d, const bf16_t *__restr
             if (lane == 0) {
                 sh_cnt = m;
                 sh_listed = ok;
-                d.cluster_cnt[(size_t)u * d.C + c] = m;
             }
         }
         lds_barrier();
         cnt = sh_cnt;
         listed = sh_listed != 0;
+        int own;
+        if (!listed && R <= 64) pieces.load(0, lane, 0, first, first_at, own);
     }
     // lane l: the token of member j0 + l, -1 from `end` on (all lanes take part)
     auto member = [&](int j0, int end) -> int {
         const int j = j0 + lane;
         int at;
-        if (few) {
+        if constexpr (NP == 1) {
+            at = from[0] + j;
+        } else if constexpr (NP == kFewPieces) {
             at = from[0] + j;
 #pragma unroll
             for (int r = 1; r < kFewPieces; ++r)
-                if (r < R && j >= before[r]) at = from[r] + j - before[r];
-        } else if (listed) {
-            at = slots[min(j, kMemberSlots - 1)];
+                if (j >= before[r]) at = from[r] + j - before[r];
         } else {
-            at = pieces.search(j0, j, lane);
+            if (listed) at = slots[min(j, kMemberSlots - 1)];
+            else if (R <= 64) at = Pieces::find(first, first_at, j);
+            else at = pieces.search(j0, j, lane);
         }
         int tok = -1;
         if (j < end) tok = order[at];
@@ -960,8 +971,10 @@ __global__ __launch_bounds__(256) void means_kernel(Dev d, const bf16_t *__restr
     // Group g of a wave sums rows g, g+4, g+8, ... of the wave's range in that order.  The member
     // list is read 64 entries at a time (one per lane) and the rows are fetched eight per group at
     // once, so a wave keeps 8 KB of key rows in flight instead of one dependent load pair per step.
+    // The next 64 entries are looked up while the rows of these are on their way.
+    int mine = member(lo, hi);
     for (int base = lo; base < hi; base += 64) {
-        const int mine = member(base, hi);
+        int next = -1;
         const int rows = min(64, hi - base);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -972,6 +985,7 @@ __global__ __launch_bounds__(256) void means_kernel(Dev d, const bf16_t *__restr
                 const int tok = __shfl(mine, 4 * (h * 8 + k) + g);
                 w[k] = tok >= 0 ? load16<STREAM>((const uint4 *)(Ku + (size_t)tok * kD) + ch) : make_uint4(0, 0, 0, 0);
             }
+            if (h == 0 && base + 64 < hi) next = member(base + 64, hi);
 #pragma unroll
             for (int k = 0; k < 8; ++k) {  // rows past the end add +0
                 acc[0] += bf16_lo(w[k].x); acc[1] += bf16_hi(w[k].x);
@@ -980,6 +994,7 @@ __global__ __launch_bounds__(256) void means_kernel(Dev d, const bf16_t *__restr
                 acc[6] += bf16_lo(w[k].w); acc[7] += bf16_hi(w[k].w);
             }
         }
+        mine = next;
     }
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -1039,6 +1054,8 @@ __global__ __launch_bounds__(256) void means_kernel(Dev d, const bf16_t *__restr
         }
         nn += ef * ef;
     }
+    // (stored here and not where it is known: the first loads' wait would cover an earlier store)
+    if (lane == 0) d.cluster_cnt[(size_t)u * d.C + c] = cnt;
     if (g == 0) {
         float *sum = d.cluster_sum + ((size_t)u * d.C + c) * kD + ch * 8;
         ((float4 *)sum)[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
@@ -1052,8 +1069,15 @@ __global__ __launch_bounds__(256) void means_kernel(Dev d, const bf16_t *__restr
 
 void launch_means(const Dev &d, const bf16_t *K, int n, int cur, hipStream_t st) {
     const int L = sort_range_len(d.U, n, d.Cpad), R = (n + L - 1) / L;
-    if (keys_exceed_cache(d, n)) hipLaunchKernelGGL(means_kernel<true>, dim3(d.C, d.U), dim3(256), 0, st, d, K, n, cur, R, L);
-    else hipLaunchKernelGGL(means_kernel<false>, dim3(d.C, d.U), dim3(256), 0, st, d, K, n, cur, R, L);
+#define ICE_MEANS(np)                                                                                                     \
+    do {                                                                                                                  \
+        if (keys_exceed_cache(d, n)) hipLaunchKernelGGL((means_kernel<true, np>), dim3(d.C, d.U), dim3(256), 0, st, d, K, n, cur, R, L); \
+        else hipLaunchKernelGGL((means_kernel<false, np>), dim3(d.C, d.U), dim3(256), 0, st, d, K, n, cur, R, L);          \
+    } while (0)
+    if (R == 1) ICE_MEANS(1);
+    else if (R <= kFewPieces) ICE_MEANS(kFewPieces);
+    else ICE_MEANS(0);
+#undef ICE_MEANS
 }
 
 // ------------------------------------------------------------------------------------------------
