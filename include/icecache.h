@@ -18,7 +18,9 @@
  *             ice_build_index COPIES K and V into page tiles; the originals may be freed.
  *   Streams   `stream` is a hipStream_t (NULL = default stream).  Every call only enqueues
  *             work; no call synchronises or reads device memory on the host.  Calls on one
- *             index must be issued in order on one stream (or be ordered by the caller).
+ *             index must be issued in order on one stream (or be ordered by the caller): they
+ *             share scratch in its workspace, also those that leave the index as it is
+ *             (ice_attend_tokens alone does not).
  *   Errors    Every call returns an ice_status_t and never throws or aborts.  All errors are
  *             detected on the host from the arguments and host-side counters BEFORE anything is
  *             enqueued; ice_last_error() returns a thread-local description of the last failure.
@@ -193,9 +195,10 @@ ice_status_t ice_select_attend_resident(ice_index_t *idx, const void *q, int32_t
  *       n_tok int32 [B, H_kv].  n_ids_per_unit in [1, 1024].
  *   ice_attend_tokens    attention (Eq. 1) of q over rows token_pos[b, h, 0 .. n_tok[b, h]) of a
  *       dense cache K, V bf16 [B, H_kv, n_rows, d] (any layer's; caller-owned device memory);
- *       max_tok = length of a unit's position list.  The index supplies B, H_kv, the group size and
- *       scratch in its workspace, not its tables (STATE before a build or import).  Positions must lie in [0, n_rows) (others are
- *       clamped into the cache, not skipped).
+ *       max_tok = length of a unit's position list.  The index only supplies B, H_kv and the group
+ *       size (STATE before a build or import): its workspace is neither read nor written, so these calls
+ *       may overlap with each other and with any other call on the index.  Positions must lie in
+ *       [0, n_rows) (others are clamped into the cache, not skipped).
  * With the cache the index was built from, ice_attend_tokens over ice_selected_tokens' positions
  * gives ice_attend's result over those pages. */
 ice_status_t ice_selected_tokens(ice_index_t *idx, const int32_t *page_ids, const int32_t *n_selected,

@@ -117,7 +117,6 @@ ice_status_t ensure_layout(ice_index *ix, int s, int C) {
     ix->dev.tk = ix->geometry;
     ix->laid_out = true;
     ix->built = false;
-    ix->armed = false;
     return ICE_OK;
 }
 
@@ -209,7 +208,6 @@ ice_status_t ice_create(const ice_config_t *cfg, void *workspace, size_t workspa
     ix->ws_bytes = workspace_bytes;
     ix->laid_out = false;
     ix->built = false;
-    ix->armed = false;
     ix->n_tokens = 0;
     ix->build_n = 0;
     ix->n_top = 0;
@@ -257,7 +255,6 @@ ice_status_t ice_build_index(ice_index_t *ix, const void *K, const void *V, int3
     ix->build_n = n;
     ix->n_top = 0;
     ix->built = true;
-    ix->armed = true;
     return ICE_OK;
 }
 
@@ -380,8 +377,7 @@ ice_status_t ice_attend_tokens(ice_index_t *ix, const void *q, const void *K, co
     if (!pos || !n_tok || !out) return fail(ICE_ERR_INVALID_ARG, "token_pos, n_tok or out is null");
     if (n_rows < 1 || max_tok < 1) return fail(ICE_ERR_SHAPE, "n_rows and max_tok must be >= 1");
     const Resident res = {static_cast<const bf16_t *>(K), static_cast<const bf16_t *>(V), max_tok, pos, n_tok, n_rows};
-    // (split over workgroups only where a build or an import has zeroed the arrival counters)
-    launch_attend(ix->dev, static_cast<const bf16_t *>(q), nullptr, nullptr, 1, res, out, static_cast<hipStream_t>(stream), 4, 0, ix->armed);
+    launch_attend(ix->dev, static_cast<const bf16_t *>(q), nullptr, nullptr, 1, res, out, static_cast<hipStream_t>(stream));
     return device_status("ice_attend_tokens");
 }
 
@@ -556,7 +552,6 @@ ice_status_t ice_import_index(ice_index_t *ix, const ice_index_view_t *v, void *
     ix->build_n = 0;  // (not the product of a build here: no stage to re-run)
     ix->n_top = 0;
     ix->built = true;
-    ix->armed = true;
     return ICE_OK;
 }
 

@@ -786,7 +786,8 @@ __global__ __launch_bounds__(NW * 64, 4) void attend_kernel(const bf16_t *__rest
 // unit's arrival counter once those stores have completed; the last one to arrive merges the shares:
 // out = sum_s O_s e^(M_s - M) / sum_s L_s e^(M_s - M).  `arrive` is zero between launches (the last
 // workgroup puts it back).  RES: the first SP shares are the pages', the others take `rper` 16-token blocks
-// each of the dense run or of the list of positions (SP = 0: no pages at all).
+// each of the dense run.  `part` and `arrive` belong to the index: rows by position alone, which need nothing of the
+// index and may be attended to on several streams at once, are not split.
 template <int G, int NW, int RES>
 __global__ __launch_bounds__(NW * 64, 4) void attend_split_kernel(const bf16_t *__restrict__ q, const int *__restrict__ ids,
                                                                 const int *__restrict__ n_sel, int P, int SP, int rper, int after_select, Dev d,
@@ -875,12 +876,11 @@ constexpr int kSplitMaxLdsBytes = 128 * 1024;
 constexpr int kPagesPerShare = 8;
 constexpr int kFusedSplitMinShares = 4;  // when the attention follows the selection of the same call (it then takes a launch of its own)
 constexpr int kRowsSplitMinBlocks = 48, kRowsSplitMaxUnits = 32;  // pages and a dense run, in blocks of 16 tokens
-constexpr int kTokensSplitMinBlocks = 17;                         // gathered rows alone
 struct SplitPlan {
     int S = 1, SP = 1;  // shares per unit; of them the pages'
-    int rper = 0;       // 16-token blocks per share of the dense run or list of positions
+    int rper = 0;       // 16-token blocks per share of the dense run
 };
-// P pages (0: none) and n_rows rows beside them
+// P pages and n_rows rows beside them
 SplitPlan attend_shares(const Dev &d, int P, int n_rows, int min_shares) {
     const int NW = d.G == 8 ? 8 : 16;
     SplitPlan p;
@@ -892,17 +892,14 @@ SplitPlan attend_shares(const Dev &d, int P, int n_rows, int min_shares) {
     // the work splits from 48 blocks on while there are at most 32 units: 8 units x (16 + 32) blocks 19.6 us
     // in one workgroup per unit and 17.8 split, 8 x (64 + 32) 36.9 and 30.5, 32 x (32 + 32) 28.5 and 26.3;
     // eight heads a group 4 x (16 + 32) 17.4 and 17.3, 8 x (92 + 19) 24.6 and 19.6; but 8 x (16 + 13) 14.8 and
-    // 15.9, 64 x (16 + 32) 25.1 and 26.1, 128 x (16 + 64) 31.9 and 36.1.  Gathered rows split from 17 blocks on
-    // (32 units x 512 positions, two such layers behind a step: 46.6 and 44.5 us).
+    // 15.9, 64 x (16 + 32) 25.1 and 26.1, 128 x (16 + 64) 31.9 and 36.1.
     const int blocks = (n_rows + 15) / 16, items = P + blocks;
-    if (blocks > 0 && (P > 0 ? d.U > kRowsSplitMaxUnits || (long long)P * (d.s / 16) + blocks < kRowsSplitMinBlocks
-                             : blocks < kTokensSplitMinBlocks))
-        return p;
+    if (blocks > 0 && (d.U > kRowsSplitMaxUnits || (long long)P * (d.s / 16) + blocks < kRowsSplitMinBlocks)) return p;
     if (blocks == 0 && (items + NW - 1) / NW < min_shares) return p;
     const int fit = kSplitMaxLdsBytes / (int)(sizeof(float) * d.G * (kD + 2));  // shares whose results fit the merging workgroup's LDS
     const int S = std::min({256 / std::max(d.U, 1), (items + kPagesPerShare - 1) / kPagesPerShare, fit});
-    if (S < (P > 0) + (blocks > 0) || S < 2) return p;
-    int SR = blocks == 0 ? 0 : P == 0 ? S : std::max(1, std::min(S - 1, (int)(((long long)S * blocks + items / 2) / items)));
+    if (S < 2) return p;
+    int SR = blocks == 0 ? 0 : std::max(1, std::min(S - 1, (int)(((long long)S * blocks + items / 2) / items)));
     p.SP = S - SR;
     if (blocks) {
         p.rper = (blocks + SR - 1) / SR;
@@ -987,10 +984,10 @@ void launch_selected_tokens(const Dev &d, const int *ids, const int *n_sel, int 
 }
 
 void launch_attend(const Dev &d, const bf16_t *q, const int *ids, const int *n_sel, int P, const Resident &res_in,
-                   float *out, hipStream_t st, int min_shares, int after_select, bool may_split) {
+                   float *out, hipStream_t st, int min_shares, int after_select) {
     const Resident res = res_in;
     const int n_res = res.n;
-    const SplitPlan sp = may_split ? attend_shares(d, ids ? P : 0, n_res, min_shares) : SplitPlan{};
+    const SplitPlan sp = ids ? attend_shares(d, P, n_res, min_shares) : SplitPlan{};
     if (sp.S > 1) {
 #define ICE_ATTEND_SPLIT_K(g, nw, rows)                                                                                    \
     do {                                                                                                                   \
@@ -1000,8 +997,7 @@ void launch_attend(const Dev &d, const bf16_t *q, const int *ids, const int *n_s
     } while (0)
 #define ICE_ATTEND_SPLIT(g, nw)                                                                                            \
     do {                                                                                                                   \
-        if (res.pos) ICE_ATTEND_SPLIT_K(g, nw, kGatheredRows);                                                             \
-        else if (n_res > 0) ICE_ATTEND_SPLIT_K(g, nw, kDenseRows);                                                         \
+        if (n_res > 0) ICE_ATTEND_SPLIT_K(g, nw, kDenseRows);                                                              \
         else ICE_ATTEND_SPLIT_K(g, nw, kNoRows);                                                                           \
     } while (0)
         switch (d.G) {

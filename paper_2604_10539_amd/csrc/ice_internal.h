@@ -79,7 +79,6 @@ struct Host {
     Dev dev;
     bool laid_out;   // dev pointers valid for (s, C)
     bool built;
-    bool armed;      // the arrival counters of the split attention have been zeroed under this layout
     int n_tokens;    // per unit
     int build_n;     // tokens per unit of the last ice_build_index (0: none, or the index was imported)
     int n_top;       // nodes of the level above the clusters (0: not built)
@@ -155,11 +154,11 @@ struct Resident {
     int b0 = 0, b1 = 1 << 30;  // the 16-token blocks of the run or list that the workgroup takes
 };
 
-// min_shares: workgroups' worth of pages per unit from which they are split; may_split false: never; after_select: it follows the selection of the
-// same call, a unit that could not be selected (negative n_sel) gets zeros
+// min_shares: workgroups' worth of pages per unit from which they are split; after_select: it follows the selection of the
+// same call, a unit that could not be selected (negative n_sel) gets zeros.  Without a page list the workspace is neither
+// read nor written: such a call may run beside any other one of the same index.
 void launch_attend(const Dev &d, const bf16_t *q, const int *ids_or_null, const int *n_sel, int P, const Resident &res,
-                   float *out, hipStream_t st, int min_shares = 4, int after_select = 0,
-                   bool may_split = true);
+                   float *out, hipStream_t st, int min_shares = 4, int after_select = 0);
 // the same attention with the shares' partial results in the library's own static device array
 // (no workspace region involved); at most attend_static_max_units() units
 hipError_t launch_attend_static(const Dev &d, const bf16_t *q, const int *ids, const int *n_sel, int P, float *out,

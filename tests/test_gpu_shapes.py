@@ -226,9 +226,9 @@ def test_attention_split_over_workgroups_with_rows_beside_the_pages(U, G, s, bud
 
 @pytest.mark.parametrize("U,G,max_tok,built", [(1, 4, 1, True), (2, 8, 512, True), (8, 4, 513, True), (5, 1, 250, True), (40, 2, 300, True),
                                                 (2, 4, 600, False)])
-def test_attention_by_position_split_over_workgroups(U, G, max_tok, built):
-    """Gathered rows on both sides of the split, lists that end anywhere (also at once), and on an index that was laid
-    out but never built (whose workspace holds anything)."""
+def test_attention_by_position(U, G, max_tok, built):
+    """Gathered rows: lists that end anywhere (also at once), and on an index that was laid out but never built (whose
+    workspace holds anything).  The workspace is left as it is: such calls may overlap."""
     from paper_2604_10539_amd import IceIndex
     n = 1500
     w = datagen.small(n_tokens=n, n_clusters=24, n_kv_heads=U, group_size=G)
@@ -249,12 +249,41 @@ def test_attention_by_position_split_over_workgroups(U, G, max_tok, built):
         pos[0, u, n_tok[0, u]:] = -1
     q = datagen.queries(w)
     qf = widen(q).astype(np.float64).reshape(U, G, D)
-    for _ in range(2):  # (the second call finds what the first left behind)
+    before = ix.workspace.clone()
+    for _ in range(2):
         out = down(ix.attend_tokens(up(q), up(K), up(V), up(pos), up(n_tok))).reshape(U, G, D)
         for u in range(U):
             p = pos[0, u, :n_tok[0, u]]
             ref = _attention_rows(qf[u], widen(K[0, u, p]).astype(np.float64), widen(V[0, u, p]).astype(np.float64)) if len(p) else np.zeros((G, D))
             assert np.abs(out[u] - ref).max() <= ATTEND_TOL
+    assert bool((ix.workspace == before).all())
+
+
+def test_attention_by_position_on_several_streams_at_once():
+    """Layers that reuse one anchor's selection may attend side by side through the anchor's index."""
+    import torch
+    from paper_2604_10539_amd import IceIndex
+    U, G, n, m = 4, 4, 6000, 2000
+    w = datagen.small(n_tokens=n, n_clusters=24, n_kv_heads=U, group_size=G)
+    K, V = datagen.keys_values(w)
+    ix = IceIndex(1, U, G, n, 16, 24, kmeans_iters=1, init_idx=up(datagen.init_indices(w)))
+    ix.build_index(up(K), up(V))
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    layers = []
+    for _ in range(4):
+        rows = torch.randn(3, 1, U, n, D, generator=gen, device="cuda").to(torch.bfloat16).view(torch.int16)
+        pos = torch.argsort(torch.rand(1, U, n, generator=gen, device="cuda"), dim=2)[:, :, :m].int().contiguous()
+        layers.append((rows[2, :, :, :G].reshape(1, U * G, D).contiguous(), rows[0], rows[1], pos, torch.full((1, U), m, dtype=torch.int32, device="cuda")))
+    want = [ix.attend_tokens(*x) for x in layers]
+    streams = [torch.cuda.Stream() for _ in layers]
+    torch.cuda.synchronize()
+    for _ in range(5):
+        got = []
+        for s, x in zip(streams, layers):
+            with torch.cuda.stream(s):
+                got.append([ix.attend_tokens(*x) for _ in range(4)])
+        torch.cuda.synchronize()
+        assert all(torch.equal(g, y) for gs, y in zip(got, want) for g in gs)
 
 
 def test_unit_whose_selection_failed_gets_zeros_with_a_window_too():
