@@ -728,8 +728,9 @@ __global__ __launch_bounds__(1024) void range_sort_kernel(Dev d, int n, int L, i
     for (int j = 0; j < NG; ++j) {  // v[j]: from here on cluster << 16 | rank
         const int i = beg + j * 64 + lane;
         const bool valid = i < end;
-        // (always < Cpad for finite keys; clamped so that no input can send a counter out of range)
-        const int a = (int)min(0xFFFFFFFFu - v[j], (uint32_t)Cpad - 1u);
+        // (always < C for finite keys; a key with no finite score may come out with a padding row: it goes to the last
+        // cluster, so that every token has a page whatever its key holds)
+        const int a = (int)min(0xFFFFFFFFu - v[j], (uint32_t)d.C - 1u);
         v[j] = (uint32_t)a << 16;
         if (beg + j * 64 >= end) continue;  // (wave-uniform)
         u64 peers;

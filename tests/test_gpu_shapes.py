@@ -129,6 +129,30 @@ def test_pages_hold_the_members_in_ascending_position(U, n, C, s, lump):
         assert np.array_equal(e2["page_sum"][u, p], old + widen(k1[0, u]))
 
 
+@pytest.mark.parametrize("C,tk", [(1, 0), (10, 0), (10, 1), (33, 0), (40, 0), (600, 1)])
+def test_keys_that_are_not_finite_keep_their_pages(C, tk):
+    """A key whose scores do not compare (infinities, NaN) is nearest to nothing; its token still sits in a page of a
+    cluster, as every other one does."""
+    from paper_2604_10539_amd import IceIndex
+    n, U, s = 2000, 2, 16
+    w = datagen.small(n_tokens=n, n_clusters=C, n_kv_heads=U, n_components=max(2, C // 3))
+    K, V = datagen.keys_values(w)
+    init = datagen.init_indices(w)
+    odd = [t for t in range(100, 1900, 150) if t not in init[0, 1]]
+    for i, t in enumerate(odd):
+        K[0, 1, t, i % D:] = [0x7FC0, 0x7F80, 0xFF80, 0xFFC0][i % 4]  # NaN, inf, -inf, -NaN
+    ix = IceIndex(1, U, 4, n, s, C, kmeans_iters=2, init_idx=up(init), geometry=tk)
+    ix.build_index(up(K), up(V))
+    ex = {k: down(v) for k, v in ix.export().items() if k != "view"}
+    for u in range(U):
+        a = ex["assign"][u, :n]
+        assert a.min() >= 0 and a.max() < C
+        assert np.array_equal(ex["cluster_cnt"][u], np.bincount(a, minlength=C))
+        pos = ex["page_pos"][u]
+        assert np.array_equal(np.sort(pos[pos >= 0]), np.arange(n))
+        assert int(ex["page_fill"][u].sum()) == n and np.array_equal(ex["page_cluster"][u, :ex["n_pages"][u]], a[pos[:ex["n_pages"][u], 0]])
+
+
 def test_a_prefill_of_thousands_of_ranges():
     """Nothing in the build is sized by the number of ranges the sort cuts a unit into: 25.3 million tokens in ranges of
     8192 (the longest beside 4640 clusters) are 3089 of them, and the pages still hold the clusters' members in order."""
