@@ -871,9 +871,16 @@ static size_t attend_split_lds(int G, int NW, int S) {
     return sizeof(float) * std::max<size_t>(attend_scratch_floats(G, NW), (size_t)S * G * (kD + 2));
 }
 constexpr int kSplitMaxLdsBytes = 128 * 1024;
-// shares per unit of the split attention: as many workgroups as the chip has CUs, at least one page
-// per wave; below `min_shares` the exchange of the partial results costs more than the shares save
-constexpr int kPagesPerShare = 8;
+// Shares per unit of the split attention, from its 16-token blocks (a page of 64 tokens is four of them).  A CU draws
+// ~30 GB/s from cold HBM however many waves ask, so what shortens the attention is the number of CUs, until the results to
+// merge are too many: up to four shares of four blocks, up to eight of eight, beyond that shares of sixteen.  Measured for 8
+// units, us of the attention alone with that many shares: 16 blocks 4: 6.7, 2: 7.0, 1: 7.9; 32 blocks 8: 7.2, 4: 7.4, 2: 8.1
+// (eight query heads 9.1, 8.6, 8.9); 64 blocks 16: 8.9, 8: 7.9, 4: 8.8; 128 blocks 32: 12.5, 16: 9.85, 8: 9.5; 256 blocks 32:
+// 13.4, 16: 11.0; pages of 64 tokens, 64 blocks 16: 9.8, 8: 9.25, 4: 9.15, 2: 10.1; 256 blocks 32: 14.3, 16: 11.8, 8: 11.85.
+// With a dense run beside the pages up to twelve shares of eight (96 blocks 12: 8.85, 8: 9.3).
+static long long best_shares(long long blocks, bool rows) {
+    return std::max({std::min<long long>((blocks + 3) / 4, 4), std::min<long long>((blocks + 7) / 8, rows ? 12 : 8), (blocks + 15) / 16});
+}
 constexpr int kFusedSplitMinShares = 4;  // when the attention follows the selection of the same call (it then takes a launch of its own)
 constexpr int kRowsSplitMinBlocks = 48, kRowsSplitMaxUnits = 32;  // pages and a dense run, in blocks of 16 tokens
 struct SplitPlan {
@@ -884,20 +891,19 @@ struct SplitPlan {
 SplitPlan attend_shares(const Dev &d, int P, int n_rows, int min_shares) {
     const int NW = d.G == 8 ? 8 : 16;
     SplitPlan p;
-    // A CU draws ~30 GB/s from cold HBM however many waves ask, so what shortens the attention is the number of
-    // CUs: a share is kPagesPerShare pages, or as many 16-row blocks, even though a workgroup of 16 waves
-    // could take 16 at once.  (Eight beat four, whose shares are twice as many to merge: fused step of 8 units
-    // x (64 pages + 512 rows) 30.5 us against 31.5, x (16 pages + 1024 rows) 18.2 against 19.5.)  Pages alone: less than
-    // min_shares workgroups' worth, counted NW to a workgroup, is not split.  With a dense run beside them
-    // the work splits from 48 blocks on while there are at most 32 units: 8 units x (16 + 32) blocks 19.6 us
-    // in one workgroup per unit and 17.8 split, 8 x (64 + 32) 36.9 and 30.5, 32 x (32 + 32) 28.5 and 26.3;
-    // eight heads a group 4 x (16 + 32) 17.4 and 17.3, 8 x (92 + 19) 24.6 and 19.6; but 8 x (16 + 13) 14.8 and
-    // 15.9, 64 x (16 + 32) 25.1 and 26.1, 128 x (16 + 64) 31.9 and 36.1.
-    const int blocks = (n_rows + 15) / 16, items = P + blocks;
-    if (blocks > 0 && (d.U > kRowsSplitMaxUnits || (long long)P * (d.s / 16) + blocks < kRowsSplitMinBlocks)) return p;
-    if (blocks == 0 && (items + NW - 1) / NW < min_shares) return p;
+    // Pages alone: less than min_shares workgroups' worth, counted NW to a workgroup, is not split.  With a dense run
+    // beside them the work splits from 48 blocks on while there are at most 32 units (a page of 64 tokens counted as three
+    // blocks: it is seldom full).  Fused steps, us in one workgroup per unit and split: 8 units x (16 + 32) blocks 18.95
+    // and 17.5, 8 x (64 + 32) 36.8 and 30.5, 16 x (32 + 16) 24.4 and 24.1, 32 x (32 + 32) 27.8 and 25.8; eight heads a
+    // group 4 x (16 + 32) 19.1 and 18.2, 8 x (92 + 19) 31.5 and 25.3; pages of 64 tokens 8 x (16 pages + 32) 23.2 and
+    // 19.05, 32 x (8 pages + 32) 20.3 and 19.5; but 8 x (16 + 13) 16.9 and 17.1, 8 x (8 pages of 64 + 16) 17.4 and 17.8,
+    // 64 x (16 + 32) 24.4 and 25.7.
+    const int blocks = (n_rows + 15) / 16;
+    const long long items = (long long)P * (d.s / 16) + blocks;
+    if (blocks > 0 && (d.U > kRowsSplitMaxUnits || (long long)P * (d.s == 64 ? 3 : d.s / 16) + blocks < kRowsSplitMinBlocks)) return p;
+    if (blocks == 0 && (P + NW - 1) / NW < min_shares) return p;
     const int fit = kSplitMaxLdsBytes / (int)(sizeof(float) * d.G * (kD + 2));  // shares whose results fit the merging workgroup's LDS
-    const int S = std::min({256 / std::max(d.U, 1), (items + kPagesPerShare - 1) / kPagesPerShare, fit});
+    const int S = (int)std::min<long long>({256 / std::max(d.U, 1), best_shares(items, blocks > 0), fit});
     if (S < 2) return p;
     int SR = blocks == 0 ? 0 : std::max(1, std::min(S - 1, (int)(((long long)S * blocks + items / 2) / items)));
     p.SP = S - SR;
@@ -1077,7 +1083,7 @@ hipError_t launch_attend_static(const Dev &d, const bf16_t *q, const int *ids, c
     if (!part) return err;
     const int NW = d.G == 8 ? 8 : 16;
     const int fit = kSplitMaxLdsBytes / (int)(sizeof(float) * d.G * (kD + 2));
-    const int S = std::max(1, std::min({kStaticPairs / d.U, (P + kPagesPerShare - 1) / kPagesPerShare, fit}));
+    const int S = (int)std::max<long long>(1, std::min<long long>({kStaticPairs / d.U, best_shares((long long)P * (d.s / 16), false), fit}));
 #define ICE_ATTEND_SPLIT(g, nw)                                                                                            \
     do {                                                                                                                   \
         allow_dynamic_lds((const void *)attend_split_kernel<g, nw, kNoRows>, attend_split_lds(g, nw, S));                  \

@@ -214,6 +214,8 @@ ATTEND_TOL = 2e-4
     (2, 4, 16, 560, 497),     # ragged shares of both
     (1, 8, 64, 64, 400),      # one page, many row shares
     (3, 2, 32, 1600, 16),     # many pages, one row share
+    (2, 4, 64, 64 * 50, 0),   # pages of 64 alone, shares of four and fewer
+    (4, 1, 64, 1024, 500),    # ... and beside rows
     (33, 1, 16, 512, 700),    # too many units to split
     (4, 4, 16, 256, 1),       # too little to split
     (130, 4, 16, 640, 0),     # fills fetched ahead, no rows
