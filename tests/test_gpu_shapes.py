@@ -64,15 +64,21 @@ def test_assignment_at_every_share_of_a_centroid_slice(tiles, n):
 
 
 @pytest.mark.parametrize("U,n,C,s,lump", [
+    # ranges of the sort and what they are read by (L tokens per range, R ranges per unit)
     (1, 1, 1, 16, 0),            # one token
-    (2, 1023, 7, 16, 0), (2, 1024, 7, 16, 0), (2, 1025, 7, 64, 0),    # around one range; clusters longer than the member table
-    (3, 2500, 300, 16, 600),     # 600 tokens in a row of one cluster: a piece longer than the table takes
-    (40, 3000, 40, 32, 0),       # many units: longer ranges
-    (1, 66000, 900, 16, 0),      # two centroid slices; ranges of 2048
-    (1, 270000, 64, 64, 5000),   # more than 64 ranges
-    (1, 9000, 8192, 16, 0),      # four segments per range
-    (300, 1100, 24, 16, 0),      # more units than CUs: one range each
-    (1, 1050000, 64, 64, 0),     # ranges of 32768, the longest
+    (2, 1023, 7, 16, 0), (2, 1024, 7, 16, 0), (2, 1025, 7, 64, 0),    # around one range
+    (60, 9000, 40, 32, 0),       # R 3, picked per member; L 4096, the longest that ranks in four groups
+    (1, 8000, 100, 16, 0),       # R 8, the most that are picked
+    (1, 40000, 200, 16, 0),      # R 40, most clusters listed in LDS
+    (1, 12000, 300, 16, 600),    # R 12, 600 tokens in a row of one cluster: a piece longer than the list takes, searched
+    (1, 66000, 900, 16, 0),      # R 33, two centroid slices
+    (1, 270000, 64, 64, 5000),   # L 8192, lane masks; clusters longer than the list
+    (1, 70000, 8192, 16, 0),     # L 2048 in four segments, no lane masks
+    (1, 530000, 8192, 16, 0),    # R 65, more than one wave holds; L 8192, the longest of four segments
+    (1, 9000, 8192, 16, 0),      # four segments, one token per cluster or none
+    (300, 1100, 24, 16, 0),      # more units than CUs: R 1
+    (260, 4100, 40, 16, 0),      # R 1, L 8192
+    (1, 1050000, 64, 64, 0),     # L 32768, the longest
 ])
 def test_pages_hold_the_members_in_ascending_position(U, n, C, s, lump):
     """The page layout is the stable sort of the assignment, whatever the sort's ranges and segments are, and the
@@ -85,9 +91,11 @@ def test_pages_hold_the_members_in_ascending_position(U, n, C, s, lump):
         K, V = K[:, :, at], V[:, :, at[::-1]]
     if lump:
         K[0, 0, n // 3:n // 3 + lump] = K[0, 0, n // 3]
-    ix = IceIndex(1, U, 4, n, s, C, kmeans_iters=2, init_idx=up(datagen.init_indices(w)))
+    tk = int(lump > 0)  # (the transformed keys' extra coordinate is summed over the same members)
+    ix = IceIndex(1, U, 4, n, s, C, kmeans_iters=2, init_idx=up(datagen.init_indices(w)), geometry=tk)
     ix.build_index(up(K), up(V))
     ex = {k: down(v) for k, v in ix.export().items() if k != "view"}
+    geo = {k: down(v) for k, v in ix.export_geometry().items()} if tk else None
     for u in range(U):
         a = ex["assign"][u, :n]
         order = np.argsort(a, kind="stable")
@@ -114,9 +122,12 @@ def test_pages_hold_the_members_in_ascending_position(U, n, C, s, lump):
         # at most cnt + 8 roundings of partial sums bounded by the sum of magnitudes
         seen = np.flatnonzero(cnt)[:200]
         assert np.all(np.abs(ex["cluster_sum"][u] - sums)[seen] <= ((cnt[:, None] + 8) * 2.0 ** -24 * mags)[seen])
+        if tk:
+            extra = np.bincount(a, weights=widen(geo["key_extra"][u, :n]).astype(np.float64), minlength=C)
+            assert np.all(np.abs(geo["cluster_sum_extra"][u] - extra) <= (cnt + 8) * 2.0 ** -24 * extra)  # (none is negative)
     # an insertion finds the tail pages' state beside the clusters
     k1 = narrow(np.random.default_rng(5).standard_normal((1, U, D)).astype(np.float32))
-    ix2 = IceIndex(1, U, 4, n + 1, s, C, kmeans_iters=2, init_idx=up(datagen.init_indices(w)))
+    ix2 = IceIndex(1, U, 4, n + 1, s, C, kmeans_iters=2, init_idx=up(datagen.init_indices(w)), geometry=tk)
     ix2.build_index(up(K), up(V))
     ix2.insert(up(k1), up(k1))
     e2 = {k: down(v) for k, v in ix2.export().items() if k != "view"}
@@ -212,7 +223,7 @@ ATTEND_TOL = 2e-4
 @pytest.mark.parametrize("U,G,s,budget,n_res", [
     (2, 4, 16, 512, 512),     # split: pages' and rows' shares, none of them ragged
     (2, 4, 16, 560, 497),     # ragged shares of both
-    (1, 8, 64, 64, 400),      # one page, many row shares
+    (1, 8, 64, 64, 800),      # one page, many row shares
     (3, 2, 32, 1600, 16),     # many pages, one row share
     (2, 4, 64, 64 * 50, 0),   # pages of 64 alone, shares of four and fewer
     (4, 1, 64, 1024, 500),    # ... and beside rows

@@ -40,7 +40,7 @@ def test_noalloc_attention_equals_ice_attend_on_shrinking_calls():
     w, ix = _index(2, 6000, 40, seed=21)
     ex = export_np(ix)
     o = oracle_from_export(ix, ex)
-    # three calls in a row on one GPU: 96 pages per unit (6 shares), then 20 (2 shares), then 3 (1 share);
+    # three calls in a row on one GPU: 96 pages per unit (8 shares), then 20 (4 shares), then 3 (1 share);
     # every later call leaves most of the array as the call before wrote it
     for step, budget in enumerate((96 * 16, 20 * 16, 3 * 16)):
         qn = datagen.queries(w, step=step)
