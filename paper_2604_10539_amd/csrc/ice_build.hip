@@ -445,10 +445,7 @@ __global__ __launch_bounds__(512) void assign_kernel(const bf16_t *__restrict__ 
     };
     auto store_aug = [&](int buf) {
         if constexpr (AUG) {
-            if (tid < kAssignTile) {
-                kext[(buf * kAssignTile + tid) * 2] = make_uint4(stage_aug, 0, 0, 0);
-                kext[(buf * kAssignTile + tid) * 2 + 1] = make_uint4(0, 0, 0, 0);
-            }
+            if (tid < kAssignTile) *(uint32_t *)&kext[(buf * kAssignTile + tid) * 2] = stage_aug;  // (the other 28 bytes stay zero)
         }
     };
     // rows past the end of the range are never written back: they may hold any valid key
@@ -478,11 +475,11 @@ __global__ __launch_bounds__(512) void assign_kernel(const bf16_t *__restrict__ 
         *(uint4 *)(keys + slot(row, ch)) = cst[i];
     }
     if constexpr (AUG) {
-        if (tid < R) {  // the centroids' extra coordinate, then 15 zeros
-            const uint32_t a = crow0 + tid < Cpad ? d.caug[cur][(size_t)u * Cpad + crow0 + tid] : 0u;
-            kext[tid * 2] = make_uint4(a, 0, 0, 0);
-            kext[tid * 2 + 1] = make_uint4(0, 0, 0, 0);
-        }
+        // the centroids' extra coordinate, then 15 zeros (both buffers' 512 rows: the zeros serve the keys as well)
+        static_assert(2 * kAssignTile == 512, "one thread per row");
+        const uint32_t a = tid < R && crow0 + tid < Cpad ? d.caug[cur][(size_t)u * Cpad + crow0 + tid] : 0u;
+        kext[tid * 2] = make_uint4(a, 0, 0, 0);
+        kext[tid * 2 + 1] = make_uint4(0, 0, 0, 0);
     }
     if (tid < 2 * kAssignTile) best[tid] = 0ull;
     __syncthreads();

@@ -47,3 +47,12 @@ def test_a_share_of_the_split_attention_arrives_after_its_stores(kernels):
         assert any("sc1" in code[i] for i in stores), name  # (the partial results: device-scope words)
         assert not any(re.match(r"(global|flat|buffer)_store", code[i]) for i in range(barrier, arrive)), name
         assert any("s_waitcnt" in code[i] and "vmcnt(0)" in code[i] for i in range(stores[-1], barrier)), name
+
+
+def test_the_assignment_keeps_its_operands_in_registers(kernels):
+    """The centroid operand, the seeds and the accumulators of a wave fill the register file almost to the last; nothing of
+    them goes through scratch memory in any form of the kernel."""
+    assign = {k: v for k, v in kernels.items() if "13assign_kernelI" in k}
+    assert len(assign) >= 16
+    for name, code in assign.items():
+        assert not any(x.startswith("scratch_") for x in code), name
