@@ -868,6 +868,7 @@ struct Pieces {
 // One wave counts the members of a cluster and lists their indexes into `order` in slots[0..kMemberSlots), piece by piece,
 // as long as they fit and no piece has more than kMemberPiece of them (*listed): one read per member instead of a search.
 constexpr int kMemberSlots = 512, kMemberPiece = 32, kFewPieces = 8;
+constexpr int kAugAlone = 256, kAugChunk = 1024;
 __device__ inline int list_members(const Pieces &pieces, int lane, int *slots, bool *listed) {
     int total = 0;
     bool ok = true;
@@ -906,6 +907,7 @@ template <bool STREAM, int NP>
 __global__ __launch_bounds__(256, 8) void means_kernel(Dev d, const bf16_t *__restrict__ K, int n, int cur, int R, int L) {
     __shared__ float4 part_sum[3][16][2];
     __shared__ int slots[kMemberSlots], sh_cnt, sh_listed;
+    __shared__ float aug_lds[kAugChunk];
     const int u = blockIdx.y, c = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int g = lane >> 4, ch = lane & 15;
     const int *order = d.order + (size_t)u * d.max_tokens;
@@ -999,14 +1001,43 @@ __global__ __launch_bounds__(256, 8) void means_kernel(Dev d, const bf16_t *__re
         acc[j] += __shfl_xor(acc[j], 16);
         acc[j] += __shfl_xor(acc[j], 32);
     }
-    // (transformed keys) sum of the members' extra coordinates: lane-strided partial sums in member
-    // order by the first wave, requested before the waves meet
+    // (transformed keys) sum of the members' extra coordinates: lane-strided partial sums in member order by the first
+    // wave, requested before the waves meet.  Beyond kAugAlone members all four waves look them up and leave the
+    // coordinates in LDS, kAugChunk at a time, for the first one to add (by itself it took 116 us at clusters of thousands,
+    // 2 units x 131072 x 64, against 58 over one contiguous list).
     float aug_part = 0.f;
-    if (d.tk && wave == 0)
-        for (int r0 = 0; r0 < cnt; r0 += 64) {
-            const int tok = member(r0, cnt);
-            if (tok >= 0) aug_part += bf16_to_f32(d.kaug[(size_t)u * d.max_tokens + tok]);
+    if (d.tk) {
+        const bf16_t *extra = d.kaug + (size_t)u * d.max_tokens;
+        const bool alone = cnt <= kAugAlone;
+        for (int j0 = 0; j0 < cnt; j0 += kAugChunk) {
+            constexpr int NB = 4;  // 64 members each
+            static_assert(kAugAlone == 64 * NB && kAugChunk == 4 * kAugAlone, "four look-ups per wave at a time");
+            int tok[NB];
+            float a[NB];
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                const int b = alone ? i : 4 * i + wave;
+                tok[i] = -1;
+                if (j0 + 64 * b < cnt && (wave == 0 || !alone)) tok[i] = member(j0 + 64 * b, cnt);  // (wave-uniform)
+            }
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                a[i] = 0.f;
+                if (tok[i] >= 0) a[i] = bf16_to_f32(extra[tok[i]]);
+            }
+            if (alone) {
+#pragma unroll
+                for (int i = 0; i < NB; ++i) aug_part += a[i];  // (no coordinate is negative: +0 past the end changes nothing)
+                break;
+            }
+            if (j0 > 0) __syncthreads();  // (the first wave has added the last chunk)
+#pragma unroll
+            for (int i = 0; i < NB; ++i) aug_lds[(4 * i + wave) * 64 + lane] = a[i];
+            __syncthreads();
+            if (wave == 0)
+                for (int b = 0; b < 4 * NB && j0 + 64 * b < cnt; ++b) aug_part += aug_lds[64 * b + lane];
         }
+    }
     if (wave > 0 && g == 0) {
         part_sum[wave - 1][ch][0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
         part_sum[wave - 1][ch][1] = make_float4(acc[4], acc[5], acc[6], acc[7]);

@@ -69,6 +69,8 @@ def test_assignment_at_every_share_of_a_centroid_slice(tiles, n):
     (2, 1023, 7, 16, 0), (2, 1024, 7, 16, 0), (2, 1025, 7, 64, 0),    # around one range
     (60, 9000, 40, 32, 0),       # R 3, picked per member; L 4096, the longest that ranks in four groups
     (1, 8000, 100, 16, 0),       # R 8, the most that are picked
+    (2, 256, 1, 16, 9), (2, 257, 1, 16, 9), (2, 1024, 1, 16, 9),      # transformed: one wave adds the coordinates, four of them do
+    (3, 2500, 4, 16, 600),       # ... in two chunks, picked
     (1, 40000, 200, 16, 0),      # R 40, most clusters listed in LDS
     (1, 12000, 300, 16, 600),    # R 12, 600 tokens in a row of one cluster: a piece longer than the list takes, searched
     (1, 66000, 900, 16, 0),      # R 33, two centroid slices
