@@ -636,8 +636,8 @@ void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, bool clear, hi
     } while (0)
 #define ICE_ASSIGN_A(ct, cw, aug)                                                                   \
     do {                                                                                            \
-        if (full || ct * cw <= 2) ICE_ASSIGN_F(ct, cw, aug, true);  /* (one or two tiles are always full) */ \
-        else ICE_ASSIGN_F(ct, cw, aug, false);                                                      \
+        if (full) ICE_ASSIGN_F(ct, cw, aug, true);                                                  \
+        else ICE_ASSIGN_F(ct, cw, aug, (ct * cw <= 2));  /* (one or two tiles are always full: no such variant) */ \
     } while (0)
 #define ICE_ASSIGN(ct, cw)                                                                          \
     do {                                                                                            \
