@@ -199,8 +199,8 @@ void launch_refresh_tails(const Dev &d, hipStream_t st) {
 // An import in one launch: the caller's arrays are copied, what is derived from them is formed from the
 // caller's copies beside that (the centroids' bf16 rounding and squared norms for both buffers, the tail
 // pages' state), and the decode state is set.  Bound by the copy; apart, twelve copies and seven small
-// launches cost their start-up and drain each (32 units x 8392 tokens, 400 MB read and written: 81 us in one launch
-// where a turn of 200 tokens took 252 us with them apart and 221 with this).
+// launches cost their start-up and drain each (32 units x 8392 tokens, 385 MB read and written: 71 us in one launch;
+// a turn of 200 tokens took 252 us with them apart and 211 with this).
 // Blocks [0, copy_blocks) copy 32 KB each, the next cluster_blocks take four clusters each (one wave per
 // cluster), the rest the score slots and the units' counters.
 constexpr int kImportArrays = 12, kImportChunk = 32768;
@@ -222,10 +222,10 @@ __global__ __launch_bounds__(256) void import_kernel(Dev d, ImportArgs a) {
 #pragma unroll
         for (int i = 1; i < kImportArrays; ++i) x = blk >= a.first[i] ? i : x;
         const size_t at = (size_t)(blk - a.first[x]) * kImportChunk, left = a.bytes[x] - at;
-        const uint4 *src = (const uint4 *)(a.src[x] + at);
-        uint4 *dst = (uint4 *)(a.dst[x] + at);
+        const u32x4 *src = (const u32x4 *)(a.src[x] + at);
+        u32x4 *dst = (u32x4 *)(a.dst[x] + at);
         if (left >= (size_t)kImportChunk) {
-            uint4 w[8];
+            u32x4 w[8];  // (of uint4 structures the compiler keeps a copy in scratch memory)
 #pragma unroll
             for (int i = 0; i < 8; ++i) w[i] = src[i * 256 + tid];
 #pragma unroll

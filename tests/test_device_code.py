@@ -56,3 +56,8 @@ def test_the_assignment_keeps_its_operands_in_registers(kernels):
     assert len(assign) == 16  # (1, 2, 4, 8 or 16 tiles; transformed or not; 4 and more: slices that are full or not)
     for name, code in assign.items():
         assert not any(x.startswith("scratch_") for x in code), name
+
+
+def test_an_import_copies_through_registers(kernels):
+    code = next(v for k, v in kernels.items() if "import_kernel" in k)
+    assert not any(x.startswith("scratch_") for x in code)
