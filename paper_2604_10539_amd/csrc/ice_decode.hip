@@ -915,8 +915,8 @@ SplitPlan attend_shares(const Dev &d, int P, int n_rows, int min_shares) {
     return p;
 }
 
-// Whether the attention over P pages fetches the pages' fills first (FILLS of attend_pages): with at least half
-// the chip's CUs busy and several pages per wave it is bound by its bytes (256 units x 64 pages of 16 slots,
+// Whether the attention over P pages fetches the pages' fills first (FILLS of attend_pages) in the flat step and by
+// itself: with at least half the chip's CUs busy and several pages per wave it is bound by its bytes (256 units x 64 pages of 16 slots,
 // fused step: 49.4 us without, 47.3 with); with few units by its round trips (8 units x 32 pages: 20.1
 // without, 20.6 with).
 static bool attend_by_fills(const Dev &d, int P) { return d.U >= 128 && P > 2 * (d.G == 8 ? 8 : 16); }

@@ -606,9 +606,14 @@ void launch_decode_hier(const Dev &d, const bf16_t *q, int cur, int P, int n_top
     }
     if (np_hint > d.max_pages) np_hint = d.max_pages;
     const int E = (d.max_pages + NW * 64 - 1) / (NW * 64);
-    // half the chip's CUs busy: the attention is bound by its bytes, and rows past a page's fill are not read (128
-    // units x 16 pages: 25.0 us per call without, 24.3 with); few units wait for the fills
-    const bool fills = d.U >= 128;
+    // Which form the attention takes.  In the general one the compiled code requests a page's values only when its first
+    // keys have come back; in the form that fetches the fills first all eight pieces of a block are under way at once, also
+    // where every wave has one page and no row is spared.  That is worth more here than the extra wait for the fills from
+    // 24 units on (the flat step draws its line elsewhere: attend_by_fills).  us per call, general and fills first: 256
+    // units x 16 pages 27.3 and 26.7, 128 x 16 24.4 and 23.8, 128 x 48 34.2 and 31.5, 64 x 16 23.5 and 23.1, 32 x 32 26.5
+    // and 25.9, 24 x 16 22.8 and 22.7; but 16 x 16 22.4 and 22.45, 8 x 16 22.2 and 22.35; eight query heads (eight waves
+    // with twice the registers) the same with either, 128 x 16 24.9 and 25.0.
+    const bool fills = d.U >= 24 && d.G < 8;
 #define ICE_HIER_T(g, nw, e, top, fills)                                                                             \
     do {                                                                                                             \
         allow_dynamic_lds((const void *)decode_hier_kernel<g, nw, e, top, fills>, lds);                              \
@@ -618,8 +623,8 @@ void launch_decode_hier(const Dev &d, const bf16_t *q, int cur, int P, int n_top
     } while (0)
 #define ICE_HIER(g, nw, e)                                                                                           \
     do {                                                                                                             \
-        if (n_top > 0) { if (fills) ICE_HIER_T(g, nw, e, true, true); else ICE_HIER_T(g, nw, e, true, false); }      \
-        else { if (fills) ICE_HIER_T(g, nw, e, false, true); else ICE_HIER_T(g, nw, e, false, false); }              \
+        if (n_top > 0) { if (fills) ICE_HIER_T(g, nw, e, true, (g < 8)); else ICE_HIER_T(g, nw, e, true, false); }   \
+        else { if (fills) ICE_HIER_T(g, nw, e, false, (g < 8)); else ICE_HIER_T(g, nw, e, false, false); }           \
     } while (0)
     if (d.G == 8) { if (E <= 8) ICE_HIER(8, 8, 8); else ICE_HIER(8, 8, 32); }
     else if (d.G == 4) { if (E <= 4) ICE_HIER(4, 16, 4); else ICE_HIER(4, 16, 16); }

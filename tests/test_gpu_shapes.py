@@ -263,6 +263,27 @@ def test_attention_split_over_workgroups_with_rows_beside_the_pages(U, G, s, bud
             assert np.abs(down(got).reshape(U, G, D)[u] - _attention_rows(qf[u], k, v)).max() <= ATTEND_TOL
 
 
+@pytest.mark.parametrize("U,G,s,budget,tops", [(23, 4, 16, 256, 0), (24, 4, 16, 640, 0), (24, 1, 64, 256, 0), (40, 2, 32, 256, 8), (40, 8, 16, 640, 0)])
+def test_attention_behind_a_staged_selection(U, G, s, budget, tops):
+    """Both forms of the attention that follow the staged selection in its launch, over its own pages."""
+    from paper_2604_10539_amd import IceIndex
+    w = datagen.small(n_tokens=2600, n_clusters=40, n_kv_heads=U, group_size=G, page_size=s, n_components=16)
+    K, V = datagen.keys_values(w)
+    ix = IceIndex(1, U, G, 2600, s, 40, kmeans_iters=1, init_idx=up(datagen.init_indices(w)))
+    ix.build_index(up(K), up(V))
+    q = datagen.queries(w)
+    if tops:
+        ix.build_top_level(tops)
+        ids, n_sel, out = (ix.select_hier3(up(q), budget, tops // 2, 30)[i] for i in (0, 1, -1))
+    else:
+        ids, n_sel, out = (ix.select_hier(up(q), budget, 30)[i] for i in (0, 1, -1))
+    ex = {k: down(v) for k, v in ix.export().items() if k != "view"}
+    qf = widen(q).astype(np.float64).reshape(U, G, D)
+    for u in range(U):
+        k, v = _listed_rows(ex, u, down(ids)[0, u], int(n_sel[0, u]))
+        assert len(k) and np.abs(down(out).reshape(U, G, D)[u] - _attention_rows(qf[u], k, v)).max() <= ATTEND_TOL
+
+
 @pytest.mark.parametrize("U,G,max_tok,built", [(1, 4, 1, True), (2, 8, 512, True), (8, 4, 513, True), (5, 1, 250, True), (40, 2, 300, True),
                                                 (2, 4, 600, False)])
 def test_attention_by_position(U, G, max_tok, built):
