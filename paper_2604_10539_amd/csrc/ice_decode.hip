@@ -924,7 +924,7 @@ static bool attend_by_fills(const Dev &d, int P) { return d.U >= 128 && P > 2 * 
 // the token positions of the listed pages, in list and slot order, padded with -1
 // One workgroup per unit, bound by two dependent round trips: the ids, then every page's fill and the positions in it
 // side by side (the first kTokPrefetch of a thread before the fills' scan); the fills are scanned in LDS.  (Walking
-// the list on one thread took 6.1 us for 32 units x 32 pages, this 4.1; 64 pages of 8 units, with two layers that reuse them, 49.4 and 40.1.)
+// the list on one thread took 6.1 us for 32 units x 32 pages, this 3.9.)
 constexpr int kTokThreads = 512, kTokPrefetch = 4;
 __global__ __launch_bounds__(kTokThreads) void selected_tokens_kernel(int P, int sh, int max_pages, const int *__restrict__ ids,
                                                                        const int *__restrict__ n_sel, const int *__restrict__ page_fill,
