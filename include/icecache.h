@@ -18,9 +18,9 @@
  *             ice_build_index COPIES K and V into page tiles; the originals may be freed.
  *   Streams   `stream` is a hipStream_t (NULL = default stream).  Every call only enqueues
  *             work; no call synchronises or reads device memory on the host.  Calls on one
- *             index must be issued in order on one stream (or be ordered by the caller): they
- *             share scratch in its workspace, also those that leave the index as it is
- *             (ice_attend_tokens alone does not).
+ *             index must be issued in order on one stream (or be ordered by the caller): most
+ *             use scratch in its workspace, also where they leave the index as it is.  Only
+ *             ice_attend_tokens does not touch the workspace and may overlap with other calls.
  *   Errors    Every call returns an ice_status_t and never throws or aborts.  All errors are
  *             detected on the host from the arguments and host-side counters BEFORE anything is
  *             enqueued; ice_last_error() returns a thread-local description of the last failure.
