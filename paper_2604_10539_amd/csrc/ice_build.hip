@@ -18,6 +18,17 @@ __device__ inline float dot2(uint32_t a, uint32_t b, float c) {
     return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, a), __builtin_bit_cast(bf16x2, b), c, false);
 }
 
+// inclusive sum over the wave on the vector unit (no trip through LDS)
+__device__ inline int wave_scan_add(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);  // row_shr 1, 2, 4, 8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);  // row_bcast 15 into rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // row_bcast 31 into rows 2 and 3
+    return x;
+}
+
 __device__ inline uint64_t splitmix64(uint64_t x) {
     x += 0x9E3779B97F4A7C15ull;
     x = (x ^ (x >> 30)) * 0xBF58476D1CE4E5B9ull;
@@ -94,6 +105,7 @@ __global__ __launch_bounds__(64) void init_centroids_kernel(Dev d, const bf16_t 
     const int c = blockIdx.x, u = blockIdx.y, lane = threadIdx.x;
     uint32_t *cb0 = (uint32_t *)(d.cent_bf16[cur] + ((size_t)u * d.Cpad + c) * kD);
     uint32_t *cb1 = (uint32_t *)(d.cent_bf16[cur ^ 1] + ((size_t)u * d.Cpad + c) * kD);
+    if (lane == 0) d.moved[(size_t)u * d.Cpad + c] = d.touched[(size_t)u * d.Cpad + c] = 0;
     if (c >= d.C) {
         cb0[lane] = 0u;
         cb1[lane] = 0u;
@@ -300,8 +312,10 @@ void launch_import(const Dev &d, const void *const *src, void *const *dst, const
     hipLaunchKernelGGL(import_kernel, dim3(a.copy_blocks + a.cluster_blocks + (unsigned)((state + 255) / 256)), dim3(256), 0, st, d, a);
 }
 
-__global__ void fill_u64_kernel(u64 *p, size_t n, u64 v) {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = v;
+// zero winners for a contraction whose slices meet by atomic maxima (go: a unit whose centroids stayed keeps its own)
+__global__ __launch_bounds__(256) void clear_winners_kernel(Dev d, int n, const int *go) {
+    const int u = blockIdx.y, i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n && (!go || go[2 * u] != 0)) d.packed[(size_t)u * d.max_tokens + i] = 0ull;
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -376,7 +390,7 @@ __host__ __device__ constexpr int assign_lds_bytes(bool aug) {
 template <int CT, int CW, bool AUG, bool FULL>
 __global__ __launch_bounds__(512) void assign_kernel(const bf16_t *__restrict__ K, const bf16_t *__restrict__ cent,
                                                       const float *__restrict__ cnorm, int n, int keys_per_wg, int zsplit,
-                                                      int Cpad, int cur, Dev d) {  // (scalars first: preloaded at wave start)
+                                                      int Cpad, int cur, const int *__restrict__ go, Dev d) {  // (scalars first: preloaded at wave start)
     constexpr int KW = 8 / CW;
     constexpr int KS = AUG ? 9 : 8;  // 16-wide steps of the contraction
     extern __shared__ __align__(16) char smem[];
@@ -434,6 +448,7 @@ __global__ __launch_bounds__(512) void assign_kernel(const bf16_t *__restrict__ 
         }
     }
 
+    const int goes = go ? go[2 * u] : 1;
     // The first key tile travels through registers (it is requested before the centroid block is
     // staged in the very buffers it goes to); every later tile goes straight to LDS.
     uint32_t stage_aug = 0;  // (AUG) extra coordinate of key `tid` of the next tile, threads 0..255
@@ -469,6 +484,7 @@ __global__ __launch_bounds__(512) void assign_kernel(const bf16_t *__restrict__ 
         first[i] = ((const u32x4 *)(Ku + (size_t)key * kD))[ch];
     }
     load_aug(0);
+    if (goes == 0) return;  // (a later round of a unit whose centroids stayed: every winner stands)
 #pragma unroll
     for (int i = 0; i < R / 32; ++i) {
         const int id = tid + 512 * i, row = id >> 4, ch = id & 15;
@@ -573,8 +589,8 @@ __global__ __launch_bounds__(512) void assign_kernel(const bf16_t *__restrict__ 
         ICE_BSTAMP(2 + 2 * (t & 3));
         ICE_WSTAMP(t, 1);
         if (t + 1 < ntiles) {
-            store_aug(buf ^ 1);
             wait_lds_dma();  // this wave's share of the next tile is in LDS
+            store_aug(buf ^ 1);
         }
         ICE_WSTAMP(t, 2);
         __syncthreads();
@@ -598,8 +614,27 @@ __global__ __launch_bounds__(512) void assign_kernel(const bf16_t *__restrict__ 
 // Slices of at most 512 centroids (blockIdx.y) that meet through an atomic maximum in `packed`.
 int assign_slices(const Dev &d) { return (d.Cpad + 511) / 512; }
 
-// clear: with several slices the winners start from zero, here or (between Lloyd rounds) by the sort that read them
-void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, bool clear, hipStream_t st) {
+// Key tiles per workgroup: the run for which the chip's rounds of 256 workgroups, each its tiles plus a prologue worth
+// about one, come out shortest (as for assign_kernel, whose grid also counts the slices).
+static int assign_run(int U, int n, int slices) {
+    const int ktiles = (n + kAssignTile - 1) / kAssignTile;
+    int run = 1;
+    long long best_cost = -1;
+    for (int g = 1; g <= ktiles && g <= 4096; ++g) {  // g workgroups per unit and slice
+        const int r = (ktiles + g - 1) / g;
+        const long long wgs = (long long)((ktiles + r - 1) / r) * slices * U;
+        const long long cost = (wgs + 255) / 256 * (r + 1);
+        if (best_cost < 0 || cost < best_cost) { best_cost = cost; run = r; }
+        if (wgs > 256 * 64) break;  // (more, shorter runs only repeat the prologue)
+    }
+    return run;
+}
+
+// (with several slices the winners start from zero)
+// whether a centroid of the unit moved in the round before round t: element 2 u of the result (all units go in the first round)
+static const int *round_goes(const Dev &d, int t) { return t > 0 ? d.any_moved + ((t - 1) & 1) : nullptr; }
+
+void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, int t, hipStream_t st) {
     const int tiles = d.Cpad / 32;
     int CT = tiles == 1 ? 1 : 2, CW = 1;
     while (CW < 8 && CW * CT < tiles) CW *= 2;
@@ -610,29 +645,18 @@ void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, bool clear, hi
     // 16 units x 92 tiles, 12 of 16 centroid tiles, transformed, are 192 workgroups of 8 tiles and took
     // 56 us, 256 of 6 with the tiles dealt over the SIMDs 43; a ten-round build of 8 units x 40001 keys
     // with 625 clusters, 160 workgroups of 8 tiles against 256 of 10, 1314 us against 1031.)
-    const int ktiles = (n + kAssignTile - 1) / kAssignTile;
-    int run = 1;
-    long long best_cost = -1;
-    for (int g = 1; g <= ktiles && g <= 4096; ++g) {  // g workgroups per unit and slice
-        const int r = (ktiles + g - 1) / g;
-        const long long wgs = (long long)((ktiles + r - 1) / r) * zsplit * d.U;
-        const long long cost = (wgs + 255) / 256 * (r + 1);
-        if (best_cost < 0 || cost < best_cost) { best_cost = cost; run = r; }
-        if (wgs > 256 * 64) break;  // (more, shorter runs only repeat the prologue)
-    }
-    const int keys_per_wg = run * kAssignTile;
+    const int keys_per_wg = assign_run(d.U, n, zsplit) * kAssignTile;
     dim3 grid((n + keys_per_wg - 1) / keys_per_wg, zsplit, d.U);
     const size_t lds = assign_lds_bytes(d.tk != 0);
-    if (zsplit > 1 && clear) {
-        const size_t tot = (size_t)d.U * d.max_tokens;
-        hipLaunchKernelGGL(fill_u64_kernel, dim3(1024), dim3(256), 0, st, d.packed, tot, 0ull);
+    if (zsplit > 1) {
+        hipLaunchKernelGGL(clear_winners_kernel, dim3((n + 255) / 256, d.U), dim3(256), 0, st, d, n, round_goes(d, t));
     }
     const bool full = tiles % (CT * CW) == 0;
 #define ICE_ASSIGN_F(ct, cw, aug, full)                                                             \
     do {                                                                                            \
         allow_dynamic_lds((const void *)assign_kernel<ct, cw, aug, full>, lds);                     \
         hipLaunchKernelGGL((assign_kernel<ct, cw, aug, full>), grid, dim3(512), lds, st, K, d.cent_bf16[cur], d.cnorm[cur], n, \
-                           keys_per_wg, zsplit, d.Cpad, cur, d);                                    \
+                           keys_per_wg, zsplit, d.Cpad, cur, round_goes(d, t), d);                  \
     } while (0)
 #define ICE_ASSIGN_A(ct, cw, aug)                                                                   \
     do {                                                                                            \
@@ -652,6 +676,369 @@ void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, bool clear, hi
 #undef ICE_ASSIGN
 #undef ICE_ASSIGN_A
 #undef ICE_ASSIGN_F
+}
+
+// ------------------------------------------------------------------------------------------------
+// The assignment of a later round.  Between two rounds most centroids stay where they are, bit for bit (clusters of
+// about 64 keys in 128 dimensions settle fast: of 512 clusters over 32768 keys of the benchmark's mixture 79 % moved
+// after the first round, 50 % after the second, 29, 18, 5, 2 and below 1 % after that), and a score is the
+// same bits whichever slot of the matrix instruction it comes out of.  So the winner among the centroids that did not
+// move is known from the last round for every key whose own centroid did not, and what the full contraction
+// would leave in `packed` follows from less of it:
+//   moved  every key against the moved centroids only (`d.moved`, listed in ascending id in LDS), winner m.  With `old` the
+//          last round's winner (score, ~id), which no centroid that stayed can beat:
+//            m >  old: m;   m <= old and old's centroid stayed: old;   m == old (its score came out the same): old;
+//            m <  old and old's centroid moved: a centroid that stayed may lie between, the key is listed;
+//   again  the listed keys, gathered, against all centroids.  (A key without a comparable score goes here too: what the
+//          contraction leaves of one depends on all scores of a tile.)
+// A unit of which more than three quarters of the centroids moved takes all keys against all centroids at once.
+// One workgroup takes a run of 256-key tiles through all of this; more than 512 centroids are slices that it takes one
+// after the other, its keys' winners so far in `tmp`.  A slice of few tiles splits the keys among the waves instead of
+// the centroids (slice<CW>: CW waves share the centroids of a key).  Bound as assign_kernel is while many centroids
+// move, by the read of the keys once few do.
+// `tmp` and the key lists are scratch at the start of the unit's key tiles, 12 of the 256 bytes per token that the page
+// layout overwrites in any case.
+enum { kAllCentroids = 0, kMovedCentroids = 1, kListedKeys = 2 };  // what a pass over the keys is about
+__host__ __device__ inline int reassign_lds_bytes(bool aug, int Cpad) {
+    return 2 * 256 * 256 + 2 * 256 * 8 + 512 * 4 + (aug ? 1024 * 4 : 0) + Cpad * 2 + Cpad / 8;
+}
+__device__ inline bool ordered_is_nan(uint32_t k) { return k > 0xFF800000u || k < 0x007FFFFFu; }
+
+template <bool AUG>
+__global__ __launch_bounds__(512) void reassign_kernel(const bf16_t *__restrict__ K, const bf16_t *__restrict__ cent,
+                                                       const float *__restrict__ cnorm, int n, int keys_per_wg, int Cpad, int cur,
+                                                       int C, const int *__restrict__ go, Dev d) {  // (scalars first: preloaded at wave start)
+    constexpr int KS = AUG ? 9 : 8;
+    extern __shared__ __align__(16) char smem[];
+    char *keys = smem;                                             // [2][256][256 B], chunks swizzled as in assign_kernel
+    u64 *best = (u64 *)(smem + 2 * kAssignTile * 256);             // [2][256]
+    float *seeds = (float *)(best + 2 * kAssignTile);              // [512] of the slice at hand
+    uint32_t *kext = (uint32_t *)(seeds + 512);                    // (AUG) [2][256] the keys' extra coordinates
+    uint32_t *cext = kext + 2 * kAssignTile;                       // (AUG) [512] the centroids' of the slice at hand
+    uint16_t *list = (uint16_t *)(kext + (AUG ? 1024 : 0));        // [Cpad] moved centroids, ascending
+    uint16_t *bits = list + Cpad;                                  // [Cpad / 16] the same as a mask
+    __shared__ int sh_wave[8], sh_fails;
+    auto slot = [](int r, int c) { return r * 256 + ((c ^ (r & 15)) << 4); };
+
+    const int u = blockIdx.y;
+    int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int k0 = blockIdx.x * keys_per_wg;
+    const bf16_t *Ku = K + (size_t)u * n * kD;
+    u64 *packed = d.packed + (size_t)u * d.max_tokens;
+    u64 *tmp = (u64 *)(d.Kp + (size_t)u * d.max_pages * d.s * kD);
+    uint32_t *fails = (uint32_t *)(tmp + n) + k0;
+
+    // the pass at hand: job, number of keys and of centroids
+    int job = kMovedCentroids, nk = min(n, k0 + keys_per_wg) - k0, ncent = 0;
+    auto key_of = [&](int pos) -> int {
+        int key = k0 + min(pos, nk - 1);
+        if (job == kListedKeys) {
+            key = (int)fails[min(pos, nk - 1)];
+            asm volatile("" : "+v"(key));  // (see rows_of)
+        }
+        return key;
+    };
+    // this thread's rows of a key tile (eight, 32 apart).  (The listed keys are waited for where they are loaded: left to
+    // the compiler the wait is at every use, in the other passes too, and each key row waits for the one before.)
+    auto rows_of = [&](int t, int (&key)[8]) {
+        const int base = t * kAssignTile + (tid >> 4);
+        if (job == kListedKeys) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) key[i] = (int)fails[min(base + 32 * i, nk - 1)];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(key[i]));
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) key[i] = k0 + min(base + 32 * i, nk - 1);
+        }
+    };
+
+    // ---- which centroids moved
+    {
+        const int lane = tid & 63, goes = go[2 * u];
+        uint32_t m = 0;
+        if (tid * 16 < Cpad) {
+            const uint4 w = ((const uint4 *)(d.moved + (size_t)u * Cpad))[tid];
+            auto nibble = [](uint32_t x) { return (x & 1u) | (x >> 7 & 2u) | (x >> 14 & 4u) | (x >> 21 & 8u); };
+            m = nibble(w.x) | nibble(w.y) << 4 | nibble(w.z) << 8 | nibble(w.w) << 12;
+            bits[tid] = (uint16_t)m;
+        }
+        if (goes == 0) return;  // (none: every winner stands)
+        const int cnt = __popc(m), incl = wave_scan_add(cnt);
+        if (lane == 63) sh_wave[wave] = incl;
+        if (tid == 0) sh_fails = 0;
+        if (tid < 2 * kAssignTile) best[tid] = 0ull;
+        __syncthreads();
+        int pos = incl - cnt;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) {
+            const int x = sh_wave[w];
+            pos += w < wave ? x : 0;
+            ncent += x;
+        }
+        for (; m; m &= m - 1) list[pos++] = (uint16_t)(tid * 16 + __ffs(m) - 1);
+        ncent = __builtin_amdgcn_readfirstlane(ncent);
+        // (in tiles of 256 keys x 512 centroids, `steps` of them the whole contraction: the listed keys are about 0.45 of the
+        // moved share, their pass a prologue worth about 1.15 more)
+        const int steps = (nk + kAssignTile - 1) / kAssignTile * ((Cpad + 511) / 512);
+        if (145 * ncent >= C * (100 - 115 / steps)) {
+            job = kAllCentroids;
+            ncent = Cpad;
+        }
+        __syncthreads();
+    }
+
+    auto slice = [&](auto cw_arg, auto full_arg, int c0) __attribute__((always_inline)) {
+        constexpr int CW = decltype(cw_arg)::value, KW = 8 / CW, NSUB = 8 / KW, R = CW * 64;
+        constexpr bool FULL = decltype(full_arg)::value;
+        // (opaque in every slice: hoisted out of the forms and the loops, the lanes' addresses would not fit the registers)
+        asm volatile("" : "+v"(tid));
+        const int lane = tid & 63, col = lane & 31, half = lane >> 5;
+        constexpr int CS = FULL ? 1 : CW;  // distance between a wave's two tiles (dealt over the SIMDs as in assign_kernel)
+        const int kw = wave / CW, cw = FULL || CW == 8 ? wave % CW : (wave + (wave >> 2) * (CW / 2)) % CW;
+        const int wt0 = FULL ? cw * 2 : cw, nt = (min(512, ncent - c0) + 31) / 32;
+        const int ctv = wt0 >= nt ? 0 : wt0 + CS < nt ? 2 : 1;
+        const bool last = c0 + 512 >= ncent;
+        const int ntiles = (nk + kAssignTile - 1) / kAssignTile;
+        auto centroid = [&](int pos) { return job == kMovedCentroids ? (int)list[pos] : pos; };
+        // ---- prologue: the slice's centroid rows through LDS into the waves' operand registers (the first key tile goes
+        // through registers: the rows are staged where it belongs)
+        u32x4 first[8];
+        {
+            int key[8];
+            rows_of(0, key);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) first[i] = ((const u32x4 *)(Ku + (size_t)key[i] * kD))[tid & 15];
+        }
+        uint4 cst[R / 32];
+#pragma unroll
+        for (int i = 0; i < R / 32; ++i) {
+            const int id = tid + 512 * i, pos = c0 + (id >> 4);
+            const uint4 w = ((const uint4 *)(cent + ((size_t)u * Cpad + centroid(min(pos, ncent - 1))) * kD))[id & 15];
+            cst[i] = pos < ncent ? w : make_uint4(0, 0, 0, 0);
+        }
+        float seed_in = -INFINITY;
+        uint32_t cext_in = 0u, kext_in = 0u;
+        if (tid < R && c0 + tid < ncent) {
+            const int c = centroid(c0 + tid);
+            seed_in = -0.5f * cnorm[(size_t)u * Cpad + c];
+            if constexpr (AUG) cext_in = d.caug[cur][(size_t)u * Cpad + c];
+        }
+        auto load_aug = [&](int t) {
+            if constexpr (AUG) {
+                const int pos = t * kAssignTile + tid;
+                kext_in = tid < kAssignTile && pos < nk ? d.kaug[(size_t)u * d.max_tokens + key_of(pos)] : 0u;
+            }
+        };
+        auto store_aug = [&](int buf) {
+            if constexpr (AUG) {
+                if (tid < kAssignTile) kext[buf * kAssignTile + tid] = kext_in;
+            }
+        };
+        load_aug(0);
+#pragma unroll
+        for (int i = 0; i < R / 32; ++i) {
+            const int id = tid + 512 * i;
+            *(uint4 *)(keys + slot(id >> 4, id & 15)) = cst[i];
+        }
+        if (tid < R) {
+            seeds[tid] = seed_in;
+            if constexpr (AUG) cext[tid] = cext_in;
+        }
+        __syncthreads();
+        bf16x8 A[2][KS];
+        f32x16 seed[2];
+#pragma unroll
+        for (int ct = 0; ct < 2; ++ct) {
+            const int t0 = (wt0 + ct * CS) * 32, r = t0 + col;
+#pragma unroll
+            for (int ks = 0; ks < 8; ++ks) A[ct][ks] = __builtin_bit_cast(bf16x8, *(const uint4 *)(keys + slot(r, 2 * ks + half)));
+            if constexpr (AUG) A[ct][8] = __builtin_bit_cast(bf16x8, make_uint4(half ? 0u : cext[r], 0, 0, 0));
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float4 w = *(const float4 *)(seeds + t0 + 8 * v + 4 * half);
+                seed[ct][4 * v] = w.x; seed[ct][4 * v + 1] = w.y; seed[ct][4 * v + 2] = w.z; seed[ct][4 * v + 3] = w.w;
+            }
+        }
+        __syncthreads();  // every wave holds its fragments before the first key tile overwrites them
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int id = tid + 512 * i;
+            *(u32x4 *)(keys + slot(id >> 4, id & 15)) = first[i];
+        }
+        store_aug(0);
+        __syncthreads();
+        uint32_t frag[8];
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) frag[ks] = (uint32_t)slot(col, 2 * ks + half);
+        const uint32_t inv0 = 0xFFFFFFFFu - (uint32_t)(c0 + wt0 * 32 + 4 * half);  // low word of a winner: ~(place in the list)
+
+        for (int t = 0; t < ntiles; ++t) {
+            const int buf = t & 1;
+            u64 *bestt = best + buf * kAssignTile;
+            asm volatile("" : "+v"(tid));
+            if (t + 1 < ntiles) {
+                const int ch = tid & 15, r16 = (tid >> 4) & 15;
+                int key[8];
+                rows_of(t + 1, key);
+                load_aug(t + 1);
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                    lds_dma16((const uint4 *)(Ku + (size_t)key[i] * kD) + (ch ^ r16), keys + (buf ^ 1) * (kAssignTile * 256) + (4 * wave + 32 * i) * 256);
+            }
+            // (the last slice of the moved centroids: what the tile's keys are compared with, in flight during the contraction)
+            u64 old = 0ull, sofar = 0ull;
+            if (job == kMovedCentroids && last && tid < kAssignTile) {
+                const int key = key_of(t * kAssignTile + tid);
+                old = packed[key];
+                if (c0 > 0) sofar = tmp[key];
+            }
+            auto load_b = [&](int i, bf16x8 (&dst)[KS]) {
+                const char *sub = keys + buf * (kAssignTile * 256) + (kw + i * KW) * 32 * 256;
+#pragma unroll
+                for (int ks = 0; ks < 8; ++ks) dst[ks] = __builtin_bit_cast(bf16x8, *(const uint4 *)(sub + frag[ks]));
+                if constexpr (AUG) {
+                    const uint32_t e = kext[buf * kAssignTile + (kw + i * KW) * 32 + col];
+                    dst[8] = __builtin_bit_cast(bf16x8, make_uint4(half ? 0u : e, 0, 0, 0));
+                }
+            };
+            auto chain = [&](int ct, const bf16x8 (&b)[KS], f32x16 &dst) {
+                dst = seed[ct];
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) dst = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[ct][ks], b[ks], dst, 0, 0, 0);
+            };
+            float sv = 0.f;
+            uint32_t sidx = 0;
+            auto reduce = [&](const f32x16 &acc, int i, int ct, int ctv_of) {  // as in assign_kernel
+                float m;
+                uint32_t li;
+                argmax16(acc, m, li);
+                asm("" : "+v"(li));  // (worked out in any case: as a branch around its selects it ends the pipeline of chains)
+                if (ct == 0) {
+                    sv = m;
+                    sidx = li;
+                } else {
+                    const bool gt = m > sv;
+                    sv = gt ? m : sv;
+                    sidx = gt ? li + 32u * CS * ct : sidx;
+                }
+                if (ct == ctv_of - 1)
+                    atomicMax(&bestt[(kw + i * KW) * 32 + col], ((u64)f32_ordered(sv + 0.0f) << 32) | (u64)(inv0 - sidx));
+            };
+            const int subs = min(8, (nk - t * kAssignTile + 31) / 32);  // 32-key sub-tiles with keys
+            auto compute = [&](auto tiles_held) __attribute__((always_inline)) {
+                constexpr int CTV = decltype(tiles_held)::value, NSLOT = NSUB * CTV;
+                if (subs > 4) {  // (the software pipeline of assign_kernel)
+                    bf16x8 B[2][KS];
+                    f32x16 acc[2];
+                    load_b(0, B[0]);
+                    if (CTV == 1 && NSUB > 1) load_b(1, B[1]);
+                    chain(0, B[0], acc[0]);
+#pragma unroll
+                    for (int j = 0; j < NSLOT; ++j) {
+                        const int i = j / CTV, ct = j % CTV, i1 = (j + 1) / CTV;
+                        if ((j + 2) % CTV == 0 && (j + 2) / CTV < NSUB && (j + 2) / CTV >= 1 && !(CTV == 1 && j + 2 == 1))
+                            load_b((j + 2) / CTV, B[((j + 2) / CTV) & 1]);
+                        if (j + 1 < NSLOT) chain((j + 1) % CTV, B[i1 & 1], acc[(j + 1) & 1]);
+                        reduce(acc[j & 1], i, ct, CTV);
+                    }
+                } else {  // a tile of few keys: no work for the empty sub-tiles
+                    for (int i = 0; kw + i * KW < subs; ++i) {
+                        bf16x8 B[KS];
+                        f32x16 acc[CTV];
+                        load_b(i, B);
+#pragma unroll
+                        for (int ct = 0; ct < CTV; ++ct) chain(ct, B, acc[ct]);
+#pragma unroll
+                        for (int ct = 0; ct < CTV; ++ct) reduce(acc[ct], i, ct, CTV);
+                    }
+                }
+            };
+            if (FULL || ctv == 2) compute(std::integral_constant<int, 2>{});  // (wave-uniform)
+            else if (ctv == 1) compute(std::integral_constant<int, 1>{});
+            if (t + 1 < ntiles) {
+                wait_lds_dma();
+                asm volatile("" : "+v"(kext_in));
+                store_aug(buf ^ 1);
+            }
+            // (what was requested ahead counts as arrived here for every lane: a wait left for a later place would also
+            // cover the next tile's direct loads)
+            asm volatile("" : "+v"(old), "+v"(sofar));
+            __syncthreads();
+            // the tile's winners, first 256 threads (a key's are the same thread's in every slice)
+            if (tid < kAssignTile) {
+                const int pos = t * kAssignTile + tid;
+                const bool valid = pos < nk;
+                bool fail = false;
+                const int key = key_of(pos);
+                u64 b = bestt[tid];
+                bestt[tid] = 0ull;
+                if (valid && !(job == kMovedCentroids && last)) {
+                    u64 *dst = (job == kMovedCentroids ? tmp : packed) + key;
+                    if (c0 > 0) atomicMax(dst, b);  // (nothing waits for it)
+                    else *dst = b;
+                } else if (valid) {
+                    b = max(b, sofar);
+                    const uint32_t at = ~(uint32_t)b, own = min(~(uint32_t)old, (uint32_t)Cpad - 1u);
+                    const uint32_t id = at < (uint32_t)ncent ? list[at] : 0x7FFFFFFFu;  // (a place past the list: no centroid)
+                    const u64 m = (b & 0xFFFFFFFF00000000ull) | (u64)(0xFFFFFFFFu - id);
+                    const bool own_moved = (bits[own >> 4] >> (own & 15u)) & 1u;
+                    fail = ordered_is_nan((uint32_t)(b >> 32)) || ordered_is_nan((uint32_t)(old >> 32)) || (own_moved && m < old);
+                    if (!fail && m > old) packed[key] = m;
+                }
+                if (job == kMovedCentroids && last) {
+                    const u64 f = __ballot(fail);
+                    int at = 0;
+                    if (lane == 0 && f) at = atomicAdd(&sh_fails, (int)__popcll(f));
+                    at = __builtin_amdgcn_readfirstlane(at);
+                    if (fail) fails[at + (int)__popcll(f & ((1ull << lane) - 1ull))] = (uint32_t)key;
+                }
+            }
+        }
+    };
+    for (;;) {
+        for (int c0 = 0; c0 < ncent; c0 += 512) {
+            const int nt = (min(512, ncent - c0) + 31) / 32;
+            if (nt <= 2) slice(std::integral_constant<int, 1>{}, std::false_type{}, c0);
+            else if (nt <= 4) slice(std::integral_constant<int, 2>{}, std::false_type{}, c0);
+            else if (nt <= 8) slice(std::integral_constant<int, 4>{}, std::false_type{}, c0);
+            else if (nt < 16) slice(std::integral_constant<int, 8>{}, std::false_type{}, c0);
+            else slice(std::integral_constant<int, 8>{}, std::true_type{}, c0);
+        }
+        if (job != kMovedCentroids) return;
+        wait_vmem();  // (the key lists of all waves are read by all)
+        __threadfence_block();
+        __syncthreads();
+        nk = __builtin_amdgcn_readfirstlane(sh_fails);
+        if (nk == 0) return;
+        job = kListedKeys;
+        ncent = Cpad;
+    }
+}
+
+// Round t by reassign_kernel instead of assign_kernel: from the third on (the first means move nearly all centroids) and
+// where the whole contraction is at least four tiles of 256 keys x 512 centroids per workgroup.  Measured, us per round, whole
+// contraction and rounds 2, 3, ... so: 8 units x 32768 x 512 (four tiles) 34 and 38, 41, 33, 27, 24, 23, 22, 22; 8 x 131072 x 2048
+// (64) 420 and 476, 480, 428, 290, 194, 150, 110, 97; but 8 x 16384 x 256 (one) 13 and 21, 19, 16, 15, 15.
+bool reassign_pays(const Dev &d, int n, int t) {
+    const int tiles = d.Cpad / 32, full = tiles / 16, rest = tiles % 16;
+    return t >= 2 && assign_run(d.U, n, 1) * (16 * full + rest) >= 64;
+}
+
+void launch_reassign(const Dev &d, const bf16_t *K, int n, int cur, int t, hipStream_t st) {
+    const int keys_per_wg = assign_run(d.U, n, 1) * kAssignTile;
+    const size_t lds = reassign_lds_bytes(d.tk != 0, d.Cpad);
+    const dim3 grid((n + keys_per_wg - 1) / keys_per_wg, d.U);
+#define ICE_REASSIGN(aug)                                                                                                  \
+    do {                                                                                                                   \
+        allow_dynamic_lds((const void *)reassign_kernel<aug>, lds);                                                        \
+        hipLaunchKernelGGL((reassign_kernel<aug>), grid, dim3(512), lds, st, K, d.cent_bf16[cur], d.cnorm[cur], n, keys_per_wg, d.Cpad, \
+                           cur, d.C, round_goes(d, t), d);                                                                 \
+    } while (0)
+    if (d.tk) ICE_REASSIGN(true);
+    else ICE_REASSIGN(false);
+#undef ICE_REASSIGN
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -696,23 +1083,40 @@ size_t sort_ranges_max(int U, int max_tokens, int Cpad) {
 // cluster in LDS (OR, read back, clear) instead of by ballots: cheaper per group, but the masks have to be cleared and
 // take 8 more bytes per counter, so it is for long ranges (256 units x 32768 tokens: 78 us with ballots, 69 so).
 template <int NG, bool MASK>
-__global__ __launch_bounds__(1024) void range_sort_kernel(Dev d, int n, int L, int W, int nbits, int clear, float *best_out,
+__global__ __launch_bounds__(1024) void range_sort_kernel(Dev d, int n, int L, int W, int nbits, int round, float *best_out,
                                                           int *assign_out) {
     extern __shared__ __align__(16) int pos_all[];  // [W][Cpad]
     __shared__ int wsum[16];
     __shared__ int carry;
     const int r = blockIdx.x, R = gridDim.x, u = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int Cpad = d.Cpad;
+    const int goes = round > 0 ? d.any_moved[2 * u + ((round - 1) & 1)] : 1;
+    if (r == 0 && tid == 0) d.any_moved[2 * u + (round & 1)] = 0;  // (for this round's means)
     const int rb = r * L, re = min(n, rb + L), seg = L / W;
     // low word of a packed winner = ~cluster id (the high word, the score, is read only for best_out)
-    u64 *packed = d.packed + (size_t)u * d.max_tokens;
-    const uint32_t *pk = (const uint32_t *)packed;
+    const uint32_t *pk = (const uint32_t *)(d.packed + (size_t)u * d.max_tokens);
     const int beg = min(re, rb + wave * seg), end = wave < W ? min(re, beg + seg) : beg;  // this wave's tokens
     uint32_t v[NG];
+    constexpr bool AHEAD = NG <= 16;  // (the registers of the longest form do not hold the last round's clusters as well)
+    int was[AHEAD ? NG : 1];
 #pragma unroll
     for (int j = 0; j < NG; ++j) {
         const int i = beg + j * 64 + lane;
         v[j] = i < end ? pk[2 * i] : 0u;
+        if constexpr (AHEAD) was[j] = round > 0 && i < end ? d.assign[(size_t)u * d.max_tokens + i] : 0;
+    }
+    if (goes == 0) return;  // (no centroid moved: nor did a token)
+    if (round > 0) {  // a later round of a build: the clusters that lost or gained a token are marked
+        // (a range without such a token could be left as it is, but finding that out for the whole workgroup takes as long
+        // as sorting 1024 tokens: 6.3 us with the exit taken or not)
+#pragma unroll
+        for (int j = 0; j < NG; ++j) {
+            const int i = beg + j * 64 + lane;
+            if (i < end) {
+                const int a = (int)min(0xFFFFFFFFu - v[j], (uint32_t)d.C - 1u), b = AHEAD ? was[AHEAD ? j : 0] : d.assign[(size_t)u * d.max_tokens + i];
+                if (a != b) d.touched[(size_t)u * Cpad + a] = d.touched[(size_t)u * Cpad + b] = 1;
+            }
+        }
     }
     for (int x = tid; x < W * Cpad / 4 * (MASK ? 3 : 1); x += 1024) ((int4 *)pos_all)[x] = make_int4(0, 0, 0, 0);  // (Cpad is a multiple of 32)
     if (tid == 0) carry = 0;
@@ -752,7 +1156,6 @@ __global__ __launch_bounds__(1024) void range_sort_kernel(Dev d, int n, int L, i
             d.assign[(size_t)u * d.max_tokens + i] = a;
             if (assign_out) assign_out[(size_t)u * n + i] = a;
             if (best_out) best_out[(size_t)u * n + i] = -2.0f * ordered_f32(pk[2 * i + 1]);
-            if (clear) packed[i] = 0ull;
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // (the LDS unit executes a wave's accesses in order)
     }
@@ -798,17 +1201,16 @@ __global__ __launch_bounds__(1024) void range_sort_kernel(Dev d, int n, int L, i
     }
 }
 
-void launch_sort(const Dev &d, int n, bool clear, float *best_out, int *assign_out, hipStream_t st) {
+void launch_sort(const Dev &d, int n, int t, float *best_out, int *assign_out, hipStream_t st) {
     const int L = sort_range_len(d.U, n, d.Cpad), R = (n + L - 1) / L, W = sort_segments(d.Cpad);
     int nbits = 0;
     while ((1 << nbits) < d.Cpad) ++nbits;
     const bool masks = L / W > 4 * 64 && W * d.Cpad * 3 <= kSortCounters;
     const size_t lds = (size_t)W * d.Cpad * (masks ? 12 : 4);
-    clear = clear && assign_slices(d) > 1;
 #define ICE_SORT(ng, mk)                                                                                                   \
     do {                                                                                                                   \
         allow_dynamic_lds((const void *)range_sort_kernel<ng, mk>, lds);                                                   \
-        hipLaunchKernelGGL((range_sort_kernel<ng, mk>), dim3(R, d.U), dim3(1024), lds, st, d, n, L, W, nbits, clear ? 1 : 0, best_out, assign_out); \
+        hipLaunchKernelGGL((range_sort_kernel<ng, mk>), dim3(R, d.U), dim3(1024), lds, st, d, n, L, W, nbits, t, best_out, assign_out); \
     } while (0)
     if (L / W <= 4 * 64) ICE_SORT(4, false);
     else if (L / W <= 16 * 64) { if (masks) ICE_SORT(16, true); else ICE_SORT(16, false); }
@@ -816,16 +1218,6 @@ void launch_sort(const Dev &d, int n, bool clear, float *best_out, int *assign_o
 #undef ICE_SORT
 }
 
-// inclusive sum over the wave on the vector unit (no trip through LDS)
-__device__ inline int wave_scan_add(int x) {
-    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);  // row_shr 1, 2, 4, 8
-    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);
-    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);  // row_bcast 15 into rows 1 and 3
-    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // row_bcast 31 into rows 2 and 3
-    return x;
-}
 // The members of cluster c in ascending position, out of the ranges' sorted pieces: member j sits in the last piece that
 // starts at or before it.  A wave holds 64 pieces at a time, one per lane: `first` = members in the pieces before the lane's
 // own, `from` = index into the unit's `order` of its first one.  Nothing is kept per range, so any number of ranges will do.
@@ -835,8 +1227,11 @@ struct Pieces {
     __device__ uint32_t word(int r) const { return r < R ? off[(size_t)r * Cpad] : 0u; }
     // pieces r0 .. r0 + 63, `before` members in front of them; returns the members up to their end (the same on every lane)
     __device__ int load(int r0, int lane, int before, int &first, int &from, int &cnt) const {
+        return take(word(r0 + lane), r0, lane, before, first, from, cnt);
+    }
+    // ... of which the lane's word is at hand
+    __device__ int take(uint32_t o, int r0, int lane, int before, int &first, int &from, int &cnt) const {
         const int r = r0 + lane;
-        const uint32_t o = word(r);
         cnt = (int)(o & 0xFFFFu);
         const int incl = wave_scan_add(cnt);
         first = before + incl - cnt;
@@ -869,12 +1264,12 @@ struct Pieces {
 // as long as they fit and no piece has more than kMemberPiece of them (*listed): one read per member instead of a search.
 constexpr int kMemberSlots = 512, kMemberPiece = 32, kFewPieces = 8;
 constexpr int kAugAlone = 256, kAugChunk = 1024;
-__device__ inline int list_members(const Pieces &pieces, int lane, int *slots, bool *listed) {
+__device__ inline int list_members(const Pieces &pieces, uint32_t word0, int lane, int *slots, bool *listed) {
     int total = 0;
     bool ok = true;
     for (int r0 = 0; r0 < pieces.R; r0 += 64) {
         int first, from, cnt;
-        total = pieces.load(r0, lane, total, first, from, cnt);
+        total = pieces.take(r0 == 0 ? word0 : pieces.word(r0 + lane), r0, lane, total, first, from, cnt);
         ok = ok && total <= kMemberSlots && __ballot(cnt > kMemberPiece) == 0ull;
         for (int e = 0; ok && __ballot(e < cnt) != 0ull; ++e)
             if (e < cnt) slots[first + e] = from + e;
@@ -904,22 +1299,41 @@ static bool keys_exceed_cache(const Dev &d, int n) { return (size_t)d.U * (size_
 // 59 through LDS, 56.4, 53.5; 8 units x 131072 x 2048, 32 pieces, 61.7, 60.7, 55; 2 x 131072 x 64, clusters of thousands, 131, 108, 103.
 // (Eight waves per SIMD: 256 units 418 us with seven; the last form keeps two registers in scratch for it, 62 -> 60.6 at 8 units.)
 template <bool STREAM, int NP>
-__global__ __launch_bounds__(256, 8) void means_kernel(Dev d, const bf16_t *__restrict__ K, int n, int cur, int R, int L) {
+__global__ __launch_bounds__(256, 8) void means_kernel(Dev d, const bf16_t *__restrict__ K, int n, int cur, int R, int L, int round) {
     __shared__ float4 part_sum[3][16][2];
     __shared__ int slots[kMemberSlots], sh_cnt, sh_listed;
     __shared__ float aug_lds[kAugChunk];
     const int u = blockIdx.y, c = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int g = lane >> 4, ch = lane & 15;
+    const size_t row = (size_t)u * d.Cpad + c;
     const int *order = d.order + (size_t)u * d.max_tokens;
     const Pieces pieces = {d.range_off + (size_t)u * R * d.Cpad + c, d.Cpad, R, L};
+    // (requested ahead of the flags, which mostly say that it was in vain, late in a build)
+    uint32_t word0 = pieces.word(NP == 1 ? 0 : lane);
+    if (round > 0) {
+        const int goes = d.any_moved[2 * u + ((round - 1) & 1)], touched = d.touched[row], had_moved = d.moved[row];
+        asm volatile("" : "+v"(word0));
+        if (goes == 0) return;  // (no centroid of the unit moved in the last round: both buffers hold the same, no token moved)
+        if (touched == 0) {     // the members of the last round: the same mean
+            if (wave == 0 && had_moved != 0) {
+                if (g == 0) ((uint4 *)(d.cent_bf16[cur ^ 1] + row * kD))[ch] = ((const uint4 *)(d.cent_bf16[cur] + row * kD))[ch];
+                if (lane == 0) {
+                    d.cnorm[cur ^ 1][row] = d.cnorm[cur][row];
+                    if (d.tk) d.caug[cur ^ 1][row] = d.caug[cur][row];
+                    d.moved[row] = 0;
+                }
+            }
+            return;
+        }
+    }
     int before[kFewPieces], from[kFewPieces], cnt = 0, first = 0, first_at = 0;
     bool listed = false;
     if constexpr (NP == 1) {
-        const uint32_t o = pieces.word(0);
+        const uint32_t o = word0;
         from[0] = (int)(o >> 16);
         cnt = (int)(o & 0xFFFFu);
     } else if constexpr (NP == kFewPieces) {
-        const uint32_t o = pieces.word(lane);
+        const uint32_t o = word0;
 #pragma unroll
         for (int r = 0; r < kFewPieces; ++r) {
             const uint32_t x = __builtin_amdgcn_readlane(o, r);  // (no members past the last piece)
@@ -930,7 +1344,7 @@ __global__ __launch_bounds__(256, 8) void means_kernel(Dev d, const bf16_t *__re
     } else {
         if (wave == 0) {
             bool ok;
-            const int m = list_members(pieces, lane, slots, &ok);
+            const int m = list_members(pieces, word0, lane, slots, &ok);
             if (lane == 0) {
                 sh_cnt = m;
                 sh_listed = ok;
@@ -940,7 +1354,7 @@ __global__ __launch_bounds__(256, 8) void means_kernel(Dev d, const bf16_t *__re
         cnt = sh_cnt;
         listed = sh_listed != 0;
         int own;
-        if (!listed && R <= 64) pieces.load(0, lane, 0, first, first_at, own);
+        if (!listed && R <= 64) pieces.take(word0, 0, lane, 0, first, first_at, own);
     }
     // lane l: the token of member j0 + l, -1 from `end` on (all lanes take part)
     auto member = [&](int j0, int end) -> int {
@@ -1038,6 +1452,9 @@ __global__ __launch_bounds__(256, 8) void means_kernel(Dev d, const bf16_t *__re
                 for (int b = 0; b < 4 * NB && j0 + 64 * b < cnt; ++b) aug_part += aug_lds[64 * b + lane];
         }
     }
+    // what the last assignment saw of the centroid (in flight while the waves meet)
+    const uint4 was = ((const uint4 *)(d.cent_bf16[cur] + row * kD))[ch];
+    const float was_norm = d.cnorm[cur][row];
     if (wave > 0 && g == 0) {
         part_sum[wave - 1][ch][0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
         part_sum[wave - 1][ch][1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
@@ -1069,6 +1486,7 @@ __global__ __launch_bounds__(256, 8) void means_kernel(Dev d, const bf16_t *__re
         nn += f0 * f0 + f1 * f1;
     }
     nn = row16_sum(nn);
+    bool moved = __ballot(was.x != pk[0] || was.y != pk[1] || was.z != pk[2] || was.w != pk[3]) != 0ull;
     if (d.tk) {
         // the centroid's extra coordinate: mean of the members' extra coordinates (the fixed wave
         // reduction of the partial sums above)
@@ -1079,12 +1497,19 @@ __global__ __launch_bounds__(256, 8) void means_kernel(Dev d, const bf16_t *__re
         if (lane == 0) {
             d.csum_aug[(size_t)u * d.C + c] = asum;
             d.cent_aug[(size_t)u * d.C + c] = e;
-            d.caug[cur ^ 1][(size_t)u * d.Cpad + c] = eb;
+            d.caug[cur ^ 1][row] = eb;
         }
+        moved |= d.caug[cur][row] != eb;
         nn += ef * ef;
     }
+    moved |= __float_as_uint(was_norm) != __float_as_uint(nn);  // (a promoted key's is summed in another order)
     // (stored here and not where it is known: the first loads' wait would cover an earlier store)
-    if (lane == 0) d.cluster_cnt[(size_t)u * d.C + c] = cnt;
+    if (lane == 0) {
+        d.cluster_cnt[(size_t)u * d.C + c] = cnt;
+        d.moved[row] = moved ? 1 : 0;
+        if (moved) d.any_moved[2 * u + (round & 1)] = 1;
+        d.touched[row] = 0;
+    }
     if (g == 0) {
         float *sum = d.cluster_sum + ((size_t)u * d.C + c) * kD + ch * 8;
         ((float4 *)sum)[0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
@@ -1096,12 +1521,12 @@ __global__ __launch_bounds__(256, 8) void means_kernel(Dev d, const bf16_t *__re
     }
 }
 
-void launch_means(const Dev &d, const bf16_t *K, int n, int cur, hipStream_t st) {
+void launch_means(const Dev &d, const bf16_t *K, int n, int cur, int t, hipStream_t st) {
     const int L = sort_range_len(d.U, n, d.Cpad), R = (n + L - 1) / L;
 #define ICE_MEANS(np)                                                                                                     \
     do {                                                                                                                  \
-        if (keys_exceed_cache(d, n)) hipLaunchKernelGGL((means_kernel<true, np>), dim3(d.C, d.U), dim3(256), 0, st, d, K, n, cur, R, L); \
-        else hipLaunchKernelGGL((means_kernel<false, np>), dim3(d.C, d.U), dim3(256), 0, st, d, K, n, cur, R, L);          \
+        if (keys_exceed_cache(d, n)) hipLaunchKernelGGL((means_kernel<true, np>), dim3(d.C, d.U), dim3(256), 0, st, d, K, n, cur, R, L, t); \
+        else hipLaunchKernelGGL((means_kernel<false, np>), dim3(d.C, d.U), dim3(256), 0, st, d, K, n, cur, R, L, t); \
     } while (0)
     if (R == 1) ICE_MEANS(1);
     else if (R <= kFewPieces) ICE_MEANS(kFewPieces);

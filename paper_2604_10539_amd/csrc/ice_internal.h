@@ -63,6 +63,9 @@ struct Dev {
     int *assign;                // [U][max_tokens]
     unsigned long long *packed; // [U][max_tokens] (ordered score << 32) | ~cluster
     int *order;                 // [U][max_tokens] tokens sorted by (cluster, position) inside every range of the sort
+    unsigned char *moved;       // [U][Cpad] the last round's means changed the centroid's bits
+    unsigned char *touched;     // [U][Cpad] the cluster lost or gained a token since the last means (zero between rounds)
+    int *any_moved;             // [U][2] some centroid of the unit moved: in even rounds, in odd ones
     int *page_base;             // [U][C] exclusive scan of pages per cluster
     float *attn_part;           // [256][G][130] partial results of the split attention (shares x units <= 256)
     int *attn_arrive;           // [U] arrival counters of its shares (zero between launches)
@@ -98,10 +101,15 @@ void launch_init_centroids(const Dev &d, const bf16_t *K, int n, const int *init
                            uint64_t seed, int cur, hipStream_t st);
 void launch_load_centroids(const Dev &d, const bf16_t *cent, int cur, hipStream_t st);
 void launch_key_aug(const Dev &d, const bf16_t *K, int n, hipStream_t st);
-void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, bool clear, hipStream_t st);
-void launch_sort(const Dev &d, int n, bool clear, float *best_out_or_null, int *assign_out_or_null, hipStream_t st);
+// The stages of round t of a build; t = 0 by itself stands for the whole stage.  A later round does again what changed since the
+// one before and leaves what all of it would: its assignment either by launch_assign (units of which a centroid moved) or, where
+// reassign_pays, by launch_reassign (moved centroids only); tokens are sorted and means formed where a token went elsewhere.
+void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, int t, hipStream_t st);
+bool reassign_pays(const Dev &d, int n, int t);
+void launch_reassign(const Dev &d, const bf16_t *K, int n, int cur, int t, hipStream_t st);
+void launch_sort(const Dev &d, int n, int t, float *best_out_or_null, int *assign_out_or_null, hipStream_t st);
 size_t sort_ranges_max(int U, int max_tokens, int Cpad);  // (unit, range) pairs of any sort of at most max_tokens tokens
-void launch_means(const Dev &d, const bf16_t *K, int n, int cur, hipStream_t st);
+void launch_means(const Dev &d, const bf16_t *K, int n, int cur, int t, hipStream_t st);
 // arm: also the decode state of a fresh index (token counters, arrival counters, empty score slots)
 void launch_paginate(const Dev &d, const bf16_t *K, const bf16_t *V, int n, bool arm, hipStream_t st);
 void launch_refresh_centroids(const Dev &d, int cur, hipStream_t st);

@@ -451,3 +451,51 @@ def test_imports_in_one_launch_and_through_copies(kw, odd):
     ea, eb = a.export(), b.export()
     for f in ("page_fill", "page_pos", "cluster_cnt", "cluster_sum", "centroid", "cluster_tail", "n_pages"):
         assert torch.equal(ea[f], eb[f]), f
+
+
+@pytest.mark.parametrize("U,n,C,tk,odd", [(3, 700, 40, 0, False), (2, 3000, 130, 1, False), (2, 4100, 520, 0, False), (1, 1500, 1100, 1, False),
+                                          (5, 2600, 500, 0, False), (2, 5000, 16, 1, False), (1, 9000, 250, 0, True), (2, 2000, 700, 1, True)])
+def test_later_rounds_do_again_what_changed_and_leave_what_all_of_it_would(U, n, C, tk, odd):
+    """A build's rounds after the first score only what the last round's means changed, and sum only clusters whose members
+    changed.  Every stage of the last round once more, over everything, leaves the same bits, after two rounds, three, ...
+    (each of them started from the state that the test before it found right).  Few and many centroid tiles, several
+    slices of 512, clusters of one key; `odd`: among keys without a comparable score and equal keys."""
+    import torch
+    from paper_2604_10539_amd import IceIndex
+    from paper_2604_10539_amd.binding import ICE_GEOMETRY_RAW, ICE_GEOMETRY_TRANSFORMED, ice_debug_rerun_stage
+    w = datagen.small(n_tokens=n, n_clusters=C, n_kv_heads=U, n_components=max(4, C // 2), outlier_frac=0.05)
+    K, V = datagen.keys_values(w)
+    if odd:
+        K[0, :, 100:400] = K[0, :, 100:101]
+        for i, t in enumerate(range(5, n, 211)):
+            K[0, :, t, i % D:] = [0x7FC0, 0x7F80, 0xFF80, 0xFFC0][i % 4]  # NaN, inf, -inf, -NaN
+    Kd, Vd, init = up(K), up(V), up(datagen.init_indices(w))
+    settled = False
+    for T in (2, 3, 4, 5, 6, 8, 12, 30):
+        ix = IceIndex(1, U, 4, n, 16, C, kmeans_iters=T, init_idx=init, geometry=ICE_GEOMETRY_TRANSFORMED if tk else ICE_GEOMETRY_RAW)
+        ix.build_index(Kd, Vd)
+
+        def state():
+            ex = dict(ix.export())
+            out = {f: ex[f] for f in ("assign", "cluster_cnt", "cluster_sum", "centroid", "Kp", "page_pos", "page_sum", "n_pages")}
+            geo = ix.export_geometry()
+            if geo:
+                out.update({f: geo[f] for f in ("centroid_extra", "cluster_sum_extra")})
+            torch.cuda.synchronize()
+            return {f: (x.view(torch.int32) if x.dtype == torch.float32 else x).clone() for f, x in out.items()}
+        had = state()
+        for stage in range(4):
+            ice_debug_rerun_stage(ix.handle, Kd, Vd, stage)
+        now = state()
+        for f in had:
+            if f == "Kp":  # (live pages)
+                for u in range(U):
+                    p = int(had["n_pages"][u])
+                    assert torch.equal(had[f][u, :p], now[f][u, :p]), (T, f, u)
+            else:
+                assert torch.equal(had[f], now[f]), (T, f)
+        if T == 12:
+            last = had
+        if T == 30 and not odd:
+            settled = torch.equal(last["assign"], had["assign"])
+    assert settled or odd or n > 100 * C  # (rounds in which nothing moves were among them, unless clusters are large)
