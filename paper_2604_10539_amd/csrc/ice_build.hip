@@ -514,6 +514,7 @@ __global__ __launch_bounds__(512) void assign_kernel(const bf16_t *__restrict__ 
         const int id = tid + 512 * i, row = id >> 4, ch = id & 15;
         *(u32x4 *)(keys + slot(row, ch)) = first[i];
     }
+    if constexpr (AUG) asm volatile("" : "+v"(stage_aug));  // (as in the loop below)
     store_aug(0);
     __syncthreads();
     // byte address of this lane's fragment chunk ks in row `col` of buffer 0; sub-tiles and the
@@ -592,6 +593,9 @@ __global__ __launch_bounds__(512) void assign_kernel(const bf16_t *__restrict__ 
             wait_lds_dma();  // this wave's share of the next tile is in LDS
             store_aug(buf ^ 1);
         }
+        // (the coordinates count as arrived here in every wave and on every path: a wait left for the next such load would
+        // cover the direct loads issued before it, i.e. come before the contraction: 54 against 46 us, 16 units x 23457 x 366)
+        if constexpr (AUG) asm volatile("" : "+v"(stage_aug));
         ICE_WSTAMP(t, 2);
         __syncthreads();
         ICE_WSTAMP(t, 3);
