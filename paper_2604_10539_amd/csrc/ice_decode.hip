@@ -777,7 +777,7 @@ __global__ __launch_bounds__(NW * 64, 4) void attend_kernel(const bf16_t *__rest
     load_query_operand<G>(q, u, threadIdx.x & 63, qa, nullptr);
     const int *list = ids + (size_t)u * P;
     const int ns = ids ? max(0, min(n_sel[u], P)) : 0;  // (no page list: resident tokens only; negative count: none)
-    attend_pages<G, NW, RES, false, FILLS>(d, u, qa, [=](int x) { return list[x]; }, ns, res, out, (float *)smem, [] {});
+    attend_pages<G, NW, RES, false, FILLS>(d, u, qa, [=](int x) { return list[x]; }, ns, res, out, (float *)smem, [](int, int) {});
 }
 
 // Few units and many pages per unit: one workgroup per unit would pull every tile through a single
@@ -811,13 +811,13 @@ __global__ __launch_bounds__(NW * 64, 4) void attend_split_kernel(const bf16_t *
         const int ns = max(0, min(n_sel[u], P));
         const int cnt = max(0, min(ns - lo, per));
         attend_pages<G, NW, kNoRows, true, false>(d, u, qa, [=](int x) { return x == wave ? first : list[x]; }, cnt,
-                                                  Resident{nullptr, nullptr, 0, nullptr, nullptr, 0}, mine, (float *)smem, [] {});
+                                                  Resident{nullptr, nullptr, 0, nullptr, nullptr, 0}, mine, (float *)smem, [](int, int) {});
     } else if constexpr (RES != kNoRows) {
         Resident r = res;
         r.b0 = (s - SP) * rper;
         r.b1 = r.b0 + rper;
         if (after_select && n_sel[u] < 0) r.b1 = r.b0;  // (a unit whose selection failed: zero output)
-        attend_pages<G, NW, RES, true, true>(d, u, qa, [](int) { return -1; }, 0, r, mine, (float *)smem, [] {});
+        attend_pages<G, NW, RES, true, true>(d, u, qa, [](int) { return -1; }, 0, r, mine, (float *)smem, [](int, int) {});
     }
     if (s == 0) ICE_STAMP(17);
     wait_vmem();      // this wave's partial stores have completed (the barrier alone does not wait for them)
@@ -1100,6 +1100,23 @@ hipError_t launch_attend_static(const Dev &d, const bf16_t *q, const int *ids, c
     return hipSuccess;
 }
 
+// Maximum over N lanes of a wave spread as far as they go: lane l gets the maximum over the lanes l mod 64 / N.  The keys of
+// lanes side by side are pages side by side, which mostly belong to one cluster and score alike; a group of neighbours stands
+// for a whole cluster's pages with one maximum, so that a threshold taken from such maxima lets many keys through (8
+// units x 9400 pages, 64 wanted: candidates listed and ranked in 7.4 us, with spread groups in 2.8).
+__device__ inline uint32_t across_max(uint32_t x, bool half) {  // with the lane 32 (half) or 16 away
+    const auto r = half ? __builtin_amdgcn_permlane32_swap(x, x, false, false) : __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    return max(r[0], r[1]);
+}
+template <int N>
+__device__ inline uint32_t group_max(uint32_t x) {
+    static_assert(N == 4 || N == 8 || N == 16, "lanes per group");
+    if (N >= 8) x = max(x, dpp_u32<0x128>(x));   // row_ror 8
+    if (N >= 16) x = max(x, dpp_u32<0x124>(x));  // row_ror 4
+    x = across_max(x, false);
+    return across_max(x, true);
+}
+
 // ------------------------------------------------------------------------------------------------
 // One decode step for all units in ONE launch: score every page representative, pick the top-P
 // pages, attend over them (Sec. 4.3-4.4, Alg. 3, Eq. 1).
@@ -1185,7 +1202,6 @@ __global__ __launch_bounds__(NW * 64, EMAX * NW <= 64 ? 4 : 1) void decode_step_
         const int p0 = chunk * per, pend = min(np_hint, p0 + per);
         const int nblk = (pend - p0 + 15) >> 4;
         constexpr int UNR = 4;
-        static_assert(NW * UNR == 4 * NW, "sh_rowmax holds one maximum per (wave, unroll slot)");
         uint4 bb[UNR][4];
         int word[4];
 #pragma unroll
@@ -1216,9 +1232,7 @@ __global__ __launch_bounds__(NW * 64, EMAX * NW <= 64 ? 4 : 1) void decode_step_
         const bool owner = SR::owner(lane);
         if (chunk == 0) ICE_STAMP(13);
         const int lim = min(np, pend);
-        float gmax[UNR];  // running maximum of the scores this lane produced in unroll slot x
-#pragma unroll
-        for (int x = 0; x < UNR; ++x) gmax[x] = -INFINITY;
+        float gmax = -INFINITY;  // running maximum of the scores this lane produced
         while (b0 < nblk) {
 #pragma unroll
             for (int x = 0; x < UNR; ++x) {
@@ -1234,26 +1248,17 @@ __global__ __launch_bounds__(NW * 64, EMAX * NW <= 64 ? 4 : 1) void decode_step_
                 if (owner && page < lim) {
                     if (single) sc_lds[page] = __float_as_uint(sc);
                     else if (!muted) __hip_atomic_store(S + page, __float_as_uint(sc), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    gmax[x] = fmaxf(gmax[x], sc);
+                    gmax = fmaxf(gmax, sc);
                 }
             }
             b0 += NW * UNR;
             if (b0 < nblk) request(b0, lim);
         }
         // With one workgroup per unit the selection threshold needs the maxima of 4*NW disjoint
-        // groups of scores: group (wave, x) is ready here, for free (the kernel is waiting for HBM).
+        // groups of scores: they are ready here, for free (the kernel is waiting for HBM).
         if (single) {
-#pragma unroll
-            for (int x = 0; x < UNR; ++x) {
-                float r = gmax[x];
-                r = fmaxf(r, dpp_f32<0xB1>(r));
-                r = fmaxf(r, dpp_f32<0x4E>(r));
-                r = fmaxf(r, dpp_f32<0x141>(r));
-                r = fmaxf(r, dpp_f32<0x140>(r));
-                r = fmaxf(r, __shfl_xor(r, 16));  // (the owners sit in two row groups)
-                r = fmaxf(r, __shfl_xor(r, 32));
-                if (lane == 0) sh_rowmax[wave * 4 + x] = f32_ordered(r);
-            }
+            const uint32_t r = group_max<16>(f32_ordered(gmax));  // (the owners sit in two row groups, the others hold -inf)
+            if (lane < 4) sh_rowmax[wave * 4 + lane] = r;
         }
     }
     // ---- arrival: count, and let the last workgroup of the unit go on.  No device-scope fence is
@@ -1390,7 +1395,7 @@ __global__ __launch_bounds__(NW * 64, EMAX * NW <= 64 ? 4 : 1) void decode_step_
         const bool by_groups = k > NR / 2 && k <= NQ / 2;
         const bool by_prefix = k > NQ / 2;
         if (by_groups) {
-            // B1, medium budgets: group maxima of the key registers, made distinct by the group's number
+            // B1, medium budgets: group maxima of the key registers (groups of 8 or 4 lanes), made distinct by the group's number
             // in their low byte (the threshold need not be a key: any value that k keys reach will do),
             // so that ranking a maximum among the N is one comparison per pair; the lanes of a group
             // share its N comparisons.
@@ -1399,11 +1404,10 @@ __global__ __launch_bounds__(NW * 64, EMAX * NW <= 64 ? 4 : 1) void decode_step_
             uint32_t lmax = key[0];
 #pragma unroll
             for (int e = 1; e < EMAX; ++e) lmax = max(lmax, key[e]);
-            lmax = max(lmax, dpp_u32<0xB1>(lmax));  // quad_perm [1,0,3,2]
-            lmax = max(lmax, dpp_u32<0x4E>(lmax));  // quad_perm [2,3,0,1]
-            if (!quads) lmax = max(lmax, dpp_u32<0x141>(lmax));  // row_half_mirror: 8 lanes
-            const int i = tid >> lg, part = tid & (gs - 1);
-            if (part == 0) sh_quadmax[i] = (lmax & 0xFFFFFF00u) | (uint32_t)(255 - i);
+            lmax = quads ? group_max<4>(lmax) : group_max<8>(lmax);
+            const int own = wave * (64 >> lg) + lane;
+            if (lane < 64 >> lg) sh_quadmax[own] = (lmax & 0xFFFFFF00u) | (uint32_t)(255 - own);
+            const int i = tid >> lg, part = tid & (gs - 1);  // the group this lane helps to rank
             lds_barrier();
             const uint32_t v = sh_quadmax[i];
             const int len = NGr >> lg;  // comparisons per lane
@@ -1416,15 +1420,15 @@ __global__ __launch_bounds__(NW * 64, EMAX * NW <= 64 ? 4 : 1) void decode_step_
             if (part == 0 && (int)c == k - 1) sh_pre = v & 0xFFFFFF00u;
         } else if (!by_prefix) {
             // B1, small budgets: the k-th largest of the 4*NW group maxima (groups without keys count as the
-            // smallest key).  With several workgroups per unit the groups are the 16-lane rows of
-            // the key registers; with one they were formed while scoring.
+            // smallest key).  With several workgroups per unit the groups are 16 lanes' key registers;
+            // with one they were formed while scoring.
             if (!single) {
                 uint32_t lmax = key[0];
 #pragma unroll
                 for (int e = 1; e < EMAX; ++e) lmax = max(lmax, key[e]);
-                lmax = row16_max_u32(lmax);
-                if (ch == 0) sh_rowmax[wave * 4 + g] = lmax;
-                __syncthreads();
+                lmax = group_max<16>(lmax);
+                if (lane < 4) sh_rowmax[wave * 4 + lane] = lmax;
+                lds_barrier();
             }
             // rank of row maximum i among the NR (equal values: lower row first); 16 lanes share the work
             const int i = tid >> 4, part = tid & 15;
@@ -1513,6 +1517,7 @@ __global__ __launch_bounds__(NW * 64, EMAX * NW <= 64 ? 4 : 1) void decode_step_
             int tot = 0, tot_a = 0;
 #pragma unroll
             for (int e = 0; e < EMAX; ++e) {
+                if (e * NT >= np) break;  // (here and below: uniform, no key beyond)
                 tot += (int)__popcll(listed(e));
                 if constexpr (PREFIX) tot_a += (int)__popcll(is_above(e));
             }
@@ -1522,6 +1527,7 @@ __global__ __launch_bounds__(NW * 64, EMAX * NW <= 64 ? 4 : 1) void decode_step_
             const u64 lower = (1ull << lane) - 1ull;
 #pragma unroll
             for (int e = 0; e < EMAX; ++e) {
+                if (e * NT >= np) break;
                 const int pid = e * NT + tid;
                 const u64 bal = listed(e);
                 const int slot = base + (int)__popcll(bal & lower);
@@ -1696,25 +1702,20 @@ __global__ __launch_bounds__(NW * 64, EMAX * NW <= 64 ? 4 : 1) void decode_step_
     // ---- phase C: attention over the winners, in rank order (the ids' ascending order is only an
     // output format and is produced afterwards, off the critical path)
     const bool all_pages = k == np;
-    // B4: the winners' places in ascending id order; during the attention it runs where the first
-    // waves would wait for the last ones
-    auto order_ids = [&] {
+    // B4: the winners' places in ascending id order
+    auto order_ids = [&](int part, int parts) {
         // (every global store of the selection is issued here, after the ranking: a store in flight
         // makes the next wait of its wave as long as a write to memory)
-        for (int x = k + tid; x < P; x += NT) {
+        for (int x = k + part * 64 + lane; x < P; x += parts * 64) {
             ids[x] = -1;
             if (sco) sco[x] = 0.f;
         }
-        if (tid == 0) n_sel_out[u] = k;
+        if (part == 0 && lane == 0) n_sel_out[u] = k;
         if (all_pages) return;
-        for (int t = tid; t < k; t += NT) {
-            const u64 mine = sel_comp[t];
-            const uint32_t myid = 0xFFFFFFFFu - (uint32_t)mine;
-            int pos = 0;
-            for (int j = 0; j < k; ++j) pos += (0xFFFFFFFFu - (uint32_t)sel_comp[j]) < myid;
-            ids[pos] = (int)myid;
-            if (sco) sco[pos] = ordered_f32((uint32_t)(mine >> 32));
-        }
+        place_by_id(sel_comp, k, part, parts, lane, [&](int pos, u64 w) {
+            ids[pos] = (int)(0xFFFFFFFFu - (uint32_t)w);
+            if (sco) sco[pos] = ordered_f32((uint32_t)(w >> 32));
+        });
     };
     if (out) {
         ICE_STAMP(6);
@@ -1724,7 +1725,7 @@ __global__ __launch_bounds__(NW * 64, EMAX * NW <= 64 ? 4 : 1) void decode_step_
                                  res, out, (float *)region, order_ids);
         ICE_STAMP(7);
     } else {
-        order_ids();
+        order_ids(wave, NW);
     }
     ICE_USTAMP(3);
 }

@@ -21,6 +21,44 @@ __device__ inline float dot8(const uint4 &a, const uint4 &b) {
     return dot2(a.w, b.w, dot2(a.z, b.z, dot2(a.y, b.y, dot2(a.x, b.x, 0.f))));
 }
 
+// The places of the n winners (composites with ~id in the low word, LDS) in ascending id order: put(place, winner) on one lane
+// each.  Wave `part` of `parts` takes winners part, part + parts, ...; one ballot over 64 winners at a time counts the lower
+// ids.  (By one thread per winner, each reading all of them: 64 winners 3 us on the first wave, 16 one.)
+template <typename Put>
+__device__ inline void place_by_id(const u64 *win, int n, int part, int parts, int lane, Put put) {
+    if (n <= 64) {  // all of them side by side on the lanes
+        const u64 w = win[min(lane, max(n - 1, 0))];
+        const uint32_t lo = (uint32_t)w, hi = (uint32_t)(w >> 32);
+        for (int t = part; t < n; t += parts) {  // (t is the same for the whole wave)
+            const uint32_t mine = (uint32_t)__builtin_amdgcn_readlane((int)lo, t), score = (uint32_t)__builtin_amdgcn_readlane((int)hi, t);
+            const int pos = (int)__popcll(__ballot(lane < n && lo > mine));
+            if (lane == 0) put(pos, ((u64)score << 32) | mine);
+        }
+        return;
+    }
+    for (int t = part; t < n; t += parts) {
+        const u64 mine = win[t];  // (the same word on every lane)
+        int pos = 0;
+        for (int j0 = 0; j0 < n; j0 += 64) {
+            const int j = j0 + lane;
+            pos += (int)__popcll(__ballot(j < n && (uint32_t)win[min(j, n - 1)] > (uint32_t)mine));
+        }
+        if (lane == 0) put(pos, mine);
+    }
+}
+
+// The set bits of a mask of `words` 32-bit words (LDS) in ascending order, by one wave: out[0], out[1], ...
+__device__ inline void list_bits(const uint32_t *mask, int words, int lane, int *out) {
+    int before = 0;
+    for (int w0 = 0; w0 < words; w0 += 64) {
+        uint32_t w = w0 + lane < words ? mask[w0 + lane] : 0u;
+        const int cnt = __popc(w), incl = wave_scan_add(cnt);
+        int pos = before + incl - cnt;
+        for (; w; w &= w - 1) out[pos++] = 32 * (w0 + lane) + __ffs(w) - 1;
+        before += __builtin_amdgcn_readlane(incl, 63);
+    }
+}
+
 // Sparse paged attention over a list of pages (Eq. 1 with the mask set on the tokens of the listed
 // pages), for one unit, by the NW waves of the calling workgroup.  Wave w streams pages w, w+NW, ...;
 // a page's key tile and value tile are each s x 256 contiguous bytes.  Per 16-token block:
@@ -37,8 +75,9 @@ __device__ inline float dot8(const uint4 &a, const uint4 &b) {
 //            column tiles if tile j is made of dims {8c + j} and contraction slot 4g+i stands for
 //            token 4i+g (a permutation of the sum); two byte-permutes per tile pack it.
 // The NW waves are merged by the (max, sum, output) rule.  page_of(x) names the x-th listed page
-// (x differs by lane); `red` is LDS scratch of attend_scratch_floats() floats; aside() is work of the
-// caller that needs no barrier and runs where a wave would otherwise wait for the slowest wave's pages.
+// (x differs by lane); `red` is LDS scratch of attend_scratch_floats() floats; aside(part, parts) is work of the
+// caller that needs no barrier: the waves that the output leaves idle do it beside the others, each its part.  (In front of the last
+// barrier, or while the first tiles are on their way, it was 0.3 us longer for 16 winners.)
 __host__ __device__ constexpr int attend_scratch_floats(int G, int NW) { return NW * (G * (kD + 2) + 16 * 8); }
 
 template <int G>
@@ -413,7 +452,6 @@ __device__ inline void attend_pages(const Dev &d, int u, const bf16x8 (&qa)[4], 
         for (int v = 0; v < 4; ++v)
             if (4 * g + v < G) { wm[wave][4 * g + v] = m[v]; wl[wave][4 * g + v] = l[v]; }
     }
-    aside();
     __syncthreads();
     ICE_STAMP(11);
     // per head: the waves' merge weights exp(m_w - M) / L, one 16-lane row per head, one lane per wave
@@ -439,6 +477,13 @@ __device__ inline void attend_pages(const Dev &d, int u, const bf16x8 (&qa)[4], 
         }
     }
     __syncthreads();
+    constexpr int OW = G * kD / 64;  // waves' worth of outputs
+    if constexpr (OW < NW) {
+        if (wave >= OW) {
+            aside(wave - OW, NW - OW);
+            return;
+        }
+    }
     for (int o = tid; o < G * kD; o += NW * 64) {
         const int h = o / kD, j = o % kD;
         float O = 0.f;
@@ -447,6 +492,7 @@ __device__ inline void attend_pages(const Dev &d, int u, const bf16x8 (&qa)[4], 
         if constexpr (PARTIAL) __hip_atomic_store(out + h * (kD + 2) + j, O, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         else out[((size_t)u * G + h) * kD + j] = O;
     }
+    if constexpr (OW >= NW) aside(wave, NW);
 }
 
 }  // namespace ice

@@ -542,48 +542,27 @@ __global__ __launch_bounds__(NW * 64) void decode_hier_kernel(int Cpad, int max_
         win = sel3;
     }
     ICE_HSTAMP(6);
-    // the winners' places in ascending id order; during the attention it runs where the first
-    // waves would wait for the last ones
-    auto order_ids = [&] {
+    // the winners' places in ascending id order
+    auto order_ids = [&](int part, int parts) {
         if (TOP && tops_out) {  // the kept top nodes, ascending
             int *to = tops_out + (size_t)u * n_probe_top;
-            for (int t = tid; t < n_probe_top; t += NT) {
-                if (t < n_keep0) {
-                    const uint32_t mine = 0xFFFFFFFFu - (uint32_t)sel0[t];
-                    int pos = 0;
-                    for (int j = 0; j < n_keep0; ++j) pos += (0xFFFFFFFFu - (uint32_t)sel0[j]) < mine;
-                    to[pos] = (int)mine;
-                } else {
-                    to[t] = -1;
-                }
-            }
+            if (part == parts - 1) list_bits(member0, kTopMax / 32, lane, to);
+            for (int t = n_keep0 + part * 64 + lane; t < n_probe_top; t += parts * 64) to[t] = -1;
         }
         if (clusters_out) {  // the kept clusters, ascending
             int *co = clusters_out + (size_t)u * n_probe;
-            for (int t = tid; t < n_probe; t += NT) {
-                if (t < n_keep) {
-                    const uint32_t myc = 0xFFFFFFFFu - (uint32_t)sel1[t];
-                    int pos = 0;
-                    for (int j = 0; j < n_keep; ++j) pos += (0xFFFFFFFFu - (uint32_t)sel1[j]) < myc;
-                    co[pos] = (int)myc;
-                } else {
-                    co[t] = -1;
-                }
-            }
+            if (part == parts - 1) list_bits(member, Cpad / 32, lane, co);
+            for (int t = n_keep + part * 64 + lane; t < n_probe; t += parts * 64) co[t] = -1;
         }
-        for (int t = tid; t < k; t += NT) {
-            const u64 mine = win[t];
-            const uint32_t myid = 0xFFFFFFFFu - (uint32_t)mine;
-            int pos = 0;
-            for (int j = 0; j < k; ++j) pos += (0xFFFFFFFFu - (uint32_t)win[j]) < myid;
-            ids[pos] = (int)myid;
-            if (sco) sco[pos] = ordered_f32((uint32_t)(mine >> 32));
-        }
+        place_by_id(win, k, part, parts, lane, [&](int pos, u64 w) {
+            ids[pos] = (int)(0xFFFFFFFFu - (uint32_t)w);
+            if (sco) sco[pos] = ordered_f32((uint32_t)(w >> 32));
+        });
     };
     bf16x8 qa[4];
     if (out) SR::to_plain(qs, lane, qa);
     if (out) attend_pages<G, NW, kNoRows, false, FILLS>(d, u, qa, [=](int x) { return (int)(0xFFFFFFFFu - (uint32_t)win[x]); }, k, Resident{nullptr, nullptr, 0, nullptr, nullptr, 0}, out, red, order_ids);
-    else order_ids();
+    else order_ids(wave, NW);
     ICE_HSTAMP(7);
 }
 

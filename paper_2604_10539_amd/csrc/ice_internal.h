@@ -236,6 +236,16 @@ __device__ inline float wave_sum(float x) {
     return x;
 }
 
+// inclusive sum over the wave on the vector unit (no trip through LDS)
+__device__ inline int wave_scan_add(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);  // row_shr 1, 2, 4, 8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);  // row_bcast 15 into rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // row_bcast 31 into rows 2 and 3
+    return x;
+}
 // squared norm of a key held 8 dims per lane by a 16-lane row (fixed summation order), and the extra
 // coordinate sqrt(c^2 - ||k||^2) of the transformed keys (Eq. 2), rounded to bf16
 // Workgroup barrier that orders LDS traffic only: global loads and stores that are still outstanding stay in

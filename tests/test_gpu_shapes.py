@@ -499,3 +499,44 @@ def test_later_rounds_do_again_what_changed_and_leave_what_all_of_it_would(U, n,
         if T == 30 and not odd:
             settled = torch.equal(last["assign"], had["assign"])
     assert settled or odd or n > 100 * C  # (rounds in which nothing moves were among them, unless clusters are large)
+
+
+@pytest.mark.parametrize("U,G", [(3, 4), (2, 8), (256, 1), (256, 8)])
+def test_pages_of_one_cluster_side_by_side_at_every_budget(U, G):
+    """Pages that score alike sit beside each other, so whole clusters fall into one group of the selection's threshold; the
+    budgets are those where its groups, the list behind it and the order of the returned ids change (and kept clusters of the
+    staged selection beside them): several workgroups per unit and one."""
+    import torch
+    from paper_2604_10539_amd import IceIndex
+    n, C, s = (4096, 64, 16) if U < 256 else (1500, 40, 16)
+    w = datagen.small(n_tokens=n, n_clusters=C, n_kv_heads=min(U, 8), n_components=C // 2, group_size=G)
+    K, V = datagen.keys_values(w)
+    K, V = (np.ascontiguousarray(np.resize(x[0], (U,) + x.shape[2:]))[None] for x in (K, V))
+    q = np.ascontiguousarray(np.resize(datagen.queries(w)[0], (U * G, D)))[None]
+    ix = IceIndex(1, U, G, n, s, C, kmeans_iters=3, init_idx=up(np.resize(datagen.init_indices(w)[0], (U, C))[None]))
+    ix.build_index(up(K), up(V))
+    ex = ix.export()
+    torch.cuda.synchronize()
+    npg, rep = down(ex["n_pages"]), widen(down(ex["rep"])).astype(np.float64)
+    qf = widen(q[0]).astype(np.float64).reshape(U, G, D)
+    qf /= np.linalg.norm(qf, axis=2, keepdims=True)
+    units = range(U) if U < 256 else (0, 1, 100, 255)
+    for P in (1, 2, 16, 17, 31, 32, 33, 63, 64, 65, 127, 128, 129, 200, int(npg.min()) - 1):
+        if P < 1 or P >= npg.min():
+            continue
+        ids, n_sel, out = (down(x) for x in ix.select_attend(up(q), P * s))
+        for u in units:
+            got = ids[0, u]
+            assert n_sel[0, u] == P and np.all(np.diff(got) > 0)
+            sc = (rep[u, :npg[u]] @ qf[u].T).max(1)
+            kth = np.sort(sc)[::-1][P - 1]
+            # fp32 scores of unit-length rows: chains of 128 additions on values of at most a few units
+            assert np.all(sc[got] >= kth - 1e-5 * max(1.0, abs(kth))), (P, u)
+    for probe in (1, 31, C - 1):
+        ids, n_sel, _, cl, _ = ix.select_hier(up(q), 64, probe)
+        cl = down(cl)[0]
+        pc = down(ex["page_cluster"])
+        for u in units:
+            assert np.all(np.diff(cl[u]) > 0) and 0 <= cl[u, 0] and cl[u, -1] < C
+            k = int(down(n_sel)[0, u])
+            assert set(pc[u, down(ids)[0, u, :k]]) <= set(cl[u])
