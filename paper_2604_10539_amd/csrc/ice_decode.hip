@@ -24,6 +24,7 @@ constexpr int kUnitFailed = -(1 << 30);        // arrival counter of a unit whos
 // and squared norm) and the row is appended to the cluster's tail page (page sum -> representative).
 constexpr int kInsertWaves = 16;
 constexpr int kInsertTokens = 16;  // tokens per round of the batched kernel at most (one per wave)
+constexpr int kScanAhead = kInsertWaves - 2;  // waves that score the next round's tokens while two settle this one's
 
 __device__ inline float insert_objective(float w, float dot, float kaf, float ce) {
     return __builtin_fmaf(-2.0f, __builtin_fmaf(kaf, ce, dot), w);
@@ -313,7 +314,11 @@ __global__ __launch_bounds__(kInsertWaves * 64) void insert_one_kernel(const bf1
 // after the other (about 3 us each on one wave).
 // More tokens than the tables hold (`per`: 16, fewer when the clusters are many) are taken in rounds by the same
 // workgroup: bound by the steps' latencies, a round saves the launch, the start of 16 waves and the argument loads of
-// a launch per 16 tokens (32 units, 128 clusters, 200 tokens: 163 us in 13 launches, 127 in one).
+// a launch per 16 tokens (32 units, 128 clusters, 200 tokens: 163 us in 13 launches, 127 in one).  Where LDS holds a second D
+// (up to about 440 clusters) the scan of the next round runs beside the settling, which needs two of the 16 waves: its rows are
+// requested in front of the guess, and the columns of the rows that this round moves are worked out again from `lrow` (the
+// same instruction sequence, so the same bits).  9.7 -> 8.4 us per round; what is left of a round: guess 3.2 (about half of it on the vector unit),
+// settle with its barriers 1.6, commit and append 1.2, stores and the way back 1.4.
 // k, v: bf16 [U, m_total, d].
 __host__ __device__ inline int insert_row_stride(int C) { return round_up(C, 16) + 4; }  // (+4: the four token groups of a store hit different banks)
 // dynamic LDS: D [mt][stride], norms [Cr] (+ extras [Cr]), the tokens' keys and moved rows [16][64] words each,
@@ -324,7 +329,7 @@ __host__ __device__ inline size_t insert_fixed_lds(int C, bool tk) {
 
 __global__ __launch_bounds__(kInsertWaves * 64) void insert_batch_kernel(const bf16_t *__restrict__ k, const bf16_t *__restrict__ v,
                                                                           bf16_t *cent, float *cnorm, int m_total, int per,
-                                                                          int cur, int C, int Cpad, int stage_tiles, int tk_arg,
+                                                                          int cur, int C, int Cpad, int stage_tiles, int flags,
                                                                           Dev d_arg) {  // (scalars first: preloaded)
     extern __shared__ __align__(16) char insert_lds[];
     __shared__ u64 s_best[kInsertTokens];        // the guess: (ordered objective, cluster), ~0 when every objective is NaN
@@ -334,6 +339,7 @@ __global__ __launch_bounds__(kInsertWaves * 64) void insert_batch_kernel(const b
     __shared__ float s_nn[kInsertTokens], s_ef[kInsertTokens];  // squared norm and extra coordinate of the row token t's move forms
     __shared__ float s_dm[kInsertTokens][kInsertTokens];        // [t'][t]: token t against the row token t' moved
     __shared__ bf16_t s_ka[kInsertTokens];
+    __shared__ int s_row[kInsertTokens];                        // cluster token t' moved, -1 when a later token moved it again
     __shared__ u64 s_best2[kInsertTokens];                      // the runner-up of the guess
     __shared__ int s_fail[kInsertTokens];                       // bit t': token t's guess fails if token t' < t moves as it guessed
     __shared__ int s_stood;                                     // bit t: token t's guessed move stands (wave t stores it); bit 16: every token went where it guessed
@@ -366,64 +372,76 @@ __global__ __launch_bounds__(kInsertWaves * 64) void insert_batch_kernel(const b
     };
     request();
     // The other arguments are fetched here, once, while tiles and keys are on their way.
-    const bool tk = tk_arg != 0;
+    const bool tk = (flags & 1) != 0, ahead = (flags & 2) != 0;
     Dev d;
     bf16_t *caug_cur;
     pin_insert_fields(d, d_arg, cur, caug_cur);
     float *Dl = (float *)(insert_lds + kInsertWaves * stage_tiles * kInsertTileBytes);
-    float *lw = Dl + (size_t)mt * Cs;  // (the first round is the longest)
+    float *lw = Dl + (size_t)(ahead ? 2 * per : mt) * Cs;  // (the first round is the longest)
     float *lce = lw + Cr;
     uint32_t *lkey = (uint32_t *)(lce + (tk ? Cr : 0));
     uint32_t *lrow = lkey + kInsertTokens * 64;  // [t][64]: the bf16 row token t's move forms (a B operand is read back from it)
     float2 *s_cs = (float2 *)(lrow + kInsertTokens * 64);  // slot t: the guessed cluster's sum as it stands
     float2 *s_cs1 = s_cs + kInsertTokens * 64;             // ... and after token t's guessed move
     float2 *s_ps = s_cs1 + kInsertTokens * 64;             // ... and its tail page's sum before this launch
-    for (int t0 = 0;;) {
+    int np0 = 0, tok0 = 0;
+    uint32_t kw_next = 0, vw_next = 0;  // (ahead) the next round's tokens: this wave's, and the operand of all
+    bf16x8 ka_next[4];
+    for (int t0 = 0, round = 0;; ++round) {
         // (opaque to the compiler in every round: hoisted out of the loop, the lanes' addresses would not fit the registers)
         asm volatile("" : "+v"(tid));
         const int wave = tid >> 6, lane = tid & 63;
         const int g = lane >> 4, i = lane & 15;
+        float *Dc = Dl + (ahead && (round & 1) ? (size_t)per * Cs : 0), *Dn = Dl + (ahead && !(round & 1) ? (size_t)per * Cs : 0);
         uint32_t vw = 0;
-        if (wave < mt) {
-            lkey[wave * 64 + lane] = ((const uint32_t *)(ku + (size_t)wave * kD))[lane];
-            vw = ((const uint32_t *)(vu + (size_t)wave * kD))[lane];
-        }
-        for (int r = tid; r < Cr; r += kInsertWaves * 64) {
-            lw[r] = r < C ? wn[r] : INFINITY;
-            if (tk) lce[r] = r < C ? bf16_to_f32(caug_cur[(size_t)u * Cpad + r]) : 0.f;
-        }
-        auto store_dots = [&](const f32x4 &acc, int tile) {
+        auto store_dots = [&](float *D, int m, const f32x4 &acc, int tile) {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                if (4 * g + j < mt) Dl[(size_t)(4 * g + j) * Cs + tile * 16 + i] = acc[j];
+                if (4 * g + j < m) D[(size_t)(4 * g + j) * Cs + tile * 16 + i] = acc[j];
         };
-        for (int tile = wave; tile < tiles; tile += stage_tiles * kInsertWaves) {
-            const int tb = tile + kInsertWaves;
-            const bool two = stage_tiles == 2 && tb < tiles;
-            if (tile != wave) {
-                insert_stage_tile(cb, tile, stg, lane);
-                if (two) insert_stage_tile(cb, tb, stg + kInsertTileBytes, lane);
+        if (ahead && round > 0) {  // D and the norms are there
+            if (wave < mt) lkey[wave * 64 + lane] = kw_next;
+            vw = vw_next;
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) ka[ks] = ka_next[ks];
+        } else {
+            if (wave < mt) {
+                lkey[wave * 64 + lane] = ((const uint32_t *)(ku + (size_t)wave * kD))[lane];
+                vw = ((const uint32_t *)(vu + (size_t)wave * kD))[lane];
             }
-            wait_lds_dma();
-            uint4 b0[4];
-            insert_read_tile(stg, lane, b0);
-            store_dots(insert_dots(ka, b0), tile);
-            if (two) {
-                uint4 b1[4];
-                insert_read_tile(stg + kInsertTileBytes, lane, b1);
-                store_dots(insert_dots(ka, b1), tb);
+            for (int r = tid; r < Cr; r += kInsertWaves * 64) {
+                lw[r] = r < C ? wn[r] : INFINITY;
+                if (tk) lce[r] = r < C ? bf16_to_f32(caug_cur[(size_t)u * Cpad + r]) : 0.f;
             }
+            for (int tile = wave; tile < tiles; tile += stage_tiles * kInsertWaves) {
+                const int tb = tile + kInsertWaves;
+                const bool two = stage_tiles == 2 && tb < tiles;
+                if (tile != wave) {
+                    insert_stage_tile(cb, tile, stg, lane);
+                    if (two) insert_stage_tile(cb, tb, stg + kInsertTileBytes, lane);
+                }
+                wait_lds_dma();
+                uint4 b0[4];
+                insert_read_tile(stg, lane, b0);
+                store_dots(Dc, mt, insert_dots(ka, b0), tile);
+                if (two) {
+                    uint4 b1[4];
+                    insert_read_tile(stg + kInsertTileBytes, lane, b1);
+                    store_dots(Dc, mt, insert_dots(ka, b1), tb);
+                }
+            }
+            np0 = d.n_pages[u];
+            tok0 = d.n_tokens[u];
+            ICE_STAMP(33);
+            __syncthreads();
         }
-        const int np0 = d.n_pages[u], tok0 = d.n_tokens[u];
-        ICE_STAMP(33);
-        __syncthreads();
         ICE_STAMP(34);
 
         // nearest row for token t over all rows, from LDS
         auto nearest = [&](int t, float kaf) {
             u64 b = ~0ull;
             for (int c = lane; c < C; c += 64) {
-                const float val = insert_objective(lw[c], Dl[(size_t)t * Cs + c], kaf, tk ? lce[c] : 0.f);
+                const float val = insert_objective(lw[c], Dc[(size_t)t * Cs + c], kaf, tk ? lce[c] : 0.f);
                 if (!(val != val)) {
                     const u64 key = insert_pack(val, c);
                     b = key < b ? key : b;
@@ -442,6 +460,15 @@ __global__ __launch_bounds__(kInsertWaves * 64) void insert_batch_kernel(const b
             return insert_dots(ka, bm);
         };
 
+        // (ahead) The next round's tokens are scored during this round's settling, against the rows as they are now: the rows
+        // that this round moves (some are being stored meanwhile) are put right from `lrow` afterwards.  Requested here: the rows
+        // arrive with what the guess waits for.
+        const int mt_next = ahead ? min(per, m_total - t0 - mt) : 0;
+        if (mt_next > 0 && wave >= 2) {
+            if (wave - 2 < tiles) insert_stage_tile(cb, wave - 2, stg, lane);
+            if (stage_tiles == 2 && wave - 2 + kScanAhead < tiles) insert_stage_tile(cb, wave - 2 + kScanAhead, stg + kInsertTileBytes, lane);
+        }
+
         // ---- guess
         ClusterMove mine = {};
         if (wave < mt) {
@@ -451,7 +478,7 @@ __global__ __launch_bounds__(kInsertWaves * 64) void insert_batch_kernel(const b
             const float kaf = bf16_to_f32(kab);
             u64 b = ~0ull, b2 = ~0ull;  // the nearest row and the runner-up
             for (int c = lane; c < C; c += 64) {
-                const float val = insert_objective(lw[c], Dl[(size_t)t * Cs + c], kaf, tk ? lce[c] : 0.f);
+                const float val = insert_objective(lw[c], Dc[(size_t)t * Cs + c], kaf, tk ? lce[c] : 0.f);
                 if (!(val != val)) merge_min2(b, b2, insert_pack(val, c), ~0ull);
             }
             wave_min2_u64(b, b2);
@@ -487,6 +514,19 @@ __global__ __launch_bounds__(kInsertWaves * 64) void insert_batch_kernel(const b
             if (i == 0) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) s_dm[t][4 * g + j] = acc[j];
+            }
+        }
+        if (mt_next > 0) {
+            const bf16_t *kn = ku + (size_t)mt * kD, *vn = vu + (size_t)mt * kD;
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                uint4 w = make_uint4(0, 0, 0, 0);
+                if (i < mt_next) w = ((const uint4 *)(kn + (size_t)i * kD))[ks * 4 + g];
+                ka_next[ks] = __builtin_bit_cast(bf16x8, w);
+            }
+            if (wave < mt_next) {
+                kw_next = ((const uint32_t *)(kn + (size_t)wave * kD))[lane];
+                vw_next = ((const uint32_t *)(vn + (size_t)wave * kD))[lane];
             }
         }
         ICE_STAMP(35);
@@ -542,6 +582,29 @@ __global__ __launch_bounds__(kInsertWaves * 64) void insert_batch_kernel(const b
             }
             if (lane == 0) t_pages[buf] = __popcll(openers);
         };
+
+        // (ahead) While waves 0 and 1 settle, the others score the next round's tokens.
+        if (mt_next > 0) {
+            if (wave >= 2) {
+                for (int tile = wave - 2; tile < tiles; tile += stage_tiles * kScanAhead) {
+                    const int tb = tile + kScanAhead;
+                    const bool two = stage_tiles == 2 && tb < tiles;
+                    if (tile != wave - 2) {
+                        insert_stage_tile(cb, tile, stg, lane);
+                        if (two) insert_stage_tile(cb, tb, stg + kInsertTileBytes, lane);
+                    }
+                    wait_lds_dma();
+                    uint4 b0[4];
+                    insert_read_tile(stg, lane, b0);
+                    store_dots(Dn, mt_next, insert_dots(ka_next, b0), tile);
+                    if (two) {
+                        uint4 b1[4];
+                        insert_read_tile(stg + kInsertTileBytes, lane, b1);
+                        store_dots(Dn, mt_next, insert_dots(ka_next, b1), tb);
+                    }
+                }
+            }
+        }
 
         if (wave == 1) {
             // while wave 0 settles: the table as it is if every token goes where it guessed
@@ -606,7 +669,7 @@ __global__ __launch_bounds__(kInsertWaves * 64) void insert_batch_kernel(const b
                     for (u64 need = live & ~patched; need; need &= need - 1) {
                         const int j = __ffsll((long long)need) - 1;
                         const int row = __builtin_amdgcn_readlane(r_row, j);
-                        if (lane >= t && lane < mt) Dl[(size_t)lane * Cs + row] = s_dm[j][lane];
+                        if (lane >= t && lane < mt) Dc[(size_t)lane * Cs + row] = s_dm[j][lane];
                         if (lane == 0) {
                             lw[row] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r_nn), j));
                             if (tk) lce[row] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r_ef), j));
@@ -654,8 +717,8 @@ __global__ __launch_bounds__(kInsertWaves * 64) void insert_batch_kernel(const b
                     }
                     post &= ~same_slot;
                     if (lane == t) { r_nn = mv.nn; r_ef = mv.ef; }
+                    lrow[t * 64 + lane] = mv.packed;
                     if (t + 1 < mt) {
-                        lrow[t * 64 + lane] = mv.packed;
                         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                         const f32x4 acc = row_dots(lrow + t * 64);
                         if (i == 0) {
@@ -672,6 +735,11 @@ __global__ __launch_bounds__(kInsertWaves * 64) void insert_batch_kernel(const b
                 live |= 1ull << t;
                 if (lane == t) r_row = c;
             }
+            if (lane < mt) {
+                s_row[lane] = (live >> lane) & 1ull ? r_row : -1;
+                s_nn[lane] = r_nn;
+                s_ef[lane] = r_ef;
+            }
             if (lane == 0) s_stood = (int)stood | (all_guessed ? 1 << 16 : 0);
             if (!all_guessed) page_table(1, r_row, r_guess, r_tail, r_fill);
         }
@@ -679,14 +747,34 @@ __global__ __launch_bounds__(kInsertWaves * 64) void insert_batch_kernel(const b
         __syncthreads();
         ICE_STAMP(38);
 
+        const int stood_all = s_stood, buf = (stood_all >> 16) & 1 ? 0 : 1;
+        if (mt_next > 0 && wave == kInsertWaves - 1) {  // (ahead) the next tokens against the rows moved in this round
+            uint4 bm[4];
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) {
+                bm[ks] = make_uint4(0, 0, 0, 0);
+                if (i < mt) bm[ks] = ((const uint4 *)(lrow + i * 64))[ks * 4 + g];
+            }
+            const f32x4 acc = insert_dots(ka_next, bm);
+            const int row = i < mt ? s_row[i] : -1;
+            if (row >= 0) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    if (4 * g + j < mt_next) Dn[(size_t)(4 * g + j) * Cs + row] = acc[j];
+                if (g == 0) {
+                    lw[row] = s_nn[i];
+                    if (tk) lce[row] = s_ef[i];
+                }
+            }
+        }
+
         // ---- commit
-        const int stood_all = s_stood;
         if (wave < mt && ((stood_all >> wave) & 1)) insert_store_move(d, cent, cnorm, caug_cur, u, s_cluster[wave], Cpad, lane, mine, tk);
 
         // ---- append
         ICE_STAMP(53);
         if (wave < mt) {
-            const int s = d.s, t = wave, buf = (stood_all >> 16) & 1 ? 0 : 1;
+            const int s = d.s, t = wave;
             const int lt = lane < mt ? lane : 0;
             const int cj = lane < mt ? t_cluster[buf][lt] : -1 - lane, page = lane < mt ? t_page[buf][lt] : -1 - lane;
             const int c = t_cluster[buf][t], pg_t = t_page[buf][t], slot_t = t_slot[buf][t] & ~(1 << 30), src_t = t_src[buf][t];
@@ -733,6 +821,8 @@ __global__ __launch_bounds__(kInsertWaves * 64) void insert_batch_kernel(const b
         ICE_STAMP(55);
         // ---- the next tokens: what this round stored is read back by this workgroup, whose waves share a vector
         // cache, once every wave's stores are done
+        np0 += t_pages[buf];
+        tok0 += mt;
         t0 += mt;
         if (t0 >= m_total) break;
         ku += (size_t)mt * kD;
@@ -741,7 +831,7 @@ __global__ __launch_bounds__(kInsertWaves * 64) void insert_batch_kernel(const b
         wait_vmem();
         __threadfence_block();
         __syncthreads();
-        request();
+        if (!ahead) request();
     }
 }
 
@@ -759,11 +849,14 @@ void launch_insert(const Dev &d, const bf16_t *k, const bf16_t *v, int m, int cu
         return;
     }
     const int per = std::min(cap, m);
-    const int stage_tiles = fixed + per * row + 2 * stage1 <= budget ? 2 : 1;
-    const size_t lds = fixed + per * row + stage_tiles * stage1;
+    // the next round's scores worked out during this one's settling, where there is a next round and a second table fits
+    const bool ahead = m > per && fixed + 2 * per * row + stage1 <= budget;
+    const size_t tables = (ahead ? 2 : 1) * per * row;
+    const int stage_tiles = fixed + tables + 2 * stage1 <= budget ? 2 : 1;
+    const size_t lds = fixed + tables + stage_tiles * stage1;
     allow_dynamic_lds((const void *)insert_batch_kernel, lds);
     hipLaunchKernelGGL(insert_batch_kernel, dim3(d.U), dim3(kInsertWaves * 64), lds, st, k, v, d.cent_bf16[cur], d.cnorm[cur], m, per, cur, d.C,
-                       d.Cpad, stage_tiles, d.tk, d);
+                       d.Cpad, stage_tiles, (d.tk ? 1 : 0) | (ahead ? 2 : 0), d);
 }
 
 // ------------------------------------------------------------------------------------------------
