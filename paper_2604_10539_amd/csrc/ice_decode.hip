@@ -1312,12 +1312,15 @@ __global__ __launch_bounds__(NW * 64, EMAX * NW <= 64 ? 4 : 1) void decode_step_
         };
         // The first round of representative rows is requested together with the query rows, before
         // anything waits for either (and before np is known: np <= np_hint <= max_pages): the
-        // kernel starts with one memory round trip, not two.
+        // kernel starts with one memory round trip, not two.  The query rows go first: their norms are worked out while
+        // the others are on their way.
+        uint4 qw[2];
+        SR::request_query(q, u, lane, qw);
         int b0 = wave;
         if (b0 < nblk) request(b0, pend);
         if (chunk == 0) ICE_STAMP(12);
         float invn;
-        SR::load_query(q, u, lane, qs, &invn);
+        SR::take_query(qw, qs, &invn);
         if (!live) return;  // (nothing written, no barrier passed yet)
         float inv[4];
 #pragma unroll

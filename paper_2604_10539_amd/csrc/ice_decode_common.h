@@ -63,8 +63,11 @@ __device__ inline void list_bits(const uint32_t *mask, int words, int lane, int 
 // pages), for one unit, by the NW waves of the calling workgroup.  Wave w streams pages w, w+NW, ...;
 // a page's key tile and value tile are each s x 256 contiguous bytes.  Per 16-token block:
 //   logits   one v_mfma_f32_16x16x32_bf16 chain, A = the G query rows, B = the 16 key rows (lane
-//            (g, r) reads bytes [64*ks + 16*g, +16) of key row r): lane r of row group 0 gets the
-//            logits of token r for heads 0..3 (group 1: heads 4..7);
+//            (g, r) reads bytes [64*ks + 16*g, +16) of key row r).  Head h sits in row 4 (h % 4) + h / 4 of A, so lane (g, r)
+//            gets the logits of token r for heads g and g + 4: with the heads in rows 0, 1, ... one row group of lanes
+//            held up to four heads and the others none, i.e. four times the vector instructions of the softmax, and
+//            16 waves of a CU share four vector units (8 units x 16 pages, from the tiles' request to the last wave's sums:
+//            2.95 us then, 2.5 now; 32 x 512 rows by position 8.9 and 8.4);
 //   softmax  running maximum and denominator per head, shared by the whole wave (DPP row maxima),
 //            fp32; the 16 x G weights cross to the matrix-operand layout via LDS;
 //   values   also on the matrix cores: out[head][dim] += sum_token p[head][token] v[token][dim] as
@@ -80,13 +83,19 @@ __device__ inline void list_bits(const uint32_t *mask, int words, int lane, int 
 // barrier, or while the first tiles are on their way, it was 0.3 us longer for 16 winners.)
 __host__ __device__ constexpr int attend_scratch_floats(int G, int NW) { return NW * (G * (kD + 2) + 16 * 8); }
 
+// the head in row r of the attention's query operand, -1: a zero row
+template <int G>
+__device__ inline int operand_head(int r) {
+    const int hg = r >> 2, v = r & 3;
+    return v < (G + 3) / 4 && hg < (G < 4 ? G : 4) ? hg + 4 * v : -1;
+}
 template <int G>
 __device__ inline void load_query_operand(const bf16_t *q, int u, int lane, bf16x8 (&qa)[4], float *sumsq) {
-    const int g = lane >> 4, ch = lane & 15;
+    const int g = lane >> 4, h = operand_head<G>(lane & 15);
     float nn = 0.f;
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
-        const uint4 w = ch < G ? ((const uint4 *)(q + ((size_t)u * G + ch) * kD))[ks * 4 + g] : make_uint4(0, 0, 0, 0);
+        const uint4 w = h >= 0 ? ((const uint4 *)(q + ((size_t)u * G + h) * kD))[ks * 4 + g] : make_uint4(0, 0, 0, 0);
         qa[ks] = __builtin_bit_cast(bf16x8, w);
         nn += dot8(w, w);
     }
@@ -115,38 +124,50 @@ struct SplitRow {
     // The A operand straight from memory: lane (g, c) holds q_c dims [64t + 8g, +8) for c < G and
     // q_{c-G} dims [64t + 32 + 8g, +8) for G <= c < 2G (t = 0, 1), zeros from row 2G on.  *inv_norm =
     // 1 / max(||q_h||, 1e-20) on the lanes with c = h and c = G + h.
-    __device__ static void load_query(const bf16_t *q, int u, int lane, bf16x8 (&qs)[2], float *inv_norm) {
+    __device__ static void request_query(const bf16_t *q, int u, int lane, uint4 (&w)[2]) {
         const int g = lane >> 4, c = lane & 15;
         const int upper = c >= G ? 1 : 0, h = c - G * upper;
         const uint4 *row = (const uint4 *)(q + ((size_t)u * G + h) * kD);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) w[t] = c < 2 * G ? row[8 * t + 4 * upper + g] : make_uint4(0, 0, 0, 0);
+    }
+    __device__ static void take_query(const uint4 (&w)[2], bf16x8 (&qs)[2], float *inv_norm) {
         float nn = 0.f;
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
-            const uint4 w = c < 2 * G ? row[8 * t + 4 * upper + g] : make_uint4(0, 0, 0, 0);
-            qs[t] = __builtin_bit_cast(bf16x8, w);
-            nn += dot8(w, w);
+            qs[t] = __builtin_bit_cast(bf16x8, w[t]);
+            nn += dot8(w[t], w[t]);
         }
         nn += __shfl_xor(nn, 16);
         nn += __shfl_xor(nn, 32);
         nn += __shfl_xor(nn, G);  // the other half of the row
         *inv_norm = 1.0f / fmaxf(sqrtf(nn), 1e-20f);
     }
-    // The plain operand of the logit MFMAs (lane (g, h): dims [32ks + 8g, +8) of q_h, zero rows from
-    // G on) out of the split one, by lane exchange: no second trip to memory for the query rows.
+    __device__ static void load_query(const bf16_t *q, int u, int lane, bf16x8 (&qs)[2], float *inv_norm) {
+        uint4 w[2];
+        request_query(q, u, lane, w);
+        take_query(w, qs, inv_norm);
+    }
+    // The operand of the logit MFMAs (lane (g, r): dims [32ks + 8g, +8) of the head in row r, zeros where there is none) out of
+    // the split one, by lane exchange: no second trip to memory for the query rows.
     __device__ static void to_plain(const bf16x8 (&qs)[2], int lane, bf16x8 (&qa)[4]) {
-        const bool low = (lane & 15) < G;
+        const int h = operand_head<G>(lane & 15);
         const uint4 zero = make_uint4(0, 0, 0, 0);
-        const int src = (lane + G) & 63;  // row G + h holds the upper halves of q_h
+        const int src = (lane & 48) + max(h, 0);  // row h holds the lower halves of q_h, row G + h the upper ones
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
             const uint4 w = __builtin_bit_cast(uint4, qs[t]);
-            uint4 up;
-            up.x = __shfl(w.x, src);
-            up.y = __shfl(w.y, src);
-            up.z = __shfl(w.z, src);
-            up.w = __shfl(w.w, src);
-            qa[2 * t] = __builtin_bit_cast(bf16x8, low ? w : zero);
-            qa[2 * t + 1] = __builtin_bit_cast(bf16x8, low ? up : zero);
+            uint4 lo, up;
+            lo.x = __shfl(w.x, src);
+            lo.y = __shfl(w.y, src);
+            lo.z = __shfl(w.z, src);
+            lo.w = __shfl(w.w, src);
+            up.x = __shfl(w.x, src + G);
+            up.y = __shfl(w.y, src + G);
+            up.z = __shfl(w.z, src + G);
+            up.w = __shfl(w.w, src + G);
+            qa[2 * t] = __builtin_bit_cast(bf16x8, h >= 0 ? lo : zero);
+            qa[2 * t + 1] = __builtin_bit_cast(bf16x8, h >= 0 ? up : zero);
         }
     }
     // uint4 index inside a 16-row block (rows of 16 uint4) of the load that feeds MFMA t of 8-row
@@ -185,7 +206,7 @@ struct SplitRow {
 template <int G, int NW, int RES, bool PARTIAL, bool FILLS, typename PageOf, typename Aside>
 __device__ inline void attend_pages(const Dev &d, int u, const bf16x8 (&qa)[4], PageOf page_of, int ns, Resident res,
                                     float *__restrict__ out, float *red, Aside aside) {
-    constexpr int GR = (G + 3) / 4;  // row groups that hold logits and outputs
+    constexpr int HV = (G + 3) / 4;  // heads per lane: g + 4 v, v < HV, on lanes (g, .) with g < G
     float(*wacc)[G][kD] = (float(*)[G][kD])red;                   // [NW][G][128]
     float(*wm)[G] = (float(*)[G])(red + NW * G * kD);             // [NW][G]
     float(*wl)[G] = (float(*)[G])(red + NW * G * (kD + 1));       // [NW][G]
@@ -194,12 +215,12 @@ __device__ inline void attend_pages(const Dev &d, int u, const bf16x8 (&qa)[4], 
     float *px = red + NW * G * (kD + 2) + wave * (16 * 8);        // [16 tokens][8 heads] weights of this wave
     const float scale = 0.08838834764831845f;  // 1/sqrt(128)
     const int s = d.s;
-    // lane (g, r): m, l of heads 4g..4g+3 (wave-wide maxima, own-token denominators);
-    // acc[j][v] = output of head 4g+v, dim 8r+j
-    float m[4], l[4];
+    // lane (g, r): m, l of heads g + 4 v (wave-wide maxima, own-token denominators);
+    // acc[j][v] = output of head g + 4 v, dim 8r+j
+    float m[HV], l[HV];
     f32x4 acc[8];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) { m[v] = -INFINITY; l[v] = 0.f; }
+    for (int v = 0; v < HV; ++v) { m[v] = -INFINITY; l[v] = 0.f; }
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
     bool first = true;
@@ -213,29 +234,33 @@ __device__ inline void attend_pages(const Dev &d, int u, const bf16x8 (&qa)[4], 
             z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[ks], __builtin_bit_cast(bf16x8, kb[ks]), z, 0, 0, 0);
         next_keys();
         const bool tok_ok = ch < nv;  // this lane's logits belong to token ch of the block
-        float pw[4], alpha[4];
+        float pw[HV], alpha[HV];
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
+        for (int v = 0; v < HV; ++v) {
             const float zz = tok_ok ? z[v] * scale : -INFINITY;
             float mx = zz;
             mx = fmaxf(mx, dpp_f32<0xB1>(mx));
             mx = fmaxf(mx, dpp_f32<0x4E>(mx));
             mx = fmaxf(mx, dpp_f32<0x141>(mx));
-            mx = fmaxf(mx, dpp_f32<0x140>(mx));   // block maximum of head 4g+v on all 16 lanes of the row
+            mx = fmaxf(mx, dpp_f32<0x140>(mx));   // block maximum of head g + 4 v on all 16 lanes of the row
             const float mn = fmaxf(m[v], mx);     // finite: every block has at least one token
             alpha[v] = __expf(m[v] - mn);
             pw[v] = __expf(zz - mn);
             l[v] = l[v] * alpha[v] + pw[v];
             m[v] = mn;
         }
-        if (g < GR) *(float4 *)(px + ch * 8 + 4 * g) = make_float4(pw[0], pw[1], pw[2], pw[3]);
+        if (g < G) {  // (head g + 4 v in slot HV g + v)
+            if constexpr (HV == 2) *(float2 *)(px + ch * 8 + 2 * g) = make_float2(pw[0], pw[1]);
+            else px[ch * 8 + g] = pw[0];
+        }
         __builtin_amdgcn_wave_barrier();
-        // A operand: lane (g, h) holds p[head h][token 4i+g], i = 0..3, as hi + lo bf16 terms
+        // A operand: lane (g, r) holds p[head in row r][token 4i+g], i = 0..3, as hi + lo bf16 terms
         float pa[4];
+        const bool row_used = operand_head<G>(ch) >= 0;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const float t = px[(4 * i + g) * 8 + (ch & 7)];  // (unconditional read, then select: no branch)
-            pa[i] = ch < G ? t : 0.f;
+            const float t = px[(4 * i + g) * 8 + HV * (ch >> 2) + (ch & (HV - 1))];  // (unconditional read, then select: no branch)
+            pa[i] = row_used ? t : 0.f;
         }
         uint32_t hi[4], lo[4];
 #pragma unroll
@@ -249,7 +274,7 @@ __device__ inline void attend_pages(const Dev &d, int u, const bf16x8 (&qa)[4], 
 #pragma unroll
             for (int j = 0; j < 8; ++j)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) acc[j][v] *= alpha[v];
+                for (int v = 0; v < HV; ++v) acc[j][v] *= alpha[v];
         }
         first = false;
         if (nv < 16) {  // a partly filled block: rows past the end must not reach the matrix core
@@ -435,22 +460,15 @@ __device__ inline void attend_pages(const Dev &d, int u, const bf16x8 (&qa)[4], 
         }
     }
     ICE_STAMP(10);
-    if (g < GR) {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            if (4 * g + v < G) {
-                float *dst = &wacc[wave][4 * g + v][ch * 8];
-                *(float4 *)dst = make_float4(acc[0][v], acc[1][v], acc[2][v], acc[3][v]);
-                *(float4 *)(dst + 4) = make_float4(acc[4][v], acc[5][v], acc[6][v], acc[7][v]);
-            }
+    for (int v = 0; v < HV; ++v) {
+        l[v] = row16_sum(l[v]);
+        if (g < G) {  // (with more than four heads every g + 4 v is one)
+            float *dst = &wacc[wave][g + 4 * v][ch * 8];
+            *(float4 *)dst = make_float4(acc[0][v], acc[1][v], acc[2][v], acc[3][v]);
+            *(float4 *)(dst + 4) = make_float4(acc[4][v], acc[5][v], acc[6][v], acc[7][v]);
+            if (ch == 0) { wm[wave][g + 4 * v] = m[v]; wl[wave][g + 4 * v] = l[v]; }
         }
-    }
-#pragma unroll
-    for (int v = 0; v < 4; ++v) l[v] = row16_sum(l[v]);
-    if (g < GR && ch == 0) {
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-            if (4 * g + v < G) { wm[wave][4 * g + v] = m[v]; wl[wave][4 * g + v] = l[v]; }
     }
     __syncthreads();
     ICE_STAMP(11);
