@@ -245,10 +245,11 @@ ice_status_t ice_build_index(ice_index_t *ix, const void *K, const void *V, int3
     int cur = 0;
     if (d.tk) launch_key_aug(d, Kb, n, s);
     launch_init_centroids(d, Kb, n, ix->cfg.init_idx, ix->cfg.seed, cur, s);
+    const bool fused = sort_is_fused(d, n);
     for (int t = 0; t < ix->cfg.kmeans_iters; ++t) {
-        if (reassign_pays(d, n, t)) launch_reassign(d, Kb, n, cur, t, s);
-        else launch_assign(d, Kb, n, cur, t, s);
-        launch_sort(d, n, t, nullptr, nullptr, s);
+        if (reassign_pays(d, n, t)) launch_reassign(d, Kb, n, cur, t, fused, s);
+        else launch_assign(d, Kb, n, cur, t, fused, s);
+        if (!fused) launch_sort(d, n, t, nullptr, nullptr, s);
         launch_means(d, Kb, n, cur, t, s);
         cur ^= 1;
     }
@@ -574,7 +575,7 @@ ice_status_t ice_debug_assign(ice_index_t *ix, const void *K, int32_t n, const v
     hipStream_t s = static_cast<hipStream_t>(stream);
     const Dev &d = ix->dev;
     launch_load_centroids(d, static_cast<const bf16_t *>(cent), 0, s);
-    launch_assign(d, static_cast<const bf16_t *>(K), n, 0, 0, s);
+    launch_assign(d, static_cast<const bf16_t *>(K), n, 0, 0, false, s);
     if (assign_out) launch_sort(d, n, 0, best_out, assign_out, s);  // (unpacks the winners; without it only the kernel is timed)
     return device_status("ice_debug_assign");
 }
@@ -589,7 +590,7 @@ ice_status_t ice_debug_rerun_stage(ice_index_t *ix, const void *K, const void *V
     const bf16_t *Kb = static_cast<const bf16_t *>(K), *Vb = static_cast<const bf16_t *>(V);
     const int n = ix->build_n, prev = ix->cur ^ 1;  // the last round read buffer `prev` and wrote the live one
     switch (stage) {
-        case ICE_STAGE_ASSIGN: launch_assign(d, Kb, n, prev, 0, s); break;
+        case ICE_STAGE_ASSIGN: launch_assign(d, Kb, n, prev, 0, false, s); break;
         case ICE_STAGE_SORT: launch_sort(d, n, 0, nullptr, nullptr, s); break;
         case ICE_STAGE_MEANS: launch_means(d, Kb, n, prev, 0, s); break;
         case ICE_STAGE_PAGINATE: launch_paginate(d, Kb, Vb, n, false, s); break;

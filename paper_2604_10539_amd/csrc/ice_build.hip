@@ -308,6 +308,180 @@ __global__ __launch_bounds__(256) void clear_winners_kernel(Dev d, int n, const 
 }
 
 // ------------------------------------------------------------------------------------------------
+// Sorting the tokens by cluster (ascending position inside a cluster), range by range: a unit's tokens
+// are cut into R ranges of L, one workgroup each, and every range is sorted by itself (`order`, stable
+// counting sort) with every cluster's piece (first slot, members) beside it (`range_off`).  The members of
+// a cluster in ascending position are its pieces of range 0, 1, ...: what reads members (the means, the
+// page layout) finds member j through the pieces' lengths (Pieces), so no pass over the
+// whole unit ties the ranges together: one launch per round, bound by its latencies.  (With a second
+// launch that turned the ranges' totals into unit-wide positions the two took 17.2 us per round at
+// 8 units x 32768 tokens x 512 clusters and 32 us at 131072 x 2048, most of it reading R totals per
+// cluster in every workgroup; this one takes 6.1 and 16 us, and the means
+// read their lists at 3 to 6 us more.  A fifth wave in the means that prepared the next cluster's list while
+// four summed was slower, 24 against 17.3 us: its chain of list reads is the longer one.)
+// A range is cut into W segments, one per wave.  A wave walks its segment 64 tokens at a time: lanes
+// with the same cluster find each other bit by bit of the id (ballots), the first of them moves the
+// segment's counter of that cluster past all of them, and a token's rank among its cluster's
+// members of the segment stays in its register.  The counters are then scanned over segments and
+// clusters and every token's slot is counter + rank.  W x Cpad counters of 4 bytes fit 144 KB.
+constexpr int kSortCounters = 36864, kSortMaxSeg = 2048;  // LDS counters; tokens per segment at most
+
+static int sort_segments(int Cpad) {
+    int W = 16;
+    while (W * Cpad > kSortCounters) W /= 2;  // (Cpad <= 8192: W >= 4)
+    return W;
+}
+static int sort_max_len(int Cpad) { return sort_segments(Cpad) * kSortMaxSeg; }
+static int sort_range_len(int U, int n, int Cpad) {
+    // short ranges keep the chip busy, few ranges keep the reading of their pieces short: at most 64 per
+    // unit and one workgroup per CU unless even the longest ranges are more (256 units x 32768 tokens: two
+    // ranges 80 us and the means 426, one range 94 and 411; 64 units: eight ranges 24 and 115, four 20 and 109)
+    int L = 1024;
+    while (L < sort_max_len(Cpad) && L < n && ((n + L - 1) / L > 64 || (long long)U * ((n + L - 1) / L) > 256)) L *= 2;
+    return L;
+}
+// Whether a build's assignment sorts its runs itself (a run is then a range of the sort): one slice of centroids, at most
+// kFusedRun tiles per workgroup (their winners sit in LDS), one workgroup per CU and at most 64 ranges per unit.  A launch and
+// the reading of the winners less per round; assignment and sort by themselves and in one, us: 8 units x 4000 x 62 5.2 + 5.8 and
+// 7.6, 8 x 16384 x 256 13.0 + 6.3 and 15.8, 8 x 32768 x 512 34.7 + 7.2 and 38.1, 16 x 23457 x 366 (transformed) 40.9 + 9.0 and 46.0.
+constexpr int kFusedRun = 16;
+static int assign_run(int U, int n, int slices);
+bool sort_is_fused(const Dev &d, int n) {
+    if (d.Cpad > 512) return false;
+    const int run = assign_run(d.U, n, 1), R = (n + run * kAssignTile - 1) / (run * kAssignTile);
+    return run <= kFusedRun && R <= 64 && (long long)d.U * R <= 256;
+}
+// tokens per range of the sort
+static int sort_len(const Dev &d, int n) { return sort_is_fused(d, n) ? assign_run(d.U, n, 1) * kAssignTile : sort_range_len(d.U, n, d.Cpad); }
+size_t sort_ranges_max(int U, int max_tokens, int Cpad) {
+    const int L = sort_max_len(Cpad);
+    return std::max<size_t>(std::max(256, U), (size_t)U * (((size_t)max_tokens + L - 1) / L));
+}
+
+// NG: groups of 64 tokens per wave at most.  MASK: the lanes of a group with the same cluster meet in a 64-bit lane mask per
+// cluster in LDS (OR, read back, clear) instead of by ballots: cheaper per group, but the masks have to be cleared and
+// take 8 more bytes per counter, so it is for long ranges (256 units x 32768 tokens: 78 us with ballots, 69 so).
+// The sort of tokens [rb, re) of unit u, its range r of R, by a workgroup of NWV waves; W segments of `seg` tokens.
+// winner(i): cluster of token i, best_of(i): what goes to best_out.  Every thread comes here.
+template <int NWV, int NG, bool MASK, typename Winner, typename BestOf>
+__device__ inline void sort_range(const Dev &d, int u, int n, int r, int R, int rb, int re, int seg, int W, int nbits, int round, int goes,
+                                  int *pos_all, float *best_out, int *assign_out, Winner winner, BestOf best_of) {
+    constexpr int NT = NWV * 64;
+    __shared__ int wsum[NWV];
+    __shared__ int carry;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int Cpad = d.Cpad;
+    const int beg = min(re, rb + wave * seg), end = wave < W ? min(re, beg + seg) : beg;  // this wave's tokens
+    uint32_t v[NG];
+    constexpr bool AHEAD = NG <= 16;  // (the registers of the longest form do not hold the last round's clusters as well)
+    int was[AHEAD ? NG : 1];
+#pragma unroll
+    for (int j = 0; j < NG; ++j) {
+        const int i = beg + j * 64 + lane;
+        v[j] = i < end ? winner(i) : 0u;
+        if constexpr (AHEAD) was[j] = round > 0 && i < end ? d.assign[(size_t)u * d.max_tokens + i] : 0;
+    }
+    if (goes == 0) return;  // (no centroid moved: nor did a token)
+    for (int x = tid; x < W * Cpad / 4 * (MASK ? 3 : 1); x += NT) ((int4 *)pos_all)[x] = make_int4(0, 0, 0, 0);  // (Cpad is a multiple of 32)
+    if (tid == 0) carry = 0;
+    __syncthreads();
+    // ---- rank inside the segment (row `wave` of the counters is this wave's alone)
+    int *pos = pos_all + (wave < W ? wave : 0) * Cpad;
+    u64 *mask = (u64 *)(pos_all + W * Cpad) + (size_t)(wave < W ? wave : 0) * Cpad;  // (MASK)
+    const u64 lt = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int j = 0; j < NG; ++j) {  // v[j]: from here on cluster << 16 | rank
+        const int i = beg + j * 64 + lane;
+        const bool valid = i < end;
+        // (always < C for finite keys; a key with no finite score may come out with a padding row: it goes to the last
+        // cluster, so that every token has a page whatever its key holds)
+        const int a = (int)min(v[j], (uint32_t)d.C - 1u);
+        v[j] = (uint32_t)a << 16;
+        if (beg + j * 64 >= end) continue;  // (wave-uniform)
+        u64 peers;
+        if constexpr (MASK) {
+            if (valid) atomicOr(&mask[a], 1ull << lane);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            peers = valid ? mask[a] : 0ull;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (valid) mask[a] = 0ull;
+        } else {
+            peers = __ballot(valid);
+            for (int b = 0; b < nbits; ++b) {
+                const bool bit = (a >> b) & 1;
+                const u64 m = __ballot(bit);
+                peers &= bit ? m : ~m;
+            }
+        }
+        if (valid) {
+            const int base = pos[a];
+            v[j] |= (uint32_t)(base + (int)__popcll(peers & lt));
+            if ((peers & lt) == 0ull) pos[a] = base + (int)__popcll(peers);
+            if constexpr (!AHEAD) {
+                if (round > 0) {
+                    const int b = d.assign[(size_t)u * d.max_tokens + i];
+                    if (a != b) d.touched[(size_t)u * Cpad + a] = d.touched[(size_t)u * Cpad + b] = 1;
+                }
+            }
+            d.assign[(size_t)u * d.max_tokens + i] = a;
+            if (assign_out) assign_out[(size_t)u * n + i] = a;
+            if (best_out) best_out[(size_t)u * n + i] = best_of(i);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // (the LDS unit executes a wave's accesses in order)
+    }
+    if (AHEAD && round > 0) {  // a later round of a build: the clusters that lost or gained a token are marked
+        // (a range without such a token could be left as it is, but finding that out for the whole workgroup takes as long
+        // as sorting 1024 tokens: 6.3 us with the exit taken or not)
+#pragma unroll
+        for (int j = 0; j < NG; ++j) {
+            const int i = beg + j * 64 + lane;
+            if (i < end) {
+                const int a = (int)(v[j] >> 16), b = was[AHEAD ? j : 0];
+                if (a != b) d.touched[(size_t)u * Cpad + a] = d.touched[(size_t)u * Cpad + b] = 1;
+            }
+        }
+    }
+    __syncthreads();
+    // ---- scan over segments and clusters
+    uint32_t *off = d.range_off + ((size_t)u * R + r) * Cpad;
+    for (int c0 = 0; c0 < Cpad; c0 += NT) {
+        const int c = c0 + tid;
+        int t[NWV], tot = 0;
+#pragma unroll
+        for (int w = 0; w < NWV; ++w) {
+            t[w] = c < Cpad && w < W ? pos_all[w * Cpad + c] : 0;
+            tot += t[w];
+        }
+        const int incl = wave_scan_add(tot);
+        if (lane == 63) wsum[wave] = incl;
+        __syncthreads();
+        int ex = carry + incl - tot;
+#pragma unroll
+        for (int w = 0; w < NWV; ++w) ex += w < wave ? wsum[w] : 0;
+        if (c < Cpad) {
+            off[c] = (uint32_t)ex << 16 | (uint32_t)tot;  // (both at most 32768)
+            int run = ex;
+#pragma unroll
+            for (int w = 0; w < NWV; ++w) {
+                if (w < W) pos_all[w * Cpad + c] = run;
+                run += t[w];
+            }
+        }
+        __syncthreads();
+        if (c0 + NT >= Cpad) break;
+        if (tid == NT - 1) carry = ex + tot;  // (threads past Cpad add nothing)
+        __syncthreads();
+    }
+    // ---- place
+    int *order = d.order + (size_t)u * d.max_tokens + rb;
+#pragma unroll
+    for (int j = 0; j < NG; ++j) {
+        const int i = beg + j * 64 + lane;
+        if (i < end) order[pos[v[j] >> 16] + (int)(v[j] & 0xFFFFu)] = i;
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
 // Nearest centroid on the matrix cores.
 //   score(i, c) = k_i . mu~_c - ||mu~_c||^2 / 2      (argmax score == argmin ||k_i - mu~_c||^2)
 // A dense (keys x 128) by (128 x centroids) contraction: v_mfma_f32_32x32x16_bf16 with the
@@ -379,13 +553,14 @@ __host__ __device__ constexpr int assign_lds_bytes(bool aug) {
 template <int CT, int CW, bool AUG, bool FULL>
 __global__ __launch_bounds__(512) void assign_kernel(const bf16_t *__restrict__ K, const bf16_t *__restrict__ cent,
                                                       const float *__restrict__ cnorm, int n, int keys_per_wg, int zsplit,
-                                                      int Cpad, int cur, const int *__restrict__ go, Dev d) {  // (scalars first: preloaded at wave start)
+                                                      int Cpad, int cur, const int *__restrict__ go, int sort_round, Dev d) {  // (scalars first: preloaded at wave start)
     constexpr int KW = 8 / CW;
     constexpr int KS = AUG ? 9 : 8;  // 16-wide steps of the contraction
     extern __shared__ __align__(16) char smem[];
     char *keys = smem;                                                // [2][256][256 B], chunks swizzled
     uint4 *kext = (uint4 *)(smem + 2 * kAssignTile * 256);            // (AUG) [2][256][2] companion chunks
     u64 *best = (u64 *)(smem + 2 * kAssignTile * 256 + (AUG ? 2 * kAssignTile * 32 : 0));  // [2][256]
+    uint16_t *won = (uint16_t *)(best + 2 * kAssignTile);             // [keys_per_wg] (sort_round >= 0) the run's winners
     // byte offset of chunk c of row r inside a buffer
     auto slot = [](int r, int c) { return r * 256 + ((c ^ (r & 15)) << 4); };
 
@@ -405,6 +580,7 @@ __global__ __launch_bounds__(512) void assign_kernel(const bf16_t *__restrict__ 
     const int ntiles = (kend - k0 + kAssignTile - 1) / kAssignTile;
     const bf16_t *Ku = K + (size_t)u * n * kD;
 
+    if (sort_round >= 0 && blockIdx.x == 0 && tid == 0) d.any_moved[2 * u + (sort_round & 1)] = 0;  // (for this round's means)
     ICE_BSTAMP(0);
     // Prologue.  The workgroup's block of centroid rows goes to LDS with fully coalesced 16-byte
     // loads (the staging area is the key buffers, not yet in use) and every wave then picks its
@@ -598,9 +774,16 @@ __global__ __launch_bounds__(512) void assign_kernel(const bf16_t *__restrict__ 
                 u64 *dst = d.packed + (size_t)u * d.max_tokens + key;
                 if (zsplit == 1) *dst = bestt[tid];
                 else atomicMax(dst, bestt[tid]);
+                if (sort_round >= 0) won[t * kAssignTile + tid] = (uint16_t)(0xFFFFFFFFu - (uint32_t)bestt[tid]);
             }
             bestt[tid] = 0ull;
         }
+    }
+    if (sort_round >= 0) {  // the run is a range of the sort as well
+        __syncthreads();    // (the winners are there; the key tiles are not needed any more)
+        sort_range<8, kFusedRun / 2, false>(d, u, n, blockIdx.x, gridDim.x, k0, kend, keys_per_wg / 8, 8, 32 - __builtin_clz((unsigned)Cpad - 1u),
+                                            sort_round, 1, (int *)smem, nullptr, nullptr, [=](int i) { return (uint32_t)won[i - k0]; },
+                                            [](int) { return 0.f; });
     }
 }
 
@@ -627,7 +810,7 @@ static int assign_run(int U, int n, int slices) {
 // whether a centroid of the unit moved in the round before round t: element 2 u of the result (all units go in the first round)
 static const int *round_goes(const Dev &d, int t) { return t > 0 ? d.any_moved + ((t - 1) & 1) : nullptr; }
 
-void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, int t, hipStream_t st) {
+void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fused, hipStream_t st) {
     const int tiles = d.Cpad / 32;
     int CT = tiles == 1 ? 1 : 2, CW = 1;
     while (CW < 8 && CW * CT < tiles) CW *= 2;
@@ -640,7 +823,7 @@ void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, int t, hipStre
     // with 625 clusters, 160 workgroups of 8 tiles against 256 of 10, 1314 us against 1031.)
     const int keys_per_wg = assign_run(d.U, n, zsplit) * kAssignTile;
     dim3 grid((n + keys_per_wg - 1) / keys_per_wg, zsplit, d.U);
-    const size_t lds = assign_lds_bytes(d.tk != 0);
+    const size_t lds = assign_lds_bytes(d.tk != 0) + (fused ? (size_t)keys_per_wg * 2 : 0);
     if (zsplit > 1) {
         hipLaunchKernelGGL(clear_winners_kernel, dim3((n + 255) / 256, d.U), dim3(256), 0, st, d, n, round_goes(d, t));
     }
@@ -649,7 +832,7 @@ void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, int t, hipStre
     do {                                                                                            \
         allow_dynamic_lds((const void *)assign_kernel<ct, cw, aug, full>, lds);                     \
         hipLaunchKernelGGL((assign_kernel<ct, cw, aug, full>), grid, dim3(512), lds, st, K, d.cent_bf16[cur], d.cnorm[cur], n, \
-                           keys_per_wg, zsplit, d.Cpad, cur, round_goes(d, t), d);                  \
+                           keys_per_wg, zsplit, d.Cpad, cur, round_goes(d, t), fused ? t : -1, d);  \
     } while (0)
 #define ICE_ASSIGN_A(ct, cw, aug)                                                                   \
     do {                                                                                            \
@@ -700,7 +883,7 @@ __device__ inline bool ordered_is_nan(uint32_t k) { return k > 0xFF800000u || k 
 template <bool AUG>
 __global__ __launch_bounds__(512) void reassign_kernel(const bf16_t *__restrict__ K, const bf16_t *__restrict__ cent,
                                                        const float *__restrict__ cnorm, int n, int keys_per_wg, int Cpad, int cur,
-                                                       int C, const int *__restrict__ go, Dev d) {  // (scalars first: preloaded at wave start)
+                                                       int C, const int *__restrict__ go, int sort_round, Dev d) {  // (scalars first: preloaded at wave start)
     constexpr int KS = AUG ? 9 : 8;
     extern __shared__ __align__(16) char smem[];
     char *keys = smem;                                             // [2][256][256 B], chunks swizzled as in assign_kernel
@@ -747,6 +930,7 @@ __global__ __launch_bounds__(512) void reassign_kernel(const bf16_t *__restrict_
         }
     };
 
+    if (sort_round >= 0 && blockIdx.x == 0 && tid == 0) d.any_moved[2 * u + (sort_round & 1)] = 0;  // (for this round's means)
     // ---- which centroids moved
     {
         const int lane = tid & 63, goes = go[2 * u];
@@ -999,14 +1183,23 @@ __global__ __launch_bounds__(512) void reassign_kernel(const bf16_t *__restrict_
             else if (nt < 16) slice(std::integral_constant<int, 8>{}, std::false_type{}, c0);
             else slice(std::integral_constant<int, 8>{}, std::true_type{}, c0);
         }
-        if (job != kMovedCentroids) return;
+        if (job != kMovedCentroids) break;
         wait_vmem();  // (the key lists of all waves are read by all)
         __threadfence_block();
         __syncthreads();
         nk = __builtin_amdgcn_readfirstlane(sh_fails);
-        if (nk == 0) return;
+        if (nk == 0) break;
         job = kListedKeys;
         ncent = Cpad;
+    }
+    if (sort_round >= 0) {  // the run is a range of the sort as well
+        wait_vmem();
+        __threadfence_block();
+        __syncthreads();
+        const uint32_t *pk = (const uint32_t *)packed;
+        sort_range<8, kFusedRun / 2, false>(d, u, n, blockIdx.x, gridDim.x, k0, min(n, k0 + keys_per_wg), keys_per_wg / 8, 8,
+                                            32 - __builtin_clz((unsigned)Cpad - 1u), sort_round, 1, (int *)smem, nullptr, nullptr,
+                                            [=](int i) { return 0xFFFFFFFFu - pk[2 * i]; }, [](int) { return 0.f; });
     }
 }
 
@@ -1019,7 +1212,7 @@ bool reassign_pays(const Dev &d, int n, int t) {
     return t >= 2 && assign_run(d.U, n, 1) * (16 * full + rest) >= 64;
 }
 
-void launch_reassign(const Dev &d, const bf16_t *K, int n, int cur, int t, hipStream_t st) {
+void launch_reassign(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fused, hipStream_t st) {
     const int keys_per_wg = assign_run(d.U, n, 1) * kAssignTile;
     const size_t lds = reassign_lds_bytes(d.tk != 0, d.Cpad);
     const dim3 grid((n + keys_per_wg - 1) / keys_per_wg, d.U);
@@ -1027,7 +1220,7 @@ void launch_reassign(const Dev &d, const bf16_t *K, int n, int cur, int t, hipSt
     do {                                                                                                                   \
         allow_dynamic_lds((const void *)reassign_kernel<aug>, lds);                                                        \
         hipLaunchKernelGGL((reassign_kernel<aug>), grid, dim3(512), lds, st, K, d.cent_bf16[cur], d.cnorm[cur], n, keys_per_wg, d.Cpad, \
-                           cur, d.C, round_goes(d, t), d);                                                                 \
+                           cur, d.C, round_goes(d, t), fused ? t : -1, d);                                                 \
     } while (0)
     if (d.tk) ICE_REASSIGN(true);
     else ICE_REASSIGN(false);
@@ -1035,167 +1228,22 @@ void launch_reassign(const Dev &d, const bf16_t *K, int n, int cur, int t, hipSt
 }
 
 // ------------------------------------------------------------------------------------------------
-// Sorting the tokens by cluster (ascending position inside a cluster), range by range: a unit's tokens
-// are cut into R ranges of L, one workgroup each, and every range is sorted by itself (`order`, stable
-// counting sort) with every cluster's piece (first slot, members) beside it (`range_off`).  The members of
-// a cluster in ascending position are its pieces of range 0, 1, ...: what reads members (the means, the
-// page layout) finds member j through the pieces' lengths (Pieces), so no pass over the
-// whole unit ties the ranges together: one launch per round, bound by its latencies.  (With a second
-// launch that turned the ranges' totals into unit-wide positions the two took 17.2 us per round at
-// 8 units x 32768 tokens x 512 clusters and 32 us at 131072 x 2048, most of it reading R totals per
-// cluster in every workgroup; this one takes 6.1 and 16 us, and the means
-// read their lists at 3 to 6 us more.  A fifth wave in the means that prepared the next cluster's list while
-// four summed was slower, 24 against 17.3 us: its chain of list reads is the longer one.)
-// A range is cut into W segments, one per wave.  A wave walks its segment 64 tokens at a time: lanes
-// with the same cluster find each other bit by bit of the id (ballots), the first of them moves the
-// segment's counter of that cluster past all of them, and a token's rank among its cluster's
-// members of the segment stays in its register.  The counters are then scanned over segments and
-// clusters and every token's slot is counter + rank.  W x Cpad counters of 4 bytes fit 144 KB.
-constexpr int kSortCounters = 36864, kSortMaxSeg = 2048;  // LDS counters; tokens per segment at most
-
-static int sort_segments(int Cpad) {
-    int W = 16;
-    while (W * Cpad > kSortCounters) W /= 2;  // (Cpad <= 8192: W >= 4)
-    return W;
-}
-static int sort_max_len(int Cpad) { return sort_segments(Cpad) * kSortMaxSeg; }
-int sort_range_len(int U, int n, int Cpad) {
-    // short ranges keep the chip busy, few ranges keep the reading of their pieces short: at most 64 per
-    // unit and one workgroup per CU unless even the longest ranges are more (256 units x 32768 tokens: two
-    // ranges 80 us and the means 426, one range 94 and 411; 64 units: eight ranges 24 and 115, four 20 and 109)
-    int L = 1024;
-    while (L < sort_max_len(Cpad) && L < n && ((n + L - 1) / L > 64 || (long long)U * ((n + L - 1) / L) > 256)) L *= 2;
-    return L;
-}
-size_t sort_ranges_max(int U, int max_tokens, int Cpad) {
-    const int L = sort_max_len(Cpad);
-    return std::max<size_t>(std::max(256, U), (size_t)U * (((size_t)max_tokens + L - 1) / L));
-}
-
-// NG: groups of 64 tokens per wave at most.  MASK: the lanes of a group with the same cluster meet in a 64-bit lane mask per
-// cluster in LDS (OR, read back, clear) instead of by ballots: cheaper per group, but the masks have to be cleared and
-// take 8 more bytes per counter, so it is for long ranges (256 units x 32768 tokens: 78 us with ballots, 69 so).
+// The sort by itself
 template <int NG, bool MASK>
 __global__ __launch_bounds__(1024) void range_sort_kernel(Dev d, int n, int L, int W, int nbits, int round, float *best_out,
                                                           int *assign_out) {
     extern __shared__ __align__(16) int pos_all[];  // [W][Cpad]
-    __shared__ int wsum[16];
-    __shared__ int carry;
-    const int r = blockIdx.x, R = gridDim.x, u = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int Cpad = d.Cpad;
+    const int r = blockIdx.x, u = blockIdx.y;
     const int goes = round > 0 ? d.any_moved[2 * u + ((round - 1) & 1)] : 1;
-    if (r == 0 && tid == 0) d.any_moved[2 * u + (round & 1)] = 0;  // (for this round's means)
-    const int rb = r * L, re = min(n, rb + L), seg = L / W;
+    if (r == 0 && threadIdx.x == 0) d.any_moved[2 * u + (round & 1)] = 0;  // (for this round's means)
     // low word of a packed winner = ~cluster id (the high word, the score, is read only for best_out)
     const uint32_t *pk = (const uint32_t *)(d.packed + (size_t)u * d.max_tokens);
-    const int beg = min(re, rb + wave * seg), end = wave < W ? min(re, beg + seg) : beg;  // this wave's tokens
-    uint32_t v[NG];
-    constexpr bool AHEAD = NG <= 16;  // (the registers of the longest form do not hold the last round's clusters as well)
-    int was[AHEAD ? NG : 1];
-#pragma unroll
-    for (int j = 0; j < NG; ++j) {
-        const int i = beg + j * 64 + lane;
-        v[j] = i < end ? pk[2 * i] : 0u;
-        if constexpr (AHEAD) was[j] = round > 0 && i < end ? d.assign[(size_t)u * d.max_tokens + i] : 0;
-    }
-    if (goes == 0) return;  // (no centroid moved: nor did a token)
-    if (round > 0) {  // a later round of a build: the clusters that lost or gained a token are marked
-        // (a range without such a token could be left as it is, but finding that out for the whole workgroup takes as long
-        // as sorting 1024 tokens: 6.3 us with the exit taken or not)
-#pragma unroll
-        for (int j = 0; j < NG; ++j) {
-            const int i = beg + j * 64 + lane;
-            if (i < end) {
-                const int a = (int)min(0xFFFFFFFFu - v[j], (uint32_t)d.C - 1u), b = AHEAD ? was[AHEAD ? j : 0] : d.assign[(size_t)u * d.max_tokens + i];
-                if (a != b) d.touched[(size_t)u * Cpad + a] = d.touched[(size_t)u * Cpad + b] = 1;
-            }
-        }
-    }
-    for (int x = tid; x < W * Cpad / 4 * (MASK ? 3 : 1); x += 1024) ((int4 *)pos_all)[x] = make_int4(0, 0, 0, 0);  // (Cpad is a multiple of 32)
-    if (tid == 0) carry = 0;
-    __syncthreads();
-    // ---- rank inside the segment (row `wave` of the counters is this wave's alone)
-    int *pos = pos_all + (wave < W ? wave : 0) * Cpad;
-    u64 *mask = (u64 *)(pos_all + W * Cpad) + (size_t)(wave < W ? wave : 0) * Cpad;  // (MASK)
-    const u64 lt = (1ull << lane) - 1ull;
-#pragma unroll
-    for (int j = 0; j < NG; ++j) {  // v[j]: from here on cluster << 16 | rank
-        const int i = beg + j * 64 + lane;
-        const bool valid = i < end;
-        // (always < C for finite keys; a key with no finite score may come out with a padding row: it goes to the last
-        // cluster, so that every token has a page whatever its key holds)
-        const int a = (int)min(0xFFFFFFFFu - v[j], (uint32_t)d.C - 1u);
-        v[j] = (uint32_t)a << 16;
-        if (beg + j * 64 >= end) continue;  // (wave-uniform)
-        u64 peers;
-        if constexpr (MASK) {
-            if (valid) atomicOr(&mask[a], 1ull << lane);
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            peers = valid ? mask[a] : 0ull;
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            if (valid) mask[a] = 0ull;
-        } else {
-            peers = __ballot(valid);
-            for (int b = 0; b < nbits; ++b) {
-                const bool bit = (a >> b) & 1;
-                const u64 m = __ballot(bit);
-                peers &= bit ? m : ~m;
-            }
-        }
-        if (valid) {
-            const int base = pos[a];
-            v[j] |= (uint32_t)(base + (int)__popcll(peers & lt));
-            if ((peers & lt) == 0ull) pos[a] = base + (int)__popcll(peers);
-            d.assign[(size_t)u * d.max_tokens + i] = a;
-            if (assign_out) assign_out[(size_t)u * n + i] = a;
-            if (best_out) best_out[(size_t)u * n + i] = -2.0f * ordered_f32(pk[2 * i + 1]);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // (the LDS unit executes a wave's accesses in order)
-    }
-    __syncthreads();
-    // ---- scan over segments and clusters
-    uint32_t *off = d.range_off + ((size_t)u * R + r) * Cpad;
-    for (int c0 = 0; c0 < Cpad; c0 += 1024) {
-        const int c = c0 + tid;
-        int t[16], tot = 0;
-#pragma unroll
-        for (int w = 0; w < 16; ++w) {
-            t[w] = c < Cpad && w < W ? pos_all[w * Cpad + c] : 0;
-            tot += t[w];
-        }
-        int incl = tot;
-        for (int o = 1; o < 64; o <<= 1) {
-            const int x = __shfl_up(incl, o);
-            if (lane >= o) incl += x;
-        }
-        if (lane == 63) wsum[wave] = incl;
-        __syncthreads();
-        int ex = carry + incl - tot;
-        for (int w = 0; w < wave; ++w) ex += wsum[w];
-        if (c < Cpad) {
-            off[c] = (uint32_t)ex << 16 | (uint32_t)tot;  // (both at most 32768)
-            int run = ex;
-#pragma unroll
-            for (int w = 0; w < 16; ++w) {
-                if (w < W) pos_all[w * Cpad + c] = run;
-                run += t[w];
-            }
-        }
-        __syncthreads();
-        if (tid == 1023) carry = ex + tot;  // (threads past Cpad add nothing)
-        __syncthreads();
-    }
-    // ---- place
-    int *order = d.order + (size_t)u * d.max_tokens + rb;
-#pragma unroll
-    for (int j = 0; j < NG; ++j) {
-        const int i = beg + j * 64 + lane;
-        if (i < end) order[pos[v[j] >> 16] + (int)(v[j] & 0xFFFFu)] = i;
-    }
+    sort_range<16, NG, MASK>(d, u, n, r, gridDim.x, r * L, min(n, r * L + L), L / W, W, nbits, round, goes, pos_all, best_out, assign_out,
+                             [=](int i) { return 0xFFFFFFFFu - pk[2 * i]; }, [=](int i) { return -2.0f * ordered_f32(pk[2 * i + 1]); });
 }
 
 void launch_sort(const Dev &d, int n, int t, float *best_out, int *assign_out, hipStream_t st) {
-    const int L = sort_range_len(d.U, n, d.Cpad), R = (n + L - 1) / L, W = sort_segments(d.Cpad);
+    const int L = sort_len(d, n), R = (n + L - 1) / L, W = sort_segments(d.Cpad);
     int nbits = 0;
     while ((1 << nbits) < d.Cpad) ++nbits;
     const bool masks = L / W > 4 * 64 && W * d.Cpad * 3 <= kSortCounters;
@@ -1515,7 +1563,7 @@ __global__ __launch_bounds__(256, 8) void means_kernel(Dev d, const bf16_t *__re
 }
 
 void launch_means(const Dev &d, const bf16_t *K, int n, int cur, int t, hipStream_t st) {
-    const int L = sort_range_len(d.U, n, d.Cpad), R = (n + L - 1) / L;
+    const int L = sort_len(d, n), R = (n + L - 1) / L;
 #define ICE_MEANS(np)                                                                                                     \
     do {                                                                                                                  \
         if (keys_exceed_cache(d, n)) hipLaunchKernelGGL((means_kernel<true, np>), dim3(d.C, d.U), dim3(256), 0, st, d, K, n, cur, R, L, t); \
@@ -1645,7 +1693,7 @@ __global__ __launch_bounds__(256) void paginate_kernel(Dev d, const bf16_t *__re
 }
 
 void launch_paginate(const Dev &d, const bf16_t *K, const bf16_t *V, int n, bool arm, hipStream_t st) {
-    const int L = sort_range_len(d.U, n, d.Cpad), R = (n + L - 1) / L;
+    const int L = sort_len(d, n), R = (n + L - 1) / L;
     const size_t lds = (size_t)4 * d.s * kD * 2;
     hipLaunchKernelGGL(layout_kernel, dim3(d.U), dim3(1024), (size_t)(d.C + 1) * 4, st, d, n, arm ? 1 : 0);
 #define ICE_PAGINATE(stream)                                                                                               \

@@ -104,9 +104,11 @@ void launch_key_aug(const Dev &d, const bf16_t *K, int n, hipStream_t st);
 // The stages of round t of a build; t = 0 by itself stands for the whole stage.  A later round does again what changed since the
 // one before and leaves what all of it would: its assignment either by launch_assign (units of which a centroid moved) or, where
 // reassign_pays, by launch_reassign (moved centroids only); tokens are sorted and means formed where a token went elsewhere.
-void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, int t, hipStream_t st);
+// fused: with the sort of its runs (sort_is_fused), else launch_sort follows
+void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fused, hipStream_t st);
+bool sort_is_fused(const Dev &d, int n);
 bool reassign_pays(const Dev &d, int n, int t);
-void launch_reassign(const Dev &d, const bf16_t *K, int n, int cur, int t, hipStream_t st);
+void launch_reassign(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fused, hipStream_t st);
 void launch_sort(const Dev &d, int n, int t, float *best_out_or_null, int *assign_out_or_null, hipStream_t st);
 size_t sort_ranges_max(int U, int max_tokens, int Cpad);  // (unit, range) pairs of any sort of at most max_tokens tokens
 void launch_means(const Dev &d, const bf16_t *K, int n, int cur, int t, hipStream_t st);
