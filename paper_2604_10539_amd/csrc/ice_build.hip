@@ -341,7 +341,7 @@ static int sort_range_len(int U, int n, int Cpad) {
     return L;
 }
 // Whether a build's assignment sorts its runs itself (a run is then a range of the sort): one slice of centroids, at most
-// kFusedRun tiles per workgroup (their winners sit in LDS), one workgroup per CU and at most 64 ranges per unit.  A launch and
+// kFusedRun tiles per workgroup (their winners sit in LDS), one workgroup per CU and at most 128 ranges per unit.  A launch and
 // the reading of the winners less per round; assignment and sort by themselves and in one, us: 8 units x 4000 x 62 5.2 + 5.8 and
 // 7.6, 8 x 16384 x 256 13.0 + 6.3 and 15.8, 8 x 32768 x 512 34.7 + 7.2 and 38.1, 16 x 23457 x 366 (transformed) 40.9 + 9.0 and 46.0.
 constexpr int kFusedRun = 16;
@@ -349,7 +349,7 @@ static int assign_run(int U, int n, int slices);
 bool sort_is_fused(const Dev &d, int n) {
     if (d.Cpad > 512) return false;
     const int run = assign_run(d.U, n, 1), R = (n + run * kAssignTile - 1) / (run * kAssignTile);
-    return run <= kFusedRun && R <= 64 && (long long)d.U * R <= 256;
+    return run <= kFusedRun && R <= 128 && (long long)d.U * R <= 256;
 }
 // tokens per range of the sort
 static int sort_len(const Dev &d, int n) { return sort_is_fused(d, n) ? assign_run(d.U, n, 1) * kAssignTile : sort_range_len(d.U, n, d.Cpad); }
