@@ -1595,11 +1595,7 @@ __global__ __launch_bounds__(1024) void layout_kernel(Dev d, int n, int arm) {
         const int c = c0 + tid;
         const size_t cl = (size_t)u * C + c;
         const int cnt = c < C ? d.cluster_cnt[cl] : 0, pages = (cnt + d.s - 1) / d.s;
-        int incl = pages;
-        for (int o = 1; o < 64; o <<= 1) {
-            const int x = __shfl_up(incl, o);
-            if (lane >= o) incl += x;
-        }
+        int incl = wave_scan_add(pages);
         if (lane == 63) wsum[wave] = incl;
         __syncthreads();
         int ex = carry + incl - pages;

@@ -1043,11 +1043,7 @@ __global__ __launch_bounds__(kTokThreads) void selected_tokens_kernel(int P, int
     }
 #pragma unroll
     for (int k = 0; k < kTokPrefetch; ++k) v[k] = k * kTokThreads + tid < P << sh ? position(k * kTokThreads + tid) : -1;
-    int incl = f[0] + f[1];
-    for (int o = 1; o < 64; o <<= 1) {
-        const int t = __shfl_up(incl, o);
-        if (lane >= o) incl += t;
-    }
+    int incl = wave_scan_add(f[0] + f[1]);
     if (lane == 63) wsum[wave] = incl;
     __syncthreads();
     int before = incl - f[0] - f[1], tot = 0;
@@ -1549,11 +1545,7 @@ __global__ __launch_bounds__(NW * 64, EMAX * NW <= 64 ? 4 : 1) void decode_step_
                 int mine = 0, incl = 0;
                 if (tid < 256) {
                     mine = h[255 - tid];
-                    incl = mine;
-                    for (int off = 1; off < 64; off <<= 1) {
-                        const int t2 = __shfl_up(incl, off);
-                        if (lane >= off) incl += t2;
-                    }
+                    incl = wave_scan_add(mine);
                     if (lane == 63) h[256 + wave] = incl;
                 }
                 lds_barrier();
@@ -1687,11 +1679,7 @@ __global__ __launch_bounds__(NW * 64, EMAX * NW <= 64 ? 4 : 1) void decode_step_
                 int h = 0, incl = 0;
                 if (tid < 256) {  // bins in descending order: thread t owns bin 255 - t
                     h = hist[255 - tid];
-                    incl = h;
-                    for (int off = 1; off < 64; off <<= 1) {
-                        const int t2 = __shfl_up(incl, off);
-                        if (lane >= off) incl += t2;
-                    }
+                    incl = wave_scan_add(h);
                     if (lane == 63) hist[256 + wave] = incl;
                 }
                 lds_barrier();
@@ -1762,11 +1750,7 @@ __global__ __launch_bounds__(NW * 64, EMAX * NW <= 64 ? 4 : 1) void decode_step_
                 int h = 0, incl = 0;
                 if (tid < 256) {  // bins in descending order: thread t owns bin 255 - t
                     h = hist[255 - tid];
-                    incl = h;
-                    for (int off = 1; off < 64; off <<= 1) {
-                        const int t2 = __shfl_up(incl, off);
-                        if (lane >= off) incl += t2;
-                    }
+                    incl = wave_scan_add(h);
                     if (lane == 63) hist[256 + wave] = incl;
                 }
                 lds_barrier();

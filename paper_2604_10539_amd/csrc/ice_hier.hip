@@ -70,11 +70,7 @@ __device__ void select_topk_lds(const u64 *comp, int n, int k, int nb, u64 *sel,
             int mine = 0, incl = 0;
             if (tid < 256) {
                 mine = h[255 - tid];
-                incl = mine;
-                for (int off = 1; off < 64; off <<= 1) {
-                    const int t2 = __shfl_up(incl, off);
-                    if (lane >= off) incl += t2;
-                }
+                incl = wave_scan_add(mine);
                 if (lane == 63) h[256 + wave] = incl;
             }
             __syncthreads();
@@ -173,11 +169,7 @@ __device__ void select_topk_lds(const u64 *comp, int n, int k, int nb, u64 *sel,
             int h = 0, incl = 0;
             if (tid < 256) {  // bins in descending order: thread t owns bin 255 - t
                 h = hist[255 - tid];
-                incl = h;
-                for (int off = 1; off < 64; off <<= 1) {
-                    const int t2 = __shfl_up(incl, off);
-                    if (lane >= off) incl += t2;
-                }
+                incl = wave_scan_add(h);
                 if (lane == 63) hist[256 + wave] = incl;
             }
             __syncthreads();
