@@ -62,24 +62,26 @@ __device__ inline void merge_min2(u64 &a, u64 &b, u64 pa, u64 pb) {
     a = a < pa ? a : pa;
     b = hi < lo2 ? hi : lo2;
 }
+// (four 32-bit minima, one instruction a step, instead of two 64-bit values side by side: four waves of a SIMD work their guesses
+// out at once and the vector unit is what they wait for)
+__device__ inline uint32_t wave_min_u32(uint32_t x) {
+    x = min(x, dpp_u32<0xB1>(x));
+    x = min(x, dpp_u32<0x4E>(x));
+    x = min(x, dpp_u32<0x141>(x));
+    x = min(x, dpp_u32<0x140>(x));
+    const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    x = min(r[0], r[1]);
+    const auto t = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return __builtin_amdgcn_readfirstlane(min(t[0], t[1]));
+}
 __device__ inline void wave_min2_u64(u64 &a, u64 &b) {
-#define ICE_MIN2_STEP(CTRL)                                                                          \
-    do {                                                                                             \
-        const u64 pa = ((u64)dpp_u32<CTRL>((uint32_t)(a >> 32)) << 32) | dpp_u32<CTRL>((uint32_t)a);  \
-        const u64 pb = ((u64)dpp_u32<CTRL>((uint32_t)(b >> 32)) << 32) | dpp_u32<CTRL>((uint32_t)b);  \
-        merge_min2(a, b, pa, pb);                                                                    \
-    } while (0)
-    ICE_MIN2_STEP(0xB1);
-    ICE_MIN2_STEP(0x4E);
-    ICE_MIN2_STEP(0x141);
-    ICE_MIN2_STEP(0x140);
-#undef ICE_MIN2_STEP
-    u64 ra = readlane_u64(a, 0), rb = readlane_u64(b, 0);
-    merge_min2(ra, rb, readlane_u64(a, 16), readlane_u64(b, 16));
-    merge_min2(ra, rb, readlane_u64(a, 32), readlane_u64(b, 32));
-    merge_min2(ra, rb, readlane_u64(a, 48), readlane_u64(b, 48));
-    a = ra;
-    b = rb;
+    const uint32_t ah = (uint32_t)(a >> 32), al = (uint32_t)a;
+    const uint32_t h1 = wave_min_u32(ah), l1 = wave_min_u32(ah == h1 ? al : ~0u);
+    const bool won = ah == h1 && al == l1;  // (one lane, or none holds a value)
+    const uint32_t bh = won ? (uint32_t)(b >> 32) : ah, bl = won ? (uint32_t)b : al;
+    const uint32_t h2 = wave_min_u32(bh), l2 = wave_min_u32(bh == h2 ? bl : ~0u);
+    a = ((u64)h1 << 32) | l1;
+    b = ((u64)h2 << 32) | l2;
 }
 // sum over the wave in a fixed order: the four row sums, then ((r0 + r1) + r2) + r3
 __device__ inline float wave_sum_rows(float x) {
@@ -327,9 +329,10 @@ __host__ __device__ inline size_t insert_fixed_lds(int C, bool tk) {
     return (size_t)round_up(C, 16) * 4 * (tk ? 2 : 1) + 2 * kInsertTokens * 64 * 4 + 3 * kInsertTokens * 64 * 8;
 }
 
+template <bool AHEAD>
 __global__ __launch_bounds__(kInsertWaves * 64) void insert_batch_kernel(const bf16_t *__restrict__ k, const bf16_t *__restrict__ v,
                                                                           bf16_t *cent, float *cnorm, int m_total, int per,
-                                                                          int cur, int C, int Cpad, int stage_tiles, int flags,
+                                                                          int cur, int C, int Cpad, int stage_tiles, int tk_arg,
                                                                           Dev d_arg) {  // (scalars first: preloaded)
     extern __shared__ __align__(16) char insert_lds[];
     __shared__ u64 s_best[kInsertTokens];        // the guess: (ordered objective, cluster), ~0 when every objective is NaN
@@ -372,7 +375,8 @@ __global__ __launch_bounds__(kInsertWaves * 64) void insert_batch_kernel(const b
     };
     request();
     // The other arguments are fetched here, once, while tiles and keys are on their way.
-    const bool tk = (flags & 1) != 0, ahead = (flags & 2) != 0;
+    constexpr bool ahead = AHEAD;
+    const bool tk = tk_arg != 0;
     Dev d;
     bf16_t *caug_cur;
     pin_insert_fields(d, d_arg, cur, caug_cur);
@@ -854,9 +858,10 @@ void launch_insert(const Dev &d, const bf16_t *k, const bf16_t *v, int m, int cu
     const size_t tables = (ahead ? 2 : 1) * per * row;
     const int stage_tiles = fixed + tables + 2 * stage1 <= budget ? 2 : 1;
     const size_t lds = fixed + tables + stage_tiles * stage1;
-    allow_dynamic_lds((const void *)insert_batch_kernel, lds);
-    hipLaunchKernelGGL(insert_batch_kernel, dim3(d.U), dim3(kInsertWaves * 64), lds, st, k, v, d.cent_bf16[cur], d.cnorm[cur], m, per, cur, d.C,
-                       d.Cpad, stage_tiles, (d.tk ? 1 : 0) | (ahead ? 2 : 0), d);
+    auto *kernel = ahead ? insert_batch_kernel<true> : insert_batch_kernel<false>;
+    allow_dynamic_lds((const void *)kernel, lds);
+    hipLaunchKernelGGL(kernel, dim3(d.U), dim3(kInsertWaves * 64), lds, st, k, v, d.cent_bf16[cur], d.cnorm[cur], m, per, cur, d.C,
+                       d.Cpad, stage_tiles, d.tk, d);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1248,8 +1253,7 @@ __global__ __launch_bounds__(NW * 64, EMAX * NW <= 64 ? 4 : 1) void decode_step_
     __shared__ uint32_t sh_rowmax[4 * NW];
     __shared__ uint32_t sh_quadmax[16 * NW];
     __shared__ u64 sh_tau;
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int g = lane >> 4, ch = lane & 15;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, ch = lane & 15;
     const int xcd = blockIdx.x & 7, r = blockIdx.x >> 3;
     const int chunk = r % chunks, u_grid = xcd + 8 * (r / chunks);
     // (the grid is padded to a multiple of 8 units; a workgroup beyond the last unit leaves after the
