@@ -975,7 +975,8 @@ constexpr int kSplitMaxLdsBytes = 128 * 1024;
 // units, us of the attention alone with that many shares: 16 blocks 4: 6.7, 2: 7.0, 1: 7.9; 32 blocks 8: 7.2, 4: 7.4, 2: 8.1
 // (eight query heads 9.1, 8.6, 8.9); 64 blocks 16: 8.9, 8: 7.9, 4: 8.8; 128 blocks 32: 12.5, 16: 9.85, 8: 9.5; 256 blocks 32:
 // 13.4, 16: 11.0; pages of 64 tokens, 64 blocks 16: 9.8, 8: 9.25, 4: 9.15, 2: 10.1; 256 blocks 32: 14.3, 16: 11.8, 8: 11.85.
-// With a dense run beside the pages up to twelve shares of eight (96 blocks 12: 8.85, 8: 9.3).
+// With a dense run beside the pages up to twelve shares of eight (96 blocks 12: 8.85, 8: 9.3).  (Measured before the softmax's
+// heads were spread over the lanes, which took 0.4 to 0.5 us off every one of them.)
 static long long best_shares(long long blocks, bool rows) {
     return std::max({std::min<long long>((blocks + 3) / 4, 4), std::min<long long>((blocks + 7) / 8, rows ? 12 : 8), (blocks + 15) / 16});
 }
