@@ -100,6 +100,7 @@ size_t lay_out(const ice_config_t &cfg, int s, int C, char *base, Dev *out) {
     d.moved = (unsigned char *)take(U * CP);
     d.touched = (unsigned char *)take(U * CP);
     d.any_moved = (int *)take(U * 2 * 4);
+    d.large_keys = (int *)take(U * 4);
     d.page_base = (int *)take(U * C * 4);
     d.range_off = (uint32_t *)take(sort_ranges_max(d.U, d.max_tokens, d.Cpad) * CP * 4);
     d.attn_part = (float *)take((size_t)256 * d.G * (kD + 2) * 4);
@@ -248,7 +249,7 @@ ice_status_t ice_build_index(ice_index_t *ix, const void *K, const void *V, int3
     const bool fused = sort_is_fused(d, n);
     for (int t = 0; t < ix->cfg.kmeans_iters; ++t) {
         if (reassign_pays(d, n, t)) launch_reassign(d, Kb, n, cur, t, fused, s);
-        else launch_assign(d, Kb, n, cur, t, fused, s);
+        else launch_assign(d, Kb, n, cur, t, fused, t == 0 && reassign_pays(d, n, ix->cfg.kmeans_iters - 1), s);
         if (!fused) launch_sort(d, n, t, nullptr, nullptr, s);
         launch_means(d, Kb, n, cur, t, s);
         cur ^= 1;
@@ -575,7 +576,7 @@ ice_status_t ice_debug_assign(ice_index_t *ix, const void *K, int32_t n, const v
     hipStream_t s = static_cast<hipStream_t>(stream);
     const Dev &d = ix->dev;
     launch_load_centroids(d, static_cast<const bf16_t *>(cent), 0, s);
-    launch_assign(d, static_cast<const bf16_t *>(K), n, 0, 0, false, s);
+    launch_assign(d, static_cast<const bf16_t *>(K), n, 0, 0, false, false, s);
     if (assign_out) launch_sort(d, n, 0, best_out, assign_out, s);  // (unpacks the winners; without it only the kernel is timed)
     return device_status("ice_debug_assign");
 }
@@ -590,7 +591,7 @@ ice_status_t ice_debug_rerun_stage(ice_index_t *ix, const void *K, const void *V
     const bf16_t *Kb = static_cast<const bf16_t *>(K), *Vb = static_cast<const bf16_t *>(V);
     const int n = ix->build_n, prev = ix->cur ^ 1;  // the last round read buffer `prev` and wrote the live one
     switch (stage) {
-        case ICE_STAGE_ASSIGN: launch_assign(d, Kb, n, prev, 0, false, s); break;
+        case ICE_STAGE_ASSIGN: launch_assign(d, Kb, n, prev, 0, false, false, s); break;
         case ICE_STAGE_SORT: launch_sort(d, n, 0, nullptr, nullptr, s); break;
         case ICE_STAGE_MEANS: launch_means(d, Kb, n, prev, 0, s); break;
         case ICE_STAGE_PAGINATE: launch_paginate(d, Kb, Vb, n, false, s); break;

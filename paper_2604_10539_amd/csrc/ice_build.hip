@@ -31,16 +31,18 @@ __device__ inline uint64_t splitmix64(uint64_t x) {
 // more coordinate a(k) = sqrt(c^2 - ||k||^2), stored as bf16 beside the keys; c^2 is the largest
 // squared norm of the unit's prefill keys (a later key with a larger norm gets a(k) = 0).
 // Pass 1: squared norms (16 lanes per key, fixed summation order) and their maximum per workgroup;
-// pass 2: the maximum per unit and the extra coordinate.
+// pass 2: the maximum per unit and the extra coordinate.  (A maximum passes over NaN: whether a norm is one, or 2^118 and
+// more, goes beside it, for `large_keys`.)
 // Bound by one read of the keys.  The workgroups leave their maxima side by side and pass 2 reduces
 // them: one atomic maximum per wave on the unit's word puts thousands of updates on one or two cache
 // lines (16 units x 23457 keys, 96 MB: 76 us for the atomic form; the whole six-round build went from
 // 753 to 692 us without them).
 __global__ __launch_bounds__(256) void key_norms_kernel(Dev d, const bf16_t *__restrict__ K, int n, float *n2_out, float *max_out) {
     // 256 keys per workgroup (16 at a time, 16 lanes each)
-    __shared__ float wmax[4];
+    __shared__ float wmax[4], wlarge[4];
     const int u = blockIdx.y, row = threadIdx.x >> 4, ch = threadIdx.x & 15;
     float mx = 0.f;
+    u64 large = 0ull;
     uint4 w[16];  // the workgroup's 64 KB of key rows are requested at once (read once: streaming loads)
 #pragma unroll
     for (int it = 0; it < 16; ++it) {
@@ -55,25 +57,42 @@ __global__ __launch_bounds__(256) void key_norms_kernel(Dev d, const bf16_t *__r
             if (ch == 0) n2_out[(size_t)u * d.max_tokens + i] = n2;
             mx = fmaxf(mx, n2);
         }
+        large |= __ballot(!(n2 < 0x1p118f));  // (rows past the end are zeros)
     }
     mx = fmaxf(mx, __shfl_xor(mx, 16));
     mx = fmaxf(mx, __shfl_xor(mx, 32));
-    if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = mx;
+    if ((threadIdx.x & 63) == 0) {
+        wmax[threadIdx.x >> 6] = mx;
+        wlarge[threadIdx.x >> 6] = large != 0ull ? 1.f : 0.f;
+    }
     __syncthreads();
-    if (threadIdx.x == 0)
-        max_out[(size_t)u * d.max_tokens + blockIdx.x] = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
+    if (threadIdx.x == 0) {
+        const size_t at = (size_t)u * d.max_tokens + blockIdx.x;
+        max_out[at] = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
+        max_out[(size_t)d.U * d.max_tokens + at] = fmaxf(fmaxf(wlarge[0], wlarge[1]), fmaxf(wlarge[2], wlarge[3]));
+    }
 }
 __global__ __launch_bounds__(256) void key_aug_kernel(Dev d, int n, const float *n2_in, const float *max_in) {
-    __shared__ float wmax[4];
+    __shared__ float wmax[4], wlarge[4];
     const int u = blockIdx.y, i = blockIdx.x * 256 + threadIdx.x;
     const float n2 = i < n ? n2_in[(size_t)u * d.max_tokens + i] : 0.f;
-    float c2 = 0.f;
-    for (int b = threadIdx.x; b < (int)gridDim.x; b += 256) c2 = fmaxf(c2, max_in[(size_t)u * d.max_tokens + b]);
+    float c2 = 0.f, large = 0.f;
+    for (int b = threadIdx.x; b < (int)gridDim.x; b += 256) {
+        c2 = fmaxf(c2, max_in[(size_t)u * d.max_tokens + b]);
+        large = fmaxf(large, max_in[((size_t)d.U + u) * d.max_tokens + b]);
+    }
     for (int off = 1; off < 64; off <<= 1) c2 = fmaxf(c2, __shfl_xor(c2, off));
-    if ((threadIdx.x & 63) == 0) wmax[threadIdx.x >> 6] = c2;
+    const u64 any_large = __ballot(large > 0.f);
+    if ((threadIdx.x & 63) == 0) {
+        wmax[threadIdx.x >> 6] = c2;
+        wlarge[threadIdx.x >> 6] = any_large != 0ull ? 1.f : 0.f;
+    }
     __syncthreads();
     c2 = fmaxf(fmaxf(wmax[0], wmax[1]), fmaxf(wmax[2], wmax[3]));
-    if (blockIdx.x == 0 && threadIdx.x == 0) d.c2[u] = c2;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        d.c2[u] = c2;
+        d.large_keys[u] = wlarge[0] + wlarge[1] + wlarge[2] + wlarge[3] > 0.f;
+    }
     if (i < n) d.kaug[(size_t)u * d.max_tokens + i] = key_extra_coordinate(c2, n2);
 }
 
@@ -95,6 +114,7 @@ __global__ __launch_bounds__(64) void init_centroids_kernel(Dev d, const bf16_t 
     uint32_t *cb0 = (uint32_t *)(d.cent_bf16[cur] + ((size_t)u * d.Cpad + c) * kD);
     uint32_t *cb1 = (uint32_t *)(d.cent_bf16[cur ^ 1] + ((size_t)u * d.Cpad + c) * kD);
     if (lane == 0) d.moved[(size_t)u * d.Cpad + c] = d.touched[(size_t)u * d.Cpad + c] = 0;
+    if (c == 0 && lane == 0 && !d.tk) d.large_keys[u] = 0;  // (transformed keys: set already)
     if (c >= d.C) {
         cb0[lane] = 0u;
         cb1[lane] = 0u;
@@ -550,10 +570,14 @@ __host__ __device__ constexpr int assign_lds_bytes(bool aug) {
     return 2 * 256 * 256 + (aug ? 2 * 256 * 32 : 0) + 2 * 256 * 8;
 }
 
+// While every coordinate is below 2^59 (here its bf16 bits; transformed keys: every squared norm below 2^118) so are the
+// means', and all scores of a build are finite.
+constexpr uint32_t kLargeKey = (127 + 59) << 7;
+
 template <int CT, int CW, bool AUG, bool FULL>
 __global__ __launch_bounds__(512) void assign_kernel(const bf16_t *__restrict__ K, const bf16_t *__restrict__ cent,
                                                       const float *__restrict__ cnorm, int n, int keys_per_wg, int zsplit,
-                                                      int Cpad, int cur, const int *__restrict__ go, int sort_round, Dev d) {  // (scalars first: preloaded at wave start)
+                                                      int Cpad, int cur, const int *__restrict__ go, int sort_round, int look, Dev d) {  // (scalars first: preloaded at wave start)
     constexpr int KW = 8 / CW;
     constexpr int KS = AUG ? 9 : 8;  // 16-wide steps of the contraction
     extern __shared__ __align__(16) char smem[];
@@ -699,6 +723,20 @@ __global__ __launch_bounds__(512) void assign_kernel(const bf16_t *__restrict__ 
             request_tile(t + 1, buf ^ 1);
             load_aug(t + 1);
         }
+        if constexpr (!AUG) {
+            if (look) {  // largest magnitude of the tile's keys (this thread's share), as 16-bit patterns: NaN is above all
+                typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+                u16x2 top = {0, 0};
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const uint4 w = *(const uint4 *)(keys + buf * (kAssignTile * 256) + (tid + 512 * i) * 16);
+                    const uint32_t x[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) top = __builtin_elementwise_max(top, __builtin_bit_cast(u16x2, x[j] & 0x7FFF7FFFu));
+                }
+                if (max(top.x, top.y) >= kLargeKey) d.large_keys[u] = 1;
+            }
+        }
         // Software pipeline over "slots" j = (sub-tile i, centroid tile ct): while the matrix cores
         // run the 8-MFMA chain of slot j+1 into one accumulator set, the vector unit
         // reduces slot j's 16 scores per lane from the other set (argmax16).  The key operand of a
@@ -810,7 +848,7 @@ static int assign_run(int U, int n, int slices) {
 // whether a centroid of the unit moved in the round before round t: element 2 u of the result (all units go in the first round)
 static const int *round_goes(const Dev &d, int t) { return t > 0 ? d.any_moved + ((t - 1) & 1) : nullptr; }
 
-void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fused, hipStream_t st) {
+void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fused, bool look, hipStream_t st) {
     const int tiles = d.Cpad / 32;
     int CT = tiles == 1 ? 1 : 2, CW = 1;
     while (CW < 8 && CW * CT < tiles) CW *= 2;
@@ -832,7 +870,7 @@ void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fu
     do {                                                                                            \
         allow_dynamic_lds((const void *)assign_kernel<ct, cw, aug, full>, lds);                     \
         hipLaunchKernelGGL((assign_kernel<ct, cw, aug, full>), grid, dim3(512), lds, st, K, d.cent_bf16[cur], d.cnorm[cur], n, \
-                           keys_per_wg, zsplit, d.Cpad, cur, round_goes(d, t), fused ? t : -1, d);  \
+                           keys_per_wg, zsplit, d.Cpad, cur, round_goes(d, t), fused ? t : -1, look ? 1 : 0, d);  \
     } while (0)
 #define ICE_ASSIGN_A(ct, cw, aug)                                                                   \
     do {                                                                                            \
@@ -865,9 +903,10 @@ void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fu
 //          last round's winner (score, ~id), which no centroid that stayed can beat:
 //            m >  old: m;   m <= old and old's centroid stayed: old;   m == old (its score came out the same): old;
 //            m <  old and old's centroid moved: a centroid that stayed may lie between, the key is listed;
-//   again  the listed keys, gathered, against all centroids.  (A key without a comparable score goes here too: what the
-//          contraction leaves of one depends on all scores of a tile.)
-// A unit of which more than three quarters of the centroids moved takes all keys against all centroids at once.
+//   again  the listed keys, gathered, against all centroids.
+// A unit of which more than three quarters of the centroids moved takes all keys against all centroids at once.  So does one
+// with keys that are not finite, or so large that a score may not be (`large_keys`): what the contraction leaves of a key
+// among whose scores are NaN depends on where in a tile they are (argmax16: nine of them side by side hide their lane's others).
 // One workgroup takes a run of 256-key tiles through all of this; more than 512 centroids are slices that it takes one
 // after the other, its keys' winners so far in `tmp`.  A slice of few tiles splits the keys among the waves instead of
 // the centroids (slice<CW>: CW waves share the centroids of a key).  Bound as assign_kernel is while many centroids
@@ -933,7 +972,7 @@ __global__ __launch_bounds__(512) void reassign_kernel(const bf16_t *__restrict_
     if (sort_round >= 0 && blockIdx.x == 0 && tid == 0) d.any_moved[2 * u + (sort_round & 1)] = 0;  // (for this round's means)
     // ---- which centroids moved
     {
-        const int lane = tid & 63, goes = go[2 * u];
+        const int lane = tid & 63, goes = go[2 * u], large = d.large_keys[u];
         uint32_t m = 0;
         if (tid * 16 < Cpad) {
             const uint4 w = ((const uint4 *)(d.moved + (size_t)u * Cpad))[tid];
@@ -959,7 +998,7 @@ __global__ __launch_bounds__(512) void reassign_kernel(const bf16_t *__restrict_
         // (in tiles of 256 keys x 512 centroids, `steps` of them the whole contraction: the listed keys are about 0.45 of the
         // moved share, their pass a prologue worth about 1.15 more)
         const int steps = (nk + kAssignTile - 1) / kAssignTile * ((Cpad + 511) / 512);
-        if (145 * ncent >= C * (100 - 115 / steps)) {
+        if (large != 0 || 145 * ncent >= C * (100 - 115 / steps)) {
             job = kAllCentroids;
             ncent = Cpad;
         }

@@ -66,6 +66,7 @@ struct Dev {
     unsigned char *moved;       // [U][Cpad] the last round's means changed the centroid's bits
     unsigned char *touched;     // [U][Cpad] the cluster lost or gained a token since the last means (zero between rounds)
     int *any_moved;             // [U][2] some centroid of the unit moved: in even rounds, in odd ones
+    int *large_keys;            // [U] some key's magnitude is 2^59 or more, infinite or NaN: a score may not be a number
     int *page_base;             // [U][C] exclusive scan of pages per cluster
     float *attn_part;           // [256][G][130] partial results of the split attention (shares x units <= 256)
     int *attn_arrive;           // [U] arrival counters of its shares (zero between launches)
@@ -105,7 +106,8 @@ void launch_key_aug(const Dev &d, const bf16_t *K, int n, hipStream_t st);
 // one before and leaves what all of it would: its assignment either by launch_assign (units of which a centroid moved) or, where
 // reassign_pays, by launch_reassign (moved centroids only); tokens are sorted and means formed where a token went elsewhere.
 // fused: with the sort of its runs (sort_is_fused), else launch_sort follows
-void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fused, hipStream_t st);
+// look: also looks for keys that reassign_kernel has to know of (large_keys; transformed keys: launch_key_aug does)
+void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fused, bool look, hipStream_t st);
 bool sort_is_fused(const Dev &d, int n);
 bool reassign_pays(const Dev &d, int n, int t);
 void launch_reassign(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fused, hipStream_t st);

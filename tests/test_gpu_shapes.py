@@ -501,6 +501,44 @@ def test_later_rounds_do_again_what_changed_and_leave_what_all_of_it_would(U, n,
     assert settled or odd or n > 100 * C  # (rounds in which nothing moves were among them, unless clusters are large)
 
 
+def test_later_rounds_where_scores_stop_comparing():
+    """A cluster that takes in an infinite key in the third round has a mean with which most scores do not compare in the
+    fourth.  With eight NaN rows around it since the start, the full contraction finds nine NaN side by side, which hide the
+    other rows held beside them; a round that looks only at the centroids that moved has to come to the same."""
+    import torch
+    from paper_2604_10539_amd import IceIndex
+    from paper_2604_10539_amd.binding import ice_debug_rerun_stage
+    C, first, j = 2048, 64, 127          # rows 64..95 are a tile
+    a, b = first + 16, first + 17        # the ninth row of the tile's first half, and the row that loses a key to it
+    rng = np.random.default_rng(3)
+    K = rng.standard_normal((C, D))      # clusters of one key, far apart
+    K *= 100.0 / np.linalg.norm(K, axis=1, keepdims=True)
+    K[a] = K[b] = 0.0
+    K[b, 0] = 10.0
+    K[:, j] = np.where(np.arange(C) > b, 1.0, -2.0 ** -10)
+    more = np.zeros((12, D))
+    more[:10, 0], more[:10, j] = 30.0, -2.0 ** -10  # row b follows them after the first round
+    more[10, 0], more[10, j] = 6.0, 1.0  # goes to b first, then to a, whose coordinate j is positive from then on
+    K = narrow(np.concatenate([K, more]).astype(np.float32))
+    K[first + np.r_[0:4, 8:12]] = 0x7FC0
+    K[C + 11, j] = 0x7F80                # nearest, at +inf, to the first row with a positive coordinate j: b + 1, then b, then a
+    Kd, init = up(K[None, None]), up(np.arange(C, dtype=np.int32)[None, None])
+    for T in (3, 4, 6):
+        ix = IceIndex(1, 1, 4, len(K), 16, C, kmeans_iters=T, init_idx=init)
+        ix.build_index(Kd, Kd)
+        ex = ix.export()
+        had = {f: ex[f].clone() for f in ("assign", "cluster_cnt", "page_pos")}
+        for stage in range(4):
+            ice_debug_rerun_stage(ix.handle, Kd, Kd, stage)
+        torch.cuda.synchronize()
+        for f in had:
+            assert torch.equal(had[f], ex[f]), (T, f)
+        if T == 3:
+            assert had["assign"][0, C + 11] == a
+        lost = int((had["assign"][0, :C] != torch.arange(C, device="cuda")).sum())
+        assert lost < 16 if T == 3 else lost > 30  # (rows 64..127 of the same lanes)
+
+
 @pytest.mark.parametrize("U,G", [(3, 4), (2, 8), (256, 1), (256, 8)])
 def test_pages_of_one_cluster_side_by_side_at_every_budget(U, G):
     """Pages that score alike sit beside each other, so whole clusters fall into one group of the selection's threshold; the
