@@ -313,6 +313,13 @@ ice_status_t ice_debug_assign(ice_index_t *idx, const void *K, int32_t n, const 
 enum { ICE_STAGE_ASSIGN = 0, ICE_STAGE_SORT = 1, ICE_STAGE_MEANS = 2, ICE_STAGE_PAGINATE = 3 };
 ice_status_t ice_debug_rerun_stage(ice_index_t *idx, const void *K, const void *V, int32_t stage, void *stream);
 
+/* Test hook: which way a build of n_tokens keys and n_clusters clusters per unit goes, worked out on the host alone
+ * (nothing is enqueued, no index is needed).  plan[0] = 1 where the assignment sorts its own runs; plan[1], plan[2] =
+ * tokens per range of the sort and ranges per unit; plan[3] = first round that scores only what changed (0: none does);
+ * plan[4] = 256-key tiles per workgroup of such a round; plan[5] = slices of 512 centroids.  cfg, n_tokens and n_clusters
+ * are checked as ice_build_index checks them. */
+ice_status_t ice_debug_build_plan(const ice_config_t *cfg, int32_t n_tokens, int32_t n_clusters, int32_t plan[6]);
+
 /* Test hook for the failure path of ice_select / ice_select_attend when a unit is served by several
  * workgroups (fewer than 256 units): those workgroups hand their page scores to the last one of
  * them through device memory, and that one waits for a missing score only a bounded number of

@@ -97,7 +97,7 @@ size_t lay_out(const ice_config_t &cfg, int s, int C, char *base, Dev *out) {
     d.assign = (int *)take(U * MT * 4);
     d.packed = (unsigned long long *)take(U * MT * 8);
     d.order = (int *)take(U * MT * 4);
-    d.moved = (unsigned char *)take(U * CP);
+    d.moved = (uint32_t *)take(U * CP * 4);
     d.touched = (unsigned char *)take(U * CP);
     d.any_moved = (int *)take(U * 2 * 4);
     d.large_keys = (int *)take(U * 4);
@@ -247,9 +247,10 @@ ice_status_t ice_build_index(ice_index_t *ix, const void *K, const void *V, int3
     if (d.tk) launch_key_aug(d, Kb, n, s);
     launch_init_centroids(d, Kb, n, ix->cfg.init_idx, ix->cfg.seed, cur, s);
     const bool fused = sort_is_fused(d, n);
+    const bool later = ix->cfg.kmeans_iters > 2 && reassign_pays(d, n);
     for (int t = 0; t < ix->cfg.kmeans_iters; ++t) {
-        if (reassign_pays(d, n, t)) launch_reassign(d, Kb, n, cur, t, fused, s);
-        else launch_assign(d, Kb, n, cur, t, fused, t == 0 && reassign_pays(d, n, ix->cfg.kmeans_iters - 1), s);
+        if (later && t >= 2 && t % kRoundNumbers != 0) launch_reassign(d, Kb, n, cur, t, fused, s);
+        else launch_assign(d, Kb, n, cur, t, fused, later && t == 0, s);
         if (!fused) launch_sort(d, n, t, nullptr, nullptr, s);
         launch_means(d, Kb, n, cur, t, s);
         cur ^= 1;
@@ -598,6 +599,21 @@ ice_status_t ice_debug_rerun_stage(ice_index_t *ix, const void *K, const void *V
         default: return fail(ICE_ERR_INVALID_ARG, "stage %d: one of ICE_STAGE_ASSIGN .. ICE_STAGE_PAGINATE", stage);
     }
     return device_status("ice_debug_rerun_stage");
+}
+
+ice_status_t ice_debug_build_plan(const ice_config_t *cfg, int32_t n, int32_t n_clusters, int32_t plan[6]) {
+    if (ice_status_t st = check_cfg(cfg)) return st;
+    if (!plan) return fail(ICE_ERR_INVALID_ARG, "plan is null");
+    if (ice_status_t st = check_shape(16, n_clusters)) return st;
+    if (n < 1) return fail(ICE_ERR_INVALID_ARG, "n_tokens must be >= 1");
+    if (n_clusters > n) return fail(ICE_ERR_SHAPE, "n_clusters %d exceeds n_tokens %d", n_clusters, n);
+    if (n > cfg->max_tokens) return fail(ICE_ERR_SHAPE, "n_tokens %d exceeds max_tokens %d", n, cfg->max_tokens);
+    Dev d{};
+    d.U = cfg->batch * cfg->n_kv_heads;
+    d.C = n_clusters;
+    d.Cpad = round_up(n_clusters, 32);
+    build_plan(d, n, plan);
+    return ICE_OK;
 }
 
 ice_status_t ice_debug_select_fault(ice_index_t *ix, const void *q, int32_t budget, int32_t *ids, int32_t *n_sel, float *out,

@@ -321,12 +321,6 @@ void launch_import(const Dev &d, const void *const *src, void *const *dst, const
     hipLaunchKernelGGL(import_kernel, dim3(a.copy_blocks + a.cluster_blocks + (unsigned)((state + 255) / 256)), dim3(256), 0, st, d, a);
 }
 
-// zero winners for a contraction whose slices meet by atomic maxima (go: a unit whose centroids stayed keeps its own)
-__global__ __launch_bounds__(256) void clear_winners_kernel(Dev d, int n, const int *go) {
-    const int u = blockIdx.y, i = blockIdx.x * 256 + threadIdx.x;
-    if (i < n && (!go || go[2 * u] != 0)) d.packed[(size_t)u * d.max_tokens + i] = 0ull;
-}
-
 // ------------------------------------------------------------------------------------------------
 // Sorting the tokens by cluster (ascending position inside a cluster), range by range: a unit's tokens
 // are cut into R ranges of L, one workgroup each, and every range is sorted by itself (`order`, stable
@@ -378,18 +372,25 @@ size_t sort_ranges_max(int U, int max_tokens, int Cpad) {
     return std::max<size_t>(std::max(256, U), (size_t)U * (((size_t)max_tokens + L - 1) / L));
 }
 
+// The thread's number out of its wave's, worked out where it is asked for.
+__device__ inline int thread_of(int wave) {
+    int lane;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+    return wave * 64 + lane;
+}
+
 // NG: groups of 64 tokens per wave at most.  MASK: the lanes of a group with the same cluster meet in a 64-bit lane mask per
 // cluster in LDS (OR, read back, clear) instead of by ballots: cheaper per group, but the masks have to be cleared and
 // take 8 more bytes per counter, so it is for long ranges (256 units x 32768 tokens: 78 us with ballots, 69 so).
 // The sort of tokens [rb, re) of unit u, its range r of R, by a workgroup of NWV waves; W segments of `seg` tokens.
 // winner(i): cluster of token i, best_of(i): what goes to best_out.  Every thread comes here.
 template <int NWV, int NG, bool MASK, typename Winner, typename BestOf>
-__device__ inline void sort_range(const Dev &d, int u, int n, int r, int R, int rb, int re, int seg, int W, int nbits, int round, int goes,
+__device__ inline void sort_range(const Dev &d, int tid, int u, int n, int r, int R, int rb, int re, int seg, int W, int nbits, int round, int goes,
                                   int *pos_all, float *best_out, int *assign_out, Winner winner, BestOf best_of) {
     constexpr int NT = NWV * 64;
     __shared__ int wsum[NWV];
     __shared__ int carry;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int lane = tid & 63, wave = tid >> 6;
     const int Cpad = d.Cpad;
     const int beg = min(re, rb + wave * seg), end = wave < W ? min(re, beg + seg) : beg;  // this wave's tokens
     uint32_t v[NG];
@@ -502,6 +503,23 @@ __device__ inline void sort_range(const Dev &d, int u, int n, int r, int R, int 
 }
 
 // ------------------------------------------------------------------------------------------------
+// A key's winner in memory: round's number (its low 19 bits) << 45 | ordered score << 13 | ~cluster (its low 13 bits).  Slices
+// of the centroids meet by atomic maxima of such words, and a later round's are above those of the rounds before: nothing is
+// cleared between rounds.  (A launch that did took 6 us of 440 at 8 units x 131072 x 2048, 5 of 33 at 2 x 32768 x 2048.)  In
+// LDS, inside one round: ordered score << 32 | ~cluster.
+constexpr int kMaxClusters = 8192;
+__device__ inline u64 winner_word(u64 best, uint32_t round) {
+    return (u64)round << 45 | (best >> 32) << 13 | (best & (kMaxClusters - 1));
+}
+__device__ inline u64 winner_of_word(u64 w) { return (w >> 13) << 32 | (0xFFFFFFFFu & ~(uint32_t)(kMaxClusters - 1)) | ((uint32_t)w & (kMaxClusters - 1)); }
+__device__ inline uint32_t cluster_of_word(uint32_t low) { return ~low & (kMaxClusters - 1); }
+// zero winners, where no round's are there
+__global__ __launch_bounds__(256) void clear_winners_kernel(Dev d, int n) {
+    const int u = blockIdx.y, i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n) d.packed[(size_t)u * d.max_tokens + i] = 0ull;
+}
+
+// ------------------------------------------------------------------------------------------------
 // Nearest centroid on the matrix cores.
 //   score(i, c) = k_i . mu~_c - ||mu~_c||^2 / 2      (argmax score == argmin ||k_i - mu~_c||^2)
 // A dense (keys x 128) by (128 x centroids) contraction: v_mfma_f32_32x32x16_bf16 with the
@@ -574,21 +592,22 @@ __host__ __device__ constexpr int assign_lds_bytes(bool aug) {
 // means', and all scores of a build are finite.
 constexpr uint32_t kLargeKey = (127 + 59) << 7;
 
+// One workgroup's run of keys [k0, kend) of unit u against slice `slice` of the centroids.  go: see round_goes (nullptr: the
+// caller knows that the unit goes); returns whether it goes.  won != nullptr: [kend - k0] (LDS) the run's winners as well.
+// look: also looks for large keys.
 template <int CT, int CW, bool AUG, bool FULL>
-__global__ __launch_bounds__(512) void assign_kernel(const bf16_t *__restrict__ K, const bf16_t *__restrict__ cent,
-                                                      const float *__restrict__ cnorm, int n, int keys_per_wg, int zsplit,
-                                                      int Cpad, int cur, const int *__restrict__ go, int sort_round, int look, Dev d) {  // (scalars first: preloaded at wave start)
+__device__ __forceinline__ bool assign_slice(const Dev &d, const bf16_t *__restrict__ K, const bf16_t *__restrict__ cent,
+                                             const float *__restrict__ cnorm, int n, int u, int slice, int k0, int kend, int zsplit,
+                                             int Cpad, int cur, const int *__restrict__ go, uint32_t round, uint16_t *won, bool look, char *smem) {
     constexpr int KW = 8 / CW;
     constexpr int KS = AUG ? 9 : 8;  // 16-wide steps of the contraction
-    extern __shared__ __align__(16) char smem[];
     char *keys = smem;                                                // [2][256][256 B], chunks swizzled
     uint4 *kext = (uint4 *)(smem + 2 * kAssignTile * 256);            // (AUG) [2][256][2] companion chunks
     u64 *best = (u64 *)(smem + 2 * kAssignTile * 256 + (AUG ? 2 * kAssignTile * 32 : 0));  // [2][256]
-    uint16_t *won = (uint16_t *)(best + 2 * kAssignTile);             // [keys_per_wg] (sort_round >= 0) the run's winners
     // byte offset of chunk c of row r inside a buffer
     auto slot = [](int r, int c) { return r * 256 + ((c ^ (r & 15)) << 4); };
 
-    const int u = blockIdx.z, tid = threadIdx.x;
+    const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63, col = lane & 31, half = lane >> 5;
     // Wave (cw, kw) holds CT centroid tiles of the slice: neighbours when every slice is full (FULL), else cw
     // and cw + CW.  Waves w and w + 4 share a SIMD: tiles missing at the slice's end are spread over the
@@ -597,21 +616,18 @@ __global__ __launch_bounds__(512) void assign_kernel(const bf16_t *__restrict__ 
     // (ctv), so a slice costs what its fullest SIMD holds: 12 tiles run in 3/4 of the time of 16.
     constexpr int CS = FULL ? 1 : CW;  // distance between a wave's tiles
     const int kw = wave / CW, cw = FULL || CW == 8 ? wave % CW : (wave + (wave >> 2) * (CW / 2)) % CW;
-    const int wt0 = FULL ? cw * CT : cw, tile0 = blockIdx.y * CW * CT + wt0;
+    const int wt0 = FULL ? cw * CT : cw, tile0 = slice * CW * CT + wt0;
     const int ctv = __builtin_amdgcn_readfirstlane(tile0 * 32 >= Cpad ? 0 : CT == 2 && (tile0 + CS) * 32 < Cpad ? 2 : 1);
-    const int k0 = blockIdx.x * keys_per_wg;
-    const int kend = min(n, k0 + keys_per_wg);
     const int ntiles = (kend - k0 + kAssignTile - 1) / kAssignTile;
     const bf16_t *Ku = K + (size_t)u * n * kD;
 
-    if (sort_round >= 0 && blockIdx.x == 0 && tid == 0) d.any_moved[2 * u + (sort_round & 1)] = 0;  // (for this round's means)
     ICE_BSTAMP(0);
     // Prologue.  The workgroup's block of centroid rows goes to LDS with fully coalesced 16-byte
     // loads (the staging area is the key buffers, not yet in use) and every wave then picks its
     // MFMA fragments from there: reading the fragments straight from global memory touches 32
     // separate rows per load instruction.  The first key tile is in flight meanwhile.
     constexpr int R = CW * CT * 32;  // centroid rows of this workgroup
-    const int crow0 = blockIdx.y * R;
+    const int crow0 = slice * R;
     uint4 cst[R / 32];
     {
         const bf16_t *csrc = cent + ((size_t)u * Cpad + crow0) * kD;
@@ -673,7 +689,7 @@ __global__ __launch_bounds__(512) void assign_kernel(const bf16_t *__restrict__ 
         first[i] = ((const u32x4 *)(Ku + (size_t)key * kD))[ch];
     }
     load_aug(0);
-    if (goes == 0) return;  // (a later round of a unit whose centroids stayed: every winner stands)
+    if (goes == 0) return false;  // (a later round of a unit whose centroids stayed: every winner stands)
 #pragma unroll
     for (int i = 0; i < R / 32; ++i) {
         const int id = tid + 512 * i, row = id >> 4, ch = id & 15;
@@ -810,19 +826,65 @@ __global__ __launch_bounds__(512) void assign_kernel(const bf16_t *__restrict__ 
             const int key = k0 + t * kAssignTile + tid;
             if (key < kend) {
                 u64 *dst = d.packed + (size_t)u * d.max_tokens + key;
-                if (zsplit == 1) *dst = bestt[tid];
-                else atomicMax(dst, bestt[tid]);
-                if (sort_round >= 0) won[t * kAssignTile + tid] = (uint16_t)(0xFFFFFFFFu - (uint32_t)bestt[tid]);
+                const u64 b = bestt[tid], w = winner_word(b, round);
+                if (zsplit == 1) *dst = w;
+                else atomicMax(dst, w);
+                if (won) won[t * kAssignTile + tid] = (uint16_t)(0xFFFFFFFFu - (uint32_t)b);
             }
             bestt[tid] = 0ull;
         }
     }
-    if (sort_round >= 0) {  // the run is a range of the sort as well
+    return true;
+}
+
+template <int CT, int CW, bool AUG, bool FULL>
+__global__ __launch_bounds__(512) void assign_kernel(const bf16_t *__restrict__ K, const bf16_t *__restrict__ cent,
+                                                      const float *__restrict__ cnorm, int n, int keys_per_wg, int zsplit,
+                                                      int Cpad, int cur, const int *__restrict__ go, int round, int fused, int look, Dev d) {  // (scalars first: preloaded at wave start)
+    extern __shared__ __align__(16) char smem[];
+    const int u = blockIdx.z, k0 = blockIdx.x * keys_per_wg, kend = min(n, k0 + keys_per_wg);
+    uint16_t *won = (uint16_t *)(smem + assign_lds_bytes(AUG));  // [keys_per_wg] (fused)
+    if (fused && blockIdx.x == 0 && threadIdx.x == 0) d.any_moved[2 * u + (round & 1)] = 0;  // (for this round's means)
+    if (!assign_slice<CT, CW, AUG, FULL>(d, K, cent, cnorm, n, u, blockIdx.y, k0, kend, zsplit, Cpad, cur, go, round % kRoundNumbers, fused ? won : nullptr,
+                                           look != 0 && blockIdx.y == 0, smem)) return;
+    if (fused) {  // the run is a range of the sort as well
         __syncthreads();    // (the winners are there; the key tiles are not needed any more)
-        sort_range<8, kFusedRun / 2, false>(d, u, n, blockIdx.x, gridDim.x, k0, kend, keys_per_wg / 8, 8, 32 - __builtin_clz((unsigned)Cpad - 1u),
-                                            sort_round, 1, (int *)smem, nullptr, nullptr, [=](int i) { return (uint32_t)won[i - k0]; },
+        sort_range<8, kFusedRun / 2, false>(d, threadIdx.x, u, n, blockIdx.x, gridDim.x, k0, kend, keys_per_wg / 8, 8, 32 - __builtin_clz((unsigned)Cpad - 1u),
+                                            round, 1, (int *)smem, nullptr, nullptr, [=](int i) { return (uint32_t)won[i - k0]; },
                                             [](int) { return 0.f; });
     }
+}
+
+// How a later round is cut (reassign_kernel), in one way and in the other.
+struct RoundPlan {
+    int run, wgs;                // moved centroids: 256-key tiles per workgroup, workgroups per unit
+    int all_run, all_wgs, slices;  // all centroids: the same, workgroups per unit and slice
+    int fixed, per_key;          // for takes_all: the prologues of the slices of all centroids, a run's keys against them
+    long long limit;             // ... and what all centroids cost (2 n times, by rounds of 256 workgroups)
+    long long all_turns;         // rounds of 256 workgroups of all centroids
+    int tiles;                   // 32-centroid tiles of a slice, as they are dealt to four SIMDs
+};
+
+// Whether the full contraction of a unit costs no more than `moved` of its centroids, which hold `keys` of its n keys,
+// and then the keys of which the winner is not known.  In contractions of 256 keys x 32 centroids: the centroids of a
+// slice are dealt to four SIMDs, a slice's prologue costs about 16 of them, and of the keys whose centroid moved about half
+// are listed (of 32768 keys and 512 clusters 0.34 to 0.5 of them in the benchmark's mixture, 0.4 to 0.55 without structure).
+__device__ inline bool takes_all(const RoundPlan &p, int moved, int keys, int n) {
+    const int S = (moved + 511) / 512, own = 16 * (S - 1) + 4 * ((moved - 512 * (S - 1) + 127) / 128);
+    // (whole numbers, 2 n times: every workgroup of the round's launches comes to the same)
+    return (long long)(p.run * own + 16 * S + p.fixed) * 2 * n + (long long)keys * p.per_key >= p.limit;
+}
+
+// What `moved` says of a unit: of the 16 centroids from 16 x on a mask and the keys they hold.
+__device__ inline uint32_t moved_of_16(const uint32_t *moved, int x, int &keys) {
+    uint32_t m = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint4 w = ((const uint4 *)moved)[4 * x + i];
+        m |= ((w.x & 1u) | (w.y & 1u) << 1 | (w.z & 1u) << 2 | (w.w & 1u) << 3) << (4 * i);
+        keys += (int)((w.x >> 1) + (w.y >> 1) + (w.z >> 1) + (w.w >> 1));
+    }
+    return m;
 }
 
 // Slices of at most 512 centroids (blockIdx.y) that meet through an atomic maximum in `packed`.
@@ -834,12 +896,13 @@ static int assign_run(int U, int n, int slices) {
     const int ktiles = (n + kAssignTile - 1) / kAssignTile;
     int run = 1;
     long long best_cost = -1;
-    for (int g = 1; g <= ktiles && g <= 4096; ++g) {  // g workgroups per unit and slice
+    for (int g = 1; g <= ktiles && g <= 4096;) {  // g workgroups per unit and slice: the fewest for each length of run
         const int r = (ktiles + g - 1) / g;
         const long long wgs = (long long)((ktiles + r - 1) / r) * slices * U;
         const long long cost = (wgs + 255) / 256 * (r + 1);
         if (best_cost < 0 || cost < best_cost) { best_cost = cost; run = r; }
-        if (wgs > 256 * 64) break;  // (more, shorter runs only repeat the prologue)
+        if (wgs > 256 * 64 || r == 1) break;  // (more, shorter runs only repeat the prologue)
+        g = (ktiles + r - 2) / (r - 1);
     }
     return run;
 }
@@ -862,15 +925,13 @@ void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fu
     const int keys_per_wg = assign_run(d.U, n, zsplit) * kAssignTile;
     dim3 grid((n + keys_per_wg - 1) / keys_per_wg, zsplit, d.U);
     const size_t lds = assign_lds_bytes(d.tk != 0) + (fused ? (size_t)keys_per_wg * 2 : 0);
-    if (zsplit > 1) {
-        hipLaunchKernelGGL(clear_winners_kernel, dim3((n + 255) / 256, d.U), dim3(256), 0, st, d, n, round_goes(d, t));
-    }
+    if (zsplit > 1 && t % kRoundNumbers == 0) hipLaunchKernelGGL(clear_winners_kernel, dim3((n + 255) / 256, d.U), dim3(256), 0, st, d, n);
     const bool full = tiles % (CT * CW) == 0;
 #define ICE_ASSIGN_F(ct, cw, aug, full)                                                             \
     do {                                                                                            \
         allow_dynamic_lds((const void *)assign_kernel<ct, cw, aug, full>, lds);                     \
         hipLaunchKernelGGL((assign_kernel<ct, cw, aug, full>), grid, dim3(512), lds, st, K, d.cent_bf16[cur], d.cnorm[cur], n, \
-                           keys_per_wg, zsplit, d.Cpad, cur, round_goes(d, t), fused ? t : -1, look ? 1 : 0, d);  \
+                           keys_per_wg, zsplit, d.Cpad, cur, round_goes(d, t), t, fused ? 1 : 0, look ? 1 : 0, d);  \
     } while (0)
 #define ICE_ASSIGN_A(ct, cw, aug)                                                                   \
     do {                                                                                            \
@@ -893,9 +954,10 @@ void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fu
 }
 
 // ------------------------------------------------------------------------------------------------
-// The assignment of a later round.  Between two rounds most centroids stay where they are, bit for bit (clusters of
+// The assignment of a later round.  Between two rounds many centroids stay where they are, bit for bit (clusters of
 // about 64 keys in 128 dimensions settle fast: of 512 clusters over 32768 keys of the benchmark's mixture 79 % moved
-// after the first round, 50 % after the second, 29, 18, 5, 2 and below 1 % after that), and a score is the
+// after the second round, 50 % after the third, then 29, 18, 5, 2 and below 1 %; of as many clusters of keys without any
+// structure 75, 71, 70, 68, 68, 67, 64 %), and a score is the
 // same bits whichever slot of the matrix instruction it comes out of.  So the winner among the centroids that did not
 // move is known from the last round for every key whose own centroid did not, and what the full contraction
 // would leave in `packed` follows from less of it:
@@ -904,48 +966,99 @@ void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fu
 //            m >  old: m;   m <= old and old's centroid stayed: old;   m == old (its score came out the same): old;
 //            m <  old and old's centroid moved: a centroid that stayed may lie between, the key is listed;
 //   again  the listed keys, gathered, against all centroids.
-// A unit of which more than three quarters of the centroids moved takes all keys against all centroids at once.  So does one
-// with keys that are not finite, or so large that a score may not be (`large_keys`): what the contraction leaves of a key
-// among whose scores are NaN depends on where in a tile they are (argmax16: nine of them side by side hide their lane's others).
-// One workgroup takes a run of 256-key tiles through all of this; more than 512 centroids are slices that it takes one
+// A unit for which that is no less work (takes_all) goes through the full contraction, by the same code as a round of
+// assign_kernel.  So does one with keys that are not finite, or so large that a score may not be (`large_keys`): what the
+// contraction leaves of a key among whose scores are NaN depends on where in a tile they are (argmax16: nine of them side by
+// side hide their lane's others).
+// One workgroup takes a run of 256-key tiles through moved and again; more than 512 centroids are slices that it takes one
 // after the other, its keys' winners so far in `tmp`.  A slice of few tiles splits the keys among the waves instead of
-// the centroids (slice<CW>: CW waves share the centroids of a key).  Bound as assign_kernel is while many centroids
-// move, by the read of the keys once few do.
+// the centroids (slice<CW>: CW waves share the centroids of a key).  In a unit that takes all, workgroups are cut over
+// slices as well.  Bound as assign_kernel is while many centroids move, by the read of the keys once few do.
 // `tmp` and the key lists are scratch at the start of the unit's key tiles, 12 of the 256 bytes per token that the page
 // layout overwrites in any case.
-enum { kAllCentroids = 0, kMovedCentroids = 1, kListedKeys = 2 };  // what a pass over the keys is about
+enum { kMovedCentroids = 1, kListedKeys = 2 };  // what a pass over the keys is about
 __host__ __device__ inline int reassign_lds_bytes(bool aug, int Cpad) {
     return 2 * 256 * 256 + 2 * 256 * 8 + 512 * 4 + (aug ? 1024 * 4 : 0) + Cpad * 2 + Cpad / 8;
 }
 __device__ inline bool ordered_is_nan(uint32_t k) { return k > 0xFF800000u || k < 0x007FFFFFu; }
 
-template <bool AUG>
+template <bool AUG, bool ALL_FULL>  // ALL_FULL: every slice of the centroids is full (FULL of assign_slice)
 __global__ __launch_bounds__(512) void reassign_kernel(const bf16_t *__restrict__ K, const bf16_t *__restrict__ cent,
-                                                       const float *__restrict__ cnorm, int n, int keys_per_wg, int Cpad, int cur,
-                                                       int C, const int *__restrict__ go, int sort_round, Dev d) {  // (scalars first: preloaded at wave start)
+                                                       const float *__restrict__ cnorm, int n, int Cpad, int cur,
+                                                       const int *__restrict__ go, int round, int fused, RoundPlan plan, Dev d) {  // (scalars first: preloaded at wave start)
     constexpr int KS = AUG ? 9 : 8;
     extern __shared__ __align__(16) char smem[];
-    char *keys = smem;                                             // [2][256][256 B], chunks swizzled as in assign_kernel
+    char *keys = smem;                                             // [2][256][256 B], chunks swizzled as in assign_slice
     u64 *best = (u64 *)(smem + 2 * kAssignTile * 256);             // [2][256]
     float *seeds = (float *)(best + 2 * kAssignTile);              // [512] of the slice at hand
     uint32_t *kext = (uint32_t *)(seeds + 512);                    // (AUG) [2][256] the keys' extra coordinates
     uint32_t *cext = kext + 2 * kAssignTile;                       // (AUG) [512] the centroids' of the slice at hand
     uint16_t *list = (uint16_t *)(kext + (AUG ? 1024 : 0));        // [Cpad] moved centroids, ascending
     uint16_t *bits = list + Cpad;                                  // [Cpad / 16] the same as a mask
-    __shared__ int sh_wave[8], sh_fails;
+    uint16_t *won = (uint16_t *)(smem + assign_lds_bytes(AUG));    // (all centroids, fused) the run's winners
+    __shared__ int sh_wave[8], sh_keys[8], sh_fails;
     auto slot = [](int r, int c) { return r * 256 + ((c ^ (r & 15)) << 4); };
 
     const int u = blockIdx.y;
     int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int k0 = blockIdx.x * keys_per_wg;
-    const bf16_t *Ku = K + (size_t)u * n * kD;
     u64 *packed = d.packed + (size_t)u * d.max_tokens;
+
+    if (fused && blockIdx.x == 0 && tid == 0) d.any_moved[2 * u + (round & 1)] = 0;  // (for this round's means)
+    // ---- which centroids moved
+    ICE_PIN(plan.limit); ICE_PIN(plan.per_key); ICE_PIN(plan.fixed); ICE_PIN(plan.run);  // (not fetched behind the barrier)
+    int ncent = 0;
+    bool all;
+    {
+        const int lane = tid & 63, goes = go[2 * u], large = __builtin_amdgcn_readfirstlane(d.large_keys[u]);
+        uint32_t m = 0;
+        int held = 0;
+        if (tid * 16 < Cpad) m = moved_of_16(d.moved + (size_t)u * Cpad, tid, held);
+        if (goes == 0) return;  // (none: every winner stands)
+        const int cnt = __popc(m), incl = wave_scan_add(cnt);
+        held = wave_scan_add(held);
+        if (lane == 63) { sh_wave[wave] = incl; sh_keys[wave] = held; }
+        if (tid == 0) sh_fails = 0;
+        __syncthreads();
+        int pos = incl - cnt, total_held = 0;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) {
+            const int x = sh_wave[w];
+            pos += w < wave ? x : 0;
+            ncent += x;
+            total_held += sh_keys[w];
+        }
+        ncent = __builtin_amdgcn_readfirstlane(ncent);
+        all = large != 0 || takes_all(plan, ncent, __builtin_amdgcn_readfirstlane(total_held), n);
+        if (!all) {
+            if (tid * 16 < Cpad) bits[tid] = (uint16_t)m;
+            for (; m; m &= m - 1) list[pos++] = (uint16_t)(tid * 16 + __ffs(m) - 1);
+            if (tid < 2 * kAssignTile) best[tid] = 0ull;
+            __syncthreads();
+        }
+    }
+    const int nbits = 32 - __builtin_clz((unsigned)Cpad - 1u);
+    if (all) {
+        const int keys_per_wg = plan.all_run * kAssignTile, which = blockIdx.x / plan.all_wgs, k0 = (blockIdx.x - which * plan.all_wgs) * keys_per_wg;
+        const int kend = min(n, k0 + keys_per_wg);
+        if (which >= plan.slices) return;
+        assign_slice<2, 8, AUG, ALL_FULL>(d, K, cent, cnorm, n, u, which, k0, kend, plan.slices, Cpad, cur, nullptr,
+                                          round % kRoundNumbers, fused ? won : nullptr, false, smem);
+        if (fused) {  // (one slice: a range of the sort, as in assign_kernel)
+            __syncthreads();
+            sort_range<8, kFusedRun / 2, false>(d, thread_of(wave), u, n, blockIdx.x, plan.all_wgs, k0, kend, keys_per_wg / 8, 8, nbits, round, 1, (int *)smem,
+                                                nullptr, nullptr, [=](int i) { return (uint32_t)won[i - k0]; }, [](int) { return 0.f; });
+        }
+        return;
+    }
+    if ((int)blockIdx.x >= plan.wgs) return;
+    const int keys_per_wg = plan.run * kAssignTile, k0 = blockIdx.x * keys_per_wg;
+    const bf16_t *Ku = K + (size_t)u * n * kD;
     u64 *tmp = (u64 *)(d.Kp + (size_t)u * d.max_pages * d.s * kD);
     uint32_t *fails = (uint32_t *)(tmp + n) + k0;
 
-    // the pass at hand: job, number of keys and of centroids
-    int job = kMovedCentroids, nk = min(n, k0 + keys_per_wg) - k0, ncent = 0;
+    // the pass at hand: job, number of keys (and of centroids, ncent)
+    int job = kMovedCentroids, nk = min(n, k0 + keys_per_wg) - k0;
     auto key_of = [&](int pos) -> int {
         int key = k0 + min(pos, nk - 1);
         if (job == kListedKeys) {
@@ -969,47 +1082,12 @@ __global__ __launch_bounds__(512) void reassign_kernel(const bf16_t *__restrict_
         }
     };
 
-    if (sort_round >= 0 && blockIdx.x == 0 && tid == 0) d.any_moved[2 * u + (sort_round & 1)] = 0;  // (for this round's means)
-    // ---- which centroids moved
-    {
-        const int lane = tid & 63, goes = go[2 * u], large = d.large_keys[u];
-        uint32_t m = 0;
-        if (tid * 16 < Cpad) {
-            const uint4 w = ((const uint4 *)(d.moved + (size_t)u * Cpad))[tid];
-            auto nibble = [](uint32_t x) { return (x & 1u) | (x >> 7 & 2u) | (x >> 14 & 4u) | (x >> 21 & 8u); };
-            m = nibble(w.x) | nibble(w.y) << 4 | nibble(w.z) << 8 | nibble(w.w) << 12;
-            bits[tid] = (uint16_t)m;
-        }
-        if (goes == 0) return;  // (none: every winner stands)
-        const int cnt = __popc(m), incl = wave_scan_add(cnt);
-        if (lane == 63) sh_wave[wave] = incl;
-        if (tid == 0) sh_fails = 0;
-        if (tid < 2 * kAssignTile) best[tid] = 0ull;
-        __syncthreads();
-        int pos = incl - cnt;
-#pragma unroll
-        for (int w = 0; w < 8; ++w) {
-            const int x = sh_wave[w];
-            pos += w < wave ? x : 0;
-            ncent += x;
-        }
-        for (; m; m &= m - 1) list[pos++] = (uint16_t)(tid * 16 + __ffs(m) - 1);
-        ncent = __builtin_amdgcn_readfirstlane(ncent);
-        // (in tiles of 256 keys x 512 centroids, `steps` of them the whole contraction: the listed keys are about 0.45 of the
-        // moved share, their pass a prologue worth about 1.15 more)
-        const int steps = (nk + kAssignTile - 1) / kAssignTile * ((Cpad + 511) / 512);
-        if (large != 0 || 145 * ncent >= C * (100 - 115 / steps)) {
-            job = kAllCentroids;
-            ncent = Cpad;
-        }
-        __syncthreads();
-    }
-
     auto slice = [&](auto cw_arg, auto full_arg, int c0) __attribute__((always_inline)) {
         constexpr int CW = decltype(cw_arg)::value, KW = 8 / CW, NSUB = 8 / KW, R = CW * 64;
         constexpr bool FULL = decltype(full_arg)::value;
-        // (opaque in every slice: hoisted out of the forms and the loops, the lanes' addresses would not fit the registers)
-        asm volatile("" : "+v"(tid));
+        // (worked out in every slice and tile: hoisted out of the forms and the loops, the lanes' addresses would not fit the
+        // registers, and kept in memory instead they would be waited for)
+        tid = thread_of(wave);
         const int lane = tid & 63, col = lane & 31, half = lane >> 5;
         constexpr int CS = FULL ? 1 : CW;  // distance between a wave's two tiles (dealt over the SIMDs as in assign_kernel)
         const int kw = wave / CW, cw = FULL || CW == 8 ? wave % CW : (wave + (wave >> 2) * (CW / 2)) % CW;
@@ -1093,7 +1171,7 @@ __global__ __launch_bounds__(512) void reassign_kernel(const bf16_t *__restrict_
         for (int t = 0; t < ntiles; ++t) {
             const int buf = t & 1;
             u64 *bestt = best + buf * kAssignTile;
-            asm volatile("" : "+v"(tid));
+            tid = thread_of(wave);
             if (t + 1 < ntiles) {
                 const int ch = tid & 15, r16 = (tid >> 4) & 15;
                 int key[8];
@@ -1104,10 +1182,10 @@ __global__ __launch_bounds__(512) void reassign_kernel(const bf16_t *__restrict_
                     lds_dma16((const uint4 *)(Ku + (size_t)key[i] * kD) + (ch ^ r16), keys + (buf ^ 1) * (kAssignTile * 256) + (4 * wave + 32 * i) * 256);
             }
             // (the last slice of the moved centroids: what the tile's keys are compared with, in flight during the contraction)
-            u64 old = 0ull, sofar = 0ull;
+            u64 last_word = 0ull, sofar = 0ull;  // (the last round's winner as it is in memory: taken apart here it would be waited for)
             if (job == kMovedCentroids && last && tid < kAssignTile) {
                 const int key = key_of(t * kAssignTile + tid);
-                old = packed[key];
+                last_word = packed[key];
                 if (c0 > 0) sofar = tmp[key];
             }
             auto load_b = [&](int i, bf16x8 (&dst)[KS]) {
@@ -1180,7 +1258,7 @@ __global__ __launch_bounds__(512) void reassign_kernel(const bf16_t *__restrict_
             }
             // (what was requested ahead counts as arrived here for every lane: a wait left for a later place would also
             // cover the next tile's direct loads)
-            asm volatile("" : "+v"(old), "+v"(sofar));
+            asm volatile("" : "+v"(last_word), "+v"(sofar));
             __syncthreads();
             // the tile's winners, first 256 threads (a key's are the same thread's in every slice)
             if (tid < kAssignTile) {
@@ -1192,16 +1270,18 @@ __global__ __launch_bounds__(512) void reassign_kernel(const bf16_t *__restrict_
                 bestt[tid] = 0ull;
                 if (valid && !(job == kMovedCentroids && last)) {
                     u64 *dst = (job == kMovedCentroids ? tmp : packed) + key;
+                    if (job != kMovedCentroids) b = winner_word(b, round % kRoundNumbers);
                     if (c0 > 0) atomicMax(dst, b);  // (nothing waits for it)
                     else *dst = b;
                 } else if (valid) {
+                    const u64 old = winner_of_word(last_word);
                     b = max(b, sofar);
                     const uint32_t at = ~(uint32_t)b, own = min(~(uint32_t)old, (uint32_t)Cpad - 1u);
                     const uint32_t id = at < (uint32_t)ncent ? list[at] : 0x7FFFFFFFu;  // (a place past the list: no centroid)
                     const u64 m = (b & 0xFFFFFFFF00000000ull) | (u64)(0xFFFFFFFFu - id);
                     const bool own_moved = (bits[own >> 4] >> (own & 15u)) & 1u;
                     fail = ordered_is_nan((uint32_t)(b >> 32)) || ordered_is_nan((uint32_t)(old >> 32)) || (own_moved && m < old);
-                    if (!fail && m > old) packed[key] = m;
+                    if (!fail && m > old) packed[key] = winner_word(m, round % kRoundNumbers);
                 }
                 if (job == kMovedCentroids && last) {
                     const u64 f = __ballot(fail);
@@ -1231,39 +1311,72 @@ __global__ __launch_bounds__(512) void reassign_kernel(const bf16_t *__restrict_
         job = kListedKeys;
         ncent = Cpad;
     }
-    if (sort_round >= 0) {  // the run is a range of the sort as well
+    if (fused) {  // the run is a range of the sort as well
         wait_vmem();
         __threadfence_block();
         __syncthreads();
         const uint32_t *pk = (const uint32_t *)packed;
-        sort_range<8, kFusedRun / 2, false>(d, u, n, blockIdx.x, gridDim.x, k0, min(n, k0 + keys_per_wg), keys_per_wg / 8, 8,
-                                            32 - __builtin_clz((unsigned)Cpad - 1u), sort_round, 1, (int *)smem, nullptr, nullptr,
-                                            [=](int i) { return 0xFFFFFFFFu - pk[2 * i]; }, [](int) { return 0.f; });
+        sort_range<8, kFusedRun / 2, false>(d, thread_of(wave), u, n, blockIdx.x, plan.wgs, k0, min(n, k0 + keys_per_wg), keys_per_wg / 8, 8, nbits, round, 1,
+                                            (int *)smem, nullptr, nullptr, [=](int i) { return cluster_of_word(pk[2 * i]); }, [](int) { return 0.f; });
     }
 }
 
-// Round t by reassign_kernel instead of assign_kernel: from the third on (the first means move nearly all centroids) and
-// where the whole contraction is at least four tiles of 256 keys x 512 centroids per workgroup.  Measured, us per round, whole
-// contraction and rounds 2, 3, ... so: 8 units x 32768 x 512 (four tiles) 34 and 38, 41, 33, 27, 24, 23, 22, 22; 8 x 131072 x 2048
-// (64) 420 and 476, 480, 428, 290, 194, 150, 110, 97; but 8 x 16384 x 256 (one) 13 and 21, 19, 16, 15, 15.
-bool reassign_pays(const Dev &d, int n, int t) {
-    const int tiles = d.Cpad / 32, full = tiles / 16, rest = tiles % 16;
-    return t >= 2 && assign_run(d.U, n, 1) * (16 * full + rest) >= 64;
+static RoundPlan round_plan(const Dev &d, int n) {
+    const int ktiles = (n + kAssignTile - 1) / kAssignTile;
+    RoundPlan p;
+    p.slices = assign_slices(d);
+    p.run = assign_run(d.U, n, 1);
+    p.wgs = (ktiles + p.run - 1) / p.run;
+    p.all_run = assign_run(d.U, n, p.slices);
+    p.all_wgs = (ktiles + p.all_run - 1) / p.all_run;
+    auto turns = [](long long wgs) { return (wgs + 255) / 256; };
+    p.tiles = p.slices > 1 ? 16 : 4 * ((d.Cpad + 127) / 128);
+    p.fixed = 16 * p.slices;
+    p.per_key = p.run * p.tiles * p.slices;
+    // (the moved centroids' launch in as many rounds of the chip as it takes)
+    p.all_turns = turns((long long)d.U * p.all_wgs * p.slices);
+    p.limit = p.all_turns * (p.all_run * p.tiles + 16) * 2 * n / turns((long long)d.U * p.wgs);
+    return p;
+}
+
+// Rounds by reassign_kernel instead of assign_kernel: from the third on (the first means move nearly all centroids), above
+// 256 clusters (eight tiles or fewer are contracted in the time that their keys take to come in) and
+// where the whole contraction is at least four tiles of 256 keys x 512 centroids per workgroup.  A unit that takes all of
+// it pays 0.7 us for finding that out; from four tiles on that is below 2 %, and what keys that settle gain is many times that.
+// Builds of ten rounds, us, without and with it, keys that settle (the benchmark's mixture) and keys without structure:
+// 8 units x 32768 x 512 (four tiles) 556 and 510, 638 and 640; transformed 632 and 581, 718 and 718; 4 x 65536 x 1024 (eight)
+// 836 and 691, 992 and 1000; 8 x 131072 x 2048 (64) 5200 and 3130, 5390 and 5390.  Below the line, with it all the same: 8 x 24576 x
+// 512 (three tiles) 407 and 374, 507 and 508; 4 x 32768 x 512 (two) 340 and 327, 406 and 411; 1 x 16384 x 1024 (one) 168.2 and
+// 168.7, 246 and 250.
+bool reassign_pays(const Dev &d, int n) {
+    if (d.Cpad <= 256) return false;
+    const RoundPlan p = round_plan(d, n);
+    return p.all_turns * p.all_run * p.tiles >= 64;
 }
 
 void launch_reassign(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fused, hipStream_t st) {
-    const int keys_per_wg = assign_run(d.U, n, 1) * kAssignTile;
-    const size_t lds = reassign_lds_bytes(d.tk != 0, d.Cpad);
-    const dim3 grid((n + keys_per_wg - 1) / keys_per_wg, d.U);
-#define ICE_REASSIGN(aug)                                                                                                  \
+    const RoundPlan p = round_plan(d, n);
+    const size_t lds = std::max<size_t>(reassign_lds_bytes(d.tk != 0, d.Cpad), assign_lds_bytes(d.tk != 0) + (fused ? (size_t)p.all_run * kAssignTile * 2 : 0));
+    const dim3 grid(std::max(p.wgs, p.all_wgs * p.slices), d.U);
+#define ICE_REASSIGN(aug, full)                                                                                            \
     do {                                                                                                                   \
-        allow_dynamic_lds((const void *)reassign_kernel<aug>, lds);                                                        \
-        hipLaunchKernelGGL((reassign_kernel<aug>), grid, dim3(512), lds, st, K, d.cent_bf16[cur], d.cnorm[cur], n, keys_per_wg, d.Cpad, \
-                           cur, d.C, round_goes(d, t), fused ? t : -1, d);                                                 \
+        allow_dynamic_lds((const void *)reassign_kernel<aug, full>, lds);                                                  \
+        hipLaunchKernelGGL((reassign_kernel<aug, full>), grid, dim3(512), lds, st, K, d.cent_bf16[cur], d.cnorm[cur], n, d.Cpad, \
+                           cur, round_goes(d, t), t, fused ? 1 : 0, p, d);                                                   \
     } while (0)
-    if (d.tk) ICE_REASSIGN(true);
-    else ICE_REASSIGN(false);
+    const bool full = d.Cpad / 32 % 16 == 0;
+    if (d.tk) { if (full) ICE_REASSIGN(true, true); else ICE_REASSIGN(true, false); }
+    else { if (full) ICE_REASSIGN(false, true); else ICE_REASSIGN(false, false); }
 #undef ICE_REASSIGN
+}
+
+void build_plan(const Dev &d, int n, int *plan) {
+    plan[0] = sort_is_fused(d, n) ? 1 : 0;
+    plan[1] = sort_len(d, n);
+    plan[2] = (n + plan[1] - 1) / plan[1];
+    plan[3] = reassign_pays(d, n) ? 2 : 0;
+    plan[4] = assign_run(d.U, n, 1);
+    plan[5] = assign_slices(d);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -1275,10 +1388,11 @@ __global__ __launch_bounds__(1024) void range_sort_kernel(Dev d, int n, int L, i
     const int r = blockIdx.x, u = blockIdx.y;
     const int goes = round > 0 ? d.any_moved[2 * u + ((round - 1) & 1)] : 1;
     if (r == 0 && threadIdx.x == 0) d.any_moved[2 * u + (round & 1)] = 0;  // (for this round's means)
-    // low word of a packed winner = ~cluster id (the high word, the score, is read only for best_out)
-    const uint32_t *pk = (const uint32_t *)(d.packed + (size_t)u * d.max_tokens);
-    sort_range<16, NG, MASK>(d, u, n, r, gridDim.x, r * L, min(n, r * L + L), L / W, W, nbits, round, goes, pos_all, best_out, assign_out,
-                             [=](int i) { return 0xFFFFFFFFu - pk[2 * i]; }, [=](int i) { return -2.0f * ordered_f32(pk[2 * i + 1]); });
+    // (a winner's low word holds its cluster; the whole of it is read only for best_out)
+    const u64 *packed = d.packed + (size_t)u * d.max_tokens;
+    const uint32_t *pk = (const uint32_t *)packed;
+    sort_range<16, NG, MASK>(d, threadIdx.x, u, n, r, gridDim.x, r * L, min(n, r * L + L), L / W, W, nbits, round, goes, pos_all, best_out, assign_out,
+                             [=](int i) { return cluster_of_word(pk[2 * i]); }, [=](int i) { return -2.0f * ordered_f32((uint32_t)(packed[i] >> 13)); });
 }
 
 void launch_sort(const Dev &d, int n, int t, float *best_out, int *assign_out, hipStream_t st) {
@@ -1586,7 +1700,7 @@ __global__ __launch_bounds__(256, 8) void means_kernel(Dev d, const bf16_t *__re
     // (stored here and not where it is known: the first loads' wait would cover an earlier store)
     if (lane == 0) {
         d.cluster_cnt[(size_t)u * d.C + c] = cnt;
-        d.moved[row] = moved ? 1 : 0;
+        d.moved[row] = moved ? (uint32_t)cnt << 1 | 1u : 0u;
         if (moved) d.any_moved[2 * u + (round & 1)] = 1;
         d.touched[row] = 0;
     }

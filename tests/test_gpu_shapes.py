@@ -453,16 +453,48 @@ def test_imports_in_one_launch_and_through_copies(kw, odd):
         assert torch.equal(ea[f], eb[f]), f
 
 
+def _every_stage_again(Kd, Vd, init, C, tk, T):
+    """The state of a build of T rounds, the same after every stage of the last round has been done again in full."""
+    import torch
+    from paper_2604_10539_amd import IceIndex, ice_debug_rerun_stage
+    from paper_2604_10539_amd.binding import ICE_GEOMETRY_RAW, ICE_GEOMETRY_TRANSFORMED
+    U, n = Kd.shape[1], Kd.shape[2]
+    ix = IceIndex(1, U, 4, n, 16, C, kmeans_iters=T, init_idx=init, geometry=ICE_GEOMETRY_TRANSFORMED if tk else ICE_GEOMETRY_RAW)
+    ix.build_index(Kd, Vd)
+
+    def state():
+        ex = dict(ix.export())
+        out = {f: ex[f] for f in ("assign", "cluster_cnt", "cluster_sum", "centroid", "Kp", "page_pos", "page_sum", "n_pages")}
+        geo = ix.export_geometry()
+        if geo:
+            out.update({f: geo[f] for f in ("centroid_extra", "cluster_sum_extra")})
+        torch.cuda.synchronize()
+        return {f: (x.view(torch.int32) if x.dtype == torch.float32 else x).clone() for f, x in out.items()}
+    had = state()
+    for stage in range(4):
+        ice_debug_rerun_stage(ix.handle, Kd, Vd, stage)
+    now = state()
+    for f in had:
+        if f == "Kp":  # (live pages)
+            for u in range(U):
+                p = int(had["n_pages"][u])
+                assert torch.equal(had[f][u, :p], now[f][u, :p]), (T, f, u)
+        else:
+            assert torch.equal(had[f], now[f]), (T, f)
+    return had
+
+
 @pytest.mark.parametrize("U,n,C,tk,odd", [(3, 700, 40, 0, False), (2, 3000, 130, 1, False), (2, 4100, 520, 0, False), (1, 1500, 1100, 1, False),
                                           (5, 2600, 500, 0, False), (2, 5000, 16, 1, False), (1, 9000, 250, 0, True), (2, 2000, 700, 1, True)])
 def test_later_rounds_do_again_what_changed_and_leave_what_all_of_it_would(U, n, C, tk, odd):
-    """A build's rounds after the first score only what the last round's means changed, and sum only clusters whose members
+    """A build's later rounds leave out units of which no centroid moved and sum only clusters whose members
     changed.  Every stage of the last round once more, over everything, leaves the same bits, after two rounds, three, ...
     (each of them started from the state that the test before it found right).  Few and many centroid tiles, several
-    slices of 512, clusters of one key; `odd`: among keys without a comparable score and equal keys."""
+    slices of 512, clusters of one key; `odd`: among keys without a comparable score and equal keys.  Builds this small score
+    all centroids in every round; the next test's do not."""
     import torch
-    from paper_2604_10539_amd import IceIndex
-    from paper_2604_10539_amd.binding import ICE_GEOMETRY_RAW, ICE_GEOMETRY_TRANSFORMED, ice_debug_rerun_stage
+    from paper_2604_10539_amd import ice_debug_build_plan, make_config
+    assert ice_debug_build_plan(make_config(1, U, 4, n), n, C)["reassign_from"] == 0
     w = datagen.small(n_tokens=n, n_clusters=C, n_kv_heads=U, n_components=max(4, C // 2), outlier_frac=0.05)
     K, V = datagen.keys_values(w)
     if odd:
@@ -472,33 +504,50 @@ def test_later_rounds_do_again_what_changed_and_leave_what_all_of_it_would(U, n,
     Kd, Vd, init = up(K), up(V), up(datagen.init_indices(w))
     settled = False
     for T in (2, 3, 4, 5, 6, 8, 12, 30):
-        ix = IceIndex(1, U, 4, n, 16, C, kmeans_iters=T, init_idx=init, geometry=ICE_GEOMETRY_TRANSFORMED if tk else ICE_GEOMETRY_RAW)
-        ix.build_index(Kd, Vd)
-
-        def state():
-            ex = dict(ix.export())
-            out = {f: ex[f] for f in ("assign", "cluster_cnt", "cluster_sum", "centroid", "Kp", "page_pos", "page_sum", "n_pages")}
-            geo = ix.export_geometry()
-            if geo:
-                out.update({f: geo[f] for f in ("centroid_extra", "cluster_sum_extra")})
-            torch.cuda.synchronize()
-            return {f: (x.view(torch.int32) if x.dtype == torch.float32 else x).clone() for f, x in out.items()}
-        had = state()
-        for stage in range(4):
-            ice_debug_rerun_stage(ix.handle, Kd, Vd, stage)
-        now = state()
-        for f in had:
-            if f == "Kp":  # (live pages)
-                for u in range(U):
-                    p = int(had["n_pages"][u])
-                    assert torch.equal(had[f][u, :p], now[f][u, :p]), (T, f, u)
-            else:
-                assert torch.equal(had[f], now[f]), (T, f)
+        had = _every_stage_again(Kd, Vd, init, C, tk, T)
         if T == 12:
             last = had
         if T == 30 and not odd:
             settled = torch.equal(last["assign"], had["assign"])
     assert settled or odd or n > 100 * C  # (rounds in which nothing moves were among them, unless clusters are large)
+
+
+@pytest.mark.parametrize("U,n,C,tk,odd,slices,run,fused", [
+    (8, 32768, 512, 0, "", 1, 4, 1),       # one slice, its sort inside, four key tiles per workgroup
+    (16, 23457, 366, 1, "", 1, 6, 1),      # ... transformed, a slice not full, a ragged last tile
+    (16, 9000, 700, 0, "", 2, 3, 0),       # two slices (and one at a time for few moved centroids)
+    (24, 3000, 1100, 1, "", 3, 2, 0),
+    (32, 2060, 2048, 0, "", 4, 2, 0),      # clusters of one key
+    (4, 40000, 600, 1, "few", 2, 3, 0),    # components far fewer than clusters: centroids go on moving
+    (16, 9000, 700, 0, "none", 2, 3, 0),   # no components at all
+    (8, 34000, 400, 0, "none", 1, 5, 1),
+    (16, 9000, 700, 1, "odd", 2, 3, 0),    # equal keys, and units of which some keys are not finite beside units of which all are
+    (8, 32768, 512, 0, "odd", 1, 4, 1),
+])
+def test_later_rounds_that_score_what_moved_leave_what_all_centroids_would(U, n, C, tk, odd, slices, run, fused):
+    """The same where later rounds score only the centroids that moved and then the keys that lost theirs: from the third
+    round on, over one slice of 512 centroids and several, with the sort inside and after it, from rounds in which most
+    centroids moved (those are done in full) to rounds in which few did and none."""
+    import torch
+    from paper_2604_10539_amd import ice_debug_build_plan, make_config
+    p = ice_debug_build_plan(make_config(1, U, 4, n), n, C)
+    assert (p["reassign_from"], p["slices"], p["run"], p["fused"]) == (2, slices, run, fused)
+    gen = torch.Generator(device="cuda").manual_seed(U * n + C)
+    K = torch.randn(1, U, n, D, generator=gen, device="cuda")
+    if odd != "none":
+        M = C // 20 if odd == "few" else C // 2
+        centers = torch.randn(U, M, D, generator=gen, device="cuda")
+        at = torch.randint(M, (U, n), generator=gen, device="cuda")
+        K = 0.3 * K + torch.gather(centers, 1, at[..., None].expand(-1, -1, D))[None]
+    K = K.to(torch.bfloat16).view(torch.int16)
+    if odd == "odd":
+        K[0, :, 100:400] = K[0, :, 100:101]
+        for i, t in enumerate(range(5, n, 211)):
+            K[0, ::2, t, i % D:] = [0x7FC0, 0x7F80, 0xFF80 - 65536, 0xFFC0 - 65536][i % 4]  # NaN, inf, -inf, -NaN
+    V = torch.randint(-16000, 16000, K.shape, generator=gen, device="cuda", dtype=torch.int16)
+    init = torch.stack([torch.sort(torch.randperm(n, generator=gen, device="cuda")[:C])[0] for _ in range(U)]).int()[None].contiguous()
+    for T in (3, 4, 5, 6, 8, 12):
+        _every_stage_again(K, V, init, C, tk, T)
 
 
 def test_later_rounds_where_scores_stop_comparing():
@@ -507,8 +556,8 @@ def test_later_rounds_where_scores_stop_comparing():
     other rows held beside them; a round that looks only at the centroids that moved has to come to the same."""
     import torch
     from paper_2604_10539_amd import IceIndex
-    from paper_2604_10539_amd.binding import ice_debug_rerun_stage
-    C, first, j = 2048, 64, 127          # rows 64..95 are a tile
+    from paper_2604_10539_amd import ice_debug_build_plan, ice_debug_rerun_stage, make_config
+    C, first, j, U = 2048, 64, 127, 32   # rows 64..95 are a tile
     a, b = first + 16, first + 17        # the ninth row of the tile's first half, and the row that loses a key to it
     rng = np.random.default_rng(3)
     K = rng.standard_normal((C, D))      # clusters of one key, far apart
@@ -522,9 +571,10 @@ def test_later_rounds_where_scores_stop_comparing():
     K = narrow(np.concatenate([K, more]).astype(np.float32))
     K[first + np.r_[0:4, 8:12]] = 0x7FC0
     K[C + 11, j] = 0x7F80                # nearest, at +inf, to the first row with a positive coordinate j: b + 1, then b, then a
-    Kd, init = up(K[None, None]), up(np.arange(C, dtype=np.int32)[None, None])
+    Kd, init = up(np.stack([K] * U)[None]), up(np.stack([np.arange(C, dtype=np.int32)] * U)[None])
+    assert ice_debug_build_plan(make_config(1, U, 4, len(K)), len(K), C)["reassign_from"] == 2
     for T in (3, 4, 6):
-        ix = IceIndex(1, 1, 4, len(K), 16, C, kmeans_iters=T, init_idx=init)
+        ix = IceIndex(1, U, 4, len(K), 16, C, kmeans_iters=T, init_idx=init)
         ix.build_index(Kd, Kd)
         ex = ix.export()
         had = {f: ex[f].clone() for f in ("assign", "cluster_cnt", "page_pos")}
