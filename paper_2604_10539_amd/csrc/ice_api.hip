@@ -252,7 +252,7 @@ ice_status_t ice_build_index(ice_index_t *ix, const void *K, const void *V, int3
         if (later && t >= 2 && t % kRoundNumbers != 0) launch_reassign(d, Kb, n, cur, t, fused, s);
         else launch_assign(d, Kb, n, cur, t, fused, later && t == 0, s);
         if (!fused) launch_sort(d, n, t, nullptr, nullptr, s);
-        launch_means(d, Kb, n, cur, t, s);
+        launch_means(d, Kb, n, cur, t, t + 1 == ix->cfg.kmeans_iters, s);
         cur ^= 1;
     }
     launch_paginate(d, Kb, Vb, n, true, s);
@@ -594,7 +594,7 @@ ice_status_t ice_debug_rerun_stage(ice_index_t *ix, const void *K, const void *V
     switch (stage) {
         case ICE_STAGE_ASSIGN: launch_assign(d, Kb, n, prev, 0, false, false, s); break;
         case ICE_STAGE_SORT: launch_sort(d, n, 0, nullptr, nullptr, s); break;
-        case ICE_STAGE_MEANS: launch_means(d, Kb, n, prev, 0, s); break;
+        case ICE_STAGE_MEANS: launch_means(d, Kb, n, prev, 0, true, s); break;
         case ICE_STAGE_PAGINATE: launch_paginate(d, Kb, Vb, n, false, s); break;
         default: return fail(ICE_ERR_INVALID_ARG, "stage %d: one of ICE_STAGE_ASSIGN .. ICE_STAGE_PAGINATE", stage);
     }

@@ -394,13 +394,16 @@ __device__ inline void sort_range(const Dev &d, int tid, int u, int n, int r, in
     const int Cpad = d.Cpad;
     const int beg = min(re, rb + wave * seg), end = wave < W ? min(re, beg + seg) : beg;  // this wave's tokens
     uint32_t v[NG];
-    constexpr bool AHEAD = NG <= 16;  // (the registers of the longest form do not hold the last round's clusters as well)
-    int was[AHEAD ? NG : 1];
+    // The last round's clusters.  The registers of the longest form hold a few of them at a time, requested kAhead groups ahead.
+    constexpr int kAhead = NG <= 16 ? NG : 8;
+    int was[kAhead];
+    const int *assign = d.assign + (size_t)u * d.max_tokens;
+    auto token = [&](int j) { return min(beg + j * 64 + lane, re - 1); };  // (past the end: read and dropped, no branch around the loads)
 #pragma unroll
-    for (int j = 0; j < NG; ++j) {
-        const int i = beg + j * 64 + lane;
-        v[j] = i < end ? winner(i) : 0u;
-        if constexpr (AHEAD) was[j] = round > 0 && i < end ? d.assign[(size_t)u * d.max_tokens + i] : 0;
+    for (int j = 0; j < NG; ++j) v[j] = winner(token(j));
+    if (round > 0) {
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) was[j] = assign[token(j)];
     }
     if (goes == 0) return;  // (no centroid moved: nor did a token)
     for (int x = tid; x < W * Cpad / 4 * (MASK ? 3 : 1); x += NT) ((int4 *)pos_all)[x] = make_int4(0, 0, 0, 0);  // (Cpad is a multiple of 32)
@@ -1493,7 +1496,7 @@ static bool keys_exceed_cache(const Dev &d, int n) { return (size_t)d.U * (size_
 // 59 through LDS, 56.4, 53.5; 8 units x 131072 x 2048, 32 pieces, 61.7, 60.7, 55; 2 x 131072 x 64, clusters of thousands, 131, 108, 103.
 // (Eight waves per SIMD: 256 units 418 us with seven; the last form keeps two registers in scratch for it, 62 -> 60.6 at 8 units.)
 template <bool STREAM, int NP>
-__global__ __launch_bounds__(256, 8) void means_kernel(Dev d, const bf16_t *__restrict__ K, int n, int cur, int R, int L, int round) {
+__global__ __launch_bounds__(256, 8) void means_kernel(Dev d, const bf16_t *__restrict__ K, int n, int cur, int R, int L, int round, int last) {
     __shared__ float4 part_sum[3][16][2];
     __shared__ int slots[kMemberSlots], sh_cnt, sh_listed;
     __shared__ float aug_lds[kAugChunk];
@@ -1647,8 +1650,12 @@ __global__ __launch_bounds__(256, 8) void means_kernel(Dev d, const bf16_t *__re
         }
     }
     // what the last assignment saw of the centroid (in flight while the waves meet)
-    const uint4 was = ((const uint4 *)(d.cent_bf16[cur] + row * kD))[ch];
-    const float was_norm = d.cnorm[cur][row];
+    uint4 was = make_uint4(0, 0, 0, 0);
+    float was_norm = 0.f;
+    if (wave == 0 && !last) {  // (behind the last round nobody asks)
+        was = ((const uint4 *)(d.cent_bf16[cur] + row * kD))[ch];
+        was_norm = d.cnorm[cur][row];
+    }
     if (wave > 0 && g == 0) {
         part_sum[wave - 1][ch][0] = make_float4(acc[0], acc[1], acc[2], acc[3]);
         part_sum[wave - 1][ch][1] = make_float4(acc[4], acc[5], acc[6], acc[7]);
@@ -1680,7 +1687,7 @@ __global__ __launch_bounds__(256, 8) void means_kernel(Dev d, const bf16_t *__re
         nn += f0 * f0 + f1 * f1;
     }
     nn = row16_sum(nn);
-    bool moved = __ballot(was.x != pk[0] || was.y != pk[1] || was.z != pk[2] || was.w != pk[3]) != 0ull;
+    bool moved = __ballot(was.x != pk[0] || was.y != pk[1] || was.z != pk[2] || was.w != pk[3]) != 0ull;  // (last: no matter)
     if (d.tk) {
         // the centroid's extra coordinate: mean of the members' extra coordinates (the fixed wave
         // reduction of the partial sums above)
@@ -1715,12 +1722,12 @@ __global__ __launch_bounds__(256, 8) void means_kernel(Dev d, const bf16_t *__re
     }
 }
 
-void launch_means(const Dev &d, const bf16_t *K, int n, int cur, int t, hipStream_t st) {
+void launch_means(const Dev &d, const bf16_t *K, int n, int cur, int t, bool last, hipStream_t st) {
     const int L = sort_len(d, n), R = (n + L - 1) / L;
 #define ICE_MEANS(np)                                                                                                     \
     do {                                                                                                                  \
-        if (keys_exceed_cache(d, n)) hipLaunchKernelGGL((means_kernel<true, np>), dim3(d.C, d.U), dim3(256), 0, st, d, K, n, cur, R, L, t); \
-        else hipLaunchKernelGGL((means_kernel<false, np>), dim3(d.C, d.U), dim3(256), 0, st, d, K, n, cur, R, L, t); \
+        if (keys_exceed_cache(d, n)) hipLaunchKernelGGL((means_kernel<true, np>), dim3(d.C, d.U), dim3(256), 0, st, d, K, n, cur, R, L, t, last ? 1 : 0); \
+        else hipLaunchKernelGGL((means_kernel<false, np>), dim3(d.C, d.U), dim3(256), 0, st, d, K, n, cur, R, L, t, last ? 1 : 0); \
     } while (0)
     if (R == 1) ICE_MEANS(1);
     else if (R <= kFewPieces) ICE_MEANS(kFewPieces);

@@ -116,7 +116,8 @@ void launch_reassign(const Dev &d, const bf16_t *K, int n, int cur, int t, bool 
 void build_plan(const Dev &d, int n, int *plan);  // ice_debug_build_plan
 void launch_sort(const Dev &d, int n, int t, float *best_out_or_null, int *assign_out_or_null, hipStream_t st);
 size_t sort_ranges_max(int U, int max_tokens, int Cpad);  // (unit, range) pairs of any sort of at most max_tokens tokens
-void launch_means(const Dev &d, const bf16_t *K, int n, int cur, int t, hipStream_t st);
+// last: no round follows that would ask which centroids moved
+void launch_means(const Dev &d, const bf16_t *K, int n, int cur, int t, bool last, hipStream_t st);
 // arm: also the decode state of a fresh index (token counters, arrival counters, empty score slots)
 void launch_paginate(const Dev &d, const bf16_t *K, const bf16_t *V, int n, bool arm, hipStream_t st);
 void launch_refresh_centroids(const Dev &d, int cur, hipStream_t st);
