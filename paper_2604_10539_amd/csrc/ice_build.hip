@@ -383,10 +383,11 @@ __device__ inline int thread_of(int wave) {
 // cluster in LDS (OR, read back, clear) instead of by ballots: cheaper per group, but the masks have to be cleared and
 // take 8 more bytes per counter, so it is for long ranges (256 units x 32768 tokens: 78 us with ballots, 69 so).
 // The sort of tokens [rb, re) of unit u, its range r of R, by a workgroup of NWV waves; W segments of `seg` tokens.
-// winner(i): cluster of token i, best_of(i): what goes to best_out.  Every thread comes here.
-template <int NWV, int NG, bool MASK, typename Winner, typename BestOf>
+// winner(i): what is known of token i's cluster, cluster(.): which it is (apart, so that nothing is waited for where it is
+// loaded), best_of(i): what goes to best_out.  Every thread comes here.
+template <int NWV, int NG, bool MASK, typename Winner, typename Cluster, typename BestOf>
 __device__ inline void sort_range(const Dev &d, int tid, int u, int n, int r, int R, int rb, int re, int seg, int W, int nbits, int round, int goes,
-                                  int *pos_all, float *best_out, int *assign_out, Winner winner, BestOf best_of) {
+                                  int *pos_all, float *best_out, int *assign_out, Winner winner, Cluster cluster, BestOf best_of) {
     constexpr int NT = NWV * 64;
     __shared__ int wsum[NWV];
     __shared__ int carry;
@@ -419,7 +420,7 @@ __device__ inline void sort_range(const Dev &d, int tid, int u, int n, int r, in
         const bool valid = i < end;
         // (always < C for finite keys; a key with no finite score may come out with a padding row: it goes to the last
         // cluster, so that every token has a page whatever its key holds)
-        const int a = (int)min(v[j], (uint32_t)d.C - 1u);
+        const int a = (int)min(cluster(v[j]), (uint32_t)d.C - 1u);
         v[j] = (uint32_t)a << 16;
         if (beg + j * 64 >= end) continue;  // (wave-uniform)
         u64 peers;
@@ -441,26 +442,27 @@ __device__ inline void sort_range(const Dev &d, int tid, int u, int n, int r, in
             const int base = pos[a];
             v[j] |= (uint32_t)(base + (int)__popcll(peers & lt));
             if ((peers & lt) == 0ull) pos[a] = base + (int)__popcll(peers);
-            if constexpr (!AHEAD) {
-                if (round > 0) {
-                    const int b = d.assign[(size_t)u * d.max_tokens + i];
-                    if (a != b) d.touched[(size_t)u * Cpad + a] = d.touched[(size_t)u * Cpad + b] = 1;
-                }
-            }
             d.assign[(size_t)u * d.max_tokens + i] = a;
             if (assign_out) assign_out[(size_t)u * n + i] = a;
             if (best_out) best_out[(size_t)u * n + i] = best_of(i);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // (the LDS unit executes a wave's accesses in order)
+        if constexpr (kAhead < NG) {
+            if (round > 0) {
+                const int b = was[j % kAhead];
+                if (valid && a != b) d.touched[(size_t)u * Cpad + a] = d.touched[(size_t)u * Cpad + b] = 1;
+                if (j + kAhead < NG) was[j % kAhead] = assign[token(j + kAhead)];
+            }
+        }
     }
-    if (AHEAD && round > 0) {  // a later round of a build: the clusters that lost or gained a token are marked
+    if (kAhead == NG && round > 0) {  // a later round of a build: the clusters that lost or gained a token are marked
         // (a range without such a token could be left as it is, but finding that out for the whole workgroup takes as long
         // as sorting 1024 tokens: 6.3 us with the exit taken or not)
 #pragma unroll
         for (int j = 0; j < NG; ++j) {
             const int i = beg + j * 64 + lane;
             if (i < end) {
-                const int a = (int)(v[j] >> 16), b = was[AHEAD ? j : 0];
+                const int a = (int)(v[j] >> 16), b = was[j % kAhead];
                 if (a != b) d.touched[(size_t)u * Cpad + a] = d.touched[(size_t)u * Cpad + b] = 1;
             }
         }
@@ -853,7 +855,7 @@ __global__ __launch_bounds__(512) void assign_kernel(const bf16_t *__restrict__ 
     if (fused) {  // the run is a range of the sort as well
         __syncthreads();    // (the winners are there; the key tiles are not needed any more)
         sort_range<8, kFusedRun / 2, false>(d, threadIdx.x, u, n, blockIdx.x, gridDim.x, k0, kend, keys_per_wg / 8, 8, 32 - __builtin_clz((unsigned)Cpad - 1u),
-                                            round, 1, (int *)smem, nullptr, nullptr, [=](int i) { return (uint32_t)won[i - k0]; },
+                                            round, 1, (int *)smem, nullptr, nullptr, [=](int i) { return (uint32_t)won[i - k0]; }, [](uint32_t w) { return w; },
                                             [](int) { return 0.f; });
     }
 }
@@ -1050,7 +1052,7 @@ __global__ __launch_bounds__(512) void reassign_kernel(const bf16_t *__restrict_
         if (fused) {  // (one slice: a range of the sort, as in assign_kernel)
             __syncthreads();
             sort_range<8, kFusedRun / 2, false>(d, thread_of(wave), u, n, blockIdx.x, plan.all_wgs, k0, kend, keys_per_wg / 8, 8, nbits, round, 1, (int *)smem,
-                                                nullptr, nullptr, [=](int i) { return (uint32_t)won[i - k0]; }, [](int) { return 0.f; });
+                                                nullptr, nullptr, [=](int i) { return (uint32_t)won[i - k0]; }, [](uint32_t w) { return w; }, [](int) { return 0.f; });
         }
         return;
     }
@@ -1320,7 +1322,7 @@ __global__ __launch_bounds__(512) void reassign_kernel(const bf16_t *__restrict_
         __syncthreads();
         const uint32_t *pk = (const uint32_t *)packed;
         sort_range<8, kFusedRun / 2, false>(d, thread_of(wave), u, n, blockIdx.x, plan.wgs, k0, min(n, k0 + keys_per_wg), keys_per_wg / 8, 8, nbits, round, 1,
-                                            (int *)smem, nullptr, nullptr, [=](int i) { return cluster_of_word(pk[2 * i]); }, [](int) { return 0.f; });
+                                            (int *)smem, nullptr, nullptr, [=](int i) { return pk[2 * i]; }, cluster_of_word, [](int) { return 0.f; });
     }
 }
 
@@ -1395,7 +1397,7 @@ __global__ __launch_bounds__(1024) void range_sort_kernel(Dev d, int n, int L, i
     const u64 *packed = d.packed + (size_t)u * d.max_tokens;
     const uint32_t *pk = (const uint32_t *)packed;
     sort_range<16, NG, MASK>(d, threadIdx.x, u, n, r, gridDim.x, r * L, min(n, r * L + L), L / W, W, nbits, round, goes, pos_all, best_out, assign_out,
-                             [=](int i) { return cluster_of_word(pk[2 * i]); }, [=](int i) { return -2.0f * ordered_f32((uint32_t)(packed[i] >> 13)); });
+                             [=](int i) { return pk[2 * i]; }, cluster_of_word, [=](int i) { return -2.0f * ordered_f32((uint32_t)(packed[i] >> 13)); });
 }
 
 void launch_sort(const Dev &d, int n, int t, float *best_out, int *assign_out, hipStream_t st) {
