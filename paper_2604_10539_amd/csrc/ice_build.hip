@@ -358,12 +358,18 @@ static int sort_range_len(int U, int n, int Cpad) {
 // kFusedRun tiles per workgroup (their winners sit in LDS), one workgroup per CU and at most 128 ranges per unit.  A launch and
 // the reading of the winners less per round; assignment and sort by themselves and in one, us: 8 units x 4000 x 62 5.2 + 5.8 and
 // 7.6, 8 x 16384 x 256 13.0 + 6.3 and 15.8, 8 x 32768 x 512 34.7 + 7.2 and 38.1, 16 x 23457 x 366 (transformed) 40.9 + 9.0 and 46.0.
-constexpr int kFusedRun = 16;
+// What reads the members pays for shorter ranges: a wave holds 64 pieces of a cluster, and beyond 64 ranges a cluster that is
+// not listed in LDS (kMemberSlots) is searched piece by piece.  So more than 64 ranges are for clusters of about 330 members and
+// fewer.  Whole builds of ten rounds, by themselves and in one: 32 ranges 8 x 32768 x 512 517 and 486, clusters of 2048 8 x 32768 x 16
+// 706 and 673; 79 ranges 1 x 20000 x 60 213 and 189, x 40 243 and 241; 128 ranges 1 x 32768 x 512 246 and 219, x 100 (328 members) 226
+// and 202, transformed 286 and 282; but x 80 (410) 246 and 248, transformed 285 and 302, x 16 376 and 423; 2 x 65536 x 200 (328) 344 and
+// 345, x 128 345 and 355, x 32 transformed 650 and 792.
+constexpr int kFusedRun = 16, kFusedMembers = 336;
 static int assign_run(int U, int n, int slices);
 bool sort_is_fused(const Dev &d, int n) {
     if (d.Cpad > 512) return false;
     const int run = assign_run(d.U, n, 1), R = (n + run * kAssignTile - 1) / (run * kAssignTile);
-    return run <= kFusedRun && R <= 128 && (long long)d.U * R <= 256;
+    return run <= kFusedRun && R <= (n <= (long long)kFusedMembers * d.C ? 128 : 64) && (long long)d.U * R <= 256;
 }
 // tokens per range of the sort
 static int sort_len(const Dev &d, int n) { return sort_is_fused(d, n) ? assign_run(d.U, n, 1) * kAssignTile : sort_range_len(d.U, n, d.Cpad); }
