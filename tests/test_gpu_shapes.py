@@ -63,29 +63,43 @@ def test_assignment_at_every_share_of_a_centroid_slice(tiles, n):
             assert np.all(obj[np.arange(n), a] - best <= 4.0 * (D + 3) * 2.0 ** -24 * mag)
 
 
-@pytest.mark.parametrize("U,n,C,s,lump", [
-    # ranges of the sort and what they are read by (L tokens per range, R ranges per unit)
-    (1, 1, 1, 16, 0),            # one token
-    (2, 1023, 7, 16, 0), (2, 1024, 7, 16, 0), (2, 1025, 7, 64, 0),    # around one range
-    (60, 9000, 40, 32, 0),       # R 3, picked per member; L 4096, the longest that ranks in four groups
-    (1, 8000, 100, 16, 0),       # R 8, the most that are picked
-    (2, 256, 1, 16, 9), (2, 257, 1, 16, 9), (2, 1024, 1, 16, 9),      # transformed: one wave adds the coordinates, four of them do
-    (3, 2500, 4, 16, 600),       # ... in two chunks, picked
-    (1, 40000, 200, 16, 0),      # R 40, most clusters listed in LDS
-    (1, 12000, 300, 16, 600),    # R 12, 600 tokens in a row of one cluster: a piece longer than the list takes, searched
-    (1, 66000, 900, 16, 0),      # R 33, two centroid slices
-    (1, 270000, 64, 64, 5000),   # L 8192, lane masks; clusters longer than the list
-    (1, 70000, 8192, 16, 0),     # L 2048 in four segments, no lane masks
-    (1, 530000, 8192, 16, 0),    # R 65, more than one wave holds; L 8192, the longest of four segments
-    (1, 9000, 8192, 16, 0),      # four segments, one token per cluster or none
-    (300, 1100, 24, 16, 0),      # more units than CUs: R 1
-    (260, 4100, 40, 16, 0),      # R 1, L 8192
-    (1, 1050000, 64, 64, 0),     # L 32768, the longest
+@pytest.mark.parametrize("U,n,C,s,lump,fused,R,L", [
+    # fused: the assignment sorts its own runs; ranges R of L tokens and what the members are read by; lump: tokens in a row of
+    # one cluster (and the transformed keys, whose extra coordinate is summed over the same members)
+    (1, 1, 1, 16, 0, 1, 1, 256),             # one token
+    (2, 256, 1, 16, 9, 1, 1, 256), (2, 257, 1, 16, 9, 1, 2, 256), (2, 1024, 1, 16, 9, 1, 4, 256),  # one wave adds the coordinates, four of them do
+    (2, 1023, 7, 16, 0, 1, 4, 256), (2, 1024, 7, 16, 0, 1, 4, 256), (2, 1025, 7, 64, 0, 1, 5, 256),
+    (1, 2048, 100, 16, 0, 1, 8, 256),        # the most pieces that are picked per member
+    (1, 2049, 100, 16, 0, 1, 9, 256),        # ... and the first that are listed in LDS
+    (60, 9000, 40, 32, 0, 1, 4, 2304),       # nine tiles per run
+    (32, 32768, 40, 16, 0, 1, 8, 4096),      # sixteen, the longest
+    (3, 2500, 4, 16, 600, 1, 10, 256),       # more members than are listed: searched
+    (1, 8000, 100, 16, 0, 1, 32, 256),
+    (1, 12000, 300, 16, 600, 1, 47, 256),    # a cluster longer than the list beside listed ones
+    (1, 16384, 40, 16, 900, 1, 64, 256),     # the most pieces that a wave holds
+    (1, 16640, 100, 16, 900, 1, 65, 256),    # ... and one more
+    (1, 20000, 60, 64, 5000, 1, 79, 256),
+    (1, 32768, 100, 16, 3000, 1, 128, 256),  # the most ranges
+    (1, 32768, 16, 16, 600, 0, 32, 1024),    # as many tokens, clusters too large for so many
+    (2, 1000, 600, 16, 0, 0, 1, 1024), (2, 1024, 600, 16, 0, 0, 1, 1024), (2, 1025, 600, 64, 0, 0, 2, 1024),  # a sort by itself around one range
+    (1, 8192, 600, 16, 0, 0, 8, 1024), (1, 8193, 600, 16, 0, 0, 9, 1024),  # ... picked, listed
+    (60, 9000, 600, 32, 0, 0, 3, 4096),      # the longest range that ranks in four groups
+    (1, 40000, 200, 16, 0, 0, 40, 1024),     # most clusters listed in LDS
+    (1, 66000, 900, 16, 0, 0, 33, 2048),     # two centroid slices
+    (1, 270000, 64, 64, 5000, 0, 33, 8192),  # lane masks; clusters longer than the list
+    (1, 70000, 8192, 16, 0, 0, 35, 2048),    # four segments, no lane masks
+    (1, 530000, 8192, 16, 0, 0, 65, 8192),   # more than one wave holds; the longest of four segments
+    (1, 9000, 8192, 16, 0, 0, 9, 1024),      # four segments, one token per cluster or none
+    (300, 1100, 24, 16, 0, 0, 1, 2048),      # more units than CUs
+    (260, 4100, 40, 16, 0, 0, 1, 8192),
+    (1, 1050000, 64, 64, 0, 0, 33, 32768),   # the longest
 ])
-def test_pages_hold_the_members_in_ascending_position(U, n, C, s, lump):
+def test_pages_hold_the_members_in_ascending_position(U, n, C, s, lump, fused, R, L):
     """The page layout is the stable sort of the assignment, whatever the sort's ranges and segments are, and the
     means are the members' means."""
-    from paper_2604_10539_amd import IceIndex
+    from paper_2604_10539_amd import IceIndex, ice_debug_build_plan, make_config
+    plan = ice_debug_build_plan(make_config(1, U, 4, n), n, C)
+    assert (plan["fused"], plan["ranges"], plan["range_len"]) == (fused, R, L)
     w = datagen.small(n_tokens=min(n, 300000), n_clusters=C, n_kv_heads=U, n_components=max(2, C // 3))
     K, V = datagen.keys_values(w)
     if n > 300000:  # (rows of a shorter draw, in another order)
