@@ -317,7 +317,7 @@ __global__ __launch_bounds__(kInsertWaves * 64) void insert_one_kernel(const bf1
 // More tokens than the tables hold (`per`: 16, fewer when the clusters are many) are taken in rounds by the same
 // workgroup: bound by the steps' latencies, a round saves the launch, the start of 16 waves and the argument loads of
 // a launch per 16 tokens (32 units, 128 clusters, 200 tokens: 163 us in 13 launches, 127 in one).  Where LDS holds a second D
-// (up to about 440 clusters) the scan of the next round runs beside the settling, which needs two of the 16 waves: its rows are
+// (up to 448 clusters) the scan of the next round runs beside the settling, which needs two of the 16 waves: its rows are
 // requested in front of the guess, and the columns of the rows that this round moves are worked out again from `lrow` (the
 // same instruction sequence, so the same bits).  9.7 -> 8.4 us per round; what is left of a round: guess 3.2 (about half of it on the vector unit),
 // settle with its barriers 1.6, commit and append 1.2, stores and the way back 1.4.
