@@ -22,28 +22,44 @@ __device__ inline float dot8(const uint4 &a, const uint4 &b) {
 }
 
 // The places of the n winners (composites with ~id in the low word, LDS) in ascending id order: put(place, winner) on one lane
-// each.  Wave `part` of `parts` takes winners part, part + parts, ...; one ballot over 64 winners at a time counts the lower
-// ids.  (By one thread per winner, each reading all of them: 64 winners 3 us on the first wave, 16 one.)
+// each, by waves `part` of `parts`.  A wave keeps up to kPlaceBlocks * 64 winners' ids on its lanes and takes winners part,
+// part + parts, ...: one comparison and one count of its lane mask per 64 ids.  Longer lists by one thread per winner that
+// reads them all from LDS.  8 units x 32768 tokens, a whole step, us, so, by one thread per winner, and with the blocks read from LDS
+// for every winner: 128 pages 23.2, 29.3, 24.8; 256 23.7, 26.3, 30.2; 300 26.7, 27.8, 34.1; 1000 50.4, 51.5, 143 (in the second
+// column other parts of the step were slower too).
+constexpr int kPlaceBlocks = 4;
+template <int NB, typename Put>
+__device__ inline void place_by_id_blocks(const u64 *win, int n, int part, int parts, int lane, Put put) {
+    uint32_t lo[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) lo[b] = 64 * b + lane < n ? (uint32_t)win[64 * b + lane] : 0u;  // (no id is as high as ~0)
+    for (int t0 = part; t0 < n; t0 += 64 * parts) {  // (64 of the wave's winners at a time, one per lane)
+        const u64 w = win[min(t0 + lane * parts, n - 1)];
+        int place = 0;
+        const int cnt = min(64, (n - t0 + parts - 1) / parts);
+        for (int x = 0; x < cnt; ++x) {
+            const uint32_t mine = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)w, x);
+            int pos = 0;
+#pragma unroll
+            for (int b = 0; b < NB; ++b) pos += (int)__popcll(__ballot(lo[b] > mine));
+            place = lane == x ? pos : place;
+        }
+        if (lane < cnt) put(place, w);
+    }
+}
 template <typename Put>
 __device__ inline void place_by_id(const u64 *win, int n, int part, int parts, int lane, Put put) {
-    if (n <= 64) {  // all of them side by side on the lanes
-        const u64 w = win[min(lane, max(n - 1, 0))];
-        const uint32_t lo = (uint32_t)w, hi = (uint32_t)(w >> 32);
-        for (int t = part; t < n; t += parts) {  // (t is the same for the whole wave)
-            const uint32_t mine = (uint32_t)__builtin_amdgcn_readlane((int)lo, t), score = (uint32_t)__builtin_amdgcn_readlane((int)hi, t);
-            const int pos = (int)__popcll(__ballot(lane < n && lo > mine));
-            if (lane == 0) put(pos, ((u64)score << 32) | mine);
+    if (n <= 64) {
+        place_by_id_blocks<1>(win, n, part, parts, lane, put);
+    } else if (n <= 64 * kPlaceBlocks) {
+        place_by_id_blocks<kPlaceBlocks>(win, n, part, parts, lane, put);
+    } else {
+        for (int t = part * 64 + lane; t < n; t += parts * 64) {
+            const u64 mine = win[t];
+            int pos = 0;
+            for (int j = 0; j < n; ++j) pos += (uint32_t)win[j] > (uint32_t)mine ? 1 : 0;
+            put(pos, mine);
         }
-        return;
-    }
-    for (int t = part; t < n; t += parts) {
-        const u64 mine = win[t];  // (the same word on every lane)
-        int pos = 0;
-        for (int j0 = 0; j0 < n; j0 += 64) {
-            const int j = j0 + lane;
-            pos += (int)__popcll(__ballot(j < n && (uint32_t)win[min(j, n - 1)] > (uint32_t)mine));
-        }
-        if (lane == 0) put(pos, mine);
     }
 }
 

@@ -623,7 +623,7 @@ def test_pages_of_one_cluster_side_by_side_at_every_budget(U, G):
     qf = widen(q[0]).astype(np.float64).reshape(U, G, D)
     qf /= np.linalg.norm(qf, axis=2, keepdims=True)
     units = range(U) if U < 256 else (0, 1, 100, 255)
-    for P in (1, 2, 16, 17, 31, 32, 33, 63, 64, 65, 127, 128, 129, 200, int(npg.min()) - 1):
+    for P in (1, 2, 16, 17, 31, 32, 33, 63, 64, 65, 127, 128, 129, 200, 256, 257, int(npg.min()) - 1):
         if P < 1 or P >= npg.min():
             continue
         ids, n_sel, out = (down(x) for x in ix.select_attend(up(q), P * s))
@@ -634,6 +634,14 @@ def test_pages_of_one_cluster_side_by_side_at_every_budget(U, G):
             kth = np.sort(sc)[::-1][P - 1]
             # fp32 scores of unit-length rows: chains of 128 additions on values of at most a few units
             assert np.all(sc[got] >= kth - 1e-5 * max(1.0, abs(kth))), (P, u)
+        if P in (2, 64, 65, 129, 256, 257):  # (the scores beside their ids, and the staged selection when it keeps every cluster)
+            ids2, n2, scores = (down(x) for x in ix.select(up(q), P * s))
+            ids3, n3, scores3 = (down(x) for x in ix.select_hier(up(q), P * s, C, attend=False)[:3])
+            for i, k, x in ((ids2, n2, scores), (ids3, n3, scores3)):
+                assert np.array_equal(i, ids) and np.array_equal(k, n_sel)
+                for u in units:
+                    sc = (rep[u, :npg[u]] @ qf[u].T).max(1)
+                    assert np.all(np.abs(x[0, u] - sc[i[0, u]]) <= 1e-5 * np.maximum(1.0, np.abs(sc[i[0, u]])))
     for probe in (1, 31, C - 1):
         ids, n_sel, _, cl, _ = ix.select_hier(up(q), 64, probe)
         cl = down(cl)[0]
