@@ -316,7 +316,7 @@ __global__ __launch_bounds__(kInsertWaves * 64) void insert_one_kernel(const bf1
 // after the other (about 3 us each on one wave).
 // More tokens than the tables hold (`per`: 16, fewer when the clusters are many) are taken in rounds by the same
 // workgroup: bound by the steps' latencies, a round saves the launch, the start of 16 waves and the argument loads of
-// a launch per 16 tokens (32 units, 128 clusters, 200 tokens: 163 us in 13 launches, 127 in one).  Where LDS holds a second D
+// a launch per 16 tokens (32 units, 128 clusters, 200 tokens: 163 us in 13 launches, 127 in one).  In long calls whose second D fits LDS
 // (up to 448 clusters) the scan of the next round runs beside the settling, which needs two of the 16 waves: its rows are
 // requested in front of the guess, and the columns of the rows that this round moves are worked out again from `lrow` (the
 // same instruction sequence, so the same bits).  9.7 -> 8.4 us per round; what is left of a round: guess 3.2 (about half of it on the vector unit),
@@ -853,8 +853,12 @@ void launch_insert(const Dev &d, const bf16_t *k, const bf16_t *v, int m, int cu
         return;
     }
     const int per = std::min(cap, m);
-    // the next round's scores worked out during this one's settling, where there is a next round and a second table fits
-    const bool ahead = m > per && fixed + 2 * per * row + stage1 <= budget;
+    // The next round's scores worked out during this one's settling, where a second table fits and it pays: it costs about 1.5 us
+    // a call (the first round fetches for two) and saves 0.1 us a round at 64 clusters, 0.33 at 128, 0.6 at 256, 0.9 at 440.  us
+    // without and with it: 128 clusters 32 tokens 21.6 and 23.0, 80 52.0 and 52.0, 112 67.5 and 66.7, 200 119 and 115; 256 clusters 48
+    // tokens 34.5 and 35.0, 64 39.7 and 39.3, 200 117 and 110; 440 clusters 32 tokens 22.1 and 22.7, 48 32.3 and 32.2, 200 121 and 111;
+    // 64 clusters 200 tokens 134 and 133; 32 clusters 400 tokens 325 and 326.
+    const bool ahead = d.C >= 64 && (long long)((m + per - 1) / per - 1) * d.C >= 640 && fixed + 2 * per * row + stage1 <= budget;
     const size_t tables = (ahead ? 2 : 1) * per * row;
     const int stage_tiles = fixed + tables + 2 * stage1 <= budget ? 2 : 1;
     const size_t lds = fixed + tables + stage_tiles * stage1;

@@ -653,9 +653,11 @@ def test_pages_of_one_cluster_side_by_side_at_every_budget(U, G):
 
 
 @pytest.mark.parametrize("m,C,s,tk", [(18, 16, 16, 0), (40, 17, 16, 1), (50, 430, 16, 1), (50, 470, 16, 0), (48, 225, 32, 0),
+                                       (64, 225, 32, 0), (180, 64, 16, 0), (200, 64, 16, 1), (200, 63, 16, 0),
                                        (50, 448, 16, 0), (70, 448, 16, 1), (50, 449, 16, 0), (70, 449, 16, 1)])
 def test_insertions_scored_a_round_ahead_equal_single_ones(m, C, s, tk):
-    """Where LDS holds a second table of scores, a round's scores come from the round before, put right for the rows it moved:
-    one tile of centroids, fewer tiles than scanning waves and more, the largest count that fits (448 clusters; transformed keys fill
-    LDS to its last byte with it) and the first that does not, four and five rounds of them."""
+    """In long calls, where LDS holds a second table of scores, a round's scores come from the round before, put right for the
+    rows it moved: fewer tiles of centroids than scanning waves and more, calls on both sides of the lengths from which it is
+    done, the largest count that fits (448 clusters; transformed keys fill LDS to its last byte with it) and the first that
+    does not, four and five rounds of them."""
     test_insertions_in_rounds_equal_single_ones(m, C, s, tk)
