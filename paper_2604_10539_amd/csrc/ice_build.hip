@@ -676,7 +676,9 @@ __device__ __forceinline__ bool assign_slice(const Dev &d, const bf16_t *__restr
     };
     auto store_aug = [&](int buf) {
         if constexpr (AUG) {
-            if (tid < kAssignTile) *(uint32_t *)&kext[(buf * kAssignTile + tid) * 2] = stage_aug;  // (the other 28 bytes stay zero)
+            // (the thread worked out again: kept in scratch memory, where registers end, it is waited for in front of the barrier)
+            const int t = thread_of(__builtin_amdgcn_readfirstlane(wave));
+            if (t < kAssignTile) *(uint32_t *)&kext[(buf * kAssignTile + t) * 2] = stage_aug;  // (the other 28 bytes stay zero)
         }
     };
     // rows past the end of the range are never written back: they may hold any valid key

@@ -58,6 +58,21 @@ def test_the_assignment_keeps_its_operands_in_registers(kernels):
         assert not any(x.startswith("scratch_") for x in code), name
 
 
+def test_a_later_rounds_assignment_keeps_its_operands_in_registers(kernels):
+    """... and the form of a build's later rounds, which holds every form of a few centroids and the full one: nothing goes
+    through scratch memory on raw keys.  On transformed keys, whose operands leave no register, a few addresses do, never
+    while direct loads are on their way, which such an access would wait for."""
+    later = {k: v for k, v in kernels.items() if "15reassign_kernelI" in k}
+    assert len(later) == 4  # (transformed or not; slices that are full or not)
+    for name, code in later.items():
+        scratch = [i for i, x in enumerate(code) if x.startswith("scratch_")]
+        assert len(scratch) <= (0 if "kernelILb0E" in name else 12), name
+        for i in scratch:
+            loads = [j for j in range(i) if "global_load_lds" in code[j]]
+            waits = [j for j in range(i) if code[j].startswith("s_waitcnt") and "vmcnt(0)" in code[j]]
+            assert not loads or waits[-1] > loads[-1], (name, i)
+
+
 def test_an_import_copies_through_registers(kernels):
     code = next(v for k, v in kernels.items() if "import_kernel" in k)
     assert not any(x.startswith("scratch_") for x in code)
