@@ -884,7 +884,7 @@ struct RoundPlan {
 // are listed (of 32768 keys and 512 clusters 0.34 to 0.5 of them in the benchmark's mixture, 0.4 to 0.55 without structure).
 __device__ inline bool takes_all(const RoundPlan &p, int moved, int keys, int n) {
     const int S = (moved + 511) / 512, own = 16 * (S - 1) + 4 * ((moved - 512 * (S - 1) + 127) / 128);
-    // (whole numbers, 2 n times: every workgroup of the round's launches comes to the same)
+    // (whole numbers, 2 n times: every workgroup of the unit comes to the same)
     return (long long)(p.run * own + 16 * S + p.fixed) * 2 * n + (long long)keys * p.per_key >= p.limit;
 }
 
@@ -900,7 +900,7 @@ __device__ inline uint32_t moved_of_16(const uint32_t *moved, int x, int &keys) 
     return m;
 }
 
-// Slices of at most 512 centroids (blockIdx.y) that meet through an atomic maximum in `packed`.
+// Slices of at most 512 centroids that meet through an atomic maximum in `packed`.
 int assign_slices(const Dev &d) { return (d.Cpad + 511) / 512; }
 
 // Key tiles per workgroup: the run for which the chip's rounds of 256 workgroups, each its tiles plus a prologue worth
@@ -920,7 +920,6 @@ static int assign_run(int U, int n, int slices) {
     return run;
 }
 
-// (with several slices the winners start from zero)
 // whether a centroid of the unit moved in the round before round t: element 2 u of the result (all units go in the first round)
 static const int *round_goes(const Dev &d, int t) { return t > 0 ? d.any_moved + ((t - 1) & 1) : nullptr; }
 

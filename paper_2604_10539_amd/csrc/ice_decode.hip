@@ -996,11 +996,12 @@ SplitPlan attend_shares(const Dev &d, int P, int n_rows, int min_shares) {
     SplitPlan p;
     // Pages alone: less than min_shares workgroups' worth, counted NW to a workgroup, is not split.  With a dense run
     // beside them the work splits from 48 blocks on while there are at most 32 units (a page of 64 tokens counted as three
-    // blocks: it is seldom full).  Fused steps, us in one workgroup per unit and split: 8 units x (16 + 32) blocks 18.95
-    // and 17.5, 8 x (64 + 32) 36.8 and 30.5, 16 x (32 + 16) 24.4 and 24.1, 32 x (32 + 32) 27.8 and 25.8; eight heads a
-    // group 4 x (16 + 32) 19.1 and 18.2, 8 x (92 + 19) 31.5 and 25.3; pages of 64 tokens 8 x (16 pages + 32) 23.2 and
-    // 19.05, 32 x (8 pages + 32) 20.3 and 19.5; but 8 x (16 + 13) 16.9 and 17.1, 8 x (8 pages of 64 + 16) 17.4 and 17.8,
-    // 64 x (16 + 32) 24.4 and 25.7.
+    // blocks: it is seldom full).  Fused steps, us in one workgroup per unit and split: 8 units x (16 + 32) blocks 17.9
+    // and 16.3, 8 x (64 + 32) 25.9 and 18.9, 16 x (32 + 16) 19.9 and 19.2, 32 x (32 + 32) 20.9 and 18.8; eight heads a
+    // group 4 x (16 + 32) 17.7 and 17.8, 8 x (92 + 19) 32.2 and 26.9; pages of 64 tokens 8 x (16 pages + 32) 22.1 and
+    // 17.8, 32 x (8 pages + 32) 19.2 and 18.6; but 8 x (16 + 13) 15.9 and 16.1, 8 x (8 pages of 64 + 16) 16.0 and 16.5,
+    // 64 x (16 + 32) 19.8 and 20.9.  (Splitting pays a little below the line, 8 x (16 + 28) 17.3 and 16.4, 8 x (8 + 32) 16.6 and
+    // 16.0, and above 32 units where the blocks are many, 64 x (64 + 32) 31.8 and 28.0.)
     const int blocks = (n_rows + 15) / 16;
     const long long items = (long long)P * (d.s / 16) + blocks;
     if (blocks > 0 && (d.U > kRowsSplitMaxUnits || (long long)P * (d.s == 64 ? 3 : d.s / 16) + blocks < kRowsSplitMinBlocks)) return p;
@@ -1019,9 +1020,10 @@ SplitPlan attend_shares(const Dev &d, int P, int n_rows, int min_shares) {
 }
 
 // Whether the attention over P pages fetches the pages' fills first (FILLS of attend_pages) in the flat step and by
-// itself: with at least half the chip's CUs busy and several pages per wave it is bound by its bytes (256 units x 64 pages of 16 slots,
-// fused step: 49.4 us without, 47.3 with); with few units by its round trips (8 units x 32 pages: 20.1
-// without, 20.6 with).
+// itself: with at least half the chip's CUs busy and several pages per wave it is bound by its bytes (fused steps without and with,
+// us: 256 units x 64 pages of 16 slots 45.1 and 41.8, x 40 35.3 and 33.5, 128 x 40 23.7 and 22.6, eight query heads 312 x 21 pages
+// of 32 34.3 and 33.3); with few units by its round trips (8 units x 32 pages 15.9 and 15.9).  (Not on that side of the line, though
+// it is the better form there too: 256 x 32 31.7 and 29.9, 64 x 40 19.3 and 18.6.)
 static bool attend_by_fills(const Dev &d, int P) { return d.U >= 128 && P > 2 * (d.G == 8 ? 8 : 16); }
 
 // the token positions of the listed pages, in list and slot order, padded with -1

@@ -581,9 +581,9 @@ void launch_decode_hier(const Dev &d, const bf16_t *q, int cur, int P, int n_top
     // keys have come back; in the form that fetches the fills first all eight pieces of a block are under way at once, also
     // where every wave has one page and no row is spared.  That is worth more here than the extra wait for the fills from
     // 24 units on (the flat step draws its line elsewhere: attend_by_fills).  us per call, general and fills first: 256
-    // units x 16 pages 27.3 and 26.7, 128 x 16 24.4 and 23.8, 128 x 48 34.2 and 31.5, 64 x 16 23.5 and 23.1, 32 x 32 26.5
-    // and 25.9, 24 x 16 22.8 and 22.7; but 16 x 16 22.4 and 22.45, 8 x 16 22.2 and 22.35; eight query heads (eight waves
-    // with twice the registers) the same with either, 128 x 16 24.9 and 25.0.
+    // units x 16 pages 21.4 and 21.4, 128 x 16 18.7 and 18.6, 128 x 48 27.4 and 25.8, 64 x 16 18.3 and 18.3, 32 x 32 20.6
+    // and 20.3, 24 x 16 17.7 and 17.8, 24 x 32 20.6 and 20.2; 16 x 16 17.6 and 17.8, 16 x 32 20.4 and 20.0, 8 x 16 17.0 and 17.3, 8 x 32
+    // 19.9 and 19.7; eight query heads (eight waves with twice the registers) the same with either.
     const bool fills = d.U >= 24 && d.G < 8;
 #define ICE_HIER_T(g, nw, e, top, fills)                                                                             \
     do {                                                                                                             \
