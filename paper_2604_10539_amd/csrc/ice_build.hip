@@ -1352,14 +1352,14 @@ static RoundPlan round_plan(const Dev &d, int n) {
 }
 
 // Rounds by reassign_kernel instead of assign_kernel: from the third on (the first means move nearly all centroids), above
-// 256 clusters (eight tiles or fewer are contracted in the time that their keys take to come in) and
-// where the whole contraction is at least four tiles of 256 keys x 512 centroids per workgroup.  A unit that takes all of
-// it pays 0.7 us for finding that out; from four tiles on that is below 2 %, and what keys that settle gain is many times that.
-// Builds of ten rounds, us, without and with it, keys that settle (the benchmark's mixture) and keys without structure:
-// 8 units x 32768 x 512 (four tiles) 556 and 510, 638 and 640; transformed 632 and 581, 718 and 718; 4 x 65536 x 1024 (eight)
-// 836 and 691, 992 and 1000; 8 x 131072 x 2048 (64) 5200 and 3130, 5390 and 5390.  Below the line, with it all the same: 8 x 24576 x
-// 512 (three tiles) 407 and 374, 507 and 508; 4 x 32768 x 512 (two) 340 and 327, 406 and 411; 1 x 16384 x 1024 (one) 168.2 and
-// 168.7, 246 and 250.
+// 256 clusters and where the whole contraction is at least four tiles of 256 keys x 512 centroids per workgroup.  A unit that
+// takes all of it pays about 0.6 us for finding that out, from four tiles on 1 %; keys that settle gain many times that.  Builds of ten
+// rounds, us, without and with it, for keys that settle (the benchmark's mixture) and keys without structure: 8 units x 32768 x 512
+// (four tiles) 528 and 485, 604 and 609, transformed 601 and 553, 679 and 684; 2 x 32768 x 2048 (four) 313 and 308, 511 and 519;
+// 4 x 65536 x 1024 (eight) 819 and 674, 897 and 904; 8 x 131072 x 2048 (64) 4930 and 2969, 5257 and 5268.  Below the line 8 x 24576 x
+// 512 (three) 380 and 354, 475 and 485; 4 x 32768 x 512 (two) 317 and 312, 384 and 391; 1 x 16384 x 1024 (one) 163 and 165, 242 and 248.
+// (Eight tiles of centroids or fewer are contracted in about the time that their keys take to come in: with 256 clusters
+// 64 x 32768 2417 and 2440, 8 x 131072 1356 and 1415, 1564 and 1603, though 128 x 16384 2346 and 2270.)
 bool reassign_pays(const Dev &d, int n) {
     if (d.Cpad <= 256) return false;
     const RoundPlan p = round_plan(d, n);
