@@ -49,9 +49,15 @@ __device__ inline void place_by_id_blocks(const u64 *win, int n, int part, int p
 }
 template <typename Put>
 __device__ inline void place_by_id(const u64 *win, int n, int part, int parts, int lane, Put put) {
-    if (n <= 64) {
-        place_by_id_blocks<1>(win, n, part, parts, lane, put);
-    } else if (n <= 64 * kPlaceBlocks) {
+    if (__builtin_expect(n <= 64, 1)) {  // (all of them side by side on the lanes: one trip to LDS)
+        const u64 w = win[min(lane, max(n - 1, 0))];
+        const uint32_t lo = (uint32_t)w, hi = (uint32_t)(w >> 32);
+        for (int t = part; t < n; t += parts) {  // (t is the same for the whole wave)
+            const uint32_t mine = (uint32_t)__builtin_amdgcn_readlane((int)lo, t), score = (uint32_t)__builtin_amdgcn_readlane((int)hi, t);
+            const int pos = (int)__popcll(__ballot(lane < n && lo > mine));
+            if (lane == 0) put(pos, ((u64)score << 32) | mine);
+        }
+    } else if (__builtin_expect(n <= 64 * kPlaceBlocks, 1)) {
         place_by_id_blocks<kPlaceBlocks>(win, n, part, parts, lane, put);
     } else {
         for (int t = part * 64 + lane; t < n; t += parts * 64) {
