@@ -537,6 +537,7 @@ def test_later_rounds_do_again_what_changed_and_leave_what_all_of_it_would(U, n,
     (8, 34000, 400, 0, "none", 1, 5, 1),
     (16, 9000, 700, 1, "odd", 2, 3, 0),    # equal keys, and units of which some keys are not finite beside units of which all are
     (8, 32768, 512, 0, "odd", 1, 4, 1),
+    (8, 32768, 512, 1, "odd", 1, 4, 1),
 ])
 def test_later_rounds_that_score_what_moved_leave_what_all_centroids_would(U, n, C, tk, odd, slices, run, fused):
     """The same where later rounds score only the centroids that moved and then the keys that lost theirs: from the third
@@ -557,7 +558,8 @@ def test_later_rounds_that_score_what_moved_leave_what_all_centroids_would(U, n,
     if odd == "odd":
         K[0, :, 100:400] = K[0, :, 100:101]
         for i, t in enumerate(range(5, n, 211)):
-            K[0, ::2, t, i % D:] = [0x7FC0, 0x7F80, 0xFF80 - 65536, 0xFFC0 - 65536][i % 4]  # NaN, inf, -inf, -NaN
+            # NaN, inf, -inf, -NaN, 2^64, -2^64 (whose products overflow)
+            K[0, ::2, t, i % D:] = [0x7FC0, 0x7F80, 0xFF80 - 65536, 0xFFC0 - 65536, 0x5F80, 0xDF80 - 65536][i % 6]
     V = torch.randint(-16000, 16000, K.shape, generator=gen, device="cuda", dtype=torch.int16)
     init = torch.stack([torch.sort(torch.randperm(n, generator=gen, device="cuda")[:C])[0] for _ in range(U)]).int()[None].contiguous()
     for T in (3, 4, 5, 6, 8, 12):
