@@ -24,7 +24,7 @@ PROF_LIB = os.path.join(PROF_DIR, "libicecache_prof.so")
 
 # stamp index -> what has happened when it is taken (decode_step_kernel)
 DECODE = [(0, "wave started"), (14, "own chunk scored"), (2, "last workgroup holds every score of the unit"),
-          (3, "threshold known"), (4, "candidates listed"), (5, "pages ranked, ids written"), (6, "attention: tiles requested"),
+          (3, "threshold known"), (4, "candidates listed"), (5, "pages ranked"), (6, "attention: tiles requested"),
           (7, "output written")]
 INSERT_ONE = [(40, "wave started"), (41, "first barrier (LDS only)"), (45, "tiles in LDS"), (46, "dot products done"),
               (47, "wave's best row known"), (42, "state of that row requested"), (43, "waves have met"),
