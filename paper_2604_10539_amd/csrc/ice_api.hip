@@ -247,9 +247,10 @@ ice_status_t ice_build_index(ice_index_t *ix, const void *K, const void *V, int3
     if (d.tk) launch_key_aug(d, Kb, n, s);
     launch_init_centroids(d, Kb, n, ix->cfg.init_idx, ix->cfg.seed, cur, s);
     const bool fused = sort_is_fused(d, n);
-    const bool later = ix->cfg.kmeans_iters > 2 && reassign_pays(d, n);
+    const bool near = ix->cfg.kmeans_iters > 1 && near_pays(d, n), later = near || (ix->cfg.kmeans_iters > 2 && reassign_pays(d, n));
     for (int t = 0; t < ix->cfg.kmeans_iters; ++t) {
-        if (later && t >= 2 && t % kRoundNumbers != 0) launch_reassign(d, Kb, n, cur, t, fused, s);
+        if (near && t >= 1 && t % kRoundNumbers != 0) launch_near(d, Kb, n, cur, t, fused, s);
+        else if (later && t >= 2 && t % kRoundNumbers != 0) launch_reassign(d, Kb, n, cur, t, fused, s);
         else launch_assign(d, Kb, n, cur, t, fused, later && t == 0, s);
         if (!fused) launch_sort(d, n, t, nullptr, nullptr, s);
         launch_means(d, Kb, n, cur, t, t + 1 == ix->cfg.kmeans_iters, s);

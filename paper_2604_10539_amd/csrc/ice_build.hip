@@ -103,6 +103,10 @@ void launch_key_aug(const Dev &d, const bf16_t *K, int n, hipStream_t st) {
     hipLaunchKernelGGL(key_aug_kernel, dim3((n + 255) / 256, d.U), dim3(256), 0, st, d, n, n2, part);
 }
 
+// A build's scratch at the start of a unit's key tiles, which the page layout overwrites in any case (see Near)
+constexpr int kNearHead = 6;
+__device__ inline char *near_scratch(const Dev &d, int u) { return (char *)(d.Kp + (size_t)u * d.max_pages * d.s * kD); }
+
 // ------------------------------------------------------------------------------------------------
 // Initial centroids = the promoted keys (Alg. 2, "random promotion" with an exact count): cluster c
 // of unit u starts at key init_idx[u][c], or, without a list, at a hashed position inside the c-th
@@ -115,6 +119,7 @@ __global__ __launch_bounds__(64) void init_centroids_kernel(Dev d, const bf16_t 
     uint32_t *cb1 = (uint32_t *)(d.cent_bf16[cur ^ 1] + ((size_t)u * d.Cpad + c) * kD);
     if (lane == 0) d.moved[(size_t)u * d.Cpad + c] = d.touched[(size_t)u * d.Cpad + c] = 0;
     if (c == 0 && lane == 0 && !d.tk) d.large_keys[u] = 0;  // (transformed keys: set already)
+    if (c == 0 && lane < kNearHead) ((int *)near_scratch(d, u))[lane] = 0;
     if (c >= d.C) {
         cb0[lane] = 0u;
         cb1[lane] = 0u;
@@ -895,7 +900,7 @@ __device__ inline uint32_t moved_of_16(const uint32_t *moved, int x, int &keys) 
     for (int i = 0; i < 4; ++i) {
         const uint4 w = ((const uint4 *)moved)[4 * x + i];
         m |= ((w.x & 1u) | (w.y & 1u) << 1 | (w.z & 1u) << 2 | (w.w & 1u) << 3) << (4 * i);
-        keys += (int)((w.x >> 1) + (w.y >> 1) + (w.z >> 1) + (w.w >> 1));
+        keys += (int)((w.x & 1u) * (w.x >> 1) + (w.y & 1u) * (w.y >> 1) + (w.z & 1u) * (w.z >> 1) + (w.w & 1u) * (w.w >> 1));
     }
     return m;
 }
@@ -994,11 +999,284 @@ __host__ __device__ inline int reassign_lds_bytes(bool aug, int Cpad) {
 }
 __device__ inline bool ordered_is_nan(uint32_t k) { return k > 0xFF800000u || k < 0x007FFFFFu; }
 
+// One slice of at most 512 of a job's centroids (places c0 .. of its list) against its keys, by a workgroup of 8 waves: CW waves share
+// the centroids of a key, the others split a key tile.  The job says which keys (nk of them: key_of(place), rows_of(tile, rows): a
+// thread's eight rows of a tile, 32 apart) and which centroids (ncent, centroid(place)), what is loaded ahead of a tile's
+// contraction (ahead) and counts as arrived behind it (arrived), and takes the winners: take(place, best, c0, lane), where
+// best = ordered score << 32 | ~place of the centroid.
+template <bool AUG, int CW, bool FULL, typename Job>
+__device__ __forceinline__ void later_slice(const Dev &d, const bf16_t *Ku, const bf16_t *__restrict__ cent, const float *__restrict__ cnorm, int u, int Cpad,
+                                            int cur, int wave, int c0, int &tid, char *keys, u64 *best, float *seeds, uint32_t *kext, uint32_t *cext, Job &job) {
+    constexpr int KS = AUG ? 9 : 8;
+    constexpr int KW = 8 / CW, NSUB = 8 / KW, R = CW * 64;
+    auto slot = [](int r, int c) { return r * 256 + ((c ^ (r & 15)) << 4); };
+    // (worked out in every slice and tile: hoisted out of the forms and the loops, the lanes' addresses would not fit the
+    // registers, and kept in memory instead they would be waited for)
+    tid = thread_of(wave);
+    const int lane = tid & 63, col = lane & 31, half = lane >> 5;
+    constexpr int CS = FULL ? 1 : CW;  // distance between a wave's two tiles (dealt over the SIMDs as in assign_kernel)
+    const int kw = wave / CW, cw = FULL || CW == 8 ? wave % CW : (wave + (wave >> 2) * (CW / 2)) % CW;
+    const int wt0 = FULL ? cw * 2 : cw, nt = (min(512, job.ncent - c0) + 31) / 32;
+    const int ctv = wt0 >= nt ? 0 : wt0 + CS < nt ? 2 : 1;
+    const int ntiles = (job.nk + kAssignTile - 1) / kAssignTile;
+    // ---- prologue: the slice's centroid rows through LDS into the waves' operand registers (the first key tile goes
+    // through registers: the rows are staged where it belongs)
+    u32x4 first[8];
+    {
+        int key[8];
+        job.rows_of(0, tid, key);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) first[i] = ((const u32x4 *)(Ku + (size_t)key[i] * kD))[tid & 15];
+    }
+    uint4 cst[R / 32];
+#pragma unroll
+    for (int i = 0; i < R / 32; ++i) {
+        const int id = tid + 512 * i, pos = c0 + (id >> 4);
+        const uint4 w = ((const uint4 *)(cent + ((size_t)u * Cpad + job.centroid(min(pos, job.ncent - 1))) * kD))[id & 15];
+        cst[i] = pos < job.ncent ? w : make_uint4(0, 0, 0, 0);
+    }
+    float seed_in = -INFINITY;
+    uint32_t cext_in = 0u, kext_in = 0u;
+    if (tid < R && c0 + tid < job.ncent) {
+        const int c = job.centroid(c0 + tid);
+        seed_in = -0.5f * cnorm[(size_t)u * Cpad + c];
+        if constexpr (AUG) cext_in = d.caug[cur][(size_t)u * Cpad + c];
+    }
+    auto load_aug = [&](int t) {
+        if constexpr (AUG) {
+            const int pos = t * kAssignTile + tid;
+            kext_in = tid < kAssignTile && pos < job.nk ? d.kaug[(size_t)u * d.max_tokens + job.key_of(pos)] : 0u;
+        }
+    };
+    auto store_aug = [&](int buf) {
+        if constexpr (AUG) {
+            if (tid < kAssignTile) kext[buf * kAssignTile + tid] = kext_in;
+        }
+    };
+    load_aug(0);
+#pragma unroll
+    for (int i = 0; i < R / 32; ++i) {
+        const int id = tid + 512 * i;
+        *(uint4 *)(keys + slot(id >> 4, id & 15)) = cst[i];
+    }
+    if (tid < R) {
+        seeds[tid] = seed_in;
+        if constexpr (AUG) cext[tid] = cext_in;
+    }
+    __syncthreads();
+    bf16x8 A[2][KS];
+    f32x16 seed[2];
+#pragma unroll
+    for (int ct = 0; ct < 2; ++ct) {
+        const int t0 = (wt0 + ct * CS) * 32, r = t0 + col;
+#pragma unroll
+        for (int ks = 0; ks < 8; ++ks) A[ct][ks] = __builtin_bit_cast(bf16x8, *(const uint4 *)(keys + slot(r, 2 * ks + half)));
+        if constexpr (AUG) A[ct][8] = __builtin_bit_cast(bf16x8, make_uint4(half ? 0u : cext[r], 0, 0, 0));
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const float4 w = *(const float4 *)(seeds + t0 + 8 * v + 4 * half);
+            seed[ct][4 * v] = w.x; seed[ct][4 * v + 1] = w.y; seed[ct][4 * v + 2] = w.z; seed[ct][4 * v + 3] = w.w;
+        }
+    }
+    __syncthreads();  // every wave holds its fragments before the first key tile overwrites them
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const int id = tid + 512 * i;
+        *(u32x4 *)(keys + slot(id >> 4, id & 15)) = first[i];
+    }
+    store_aug(0);
+    __syncthreads();
+    uint32_t frag[8];
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) frag[ks] = (uint32_t)slot(col, 2 * ks + half);
+    const uint32_t inv0 = 0xFFFFFFFFu - (uint32_t)(c0 + wt0 * 32 + 4 * half);  // low word of a winner: ~(place in the list)
+
+    for (int t = 0; t < ntiles; ++t) {
+        const int buf = t & 1;
+        u64 *bestt = best + buf * kAssignTile;
+        tid = thread_of(wave);
+        if (t + 1 < ntiles) {
+            const int ch = tid & 15, r16 = (tid >> 4) & 15;
+            int key[8];
+            job.rows_of(t + 1, tid, key);
+            load_aug(t + 1);
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+                lds_dma16((const uint4 *)(Ku + (size_t)key[i] * kD) + (ch ^ r16), keys + (buf ^ 1) * (kAssignTile * 256) + (4 * wave + 32 * i) * 256);
+        }
+        job.ahead(t, tid, c0);
+        auto load_b = [&](int i, bf16x8 (&dst)[KS]) {
+            const char *sub = keys + buf * (kAssignTile * 256) + (kw + i * KW) * 32 * 256;
+#pragma unroll
+            for (int ks = 0; ks < 8; ++ks) dst[ks] = __builtin_bit_cast(bf16x8, *(const uint4 *)(sub + frag[ks]));
+            if constexpr (AUG) {
+                const uint32_t e = kext[buf * kAssignTile + (kw + i * KW) * 32 + col];
+                dst[8] = __builtin_bit_cast(bf16x8, make_uint4(half ? 0u : e, 0, 0, 0));
+            }
+        };
+        auto chain = [&](int ct, const bf16x8 (&b)[KS], f32x16 &dst) {
+            dst = seed[ct];
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) dst = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[ct][ks], b[ks], dst, 0, 0, 0);
+        };
+        float sv = 0.f;
+        uint32_t sidx = 0;
+        auto reduce = [&](const f32x16 &acc, int i, int ct, int ctv_of) {  // as in assign_kernel
+            float m;
+            uint32_t li;
+            argmax16(acc, m, li);
+            asm("" : "+v"(li));  // (worked out in any case: as a branch around its selects it ends the pipeline of chains)
+            if (ct == 0) {
+                sv = m;
+                sidx = li;
+            } else {
+                const bool gt = m > sv;
+                sv = gt ? m : sv;
+                sidx = gt ? li + 32u * CS * ct : sidx;
+            }
+            if (ct == ctv_of - 1)
+                atomicMax(&bestt[(kw + i * KW) * 32 + col], ((u64)f32_ordered(sv + 0.0f) << 32) | (u64)(inv0 - sidx));
+        };
+        const int subs = min(8, (job.nk - t * kAssignTile + 31) / 32);  // 32-key sub-tiles with keys
+        auto compute = [&](auto tiles_held) __attribute__((always_inline)) {
+            constexpr int CTV = decltype(tiles_held)::value, NSLOT = NSUB * CTV;
+            if (subs > 4) {  // (the software pipeline of assign_kernel)
+                bf16x8 B[2][KS];
+                f32x16 acc[2];
+                load_b(0, B[0]);
+                if (CTV == 1 && NSUB > 1) load_b(1, B[1]);
+                chain(0, B[0], acc[0]);
+#pragma unroll
+                for (int j = 0; j < NSLOT; ++j) {
+                    const int i = j / CTV, ct = j % CTV, i1 = (j + 1) / CTV;
+                    if ((j + 2) % CTV == 0 && (j + 2) / CTV < NSUB && (j + 2) / CTV >= 1 && !(CTV == 1 && j + 2 == 1))
+                        load_b((j + 2) / CTV, B[((j + 2) / CTV) & 1]);
+                    if (j + 1 < NSLOT) chain((j + 1) % CTV, B[i1 & 1], acc[(j + 1) & 1]);
+                    reduce(acc[j & 1], i, ct, CTV);
+                }
+            } else {  // a tile of few keys: no work for the empty sub-tiles
+                for (int i = 0; kw + i * KW < subs; ++i) {
+                    bf16x8 B[KS];
+                    f32x16 acc[CTV];
+                    load_b(i, B);
+#pragma unroll
+                    for (int ct = 0; ct < CTV; ++ct) chain(ct, B, acc[ct]);
+#pragma unroll
+                    for (int ct = 0; ct < CTV; ++ct) reduce(acc[ct], i, ct, CTV);
+                }
+            }
+        };
+        if (FULL || ctv == 2) compute(std::integral_constant<int, 2>{});  // (wave-uniform)
+        else if (ctv == 1) compute(std::integral_constant<int, 1>{});
+        if (t + 1 < ntiles) {
+            wait_lds_dma();
+            asm volatile("" : "+v"(kext_in));
+            store_aug(buf ^ 1);
+        }
+        // (what was requested ahead counts as arrived here for every lane: a wait left for a later place would also
+        // cover the next tile's direct loads)
+        job.arrived();
+        __syncthreads();
+        // the tile's winners, first 256 threads (a key's are the same thread's in every slice)
+        if (tid < kAssignTile) {
+            const u64 b = bestt[tid];
+            bestt[tid] = 0ull;
+            job.take(t * kAssignTile + tid, b, c0, lane);
+        }
+    }
+}
+
+// every slice of the job's centroids from place c_first on
+template <bool AUG, typename Job>
+__device__ __forceinline__ void later_slices(const Dev &d, const bf16_t *Ku, const bf16_t *__restrict__ cent, const float *__restrict__ cnorm, int u, int Cpad,
+                                             int cur, int wave, int c_first, int &tid, char *keys, u64 *best, float *seeds, uint32_t *kext, uint32_t *cext, Job &job) {
+    for (int c0 = c_first; c0 < job.ncent; c0 += 512) {
+        const int nt = (min(512, job.ncent - c0) + 31) / 32;
+#define ICE_SLICE(cw, full) later_slice<AUG, cw, full>(d, Ku, cent, cnorm, u, Cpad, cur, wave, c0, tid, keys, best, seeds, kext, cext, job)
+        if (nt <= 2) ICE_SLICE(1, false);
+        else if (nt <= 4) ICE_SLICE(2, false);
+        else if (nt <= 8) ICE_SLICE(4, false);
+        else if (nt < 16) ICE_SLICE(8, false);
+        else ICE_SLICE(8, true);
+#undef ICE_SLICE
+    }
+}
+
+// The keys and centroids of reassign_kernel's two passes
+struct ReassignJob {
+    int job, nk, ncent, k0, Cpad;
+    uint32_t round;
+    u64 *packed, *tmp;
+    uint32_t *fails;
+    const uint16_t *list, *bits;
+    int *sh_fails;
+    u64 last_word, sofar;
+    __device__ __forceinline__ int key_of(int pos) const {
+        int key = k0 + min(pos, nk - 1);
+        if (job == kListedKeys) {
+            key = (int)fails[min(pos, nk - 1)];
+            asm volatile("" : "+v"(key));  // (see rows_of)
+        }
+        return key;
+    }
+    // (The listed keys are waited for where they are loaded: left to the compiler the wait is at every use, in the other pass
+    // too, and each key row waits for the one before.)
+    __device__ __forceinline__ void rows_of(int t, int tid, int (&key)[8]) const {
+        const int base = t * kAssignTile + (tid >> 4);
+        if (job == kListedKeys) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) key[i] = (int)fails[min(base + 32 * i, nk - 1)];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(key[i]));
+        } else {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) key[i] = k0 + min(base + 32 * i, nk - 1);
+        }
+    }
+    __device__ __forceinline__ int centroid(int pos) const { return job == kMovedCentroids ? (int)list[pos] : pos; }
+    // (the last slice of the moved centroids: what the tile's keys are compared with, in flight during the contraction)
+    __device__ __forceinline__ void ahead(int t, int tid, int c0) {
+        last_word = sofar = 0ull;  // (the last round's winner as it is in memory: taken apart here it would be waited for)
+        if (job == kMovedCentroids && c0 + 512 >= ncent && tid < kAssignTile) {
+            const int key = key_of(t * kAssignTile + tid);
+            last_word = packed[key];
+            if (c0 > 0) sofar = tmp[key];
+        }
+    }
+    __device__ __forceinline__ void arrived() { asm volatile("" : "+v"(last_word), "+v"(sofar)); }
+    __device__ __forceinline__ void take(int pos, u64 b, int c0, int lane) {
+        const bool valid = pos < nk, last = c0 + 512 >= ncent;
+        bool fail = false;
+        const int key = key_of(pos);
+        if (valid && !(job == kMovedCentroids && last)) {
+            u64 *dst = (job == kMovedCentroids ? tmp : packed) + key;
+            if (job != kMovedCentroids) b = winner_word(b, round);
+            if (c0 > 0) atomicMax(dst, b);  // (nothing waits for it)
+            else *dst = b;
+        } else if (valid) {
+            const u64 old = winner_of_word(last_word);
+            b = max(b, sofar);
+            const uint32_t at = ~(uint32_t)b, own = min(~(uint32_t)old, (uint32_t)Cpad - 1u);
+            const uint32_t id = at < (uint32_t)ncent ? list[at] : 0x7FFFFFFFu;  // (a place past the list: no centroid)
+            const u64 m = (b & 0xFFFFFFFF00000000ull) | (u64)(0xFFFFFFFFu - id);
+            const bool own_moved = (bits[own >> 4] >> (own & 15u)) & 1u;
+            fail = ordered_is_nan((uint32_t)(b >> 32)) || ordered_is_nan((uint32_t)(old >> 32)) || (own_moved && m < old);
+            if (!fail && m > old) packed[key] = winner_word(m, round);
+        }
+        if (job == kMovedCentroids && last) {
+            const u64 f = __ballot(fail);
+            int at = 0;
+            if (lane == 0 && f) at = atomicAdd(sh_fails, (int)__popcll(f));
+            at = __builtin_amdgcn_readfirstlane(at);
+            if (fail) fails[at + (int)__popcll(f & ((1ull << lane) - 1ull))] = (uint32_t)key;
+        }
+    }
+};
+
 template <bool AUG, bool ALL_FULL>  // ALL_FULL: every slice of the centroids is full (FULL of assign_slice)
 __global__ __launch_bounds__(512) void reassign_kernel(const bf16_t *__restrict__ K, const bf16_t *__restrict__ cent,
                                                        const float *__restrict__ cnorm, int n, int Cpad, int cur,
                                                        const int *__restrict__ go, int round, int fused, RoundPlan plan, Dev d) {  // (scalars first: preloaded at wave start)
-    constexpr int KS = AUG ? 9 : 8;
     extern __shared__ __align__(16) char smem[];
     char *keys = smem;                                             // [2][256][256 B], chunks swizzled as in assign_slice
     u64 *best = (u64 *)(smem + 2 * kAssignTile * 256);             // [2][256]
@@ -1009,7 +1287,6 @@ __global__ __launch_bounds__(512) void reassign_kernel(const bf16_t *__restrict_
     uint16_t *bits = list + Cpad;                                  // [Cpad / 16] the same as a mask
     uint16_t *won = (uint16_t *)(smem + assign_lds_bytes(AUG));    // (all centroids, fused) the run's winners
     __shared__ int sh_wave[8], sh_keys[8], sh_fails;
-    auto slot = [](int r, int c) { return r * 256 + ((c ^ (r & 15)) << 4); };
 
     const int u = blockIdx.y;
     int tid = threadIdx.x;
@@ -1069,259 +1346,17 @@ __global__ __launch_bounds__(512) void reassign_kernel(const bf16_t *__restrict_
     u64 *tmp = (u64 *)(d.Kp + (size_t)u * d.max_pages * d.s * kD);
     uint32_t *fails = (uint32_t *)(tmp + n) + k0;
 
-    // the pass at hand: job, number of keys (and of centroids, ncent)
-    int job = kMovedCentroids, nk = min(n, k0 + keys_per_wg) - k0;
-    auto key_of = [&](int pos) -> int {
-        int key = k0 + min(pos, nk - 1);
-        if (job == kListedKeys) {
-            key = (int)fails[min(pos, nk - 1)];
-            asm volatile("" : "+v"(key));  // (see rows_of)
-        }
-        return key;
-    };
-    // this thread's rows of a key tile (eight, 32 apart).  (The listed keys are waited for where they are loaded: left to
-    // the compiler the wait is at every use, in the other passes too, and each key row waits for the one before.)
-    auto rows_of = [&](int t, int (&key)[8]) {
-        const int base = t * kAssignTile + (tid >> 4);
-        if (job == kListedKeys) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) key[i] = (int)fails[min(base + 32 * i, nk - 1)];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(key[i]));
-        } else {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) key[i] = k0 + min(base + 32 * i, nk - 1);
-        }
-    };
-
-    auto slice = [&](auto cw_arg, auto full_arg, int c0) __attribute__((always_inline)) {
-        constexpr int CW = decltype(cw_arg)::value, KW = 8 / CW, NSUB = 8 / KW, R = CW * 64;
-        constexpr bool FULL = decltype(full_arg)::value;
-        // (worked out in every slice and tile: hoisted out of the forms and the loops, the lanes' addresses would not fit the
-        // registers, and kept in memory instead they would be waited for)
-        tid = thread_of(wave);
-        const int lane = tid & 63, col = lane & 31, half = lane >> 5;
-        constexpr int CS = FULL ? 1 : CW;  // distance between a wave's two tiles (dealt over the SIMDs as in assign_kernel)
-        const int kw = wave / CW, cw = FULL || CW == 8 ? wave % CW : (wave + (wave >> 2) * (CW / 2)) % CW;
-        const int wt0 = FULL ? cw * 2 : cw, nt = (min(512, ncent - c0) + 31) / 32;
-        const int ctv = wt0 >= nt ? 0 : wt0 + CS < nt ? 2 : 1;
-        const bool last = c0 + 512 >= ncent;
-        const int ntiles = (nk + kAssignTile - 1) / kAssignTile;
-        auto centroid = [&](int pos) { return job == kMovedCentroids ? (int)list[pos] : pos; };
-        // ---- prologue: the slice's centroid rows through LDS into the waves' operand registers (the first key tile goes
-        // through registers: the rows are staged where it belongs)
-        u32x4 first[8];
-        {
-            int key[8];
-            rows_of(0, key);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) first[i] = ((const u32x4 *)(Ku + (size_t)key[i] * kD))[tid & 15];
-        }
-        uint4 cst[R / 32];
-#pragma unroll
-        for (int i = 0; i < R / 32; ++i) {
-            const int id = tid + 512 * i, pos = c0 + (id >> 4);
-            const uint4 w = ((const uint4 *)(cent + ((size_t)u * Cpad + centroid(min(pos, ncent - 1))) * kD))[id & 15];
-            cst[i] = pos < ncent ? w : make_uint4(0, 0, 0, 0);
-        }
-        float seed_in = -INFINITY;
-        uint32_t cext_in = 0u, kext_in = 0u;
-        if (tid < R && c0 + tid < ncent) {
-            const int c = centroid(c0 + tid);
-            seed_in = -0.5f * cnorm[(size_t)u * Cpad + c];
-            if constexpr (AUG) cext_in = d.caug[cur][(size_t)u * Cpad + c];
-        }
-        auto load_aug = [&](int t) {
-            if constexpr (AUG) {
-                const int pos = t * kAssignTile + tid;
-                kext_in = tid < kAssignTile && pos < nk ? d.kaug[(size_t)u * d.max_tokens + key_of(pos)] : 0u;
-            }
-        };
-        auto store_aug = [&](int buf) {
-            if constexpr (AUG) {
-                if (tid < kAssignTile) kext[buf * kAssignTile + tid] = kext_in;
-            }
-        };
-        load_aug(0);
-#pragma unroll
-        for (int i = 0; i < R / 32; ++i) {
-            const int id = tid + 512 * i;
-            *(uint4 *)(keys + slot(id >> 4, id & 15)) = cst[i];
-        }
-        if (tid < R) {
-            seeds[tid] = seed_in;
-            if constexpr (AUG) cext[tid] = cext_in;
-        }
-        __syncthreads();
-        bf16x8 A[2][KS];
-        f32x16 seed[2];
-#pragma unroll
-        for (int ct = 0; ct < 2; ++ct) {
-            const int t0 = (wt0 + ct * CS) * 32, r = t0 + col;
-#pragma unroll
-            for (int ks = 0; ks < 8; ++ks) A[ct][ks] = __builtin_bit_cast(bf16x8, *(const uint4 *)(keys + slot(r, 2 * ks + half)));
-            if constexpr (AUG) A[ct][8] = __builtin_bit_cast(bf16x8, make_uint4(half ? 0u : cext[r], 0, 0, 0));
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const float4 w = *(const float4 *)(seeds + t0 + 8 * v + 4 * half);
-                seed[ct][4 * v] = w.x; seed[ct][4 * v + 1] = w.y; seed[ct][4 * v + 2] = w.z; seed[ct][4 * v + 3] = w.w;
-            }
-        }
-        __syncthreads();  // every wave holds its fragments before the first key tile overwrites them
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int id = tid + 512 * i;
-            *(u32x4 *)(keys + slot(id >> 4, id & 15)) = first[i];
-        }
-        store_aug(0);
-        __syncthreads();
-        uint32_t frag[8];
-#pragma unroll
-        for (int ks = 0; ks < 8; ++ks) frag[ks] = (uint32_t)slot(col, 2 * ks + half);
-        const uint32_t inv0 = 0xFFFFFFFFu - (uint32_t)(c0 + wt0 * 32 + 4 * half);  // low word of a winner: ~(place in the list)
-
-        for (int t = 0; t < ntiles; ++t) {
-            const int buf = t & 1;
-            u64 *bestt = best + buf * kAssignTile;
-            tid = thread_of(wave);
-            if (t + 1 < ntiles) {
-                const int ch = tid & 15, r16 = (tid >> 4) & 15;
-                int key[8];
-                rows_of(t + 1, key);
-                load_aug(t + 1);
-#pragma unroll
-                for (int i = 0; i < 8; ++i)
-                    lds_dma16((const uint4 *)(Ku + (size_t)key[i] * kD) + (ch ^ r16), keys + (buf ^ 1) * (kAssignTile * 256) + (4 * wave + 32 * i) * 256);
-            }
-            // (the last slice of the moved centroids: what the tile's keys are compared with, in flight during the contraction)
-            u64 last_word = 0ull, sofar = 0ull;  // (the last round's winner as it is in memory: taken apart here it would be waited for)
-            if (job == kMovedCentroids && last && tid < kAssignTile) {
-                const int key = key_of(t * kAssignTile + tid);
-                last_word = packed[key];
-                if (c0 > 0) sofar = tmp[key];
-            }
-            auto load_b = [&](int i, bf16x8 (&dst)[KS]) {
-                const char *sub = keys + buf * (kAssignTile * 256) + (kw + i * KW) * 32 * 256;
-#pragma unroll
-                for (int ks = 0; ks < 8; ++ks) dst[ks] = __builtin_bit_cast(bf16x8, *(const uint4 *)(sub + frag[ks]));
-                if constexpr (AUG) {
-                    const uint32_t e = kext[buf * kAssignTile + (kw + i * KW) * 32 + col];
-                    dst[8] = __builtin_bit_cast(bf16x8, make_uint4(half ? 0u : e, 0, 0, 0));
-                }
-            };
-            auto chain = [&](int ct, const bf16x8 (&b)[KS], f32x16 &dst) {
-                dst = seed[ct];
-#pragma unroll
-                for (int ks = 0; ks < KS; ++ks) dst = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[ct][ks], b[ks], dst, 0, 0, 0);
-            };
-            float sv = 0.f;
-            uint32_t sidx = 0;
-            auto reduce = [&](const f32x16 &acc, int i, int ct, int ctv_of) {  // as in assign_kernel
-                float m;
-                uint32_t li;
-                argmax16(acc, m, li);
-                asm("" : "+v"(li));  // (worked out in any case: as a branch around its selects it ends the pipeline of chains)
-                if (ct == 0) {
-                    sv = m;
-                    sidx = li;
-                } else {
-                    const bool gt = m > sv;
-                    sv = gt ? m : sv;
-                    sidx = gt ? li + 32u * CS * ct : sidx;
-                }
-                if (ct == ctv_of - 1)
-                    atomicMax(&bestt[(kw + i * KW) * 32 + col], ((u64)f32_ordered(sv + 0.0f) << 32) | (u64)(inv0 - sidx));
-            };
-            const int subs = min(8, (nk - t * kAssignTile + 31) / 32);  // 32-key sub-tiles with keys
-            auto compute = [&](auto tiles_held) __attribute__((always_inline)) {
-                constexpr int CTV = decltype(tiles_held)::value, NSLOT = NSUB * CTV;
-                if (subs > 4) {  // (the software pipeline of assign_kernel)
-                    bf16x8 B[2][KS];
-                    f32x16 acc[2];
-                    load_b(0, B[0]);
-                    if (CTV == 1 && NSUB > 1) load_b(1, B[1]);
-                    chain(0, B[0], acc[0]);
-#pragma unroll
-                    for (int j = 0; j < NSLOT; ++j) {
-                        const int i = j / CTV, ct = j % CTV, i1 = (j + 1) / CTV;
-                        if ((j + 2) % CTV == 0 && (j + 2) / CTV < NSUB && (j + 2) / CTV >= 1 && !(CTV == 1 && j + 2 == 1))
-                            load_b((j + 2) / CTV, B[((j + 2) / CTV) & 1]);
-                        if (j + 1 < NSLOT) chain((j + 1) % CTV, B[i1 & 1], acc[(j + 1) & 1]);
-                        reduce(acc[j & 1], i, ct, CTV);
-                    }
-                } else {  // a tile of few keys: no work for the empty sub-tiles
-                    for (int i = 0; kw + i * KW < subs; ++i) {
-                        bf16x8 B[KS];
-                        f32x16 acc[CTV];
-                        load_b(i, B);
-#pragma unroll
-                        for (int ct = 0; ct < CTV; ++ct) chain(ct, B, acc[ct]);
-#pragma unroll
-                        for (int ct = 0; ct < CTV; ++ct) reduce(acc[ct], i, ct, CTV);
-                    }
-                }
-            };
-            if (FULL || ctv == 2) compute(std::integral_constant<int, 2>{});  // (wave-uniform)
-            else if (ctv == 1) compute(std::integral_constant<int, 1>{});
-            if (t + 1 < ntiles) {
-                wait_lds_dma();
-                asm volatile("" : "+v"(kext_in));
-                store_aug(buf ^ 1);
-            }
-            // (what was requested ahead counts as arrived here for every lane: a wait left for a later place would also
-            // cover the next tile's direct loads)
-            asm volatile("" : "+v"(last_word), "+v"(sofar));
-            __syncthreads();
-            // the tile's winners, first 256 threads (a key's are the same thread's in every slice)
-            if (tid < kAssignTile) {
-                const int pos = t * kAssignTile + tid;
-                const bool valid = pos < nk;
-                bool fail = false;
-                const int key = key_of(pos);
-                u64 b = bestt[tid];
-                bestt[tid] = 0ull;
-                if (valid && !(job == kMovedCentroids && last)) {
-                    u64 *dst = (job == kMovedCentroids ? tmp : packed) + key;
-                    if (job != kMovedCentroids) b = winner_word(b, round % kRoundNumbers);
-                    if (c0 > 0) atomicMax(dst, b);  // (nothing waits for it)
-                    else *dst = b;
-                } else if (valid) {
-                    const u64 old = winner_of_word(last_word);
-                    b = max(b, sofar);
-                    const uint32_t at = ~(uint32_t)b, own = min(~(uint32_t)old, (uint32_t)Cpad - 1u);
-                    const uint32_t id = at < (uint32_t)ncent ? list[at] : 0x7FFFFFFFu;  // (a place past the list: no centroid)
-                    const u64 m = (b & 0xFFFFFFFF00000000ull) | (u64)(0xFFFFFFFFu - id);
-                    const bool own_moved = (bits[own >> 4] >> (own & 15u)) & 1u;
-                    fail = ordered_is_nan((uint32_t)(b >> 32)) || ordered_is_nan((uint32_t)(old >> 32)) || (own_moved && m < old);
-                    if (!fail && m > old) packed[key] = winner_word(m, round % kRoundNumbers);
-                }
-                if (job == kMovedCentroids && last) {
-                    const u64 f = __ballot(fail);
-                    int at = 0;
-                    if (lane == 0 && f) at = atomicAdd(&sh_fails, (int)__popcll(f));
-                    at = __builtin_amdgcn_readfirstlane(at);
-                    if (fail) fails[at + (int)__popcll(f & ((1ull << lane) - 1ull))] = (uint32_t)key;
-                }
-            }
-        }
-    };
+    ReassignJob job{kMovedCentroids, min(n, k0 + keys_per_wg) - k0, ncent, k0, Cpad, (uint32_t)(round % kRoundNumbers), packed, tmp, fails, list, bits, &sh_fails, 0ull, 0ull};
     for (;;) {
-        for (int c0 = 0; c0 < ncent; c0 += 512) {
-            const int nt = (min(512, ncent - c0) + 31) / 32;
-            if (nt <= 2) slice(std::integral_constant<int, 1>{}, std::false_type{}, c0);
-            else if (nt <= 4) slice(std::integral_constant<int, 2>{}, std::false_type{}, c0);
-            else if (nt <= 8) slice(std::integral_constant<int, 4>{}, std::false_type{}, c0);
-            else if (nt < 16) slice(std::integral_constant<int, 8>{}, std::false_type{}, c0);
-            else slice(std::integral_constant<int, 8>{}, std::true_type{}, c0);
-        }
-        if (job != kMovedCentroids) break;
+        later_slices<AUG>(d, Ku, cent, cnorm, u, Cpad, cur, wave, 0, tid, keys, best, seeds, kext, cext, job);
+        if (job.job != kMovedCentroids) break;
         wait_vmem();  // (the key lists of all waves are read by all)
         __threadfence_block();
         __syncthreads();
-        nk = __builtin_amdgcn_readfirstlane(sh_fails);
-        if (nk == 0) break;
-        job = kListedKeys;
-        ncent = Cpad;
+        job.nk = __builtin_amdgcn_readfirstlane(sh_fails);
+        if (job.nk == 0) break;
+        job.job = kListedKeys;
+        job.ncent = Cpad;
     }
     if (fused) {  // the run is a range of the sort as well
         wait_vmem();
@@ -1360,6 +1395,7 @@ static RoundPlan round_plan(const Dev &d, int n) {
 // 512 (three) 380 and 354, 475 and 485; 4 x 32768 x 512 (two) 317 and 312, 384 and 391; 1 x 16384 x 1024 (one) 163 and 165, 242 and 248.
 // (Eight tiles of centroids or fewer are contracted in about the time that their keys take to come in: with 256 clusters
 // 64 x 32768 2417 and 2440, 8 x 131072 1356 and 1415, 1564 and 1603, though 128 x 16384 2346 and 2270.)
+// Larger builds go by the centroids near a key's own (near_pays); the figures above are without that.
 bool reassign_pays(const Dev &d, int n) {
     if (d.Cpad <= 256) return false;
     const RoundPlan p = round_plan(d, n);
@@ -1380,48 +1416,6 @@ void launch_reassign(const Dev &d, const bf16_t *K, int n, int cur, int t, bool 
     if (d.tk) { if (full) ICE_REASSIGN(true, true); else ICE_REASSIGN(true, false); }
     else { if (full) ICE_REASSIGN(false, true); else ICE_REASSIGN(false, false); }
 #undef ICE_REASSIGN
-}
-
-void build_plan(const Dev &d, int n, int *plan) {
-    plan[0] = sort_is_fused(d, n) ? 1 : 0;
-    plan[1] = sort_len(d, n);
-    plan[2] = (n + plan[1] - 1) / plan[1];
-    plan[3] = reassign_pays(d, n) ? 2 : 0;
-    plan[4] = assign_run(d.U, n, 1);
-    plan[5] = assign_slices(d);
-}
-
-// ------------------------------------------------------------------------------------------------
-// The sort by itself
-template <int NG, bool MASK>
-__global__ __launch_bounds__(1024) void range_sort_kernel(Dev d, int n, int L, int W, int nbits, int round, float *best_out,
-                                                          int *assign_out) {
-    extern __shared__ __align__(16) int pos_all[];  // [W][Cpad]
-    const int r = blockIdx.x, u = blockIdx.y;
-    const int goes = round > 0 ? d.any_moved[2 * u + ((round - 1) & 1)] : 1;
-    if (r == 0 && threadIdx.x == 0) d.any_moved[2 * u + (round & 1)] = 0;  // (for this round's means)
-    // (a winner's low word holds its cluster; the whole of it is read only for best_out)
-    const u64 *packed = d.packed + (size_t)u * d.max_tokens;
-    const uint32_t *pk = (const uint32_t *)packed;
-    sort_range<16, NG, MASK>(d, threadIdx.x, u, n, r, gridDim.x, r * L, min(n, r * L + L), L / W, W, nbits, round, goes, pos_all, best_out, assign_out,
-                             [=](int i) { return pk[2 * i]; }, cluster_of_word, [=](int i) { return -2.0f * ordered_f32((uint32_t)(packed[i] >> 13)); });
-}
-
-void launch_sort(const Dev &d, int n, int t, float *best_out, int *assign_out, hipStream_t st) {
-    const int L = sort_len(d, n), R = (n + L - 1) / L, W = sort_segments(d.Cpad);
-    int nbits = 0;
-    while ((1 << nbits) < d.Cpad) ++nbits;
-    const bool masks = L / W > 4 * 64 && W * d.Cpad * 3 <= kSortCounters;
-    const size_t lds = (size_t)W * d.Cpad * (masks ? 12 : 4);
-#define ICE_SORT(ng, mk)                                                                                                   \
-    do {                                                                                                                   \
-        allow_dynamic_lds((const void *)range_sort_kernel<ng, mk>, lds);                                                   \
-        hipLaunchKernelGGL((range_sort_kernel<ng, mk>), dim3(R, d.U), dim3(1024), lds, st, d, n, L, W, nbits, t, best_out, assign_out); \
-    } while (0)
-    if (L / W <= 4 * 64) ICE_SORT(4, false);
-    else if (L / W <= 16 * 64) { if (masks) ICE_SORT(16, true); else ICE_SORT(16, false); }
-    else { if (masks) ICE_SORT(32, true); else ICE_SORT(32, false); }
-#undef ICE_SORT
 }
 
 // The members of cluster c in ascending position, out of the ranges' sorted pieces: member j sits in the last piece that
@@ -1466,9 +1460,864 @@ struct Pieces {
         return index;
     }
 };
+constexpr int kFewPieces = 8;
+
+// ------------------------------------------------------------------------------------------------
+// The assignment of a later round: keys that can only have gone to a centroid near their own, and the others.
+//
+// Between two rounds a key of a settled cluster has few centroids to choose from.  Let a be the (moved) centroid that won it
+// last, b the best of a list of centroids near a, da and db their distances from the key, and T a distance from a that no
+// centroid outside the list falls below.  A centroid c outside is at least |a - c| - da away, so it loses to b where
+//   |a - c| >= T > da + db.
+// In the benchmark's mixture (131072 keys, 2048 centroids, 5 % outliers) that leaves 23 % of the keys after the first
+// round and 10 to 12 % after the later ones, with 1 to 4 centroids near enough to matter.  What all keys against all
+// centroids would leave in `packed` follows from three launches:
+//   near_lists  per centroid a: up to 32 centroids next to it in ascending id, T, and whether its keys have to be looked at: a centroid
+//               that is near enough to matter for one of them moved, its members changed, or T fell below what they need.
+//               Clusters to be looked at are listed in chunks of 64 members.
+//   near        per chunk: the keys against the list (one 32 x 32 tile per 32 keys).  The winner is written where it is another
+//               one; a key that the test leaves open is marked, with the score of its own centroid.
+//   reassign    the marked keys, gathered: those whose own centroid stayed, against the centroids that moved (no other one can
+//               have overtaken), the others against all.
+// A score is the same bits whichever slot of the matrix instruction it comes out of, and a margin for the scores' rounding
+// (near_need) stands in the test, so the winner is the one that all of them would leave, bit for bit.
+// A unit goes through the full contraction instead, by the same code as a round of assign_kernel: where it has keys that are not
+// finite or so large that a score may not be (`large_keys`: what the contraction leaves of a key among whose scores are NaN
+// depends on where in a tile they are; argmax16: nine of them side by side hide their lane's others), and for the rest of the
+// build once more than 3/5 of its keys were marked in a round, or would be in the first one as far as one key of every second cluster tells
+// (keys without structure: the first two launches are in vain then).
+//
+// `Near`: what the three leave for each other, scratch at the start of the unit's key tiles: at most 153 of the 256 bytes per
+// token there (n tokens, C <= n).
+constexpr int kNearList = 32, kNearChunk = 64;
+constexpr int kNearGroups = 12;   // a list's threshold: this many groups of 16 centroids have a member at or above it
+constexpr int kMaxNearTokens = 1 << 24;  // (an item holds a cluster in 13 bits and a chunk in 19)
+constexpr int kMaxSlices = kMaxClusters / 512;
+struct Near {
+    int *head;           // items; marked keys in even rounds, in odd ones; whether the unit takes all for the rest of the build; keys
+                         // that round 1 looked at ahead, those of them that will be marked
+    uint32_t *list;      // [kMaxSlices][n] reassign's keys, per slice of the centroids
+    unsigned char *open; // [n] 0: settled; else marked: near_mark of the round if the key's own centroid moved, 1 if it stayed
+    uint16_t *near;      // [C][kNearList] ascending, the centroid itself among them, 0xFFFF behind the last
+    float *reach;        // [C] T
+    float *need;         // [C] what T has to exceed for every settled key
+    float *few;          // [C] squared distance within which few centroids were when it was last worked out, 0: to be worked out
+    uint32_t *items;     // [C + n / kNearChunk]
+};
+__device__ inline Near near_of(const Dev &d, int u, int n) {
+    Near x;
+    char *p = near_scratch(d, u);
+    x.head = (int *)p;
+    p += 64;
+    x.list = (uint32_t *)p;
+    p += (size_t)kMaxSlices * n * 4;
+    x.open = (unsigned char *)p;
+    p += (n + 63) / 64 * 64;
+    x.near = (uint16_t *)p;
+    p += (size_t)d.C * kNearList * 2;
+    x.reach = (float *)p;
+    x.need = x.reach + d.C;
+    x.few = x.need + d.C;
+    x.items = (uint32_t *)(x.few + d.C);
+    return x;
+}
+// (round 1: most of the keys that were looked at ahead will be marked)
+__device__ inline bool near_in_vain(const int *head, int round) { return head[3] != 0 || (round == 1 && head[5] * 5 > head[4] * 3); }
+__device__ inline unsigned near_mark(int round) { return 128u | ((unsigned)round & 127u); }
+
+// The margin for rounding.  A score s(c) = k . c - |c|^2 / 2 is a chain of 129 (transformed keys: 130) fp32 additions of exact
+// products: off by at most E(c) = g (|k| |c| + |c|^2), g = 2^-15 (four times (d + 2) 2^-24).  With D = |a - c| >= T > da + db:
+//   s(b) - s(c) = (dc^2 - db^2) / 2 >= (D - da - db)^2 / 2,
+//   E(b) + E(c) <= g (4 |k|^2 + 3 |a|^2 + 6 D^2)        (|c|^2 <= 2 |a|^2 + 2 D^2, |b|^2 <= 2 |k|^2 + 2 D^2),
+// so c loses in fp32 as well where D - (da + db) > sqrt(8 g (|k|^2 + |a|^2)) + sqrt(12 g) D; sqrt(12 g) < 0.0195, hence the factor
+// 1.025, which covers the rounding of these lines too.  da^2 and db^2 come out of scores, |k|^2 - 2 s, at most
+// 2 g (5 |k|^2 + 4 db^2) too low: 32 g (|k|^2 + |a|^2) is added to them.  Whatever is not a number leaves the key open.
+__device__ inline float near_need(float k2, float a2, float sa, float sb) {
+    const float w = k2 + a2, up = 0x1p-10f * w;
+    const float da = sqrtf(fmaxf(k2 - 2.f * sa, 0.f) + up), db = sqrtf(fmaxf(k2 - 2.f * sb, 0.f) + up);
+    return (da + db + sqrtf(0x1p-12f * w)) * 1.025f;
+}
+// a lower bound of the squared distance of a and a centroid of score at most s against it (the same bound on the score)
+__device__ inline float near_dist2(float a2, float s) { return fmaxf((a2 * (1.f - 0x1p-11f) - 2.f * s) * (1.f - 0x1p-11f), 0.f); }
+
+// Up to 32 rows of 256 bytes into a wave's own LDS tile (chunk c of row r in slot c ^ (r & 15)), lane first + r saying where row r is
+__device__ inline void stage_rows(const bf16_t *base, int row_of_lane, int first, int rows, char *tile, int lane) {
+    const int g = lane >> 4, i = lane & 15;
+#pragma unroll
+    for (int x = 0; x < 8; ++x) {
+        if (4 * x >= rows) break;  // (wave-uniform)
+        const int rr = 4 * x + g;
+        const int row = __shfl(row_of_lane, first + rr);
+        lds_dma16((const uint4 *)(base + (size_t)row * kD) + (i ^ (rr & 15)), tile + x * 1024);
+    }
+}
+__device__ inline void read_rows(const char *tile, int lane, bf16x8 *out) {
+    const int col = lane & 31, half = lane >> 5;
+#pragma unroll
+    for (int ks = 0; ks < 8; ++ks) out[ks] = __builtin_bit_cast(bf16x8, *(const uint4 *)(tile + col * 256 + (((2 * ks + half) ^ (col & 15)) << 4)));
+}
+
+// Per centroid the ones near it.  A workgroup of 8 waves takes 64 centroids (the B operand, in registers) against all of the
+// unit's, 32 at a time per wave, for the mask of those whose score reaches a limit.  The limit stands for a distance: within which
+// few centroids are, and no further than the centroid's keys need (with something to spare, more where the centroid or its members
+// are other ones than in the last round).  For the first list a pass over all of them finds the maximum of every group of 16, of which
+// the kNearGroups-th largest (its upper 16 bits) is taken.  Bound by the round trips to the centroid rows, one tile's behind the other's.
+constexpr int kNearA = 64;
+constexpr int kNearMaxClusters = 4096;
+// a wave's tiles of rows (two where they fit), the centroids' squared norms, the groups' maxima (the workgroup's own rows first)
+__host__ __device__ inline int near_tiles(int Cpad) { return Cpad <= 2048 ? 2 : 1; }
+__host__ __device__ inline int near_lists_lds_bytes(int Cpad) {
+    const int maxima = kNearA * (Cpad / 16 + 2) * 2;
+    return 8 * 8192 * near_tiles(Cpad) + Cpad * 4 + (maxima > 16384 ? maxima : 16384);  // (at most 153 KB)
+}
+template <bool AUG>
+__global__ __launch_bounds__(512) void near_lists_kernel(const bf16_t *__restrict__ cent, const float *__restrict__ cnorm, int n, int Cpad, int cur,
+                                                         const bf16_t *__restrict__ K, const int *__restrict__ go, int round, int R, int L, Dev d) {
+    constexpr int KS = AUG ? 9 : 8;
+    extern __shared__ __align__(16) char smem[];
+    __shared__ float limit[kNearA], close_to[kNearA];
+    __shared__ __align__(4) uint16_t moved[kNearMaxClusters / 16];
+    __shared__ int chunks[kNearA], found[kNearA];
+    const int nbuf = near_tiles(Cpad);
+    float *norms = (float *)(smem + 8 * 8192 * nbuf);  // [Cpad]
+    char *own_rows = (char *)(norms + Cpad);
+    uint16_t *gmax = (uint16_t *)own_rows;            // [kNearA][Cpad / 16 + 2] upper halves of the groups' ordered maxima
+    uint32_t *hits = (uint32_t *)gmax;                // [kNearA][Cpad / 32 + 1] afterwards: the list as a mask
+    const int groups = Cpad / 16, gstride = groups + 2, tiles = Cpad / 32, hstride = tiles + 1;
+    // (a unit's workgroups on few dies: its rows stay in their L2)
+    const int u = blockIdx.x % d.U, block = blockIdx.x / d.U, a0 = block * kNearA, tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int lane = tid & 63;
+    char *tile_lds = smem + wave * nbuf * 8192;
+    const bf16_t *cu = cent + (size_t)u * Cpad * kD;
+    const float *wn = cnorm + (size_t)u * Cpad;
+    const Near x = near_of(d, u, n);
+    auto request = [&](int t, int buf) {  // rows of a tile, direct to LDS
+        const int g = lane >> 4, i = lane & 15;
+        const uint4 *src = (const uint4 *)(cu + (size_t)t * 32 * kD);
+#pragma unroll
+        for (int y = 0; y < 8; ++y) lds_dma16(src + (4 * y + g) * 16 + (i ^ (4 * (y & 3) + g)), tile_lds + buf * 8192 + y * 1024);
+    };
+    if (wave < 2) stage_rows(cu, min(a0 + 32 * wave + (lane & 31), Cpad - 1), 0, 32, own_rows + wave * 8192, lane);
+    // a scan's first tiles
+    auto request_first = [&] {
+        if (wave < tiles) request(wave, 0);
+        if (nbuf > 1 && wave + 8 < tiles) request(wave + 8, 1);
+    };
+    request_first();
+    for (int i = tid; i < Cpad / 4; i += 512) ((float4 *)norms)[i] = ((const float4 *)wn)[i];
+    const int goes = go[2 * u], off = x.head[3], large = d.large_keys[u], open = x.head[1 + ((round - 1) & 1)];
+    uint32_t mv = 0;
+    int held = 0;
+    if (tid < groups) mv = moved_of_16(d.moved + (size_t)u * Cpad, tid, held);
+    float a2 = 0.f, need = 0.f, few = 0.f;
+    int members = 0;
+    uint32_t own_word = 0, own_extra[2] = {0, 0};
+    if constexpr (AUG) {
+#pragma unroll
+        for (int ct = 0; ct < 2; ++ct) own_extra[ct] = d.caug[cur][(size_t)u * Cpad + min(a0 + 32 * ct + (lane & 31), Cpad - 1)];
+    }
+    const bool real = tid < kNearA && a0 + tid < d.C;
+    if (real) {
+        a2 = wn[a0 + tid];
+        members = d.cluster_cnt[(size_t)u * d.C + a0 + tid];
+        own_word = d.moved[(size_t)u * Cpad + a0 + tid];
+        if (round > 1) {
+            need = x.need[a0 + tid];
+            few = x.few[a0 + tid];
+        }
+    }
+    wait_lds_dma();  // (also for a workgroup that leaves here: nothing lands in its LDS any more)
+    if (goes == 0) return;
+    if (off != 0 || large != 0 || (long long)open * 5 > (long long)n * 3) {
+        if (tid == 0) x.head[3] = 1;
+        return;
+    }
+    if (block == 0 && tid == 0) x.head[1 + (round & 1)] = 0;
+    if (tid < groups) moved[tid] = (uint16_t)mv;
+    if (wave == 0) {  // (kNearA == 64)
+        // (near_dist2 of score_at(x) is x)
+        auto score_at = [&](float dist2) { return 0.5f * (a2 * (1.f - 0x1p-11f) - dist2 * (1.f + 0x1p-11f)); };
+        const float w = (own_word != 0u ? 1.3f : 1.02f) * need;
+        close_to[tid] = need > 0.f ? score_at(w * w) : -INFINITY;
+        limit[tid] = fmaxf(close_to[tid], score_at(few));
+        chunks[tid] = (members + kNearChunk - 1) / kNearChunk;
+    }
+    lds_barrier();
+    bf16x8 B[2][KS];
+#pragma unroll
+    for (int ct = 0; ct < 2; ++ct) {
+        read_rows(own_rows + ct * 8192, lane, B[ct]);
+        if constexpr (AUG) B[ct][8] = __builtin_bit_cast(bf16x8, make_uint4(lane >= 32 ? 0u : own_extra[ct], 0, 0, 0));
+    }
+    lds_barrier();  // (read before the maxima go there)
+    // every tile of this wave: use(tile, ct, scores)
+    auto scan = [&](auto use) {
+        const int col = lane & 31, half = lane >> 5;
+        for (int t = wave, y = 0; t < tiles; t += 8, ++y) {
+            const int buf = y & (nbuf - 1);
+            uint32_t extra = 0;
+            if constexpr (AUG) extra = d.caug[cur][(size_t)u * Cpad + t * 32 + col];
+            // (behind the first tile nothing but tiles is on its way: the next one's eight loads may be)
+            if (!AUG && nbuf > 1 && y > 0 && t + 8 < tiles) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+            else wait_lds_dma();
+            bf16x8 A[KS];
+            f32x16 seed;
+            read_rows(tile_lds + buf * 8192, lane, A);
+            if constexpr (AUG) A[8] = __builtin_bit_cast(bf16x8, make_uint4(half ? 0u : extra, 0, 0, 0));
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float4 w = *(const float4 *)(norms + t * 32 + 8 * v + 4 * half);
+                seed[4 * v] = -0.5f * w.x; seed[4 * v + 1] = -0.5f * w.y; seed[4 * v + 2] = -0.5f * w.z; seed[4 * v + 3] = -0.5f * w.w;
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (read before the next tile may land there)
+            if (t + 8 * nbuf < tiles) request(t + 8 * nbuf, buf);
+#pragma unroll
+            for (int ct = 0; ct < 2; ++ct) {
+                f32x16 acc = seed;
+#pragma unroll
+                for (int ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[ks], B[ct][ks], acc, 0, 0, 0);
+                use(t, ct, acc);
+            }
+        }
+    };
+    // the kNearGroups-th largest group maximum of four centroids side by side (the chain of one is ballot, count, compare)
+    const int k = min(kNearGroups, groups / 2);
+    auto kth = [&](auto words) {
+        constexpr int NJ = decltype(words)::value, NA = NJ > 2 ? 1 : 4;
+        for (int i = 0; i < kNearA / 8; i += NA) {
+            const int a = wave * (kNearA / 8) + i;
+            uint32_t v[NA][NJ], at[NA];
+#pragma unroll
+            for (int y = 0; y < NA; ++y) {
+                at[y] = 0;
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) v[y][j] = 64 * j + lane < groups ? gmax[(a + y) * gstride + 64 * j + lane] : 0u;
+            }
+#pragma unroll
+            for (int b = 15; b >= 0; --b) {
+#pragma unroll
+                for (int y = 0; y < NA; ++y) {
+                    const uint32_t trial = at[y] | 1u << b;
+                    int cnt = 0;
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j) cnt += (int)__popcll(__ballot(v[y][j] >= trial));
+                    at[y] = cnt >= k ? trial : at[y];
+                }
+            }
+#pragma unroll
+            for (int y = 0; y < NA; ++y)
+                if (lane == 0) limit[a + y] = ordered_f32(max(at[y] << 16, 0x00800000u));  // (above -inf, the padding rows' score)
+        }
+    };
+    // masks to lists, eight centroids per wave, NA side by side
+    auto lists = [&](auto words) {
+        constexpr int NJ = decltype(words)::value, NA = NJ > 1 ? 1 : 4;
+        for (int i = 0; i < kNearA / 8; i += NA) {
+            uint32_t w[NA][NJ];
+            int at[NA][NJ], m[NA];
+            bool ok[NA];
+#pragma unroll
+            for (int y = 0; y < NA; ++y) {
+                const int al = wave * (kNearA / 8) + i + y, a = a0 + al;
+                bool own = false, any = false;
+                m[y] = 0;
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) {
+                    const int t = 64 * j + lane;
+                    w[y][j] = t < tiles ? hits[al * hstride + t] : 0u;
+                    const int cnt = __popc(w[y][j]), incl = wave_scan_add(cnt);
+                    at[y][j] = m[y] + incl - cnt;
+                    m[y] += __builtin_amdgcn_readlane(incl, 63);
+                    own |= t == a >> 5 && (w[y][j] >> (a & 31) & 1u) != 0u;
+                    any |= (w[y][j] & (t < tiles ? *(const uint32_t *)(moved + 2 * t) : 0u)) != 0u;
+                }
+                ok[y] = m[y] <= kNearList && __ballot(own) != 0ull;  // (else too many, as of centroids that are alike: no list)
+                const u64 some = __ballot(any);
+                if (lane == 0) found[al] = (ok[y] ? m[y] : 0) | (some != 0ull ? 64 : 0);
+            }
+#pragma unroll
+            for (int y = 0; y < NA; ++y) {
+                const int a = a0 + wave * (kNearA / 8) + i + y;
+                if (a >= d.C) continue;  // (wave-uniform)
+                uint16_t *out = x.near + (size_t)a * kNearList;
+                if (ok[y]) {
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j)
+                        for (uint32_t z = w[y][j]; z; z &= z - 1) out[at[y][j]++] = (uint16_t)(32 * (64 * j + lane) + __ffs(z) - 1);
+                }
+                if (lane < kNearList && lane >= (ok[y] ? m[y] : 0)) out[lane] = (uint16_t)(!ok[y] && lane == 0 ? a : 0xFFFF);
+            }
+        }
+    };
+    const int col = lane & 31, half = lane >> 5;
+    if (round == 1) {
+        scan([&](int t, int ct, const f32x16 &acc) {
+            float m = max3f(acc[0], acc[1], acc[2]);
+#pragma unroll
+            for (int v = 3; v < 15; v += 2) m = max3f(m, acc[v], acc[v + 1]);
+            m = fmaxf(m, acc[15]);
+            gmax[(32 * ct + col) * gstride + 2 * t + half] = (uint16_t)(f32_ordered(m) >> 16);
+        });
+        request_first();
+        lds_barrier();
+        if (groups <= 64) kth(std::integral_constant<int, 1>{});
+        else if (groups <= 128) kth(std::integral_constant<int, 2>{});
+        else kth(std::integral_constant<int, 4>{});
+        lds_barrier();
+        if (wave == 0) few = near_dist2(a2, limit[tid]);
+    }
+    const float lim0 = limit[col], lim1 = limit[32 + col];
+    scan([&](int t, int ct, const f32x16 &acc) {
+        const float lim = ct ? lim1 : lim0;
+        uint32_t m = 0;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) m |= acc[v] >= lim ? 1u << (8 * (v >> 2) + (v & 3)) : 0u;
+        m <<= 4 * half;
+        m |= (uint32_t)__shfl_xor((int)m, 32);
+        if (half == 0) hits[(32 * ct + col) * hstride + t] = m;
+    });
+    lds_barrier();
+    if (tiles <= 64) lists(std::integral_constant<int, 1>{});
+    else lists(std::integral_constant<int, 2>{});
+    lds_barrier();
+    if (round == 1) {  // one key of every second cluster: does its list settle it, as far as the distance from its own centroid says
+        const int g = lane >> 4, ch = lane & 15, al = wave * (kNearA / 8) + 2 * g, c = min(a0 + al, d.C - 1);
+        const uint32_t word = ch < R ? d.range_off[((size_t)u * R + ch) * Cpad + c] : 0u;  // (a member in the first 16 ranges, mostly)
+        const uint32_t has = (uint32_t)(__ballot((word & 0xFFFFu) != 0u) >> (16 * g)) & 0xFFFFu;
+        const int r = has ? __ffs(has) - 1 : 0;
+        const int at = r * L + (int)((uint32_t)__shfl((int)word, 16 * g + r) >> 16);
+        const int tok = has ? d.order[(size_t)u * d.max_tokens + at] : 0;
+        const uint4 x4 = ((const uint4 *)(K + ((size_t)u * n + tok) * kD))[ch], c4 = ((const uint4 *)(cu + (size_t)c * kD))[ch];
+        const uint32_t xs[4] = {x4.x, x4.y, x4.z, x4.w}, cs[4] = {c4.x, c4.y, c4.z, c4.w};
+        float d2 = 0.f;
+#pragma unroll
+        for (int y = 0; y < 4; ++y) {
+            const float lo = bf16_lo(xs[y]) - bf16_lo(cs[y]), hi = bf16_hi(xs[y]) - bf16_hi(cs[y]);
+            d2 += lo * lo + hi * hi;
+        }
+        if constexpr (AUG) {
+            const float e = bf16_to_f32(d.kaug[(size_t)u * d.max_tokens + tok]) - bf16_to_f32(d.caug[cur][(size_t)u * Cpad + c]);
+            d2 += ch == 0 ? e * e : 0.f;
+        }
+        d2 = row16_sum(d2);
+        const bool sample = has != 0u && a0 + al < d.C && ch == 0;
+        const u64 all = __ballot(sample), open_too = __ballot(sample && !(4.25f * d2 < near_dist2(wn[c], limit[al])));
+        if (lane == 0 && all) {
+            atomicAdd(&x.head[4], (int)__popcll(all));
+            if (open_too) atomicAdd(&x.head[5], (int)__popcll(open_too));
+        }
+    }
+    if (tid >= kNearA) return;
+    // one thread per centroid
+    int mine = 0;
+    if (real) {
+        const int f = found[tid];
+        const int m = f & 63;
+        const float dist2 = near_dist2(a2, limit[tid]), reach = m > 0 ? sqrtf(dist2) * (1.f - 0x1p-20f) : 0.f;
+        x.reach[a0 + tid] = reach;
+        // (how many there are follows the centroids' moves: a list that came out too long is left out for once, a short one may grow)
+        x.few[a0 + tid] = m == 0 ? 0.5f * dist2 : m < kNearGroups / 2 && dist2 > 0.95f * few ? 1.2f * few : few;
+        if ((f & 64) != 0 || own_word != 0u || !(reach > need) || round == 1) {
+            mine = chunks[tid];
+            x.need[a0 + tid] = 0.f;
+        }
+    }
+    const int incl = wave_scan_add(mine), total = __builtin_amdgcn_readlane(incl, 63);
+    int base = 0;
+    if (lane == 0 && total > 0) base = atomicAdd(&x.head[0], total);
+    base = __builtin_amdgcn_readfirstlane(base);
+    const int to = base + incl - mine;
+    constexpr int kAlone = 8;
+    for (int c = 0; c < min(mine, kAlone); ++c) x.items[to + c] = (uint32_t)(a0 + tid) | (uint32_t)c << 13;
+    for (u64 left = __ballot(mine > kAlone); left; left &= left - 1ull) {  // (a large cluster's chunks by the whole wave)
+        const int l = (int)__builtin_ctzll(left), cnt = __builtin_amdgcn_readlane(mine, l), first = __builtin_amdgcn_readlane(to, l);
+        for (int c = kAlone + lane; c < cnt; c += 64) x.items[first + c] = (uint32_t)(a0 + l) | (uint32_t)c << 13;
+    }
+}
+
+// The keys of the listed chunks against their centroids' lists, one wave per chunk of 64 members: the list's rows (A operand) and
+// the keys' (B, 32 at a time) through the wave's own LDS, so no wave waits for another; the next chunk is looked up and its
+// rows are requested while this one's are worked on.  Bound by the read of the keys and, where
+// chunks are few, by the chain chunk -> piece -> entry -> row.
+// NP: as in means_kernel (1 piece per cluster, at most kFewPieces, more).
+template <bool AUG, int NP>
+__global__ __launch_bounds__(64) void near_kernel(const bf16_t *__restrict__ K, const bf16_t *__restrict__ cent, const float *__restrict__ cnorm,
+                                                  int n, int Cpad, int cur, const int *__restrict__ go, int round, int R, int L, Dev d) {
+    constexpr int KS = AUG ? 9 : 8;
+    __shared__ __align__(16) char rows[2][8192];
+    __shared__ __align__(16) float seeds[32];
+    const int u = blockIdx.x % d.U, lane = threadIdx.x, col = lane & 31, half = lane >> 5;  // (a unit's workgroups on few dies: its rows stay in their L2)
+    const Near x = near_of(d, u, n);
+    const int goes = go[2 * u], items = near_in_vain(x.head, round) ? 0 : __builtin_amdgcn_readfirstlane(x.head[0]), step = gridDim.x / d.U;
+    int it = blockIdx.x / d.U;
+    if (goes == 0 || it >= items) return;
+    // (rows of the list's tile that no centroid is staged into keep finite numbers: they count with a seed of -inf)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) *(uint4 *)(&rows[0][0] + (i * 64 + lane) * 16) = make_uint4(0, 0, 0, 0);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    const bf16_t *Ku = K + (size_t)u * n * kD, *cu = cent + (size_t)u * Cpad * kD;
+    const int *order = d.order + (size_t)u * d.max_tokens;
+    u64 *packed = d.packed + (size_t)u * d.max_tokens;
+    const uint32_t tag = (uint32_t)(round % kRoundNumbers);
+    struct Chunk {
+        int c, j0, id, cnt;
+        float reach, a2;
+        uint32_t moved, word;
+    };
+    auto look_up = [&](uint32_t item) {
+        Chunk k;
+        k.c = (int)(item & 8191u);
+        k.j0 = (int)(item >> 13) * kNearChunk;
+        const size_t row = (size_t)u * Cpad + k.c;
+        k.word = Pieces{d.range_off + (size_t)u * R * Cpad + k.c, Cpad, R, L}.word(NP == 1 ? 0 : lane);
+        k.id = x.near[(size_t)k.c * kNearList + col];
+        k.reach = x.reach[k.c];
+        k.a2 = cnorm[row];
+        k.cnt = d.cluster_cnt[(size_t)u * d.C + k.c];
+        k.moved = d.moved[row];
+        return k;
+    };
+    auto token = [&](const Chunk &k) -> int {  // member j0 + lane, -1 past the last
+        const int j = k.j0 + lane;
+        const Pieces pieces = {d.range_off + (size_t)u * R * Cpad + k.c, Cpad, R, L};
+        int at;
+        if constexpr (NP == 1) {
+            at = (int)(k.word >> 16) + j;
+        } else if constexpr (NP == kFewPieces) {
+            at = 0;
+            int before = 0;
+#pragma unroll
+            for (int r = 0; r < NP; ++r) {
+                const uint32_t w = __builtin_amdgcn_readlane(k.word, r);
+                if (j >= before) at = r * L + (int)(w >> 16) + j - before;
+                before += (int)(w & 0xFFFFu);
+            }
+        } else if (R <= 64) {
+            int first, from, own;
+            pieces.take(k.word, 0, lane, 0, first, from, own);
+            at = Pieces::find(first, from, j);
+        } else {
+            at = pieces.search(k.j0, j, lane);
+        }
+        int tok = -1;
+        if (j < k.cnt) tok = order[at];
+        return tok;
+    };
+    // The rows of a chunk go to two tiles: its list's and its first 32 keys'; then the other keys' to where the list's were and the
+    // next chunk's list to where the first keys' were; then the next chunk's first keys to where the other keys' were.
+    auto list_rows = [&](const Chunk &k, char *to) {
+        stage_rows(cu, k.id == 0xFFFF ? k.c : k.id, 0, (int)__popcll(__ballot(lane < 32 && k.id != 0xFFFF)), to, lane);
+    };
+    auto key_rows = [&](const Chunk &k, int tok, int first, char *to) {
+        const int any = __builtin_amdgcn_readfirstlane(tok);  // (a chunk has a member)
+        stage_rows(Ku, tok >= 0 ? tok : any, first, min(k.cnt - k.j0 - first, 32), to, lane);
+    };
+    Chunk k = look_up(__builtin_amdgcn_readfirstlane(x.items[it]));
+    uint32_t item1 = it + step < items ? x.items[it + step] : 0u;
+    int tok = token(k);
+    list_rows(k, rows[0]);
+    key_rows(k, tok, 0, rows[1]);
+    for (int p = 0;; p ^= 1) {
+        char *list_at = rows[p], *keys_at = rows[1 - p];
+        const int c = k.c, listed = k.id == 0xFFFF ? c : k.id;
+        float seed_in = -INFINITY;
+        uint32_t cext = 0, kext = 0;
+        if (k.id != 0xFFFF) seed_in = -0.5f * cnorm[(size_t)u * Cpad + k.id];
+        if constexpr (AUG) {
+            cext = d.caug[cur][(size_t)u * Cpad + listed];
+            kext = d.kaug[(size_t)u * d.max_tokens + max(tok, 0)];
+        }
+        const u64 is_own = __ballot(lane < 32 && k.id == c);
+        const int own_at = (int)__builtin_ctzll(is_own | 1ull << 32) & 31;  // (c is in its list)
+        const int own_v = (own_at >> 3) * 4 + (own_at & 3), own_half = own_at >> 2 & 1;
+        const float reach = k.reach, a2 = k.a2;
+        k.cnt = __builtin_amdgcn_readfirstlane(k.cnt);
+        const bool own_moved = (__builtin_amdgcn_readfirstlane((int)k.moved) & 1) != 0, more = k.cnt - k.j0 > 32;
+        // the next chunk
+        it += step;
+        const bool goes_on = it < items;
+        Chunk k1 = k;
+        if (goes_on) k1 = look_up(__builtin_amdgcn_readfirstlane(item1));
+        if (it + step < items) item1 = x.items[it + step];
+        wait_lds_dma();
+        if (lane < 32) seeds[lane] = seed_in;
+        bf16x8 A[KS], B[KS];
+        f32x16 seed;
+        read_rows(list_at, lane, A);
+        if constexpr (AUG) A[8] = __builtin_bit_cast(bf16x8, make_uint4(half ? 0u : cext, 0, 0, 0));
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const float4 w = *(const float4 *)(seeds + 8 * v + 4 * half);
+            seed[4 * v] = w.x; seed[4 * v + 1] = w.y; seed[4 * v + 2] = w.z; seed[4 * v + 3] = w.w;
+        }
+        read_rows(keys_at, lane, B);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // (read before the next rows may land there)
+        if (more) key_rows(k, tok, 32, list_at);
+        int tok1 = -1;
+        if (goes_on) {
+            tok1 = token(k1);
+            list_rows(k1, keys_at);
+        }
+        float need_max = 0.f;
+        // the keys in B: members 32 h .. of the chunk
+        auto settle = [&](int h) __attribute__((always_inline)) {
+            const int key = __shfl(tok, 32 * h + col);
+            float k2 = 0.f;
+#pragma unroll
+            for (int ks = 0; ks < 8; ++ks) {
+                const uint4 w = __builtin_bit_cast(uint4, B[ks]);
+                k2 = dot2(w.w, w.w, dot2(w.z, w.z, dot2(w.y, w.y, dot2(w.x, w.x, k2))));
+            }
+            k2 += __shfl_xor(k2, 32);
+            if constexpr (AUG) {
+                const uint32_t e = __shfl(kext, 32 * h + col);
+                B[8] = __builtin_bit_cast(bf16x8, make_uint4(half ? 0u : e, 0, 0, 0));
+                const float f = __uint_as_float(e << 16);
+                k2 += f * f;
+            }
+            f32x16 acc = seed;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(A[ks], B[ks], acc, 0, 0, 0);
+            float sa = acc[0];
+#pragma unroll
+            for (int v = 1; v < 16; ++v) sa = v == own_v ? acc[v] : sa;
+            sa = __shfl(sa, col + 32 * own_half);
+            float m;
+            uint32_t li;
+            argmax16(acc, m, li);
+            const u64 mine = ((u64)f32_ordered(m + 0.0f) << 32) | (u64)(31u - (li + 4u * half));
+            const u64 other = ((u64)(uint32_t)__shfl_xor((int)(uint32_t)(mine >> 32), 32) << 32) | (u64)(uint32_t)__shfl_xor((int)(uint32_t)mine, 32);
+            const u64 best = mine > other ? mine : other;
+            const int won = __shfl(listed, (int)(31u - (uint32_t)best));
+            const float need = near_need(k2, a2, sa, ordered_f32((uint32_t)(best >> 32)));
+            const bool settled = reach > need;
+            if (half == 0 && key >= 0) {
+                x.open[key] = (unsigned char)(settled ? 0u : own_moved ? near_mark(round) : 1u);
+                // (an open key: its own centroid's score as it is now, which the marked keys' pass compares with)
+                const u64 word_of = settled ? (best & 0xFFFFFFFF00000000ull) | (u64)(0xFFFFFFFFu - (uint32_t)won)
+                                            : ((u64)f32_ordered(sa + 0.0f) << 32) | (u64)(0xFFFFFFFFu - (uint32_t)c);
+                if (!settled || won != c) packed[key] = winner_word(word_of, tag);
+                if (settled) need_max = fmaxf(need_max, need);
+            }
+        };
+        settle(0);
+        if (more) {  // (wave-uniform)
+            wait_lds_dma();
+            read_rows(list_at, lane, B);
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        }
+        if (goes_on) key_rows(k1, tok1, 0, list_at);
+        if (more) settle(1);
+        uint32_t top = row16_max_u32(__float_as_uint(need_max));  // (no need is negative)
+        top = max(top, (uint32_t)__shfl_xor((int)top, 16));
+        if (lane == 0 && top != 0u) atomicMax((int *)&x.need[c], (int)top);
+        if (!goes_on) break;
+        k = k1;
+        tok = tok1;
+    }
+}
+
+// The marked keys of a run (see above; of a unit that takes all, every key by assign_slice).  The workgroup that has slice x of
+// the centroids takes the keys whose own centroid moved against that slice (they meet in `packed`, as in assign_kernel), and
+// its share of the others against the centroids that moved (listed in ascending id in LDS, 512 at a time): with `old`
+// the word of the key's own centroid, the winner m stands where m > old.
+// Bound by its prologues where few keys are marked, as assign_kernel is else.
+struct MarkedJob {
+    bool moved;             // against the centroids that moved (`list`), else against all
+    int nk, ncent, dir, slices;
+    uint32_t round;
+    u64 *packed;
+    const uint32_t *keys;   // key x is keys[dir * x]
+    const uint16_t *list;
+    u64 last_word;
+    __device__ __forceinline__ int key_of(int pos) const {
+        int key = (int)keys[dir * min(pos, nk - 1)];
+        asm volatile("" : "+v"(key));  // (waited for where it is loaded, see ReassignJob)
+        return key;
+    }
+    __device__ __forceinline__ void rows_of(int t, int tid, int (&key)[8]) const {
+        const int base = t * kAssignTile + (tid >> 4);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) key[i] = (int)keys[dir * min(base + 32 * i, nk - 1)];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(key[i]));
+    }
+    __device__ __forceinline__ int centroid(int pos) const { return moved ? (int)list[pos] : pos; }
+    // (the moved centroids: what the tile's keys are compared with, in flight during the contraction)
+    __device__ __forceinline__ void ahead(int t, int tid, int) {
+        last_word = 0ull;  // (as it is in memory: taken apart here it would be waited for)
+        if (moved && tid < kAssignTile) last_word = packed[key_of(t * kAssignTile + tid)];
+    }
+    __device__ __forceinline__ void arrived() { asm volatile("" : "+v"(last_word)); }
+    __device__ __forceinline__ void take(int pos, u64 b, int, int) {
+        if (pos >= nk) return;
+        const int key = key_of(pos);
+        if (!moved) {
+            const u64 w = winner_word(b, round);
+            if (slices > 1) atomicMax(packed + key, w);  // (nothing waits for it)
+            else packed[key] = w;
+        } else {
+            const uint32_t at = ~(uint32_t)b;  // (a place in the list)
+            const u64 m = (b & 0xFFFFFFFF00000000ull) | (u64)(0xFFFFFFFFu - list[min(at, (uint32_t)ncent - 1u)]);
+            if (m > winner_of_word(last_word)) packed[key] = winner_word(m, round);
+        }
+    }
+};
+__host__ __device__ inline int marked_lds_bytes(bool aug, int Cpad) { return 2 * 256 * 256 + 2 * 256 * 8 + 512 * 4 + (aug ? 1024 * 4 : 0) + Cpad * 2; }
+
+template <bool AUG, bool ALL_FULL>  // ALL_FULL: every slice of the centroids is full (FULL of assign_slice)
+__global__ __launch_bounds__(512) void marked_kernel(const bf16_t *__restrict__ K, const bf16_t *__restrict__ cent,
+                                                     const float *__restrict__ cnorm, int n, int Cpad, int cur, const int *__restrict__ go,
+                                                     int round, int fused, int run, int wgs, int slices, Dev d) {  // (scalars first: preloaded at wave start)
+    extern __shared__ __align__(16) char smem[];
+    char *keys = smem;                                             // [2][256][256 B], chunks swizzled as in assign_slice
+    u64 *best = (u64 *)(smem + 2 * kAssignTile * 256);             // [2][256]
+    float *seeds = (float *)(best + 2 * kAssignTile);              // [512] of the slice at hand
+    uint32_t *kext = (uint32_t *)(seeds + 512);                    // (AUG) [2][256] the keys' extra coordinates
+    uint32_t *cext = kext + 2 * kAssignTile;                       // (AUG) [512] the centroids' of the slice at hand
+    uint16_t *list = (uint16_t *)(kext + (AUG ? 1024 : 0));        // [Cpad] moved centroids, ascending
+    uint16_t *won = (uint16_t *)(smem + assign_lds_bytes(AUG));    // (all keys, fused) the run's winners
+    __shared__ int sh_wave[8], sh_marked[2];
+
+    const int u = blockIdx.y;
+    int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    u64 *packed = d.packed + (size_t)u * d.max_tokens;
+    const int keys_per_wg = run * kAssignTile, which = blockIdx.x / wgs, range = blockIdx.x - which * wgs;
+    const int k0 = range * keys_per_wg, kend = min(n, k0 + keys_per_wg);
+    const int nbits = 32 - __builtin_clz((unsigned)Cpad - 1u);
+    int *head = (int *)near_scratch(d, u);
+
+    if (fused && blockIdx.x == 0 && tid == 0) d.any_moved[2 * u + (round & 1)] = 0;  // (for this round's means)
+    if (go[2 * u] == 0) return;  // (no centroid moved: every winner stands)
+    if (near_in_vain(head, round)) {  // (the same for the whole unit)
+        if (blockIdx.x == 0 && tid == 0) head[3] = 1;
+        assign_slice<2, 8, AUG, ALL_FULL>(d, K, cent, cnorm, n, u, which, k0, kend, slices, Cpad, cur, nullptr,
+                                          round % kRoundNumbers, fused ? won : nullptr, false, smem);
+        if (fused) {  // (one slice: a range of the sort, as in assign_kernel)
+            __syncthreads();
+            sort_range<8, kFusedRun / 2, false>(d, thread_of(wave), u, n, range, wgs, k0, kend, keys_per_wg / 8, 8, nbits, round, 1, (int *)smem,
+                                                nullptr, nullptr, [=](int i) { return (uint32_t)won[i - k0]; }, [](uint32_t w) { return w; }, [](int) { return 0.f; });
+        }
+        return;
+    }
+    if (blockIdx.x == 0 && tid == 0) head[0] = 0;  // (for the next round's near_lists)
+    // ---- which centroids moved, and the run's marked keys: whose own centroid moved from the front of the key list on,
+    // the others from its end
+    int ncent = 0, n_all, n_moved;
+    uint32_t *marked;
+    {
+        const Near x = near_of(d, u, n);
+        marked = x.list + (size_t)which * n + k0;
+        const int lane = tid & 63;
+        uint32_t m = 0;
+        int held = 0;
+        if (tid * 16 < Cpad) m = moved_of_16(d.moved + (size_t)u * Cpad, tid, held);
+        const int cnt = __popc(m), incl = wave_scan_add(cnt);
+        if (lane == 63) sh_wave[wave] = incl;
+        if (tid < 2) sh_marked[tid] = 0;
+        if (tid < 2 * kAssignTile) best[tid] = 0ull;
+        __syncthreads();
+        int pos = incl - cnt;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) {
+            const int y = sh_wave[w];
+            pos += w < wave ? y : 0;
+            ncent += y;
+        }
+        ncent = __builtin_amdgcn_readfirstlane(ncent);
+        for (; m; m &= m - 1) list[pos++] = (uint16_t)(tid * 16 + __ffs(m) - 1);
+        __syncthreads();  // (sh_wave is used again)
+        const uint32_t mark = near_mark(round);
+        const unsigned char *open = x.open + k0;
+        const int len = kend - k0;
+        // 16 keys from i0 on: those whose own centroid moved, and the others (masks)
+        auto split = [&](int i0, uint32_t &front, uint32_t &back) {
+            uint4 w = make_uint4(0, 0, 0, 0);
+            if (i0 < len) w = *(const uint4 *)(open + i0);  // (k0 is a multiple of 256)
+            const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
+            front = back = 0;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const uint32_t v = ws[e >> 2] >> (8 * (e & 3)) & 255u;
+                front |= v == mark ? 1u << e : 0u;
+                back |= v != 0u && v != mark ? 1u << e : 0u;
+            }
+            const uint32_t valid = i0 + 16 <= len ? 0xFFFFu : (1u << max(len - i0, 0)) - 1u;
+            front &= valid;
+            back &= valid;
+        };
+        int others = 0;
+        for (int b = 16 * tid; b < len; b += 16 * 512) {
+            uint32_t front, back;
+            split(b, front, back);
+            others += __popc(back);
+        }
+        others = __builtin_amdgcn_readlane(wave_scan_add(others), 63);
+        if (lane == 0) sh_wave[wave] = others;
+        __syncthreads();
+        others = 0;
+#pragma unroll
+        for (int w = 0; w < 8; ++w) others += sh_wave[w];
+        others = __builtin_amdgcn_readfirstlane(others);
+        // One pass of all marked keys against all centroids, in the first round (no winner of a round before stands behind the marks) and
+        // where the others cost no more there than by themselves against the moved ones: in tiles of 256 keys x 512 centroids, of
+        // which a pass's prologue takes about 3/4, x = others / 256 and 3/4 of a tile per 512 moved centroids + x * moved / all.
+        // (Else the workgroup has every slices-th 16 of them.)
+        const bool one_pass = round == 1 || (long long)others * (Cpad - ncent) <= 192ll * ((ncent + 511) / 512) * Cpad;
+        for (int b = 0; b < len; b += 16 * 512) {
+            const int i0 = b + 16 * tid;
+            uint32_t front, back;
+            split(i0, front, back);
+            if (one_pass) front |= back;
+            if (one_pass || (i0 >> 4) % slices != which) back = 0;
+            const int nf = __popc(front), nb = __popc(back), scan = wave_scan_add(nf | nb << 16);
+            int base_f = 0, base_b = 0;
+            if (lane == 63) {
+                base_f = atomicAdd(&sh_marked[0], scan & 0xFFFF);
+                base_b = atomicAdd(&sh_marked[1], scan >> 16);
+            }
+            int pf = __builtin_amdgcn_readlane(base_f, 63) + (scan & 0xFFFF) - nf, pb = __builtin_amdgcn_readlane(base_b, 63) + (scan >> 16) - nb;
+            for (; front; front &= front - 1) marked[pf++] = (uint32_t)(k0 + i0 + __ffs(front) - 1);
+            for (; back; back &= back - 1) marked[len - 1 - pb++] = (uint32_t)(k0 + i0 + __ffs(back) - 1);
+        }
+        wait_vmem();  // (the key lists of all waves are read by all)
+        __threadfence_block();
+        __syncthreads();
+        n_all = __builtin_amdgcn_readfirstlane(sh_marked[0]);
+        n_moved = __builtin_amdgcn_readfirstlane(sh_marked[1]);
+        const int count = (which == 0 ? n_all : 0) + n_moved;
+        if (tid == 0 && count > 0) atomicAdd(&head[1 + (round & 1)], count);
+    }
+    const bf16_t *Ku = K + (size_t)u * n * kD;
+
+    MarkedJob job{false, n_all, min(Cpad, (which + 1) * 512), 1, slices, (uint32_t)(round % kRoundNumbers), packed, marked, list, 0ull};
+    int c_first = which * 512;
+    for (;;) {
+        if (job.nk > 0) later_slices<AUG>(d, Ku, cent, cnorm, u, Cpad, cur, wave, c_first, tid, keys, best, seeds, kext, cext, job);
+        if (job.moved) break;
+        job.moved = true;
+        job.nk = n_moved;
+        job.keys = marked + (kend - k0 - 1);
+        job.dir = -1;
+        job.ncent = ncent;
+        c_first = 0;
+        __syncthreads();
+    }
+    if (fused) {  // the run is a range of the sort as well
+        wait_vmem();
+        __threadfence_block();
+        __syncthreads();
+        const uint32_t *pk = (const uint32_t *)packed;
+        sort_range<8, kFusedRun / 2, false>(d, thread_of(wave), u, n, range, wgs, k0, kend, keys_per_wg / 8, 8, nbits, round, 1,
+                                            (int *)smem, nullptr, nullptr, [=](int i) { return pk[2 * i]; }, cluster_of_word, [](int) { return 0.f; });
+    }
+}
+
+// Rounds this way, from the second on, where a full one is at least 16 tiles of 256 keys x 512 centroids per workgroup (about 110 us).
+// Builds of ten rounds, us, by the centroids that moved from the third round on (reassign_kernel) and so: 8 units x 131072 x 2048 with
+// 5 % outliers (64 tiles) 3690 and 2300; the benchmark's mixture 8 x 131072 x 1024 (32) 2554 and 1588, x 1310 transformed 3189 and 2030,
+// 64 x 32768 x 512 (32) 2720 and 2204, 8 x 65536 x 1024 (16) 1080 and 924, 2 x 131072 x 2048 (16) 1040 and 852, 16 x 32768 x 768 (16)
+// 904 and 864, 256 x 32768 x 512 10920 and 8690; below the line 8 x 49152 x 768 (12) 819 and 775, 1 x 131072 x 2048 (8) 687 and 662, 4 x
+// 65536 x 1024 (8) 677 and 685, 2 x 32768 x 2048 (4) 302 and 377, 8 x 32768 x 512 (4) 492 and 567.  Keys without any structure pay for
+// finding that out and for two empty launches in each later round: 8 x 131072 x 2048 5307 and 5395, 256 x 32768 x 512 15620 and 16000, 8 x
+// 65536 x 1024 1652 and 1720.  (The line leaves out the gains of 3 to 6 % right below it: such keys lose as much there, 8 x 49152 x 768
+// 1176 and 1248.)
+// Of the 2300 us of 8 x 131072 x 2048: first round 440, then near_lists 32 and eight times 19, near 80 to 18, marked 130 to 32,
+// sort 16, means 55 to 14 each, page copy 190.
+constexpr int kNearMinSteps = 16;
+bool near_pays(const Dev &d, int n) {
+    if (d.Cpad > kNearMaxClusters || n > kMaxNearTokens || !reassign_pays(d, n)) return false;
+    const RoundPlan p = round_plan(d, n);
+    return p.all_turns * p.all_run * p.tiles >= 16 * kNearMinSteps;
+}
+
+void launch_near(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fused, hipStream_t st) {
+    const int slices = assign_slices(d), run = assign_run(d.U, n, slices), wgs = ((n + kAssignTile - 1) / kAssignTile + run - 1) / run;
+    const int L = sort_len(d, n), R = (n + L - 1) / L;
+    const int *go = round_goes(d, t);
+    const size_t near_lds = near_lists_lds_bytes(d.Cpad);
+#define ICE_NEAR_LISTS(aug)                                                                                                \
+    do {                                                                                                                   \
+        allow_dynamic_lds((const void *)near_lists_kernel<aug>, near_lds);                                                 \
+        hipLaunchKernelGGL(near_lists_kernel<aug>, dim3((d.C + kNearA - 1) / kNearA * d.U), dim3(512), near_lds, st, d.cent_bf16[cur], d.cnorm[cur], n, \
+                           d.Cpad, cur, K, go, t, R, L, d);                                                                         \
+    } while (0)
+    if (d.tk) ICE_NEAR_LISTS(true);
+    else ICE_NEAR_LISTS(false);
+#undef ICE_NEAR_LISTS
+    // as many waves as the chip holds at once, at most one per chunk
+    const int waves = (int)std::min<long long>((2048 + d.U - 1) / d.U, (long long)d.C + n / kNearChunk);
+#define ICE_NEAR(aug, np)                                                                                                  \
+    hipLaunchKernelGGL((near_kernel<aug, np>), dim3(waves * d.U), dim3(64), 0, st, K, d.cent_bf16[cur], d.cnorm[cur], n, d.Cpad, cur, go, t, R, L, d)
+#define ICE_NEAR_P(aug)                                                                                                    \
+    do {                                                                                                                   \
+        if (R == 1) ICE_NEAR(aug, 1);                                                                                      \
+        else if (R <= kFewPieces) ICE_NEAR(aug, kFewPieces);                                                               \
+        else ICE_NEAR(aug, 0);                                                                                             \
+    } while (0)
+    if (d.tk) ICE_NEAR_P(true);
+    else ICE_NEAR_P(false);
+#undef ICE_NEAR_P
+#undef ICE_NEAR
+    const size_t lds = std::max<size_t>(marked_lds_bytes(d.tk != 0, d.Cpad), assign_lds_bytes(d.tk != 0) + (fused ? (size_t)run * kAssignTile * 2 : 0));
+#define ICE_MARKED(aug, full)                                                                                              \
+    do {                                                                                                                   \
+        allow_dynamic_lds((const void *)marked_kernel<aug, full>, lds);                                                    \
+        hipLaunchKernelGGL((marked_kernel<aug, full>), dim3(wgs * slices, d.U), dim3(512), lds, st, K, d.cent_bf16[cur], d.cnorm[cur], n, d.Cpad, \
+                           cur, go, t, fused ? 1 : 0, run, wgs, slices, d);                                                \
+    } while (0)
+    const bool full = d.Cpad / 32 % 16 == 0;
+    if (d.tk) { if (full) ICE_MARKED(true, true); else ICE_MARKED(true, false); }
+    else { if (full) ICE_MARKED(false, true); else ICE_MARKED(false, false); }
+#undef ICE_MARKED
+}
+
+void build_plan(const Dev &d, int n, int *plan) {
+    plan[0] = sort_is_fused(d, n) ? 1 : 0;
+    plan[1] = sort_len(d, n);
+    plan[2] = (n + plan[1] - 1) / plan[1];
+    plan[3] = near_pays(d, n) ? 1 : reassign_pays(d, n) ? 2 : 0;
+    plan[4] = assign_run(d.U, n, 1);
+    plan[5] = assign_slices(d);
+}
+
+// ------------------------------------------------------------------------------------------------
+// The sort by itself
+template <int NG, bool MASK>
+__global__ __launch_bounds__(1024) void range_sort_kernel(Dev d, int n, int L, int W, int nbits, int round, float *best_out,
+                                                          int *assign_out) {
+    extern __shared__ __align__(16) int pos_all[];  // [W][Cpad]
+    const int r = blockIdx.x, u = blockIdx.y;
+    const int goes = round > 0 ? d.any_moved[2 * u + ((round - 1) & 1)] : 1;
+    if (r == 0 && threadIdx.x == 0) d.any_moved[2 * u + (round & 1)] = 0;  // (for this round's means)
+    // (a winner's low word holds its cluster; the whole of it is read only for best_out)
+    const u64 *packed = d.packed + (size_t)u * d.max_tokens;
+    const uint32_t *pk = (const uint32_t *)packed;
+    sort_range<16, NG, MASK>(d, threadIdx.x, u, n, r, gridDim.x, r * L, min(n, r * L + L), L / W, W, nbits, round, goes, pos_all, best_out, assign_out,
+                             [=](int i) { return pk[2 * i]; }, cluster_of_word, [=](int i) { return -2.0f * ordered_f32((uint32_t)(packed[i] >> 13)); });
+}
+
+void launch_sort(const Dev &d, int n, int t, float *best_out, int *assign_out, hipStream_t st) {
+    const int L = sort_len(d, n), R = (n + L - 1) / L, W = sort_segments(d.Cpad);
+    int nbits = 0;
+    while ((1 << nbits) < d.Cpad) ++nbits;
+    const bool masks = L / W > 4 * 64 && W * d.Cpad * 3 <= kSortCounters;
+    const size_t lds = (size_t)W * d.Cpad * (masks ? 12 : 4);
+#define ICE_SORT(ng, mk)                                                                                                   \
+    do {                                                                                                                   \
+        allow_dynamic_lds((const void *)range_sort_kernel<ng, mk>, lds);                                                   \
+        hipLaunchKernelGGL((range_sort_kernel<ng, mk>), dim3(R, d.U), dim3(1024), lds, st, d, n, L, W, nbits, t, best_out, assign_out); \
+    } while (0)
+    if (L / W <= 4 * 64) ICE_SORT(4, false);
+    else if (L / W <= 16 * 64) { if (masks) ICE_SORT(16, true); else ICE_SORT(16, false); }
+    else { if (masks) ICE_SORT(32, true); else ICE_SORT(32, false); }
+#undef ICE_SORT
+}
+
 // One wave counts the members of a cluster and lists their indexes into `order` in slots[0..kMemberSlots), piece by piece,
 // as long as they fit and no piece has more than kMemberPiece of them (*listed): one read per member instead of a search.
-constexpr int kMemberSlots = 512, kMemberPiece = 32, kFewPieces = 8;
+constexpr int kMemberSlots = 512, kMemberPiece = 32;
 constexpr int kAugAlone = 256, kAugChunk = 1024;
 __device__ inline int list_members(const Pieces &pieces, uint32_t word0, int lane, int *slots, bool *listed) {
     int total = 0;
@@ -1716,7 +2565,7 @@ __global__ __launch_bounds__(256, 8) void means_kernel(Dev d, const bf16_t *__re
     // (stored here and not where it is known: the first loads' wait would cover an earlier store)
     if (lane == 0) {
         d.cluster_cnt[(size_t)u * d.C + c] = cnt;
-        d.moved[row] = moved ? (uint32_t)cnt << 1 | 1u : 0u;
+        d.moved[row] = (uint32_t)cnt << 1 | (moved ? 1u : 0u);
         if (moved) d.any_moved[2 * u + (round & 1)] = 1;
         d.touched[row] = 0;
     }

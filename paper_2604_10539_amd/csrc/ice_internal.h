@@ -63,7 +63,7 @@ struct Dev {
     int *assign;                // [U][max_tokens]
     unsigned long long *packed; // [U][max_tokens] a key's winner: round, ordered score, ~cluster (winner_word)
     int *order;                 // [U][max_tokens] tokens sorted by (cluster, position) inside every range of the sort
-    uint32_t *moved;            // [U][Cpad] members << 1 | 1 where the last round's means changed the centroid's bits, else 0
+    uint32_t *moved;            // [U][Cpad] members << 1 where the last round changed the members, | 1 where it changed the centroid's bits
     unsigned char *touched;     // [U][Cpad] the cluster lost or gained a token since the last means (zero between rounds)
     int *any_moved;             // [U][2] some centroid of the unit moved: in even rounds, in odd ones
     int *large_keys;            // [U] some key's magnitude is 2^59 or more, infinite or NaN: a score may not be a number
@@ -104,15 +104,17 @@ void launch_load_centroids(const Dev &d, const bf16_t *cent, int cur, hipStream_
 void launch_key_aug(const Dev &d, const bf16_t *K, int n, hipStream_t st);
 // The stages of round t of a build; t = 0 by itself stands for the whole stage.  A later round does again what changed since the
 // one before and leaves what all of it would: its assignment either by launch_assign (units of which a centroid moved) or, where
-// reassign_pays, by launch_reassign (units of which few moved: those centroids only); tokens are sorted and means formed where a
-// token went elsewhere.
+// reassign_pays, by launch_reassign (units of which few moved: those centroids only) or, where near_pays, by launch_near (a cluster's
+// keys against the centroids near its own); tokens are sorted and means formed where a token went elsewhere.
 // fused: with the sort of its runs (sort_is_fused), else launch_sort follows
-// look: also looks for keys that reassign_kernel has to know of (large_keys; transformed keys: launch_key_aug does)
+// look: also looks for keys that these two have to know of (large_keys; transformed keys: launch_key_aug does)
 void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fused, bool look, hipStream_t st);
 bool sort_is_fused(const Dev &d, int n);
 bool reassign_pays(const Dev &d, int n);     // for rounds t >= 2 but the multiples of kRoundNumbers
 constexpr int kRoundNumbers = 1 << 19;       // rounds that the winners' words tell apart (launch_assign starts them anew)
 void launch_reassign(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fused, hipStream_t st);
+bool near_pays(const Dev &d, int n);         // for rounds t >= 1 but those
+void launch_near(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fused, hipStream_t st);
 void build_plan(const Dev &d, int n, int *plan);  // ice_debug_build_plan
 void launch_sort(const Dev &d, int n, int t, float *best_out_or_null, int *assign_out_or_null, hipStream_t st);
 size_t sort_ranges_max(int U, int max_tokens, int Cpad);  // (unit, range) pairs of any sort of at most max_tokens tokens

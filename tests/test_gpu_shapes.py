@@ -566,6 +566,54 @@ def test_later_rounds_that_score_what_moved_leave_what_all_centroids_would(U, n,
         _every_stage_again(K, V, init, C, tk, T)
 
 
+@pytest.mark.parametrize("U,n,C,tk,data,ranges,fused", [
+    (256, 8200, 600, 0, "mix", 1, 0),      # a cluster is one piece; two slices, the second hardly begun; a ragged last tile
+    (300, 6100, 300, 1, "mix", 1, 0),      # more units than workgroups of a round, transformed keys
+    (32, 32768, 512, 0, "out", 8, 1),      # eight pieces, one full slice with the sort inside
+    (33, 28000, 417, 1, "mix", 7, 1),      # ... transformed, a slice that is not full, a last block of few centroids
+    (6, 65000, 1100, 0, "out", 32, 0),     # more pieces than a member is picked from directly
+    (2, 131072, 1600, 1, "out", 64, 0),
+    (1, 262144, 2112, 0, "mix", 64, 0),    # five slices; one tile of rows at a time
+    (1, 1100000, 3000, 0, "mix", 68, 0),   # more pieces than a wave holds
+    (8, 65536, 1024, 0, "lump", 32, 0),    # a cluster of a third of the keys, equal keys, centroids that are the same
+    (8, 65536, 1024, 1, "lump", 32, 0),
+    (8, 65536, 1024, 0, "few", 32, 0),     # components far fewer than clusters: lists that come out too long, centroids that go on moving
+    (8, 65536, 1024, 0, "half", 32, 0),    # every other unit without structure: those take all in every round
+    (8, 65536, 1024, 1, "odd", 32, 0),     # units with keys that are not finite beside units of which all are
+])
+def test_later_rounds_by_the_centroids_near_a_keys_own_leave_what_all_would(U, n, C, tk, data, ranges, fused):
+    """The same where every later round takes the keys of a cluster to the centroids near its own and only the keys that this
+    leaves open to more of them, from the second round on until hardly any centroid moves."""
+    import torch
+    from paper_2604_10539_amd import ice_debug_build_plan, make_config
+    p = ice_debug_build_plan(make_config(1, U, 4, n), n, C)
+    assert (p["reassign_from"], p["ranges"], p["fused"]) == (1, ranges, fused)
+    gen = torch.Generator(device="cuda").manual_seed(U * n + C)
+    K = torch.empty(1, U, n, D, dtype=torch.int16, device="cuda")
+    M = C // 20 if data == "few" else C // 2
+    for u in range(U):
+        x = torch.randn(n, D, generator=gen, device="cuda")
+        if data != "half" or u % 2 == 0:
+            x = 0.3 * x + torch.randn(M, D, generator=gen, device="cuda")[torch.randint(M, (n,), generator=gen, device="cuda")]
+        if data == "out":
+            far = torch.rand(n, generator=gen, device="cuda") < 0.05
+            x = torch.where(far[:, None], 6 * torch.rand(n, D, generator=gen, device="cuda") - 3, x)
+        if data == "lump":
+            x[n // 2: n // 2 + n // 3] = 0.01 * x[n // 2: n // 2 + n // 3]
+            x[100:400] = x[100:101]
+        K[0, u] = x.to(torch.bfloat16).view(torch.int16)
+    if data == "odd":
+        for i, t in enumerate(range(5, n, 2111)):
+            K[0, ::2, t, i % D:] = [0x7FC0, 0x7F80, 0xFF80 - 65536, 0xFFC0 - 65536, 0x5F80, 0xDF80 - 65536][i % 6]
+    V = torch.randint(-16000, 16000, K.shape, generator=gen, device="cuda", dtype=torch.int16)
+    init = torch.stack([torch.sort(torch.randperm(n, generator=gen, device="cuda")[:C])[0] for _ in range(U)])
+    if data == "lump":
+        init[:, 10:50] = torch.arange(100, 140, device="cuda")  # (centroids on equal keys)
+    init = init.int()[None].contiguous()
+    for T in (2, 3, 4, 6, 9):
+        _every_stage_again(K, V, init, C, tk, T)
+
+
 def test_later_rounds_where_scores_stop_comparing():
     """A cluster that takes in an infinite key in the third round has a mean with which most scores do not compare in the
     fourth.  With eight NaN rows around it since the start, the full contraction finds nine NaN side by side, which hide the
