@@ -1724,23 +1724,9 @@ __global__ __launch_bounds__(NW * 64, EMAX * NW <= 64 ? 4 : 1) void decode_step_
                 if ((bal >> lane) & 1ull) sel_comp[base + (int)__popcll(bal & lower)] = ((u64)key[e] << 32) | (u64)(0xFFFFFFFFu - (uint32_t)pid);
                 base += (int)__popcll(bal);
             }
-        } else if (M <= 512) {
-            // every candidate counts the candidates that beat it; `parts` lanes share one candidate
-            int lp = 0;
-            while (lp < 6 && (M << (lp + 1)) <= NT) ++lp;
-            const int parts = 1 << lp, i = tid >> lp, part = tid & (parts - 1), len = (M + parts - 1) >> lp;
-            const u64 mine = i < M ? cand[i] : ~0ull;
-            int rank = 0;
-#pragma unroll 4
-            for (int j = part * len; j < min(M, (part + 1) * len); ++j) rank += cand[j] > mine;
-            // sum over the `parts` lanes of a candidate: DPP inside a 16-lane row, shuffles beyond
-            if (parts >= 2) rank += (int)dpp_u32<0xB1>((uint32_t)rank);
-            if (parts >= 4) rank += (int)dpp_u32<0x4E>((uint32_t)rank);
-            if (parts >= 8) rank += (int)dpp_u32<0x141>((uint32_t)rank);
-            if (parts >= 16) rank += (int)dpp_u32<0x140>((uint32_t)rank);
-            if (parts >= 32) rank += __shfl_xor(rank, 16);
-            if (parts >= 64) rank += __shfl_xor(rank, 32);
-            if (part == 0 && i < M && rank < need) sel_comp[first + rank] = mine;
+        } else if (M <= kRankMax) {
+            if constexpr (NW == 8) rank_lanes<NW>(cand, M, need, tid, sel_comp + first);
+            else rank_composites<NW>(cand, M, need, wave, lane, sel_comp + first);
         } else {
             // radix select on LDS histograms, 8 bits a pass, over the (32 + nb)-bit packed composite
             int nb = 0;

@@ -69,6 +69,59 @@ __device__ inline void place_by_id(const u64 *win, int n, int part, int parts, i
     }
 }
 
+// The `need` best of n <= kRankMax distinct 64-bit composites (LDS), best first, into sel[0 .. need), by the NW waves of a
+// workgroup (a barrier in front and behind is the caller's).  Bound by vector instructions (four waves to a SIMD) and the trips to
+// LDS.  rank_blocks: every wave holds all of them on its lanes and counts, for each of its share, those above it with a lane
+// mask.  rank_lanes: up to 64 lanes to a composite walk a part of the list each; it is the flat step's with eight waves, two such
+// workgroups to a CU.  (16 waves: 84 of 512 0.8 and 2.3 us, the step of 8 units x 2300 pages, about 25 listed, 11.89 and 12.07; eight
+// waves, 312 units x 460 pages, as many listed, 35.3 and 34.9.)
+constexpr int kRankMax = 512;
+template <int NW>
+__device__ inline void rank_lanes(const u64 *cand, int n, int need, int tid, u64 *sel) {
+    constexpr int NT = NW * 64;
+    static_assert(kRankMax <= NT, "a lane to a composite at least");
+    int lp = 0;
+    while (lp < 6 && (n << (lp + 1)) <= NT) ++lp;
+    const int parts = 1 << lp, i = tid >> lp, part = tid & (parts - 1), len = (n + parts - 1) >> lp;
+    const u64 mine = i < n ? cand[i] : ~0ull;
+    int rank = 0;
+#pragma unroll 4
+    for (int j = part * len; j < min(n, (part + 1) * len); ++j) rank += cand[j] > mine;
+    // sum over the `parts` lanes of a candidate: DPP inside a 16-lane row, shuffles beyond
+    if (parts >= 2) rank += (int)dpp_u32<0xB1>((uint32_t)rank);
+    if (parts >= 4) rank += (int)dpp_u32<0x4E>((uint32_t)rank);
+    if (parts >= 8) rank += (int)dpp_u32<0x141>((uint32_t)rank);
+    if (parts >= 16) rank += (int)dpp_u32<0x140>((uint32_t)rank);
+    if (parts >= 32) rank += __shfl_xor(rank, 16);
+    if (parts >= 64) rank += __shfl_xor(rank, 32);
+    if (part == 0 && i < n && rank < need) sel[rank] = mine;
+}
+template <int NB, int NW>
+__device__ inline void rank_blocks(const u64 *cand, int n, int need, int wave, int lane, u64 *sel) {
+    u64 c[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) c[b] = 64 * b + lane < n ? cand[64 * b + lane] : 0ull;
+    const u64 own = cand[min(wave + lane * NW, n - 1)];  // this wave's: wave, wave + NW, ... (at most 64: n <= 64 NW)
+    const int cnt = (n - wave + NW - 1) / NW;
+    int rank = 0;
+    for (int x = 0; x < cnt; ++x) {
+        const u64 mine = (u64)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(own >> 32), x) << 32 |
+                         (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)own, x);
+        int r = 0;
+#pragma unroll
+        for (int b = 0; b < NB; ++b) r += (int)__popcll(__ballot(c[b] > mine));
+        rank = lane == x ? r : rank;
+    }
+    if (lane < cnt && rank < need) sel[rank] = own;
+}
+template <int NW>
+__device__ inline void rank_composites(const u64 *cand, int n, int need, int wave, int lane, u64 *sel) {
+    static_assert(kRankMax <= 64 * NW, "a wave's share on its lanes");
+    if (n <= 64) rank_blocks<1, NW>(cand, n, need, wave, lane, sel);
+    else if (n <= 128) rank_blocks<2, NW>(cand, n, need, wave, lane, sel);
+    else rank_blocks<kRankMax / 64, NW>(cand, n, need, wave, lane, sel);
+}
+
 // The set bits of a mask of `words` 32-bit words (LDS) in ascending order, by one wave: out[0], out[1], ...
 __device__ inline void list_bits(const uint32_t *mask, int words, int lane, int *out) {
     int before = 0;

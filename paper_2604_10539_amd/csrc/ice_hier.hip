@@ -16,7 +16,7 @@ namespace ice {
 
 namespace {
 
-constexpr int kListCap = 512;  // entries of the short list that is ranked by all-pairs counting
+constexpr int kListCap = kRankMax;  // entries of the short list that is ranked by counting
 
 struct SelShared {
     int M, W, M2, A;
@@ -28,8 +28,11 @@ struct SelShared {
 // Exact top-k of n distinct 64-bit composites (ordered score << 32 | ~id) held in LDS, into
 // sel[0..k) (in no particular order); requires
 // 1 <= k < n.  First a 32-bit threshold that at least k keys reach, and few more:
-//   k <= 2*NW  the k-th largest of the 4*NW sixteen-lane row maxima, element j belonging to row
-//              j mod 4*NW (so short arrays still spread over every row);
+//   k <= 2*NW  the k-th largest of the maxima of 4*NW groups, element j belonging to group
+//              j mod 4*NW (so short arrays still spread over every group);
+//   k <= 8*NW  the same with 8*NW or 16*NW groups, whichever is the first to be 2*k at least.  The maxima are made distinct
+//              by the group's number in their low byte (any value that k keys reach will do), so that ranking them is
+//              one comparison per pair;
 //   else       the 16-bit key prefix of the k-th largest key, from two 8-bit LDS histograms.
 // What passes goes to a short list that is ranked by counting; with the prefix threshold only the
 // keys that share the prefix are listed (those above it are winners as they are, and the
@@ -38,19 +41,22 @@ struct SelShared {
 // histograms runs on the whole array instead.  `nb` = bits of
 // the id field that can be set.  hist: 2 x 272 ints.  Every thread of the workgroup must call it;
 // it ends with a barrier.
+// Bound by its chain of LDS trips and barriers, which wait for LDS only (no wave waits for a store to memory here).
+// 16 waves, 64 of 512: 3.3 us by histograms, 2.6 by groups; 16 of 290 2.75 with barriers that waited for the stores in front and
+// the list ranked by rank_lanes, 1.85 so.  (One wave alone, bit by bit on its registers without any barrier: 2.8 for either.)
 template <int NW>
 __device__ void select_topk_lds(const u64 *comp, int n, int k, int nb, u64 *sel, u64 *list, int *hist, SelShared &sh) {
     constexpr int NT = NW * 64, NR = 4 * NW;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (tid == 0) { sh.M = 0; sh.W = 0; sh.A = 0; sh.pre = 0u; sh.tau = 0ull; }
-    const bool by_prefix = k > NR / 2;
-    if (!by_prefix) {
+    const bool by_prefix = k > 2 * NR;
+    if (k <= NR / 2) {
         const int row = tid >> 4, l16 = tid & 15;
         uint32_t lmax = 0u;
         for (int j = row + NR * l16; j < n; j += NR * 16) lmax = max(lmax, (uint32_t)(comp[j] >> 32));
         lmax = row16_max_u32(lmax);
         if (l16 == 0) sh.rowmax[row] = lmax;
-        __syncthreads();
+        lds_barrier();
         const uint32_t v = sh.rowmax[row];
         uint32_t c = 0;
 #pragma unroll
@@ -61,11 +67,39 @@ __device__ void select_topk_lds(const u64 *comp, int n, int k, int nb, u64 *sel,
         }
         c = row16_sum_u32(c);
         if (l16 == 0 && (int)c == k - 1) sh.pre = v;
+    } else if (!by_prefix) {
+        // (an empty group's maximum is below 256, its threshold 0: it lets every key through)
+        auto by_groups = [&](auto log_lanes) {
+            constexpr int LG = decltype(log_lanes)::value, LANES = 1 << LG, NGR = NT >> LG;  // lanes per group, groups
+            static_assert(NGR <= 256 && NGR % (4 * LANES) == 0, "a group's number in a byte, its comparisons in fours");
+            const int own = tid >> LG, part = tid & (LANES - 1);
+            uint32_t v = 0u;
+            for (int j = own + NGR * part; j < n; j += NT) v = max(v, (uint32_t)(comp[j] >> 32));
+            v = max(v, dpp_u32<0xB1>(v));
+            v = max(v, dpp_u32<0x4E>(v));
+            if (LG == 3) v = max(v, dpp_u32<0x141>(v));
+            v = (v & 0xFFFFFF00u) | (uint32_t)(255 - own);
+            if (part == 0) hist[own] = (int)v;
+            lds_barrier();
+            const uint4 *others = (const uint4 *)hist + part * (NGR / LANES / 4);  // the lanes of a group share its comparisons
+            uint32_t c = 0;
+#pragma unroll
+            for (int jj = 0; jj < NGR / LANES / 4; ++jj) {
+                const uint4 o = others[jj];
+                c += (o.x > v ? 1u : 0u) + (o.y > v ? 1u : 0u) + (o.z > v ? 1u : 0u) + (o.w > v ? 1u : 0u);
+            }
+            c += dpp_u32<0xB1>(c);
+            c += dpp_u32<0x4E>(c);
+            if (LG == 3) c += dpp_u32<0x141>(c);
+            if (part == 0 && (int)c == k - 1) sh.pre = v & 0xFFFFFF00u;
+        };
+        if (k <= NR) by_groups(std::integral_constant<int, 3>{});
+        else by_groups(std::integral_constant<int, 2>{});
     } else {
         // bucket of the k-th largest key by its top byte, then by its second byte inside that bucket
         int *h0 = hist, *h1 = hist + 272;
         if (tid < 256) { h0[tid] = 0; h1[tid] = 0; }
-        __syncthreads();
+        lds_barrier();
         auto find_bucket = [&](int *h, int kk, int shift) {  // bins in descending order: thread t owns bin 255 - t
             int mine = 0, incl = 0;
             if (tid < 256) {
@@ -73,7 +107,7 @@ __device__ void select_topk_lds(const u64 *comp, int n, int k, int nb, u64 *sel,
                 incl = wave_scan_add(mine);
                 if (lane == 63) h[256 + wave] = incl;
             }
-            __syncthreads();
+            lds_barrier();
             if (tid < 256) {
                 for (int w2 = 0; w2 < wave; ++w2) incl += h[256 + w2];
                 const int excl = incl - mine;
@@ -82,7 +116,7 @@ __device__ void select_topk_lds(const u64 *comp, int n, int k, int nb, u64 *sel,
                     sh.M2 = kk - excl;
                 }
             }
-            __syncthreads();
+            lds_barrier();
         };
         // (the top byte is sign and exponent: most keys of a wave share it, so the lanes that agree
         // with the first active lane are counted with one update)
@@ -96,7 +130,7 @@ __device__ void select_topk_lds(const u64 *comp, int n, int k, int nb, u64 *sel,
             if (lane == (int)__builtin_ctzll(act)) atomicAdd(&h0[first_bin], (int)__popcll(same));
             if (bin >= 0 && bin != first_bin) atomicAdd(&h0[bin], 1);
         }
-        __syncthreads();
+        lds_barrier();
         find_bucket(h0, k, 24);
         const uint32_t top = sh.pre >> 24;
         const int k2 = sh.M2;
@@ -104,75 +138,61 @@ __device__ void select_topk_lds(const u64 *comp, int n, int k, int nb, u64 *sel,
             const uint32_t key = (uint32_t)(comp[j] >> 32);
             if ((key >> 24) == top) atomicAdd(&h1[(int)((key >> 16) & 255u)], 1);
         }
-        __syncthreads();
+        lds_barrier();
         find_bucket(h1, k2, 16);
     }
-    __syncthreads();
+    lds_barrier();
     const uint32_t pre = sh.pre;
     // With the prefix threshold: keys above the prefix are winners (k - need of them, need = what
     // the histograms left for the prefix's own bucket) and go straight to sel; the bucket is listed.
-    // With the row-maxima threshold: everything at or above it is listed (>= k entries).
+    // With the group maxima's threshold: everything at or above it is listed (>= k entries).
     const int need = by_prefix ? sh.M2 : k, first = k - need;
-    for (int j0 = 0; j0 < n; j0 += NT) {
-        const int j = j0 + tid;
+    const u64 lower = (1ull << lane) - 1ull;
+    for (int j0 = wave * 64; j0 < n; j0 += NT) {  // (wave-uniform)
+        const int j = j0 + lane;
         const u64 cc = j < n ? comp[j] : 0ull;
         const uint32_t key = (uint32_t)(cc >> 32);
         const bool above = j < n && by_prefix && (key >> 16) > (pre >> 16);
         const bool is = j < n && key >= pre && !above;
-        const u64 bal = __ballot(is), bal_a = __ballot(above);
-        int base = 0, base_a = 0;
-        if (lane == 0 && bal) base = atomicAdd(&sh.M, (int)__popcll(bal));
-        if (lane == 0 && bal_a) base_a = atomicAdd(&sh.A, (int)__popcll(bal_a));
-        base = __shfl(base, 0);
-        base_a = __shfl(base_a, 0);
-        const u64 lower = (1ull << lane) - 1ull;
-        const int slot = base + (int)__popcll(bal & lower);
-        if (is && slot < kListCap) list[slot] = cc;
-        if (above) sel[base_a + (int)__popcll(bal_a & lower)] = cc;  // (exactly `first` of them)
-    }
-    __syncthreads();
-    const int M = sh.M;
-    const bool listed = M <= kListCap;
-    if (listed) {
-        // every listed composite counts the listed composites that beat it
-        int lp = 0;
-        while (lp < 6 && (M << (lp + 1)) <= NT) ++lp;
-        const int parts = 1 << lp, len = (M + parts - 1) >> lp;
-        for (int i0 = 0; i0 < M; i0 += NT >> lp) {
-            const int ii = i0 + (tid >> lp), part2 = tid & (parts - 1);
-            const u64 mine = ii < M ? list[ii] : ~0ull;
-            int rank = 0;
-#pragma unroll 8
-            for (int j = part2 * len; j < min(M, (part2 + 1) * len); ++j) rank += list[j] > mine;
-            if (parts >= 2) rank += (int)dpp_u32<0xB1>((uint32_t)rank);
-            if (parts >= 4) rank += (int)dpp_u32<0x4E>((uint32_t)rank);
-            if (parts >= 8) rank += (int)dpp_u32<0x141>((uint32_t)rank);
-            if (parts >= 16) rank += (int)dpp_u32<0x140>((uint32_t)rank);
-            if (parts >= 32) rank += __shfl_xor(rank, 16);
-            if (parts >= 64) rank += __shfl_xor(rank, 32);
-            if (part2 == 0 && ii < M && rank < need) sel[first + rank] = mine;
+        const u64 bal = __ballot(is);
+        if (bal) {
+            int base = 0;
+            if (lane == 0) base = atomicAdd(&sh.M, (int)__popcll(bal));
+            const int slot = __builtin_amdgcn_readfirstlane(base) + (int)__popcll(bal & lower);
+            if (is && slot < kListCap) list[slot] = cc;
+        }
+        if (by_prefix) {
+            const u64 bal_a = __ballot(above);
+            int base_a = 0;
+            if (lane == 0 && bal_a) base_a = atomicAdd(&sh.A, (int)__popcll(bal_a));
+            base_a = __builtin_amdgcn_readfirstlane(base_a);
+            if (above) sel[base_a + (int)__popcll(bal_a & lower)] = cc;  // (exactly `first` of them)
         }
     }
-    if (!listed) {  // (workgroup-uniform)
+    lds_barrier();
+    const int M = sh.M;
+    if (M <= kListCap) {
+        rank_composites<NW>(list, M, need, wave, lane, sel + first);
+    } else {  // (workgroup-uniform)
         const u64 idmask = (1ull << nb) - 1ull;
         u64 prefix = 0ull, known = 0ull;
         int kk = k;
         for (int sft = ((32 + nb - 1) / 8) * 8; sft >= 0; sft -= 8) {
             if (tid < 256) hist[tid] = 0;
-            __syncthreads();
+            lds_barrier();
             for (int t = tid; t < n; t += NT) {
                 const u64 cc = comp[t];
                 const u64 pk = ((cc >> 32) << nb) | (cc & idmask);
                 if ((pk & known) == prefix) atomicAdd(&hist[(int)((pk >> sft) & 255ull)], 1);
             }
-            __syncthreads();
+            lds_barrier();
             int h = 0, incl = 0;
             if (tid < 256) {  // bins in descending order: thread t owns bin 255 - t
                 h = hist[255 - tid];
                 incl = wave_scan_add(h);
                 if (lane == 63) hist[256 + wave] = incl;
             }
-            __syncthreads();
+            lds_barrier();
             if (tid < 256) {
                 for (int w2 = 0; w2 < wave; ++w2) incl += hist[256 + w2];
                 const int excl = incl - h;
@@ -181,11 +201,11 @@ __device__ void select_topk_lds(const u64 *comp, int n, int k, int nb, u64 *sel,
                     sh.M2 = kk - excl;
                 }
             }
-            __syncthreads();
+            lds_barrier();
             prefix = sh.tau;
             kk = sh.M2;
             known |= 255ull << sft;
-            __syncthreads();
+            lds_barrier();
         }
         // prefix = packed composite of the k-th largest; everything at or above it wins
         for (int t = tid; t < n; t += NT) {
@@ -194,7 +214,7 @@ __device__ void select_topk_lds(const u64 *comp, int n, int k, int nb, u64 *sel,
             if (pk >= prefix) sel[atomicAdd(&sh.W, 1)] = cc;
         }
     }
-    __syncthreads();
+    lds_barrier();
 }
 
 __host__ __device__ inline size_t align16(size_t x) { return (x + 15) & ~(size_t)15; }
@@ -261,18 +281,10 @@ __global__ __launch_bounds__(NW * 64) void decode_hier_kernel(int Cpad, int max_
     ICE_HSTAMP(0);
     const int np = n_pages[u];  // first needed in stage 2
     const int C = d.C;
-    // the page -> cluster table is requested now and used in stage 2; np_hint is the host's upper
-    // bound of the live pages (entries past the live pages are read and ignored)
-    int pcl[EMAX];
-    {
-        const int *pc = page_cluster + (size_t)u * max_pages;
-#pragma unroll
-        for (int e = 0; e < EMAX; ++e) pcl[e] = e * NT + tid < np_hint ? pc[e * NT + tid] : -1;
-    }
     // ---- stage 1 loads: 16 centroids per four MFMAs in the split-row form (SplitRow: whole
     // 128-byte lines per load instruction), four such blocks in flight per wave (rows of C..Cpad
     // are padding).  The first round is requested together with the query rows, before anything
-    // waits for either.
+    // waits for either; the query rows go first: their norms are worked out while the others are on their way.
     using SR = SplitRow<G>;
     const bf16_t *cb = cent_all + (size_t)u * Cpad * kD;
     const int nblk1 = Cpad >> 4;
@@ -290,13 +302,23 @@ __global__ __launch_bounds__(NW * 64) void decode_hier_kernel(int Cpad, int max_
             for (int j = 0; j < 4; ++j) bb1[x][j] = c0 < Cpad ? load16_stream(src + word[j]) : make_uint4(0, 0, 0, 0);
         }
     };
+    uint4 qw[2];
+    SR::request_query(q, u, lane, qw);
     if constexpr (!TOP) request1(wave);
+    // the page -> cluster table is requested now and used in stage 2; np_hint is the host's upper
+    // bound of the live pages (entries past the live pages are read and ignored)
+    int pcl[EMAX];
+    {
+        const int *pc = page_cluster + (size_t)u * max_pages;
+#pragma unroll
+        for (int e = 0; e < EMAX; ++e) pcl[e] = e * NT + tid < np_hint ? pc[e * NT + tid] : -1;
+    }
     // the query operand of every scoring MFMA, and 1/||q_h|| where the scores land
     bf16x8 qs[2];
     float inv[4];
     {
         float invn;
-        SR::load_query(q, u, lane, qs, &invn);
+        SR::take_query(qw, qs, &invn);
 #pragma unroll
         for (int v = 0; v < 4; ++v) inv[v] = __shfl(invn, (4 * SR::head_group(lane) + v) & 15);
     }
@@ -362,12 +384,12 @@ __global__ __launch_bounds__(NW * 64) void decode_hier_kernel(int Cpad, int max_
             b0 += NW * UNR1;
             if (b0 < nblk1) request1(b0);
         }
-        __syncthreads();
+        lds_barrier();
         ICE_HSTAMP(1);
         n_keep = min(n_probe, C);
         if (n_keep == C) {
             for (int c = tid; c < C; c += NT) sel1[c] = comp1[c];
-            __syncthreads();
+            lds_barrier();
         } else {
             int nb = 0;
             while ((1 << nb) < C) ++nb;
@@ -384,11 +406,11 @@ __global__ __launch_bounds__(NW * 64) void decode_hier_kernel(int Cpad, int max_
             const float sc = group_score(bw);
             if (owner && t < n_top) comp0[t] = ((u64)f32_ordered(sc) << 32) | (u64)(0xFFFFFFFFu - (uint32_t)t);
         }
-        __syncthreads();
+        lds_barrier();
         n_keep0 = min(n_probe_top, n_top);
         if (n_keep0 == n_top) {
             for (int t = tid; t < n_top; t += NT) sel0[t] = comp0[t];
-            __syncthreads();
+            lds_barrier();
         } else {
             int nb0 = 0;
             while ((1 << nb0) < n_top) ++nb0;
@@ -398,7 +420,7 @@ __global__ __launch_bounds__(NW * 64) void decode_hier_kernel(int Cpad, int max_
             const uint32_t tn = 0xFFFFFFFFu - (uint32_t)sel0[t];
             atomicOr(&member0[tn >> 5], 1u << (tn & 31));
         }
-        __syncthreads();
+        lds_barrier();
         // the clusters hanging under the kept nodes, in any order, ids in the low words of comp1
         const int *tof = d.top_of + (size_t)u * C;
         for (int c0 = 0; c0 < C; c0 += NT) {
@@ -411,18 +433,18 @@ __global__ __launch_bounds__(NW * 64) void decode_hier_kernel(int Cpad, int max_
             base = __shfl(base, 0);
             if (is) comp1[base + (int)__popcll(bal & ((1ull << lane) - 1ull))] = (u64)(uint32_t)c;
         }
-        __syncthreads();
+        lds_barrier();
         const int ncl = sh_ncand;
-        __syncthreads();
+        lds_barrier();
         if (tid == 0) sh_ncand = 0;  // (counts the candidate pages next)
         // ---- stage 1: scores of those clusters' centroids
         score_listed(cb, comp1, ncl);
-        __syncthreads();
+        lds_barrier();
         ICE_HSTAMP(1);
         n_keep = min(n_probe, ncl);
         if (n_keep == ncl) {
             for (int c = tid; c < ncl; c += NT) sel1[c] = comp1[c];
-            __syncthreads();
+            lds_barrier();
         } else {
             int nb = 0;
             while ((1 << nb) < C) ++nb;
@@ -435,7 +457,7 @@ __global__ __launch_bounds__(NW * 64) void decode_hier_kernel(int Cpad, int max_
         const uint32_t c = 0xFFFFFFFFu - (uint32_t)sel1[t];
         atomicOr(&member[c >> 5], 1u << (c & 31));
     }
-    __syncthreads();
+    lds_barrier();
 
     ICE_HSTAMP(3);
     // ---- stage 2a: the live pages of the kept clusters, in any order, ids in the low words of comp2
@@ -457,28 +479,23 @@ __global__ __launch_bounds__(NW * 64) void decode_hier_kernel(int Cpad, int max_
             base += (int)__popcll(bal[e]);
         }
     }
-    __syncthreads();
+    lds_barrier();
     const int ncand = sh_ncand;
     ICE_HSTAMP(4);
     // ---- stage 2b: their representatives' scores
     score_listed(d.rep + (size_t)u * d.max_pages * kD, comp2, ncand);
-    __syncthreads();
+    lds_barrier();
     ICE_HSTAMP(5);
     // how many pages stage 2 keeps: P, or n_refine of which stage 3 then keeps P
     const int k2 = min(n_refine > 0 ? n_refine : P, ncand);
     int k = min(P, k2);
     int *ids = ids_out + (size_t)u * P;
     float *sco = scores_out ? scores_out + (size_t)u * P : nullptr;
-    for (int x = k + tid; x < P; x += NT) {
-        ids[x] = -1;
-        if (sco) sco[x] = 0.f;
-    }
-    if (tid == 0) n_sel_out[u] = k;
     int nb = 0;
     while ((1 << nb) < d.max_pages) ++nb;
     if (k2 == ncand) {
         for (int x = tid; x < k2; x += NT) sel2[x] = comp2[x];
-        __syncthreads();
+        lds_barrier();
     } else {
         select_topk_lds<NW>(comp2, ncand, k2, nb, sel2, list, hist, sh);
     }
@@ -524,10 +541,10 @@ __global__ __launch_bounds__(NW * 64) void decode_hier_kernel(int Cpad, int max_
                 if (lane == 0 && x < k2) comp3[x] = ((u64)f32_ordered(best) << 32) | (u64)(0xFFFFFFFFu - pp[y]);
             }
         }
-        __syncthreads();
+        lds_barrier();
         if (k == k2) {
             for (int x = tid; x < k; x += NT) sel3[x] = comp3[x];
-            __syncthreads();
+            lds_barrier();
         } else {
             select_topk_lds<NW>(comp3, k2, k, nb, sel3, list, hist, sh);
         }
@@ -536,6 +553,12 @@ __global__ __launch_bounds__(NW * 64) void decode_hier_kernel(int Cpad, int max_
     ICE_HSTAMP(6);
     // the winners' places in ascending id order
     auto order_ids = [&](int part, int parts) {
+        // (every store of the selection is issued here: one in flight makes the next wait of its wave as long as a write to memory)
+        for (int x = k + part * 64 + lane; x < P; x += parts * 64) {
+            ids[x] = -1;
+            if (sco) sco[x] = 0.f;
+        }
+        if (part == 0 && lane == 0) n_sel_out[u] = k;
         if (TOP && tops_out) {  // the kept top nodes, ascending
             int *to = tops_out + (size_t)u * n_probe_top;
             if (part == parts - 1) list_bits(member0, kTopMax / 32, lane, to);

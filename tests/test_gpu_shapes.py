@@ -711,3 +711,41 @@ def test_insertions_scored_a_round_ahead_equal_single_ones(m, C, s, tk):
     done, the largest count that fits (448 clusters; transformed keys fill LDS to its last byte with it) and the first that
     does not, four and five rounds of them."""
     test_insertions_in_rounds_equal_single_ones(m, C, s, tk)
+
+
+@pytest.mark.parametrize("G", [4, 8])
+@pytest.mark.parametrize("C", [140, 520, 1100])
+def test_staged_selection_at_the_edges_of_its_threshold_groups(C, G):
+    """The kept clusters and pages at counts where the threshold changes its groups (half the 32, 64, 128 or 256 of them) or goes by
+    histograms, and where the list behind it is ranked in another form: they are the best of 64-bit scores."""
+    import torch
+    from paper_2604_10539_amd import IceIndex
+    n, U, s = 8 * C, 2, 16
+    w = datagen.small(n_tokens=n, n_clusters=C, n_kv_heads=U, n_components=C // 2, group_size=G)
+    K, V = datagen.keys_values(w)
+    ix = IceIndex(1, U, G, n, s, C, kmeans_iters=2, init_idx=up(datagen.init_indices(w)))
+    ix.build_index(up(K), up(V))
+    ex = ix.export()
+    torch.cuda.synchronize()
+    npg, pc = down(ex["n_pages"]), down(ex["page_cluster"])
+    rep, cen = widen(down(ex["rep"])).astype(np.float64), widen(narrow(down(ex["centroid"]))).astype(np.float64)
+    qb = datagen.queries(w)
+    qf = widen(qb[0]).astype(np.float64).reshape(U, G, D)
+    qf /= np.linalg.norm(qf, axis=2, keepdims=True)
+    ahead = 1e-5  # fp32 scores of unit-length queries: chains of 128 additions on values of at most a few units
+    for k in (1, 15, 16, 17, 31, 32, 33, 63, 64, 65, 127, 128, 129, 200):
+        if k >= C:
+            continue
+        ids, n_sel, scores, cl, _ = ix.select_hier(up(qb), k * s, k, attend=False)
+        ids, n_sel, cl = down(ids)[0], down(n_sel)[0], down(cl)[0]
+        for u in range(U):
+            sc = (cen[u, :C] @ qf[u].T).max(1)
+            kth = np.sort(sc)[::-1][k - 1]
+            assert np.all(np.diff(cl[u]) > 0) and np.all(sc[cl[u]] >= kth - ahead * max(1.0, abs(kth))), (k, u)
+            cand = np.nonzero(np.isin(pc[u, :npg[u]], cl[u]))[0]
+            P = min(k, len(cand))
+            assert n_sel[u] == P and np.all(np.diff(ids[u, :P]) > 0) and np.all(ids[u, P:] == -1)
+            assert np.all(np.isin(ids[u, :P], cand))
+            ps = (rep[u] @ qf[u].T).max(1)
+            kth = np.sort(ps[cand])[::-1][P - 1]
+            assert np.all(ps[ids[u, :P]] >= kth - ahead * max(1.0, abs(kth))), (k, u)
