@@ -1258,7 +1258,7 @@ __global__ __launch_bounds__(NW * 64, EMAX * NW <= 64 ? 4 : 1) void decode_step_
     __shared__ int sh_last, sh_M, sh_M2, sh_W, sh_fail;
     __shared__ uint32_t sh_pre;
     __shared__ uint32_t sh_rowmax[4 * NW];
-    __shared__ uint32_t sh_quadmax[16 * NW];
+    __shared__ __align__(16) uint32_t sh_quadmax[16 * NW];
     __shared__ u64 sh_tau;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, ch = lane & 15;
     const int xcd = blockIdx.x & 7, r = blockIdx.x >> 3;
@@ -1471,9 +1471,15 @@ __global__ __launch_bounds__(NW * 64, EMAX * NW <= 64 ? 4 : 1) void decode_step_
 #pragma unroll
             for (int e = 0; e < EMAX; ++e) key[e] = sc_lds[min(e * NT + tid, np - 1)];
         } else {
+            // (slots past the last page stand for it: they need no look of their own.  Slot by slot it was 1.2 us at 16 a thread, 1.0 so)
+            bool empty = false;
 #pragma unroll
-            for (int e = 0; e < EMAX; ++e)
-                if (e * NT + tid < np) key[e] = finish_score(e * NT + tid, key[e]);
+            for (int e = 0; e < EMAX; ++e) empty |= key[e] == kScoreEmpty;
+            if (__ballot(empty)) {  // (wave-uniform; seldom: a writer's store that had not landed)
+#pragma unroll
+                for (int e = 0; e < EMAX; ++e)
+                    if (e * NT + tid < np) key[e] = finish_score(e * NT + tid, key[e]);
+            }
             lds_barrier();
             if (sh_fail) {  // (workgroup-uniform)
                 report_failure();
@@ -1502,25 +1508,31 @@ __global__ __launch_bounds__(NW * 64, EMAX * NW <= 64 ? 4 : 1) void decode_step_
             // in their low byte (the threshold need not be a key: any value that k keys reach will do),
             // so that ranking a maximum among the N is one comparison per pair; the lanes of a group
             // share its N comparisons.
-            const bool quads = k > NO / 2;  // (workgroup-uniform)
-            const int lg = quads ? 2 : 3, NGr = NT >> lg, gs = 1 << lg;
-            uint32_t lmax = key[0];
+            auto by_lanes = [&](auto log_lanes) {
+                constexpr int LG = decltype(log_lanes)::value, LANES = 1 << LG, NGR = NT >> LG;  // lanes per group, groups
+                uint32_t lmax = key[0];
 #pragma unroll
-            for (int e = 1; e < EMAX; ++e) lmax = max(lmax, key[e]);
-            lmax = quads ? group_max<4>(lmax) : group_max<8>(lmax);
-            const int own = wave * (64 >> lg) + lane;
-            if (lane < 64 >> lg) sh_quadmax[own] = (lmax & 0xFFFFFF00u) | (uint32_t)(255 - own);
-            const int i = tid >> lg, part = tid & (gs - 1);  // the group this lane helps to rank
-            lds_barrier();
-            const uint32_t v = sh_quadmax[i];
-            const int len = NGr >> lg;  // comparisons per lane
-            uint32_t c = 0;
-#pragma unroll 8
-            for (int jj = 0; jj < len; ++jj) c += sh_quadmax[part * len + jj] > v ? 1u : 0u;
-            c += dpp_u32<0xB1>(c);
-            c += dpp_u32<0x4E>(c);
-            if (!quads) c += dpp_u32<0x141>(c);
-            if (part == 0 && (int)c == k - 1) sh_pre = v & 0xFFFFFF00u;
+                for (int e = 1; e < EMAX; ++e) lmax = max(lmax, key[e]);
+                lmax = group_max<LANES>(lmax);
+                const int own = wave * (64 >> LG) + lane;
+                if (lane < 64 >> LG) sh_quadmax[own] = (lmax & 0xFFFFFF00u) | (uint32_t)(255 - own);
+                const int i = tid >> LG, part = tid & (LANES - 1);  // the group this lane helps to rank
+                lds_barrier();
+                const uint32_t v = sh_quadmax[i];
+                const uint4 *others = (const uint4 *)sh_quadmax + part * (NGR / LANES / 4);
+                uint32_t c = 0;
+#pragma unroll
+                for (int jj = 0; jj < NGR / LANES / 4; ++jj) {
+                    const uint4 o = others[jj];
+                    c += (o.x > v ? 1u : 0u) + (o.y > v ? 1u : 0u) + (o.z > v ? 1u : 0u) + (o.w > v ? 1u : 0u);
+                }
+                c += dpp_u32<0xB1>(c);
+                c += dpp_u32<0x4E>(c);
+                if (LG == 3) c += dpp_u32<0x141>(c);
+                if (part == 0 && (int)c == k - 1) sh_pre = v & 0xFFFFFF00u;
+            };
+            if (k <= NO / 2) by_lanes(std::integral_constant<int, 3>{});  // (workgroup-uniform)
+            else by_lanes(std::integral_constant<int, 2>{});
         } else if (!by_prefix) {
             // B1, small budgets: the k-th largest of the 4*NW group maxima (groups without keys count as the
             // smallest key).  With several workgroups per unit the groups are 16 lanes' key registers;
@@ -1608,9 +1620,11 @@ __global__ __launch_bounds__(NW * 64, EMAX * NW <= 64 ? 4 : 1) void decode_step_
             // (the lane masks are formed twice, once to count and once to place: keeping EMAX of them
             // would not fit the scalar registers of the instantiations with many keys per thread)
             auto listed = [&](int e) {
-                const bool valid = e * NT + tid < np;
-                if constexpr (PREFIX) return __ballot(valid && (key[e] >> 16) == (pre >> 16));
-                else return __ballot(valid && key[e] >= pre);
+                u64 m;
+                if constexpr (PREFIX) m = __ballot((key[e] >> 16) == (pre >> 16));
+                else m = __ballot(key[e] >= pre);
+                if ((e + 1) * NT > np) m &= __ballot(e * NT + tid < np);  // (uniform: only the last of them has lanes without a page)
+                return m;
             };
             auto is_above = [&](int e) { return __ballot(e * NT + tid < np && (key[e] >> 16) > (pre >> 16)); };
             int tot = 0, tot_a = 0;
@@ -1629,6 +1643,9 @@ __global__ __launch_bounds__(NW * 64, EMAX * NW <= 64 ? 4 : 1) void decode_step_
                 if (e * NT >= np) break;
                 const int pid = e * NT + tid;
                 const u64 bal = listed(e);
+                // (wave-uniform: many groups of 64 pages have none.  Four waves to a SIMD: the vector instructions are what a stage
+                // of the selection takes.  8 units x 9400 pages, without this and with every lane's bound checked: 1.7 us, so 1.05)
+                if (bal == 0ull) continue;
                 const int slot = base + (int)__popcll(bal & lower);
                 if (((bal >> lane) & 1ull) && slot < cand_cap)  // (a list that overflows is not used: see B3)
                     cand[slot] = ((u64)key[e] << 32) | (u64)(0xFFFFFFFFu - (uint32_t)pid);

@@ -119,6 +119,7 @@ __device__ inline void rank_composites(const u64 *cand, int n, int need, int wav
     static_assert(kRankMax <= 64 * NW, "a wave's share on its lanes");
     if (n <= 64) rank_blocks<1, NW>(cand, n, need, wave, lane, sel);
     else if (n <= 128) rank_blocks<2, NW>(cand, n, need, wave, lane, sel);
+    else if (n <= 256) rank_blocks<4, NW>(cand, n, need, wave, lane, sel);
     else rank_blocks<kRankMax / 64, NW>(cand, n, need, wave, lane, sel);
 }
 
