@@ -30,9 +30,10 @@ struct SelShared {
 // 1 <= k < n.  First a 32-bit threshold that at least k keys reach, and few more:
 //   k <= 2*NW  the k-th largest of the maxima of 4*NW groups, element j belonging to group
 //              j mod 4*NW (so short arrays still spread over every group);
-//   k <= 8*NW  the same with 8*NW or 16*NW groups, whichever is the first to be 2*k at least.  The maxima are made distinct
-//              by the group's number in their low byte (any value that k keys reach will do), so that ranking them is
-//              one comparison per pair;
+//   k <= 64    the same with 8*NW groups or (8 waves) 16*NW, whichever is the first to be 2*k at least.  The maxima are made
+//              distinct by the group's number in their low byte (any value that k keys reach will do), so that ranking them is
+//              one comparison per pair.  (128 of 1024 by 256 groups of four lanes on 16 waves:
+//              the call 28.4 us, by the histograms 26.5: 64 comparisons a lane and twice the list to rank);
 //   else       the 16-bit key prefix of the k-th largest key, from two 8-bit LDS histograms.
 // What passes goes to a short list that is ranked by counting; with the prefix threshold only the
 // keys that share the prefix are listed (those above it are winners as they are, and the
@@ -49,7 +50,9 @@ __device__ void select_topk_lds(const u64 *comp, int n, int k, int nb, u64 *sel,
     constexpr int NT = NW * 64, NR = 4 * NW;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (tid == 0) { sh.M = 0; sh.W = 0; sh.A = 0; sh.pre = 0u; sh.tau = 0ull; }
-    const bool by_prefix = k > 2 * NR;
+    constexpr int kGroupsMax = 64;
+    static_assert(kGroupsMax <= 2 * NR, "half the groups of four lanes");
+    const bool by_prefix = k > kGroupsMax;
     if (k <= NR / 2) {
         const int row = tid >> 4, l16 = tid & 15;
         uint32_t lmax = 0u;
@@ -93,8 +96,12 @@ __device__ void select_topk_lds(const u64 *comp, int n, int k, int nb, u64 *sel,
             if (LG == 3) c += dpp_u32<0x141>(c);
             if (part == 0 && (int)c == k - 1) sh.pre = v & 0xFFFFFF00u;
         };
-        if (k <= NR) by_groups(std::integral_constant<int, 3>{});
-        else by_groups(std::integral_constant<int, 2>{});
+        if constexpr (NR < kGroupsMax) {
+            if (k <= NR) by_groups(std::integral_constant<int, 3>{});
+            else by_groups(std::integral_constant<int, 2>{});
+        } else {
+            by_groups(std::integral_constant<int, 3>{});
+        }
     } else {
         // bucket of the k-th largest key by its top byte, then by its second byte inside that bucket
         int *h0 = hist, *h1 = hist + 272;
