@@ -322,6 +322,14 @@ ice_status_t ice_debug_rerun_stage(ice_index_t *idx, const void *K, const void *
  * are checked as ice_build_index checks them. */
 ice_status_t ice_debug_build_plan(const ice_config_t *cfg, int32_t n_tokens, int32_t n_clusters, int32_t plan[6]);
 
+/* Test hook: the two bounds by which a round of a large build decides that a key need not be scored against the centroids
+ * far from its own, on n host values each.  A score is k . c - |c|^2 / 2 in fp32.  need[i] = the distance from its own
+ * centroid from which on no centroid can beat the best one known, for a key of squared norm key_norm2, an own
+ * centroid of squared norm own_norm2 and the scores of the own and of the best known centroid;
+ * dist2[i] = the least squared distance of that own centroid and one of score best_score[i] or less against it (as a key). */
+ice_status_t ice_debug_near_bounds(int32_t n, const float *key_norm2, const float *own_norm2, const float *own_score,
+                                   const float *best_score, float *need, float *dist2);
+
 /* Test hook for the failure path of ice_select / ice_select_attend when a unit is served by several
  * workgroups (fewer than 256 units): those workgroups hand their page scores to the last one of
  * them through device memory, and that one waits for a missing score only a bounded number of

@@ -17,7 +17,7 @@ ICE_OK, ICE_ERR_INVALID_ARG, ICE_ERR_SHAPE, ICE_ERR_STATE, ICE_ERR_CAPACITY, ICE
 STATUS_NAMES = ["ICE_OK", "ICE_ERR_INVALID_ARG", "ICE_ERR_SHAPE", "ICE_ERR_STATE", "ICE_ERR_CAPACITY",
                 "ICE_ERR_UNSUPPORTED", "ICE_ERR_DEVICE"]
 SYMBOLS = ["ice_workspace_bytes", "ice_create", "ice_destroy", "ice_build_index", "ice_insert", "ice_insert_batch", "ice_select",
-           "ice_attend", "ice_attend_noalloc", "ice_select_attend", "ice_attend_resident", "ice_select_attend_resident", "ice_selected_tokens", "ice_attend_tokens", "ice_select_hier", "ice_select_hier3", "ice_build_top_level", "ice_export_top_level", "ice_set_geometry", "ice_export_geometry", "ice_export_index", "ice_import_index", "ice_debug_assign", "ice_debug_rerun_stage", "ice_debug_build_plan", "ice_debug_select_fault",
+           "ice_attend", "ice_attend_noalloc", "ice_select_attend", "ice_attend_resident", "ice_select_attend_resident", "ice_selected_tokens", "ice_attend_tokens", "ice_select_hier", "ice_select_hier3", "ice_build_top_level", "ice_export_top_level", "ice_set_geometry", "ice_export_geometry", "ice_export_index", "ice_import_index", "ice_debug_assign", "ice_debug_rerun_stage", "ice_debug_build_plan", "ice_debug_near_bounds", "ice_debug_select_fault",
            "ice_debug_peak_read", "ice_debug_peak_mfma", "ice_last_error"]
 
 
@@ -100,6 +100,7 @@ def lib() -> C.CDLL:
                                        C.c_void_p, C.c_void_p]
         L.ice_debug_rerun_stage.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p]
         L.ice_debug_build_plan.argtypes = [C.POINTER(IceConfig), C.c_int32, C.c_int32, C.POINTER(C.c_int32)]
+        L.ice_debug_near_bounds.argtypes = [C.c_int32] + [C.c_void_p] * 6
         L.ice_debug_select_fault.argtypes = [C.c_void_p, C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32,
                                              C.c_int32, C.c_void_p]
         L.ice_debug_peak_read.argtypes = [C.c_void_p, C.c_size_t, C.c_void_p, C.c_void_p]
@@ -273,6 +274,17 @@ def ice_debug_build_plan(cfg: IceConfig, n_tokens, n_clusters) -> dict:
     plan = (C.c_int32 * 6)()
     _check(lib().ice_debug_build_plan(C.byref(cfg), n_tokens, n_clusters, plan))
     return dict(zip(("fused", "range_len", "ranges", "reassign_from", "run", "slices"), plan))
+
+
+def ice_debug_near_bounds(key_norm2, own_norm2, own_score, best_score):
+    """(need, dist2) of one-dimensional float32 numpy arrays of the same length."""
+    import numpy as np
+    args = [np.ascontiguousarray(x, dtype=np.float32) for x in (key_norm2, own_norm2, own_score, best_score)]
+    if any(x.shape != (args[0].size,) for x in args):
+        raise ValueError("four one-dimensional arrays of the same length")
+    need, dist2 = np.empty_like(args[0]), np.empty_like(args[0])
+    _check(lib().ice_debug_near_bounds(args[0].size, *(x.ctypes.data for x in args + [need, dist2])))
+    return need, dist2
 
 
 def ice_debug_select_fault(idx, q, token_budget, page_ids, n_selected, out, muted_chunk, wait_log2, stream=None) -> None:

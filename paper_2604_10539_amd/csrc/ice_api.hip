@@ -617,6 +617,13 @@ ice_status_t ice_debug_build_plan(const ice_config_t *cfg, int32_t n, int32_t n_
     return ICE_OK;
 }
 
+ice_status_t ice_debug_near_bounds(int32_t n, const float *k2, const float *a2, const float *sa, const float *sb, float *need, float *dist2) {
+    if (n < 0) return fail(ICE_ERR_INVALID_ARG, "n must not be negative");
+    if (!k2 || !a2 || !sa || !sb || !need || !dist2) return fail(ICE_ERR_INVALID_ARG, "a pointer is null");
+    near_bounds(n, k2, a2, sa, sb, need, dist2);
+    return ICE_OK;
+}
+
 ice_status_t ice_debug_select_fault(ice_index_t *ix, const void *q, int32_t budget, int32_t *ids, int32_t *n_sel, float *out,
                                     int32_t muted_chunk, int32_t wait_log2, void *stream) {
     if (ice_status_t st = check_select(ix, q, budget, ids, n_sel, "ice_debug_select_fault")) return st;

@@ -1532,13 +1532,18 @@ __device__ inline unsigned near_mark(int round) { return 128u | ((unsigned)round
 // so c loses in fp32 as well where D - (da + db) > sqrt(8 g (|k|^2 + |a|^2)) + sqrt(12 g) D; sqrt(12 g) < 0.0195, hence the factor
 // 1.025, which covers the rounding of these lines too.  da^2 and db^2 come out of scores, |k|^2 - 2 s, at most
 // 2 g (5 |k|^2 + 4 db^2) too low: 32 g (|k|^2 + |a|^2) is added to them.  Whatever is not a number leaves the key open.
-__device__ inline float near_need(float k2, float a2, float sa, float sb) {
-    const float w = k2 + a2, up = 0x1p-10f * w;
+// Below 2^-126 an operation is off by up to 2^-126 more, whatever its result (2^-149 where subnormal numbers are kept): a score, a
+// norm or a distance by at most 2^-118.  Counting |k|^2 + |a|^2 as 2^-90 more covers that many times over: the slack that this
+// adds to the test is above 2^-51, its square above 2^-103.
+constexpr float kNearFloor = 0x1p-90f;
+__host__ __device__ inline float near_need(float k2, float a2, float sa, float sb) {
+    const float w = k2 + a2 + kNearFloor, up = 0x1p-10f * w;
     const float da = sqrtf(fmaxf(k2 - 2.f * sa, 0.f) + up), db = sqrtf(fmaxf(k2 - 2.f * sb, 0.f) + up);
     return (da + db + sqrtf(0x1p-12f * w)) * 1.025f;
 }
-// a lower bound of the squared distance of a and a centroid of score at most s against it (the same bound on the score)
-__device__ inline float near_dist2(float a2, float s) { return fmaxf((a2 * (1.f - 0x1p-11f) - 2.f * s) * (1.f - 0x1p-11f), 0.f); }
+// a lower bound of the squared distance of a and a centroid of score at most s against it (the same bound on the score; what
+// is lost below 2^-126 stands in near_need)
+__host__ __device__ inline float near_dist2(float a2, float s) { return fmaxf((a2 * (1.f - 0x1p-11f) - 2.f * s) * (1.f - 0x1p-11f), 0.f); }
 
 // Up to 32 rows of 256 bytes into a wave's own LDS tile (chunk c of row r in slot c ^ (r & 15)), lane first + r saying where row r is
 __device__ inline void stage_rows(const bf16_t *base, int row_of_lane, int first, int rows, char *tile, int lane) {
@@ -2271,6 +2276,13 @@ void launch_near(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fuse
     if (d.tk) { if (full) ICE_MARKED(true, true); else ICE_MARKED(true, false); }
     else { if (full) ICE_MARKED(false, true); else ICE_MARKED(false, false); }
 #undef ICE_MARKED
+}
+
+void near_bounds(int n, const float *k2, const float *a2, const float *sa, const float *sb, float *need, float *dist2) {
+    for (int i = 0; i < n; ++i) {
+        need[i] = near_need(k2[i], a2[i], sa[i], sb[i]);
+        dist2[i] = near_dist2(a2[i], sb[i]);
+    }
 }
 
 void build_plan(const Dev &d, int n, int *plan) {

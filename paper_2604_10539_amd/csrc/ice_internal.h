@@ -116,6 +116,7 @@ void launch_reassign(const Dev &d, const bf16_t *K, int n, int cur, int t, bool 
 bool near_pays(const Dev &d, int n);         // for rounds t >= 1 but those
 void launch_near(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fused, hipStream_t st);
 void build_plan(const Dev &d, int n, int *plan);  // ice_debug_build_plan
+void near_bounds(int n, const float *k2, const float *a2, const float *sa, const float *sb, float *need, float *dist2);  // ice_debug_near_bounds
 void launch_sort(const Dev &d, int n, int t, float *best_out_or_null, int *assign_out_or_null, hipStream_t st);
 size_t sort_ranges_max(int U, int max_tokens, int Cpad);  // (unit, range) pairs of any sort of at most max_tokens tokens
 // last: no round follows that would ask which centroids moved

@@ -580,6 +580,8 @@ def test_later_rounds_that_score_what_moved_leave_what_all_centroids_would(U, n,
     (8, 65536, 1024, 0, "few", 32, 0),     # components far fewer than clusters: lists that come out too long, centroids that go on moving
     (8, 65536, 1024, 0, "half", 32, 0),    # every other unit without structure: those take all in every round
     (8, 65536, 1024, 1, "odd", 32, 0),     # units with keys that are not finite beside units of which all are
+    (8, 65536, 1024, 0, "tiny", 32, 0),    # products and squared distances that end among the subnormal numbers
+    (8, 65536, 1024, 1, "tiny", 32, 0),
 ])
 def test_later_rounds_by_the_centroids_near_a_keys_own_leave_what_all_would(U, n, C, tk, data, ranges, fused):
     """The same where every later round takes the keys of a cluster to the centroids near its own and only the keys that this
@@ -601,6 +603,8 @@ def test_later_rounds_by_the_centroids_near_a_keys_own_leave_what_all_would(U, n
         if data == "lump":
             x[n // 2: n // 2 + n // 3] = 0.01 * x[n // 2: n // 2 + n // 3]
             x[100:400] = x[100:101]
+        if data == "tiny":
+            x = torch.ldexp(x, torch.tensor(-50 if u == 0 else -60 - 2 * u, device="cuda"))
         K[0, u] = x.to(torch.bfloat16).view(torch.int16)
     if data == "odd":
         for i, t in enumerate(range(5, n, 2111)):
