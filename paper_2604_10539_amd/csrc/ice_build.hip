@@ -104,7 +104,7 @@ void launch_key_aug(const Dev &d, const bf16_t *K, int n, hipStream_t st) {
 }
 
 // A build's scratch at the start of a unit's key tiles, which the page layout overwrites in any case (see Near)
-constexpr int kNearHead = 6;
+constexpr int kNearHead = 6, kNearHeadBytes = 64;
 __device__ inline char *near_scratch(const Dev &d, int u) { return (char *)(d.Kp + (size_t)u * d.max_pages * d.s * kD); }
 
 // ------------------------------------------------------------------------------------------------
@@ -991,8 +991,8 @@ void launch_assign(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fu
 // after the other, its keys' winners so far in `tmp`.  A slice of few tiles splits the keys among the waves instead of
 // the centroids (slice<CW>: CW waves share the centroids of a key).  In a unit that takes all, workgroups are cut over
 // slices as well.  Bound as assign_kernel is while many centroids move, by the read of the keys once few do.
-// `tmp` and the key lists are scratch at the start of the unit's key tiles, 12 of the 256 bytes per token that the page
-// layout overwrites in any case.
+// `tmp` and the key lists are scratch at the start of the unit's key tiles (behind Near's head), 12 of the 256 bytes per token
+// that the page layout overwrites in any case.
 enum { kMovedCentroids = 1, kListedKeys = 2 };  // what a pass over the keys is about
 __host__ __device__ inline int reassign_lds_bytes(bool aug, int Cpad) {
     return 2 * 256 * 256 + 2 * 256 * 8 + 512 * 4 + (aug ? 1024 * 4 : 0) + Cpad * 2 + Cpad / 8;
@@ -1273,11 +1273,10 @@ struct ReassignJob {
     }
 };
 
+// A workgroup's part of the round of unit blockIdx.y.  in_full: the unit goes through the full contraction in any case.
 template <bool AUG, bool ALL_FULL>  // ALL_FULL: every slice of the centroids is full (FULL of assign_slice)
-__global__ __launch_bounds__(512) void reassign_kernel(const bf16_t *__restrict__ K, const bf16_t *__restrict__ cent,
-                                                       const float *__restrict__ cnorm, int n, int Cpad, int cur,
-                                                       const int *__restrict__ go, int round, int fused, RoundPlan plan, Dev d) {  // (scalars first: preloaded at wave start)
-    extern __shared__ __align__(16) char smem[];
+__device__ __forceinline__ void reassign_unit(const bf16_t *K, const bf16_t *cent, const float *cnorm, int n, int Cpad,
+                                              int cur, const int *go, int round, int fused, bool in_full, RoundPlan &plan, Dev &d, char *smem) {
     char *keys = smem;                                             // [2][256][256 B], chunks swizzled as in assign_slice
     u64 *best = (u64 *)(smem + 2 * kAssignTile * 256);             // [2][256]
     float *seeds = (float *)(best + 2 * kAssignTile);              // [512] of the slice at hand
@@ -1318,7 +1317,7 @@ __global__ __launch_bounds__(512) void reassign_kernel(const bf16_t *__restrict_
             total_held += sh_keys[w];
         }
         ncent = __builtin_amdgcn_readfirstlane(ncent);
-        all = large != 0 || takes_all(plan, ncent, __builtin_amdgcn_readfirstlane(total_held), n);
+        all = in_full || large != 0 || takes_all(plan, ncent, __builtin_amdgcn_readfirstlane(total_held), n);
         if (!all) {
             if (tid * 16 < Cpad) bits[tid] = (uint16_t)m;
             for (; m; m &= m - 1) list[pos++] = (uint16_t)(tid * 16 + __ffs(m) - 1);
@@ -1343,7 +1342,7 @@ __global__ __launch_bounds__(512) void reassign_kernel(const bf16_t *__restrict_
     if ((int)blockIdx.x >= plan.wgs) return;
     const int keys_per_wg = plan.run * kAssignTile, k0 = blockIdx.x * keys_per_wg;
     const bf16_t *Ku = K + (size_t)u * n * kD;
-    u64 *tmp = (u64 *)(d.Kp + (size_t)u * d.max_pages * d.s * kD);
+    u64 *tmp = (u64 *)(near_scratch(d, u) + kNearHeadBytes);
     uint32_t *fails = (uint32_t *)(tmp + n) + k0;
 
     ReassignJob job{kMovedCentroids, min(n, k0 + keys_per_wg) - k0, ncent, k0, Cpad, (uint32_t)(round % kRoundNumbers), packed, tmp, fails, list, bits, &sh_fails, 0ull, 0ull};
@@ -1366,6 +1365,14 @@ __global__ __launch_bounds__(512) void reassign_kernel(const bf16_t *__restrict_
         sort_range<8, kFusedRun / 2, false>(d, thread_of(wave), u, n, blockIdx.x, plan.wgs, k0, min(n, k0 + keys_per_wg), keys_per_wg / 8, 8, nbits, round, 1,
                                             (int *)smem, nullptr, nullptr, [=](int i) { return pk[2 * i]; }, cluster_of_word, [](int) { return 0.f; });
     }
+}
+
+template <bool AUG, bool ALL_FULL>
+__global__ __launch_bounds__(512) void reassign_kernel(const bf16_t *__restrict__ K, const bf16_t *__restrict__ cent,
+                                                       const float *__restrict__ cnorm, int n, int Cpad, int cur,
+                                                       const int *__restrict__ go, int round, int fused, RoundPlan plan, Dev d) {  // (scalars first: preloaded at wave start)
+    extern __shared__ __align__(16) char smem[];
+    reassign_unit<AUG, ALL_FULL>(K, cent, cnorm, n, Cpad, cur, go, round, fused, false, plan, d, smem);
 }
 
 static RoundPlan round_plan(const Dev &d, int n) {
@@ -1481,11 +1488,12 @@ constexpr int kFewPieces = 8;
 //               have overtaken), the others against all.
 // A score is the same bits whichever slot of the matrix instruction it comes out of, and a margin for the scores' rounding
 // (near_need) stands in the test, so the winner is the one that all of them would leave, bit for bit.
-// A unit goes through the full contraction instead, by the same code as a round of assign_kernel: where it has keys that are not
-// finite or so large that a score may not be (`large_keys`: what the contraction leaves of a key among whose scores are NaN
-// depends on where in a tile they are; argmax16: nine of them side by side hide their lane's others), and for the rest of the
-// build once more than 3/5 of its keys were marked in a round, or would be in the first one as far as one key of every second cluster tells
-// (keys without structure: the first two launches are in vain then).
+// A unit takes reassign_kernel's way instead, by the same code, for the rest of the build: where it has keys that are not finite or
+// so large that a score may not be (`large_keys`: what the contraction leaves of a key among whose scores are NaN depends on
+// where in a tile they are; argmax16: nine of them side by side hide their lane's others), and once more than 3/5 of its keys were marked
+// in a round, or would be in the first one as far as one key of every second cluster tells (keys of little structure: the first
+// two launches are in vain then).  The round in which it turns goes through the full contraction: the scores in `packed` are
+// the last round's only behind one.
 //
 // `Near`: what the three leave for each other, scratch at the start of the unit's key tiles: at most 153 of the 256 bytes per
 // token there (n tokens, C <= n).
@@ -1494,8 +1502,8 @@ constexpr int kNearGroups = 12;   // a list's threshold: this many groups of 16 
 constexpr int kMaxNearTokens = 1 << 24;  // (an item holds a cluster in 13 bits and a chunk in 19)
 constexpr int kMaxSlices = kMaxClusters / 512;
 struct Near {
-    int *head;           // items; marked keys in even rounds, in odd ones; whether the unit takes all for the rest of the build; keys
-                         // that round 1 looked at ahead, those of them that will be marked
+    int *head;           // items; marked keys in even rounds, in odd ones; the round in which the unit turned to reassign_kernel's way
+                         // (0: it did not); keys that round 1 looked at ahead, those of them that will be marked
     uint32_t *list;      // [kMaxSlices][n] reassign's keys, per slice of the centroids
     unsigned char *open; // [n] 0: settled; else marked: near_mark of the round if the key's own centroid moved, 1 if it stayed
     uint16_t *near;      // [C][kNearList] ascending, the centroid itself among them, 0xFFFF behind the last
@@ -1508,7 +1516,7 @@ __device__ inline Near near_of(const Dev &d, int u, int n) {
     Near x;
     char *p = near_scratch(d, u);
     x.head = (int *)p;
-    p += 64;
+    p += kNearHeadBytes;
     x.list = (uint32_t *)p;
     p += (size_t)kMaxSlices * n * 4;
     x.open = (unsigned char *)p;
@@ -1521,8 +1529,11 @@ __device__ inline Near near_of(const Dev &d, int u, int n) {
     x.items = (uint32_t *)(x.few + d.C);
     return x;
 }
-// (round 1: most of the keys that were looked at ahead will be marked)
-__device__ inline bool near_in_vain(const int *head, int round) { return head[3] != 0 || (round == 1 && head[5] * 5 > head[4] * 3); }
+// The round in which the unit turned, 0: it did not.  (Round 1: most of the keys that were looked at ahead will be marked.)
+__device__ inline int near_turned(const int *head, int round) {
+    const int turned = head[3];
+    return turned != 0 ? turned : round == 1 && head[5] * 5 > head[4] * 3 ? 1 : 0;
+}
 __device__ inline unsigned near_mark(int round) { return 128u | ((unsigned)round & 127u); }
 
 // The margin for rounding.  A score s(c) = k . c - |c|^2 / 2 is a chain of 129 (transformed keys: 130) fp32 additions of exact
@@ -1634,7 +1645,7 @@ __global__ __launch_bounds__(512) void near_lists_kernel(const bf16_t *__restric
     wait_lds_dma();  // (also for a workgroup that leaves here: nothing lands in its LDS any more)
     if (goes == 0) return;
     if (off != 0 || large != 0 || (long long)open * 5 > (long long)n * 3) {
-        if (tid == 0) x.head[3] = 1;
+        if (tid == 0 && off == 0) x.head[3] = round;
         return;
     }
     if (block == 0 && tid == 0) x.head[1 + (round & 1)] = 0;
@@ -1853,7 +1864,7 @@ __global__ __launch_bounds__(64) void near_kernel(const bf16_t *__restrict__ K, 
     __shared__ __align__(16) float seeds[32];
     const int u = blockIdx.x % d.U, lane = threadIdx.x, col = lane & 31, half = lane >> 5;  // (a unit's workgroups on few dies: its rows stay in their L2)
     const Near x = near_of(d, u, n);
-    const int goes = go[2 * u], items = near_in_vain(x.head, round) ? 0 : __builtin_amdgcn_readfirstlane(x.head[0]), step = gridDim.x / d.U;
+    const int goes = go[2 * u], items = near_turned(x.head, round) ? 0 : __builtin_amdgcn_readfirstlane(x.head[0]), step = gridDim.x / d.U;
     int it = blockIdx.x / d.U;
     if (goes == 0 || it >= items) return;
     // (rows of the list's tile that no centroid is staged into keep finite numbers: they count with a seed of -inf)
@@ -2022,7 +2033,7 @@ __global__ __launch_bounds__(64) void near_kernel(const bf16_t *__restrict__ K, 
     }
 }
 
-// The marked keys of a run (see above; of a unit that takes all, every key by assign_slice).  The workgroup that has slice x of
+// The marked keys of a run (see above; a unit that turned: reassign_unit).  The workgroup that has slice x of
 // the centroids takes the keys whose own centroid moved against that slice (they meet in `packed`, as in assign_kernel), and
 // its share of the others against the centroids that moved (listed in ascending id in LDS, 512 at a time): with `old`
 // the word of the key's own centroid, the winner m stands where m > old.
@@ -2068,12 +2079,11 @@ struct MarkedJob {
         }
     }
 };
-__host__ __device__ inline int marked_lds_bytes(bool aug, int Cpad) { return 2 * 256 * 256 + 2 * 256 * 8 + 512 * 4 + (aug ? 1024 * 4 : 0) + Cpad * 2; }
 
 template <bool AUG, bool ALL_FULL>  // ALL_FULL: every slice of the centroids is full (FULL of assign_slice)
 __global__ __launch_bounds__(512) void marked_kernel(const bf16_t *__restrict__ K, const bf16_t *__restrict__ cent,
                                                      const float *__restrict__ cnorm, int n, int Cpad, int cur, const int *__restrict__ go,
-                                                     int round, int fused, int run, int wgs, int slices, Dev d) {  // (scalars first: preloaded at wave start)
+                                                     int round, int fused, RoundPlan plan, Dev d) {  // (scalars first: preloaded at wave start)
     extern __shared__ __align__(16) char smem[];
     char *keys = smem;                                             // [2][256][256 B], chunks swizzled as in assign_slice
     u64 *best = (u64 *)(smem + 2 * kAssignTile * 256);             // [2][256]
@@ -2081,31 +2091,25 @@ __global__ __launch_bounds__(512) void marked_kernel(const bf16_t *__restrict__ 
     uint32_t *kext = (uint32_t *)(seeds + 512);                    // (AUG) [2][256] the keys' extra coordinates
     uint32_t *cext = kext + 2 * kAssignTile;                       // (AUG) [512] the centroids' of the slice at hand
     uint16_t *list = (uint16_t *)(kext + (AUG ? 1024 : 0));        // [Cpad] moved centroids, ascending
-    uint16_t *won = (uint16_t *)(smem + assign_lds_bytes(AUG));    // (all keys, fused) the run's winners
     __shared__ int sh_wave[8], sh_marked[2];
 
     const int u = blockIdx.y;
     int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     u64 *packed = d.packed + (size_t)u * d.max_tokens;
-    const int keys_per_wg = run * kAssignTile, which = blockIdx.x / wgs, range = blockIdx.x - which * wgs;
+    const int slices = plan.slices, wgs = plan.all_wgs, keys_per_wg = plan.all_run * kAssignTile, which = blockIdx.x / wgs, range = blockIdx.x - which * wgs;
     const int k0 = range * keys_per_wg, kend = min(n, k0 + keys_per_wg);
     const int nbits = 32 - __builtin_clz((unsigned)Cpad - 1u);
     int *head = (int *)near_scratch(d, u);
 
-    if (fused && blockIdx.x == 0 && tid == 0) d.any_moved[2 * u + (round & 1)] = 0;  // (for this round's means)
-    if (go[2 * u] == 0) return;  // (no centroid moved: every winner stands)
-    if (near_in_vain(head, round)) {  // (the same for the whole unit)
-        if (blockIdx.x == 0 && tid == 0) head[3] = 1;
-        assign_slice<2, 8, AUG, ALL_FULL>(d, K, cent, cnorm, n, u, which, k0, kend, slices, Cpad, cur, nullptr,
-                                          round % kRoundNumbers, fused ? won : nullptr, false, smem);
-        if (fused) {  // (one slice: a range of the sort, as in assign_kernel)
-            __syncthreads();
-            sort_range<8, kFusedRun / 2, false>(d, thread_of(wave), u, n, range, wgs, k0, kend, keys_per_wg / 8, 8, nbits, round, 1, (int *)smem,
-                                                nullptr, nullptr, [=](int i) { return (uint32_t)won[i - k0]; }, [](uint32_t w) { return w; }, [](int) { return 0.f; });
-        }
+    if (const int turned = near_turned(head, round)) {  // (the same for the whole unit)
+        if (blockIdx.x == 0 && tid == 0) head[3] = turned;
+        reassign_unit<AUG, ALL_FULL>(K, cent, cnorm, n, Cpad, cur, go, round, fused, turned == round, plan, d, smem);
         return;
     }
+    if (fused && blockIdx.x == 0 && tid == 0) d.any_moved[2 * u + (round & 1)] = 0;  // (for this round's means)
+    if (go[2 * u] == 0) return;  // (no centroid moved: every winner stands)
+    if (which >= slices) return;
     if (blockIdx.x == 0 && tid == 0) head[0] = 0;  // (for the next round's near_lists)
     // ---- which centroids moved, and the run's marked keys: whose own centroid moved from the front of the key list on,
     // the others from its end
@@ -2226,7 +2230,8 @@ __global__ __launch_bounds__(512) void marked_kernel(const bf16_t *__restrict__ 
 // 904 and 864, 256 x 32768 x 512 10920 and 8690; below the line 8 x 49152 x 768 (12) 819 and 775, 1 x 131072 x 2048 (8) 687 and 662, 4 x
 // 65536 x 1024 (8) 677 and 685, 2 x 32768 x 2048 (4) 302 and 377, 8 x 32768 x 512 (4) 492 and 567.  Keys without any structure pay for
 // finding that out and for two empty launches in each later round: 8 x 131072 x 2048 5307 and 5395, 256 x 32768 x 512 15620 and 16000, 8 x
-// 65536 x 1024 1652 and 1720.  (The line leaves out the gains of 3 to 6 % right below it: such keys lose as much there, 8 x 49152 x 768
+// 65536 x 1024 1652 and 1720.  Components of spread 0.6 instead of 0.3, from which on a unit turns to reassign_kernel's way: 8 x 131072 x
+// 2048 3090 and 3190, 256 x 32768 x 512 10930 and 11350, 8 x 65536 x 1024 1055 and 1145 (in full from there on 5020, 13700, 1515).  (The line leaves out the gains of 3 to 6 % right below it: such keys lose as much there, 8 x 49152 x 768
 // 1176 and 1248.)
 // Of the 2300 us of 8 x 131072 x 2048: first round 440, then near_lists 32 and eight times 19, near 80 to 18, marked 130 to 32,
 // sort 16, means 55 to 14 each, page copy 190.
@@ -2238,7 +2243,7 @@ bool near_pays(const Dev &d, int n) {
 }
 
 void launch_near(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fused, hipStream_t st) {
-    const int slices = assign_slices(d), run = assign_run(d.U, n, slices), wgs = ((n + kAssignTile - 1) / kAssignTile + run - 1) / run;
+    const RoundPlan p = round_plan(d, n);
     const int L = sort_len(d, n), R = (n + L - 1) / L;
     const int *go = round_goes(d, t);
     const size_t near_lds = near_lists_lds_bytes(d.Cpad);
@@ -2265,12 +2270,12 @@ void launch_near(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fuse
     else ICE_NEAR_P(false);
 #undef ICE_NEAR_P
 #undef ICE_NEAR
-    const size_t lds = std::max<size_t>(marked_lds_bytes(d.tk != 0, d.Cpad), assign_lds_bytes(d.tk != 0) + (fused ? (size_t)run * kAssignTile * 2 : 0));
+    const size_t lds = std::max<size_t>(reassign_lds_bytes(d.tk != 0, d.Cpad), assign_lds_bytes(d.tk != 0) + (fused ? (size_t)p.all_run * kAssignTile * 2 : 0));
 #define ICE_MARKED(aug, full)                                                                                              \
     do {                                                                                                                   \
         allow_dynamic_lds((const void *)marked_kernel<aug, full>, lds);                                                    \
-        hipLaunchKernelGGL((marked_kernel<aug, full>), dim3(wgs * slices, d.U), dim3(512), lds, st, K, d.cent_bf16[cur], d.cnorm[cur], n, d.Cpad, \
-                           cur, go, t, fused ? 1 : 0, run, wgs, slices, d);                                                \
+        hipLaunchKernelGGL((marked_kernel<aug, full>), dim3(std::max(p.wgs, p.all_wgs * p.slices), d.U), dim3(512), lds, st, K, d.cent_bf16[cur], \
+                           d.cnorm[cur], n, d.Cpad, cur, go, t, fused ? 1 : 0, p, d);                                      \
     } while (0)
     const bool full = d.Cpad / 32 % 16 == 0;
     if (d.tk) { if (full) ICE_MARKED(true, true); else ICE_MARKED(true, false); }

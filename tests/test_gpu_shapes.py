@@ -582,6 +582,12 @@ def test_later_rounds_that_score_what_moved_leave_what_all_centroids_would(U, n,
     (8, 65536, 1024, 1, "odd", 32, 0),     # units with keys that are not finite beside units of which all are
     (8, 65536, 1024, 0, "tiny", 32, 0),    # products and squared distances that end among the subnormal numbers
     (8, 65536, 1024, 1, "tiny", 32, 0),
+    (8, 65536, 1024, 0, "wide", 32, 0),    # components too wide: units that turn to the moved centroids in the second round
+    (32, 32768, 512, 1, "wide", 8, 1),
+    (8, 65536, 1024, 0, "late", 32, 0),    # ... that turn in the third: every second cluster is narrow, the others hold most keys
+    (32, 32768, 512, 0, "late", 8, 1),
+    (4, 131072, 1100, 1, "late", 64, 0),
+    (1, 262144, 2112, 0, "late", 64, 0),
 ])
 def test_later_rounds_by_the_centroids_near_a_keys_own_leave_what_all_would(U, n, C, tk, data, ranges, fused):
     """The same where every later round takes the keys of a cluster to the centroids near its own and only the keys that this
@@ -593,10 +599,15 @@ def test_later_rounds_by_the_centroids_near_a_keys_own_leave_what_all_would(U, n
     gen = torch.Generator(device="cuda").manual_seed(U * n + C)
     K = torch.empty(1, U, n, D, dtype=torch.int16, device="cuda")
     M = C // 20 if data == "few" else C // 2
+    broad = torch.zeros(U, n, dtype=torch.bool, device="cuda")
     for u in range(U):
         x = torch.randn(n, D, generator=gen, device="cuda")
-        if data != "half" or u % 2 == 0:
-            x = 0.3 * x + torch.randn(M, D, generator=gen, device="cuda")[torch.randint(M, (n,), generator=gen, device="cuda")]
+        if data == "late":
+            broad[u] = torch.rand(n, generator=gen, device="cuda") < (0.8 if u % 3 < 2 else 0.1)  # (every third unit does not turn)
+            at = torch.randint(M // 2, (n,), generator=gen, device="cuda") + broad[u] * (M // 2)
+            x = (0.2 + 0.6 * broad[u].float())[:, None] * x + torch.randn(M, D, generator=gen, device="cuda")[at]
+        elif data != "half" or u % 2 == 0:
+            x = (0.6 if data == "wide" else 0.3) * x + torch.randn(M, D, generator=gen, device="cuda")[torch.randint(M, (n,), generator=gen, device="cuda")]
         if data == "out":
             far = torch.rand(n, generator=gen, device="cuda") < 0.05
             x = torch.where(far[:, None], 6 * torch.rand(n, D, generator=gen, device="cuda") - 3, x)
@@ -611,6 +622,10 @@ def test_later_rounds_by_the_centroids_near_a_keys_own_leave_what_all_would(U, n
             K[0, ::2, t, i % D:] = [0x7FC0, 0x7F80, 0xFF80 - 65536, 0xFFC0 - 65536, 0x5F80, 0xDF80 - 65536][i % 6]
     V = torch.randint(-16000, 16000, K.shape, generator=gen, device="cuda", dtype=torch.int16)
     init = torch.stack([torch.sort(torch.randperm(n, generator=gen, device="cuda")[:C])[0] for _ in range(U)])
+    if data == "late":
+        for u in range(U):
+            for first in (0, 1):  # (even clusters start at narrow keys)
+                init[u, first::2] = torch.nonzero(broad[u] == bool(first))[:(C + 1 - first) // 2, 0]
     if data == "lump":
         init[:, 10:50] = torch.arange(100, 140, device="cuda")  # (centroids on equal keys)
     init = init.int()[None].contiguous()
