@@ -104,7 +104,7 @@ void launch_key_aug(const Dev &d, const bf16_t *K, int n, hipStream_t st) {
 }
 
 // A build's scratch at the start of a unit's key tiles, which the page layout overwrites in any case (see Near)
-constexpr int kNearHead = 6, kNearHeadBytes = 64;
+constexpr int kNearHead = 6, kNearHeadBytes = 256;
 __device__ inline char *near_scratch(const Dev &d, int u) { return (char *)(d.Kp + (size_t)u * d.max_pages * d.s * kD); }
 
 // ------------------------------------------------------------------------------------------------
@@ -1490,20 +1490,19 @@ constexpr int kFewPieces = 8;
 // (near_need) stands in the test, so the winner is the one that all of them would leave, bit for bit.
 // A unit takes reassign_kernel's way instead, by the same code, for the rest of the build: where it has keys that are not finite or
 // so large that a score may not be (`large_keys`: what the contraction leaves of a key among whose scores are NaN depends on
-// where in a tile they are; argmax16: nine of them side by side hide their lane's others), and once more than 3/5 of its keys were marked
-// in a round, or would be in the first one as far as one key of every second cluster tells (keys of little structure: the first
-// two launches are in vain then).  The round in which it turns goes through the full contraction: the scores in `packed` are
-// the last round's only behind one.
+// where in a tile they are; argmax16: nine of them side by side hide their lane's others), and once too many of its keys were marked
+// in a round, or would be in the first one as far as one key of every second cluster tells (keys of little structure: near_in_vain).
+// The round in which it turns goes through the full contraction: the scores in `packed` are the last round's only behind one.
 //
-// `Near`: what the three leave for each other, scratch at the start of the unit's key tiles: at most 153 of the 256 bytes per
+// `Near`: what the three leave for each other, scratch at the start of the unit's key tiles: 256 bytes and at most 153 of the 256 bytes per
 // token there (n tokens, C <= n).
 constexpr int kNearList = 32, kNearChunk = 64;
 constexpr int kNearGroups = 12;   // a list's threshold: this many groups of 16 centroids have a member at or above it
 constexpr int kMaxNearTokens = 1 << 24;  // (an item holds a cluster in 13 bits and a chunk in 19)
 constexpr int kMaxSlices = kMaxClusters / 512;
 struct Near {
-    int *head;           // items; marked keys in even rounds, in odd ones; the round in which the unit turned to reassign_kernel's way
-                         // (0: it did not); keys that round 1 looked at ahead, those of them that will be marked
+    int *head;           // items; marked keys in even rounds, in odd ones; near_turned; (8 bytes) workgroups that looked at keys ahead in
+                         // round 1 << 40 | these keys << 20 | those of them that will be marked
     uint32_t *list;      // [kMaxSlices][n] reassign's keys, per slice of the centroids
     unsigned char *open; // [n] 0: settled; else marked: near_mark of the round if the key's own centroid moved, 1 if it stayed
     uint16_t *near;      // [C][kNearList] ascending, the centroid itself among them, 0xFFFF behind the last
@@ -1529,11 +1528,23 @@ __device__ inline Near near_of(const Dev &d, int u, int n) {
     x.items = (uint32_t *)(x.few + d.C);
     return x;
 }
-// The round in which the unit turned, 0: it did not.  (Round 1: most of the keys that were looked at ahead will be marked.)
-__device__ inline int near_turned(const int *head, int round) {
-    const int turned = head[3];
-    return turned != 0 ? turned : round == 1 && head[5] * 5 > head[4] * 3 ? 1 : 0;
+// Whether a unit's keys are settled too seldom: so many of them were marked in a round, or (sample) so many of those that round 1 looked
+// at ahead will be.  Ten rounds, us, this way throughout and turned in round 1, by the spread of the components (the benchmark's: 0.3), behind
+// it the share of the keys that were looked at ahead and left open and the share that was marked in round 1:
+//                          0.5                         0.52                        0.55                        0.6
+//   8 x 131072 x 2048      2613  3354  0.34 0.49       2811  3359  0.45 0.62       3184  3373  0.66 0.80       3698  3402  0.89 0.96
+//   2 x 131072 x 2048      1024  1139                  1093  1153                  1192  1148                  1289  1151
+//   8 x 65536 x 1024       1104  1203  0.26 0.39       1178  1201  0.35 0.51       1266  1199  0.55 0.72       1412  1199  0.88 0.93
+//   64 x 32768 x 512       2667  2872  0.25 0.28       2798  2867  0.28 0.36       3129  2893  0.43 0.52       3609  2891  0.68 0.83
+// Two of the three launches cost the same for any number of clusters, a full round does not: with more of them fewer settled keys pay.
+__device__ inline bool near_in_vain(int open, int of, int Cpad, bool sample) {
+    const int limit = Cpad <= 768 ? (sample ? 8 : 9) : Cpad <= 1024 ? (sample ? 9 : 12) : (sample ? 12 : 15);  // twentieths
+    return (long long)open * 20 > (long long)of * limit;
 }
+// The round in which unit u turned, 0: it did not.  joint: a build's units turn together.  (While the chip holds a round's workgroups
+// at once, or nearly, a unit that takes the other way is what the others wait for: 64 x 32768 x 512 of spread 0.5, of which some turned,
+// 3187, and 2667 and 2872 with none and all.  In more turns than two a unit's work adds to the others'.)
+__device__ inline int *near_turned(const Dev &d, int u, int joint) { return (int *)near_scratch(d, joint ? 0 : u) + 3; }
 __device__ inline unsigned near_mark(int round) { return 128u | ((unsigned)round & 127u); }
 
 // The margin for rounding.  A score s(c) = k . c - |c|^2 / 2 is a chain of 129 (transformed keys: 130) fp32 additions of exact
@@ -1588,10 +1599,11 @@ __host__ __device__ inline int near_lists_lds_bytes(int Cpad) {
 }
 template <bool AUG>
 __global__ __launch_bounds__(512) void near_lists_kernel(const bf16_t *__restrict__ cent, const float *__restrict__ cnorm, int n, int Cpad, int cur,
-                                                         const bf16_t *__restrict__ K, const int *__restrict__ go, int round, int R, int L, Dev d) {
+                                                         const bf16_t *__restrict__ K, const int *__restrict__ go, int round, int R, int L, int joint, Dev d) {
     constexpr int KS = AUG ? 9 : 8;
     extern __shared__ __align__(16) char smem[];
     __shared__ float limit[kNearA], close_to[kNearA];
+    __shared__ int sampled, will_be_open;
     __shared__ __align__(4) uint16_t moved[kNearMaxClusters / 16];
     __shared__ int chunks[kNearA], found[kNearA];
     const int nbuf = near_tiles(Cpad);
@@ -1613,6 +1625,18 @@ __global__ __launch_bounds__(512) void near_lists_kernel(const bf16_t *__restric
 #pragma unroll
         for (int y = 0; y < 8; ++y) lds_dma16(src + (4 * y + g) * 16 + (i ^ (4 * (y & 3) + g)), tile_lds + buf * 8192 + y * 1024);
     };
+    int *turned = near_turned(d, u, joint);
+    // whether the unit does not go this way in this round
+    auto ends = [&] {
+        const int goes = go[2 * u], off = *turned, large = d.large_keys[u], open = x.head[1 + ((round - 1) & 1)];
+        // (a unit that turns in this very launch is not looked at: the waves of a workgroup might see it turn between them)
+        const bool over = goes == 0 || (off != 0 && off != round), turns = large != 0 || near_in_vain(open, n, Cpad, false);
+        if (tid == 0 && turns && !over) *turned = round;
+        return over || turns;
+    };
+    // (Where a CU takes several workgroups one after the other, each would wait for its rows in vain: 256 units x 512 clusters that
+    // turned 42 us a launch, 6 so.  Where it takes one, the rows are on their way while the flags are: 20.0 us at 8 units x 2048, 21.2 else.)
+    if (gridDim.x > 256 && ends()) return;
     if (wave < 2) stage_rows(cu, min(a0 + 32 * wave + (lane & 31), Cpad - 1), 0, 32, own_rows + wave * 8192, lane);
     // a scan's first tiles
     auto request_first = [&] {
@@ -1621,7 +1645,7 @@ __global__ __launch_bounds__(512) void near_lists_kernel(const bf16_t *__restric
     };
     request_first();
     for (int i = tid; i < Cpad / 4; i += 512) ((float4 *)norms)[i] = ((const float4 *)wn)[i];
-    const int goes = go[2 * u], off = x.head[3], large = d.large_keys[u], open = x.head[1 + ((round - 1) & 1)];
+    const bool out = gridDim.x <= 256 && ends();
     uint32_t mv = 0;
     int held = 0;
     if (tid < groups) mv = moved_of_16(d.moved + (size_t)u * Cpad, tid, held);
@@ -1643,11 +1667,7 @@ __global__ __launch_bounds__(512) void near_lists_kernel(const bf16_t *__restric
         }
     }
     wait_lds_dma();  // (also for a workgroup that leaves here: nothing lands in its LDS any more)
-    if (goes == 0) return;
-    if (off != 0 || large != 0 || (long long)open * 5 > (long long)n * 3) {
-        if (tid == 0 && off == 0) x.head[3] = round;
-        return;
-    }
+    if (out) return;
     if (block == 0 && tid == 0) x.head[1 + (round & 1)] = 0;
     if (tid < groups) moved[tid] = (uint16_t)mv;
     if (wave == 0) {  // (kNearA == 64)
@@ -1657,6 +1677,7 @@ __global__ __launch_bounds__(512) void near_lists_kernel(const bf16_t *__restric
         close_to[tid] = need > 0.f ? score_at(w * w) : -INFINITY;
         limit[tid] = fmaxf(close_to[tid], score_at(few));
         chunks[tid] = (members + kNearChunk - 1) / kNearChunk;
+        if (tid == 0) sampled = will_be_open = 0;
     }
     lds_barrier();
     bf16x8 B[2][KS];
@@ -1766,6 +1787,7 @@ __global__ __launch_bounds__(512) void near_lists_kernel(const bf16_t *__restric
         }
     };
     const int col = lane & 31, half = lane >> 5;
+    bool no_lists = false;
     if (round == 1) {
         scan([&](int t, int ct, const f32x16 &acc) {
             float m = max3f(acc[0], acc[1], acc[2]);
@@ -1781,22 +1803,7 @@ __global__ __launch_bounds__(512) void near_lists_kernel(const bf16_t *__restric
         else kth(std::integral_constant<int, 4>{});
         lds_barrier();
         if (wave == 0) few = near_dist2(a2, limit[tid]);
-    }
-    const float lim0 = limit[col], lim1 = limit[32 + col];
-    scan([&](int t, int ct, const f32x16 &acc) {
-        const float lim = ct ? lim1 : lim0;
-        uint32_t m = 0;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) m |= acc[v] >= lim ? 1u << (8 * (v >> 2) + (v & 3)) : 0u;
-        m <<= 4 * half;
-        m |= (uint32_t)__shfl_xor((int)m, 32);
-        if (half == 0) hits[(32 * ct + col) * hstride + t] = m;
-    });
-    lds_barrier();
-    if (tiles <= 64) lists(std::integral_constant<int, 1>{});
-    else lists(std::integral_constant<int, 2>{});
-    lds_barrier();
-    if (round == 1) {  // one key of every second cluster: does its list settle it, as far as the distance from its own centroid says
+        // one key of every second cluster: does its list settle it, as far as the distance from its own centroid says
         const int g = lane >> 4, ch = lane & 15, al = wave * (kNearA / 8) + 2 * g, c = min(a0 + al, d.C - 1);
         const uint32_t word = ch < R ? d.range_off[((size_t)u * R + ch) * Cpad + c] : 0u;  // (a member in the first 16 ranges, mostly)
         const uint32_t has = (uint32_t)(__ballot((word & 0xFFFFu) != 0u) >> (16 * g)) & 0xFFFFu;
@@ -1819,9 +1826,41 @@ __global__ __launch_bounds__(512) void near_lists_kernel(const bf16_t *__restric
         const bool sample = has != 0u && a0 + al < d.C && ch == 0;
         const u64 all = __ballot(sample), open_too = __ballot(sample && !(4.25f * d2 < near_dist2(wn[c], limit[al])));
         if (lane == 0 && all) {
-            atomicAdd(&x.head[4], (int)__popcll(all));
-            if (open_too) atomicAdd(&x.head[5], (int)__popcll(open_too));
+            atomicAdd(&sampled, (int)__popcll(all));
+            if (open_too) atomicAdd(&will_be_open, (int)__popcll(open_too));
         }
+        lds_barrier();
+        const int of = sampled, will = will_be_open;
+        // (the unit's last workgroup says whether it turns; one that sees little but open keys needs no lists)
+        if (tid == 0) {
+            u64 sum = 1ull << 40 | (u64)of << 20 | (u64)will;
+            sum += atomicAdd((u64 *)(x.head + 4), sum);
+            if ((int)(sum >> 40) == (d.C + kNearA - 1) / kNearA && near_in_vain((int)(sum & 0xFFFFFu), (int)(sum >> 20 & 0xFFFFFu), Cpad, true)) *turned = 1;
+        }
+        no_lists = will * 4 > of * 3;
+    }
+    if (no_lists) {  // (workgroup-uniform)
+        wait_lds_dma();
+        for (int i = tid; i < kNearA * kNearList; i += 512) {
+            const int a = a0 + i / kNearList;
+            if (a < d.C) x.near[(size_t)a * kNearList + i % kNearList] = (uint16_t)(i % kNearList == 0 ? a : 0xFFFF);
+        }
+        if (tid < kNearA) found[tid] = 0;
+    } else {
+        const float lim0 = limit[col], lim1 = limit[32 + col];
+        scan([&](int t, int ct, const f32x16 &acc) {
+            const float lim = ct ? lim1 : lim0;
+            uint32_t m = 0;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) m |= acc[v] >= lim ? 1u << (8 * (v >> 2) + (v & 3)) : 0u;
+            m <<= 4 * half;
+            m |= (uint32_t)__shfl_xor((int)m, 32);
+            if (half == 0) hits[(32 * ct + col) * hstride + t] = m;
+        });
+        lds_barrier();
+        if (tiles <= 64) lists(std::integral_constant<int, 1>{});
+        else lists(std::integral_constant<int, 2>{});
+        lds_barrier();
     }
     if (tid >= kNearA) return;
     // one thread per centroid
@@ -1858,15 +1897,15 @@ __global__ __launch_bounds__(512) void near_lists_kernel(const bf16_t *__restric
 // NP: as in means_kernel (1 piece per cluster, at most kFewPieces, more).
 template <bool AUG, int NP>
 __global__ __launch_bounds__(64) void near_kernel(const bf16_t *__restrict__ K, const bf16_t *__restrict__ cent, const float *__restrict__ cnorm,
-                                                  int n, int Cpad, int cur, const int *__restrict__ go, int round, int R, int L, Dev d) {
+                                                  int n, int Cpad, int cur, const int *__restrict__ go, int round, int R, int L, int joint, Dev d) {
     constexpr int KS = AUG ? 9 : 8;
     __shared__ __align__(16) char rows[2][8192];
     __shared__ __align__(16) float seeds[32];
     const int u = blockIdx.x % d.U, lane = threadIdx.x, col = lane & 31, half = lane >> 5;  // (a unit's workgroups on few dies: its rows stay in their L2)
     const Near x = near_of(d, u, n);
-    const int goes = go[2 * u], items = near_turned(x.head, round) ? 0 : __builtin_amdgcn_readfirstlane(x.head[0]), step = gridDim.x / d.U;
+    const int goes = go[2 * u], off = *near_turned(d, u, joint), items = __builtin_amdgcn_readfirstlane(x.head[0]), step = gridDim.x / d.U;
     int it = blockIdx.x / d.U;
-    if (goes == 0 || it >= items) return;
+    if (it >= items || goes == 0 || off != 0) return;
     // (rows of the list's tile that no centroid is staged into keep finite numbers: they count with a seed of -inf)
 #pragma unroll
     for (int i = 0; i < 16; ++i) *(uint4 *)(&rows[0][0] + (i * 64 + lane) * 16) = make_uint4(0, 0, 0, 0);
@@ -2083,7 +2122,7 @@ struct MarkedJob {
 template <bool AUG, bool ALL_FULL>  // ALL_FULL: every slice of the centroids is full (FULL of assign_slice)
 __global__ __launch_bounds__(512) void marked_kernel(const bf16_t *__restrict__ K, const bf16_t *__restrict__ cent,
                                                      const float *__restrict__ cnorm, int n, int Cpad, int cur, const int *__restrict__ go,
-                                                     int round, int fused, RoundPlan plan, Dev d) {  // (scalars first: preloaded at wave start)
+                                                     int round, int fused, int joint, RoundPlan plan, Dev d) {  // (scalars first: preloaded at wave start)
     extern __shared__ __align__(16) char smem[];
     char *keys = smem;                                             // [2][256][256 B], chunks swizzled as in assign_slice
     u64 *best = (u64 *)(smem + 2 * kAssignTile * 256);             // [2][256]
@@ -2102,13 +2141,14 @@ __global__ __launch_bounds__(512) void marked_kernel(const bf16_t *__restrict__ 
     const int nbits = 32 - __builtin_clz((unsigned)Cpad - 1u);
     int *head = (int *)near_scratch(d, u);
 
-    if (const int turned = near_turned(head, round)) {  // (the same for the whole unit)
-        if (blockIdx.x == 0 && tid == 0) head[3] = turned;
+    int goes = go[2 * u], turned = *near_turned(d, u, joint);  // (nothing in this launch changes it)
+    asm volatile("" : "+v"(goes), "+v"(turned));  // (one trip for both)
+    if (turned != 0) {
         reassign_unit<AUG, ALL_FULL>(K, cent, cnorm, n, Cpad, cur, go, round, fused, turned == round, plan, d, smem);
         return;
     }
     if (fused && blockIdx.x == 0 && tid == 0) d.any_moved[2 * u + (round & 1)] = 0;  // (for this round's means)
-    if (go[2 * u] == 0) return;  // (no centroid moved: every winner stands)
+    if (goes == 0) return;  // (no centroid moved: every winner stands)
     if (which >= slices) return;
     if (blockIdx.x == 0 && tid == 0) head[0] = 0;  // (for the next round's near_lists)
     // ---- which centroids moved, and the run's marked keys: whose own centroid moved from the front of the key list on,
@@ -2228,11 +2268,11 @@ __global__ __launch_bounds__(512) void marked_kernel(const bf16_t *__restrict__ 
 // 5 % outliers (64 tiles) 3690 and 2300; the benchmark's mixture 8 x 131072 x 1024 (32) 2554 and 1588, x 1310 transformed 3189 and 2030,
 // 64 x 32768 x 512 (32) 2720 and 2204, 8 x 65536 x 1024 (16) 1080 and 924, 2 x 131072 x 2048 (16) 1040 and 852, 16 x 32768 x 768 (16)
 // 904 and 864, 256 x 32768 x 512 10920 and 8690; below the line 8 x 49152 x 768 (12) 819 and 775, 1 x 131072 x 2048 (8) 687 and 662, 4 x
-// 65536 x 1024 (8) 677 and 685, 2 x 32768 x 2048 (4) 302 and 377, 8 x 32768 x 512 (4) 492 and 567.  Keys without any structure pay for
-// finding that out and for two empty launches in each later round: 8 x 131072 x 2048 5307 and 5395, 256 x 32768 x 512 15620 and 16000, 8 x
-// 65536 x 1024 1652 and 1720.  Components of spread 0.6 instead of 0.3, from which on a unit turns to reassign_kernel's way: 8 x 131072 x
-// 2048 3090 and 3190, 256 x 32768 x 512 10930 and 11350, 8 x 65536 x 1024 1055 and 1145 (in full from there on 5020, 13700, 1515).  (The line leaves out the gains of 3 to 6 % right below it: such keys lose as much there, 8 x 49152 x 768
-// 1176 and 1248.)
+// 65536 x 1024 (8) 677 and 685, 2 x 32768 x 2048 (4) 302 and 377, 8 x 32768 x 512 (4) 492 and 567.  Keys that the near centroids do not
+// settle pay for finding that out and for two empty launches (3.5 us each) in each later round.  Without any structure: 8 x 131072 x 2048 5090 and
+// 5220, 64 x 32768 x 512 3820 and 3920, 8 x 65536 x 1024 1557 and 1644; components of spread 0.6: 3048 and 3154, 2730 and 2825, 1053 and 1145,
+// 2 x 131072 x 2048 996 and 1086, 16 x 32768 x 768 897 and 983.  (The line leaves out the gains of 3 to 6 % right below it: such keys
+// lose more there, 8 x 49152 x 768 without structure 1176 and 1248.)
 // Of the 2300 us of 8 x 131072 x 2048: first round 440, then near_lists 32 and eight times 19, near 80 to 18, marked 130 to 32,
 // sort 16, means 55 to 14 each, page copy 190.
 constexpr int kNearMinSteps = 16;
@@ -2244,6 +2284,7 @@ bool near_pays(const Dev &d, int n) {
 
 void launch_near(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fused, hipStream_t st) {
     const RoundPlan p = round_plan(d, n);
+    const int joint = p.all_turns <= 2 ? 1 : 0;
     const int L = sort_len(d, n), R = (n + L - 1) / L;
     const int *go = round_goes(d, t);
     const size_t near_lds = near_lists_lds_bytes(d.Cpad);
@@ -2251,7 +2292,7 @@ void launch_near(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fuse
     do {                                                                                                                   \
         allow_dynamic_lds((const void *)near_lists_kernel<aug>, near_lds);                                                 \
         hipLaunchKernelGGL(near_lists_kernel<aug>, dim3((d.C + kNearA - 1) / kNearA * d.U), dim3(512), near_lds, st, d.cent_bf16[cur], d.cnorm[cur], n, \
-                           d.Cpad, cur, K, go, t, R, L, d);                                                                         \
+                           d.Cpad, cur, K, go, t, R, L, joint, d);                                                                  \
     } while (0)
     if (d.tk) ICE_NEAR_LISTS(true);
     else ICE_NEAR_LISTS(false);
@@ -2259,7 +2300,7 @@ void launch_near(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fuse
     // as many waves as the chip holds at once, at most one per chunk
     const int waves = (int)std::min<long long>((2048 + d.U - 1) / d.U, (long long)d.C + n / kNearChunk);
 #define ICE_NEAR(aug, np)                                                                                                  \
-    hipLaunchKernelGGL((near_kernel<aug, np>), dim3(waves * d.U), dim3(64), 0, st, K, d.cent_bf16[cur], d.cnorm[cur], n, d.Cpad, cur, go, t, R, L, d)
+    hipLaunchKernelGGL((near_kernel<aug, np>), dim3(waves * d.U), dim3(64), 0, st, K, d.cent_bf16[cur], d.cnorm[cur], n, d.Cpad, cur, go, t, R, L, joint, d)
 #define ICE_NEAR_P(aug)                                                                                                    \
     do {                                                                                                                   \
         if (R == 1) ICE_NEAR(aug, 1);                                                                                      \
@@ -2275,7 +2316,7 @@ void launch_near(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fuse
     do {                                                                                                                   \
         allow_dynamic_lds((const void *)marked_kernel<aug, full>, lds);                                                    \
         hipLaunchKernelGGL((marked_kernel<aug, full>), dim3(std::max(p.wgs, p.all_wgs * p.slices), d.U), dim3(512), lds, st, K, d.cent_bf16[cur], \
-                           d.cnorm[cur], n, d.Cpad, cur, go, t, fused ? 1 : 0, p, d);                                      \
+                           d.cnorm[cur], n, d.Cpad, cur, go, t, fused ? 1 : 0, joint, p, d);                               \
     } while (0)
     const bool full = d.Cpad / 32 % 16 == 0;
     if (d.tk) { if (full) ICE_MARKED(true, true); else ICE_MARKED(true, false); }

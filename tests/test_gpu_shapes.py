@@ -588,6 +588,9 @@ def test_later_rounds_that_score_what_moved_leave_what_all_centroids_would(U, n,
     (32, 32768, 512, 0, "late", 8, 1),
     (4, 131072, 1100, 1, "late", 64, 0),
     (1, 262144, 2112, 0, "late", 64, 0),
+    (600, 4000, 450, 0, "half", 1, 0),     # many units, which turn one by one
+    (600, 4000, 450, 1, "odd", 1, 0),
+    (600, 4000, 450, 0, "late", 1, 0),
 ])
 def test_later_rounds_by_the_centroids_near_a_keys_own_leave_what_all_would(U, n, C, tk, data, ranges, fused):
     """The same where every later round takes the keys of a cluster to the centroids near its own and only the keys that this
@@ -605,7 +608,7 @@ def test_later_rounds_by_the_centroids_near_a_keys_own_leave_what_all_would(U, n
         if data == "late":
             broad[u] = torch.rand(n, generator=gen, device="cuda") < (0.8 if u % 3 < 2 else 0.1)  # (every third unit does not turn)
             at = torch.randint(M // 2, (n,), generator=gen, device="cuda") + broad[u] * (M // 2)
-            x = (0.2 + 0.6 * broad[u].float())[:, None] * x + torch.randn(M, D, generator=gen, device="cuda")[at]
+            x = (0.1 + 0.7 * broad[u].float())[:, None] * x + torch.randn(M, D, generator=gen, device="cuda")[at]
         elif data != "half" or u % 2 == 0:
             x = (0.6 if data == "wide" else 0.3) * x + torch.randn(M, D, generator=gen, device="cuda")[torch.randint(M, (n,), generator=gen, device="cuda")]
         if data == "out":
