@@ -1477,38 +1477,40 @@ constexpr int kFewPieces = 8;
 // centroid outside the list falls below.  A centroid c outside is at least |a - c| - da away, so it loses to b where
 //   |a - c| >= T > da + db.
 // In the benchmark's mixture (131072 keys, 2048 centroids, 5 % outliers) that leaves 23 % of the keys after the first
-// round and 10 to 12 % after the later ones, with 1 to 4 centroids near enough to matter.  What all keys against all
-// centroids would leave in `packed` follows from three launches:
+// round and 10 to 12 % after the later ones, with 1 to 4 centroids near enough to matter.  The winning cluster that all
+// keys against all centroids would leave in `packed` follows from three launches (the score and the round beside it may be an earlier
+// round's, where a key was settled and stayed, or not looked at):
 //   near_lists  per centroid a: up to 32 centroids next to it in ascending id, T, and whether its keys have to be looked at: a centroid
 //               that is near enough to matter for one of them moved, its members changed, or T fell below what they need.
 //               Clusters to be looked at are listed in chunks of 64 members.
 //   near        per chunk: the keys against the list (one 32 x 32 tile per 32 keys).  The winner is written where it is another
 //               one; a key that the test leaves open is marked, with the score of its own centroid.
-//   reassign    the marked keys, gathered: those whose own centroid stayed, against the centroids that moved (no other one can
+//   marked      the marked keys, gathered: those whose own centroid stayed, against the centroids that moved (no other one can
 //               have overtaken), the others against all.
 // A score is the same bits whichever slot of the matrix instruction it comes out of, and a margin for the scores' rounding
-// (near_need) stands in the test, so the winner is the one that all of them would leave, bit for bit.
+// (near_need) stands in the test, so the winner is the one that all of them would leave.
 // A unit takes reassign_kernel's way instead, by the same code, for the rest of the build: where it has keys that are not finite or
 // so large that a score may not be (`large_keys`: what the contraction leaves of a key among whose scores are NaN depends on
 // where in a tile they are; argmax16: nine of them side by side hide their lane's others), and once too many of its keys were marked
 // in a round, or would be in the first one as far as one key of every second cluster tells (keys of little structure: near_in_vain).
 // The round in which it turns goes through the full contraction: the scores in `packed` are the last round's only behind one.
 //
-// `Near`: what the three leave for each other, scratch at the start of the unit's key tiles: 256 bytes and at most 153 of the 256 bytes per
+// `Near`: what the three leave for each other, scratch at the start of the unit's key tiles: 256 bytes and at most 114 of the 256 bytes per
 // token there (n tokens, C <= n).
 constexpr int kNearList = 32, kNearChunk = 64;
 constexpr int kNearGroups = 12;   // a list's threshold: this many groups of 16 centroids have a member at or above it
 constexpr int kMaxNearTokens = 1 << 24;  // (an item holds a cluster in 13 bits and a chunk in 19)
-constexpr int kMaxSlices = kMaxClusters / 512;
+constexpr int kNearMaxClusters = 4096;   // (what near_lists holds of a unit in LDS)
 struct Near {
     int *head;           // items; marked keys in even rounds, in odd ones; near_turned; (8 bytes) workgroups that looked at keys ahead in
                          // round 1 << 40 | these keys << 20 | those of them that will be marked
-    uint32_t *list;      // [kMaxSlices][n] reassign's keys, per slice of the centroids
+    uint32_t *list;      // [kNearMaxClusters / 512][n] marked's keys, per slice of the centroids
     unsigned char *open; // [n] 0: settled; else marked: near_mark of the round if the key's own centroid moved, 1 if it stayed
     uint16_t *near;      // [C][kNearList] ascending, the centroid itself among them, 0xFFFF behind the last
     float *reach;        // [C] T
     float *need;         // [C] what T has to exceed for every settled key
-    float *few;          // [C] squared distance within which few centroids were when it was last worked out, 0: to be worked out
+    float *few;          // [C] squared distance within which few centroids were when it was last worked out (0: a dozen and more are the same as this one; its keys
+                         // stay open)
     uint32_t *items;     // [C + n / kNearChunk]
 };
 __device__ inline Near near_of(const Dev &d, int u, int n) {
@@ -1517,7 +1519,7 @@ __device__ inline Near near_of(const Dev &d, int u, int n) {
     x.head = (int *)p;
     p += kNearHeadBytes;
     x.list = (uint32_t *)p;
-    p += (size_t)kMaxSlices * n * 4;
+    p += (size_t)(kNearMaxClusters / 512) * n * 4;
     x.open = (unsigned char *)p;
     p += (n + 63) / 64 * 64;
     x.near = (uint16_t *)p;
@@ -1590,7 +1592,6 @@ __device__ inline void read_rows(const char *tile, int lane, bf16x8 *out) {
 // are other ones than in the last round).  For the first list a pass over all of them finds the maximum of every group of 16, of which
 // the kNearGroups-th largest (its upper 16 bits) is taken.  Bound by the round trips to the centroid rows, one tile's behind the other's.
 constexpr int kNearA = 64;
-constexpr int kNearMaxClusters = 4096;
 // a wave's tiles of rows (two where they fit), the centroids' squared norms, the groups' maxima (the workgroup's own rows first)
 __host__ __device__ inline int near_tiles(int Cpad) { return Cpad <= 2048 ? 2 : 1; }
 __host__ __device__ inline int near_lists_lds_bytes(int Cpad) {
@@ -1602,7 +1603,7 @@ __global__ __launch_bounds__(512) void near_lists_kernel(const bf16_t *__restric
                                                          const bf16_t *__restrict__ K, const int *__restrict__ go, int round, int R, int L, int joint, Dev d) {
     constexpr int KS = AUG ? 9 : 8;
     extern __shared__ __align__(16) char smem[];
-    __shared__ float limit[kNearA], close_to[kNearA];
+    __shared__ float limit[kNearA];
     __shared__ int sampled, will_be_open;
     __shared__ __align__(4) uint16_t moved[kNearMaxClusters / 16];
     __shared__ int chunks[kNearA], found[kNearA];
@@ -1674,8 +1675,7 @@ __global__ __launch_bounds__(512) void near_lists_kernel(const bf16_t *__restric
         // (near_dist2 of score_at(x) is x)
         auto score_at = [&](float dist2) { return 0.5f * (a2 * (1.f - 0x1p-11f) - dist2 * (1.f + 0x1p-11f)); };
         const float w = (own_word != 0u ? 1.3f : 1.02f) * need;
-        close_to[tid] = need > 0.f ? score_at(w * w) : -INFINITY;
-        limit[tid] = fmaxf(close_to[tid], score_at(few));
+        limit[tid] = fmaxf(need > 0.f ? score_at(w * w) : -INFINITY, score_at(few));
         chunks[tid] = (members + kNearChunk - 1) / kNearChunk;
         if (tid == 0) sampled = will_be_open = 0;
     }
