@@ -503,7 +503,7 @@ def _every_stage_again(Kd, Vd, init, C, tk, T):
 def test_later_rounds_do_again_what_changed_and_leave_what_all_of_it_would(U, n, C, tk, odd):
     """A build's later rounds leave out units of which no centroid moved and sum only clusters whose members
     changed.  Every stage of the last round once more, over everything, leaves the same bits, after two rounds, three, ...
-    (each of them started from the state that the test before it found right).  Few and many centroid tiles, several
+    nine (each of them started from the state that the one before found right), twelve and thirty.  Few and many centroid tiles, several
     slices of 512, clusters of one key; `odd`: among keys without a comparable score and equal keys.  Builds this small score
     all centroids in every round; the next test's do not."""
     import torch
@@ -517,7 +517,7 @@ def test_later_rounds_do_again_what_changed_and_leave_what_all_of_it_would(U, n,
             K[0, :, t, i % D:] = [0x7FC0, 0x7F80, 0xFF80, 0xFFC0][i % 4]  # NaN, inf, -inf, -NaN
     Kd, Vd, init = up(K), up(V), up(datagen.init_indices(w))
     settled = False
-    for T in (2, 3, 4, 5, 6, 8, 12, 30):
+    for T in (2, 3, 4, 5, 6, 7, 8, 9, 12, 30):
         had = _every_stage_again(Kd, Vd, init, C, tk, T)
         if T == 12:
             last = had
@@ -540,8 +540,8 @@ def test_later_rounds_do_again_what_changed_and_leave_what_all_of_it_would(U, n,
     (8, 32768, 512, 1, "odd", 1, 4, 1),
 ])
 def test_later_rounds_that_score_what_moved_leave_what_all_centroids_would(U, n, C, tk, odd, slices, run, fused):
-    """The same where later rounds score only the centroids that moved and then the keys that lost theirs: from the third
-    round on, over one slice of 512 centroids and several, with the sort inside and after it, from rounds in which most
+    """The same, after three rounds to nine and after twelve, where later rounds score only the centroids that moved and then the
+    keys that lost theirs: from the third round on, over one slice of 512 centroids and several, with the sort inside and after it, from rounds in which most
     centroids moved (those are done in full) to rounds in which few did and none."""
     import torch
     from paper_2604_10539_amd import ice_debug_build_plan, make_config
@@ -562,7 +562,7 @@ def test_later_rounds_that_score_what_moved_leave_what_all_centroids_would(U, n,
             K[0, ::2, t, i % D:] = [0x7FC0, 0x7F80, 0xFF80 - 65536, 0xFFC0 - 65536, 0x5F80, 0xDF80 - 65536][i % 6]
     V = torch.randint(-16000, 16000, K.shape, generator=gen, device="cuda", dtype=torch.int16)
     init = torch.stack([torch.sort(torch.randperm(n, generator=gen, device="cuda")[:C])[0] for _ in range(U)]).int()[None].contiguous()
-    for T in (3, 4, 5, 6, 8, 12):
+    for T in (3, 4, 5, 6, 7, 8, 9, 12):
         _every_stage_again(K, V, init, C, tk, T)
 
 
@@ -591,10 +591,16 @@ def test_later_rounds_that_score_what_moved_leave_what_all_centroids_would(U, n,
     (600, 4000, 450, 0, "half", 1, 0),     # many units, which turn one by one
     (600, 4000, 450, 1, "odd", 1, 0),
     (600, 4000, 450, 0, "late", 1, 0),
+    (1, 200000, 2500, 1, "mix", 49, 0),    # transformed keys where one tile of rows fits and a list is two words to a lane
+    (8, 65536, 1024, 0, "offset 5", 32, 0),    # a common offset: distances out of cancelled squares, the margin of many times what
+    (8, 65536, 1024, 1, "offset 5", 32, 0),    # they are without it
+    (8, 65536, 1024, 0, "offset 8", 32, 0),    # ... where it leaves part of the keys open
+    (8, 65536, 1024, 0, "offset 20", 32, 0),   # ... nearly all of them
+    (8, 65536, 1024, 1, "offset 100", 32, 0),
 ])
 def test_later_rounds_by_the_centroids_near_a_keys_own_leave_what_all_would(U, n, C, tk, data, ranges, fused):
     """The same where every later round takes the keys of a cluster to the centroids near its own and only the keys that this
-    leaves open to more of them, from the second round on until hardly any centroid moves."""
+    leaves open to more of them, from the second round on until hardly any centroid moves; every round is looked at."""
     import torch
     from paper_2604_10539_amd import ice_debug_build_plan, make_config
     p = ice_debug_build_plan(make_config(1, U, 4, n), n, C)
@@ -617,6 +623,8 @@ def test_later_rounds_by_the_centroids_near_a_keys_own_leave_what_all_would(U, n
         if data == "lump":
             x[n // 2: n // 2 + n // 3] = 0.01 * x[n // 2: n // 2 + n // 3]
             x[100:400] = x[100:101]
+        if data.startswith("offset"):  # (so many times the components' spread)
+            x = x + float(data.split()[1]) * torch.randn(D, generator=gen, device="cuda")
         if data == "tiny":
             x = torch.ldexp(x, torch.tensor(-50 if u == 0 else -60 - 2 * u, device="cuda"))
         K[0, u] = x.to(torch.bfloat16).view(torch.int16)
@@ -632,7 +640,7 @@ def test_later_rounds_by_the_centroids_near_a_keys_own_leave_what_all_would(U, n
     if data == "lump":
         init[:, 10:50] = torch.arange(100, 140, device="cuda")  # (centroids on equal keys)
     init = init.int()[None].contiguous()
-    for T in (2, 3, 4, 6, 9):
+    for T in range(2, 10):
         _every_stage_again(K, V, init, C, tk, T)
 
 
@@ -738,8 +746,8 @@ def test_insertions_scored_a_round_ahead_equal_single_ones(m, C, s, tk):
 @pytest.mark.parametrize("G", [4, 8])
 @pytest.mark.parametrize("C", [140, 520, 1100])
 def test_staged_selection_at_the_edges_of_its_threshold_groups(C, G):
-    """The kept clusters and pages at counts where the threshold changes its groups (half the 32, 64, 128 or 256 of them) or goes by
-    histograms, and where the list behind it is ranked in another form: they are the best of 64-bit scores."""
+    """The kept clusters and pages at counts where the threshold changes its groups (half the 32, 64 or 128 of them) or goes by
+    histograms (above 64), and where the list behind it is ranked in another form: they are the best of 64-bit scores."""
     import torch
     from paper_2604_10539_amd import IceIndex
     n, U, s = 8 * C, 2, 16
@@ -771,3 +779,31 @@ def test_staged_selection_at_the_edges_of_its_threshold_groups(C, G):
             ps = (rep[u] @ qf[u].T).max(1)
             kth = np.sort(ps[cand])[::-1][P - 1]
             assert np.all(ps[ids[u, :P]] >= kth - ahead * max(1.0, abs(kth))), (k, u)
+
+
+@pytest.mark.parametrize("G", [4, 8])
+def test_staged_selection_among_more_equal_scores_than_its_list_holds(G):
+    """700 clusters with the same centroid and 700 pages with the same representative: more of them pass the threshold than are ranked
+    by counting, and the lowest ids are kept."""
+    import torch
+    from paper_2604_10539_amd import IceIndex
+    same, C, s, U = 700, 1100, 16, 2
+    n = s * same + 8 * (C - same)
+    rng = np.random.default_rng(5)
+    K = rng.standard_normal((1, U, n, D))
+    K[:, :, :s * same] = 3.0 * rng.standard_normal((1, U, 1, D))
+    K = narrow(K.astype(np.float32))
+    init = np.concatenate([s * np.arange(same), s * same + 8 * np.arange(C - same)]).astype(np.int32)  # (the first keeps all equal keys)
+    ix = IceIndex(1, U, G, n, s, C, kmeans_iters=2, init_idx=up(np.ascontiguousarray(np.broadcast_to(init, (1, U, C)))))
+    ix.build_index(up(K), up(K))
+    ex = ix.export()
+    torch.cuda.synchronize()
+    cen, pc = down(ex["centroid"])[:, :same], down(ex["page_cluster"])
+    assert np.all(cen == cen[:, :1]) and np.all(pc[:, :same] == 0)
+    q = np.ascontiguousarray(np.repeat(K[:, :, :1], G, axis=2)).reshape(1, U * G, D)
+    for k in (15, 17, 33, 64, 65, 200):
+        for P in (15, 17, 33, 64, 65, 200):
+            ids, n_sel, _, cl, _ = ix.select_hier(up(q), P * s, k, attend=False)
+            assert np.all(down(n_sel) == P), (k, P)
+            assert np.array_equal(down(cl)[0], np.tile(np.arange(k), (U, 1))), (k, P)
+            assert np.array_equal(down(ids)[0], np.tile(np.arange(P), (U, 1))), (k, P)
