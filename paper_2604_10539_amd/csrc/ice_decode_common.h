@@ -73,8 +73,10 @@ __device__ inline void place_by_id(const u64 *win, int n, int part, int parts, i
 // workgroup (a barrier in front and behind is the caller's).  Bound by vector instructions (four waves to a SIMD) and the trips to
 // LDS.  rank_blocks: every wave holds all of them on its lanes and counts, for each of its share, those above it with a lane
 // mask.  rank_lanes: up to 64 lanes to a composite walk a part of the list each; it is the flat step's with eight waves, two such
-// workgroups to a CU.  (16 waves: 84 of 512 0.8 and 2.3 us, the step of 8 units x 2300 pages, about 25 listed, 11.89 and 12.07; eight
-// waves, 312 units x 460 pages, as many listed, 35.3 and 34.9.)
+// workgroups to a CU.  (16 waves: 84 of 512 0.8 and 2.3 us, the step of 8 units x 2300 pages, about 25 listed, 11.89 and 12.07.  Eight
+// waves, of which a wave's share is twice as long: 312 units x 460 pages 35.3 and 34.9, 368 pages of 32 tokens 28.9 and 28.6; where there is one
+// such workgroup to a CU no difference but with long lists: 8 units x 2300 pages, 16 kept, 12.6 and 12.6, 64 kept 19.3 and 19.0, 32 x 2300,
+// 32 kept, 19.2 and 19.1, 128 x 1150 23.6 and 23.6, 256 x 2300 33.5 and 33.4, 2 x 300 10.6 and 10.6.)
 constexpr int kRankMax = 512;
 template <int NW>
 __device__ inline void rank_lanes(const u64 *cand, int n, int need, int tid, u64 *sel) {

@@ -73,6 +73,14 @@ def test_a_later_rounds_assignment_keeps_its_operands_in_registers(kernels):
             assert not loads or waits[-1] > loads[-1], (name, i)
 
 
+def test_the_rounds_of_large_builds_keep_their_operands_in_registers(kernels):
+    """... and their three launches, by the near centroids: whose addresses are worked out again and again for it."""
+    rounds = {k: v for k, v in kernels.items() if "13marked_kernelI" in k or "11near_kernelI" in k or "17near_lists_kernelI" in k}
+    assert len(rounds) == 4 + 6 + 2  # (transformed or not; slices that are full or not; a cluster in one piece, in a few, in many)
+    for name, code in rounds.items():
+        assert not any(x.startswith("scratch_") for x in code), name
+
+
 def test_an_import_copies_through_registers(kernels):
     code = next(v for k, v in kernels.items() if "import_kernel" in k)
     assert not any(x.startswith("scratch_") for x in code)
