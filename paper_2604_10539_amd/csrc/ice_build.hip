@@ -2141,15 +2141,16 @@ __global__ __launch_bounds__(512) void marked_kernel(const bf16_t *__restrict__ 
     const int nbits = 32 - __builtin_clz((unsigned)Cpad - 1u);
     int *head = (int *)near_scratch(d, u);
 
-    int goes = go[2 * u], turned = *near_turned(d, u, joint);  // (nothing in this launch changes it)
-    asm volatile("" : "+v"(goes), "+v"(turned));  // (one trip for both)
-    if (turned != 0) {
+    int goes_in = go[2 * u], turned_in = *near_turned(d, u, joint);  // (nothing in this launch changes it)
+    asm volatile("" : "+v"(goes_in), "+v"(turned_in));               // (one trip for both)
+    const int goes = __builtin_amdgcn_readfirstlane(goes_in), turned = __builtin_amdgcn_readfirstlane(turned_in);
+    if (turned != 0 || which >= slices) {  // (one branch: as two the transformed forms kept addresses in scratch memory)
+        if (turned == 0) return;
         reassign_unit<AUG, ALL_FULL>(K, cent, cnorm, n, Cpad, cur, go, round, fused, turned == round, plan, d, smem);
         return;
     }
     if (fused && blockIdx.x == 0 && tid == 0) d.any_moved[2 * u + (round & 1)] = 0;  // (for this round's means)
     if (goes == 0) return;  // (no centroid moved: every winner stands)
-    if (which >= slices) return;
     if (blockIdx.x == 0 && tid == 0) head[0] = 0;  // (for the next round's near_lists)
     // ---- which centroids moved, and the run's marked keys: whose own centroid moved from the front of the key list on,
     // the others from its end

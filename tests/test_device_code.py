@@ -74,7 +74,7 @@ def test_a_later_rounds_assignment_keeps_its_operands_in_registers(kernels):
 
 
 def test_the_rounds_of_large_builds_keep_their_operands_in_registers(kernels):
-    """... and their three launches, by the near centroids: whose addresses are worked out again and again for it."""
+    """... and their three launches, by the near centroids: nothing goes through scratch memory."""
     rounds = {k: v for k, v in kernels.items() if "13marked_kernelI" in k or "11near_kernelI" in k or "17near_lists_kernelI" in k}
     assert len(rounds) == 4 + 6 + 2  # (transformed or not; slices that are full or not; a cluster in one piece, in a few, in many)
     for name, code in rounds.items():
