@@ -5,8 +5,9 @@
 
 The stamps are compiled in only with -DICE_PROF (csrc/ice_prof.h); this module builds that variant
 into _build/prof/ beside the product library, which it never touches, loads it instead of the
-product library, runs config 2 (one layer = 8 units, and 32 layers = 256 units) with a cold index,
-and prints the phases of the workgroup that finishes a unit.  Times are microseconds after the
+product library, runs config 2 (one layer = 8 units, and 32 layers = 256 units; the staged selection on
+16 layers = 128 units) and the selection of config 3, with a cold index (these two also without), and
+prints the phases of the workgroup that finishes a unit.  Times are microseconds after the
 wave's first stamp; a stamp is taken by thread 0 of unit 0's workgroup (decode: of the workgroup
 that is last to deliver its scores), so they are one workgroup's view, not a chip-wide average; the
 per-unit table gives the spread over all units."""
@@ -26,6 +27,11 @@ PROF_LIB = os.path.join(PROF_DIR, "libicecache_prof.so")
 DECODE = [(0, "wave started"), (14, "own chunk scored"), (2, "last workgroup holds every score of the unit"),
           (3, "threshold known"), (4, "candidates listed"), (5, "pages ranked"), (6, "attention: tiles requested"),
           (7, "output written")]
+# (where the attention is a launch of its own)
+SELECT = DECODE[:6]
+# decode_hier_kernel
+HIER = [(0, "wave started"), (1, "centroids scored"), (2, "clusters selected"), (3, "clusters as a mask"), (4, "their pages listed"),
+        (5, "pages scored"), (6, "pages selected"), (7, "output written")]
 INSERT_ONE = [(40, "wave started"), (41, "first barrier (LDS only)"), (45, "tiles in LDS"), (46, "dot products done"),
               (47, "wave's best row known"), (42, "state of that row requested"), (43, "waves have met"),
               (49, "cluster moved"), (44, "row appended")]
@@ -39,9 +45,9 @@ def build() -> str:
     return build_library(extra_flags=("-DICE_PROF",), lib_path=PROF_LIB, obj_dir=os.path.join(PROF_DIR, "obj"))
 
 
-def _stamps(lib, n=64):
+def _stamps(lib, n=64, kernels="decode"):
     buf = (ctypes.c_longlong * n)()
-    assert lib.ice_debug_prof_decode(buf, n) == 0
+    assert getattr(lib, "ice_debug_prof_" + kernels)(buf, n) == 0
     return list(buf)
 
 
@@ -74,7 +80,7 @@ def run() -> None:
         flush.sum()
         torch.cuda.synchronize()
 
-    for layers in (1, 32):
+    for layers in (1, 16, 32):
         gen = [(datagen.keys_values(w, seed=w.seed + l), datagen.init_indices(w, seed=w.seed + l)[0],
                 datagen.queries(w, seed=w.seed + l)[0], datagen.DecodeStream(w, seed=w.seed + l).take(34)) for l in range(layers)]
         K = up(np.stack([g[0][0][0] for g in gen]))
@@ -86,6 +92,16 @@ def run() -> None:
         ix.build_index(K, V)
         U = layers * w.n_kv_heads
         print("\n## config 2, %d layer%s in one launch (%d units)" % (layers, "" if layers == 1 else "s", U))
+        if layers == 16:
+            def staged():
+                ix.select_hier(q, w.token_budget, 64)
+                torch.cuda.synchronize()
+                return _stamps(lib, kernels="hier")
+            staged()
+            _table("staged step (ice_select_hier, 64 of %d clusters), repeated: workgroup 0" % w.n_clusters, HIER, [staged() for _ in range(3)])
+            _table("the same, cold index", HIER, [(cold(), staged())[1] for _ in range(3)])
+            del ix, K, V
+            continue
         runs, per_unit = [], None
         ix.select_attend(q, w.token_budget)
         for _ in range(3):
@@ -118,6 +134,21 @@ def run() -> None:
             runs.append(_stamps(lib))
         _table("16 tokens (ice_insert_batch), cold index: unit 0", INSERT_BATCH, runs)
         del ix, K, V
+
+    w = datagen.WORKLOADS["cfg3"]
+    K, V = (up(x) for x in datagen.keys_values(w))
+    ix = IceIndex(1, w.n_kv_heads, w.group_size, w.n_tokens, w.page_size, w.n_clusters, kmeans_iters=4, init_idx=up(datagen.init_indices(w)), device=dev)
+    ix.build_index(K, V)
+    q = up(datagen.queries(w))
+    print("\n## config 3 (%d units)" % w.n_kv_heads)
+
+    def select():
+        ix.select_attend(q, w.token_budget)
+        torch.cuda.synchronize()
+        return _stamps(lib)
+    select()
+    _table("selection of a decode step (ice_select_attend; its attention is the next launch), repeated: unit 0", SELECT, [select() for _ in range(3)])
+    _table("the same, cold index", SELECT, [(cold(), select())[1] for _ in range(3)])
 
 
 if __name__ == "__main__":
