@@ -1,12 +1,13 @@
 """The bounds behind a large build's later rounds, on the host: where they say that a key need not be scored against a centroid,
 that centroid loses to the best one known in fp32, in whatever order the products are added, and the bound on a distance lies
 below it.  The keys sit where the rounding of the scores decides: just short of half way to the centroid that is left out, far
-from the origin (the distances come out of cancelled squares) and so close to it that products and sums are subnormal."""
+from the origin (the distances come out of cancelled squares) and so close to it that products and sums are subnormal.  And which builds
+go that way."""
 import numpy as np
 import pytest
 
 from datagen import bf16_bits_to_f32 as widen, f32_to_bf16_bits as narrow
-from paper_2604_10539_amd import ice_debug_near_bounds
+from paper_2604_10539_amd import ice_debug_build_plan, ice_debug_near_bounds, make_config
 
 D = 128
 TINY = np.float32(2.0 ** -126)
@@ -93,3 +94,14 @@ def test_bounds_leave_open_what_is_not_a_number_and_settle_zero_keys():
     need, _ = ice_debug_near_bounds([0], [0], [0], [0])
     _, dist2 = ice_debug_near_bounds([0], [0], [0], [-0.5])  # (the nearest other centroid, of norm 1)
     assert 0 < need[0] < 2.0 ** -40 and 0.99 < dist2[0] <= 1
+
+
+@pytest.mark.parametrize("U,n,C,near", [
+    (256, 9600, 300, True), (256, 9599, 300, False),        # 32 keys per cluster
+    (64, 32768, 2048, True), (64, 32767, 2048, False),      # 16 where a unit has 32768 keys
+    (64, 40000, 2500, True), (64, 40000, 2501, False),
+    (600, 4000, 450, False), (300, 6100, 300, False), (32, 16384, 2048, False),
+])
+def test_builds_of_few_keys_per_cluster_make_no_lists_of_near_centroids(U, n, C, near):
+    """They took 1.02 to 1.37 times as long with them (600 units x 4000 keys x 450 clusters: 3630 and 4970 us)."""
+    assert ice_debug_build_plan(make_config(1, U, 4, n), n, C)["reassign_from"] == (1 if near else 2)
