@@ -315,7 +315,7 @@ ice_status_t ice_debug_rerun_stage(ice_index_t *idx, const void *K, const void *
 
 /* Test hook: which way a build of n_tokens keys and n_clusters clusters per unit goes, worked out on the host alone
  * (nothing is enqueued, no index is needed).  plan[0] = 1 where the assignment sorts its own runs; plan[1], plan[2] =
- * tokens per range of the sort and ranges per unit; plan[3] = first round that scores only what changed (0: none does;
+ * tokens per range of the sort and ranges per unit; plan[3] = first of cfg's rounds that scores only what changed (0: none does;
  * 1: every round after the first takes the keys of a cluster to the centroids near its own; 2: from the third round on all keys
  * to the centroids that moved);
  * plan[4] = 256-key tiles per workgroup of such a round; plan[5] = slices of 512 centroids.  cfg, n_tokens and n_clusters

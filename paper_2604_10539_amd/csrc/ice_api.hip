@@ -247,7 +247,7 @@ ice_status_t ice_build_index(ice_index_t *ix, const void *K, const void *V, int3
     if (d.tk) launch_key_aug(d, Kb, n, s);
     launch_init_centroids(d, Kb, n, ix->cfg.init_idx, ix->cfg.seed, cur, s);
     const bool fused = sort_is_fused(d, n);
-    const bool near = ix->cfg.kmeans_iters > 1 && near_pays(d, n), later = near || (ix->cfg.kmeans_iters > 2 && reassign_pays(d, n));
+    const bool near = near_pays(d, n, ix->cfg.kmeans_iters), later = near || (ix->cfg.kmeans_iters > 2 && reassign_pays(d, n));
     for (int t = 0; t < ix->cfg.kmeans_iters; ++t) {
         if (near && t >= 1 && t % kRoundNumbers != 0) launch_near(d, Kb, n, cur, t, fused, s);
         else if (later && t >= 2 && t % kRoundNumbers != 0) launch_reassign(d, Kb, n, cur, t, fused, s);
@@ -613,7 +613,7 @@ ice_status_t ice_debug_build_plan(const ice_config_t *cfg, int32_t n, int32_t n_
     d.U = cfg->batch * cfg->n_kv_heads;
     d.C = n_clusters;
     d.Cpad = round_up(n_clusters, 32);
-    build_plan(d, n, plan);
+    build_plan(d, n, cfg->kmeans_iters, plan);
     return ICE_OK;
 }
 

@@ -2281,8 +2281,13 @@ __global__ __launch_bounds__(512) void marked_kernel(const bf16_t *__restrict__ 
 // 300 x 6100 x 300 (20) 1920 and 2340, 32 x 16384 x 2048 (8) 1325 and 1605, 600 x 4000 x 450 (9) 3630 and 4970 (64 x 24576 x 1024 (24) 2220 and 2160).
 // Of the 2300 us of 8 x 131072 x 2048: first round 440, then near_lists 32 and eight times 19, near 80 to 18, marked 130 to 32,
 // sort 16, means 55 to 14 each, page copy 190.
+// With up to 512 clusters the first of these rounds (the first lists, nearly all keys looked at) takes longer than a full one, and the later ones
+// have to make up for it: from four rounds on, up to 384 clusters six.  Two, three, four and six rounds: 256 x 32768 x 512 4240 and 4420, 5530 and 5515, 6710
+// and 6315, 8320 and 7370; 256 x 24576 x 384 2815 and 3060, 3610 and 3820, 4320 and 4370, 5490 and 5130; 512 x 16384 x 260 3620 and 3980, 4625 and 4980, 5525
+// and 5715, 6980 and 6740.  Above 512 two rounds do: 128 x 20480 x 640 1870 and 1815, 48 x 32768 x 1536 1712 and 1718, 8 x 131072 x 2048 1269 and 1044.
 constexpr int kNearMinSteps = 16;
-bool near_pays(const Dev &d, int n) {
+bool near_pays(const Dev &d, int n, int rounds) {
+    if (rounds < (d.Cpad <= 384 ? 6 : d.Cpad <= 512 ? 4 : 2)) return false;
     if (d.Cpad > kNearMaxClusters || n > kMaxNearTokens || !reassign_pays(d, n)) return false;
     if (n < 32ll * d.C && (n < 32768 || n < 16ll * d.C)) return false;
     const RoundPlan p = round_plan(d, n);
@@ -2338,11 +2343,11 @@ void near_bounds(int n, const float *k2, const float *a2, const float *sa, const
     }
 }
 
-void build_plan(const Dev &d, int n, int *plan) {
+void build_plan(const Dev &d, int n, int rounds, int *plan) {
     plan[0] = sort_is_fused(d, n) ? 1 : 0;
     plan[1] = sort_len(d, n);
     plan[2] = (n + plan[1] - 1) / plan[1];
-    plan[3] = near_pays(d, n) ? 1 : reassign_pays(d, n) ? 2 : 0;
+    plan[3] = near_pays(d, n, rounds) ? 1 : rounds > 2 && reassign_pays(d, n) ? 2 : 0;
     plan[4] = assign_run(d.U, n, 1);
     plan[5] = assign_slices(d);
 }

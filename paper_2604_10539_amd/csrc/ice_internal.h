@@ -113,9 +113,9 @@ bool sort_is_fused(const Dev &d, int n);
 bool reassign_pays(const Dev &d, int n);     // for rounds t >= 2 but the multiples of kRoundNumbers
 constexpr int kRoundNumbers = 1 << 19;       // rounds that the winners' words tell apart (launch_assign starts them anew)
 void launch_reassign(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fused, hipStream_t st);
-bool near_pays(const Dev &d, int n);         // for rounds t >= 1 but those
+bool near_pays(const Dev &d, int n, int rounds);  // for rounds t >= 1 but those, of so many in all
 void launch_near(const Dev &d, const bf16_t *K, int n, int cur, int t, bool fused, hipStream_t st);
-void build_plan(const Dev &d, int n, int *plan);  // ice_debug_build_plan
+void build_plan(const Dev &d, int n, int rounds, int *plan);  // ice_debug_build_plan
 void near_bounds(int n, const float *k2, const float *a2, const float *sa, const float *sb, float *need, float *dist2);  // ice_debug_near_bounds
 void launch_sort(const Dev &d, int n, int t, float *best_out_or_null, int *assign_out_or_null, hipStream_t st);
 size_t sort_ranges_max(int U, int max_tokens, int Cpad);  // (unit, range) pairs of any sort of at most max_tokens tokens

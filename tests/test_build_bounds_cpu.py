@@ -105,3 +105,10 @@ def test_bounds_leave_open_what_is_not_a_number_and_settle_zero_keys():
 def test_builds_of_few_keys_per_cluster_make_no_lists_of_near_centroids(U, n, C, near):
     """They took 1.02 to 1.37 times as long with them (600 units x 4000 keys x 450 clusters: 3630 and 4970 us)."""
     assert ice_debug_build_plan(make_config(1, U, 4, n), n, C)["reassign_from"] == (1 if near else 2)
+
+
+@pytest.mark.parametrize("U,n,C,rounds", [(512, 16384, 260, 6), (256, 24576, 384, 6), (256, 24576, 385, 4), (256, 32768, 512, 4), (256, 32768, 513, 2), (8, 131072, 2048, 2)])
+def test_builds_of_few_rounds_and_clusters_make_no_lists_of_near_centroids(U, n, C, rounds):
+    """The first round with them costs more than a full one there (512 units x 16384 keys x 260 clusters, three rounds: 4625 and 4980 us)."""
+    first = lambda T: ice_debug_build_plan(make_config(1, U, 4, n, kmeans_iters=T), n, C)["reassign_from"]
+    assert [first(T) for T in (1, 2, 3, 4, 5, 6, 10)] == [1 if T >= rounds else 2 if T > 2 else 0 for T in (1, 2, 3, 4, 5, 6, 10)]

@@ -600,10 +600,13 @@ def test_later_rounds_that_score_what_moved_leave_what_all_centroids_would(U, n,
 ])
 def test_later_rounds_by_the_centroids_near_a_keys_own_leave_what_all_would(U, n, C, tk, data, ranges, fused):
     """The same where every later round takes the keys of a cluster to the centroids near its own and only the keys that this
-    leaves open to more of them, from the second round on until hardly any centroid moves; every round is looked at."""
+    leaves open to more of them, from the second round on until hardly any centroid moves; every round is looked at.  Builds of
+    so few rounds that they go another way stand for none of them: the shortest build that goes this way leaves then what its units
+    leave by themselves."""
     import torch
     from paper_2604_10539_amd import ice_debug_build_plan, make_config
-    p = ice_debug_build_plan(make_config(1, U, 4, n), n, C)
+    plan_of = lambda U, T: ice_debug_build_plan(make_config(1, U, 4, n, kmeans_iters=T), n, C)
+    p = plan_of(U, 10)
     assert (p["reassign_from"], p["ranges"], p["fused"]) == (1, ranges, fused)
     gen = torch.Generator(device="cuda").manual_seed(U * n + C)
     K = torch.empty(1, U, n, D, dtype=torch.int16, device="cuda")
@@ -640,8 +643,15 @@ def test_later_rounds_by_the_centroids_near_a_keys_own_leave_what_all_would(U, n
     if data == "lump":
         init[:, 10:50] = torch.arange(100, 140, device="cuda")  # (centroids on equal keys)
     init = init.int()[None].contiguous()
+    shortest = next(T for T in range(2, 10) if plan_of(U, T)["reassign_from"] == 1)
     for T in range(2, 10):
-        _every_stage_again(K, V, init, C, tk, T)
+        had = _every_stage_again(K, V, init, C, tk, T)
+        if T == shortest > 2:
+            for u in {0, 1, U // 2, U - 1}:
+                assert plan_of(1, T)["reassign_from"] != 1
+                alone = _every_stage_again(K[:, u:u + 1], V[:, u:u + 1], init[:, u:u + 1], C, tk, T)
+                for f in ("assign", "cluster_cnt", "cluster_sum", "centroid", "n_pages"):
+                    assert torch.equal(had[f][u], alone[f][0]), (T, f, u)
 
 
 def test_later_rounds_where_scores_stop_comparing():
