@@ -2274,11 +2274,12 @@ __global__ __launch_bounds__(512) void marked_kernel(const bf16_t *__restrict__ 
 // 5220, 64 x 32768 x 512 3820 and 3920, 8 x 65536 x 1024 1557 and 1644; components of spread 0.6: 3048 and 3154, 2730 and 2825, 1053 and 1145,
 // 2 x 131072 x 2048 996 and 1086, 16 x 32768 x 768 897 and 983.  (The line leaves out the gains of 3 to 6 % right below it: such keys
 // lose more there, 8 x 49152 x 768 without structure 1176 and 1248.)
-// And from 32 keys per cluster on (16 where a unit has 32768 keys): the lists of near centroids are worked out per cluster, by all
-// centroids.  From there on 256 units x 9600 x 300 (32 keys) 2440 and 2400, 256 x 16384 x 512 (32) 4600 and 4200, 64 x 32768 x 1024 (32) 3070 and
-// 2630, 64 x 32768 x 2048 (16) 4230 and 3990, 16 x 65536 x 4096 (16) 3330 and 3000, 48 x 32768 x 1536 (21) 3320 and 2980; below 64 x 20480 x 1024 (20) 1880 and 1910,
-// 256 x 12288 x 512 (24) 3410 and 3440, 32 x 24576 x 1536 (16) 1510 and 1550, 64 x 16384 x 1024 (16) 1535 and 1690, 256 x 8192 x 512 (16) 2380 and 2700,
-// 300 x 6100 x 300 (20) 1920 and 2340, 32 x 16384 x 2048 (8) 1325 and 1605, 600 x 4000 x 450 (9) 3630 and 4970 (64 x 24576 x 1024 (24) 2220 and 2160).
+// And from 16384 keys and 32 keys per cluster on (20 from 32768 keys on): the lists of near centroids are worked out per cluster, by all
+// centroids.  From there on 256 units x 16384 x 512 (32 keys) 4600 and 4200, 64 x 32768 x 1024 (32) 3070 and 2630, 48 x 32768 x 1536 (21) 3320 and
+// 2980; below 64 x 20480 x 1024 (20) 1880 and 1910, 256 x 12288 x 512 (24) 3410 and 3440, 64 x 16384 x 1024 (16) 1535 and 1690, 256 x 8192 x 512 (16)
+// 2380 and 2700, 300 x 6100 x 300 (20) 1920 and 2340, 32 x 16384 x 2048 (8) 1325 and 1605, 600 x 4000 x 450 (9) 3630 and 4970.  (The line leaves
+// out gains that components of spread 0.45 and 0.6 turn into losses, 64 x 32768 x 2048 (16) 4960 and 4830, 4400 and 4560, 4820 and 5140, 256 x 9600 x 300
+// (32) 2440 and 2400, 2610 and 2675, 2640 and 2800; and 16 x 65536 x 4096 (16) 3330 and 3000.)
 // Of the 2300 us of 8 x 131072 x 2048: first round 440, then near_lists 32 and eight times 19, near 80 to 18, marked 130 to 32,
 // sort 16, means 55 to 14 each, page copy 190.
 // With up to 512 clusters the first of these rounds (the first lists, nearly all keys looked at) takes longer than a full one, and the later ones
@@ -2289,7 +2290,7 @@ constexpr int kNearMinSteps = 16;
 bool near_pays(const Dev &d, int n, int rounds) {
     if (rounds < (d.Cpad <= 384 ? 6 : d.Cpad <= 512 ? 4 : 2)) return false;
     if (d.Cpad > kNearMaxClusters || n > kMaxNearTokens || !reassign_pays(d, n)) return false;
-    if (n < 32ll * d.C && (n < 32768 || n < 16ll * d.C)) return false;
+    if (n < 16384 || n < (n < 32768 ? 32ll : 20ll) * d.C) return false;
     const RoundPlan p = round_plan(d, n);
     return p.all_turns * p.all_run * p.tiles >= 16 * kNearMinSteps;
 }

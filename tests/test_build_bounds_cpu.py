@@ -97,9 +97,8 @@ def test_bounds_leave_open_what_is_not_a_number_and_settle_zero_keys():
 
 
 @pytest.mark.parametrize("U,n,C,near", [
-    (256, 9600, 300, True), (256, 9599, 300, False),        # 32 keys per cluster
-    (64, 32768, 2048, True), (64, 32767, 2048, False),      # 16 where a unit has 32768 keys
-    (64, 40000, 2500, True), (64, 40000, 2501, False),
+    (256, 16384, 512, True), (256, 16384, 513, False), (256, 16383, 300, False),  # 16384 keys, 32 per cluster
+    (64, 32768, 1638, True), (64, 32768, 1639, False), (64, 32767, 1638, False),  # 20 from 32768 keys on
     (600, 4000, 450, False), (300, 6100, 300, False), (32, 16384, 2048, False),
 ])
 def test_builds_of_few_keys_per_cluster_make_no_lists_of_near_centroids(U, n, C, near):

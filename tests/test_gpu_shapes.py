@@ -568,7 +568,7 @@ def test_later_rounds_that_score_what_moved_leave_what_all_centroids_would(U, n,
 
 @pytest.mark.parametrize("U,n,C,tk,data,ranges,fused", [
     (256, 19300, 600, 0, "mix", 1, 0),     # a cluster is one piece; two slices, the second hardly begun; a ragged last tile
-    (300, 9700, 300, 1, "mix", 1, 0),      # more units than workgroups of a round, transformed keys
+    (300, 16500, 300, 1, "mix", 1, 0),     # more units than workgroups of a round, transformed keys
     (32, 32768, 512, 0, "out", 8, 1),      # eight pieces, one full slice with the sort inside
     (33, 28000, 417, 1, "mix", 7, 1),      # ... transformed, a slice that is not full, a last block of few centroids
     (6, 65000, 1100, 0, "out", 32, 0),     # more pieces than a member is picked from directly
@@ -588,9 +588,9 @@ def test_later_rounds_that_score_what_moved_leave_what_all_centroids_would(U, n,
     (32, 32768, 512, 0, "late", 8, 1),
     (4, 131072, 1100, 1, "late", 64, 0),
     (1, 262144, 2112, 0, "late", 64, 0),
-    (520, 14500, 450, 0, "half", 1, 0),    # many units, which turn one by one
-    (520, 14500, 450, 1, "odd", 1, 0),
-    (520, 14500, 450, 0, "late", 1, 0),
+    (520, 16500, 450, 0, "half", 1, 0),    # many units, which turn one by one
+    (520, 16500, 450, 1, "odd", 1, 0),
+    (520, 16500, 450, 0, "late", 1, 0),
     (1, 200000, 2500, 1, "mix", 49, 0),    # transformed keys where one tile of rows fits and a list is two words to a lane
     (8, 65536, 1024, 0, "offset 5", 32, 0),    # a common offset: distances out of cancelled squares, the margin of many times what
     (8, 65536, 1024, 1, "offset 5", 32, 0),    # they are without it
